@@ -23,6 +23,7 @@ struct dnb_block {
   std::vector<size_t> off_stat_b;            // per layer mean[B], istd[B]
   std::vector<size_t> off_fold1, off_fold2;  // fused schedule: per layer folded (scale, shift) of BN1 / BN2
   size_t off_part;                           // reduction partials of the main chain (BN)
+  size_t off_K, part1_floats;                // bf16 backward: K0, K1 per channel; where BN2's partials start in off_part
   size_t partA_floats, partB_floats;         // size of one weight-gradient partial buffer
   size_t off_partA, off_partB;               // partials of the 3x3 / 1x1 weight gradients
   // with concurrency on, backward runs three chains: the data-gradient chain on the caller's
@@ -33,7 +34,6 @@ struct dnb_block {
   hipStream_t sA, sB;
   std::vector<hipEvent_t> ev;                // per layer: main done, db ready, S1/S2 ready, wgrad1 done
   hipEvent_t ev_start, ev_endA, ev_endB;
-  std::vector<hipEvent_t> evc;  // bf16: two more events per layer (BN1 reduction done, slab share done)
   size_t off_pack;                           // packed weights of all layers
   std::vector<size_t> pk;                    // per layer: float offset of its packed weights
   std::vector<size_t> poff;                  // parameter offsets (elements) per layer
@@ -193,13 +193,11 @@ int forward_bf16(dnb_block* b, const void* x0, const float* params, void* yv, ch
 
 // The helper streams and the events of the concurrent backward pass, created on first use
 // (default priority; four events per layer: main chain done, db_l ready, storage 1/2 ready,
-// 1x1 weight gradient done; the bf16 path has two more events per layer and uses one helper stream).
+// 1x1 weight gradient done).
 // Destroys whatever of the helper streams and events exists (handles are null until created).
 void release_helper_streams(dnb_block* b) {
   for (hipEvent_t e : b->ev) if (e) (void)hipEventDestroy(e);
-  for (hipEvent_t e : b->evc) if (e) (void)hipEventDestroy(e);
   b->ev.clear();
-  b->evc.clear();
   for (hipEvent_t* e : {&b->ev_start, &b->ev_endA, &b->ev_endB}) {
     if (*e) (void)hipEventDestroy(*e);
     *e = nullptr;
@@ -216,9 +214,7 @@ int ensure_helper_streams(dnb_block* b) {
   bool ok = hipStreamCreateWithFlags(&b->sA, hipStreamNonBlocking) == hipSuccess &&
             hipStreamCreateWithFlags(&b->sB, hipStreamNonBlocking) == hipSuccess;
   b->ev.assign((size_t)4 * (b->d.layers + 2), nullptr);
-  b->evc.assign((size_t)2 * (b->d.layers + 2), nullptr);
   for (auto& e : b->ev) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
-  for (auto& e : b->evc) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
   for (hipEvent_t* e : {&b->ev_start, &b->ev_endA, &b->ev_endB})
     ok = ok && hipEventCreateWithFlags(e, hipEventDisableTiming) == hipSuccess;
   if (!ok) {  // nothing half-made is kept: the next call starts over
@@ -229,152 +225,66 @@ int ensure_helper_streams(dnb_block* b) {
   return DNB_OK;
 }
 
-int backward_bf16(dnb_block* b, const float* params, const void* yv, const void* dy, void* dx0, float* dparams,
+// Program order on the caller's stream.  Shared schedule (Section 4): before a layer's
+// back-propagation its storage 3, then storage 1 and 2, are re-populated from the kept conv outputs
+// and the cached folded statistics; store-everything keeps them per layer; in the fused schedule the
+// weight gradients apply BN+ReLU in their operand staging and the chain reads y in place.
+int backward_bf16(dnb_block* b, const void* yv, const void* dy, void* dx0, float* dparams,
                   char* ws, hipStream_t st) {
   const dnb_block_desc& d = b->d;
   const int n = d.n, m = d.layers, k = d.growth, B = d.bottleneck, cout = b->cout;
   const int64_t P = b->P;
   const unsigned short* y = (const unsigned short*)yv;
-  float* mean_y = (float*)(ws + b->off_stat_y);
-  float* istd_y = mean_y + cout;
-  float* part = (float*)(ws + b->off_part);
   float* partA = (float*)(ws + b->off_partA);
   float* partB = (float*)(ws + b->off_partB);
-  float* G = (float*)(ws + b->off_G);
-  unsigned short* dS2 = (unsigned short*)(ws + b->off_dS2);
-  unsigned short* dS3 = (unsigned short*)(ws + b->off_dS3);
   const unsigned short* pack = (const unsigned short*)(ws + b->off_pack);
   const size_t B16 = (size_t)((B + 15) & ~15), k16 = (size_t)((k + 15) & ~15), B32 = (size_t)((B + 31) & ~31);
-  // Two chains.  Only the data-gradient chain (dgrad 3x3 -> BN2 bwd -> dgrad 1x1 -> BN1 reduction
-  // -> BN1 element-wise pass on the k channels of x_{l-1}) carries the dependence from layer l to
-  // layer l-1: the next layer down reads nothing of the slab but that slice.  With concurrency on,
-  // the two weight gradients (with their sums) and the rest of BN1's element-wise pass (channels
-  // below x_{l-1}, the bulk of its traffic) run on a helper stream, ordered by events where buffers
-  // are shared: the 3x3 weight gradient needs the slab's slice g_l complete (layer l+1's share on
-  // the main chain), the 1x1 needs db_l in dS3, which the next layer's 3x3 data gradient
-  // overwrites, and the helper's share of BN1 reads dS2, which the next layer's 1x1 data gradient
-  // overwrites.  Every slab element still receives its layers' contributions in the order m, m-1,
-  // ...: the helper adds them in stream order and the main chain's share of layer l waits for the
-  // helper's share of layer l+1, so serial and concurrent runs give the same bits.  The slices of
-  // the fp32 slab that the two chains touch at the same time are disjoint channel ranges.
-  //
-  // One helper stream, and at every fork the main chain's launch issued first: a captured graph
-  // keeps the first successor of a node on the node's hardware queue, and a change of queue costs
-  // the main chain about 10 us.  Measured per step of the DenseNet-161-shaped blocks: this order
-  // 13.9 ms; three helper streams with the helpers' launches first 14.4 ms (the main chain then
-  // changes queue twice per layer); three helper streams with the main chain's launches first
-  // 19.9 ms (the graph puts all helpers on one queue in an order that makes the main chain wait).
-  if (d.schedule != DNB_SCHED_FUSED) {
-    // Materialised schedules, in program order on the caller's stream.  Shared (Section 4): before
-    // a layer's back-propagation its storage 3, then storage 1 and 2, are re-populated from the
-    // kept conv outputs and the cached folded statistics; store-everything keeps them per layer.
-    const bool recompute = d.schedule == DNB_SCHED_SHARED;
-    DNB_TRY(nhwc::bf16_to_f32(dy, G, P * cout, st));
-    for (int l = m; l >= 1; --l) {
-      const int c = c_in(d, l);
-      const LayerParams p = layer_ptrs<LayerParams, const float>(b, params, l);
-      const LayerGrads gp = layer_ptrs<LayerGrads, float>(b, dparams, l);
-      const unsigned short* bl = (const unsigned short*)(ws + b->off_b[l]);
-      float* mean_b = (float*)(ws + b->off_stat_b[l]);
-      float* istd_b = mean_b + B;
-      const float2* fold1 = (const float2*)(ws + b->off_fold1[l]);
-      const float2* fold2 = (const float2*)(ws + b->off_fold2[l]);
-      unsigned short* S1 = (unsigned short*)(ws + b->off_u[l]);
-      unsigned short* S2 = (unsigned short*)(ws + b->off_a[l]);
-      unsigned short* S3 = (unsigned short*)(ws + b->off_a2[l]);
-      const size_t c16 = (size_t)((c + 15) & ~15), c32 = (size_t)((c + 31) & ~31);
-      const unsigned short* pk1t = pack + b->pk[l] + B16 * c32;
-      const unsigned short* pk3t = pack + b->pk[l] + B16 * c32 + c16 * B32 + 9 * k16 * B32;
-      const float* gl = G + c;
-      if (recompute) DNB_TRY(nhwc::bn_relu_rows(bl, B, fold2, S3, B, nullptr, 0, P, B, st));
-      DNB_TRY(nhwc::wgrad(S3, B, gl, cout, true, partA, gp.W3, n, B, k, d.h, d.w, 9, nullptr, st));
-      DNB_TRY(nhwc::conv(gl, cout, true, pk3t, dS3, B, n, k, B, d.h, d.w, 9, nullptr, nullptr, nullptr, st));
-      DNB_TRY(nhwc::bn_relu_bwd(bl, B, dS3, B, dS3, B, nullptr, 0, P, B, p.g2, p.b2, mean_b, istd_b, gp.g2, gp.b2,
-                                part, st));
-      if (recompute) DNB_TRY(nhwc::bn_relu_rows(y, cout, fold1, S2, c, S1, c, P, c, st));
-      DNB_TRY(nhwc::wgrad(S2, c, dS3, B, false, partB, gp.W1, n, c, B, d.h, d.w, 1, nullptr, st));
-      DNB_TRY(nhwc::conv(dS3, B, false, pk1t, dS2, c, n, B, c, d.h, d.w, 1, nullptr, nullptr, nullptr, st));
-      // BN1+ReLU backward reads the concatenated features from storage 1; concat backward adds into the slab
-      DNB_TRY(nhwc::bn_relu_bwd_reduce(S1, c, dS2, c, P, c, p.g1, p.b1, mean_y, istd_y, gp.g1, gp.b1, part, st));
-      DNB_TRY(nhwc::bn_relu_bwd_apply(S1, c, dS2, c, nullptr, 0, G, cout, P, c, p.g1, p.b1, mean_y, istd_y, gp.g1, gp.b1,
-                                      st));
-    }
-    DNB_TRY(nhwc::f32_rows_to_bf16(G, cout, dx0, P, d.c0, st));
-    return DNB_OK;
-  }
-  const bool conc = b->concurrency != 0;
-  if (conc) {
-    const int rc = ensure_helper_streams(b);
-    if (rc != DNB_OK) return rc;
-  }
-  hipStream_t sH = conc ? b->sA : st;
-  enum { EV_MAIN = 0, EV_DB = 1, EV_WG1 = 3, EV_RED = 0, EV_REST = 1 };
-  auto ev = [&](int l, int which) -> hipEvent_t { return conc ? b->ev[(size_t)4 * l + which] : nullptr; };
-  auto evc = [&](int l, int which) -> hipEvent_t { return conc ? b->evc[(size_t)2 * l + which] : nullptr; };
-  auto record = [&](hipEvent_t e, hipStream_t s) { return conc ? hipEventRecord(e, s) : hipSuccess; };
-  auto wait = [&](hipStream_t s, hipEvent_t e) { return conc ? hipStreamWaitEvent(s, e, 0) : hipSuccess; };
-
-  DNB_TRY(nhwc::bf16_to_f32(dy, G, P * cout, st));
-  DNB_TRY(record(conc ? b->ev_start : nullptr, st));
-  DNB_TRY(wait(sH, conc ? b->ev_start : nullptr));
+  const bool fused = d.schedule == DNB_SCHED_FUSED, recompute = d.schedule == DNB_SCHED_SHARED;
+  nhwc::BwdLayer L{};
+  L.n = n; L.h = d.h; L.w = d.w; L.k = k; L.B = B; L.ld = cout;
+  L.y = y; L.dy = dy;
+  L.G = (float*)(ws + b->off_G);
+  L.gl = ws + b->off_dS2;  // the 1x1 data gradient is consumed where it is formed: its storage holds g_l
+  L.db = ws + b->off_dS3;
+  L.mean_y = (const float*)(ws + b->off_stat_y);
+  L.istd_y = L.mean_y + cout;
+  L.part1 = (float*)(ws + b->off_part);
+  L.part2 = L.part1 + b->part1_floats;
+  L.K = (float2*)(ws + b->off_K);
   for (int l = m; l >= 1; --l) {
     const int c = c_in(d, l);
-    const LayerParams p = layer_ptrs<LayerParams, const float>(b, params, l);
     const LayerGrads gp = layer_ptrs<LayerGrads, float>(b, dparams, l);
-    const unsigned short* bl = (const unsigned short*)(ws + b->off_b[l]);
-    float* mean_b = (float*)(ws + b->off_stat_b[l]);
-    float* istd_b = mean_b + B;
-    const float2* fold1 = (const float2*)(ws + b->off_fold1[l]);
-    const float2* fold2 = (const float2*)(ws + b->off_fold2[l]);
     const size_t c16 = (size_t)((c + 15) & ~15), c32 = (size_t)((c + 31) & ~31);
-    const unsigned short* pk1t = pack + b->pk[l] + B16 * c32;                         // 1x1 data gradient
-    const unsigned short* pk3t = pack + b->pk[l] + B16 * c32 + c16 * B32 + 9 * k16 * B32;  // 3x3 data gradient
-    const float* gl = G + c;  // gradient of x_l (fp32, pixel stride C_out), complete at this point
-
-    // ---- main chain: 3x3 data gradient; dS3 is still read by layer l+1's 1x1 weight gradient
-    if (l < m) DNB_TRY(wait(st, ev(l + 1, EV_WG1)));
-    DNB_TRY(nhwc::conv(gl, cout, true, pk3t, dS3, B, n, k, B, d.h, d.w, 9, nullptr, nullptr, nullptr, st));
-
-    // ---- helper: 3x3 weight gradient (BN2+ReLU of b_l recomputed in the operand staging)
-    if (l < m) DNB_TRY(wait(sH, ev(l + 1, EV_MAIN)));
-    DNB_TRY(nhwc::wgrad(bl, B, gl, cout, true, partA, gp.W3, n, B, k, d.h, d.w, 9, fold2, sH));
-
-    // ---- main chain, continued: BN2 backward, then the 1x1 data gradient (dS2 and the slab's
-    // lower channels are the helper's until its share of layer l+1 is done)
-    DNB_TRY(nhwc::bn_relu_bwd(bl, B, dS3, B, dS3, B, nullptr, 0, P, B, p.g2, p.b2, mean_b, istd_b, gp.g2, gp.b2,
-                              part, st));
-    DNB_TRY(record(ev(l, EV_DB), st));
-    if (l < m) DNB_TRY(wait(st, evc(l + 1, EV_REST)));
-    DNB_TRY(nhwc::conv(dS3, B, false, pk1t, dS2, c, n, B, c, d.h, d.w, 1, nullptr, nullptr, nullptr, st));
-
-    // ---- helper: 1x1 weight gradient (BN1+ReLU of y[..., :C_l] recomputed in the operand staging)
-    DNB_TRY(wait(sH, ev(l, EV_DB)));
-    DNB_TRY(nhwc::wgrad(y, cout, dS3, B, false, partB, gp.W1, n, c, B, d.h, d.w, 1, fold1, sH));
-    DNB_TRY(record(ev(l, EV_WG1), sH));
-
-    // ---- main chain, continued: BN1's reduction, and BN1's element-wise pass with the concat
-    // backward (accumulate into the slab) on the k channels of x_{l-1}.  The channels below go to
-    // the helper; layer 1 has only those (x_0); on one stream the pass is one launch.
-    DNB_TRY(nhwc::bn_relu_bwd_reduce(y, cout, dS2, c, P, c, p.g1, p.b1, mean_y, istd_y, gp.g1, gp.b1, part, st));
-    DNB_TRY(record(evc(l, EV_RED), st));
-    const int lo = !conc ? 0 : (l >= 2 ? c - k : c);
-    if (lo < c)
-      DNB_TRY(nhwc::bn_relu_bwd_apply(y + lo, cout, dS2 + lo, c, nullptr, 0, G + lo, cout, P, c - lo, p.g1 + lo,
-                                      p.b1 + lo, mean_y + lo, istd_y + lo, gp.g1 + lo, gp.b1 + lo, st));
-    DNB_TRY(record(ev(l, EV_MAIN), st));
-
-    // ---- helper: the same pass on the channels below
-    DNB_TRY(wait(sH, evc(l, EV_RED)));
-    if (lo > 0)
-      DNB_TRY(nhwc::bn_relu_bwd_apply(y, cout, dS2, c, nullptr, 0, G, cout, P, lo, p.g1, p.b1, mean_y, istd_y, gp.g1,
-                                      gp.b1, sH));
-    DNB_TRY(record(evc(l, EV_REST), sH));
+    void* S1 = ws + b->off_u[l];
+    void* S2 = ws + b->off_a[l];
+    void* S3 = ws + b->off_a2[l];
+    L.c = c;
+    L.last = l == m;
+    L.above_first = l + 1 == m;
+    L.b = ws + b->off_b[l];
+    L.x = fused ? (const void*)y : S1; L.x_ld = fused ? cout : c;
+    L.pk1t = pack + b->pk[l] + B16 * c32;                              // 1x1 data gradient
+    L.pk3t = pack + b->pk[l] + B16 * c32 + c16 * B32 + 9 * k16 * B32;  // 3x3 data gradient
+    L.above_fold1 = L.fold1;
+    L.above_dgamma = L.dgamma1; L.above_dbeta = L.dbeta1;
+    L.fold1 = (const float2*)(ws + b->off_fold1[l]);
+    L.fold2 = (const float2*)(ws + b->off_fold2[l]);
+    L.mean_b = (const float*)(ws + b->off_stat_b[l]);
+    L.istd_b = L.mean_b + B;
+    L.dgamma1 = gp.g1; L.dbeta1 = gp.b1; L.dgamma2 = gp.g2; L.dbeta2 = gp.b2;
+    DNB_TRY(nhwc::bwd_dgrad3(L, st));
+    if (recompute) {
+      DNB_TRY(nhwc::bn_relu_rows(L.b, B, L.fold2, S3, B, nullptr, 0, P, B, st));
+      DNB_TRY(nhwc::bn_relu_rows(y, cout, L.fold1, S2, c, S1, c, P, c, st));
+    }
+    DNB_TRY(nhwc::bwd_dgrad1(L, st));
+    const void* gl = l == m ? (const void*)((const unsigned short*)dy + c) : L.gl;
+    DNB_TRY(nhwc::wgrad(fused ? L.b : S3, B, gl, l == m ? cout : k, false, partA, gp.W3, n, B, k, d.h, d.w, 9,
+                        fused ? L.fold2 : nullptr, st));
+    DNB_TRY(nhwc::wgrad(fused ? (const void*)y : S2, fused ? cout : c, L.db, B, false, partB, gp.W1, n, c, B, d.h, d.w, 1,
+                        fused ? L.fold1 : nullptr, st));
   }
-  if (conc) {  // join: the caller's stream is done only when the helper chain is
-    DNB_TRY(hipEventRecord(b->ev_endA, sH));
-    DNB_TRY(hipStreamWaitEvent(st, b->ev_endA, 0));
-  }
-  DNB_TRY(nhwc::f32_rows_to_bf16(G, cout, dx0, P, d.c0, st));
+  DNB_TRY(nhwc::bwd_dx0(L, dx0, st));
   return DNB_OK;
 }
 
@@ -592,15 +502,17 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
     need(nhwc::stats_partial_floats(P, d.c0));
     need(nhwc::conv_stats_partial_floats(d.n, B, d.h, d.w));
     need(nhwc::conv_stats_partial_floats(d.n, k, d.h, d.w));
-    need(nhwc::bn_bwd_partial_floats(P, B));
-    size_t pe = 0;  // bf16 elements
+    size_t pe = 0, p1 = 0;  // pe: bf16 elements
     for (int l = 1; l <= m; ++l) {
-      need(nhwc::bn_bwd_partial_floats(P, c_in(d, l)));
+      const size_t f1 = nhwc::bwd_partial1_floats(P, c_in(d, l));
+      if (f1 > p1) p1 = f1;
       const size_t f = nhwc::wgrad_partial_floats(d.n, c_in(d, l), B, d.h, d.w, 1);
       if (f > partB) partB = f;
       b->pk[l] = pe;
       pe += nhwc::packed_layer_elems(c_in(d, l), k, B);
     }
+    b->part1_floats = p1;
+    need(p1 + nhwc::bwd_partial2_floats(d.n, d.h, d.w, k, B));
     partA = nhwc::wgrad_partial_floats(d.n, B, k, d.h, d.w, 9);
     pack = (pe + 1) / 2;
   } else {
@@ -627,7 +539,8 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
       for (int l = 1; l <= m; ++l) { b->pk[l] = pack; pack += packed_layer_floats(c_in(d, l), k, B); }
     }
   }
-  mem.scratch_bytes = (uint64_t)(part + (bf16 ? 1 : 2) * (partA + partB) + pack) * sizeof(float);
+  const size_t kf = bf16 ? (size_t)cout * 2 : 0;
+  mem.scratch_bytes = (uint64_t)(part + (bf16 ? 1 : 2) * (partA + partB) + pack + kf) * sizeof(float);
   b->off_part = carve(part * sizeof(float), false);
   // fp32: two buffers each, used alternately by consecutive layers (a layer's partials are
   // summed by extra workgroups of the next layer's weight-gradient launch)
@@ -637,10 +550,11 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
   b->off_partA = carve(nbuf * partA * sizeof(float), false);
   b->off_partB = carve(nbuf * partB * sizeof(float), false);
   b->off_pack = carve(pack * sizeof(float), false);
-  // measured on MI355X: with the weight gradients on helper streams the fp32 step is slower
-  // (idle time between dependent launches of different streams outweighs the overlap), the
-  // bf16 step, whose helper chains carry long kernels, a fifth faster
-  b->concurrency = d.dtype == DNB_BF16 ? 1 : 0;
+  b->off_K = carve(kf * sizeof(float), false);
+  // measured on MI355X: with the weight gradients on helper streams the fp32 step is slower (idle
+  // time between dependent launches of different streams outweighs the overlap); the bf16 backward
+  // pass is one chain of launches on the caller's stream
+  b->concurrency = 0;
   b->streams_ready = false;
   b->sA = b->sB = nullptr;
   b->ev_start = b->ev_endA = b->ev_endB = nullptr;
@@ -834,7 +748,7 @@ int dnb_block_backward(dnb_block* b, const void* paramsv, const void* yv, const 
   hipStream_t st = (hipStream_t)stream;
   const dnb_block_desc& d = b->d;
   if (d.dtype == DNB_BF16)
-    return backward_bf16(b, (const float*)paramsv, yv, dyv, dx0v, (float*)dparamsv, (char*)wsv, st);
+    return backward_bf16(b, yv, dyv, dx0v, (float*)dparamsv, (char*)wsv, st);
   if (d.bottleneck == 0)
     return backward_plain3x3(b, (const float*)paramsv, (const float*)yv, (const float*)dyv, (float*)dx0v,
                              (float*)dparamsv, (char*)wsv, st);

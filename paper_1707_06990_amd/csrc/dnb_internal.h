@@ -180,8 +180,6 @@ hipError_t copy_rows(const void* src, int64_t sld, void* dst, int64_t dld, int64
 // out = bf16(max(0, fma(x, fold.x, fold.y))) per channel; copy (may be null) = x  (storage 2 / storage 1)
 hipError_t bn_relu_rows(const void* x, int64_t ld, const float2* fold, void* out, int64_t old, void* copy, int64_t cld,
                         int64_t P, int c, hipStream_t st);
-hipError_t bf16_to_f32(const void* src, float* dst, int64_t count, hipStream_t st);
-hipError_t f32_rows_to_bf16(const float* src, int64_t sld, void* dst, int64_t P, int c, hipStream_t st);
 size_t stats_partial_floats(int64_t P, int c);
 hipError_t stats_partial(const void* x, int64_t ld, int64_t P, int c, float* part, int* T, hipStream_t st);
 // per layer, in order: 1x1 forward [B16][c32], 1x1 dgrad [c16][B32], 3x3 forward [9][k16][B32],
@@ -203,14 +201,32 @@ hipError_t bn_relu_bwd(const void* x, int64_t x_ld, const void* dact, int64_t d_
                        float* G, int64_t g_ld, int64_t P, int c, const float* gamma, const float* beta,
                        const float* mean, const float* istd, float* dgamma, float* dbeta, float* part,
                        hipStream_t st);
-// its two passes on their own (the element-wise pass also over a channel sub-range)
-hipError_t bn_relu_bwd_reduce(const void* x, int64_t x_ld, const void* dact, int64_t d_ld, int64_t P, int c,
-                              const float* gamma, const float* beta, const float* mean, const float* istd,
-                              float* dgamma, float* dbeta, float* part, hipStream_t st);
-hipError_t bn_relu_bwd_apply(const void* x, int64_t x_ld, const void* dact, int64_t d_ld, void* du_bf, int64_t du_ld,
-                             float* G, int64_t g_ld, int64_t P, int c, const float* gamma, const float* beta,
-                             const float* mean, const float* istd, const float* dgamma, const float* dbeta,
-                             hipStream_t st);
+
+// One layer of the backward chain (dnb_nhwc_bwd.hip).  c = C_l input channels, ld = C_out.
+struct BwdLayer {
+  int n, h, w, c, k, B;
+  int64_t ld;
+  bool last;                     // l = m: the slab is not written yet, dy stands in for it
+  bool above_first;              // layer l+1 is the last one: K0 / K1 are set, not added to
+  const void *y, *dy, *b;        // features, gradient of the output, b_l
+  const void* x; int64_t x_ld;   // concatenated input of the layer: y in place, or storage 1
+  float* G;                      // gradient slab
+  void *gl, *db;                 // g_l in bf16 [P][k] (l < m), gradient of b_l [P][B]
+  const void *pk1t, *pk3t;       // packed data-gradient weights
+  const float2 *fold1, *fold2, *above_fold1;
+  const float *mean_y, *istd_y, *mean_b, *istd_b;
+  float *dgamma1, *dbeta1, *dgamma2, *dbeta2, *above_dgamma, *above_dbeta;
+  float *part1, *part2;          // partial sums of BN1 (kept for the next layer down) and BN2
+  float2* K;                     // per channel of y: K0, K1
+};
+size_t bwd_partial1_floats(int64_t P, int C);
+size_t bwd_partial2_floats(int n, int h, int w, int k, int B);
+// 3x3 data gradient and BN2 backward: db, g_l, BN2's parameter gradients, and layer l+1's BN1 parameter gradients
+hipError_t bwd_dgrad3(const BwdLayer& L, hipStream_t st);
+// 1x1 data gradient, BN1 backward and concat backward into the slab
+hipError_t bwd_dgrad1(const BwdLayer& L, hipStream_t st);
+// gradient of the block input and layer 1's BN1 parameter gradients (L: layer 1)
+hipError_t bwd_dx0(const BwdLayer& L, void* dx0, hipStream_t st);
 }  // namespace nhwc
 
 }  // namespace dnb

@@ -12,39 +12,13 @@
 // the slow axis, so both operands are transposed on their way into LDS ([channel][pixel]); the
 // 3x3 stages a row tile once and reads its nine taps as shifted fragments.
 #include "dnb_internal.h"
+#include "dnb_nhwc_dev.h"
 #include "dnb_stats.h"
 
 namespace dnb {
 namespace nhwc {
 
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned short u16;
-
-__device__ __forceinline__ float bf2f(u16 v) { return __uint_as_float((unsigned)v << 16); }
-// round to nearest even (the hardware conversion of gfx950)
-__device__ __forceinline__ u16 f2bf(float f) {
-  const __bf16 b = (__bf16)f;
-  return __builtin_bit_cast(u16, b);
-}
-
-union V8 {          // 8 bf16 = 16 bytes
-  uint4 q;
-  u16 h[8];
-  bf16x8 v;
-};
-
-__device__ __forceinline__ f32x4 mfma_bf16(const V8& a, const V8& b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, c, 0, 0, 0);
-}
-
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
 
 // ----------------------------------------------------------------------------- small kernels
 
@@ -81,35 +55,6 @@ __global__ __launch_bounds__(256) void k_bn_relu_rows(const u16* __restrict__ x,
     }
     *reinterpret_cast<uint4*>(out + p * old + 8 * v) = o.q;
     if (copy) *reinterpret_cast<uint4*>(copy + p * cld + 8 * v) = r.q;
-  }
-}
-
-// G (fp32, [P][c]) = dy (bf16, [P][c])
-__global__ __launch_bounds__(256) void k_bf16_to_f32(const u16* __restrict__ src, float* __restrict__ dst,
-                                                     int64_t total8) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total8; i += (int64_t)gridDim.x * 256) {
-    V8 s;
-    s.q = *reinterpret_cast<const uint4*>(src + 8 * i);
-    float4 a = make_float4(bf2f(s.h[0]), bf2f(s.h[1]), bf2f(s.h[2]), bf2f(s.h[3]));
-    float4 b = make_float4(bf2f(s.h[4]), bf2f(s.h[5]), bf2f(s.h[6]), bf2f(s.h[7]));
-    *reinterpret_cast<float4*>(dst + 8 * i) = a;
-    *reinterpret_cast<float4*>(dst + 8 * i + 4) = b;
-  }
-}
-
-// dst (bf16, [P][c]) = src (fp32, [P][ld]) first c channels
-__global__ __launch_bounds__(256) void k_f32_rows_to_bf16(const float* __restrict__ src, int64_t sld,
-                                                          u16* __restrict__ dst, int64_t P, int cv) {
-  const int64_t total = P * cv;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-    const int64_t p = i / cv;
-    const int v = (int)(i - p * cv);
-    const float4 a = *reinterpret_cast<const float4*>(src + p * sld + 8 * v);
-    const float4 b = *reinterpret_cast<const float4*>(src + p * sld + 8 * v + 4);
-    V8 o;
-    o.h[0] = f2bf(a.x); o.h[1] = f2bf(a.y); o.h[2] = f2bf(a.z); o.h[3] = f2bf(a.w);
-    o.h[4] = f2bf(b.x); o.h[5] = f2bf(b.y); o.h[6] = f2bf(b.z); o.h[7] = f2bf(b.w);
-    *reinterpret_cast<uint4*>(dst + p * (int64_t)(8 * cv) + 8 * v) = o.q;
   }
 }
 
@@ -1198,18 +1143,6 @@ hipError_t bn_relu_rows(const void* x, int64_t ld, const float2* fold, void* out
   return hipGetLastError();
 }
 
-hipError_t bf16_to_f32(const void* src, float* dst, int64_t count, hipStream_t st) {
-  hipLaunchKernelGGL(k_bf16_to_f32, dim3(grid1d(count / 8, 512, 16384)), dim3(256), 0, st, (const u16*)src, dst,
-                     count / 8);
-  return hipGetLastError();
-}
-
-hipError_t f32_rows_to_bf16(const float* src, int64_t sld, void* dst, int64_t P, int c, hipStream_t st) {
-  hipLaunchKernelGGL(k_f32_rows_to_bf16, dim3(grid1d(P * (c / 8), 512, 16384)), dim3(256), 0, st, src, sld,
-                     (u16*)dst, P, c / 8);
-  return hipGetLastError();
-}
-
 int stats_splits(int64_t P, int c) {
   const int groups = (c / 8 + 31) / 32;
   int s = 1024 / groups;
@@ -1378,6 +1311,7 @@ hipError_t wgrad(const void* a, int64_t a_ld, const void* g, int64_t g_ld, bool 
                        (int)grid.z, cin, cout, dw);
     return hipGetLastError();
   }
+  if (g_f32 && fold) return hipErrorInvalidValue;  // the block's gradient operands are bf16
   const Wg3Geom q3 = wg3_geom(h, w);
   const bool three = taps == 9 && q3.ok;
   const int tpi = three ? q3.tpi : (h * w + 63) / 64, tiles = n * tpi;
@@ -1388,7 +1322,7 @@ hipError_t wgrad(const void* a, int64_t a_ld, const void* g, int64_t g_ld, bool 
 #define DNB_W3(TG, PRO)                                                                                \
   hipLaunchKernelGGL((k_wgrad3<TG, PRO>), grid, dim3(512), 0, st, (const u16*)a, a_ld, (const TG*)g, \
                      g_ld, part, cin, cout, n, h, w, q3.R, q3.FR, tpi, tps, fold)
-    if (g_f32) { if (fold) DNB_W3(float, true); else DNB_W3(float, false); }
+    if (g_f32) DNB_W3(float, false);
     else       { if (fold) DNB_W3(u16, true); else DNB_W3(u16, false); }
 #undef DNB_W3
     const int64_t per_split = (int64_t)grid.y * grid.z * WG3_BLOCK;
@@ -1400,11 +1334,10 @@ hipError_t wgrad(const void* a, int64_t a_ld, const void* g, int64_t g_ld, bool 
   hipLaunchKernelGGL((k_wgrad<TAPS, TG, PRO>), grid, dim3(256), 0, st, (const u16*)a, a_ld, (const TG*)g, \
                      g_ld, part, cin, cout, n, h, w, tpi, tps, fold)
   if (taps == 9) {
-    if (g_f32) { if (fold) DNB_W(9, float, true); else DNB_W(9, float, false); }
+    if (g_f32) DNB_W(9, float, false);
     else       { if (fold) DNB_W(9, u16, true); else DNB_W(9, u16, false); }
   } else {
-    if (g_f32) { if (fold) DNB_W(1, float, true); else DNB_W(1, float, false); }
-    else       { if (fold) DNB_W(1, u16, true); else DNB_W(1, u16, false); }
+    DNB_W(1, float, false);  // (a bf16 gradient operand has taken k_wgrad1 above)
   }
 #undef DNB_W
   hipError_t e = hipGetLastError();
@@ -1436,7 +1369,7 @@ int bn_bwd_splits(int64_t P, int c) {
 size_t bn_bwd_partial_floats(int64_t P, int c) { return (size_t)c * bn_bwd_splits(P, c) * 2; }
 
 // BN+ReLU backward, reduction pass: dgamma / dbeta over (P, c).
-hipError_t bn_relu_bwd_reduce(const void* x, int64_t x_ld, const void* dact, int64_t d_ld, int64_t P, int c,
+static hipError_t bn_relu_bwd_reduce(const void* x, int64_t x_ld, const void* dact, int64_t d_ld, int64_t P, int c,
                               const float* gamma, const float* beta, const float* mean, const float* istd,
                               float* dgamma, float* dbeta, float* part, hipStream_t st) {
   const int S = bn_bwd_splits(P, c), lsh = bn_bwd_lsh(c), L = 1 << lsh;
@@ -1453,7 +1386,7 @@ hipError_t bn_relu_bwd_reduce(const void* x, int64_t x_ld, const void* dact, int
 // accumulated into the fp32 slab (row stride g_ld); else du is written as bf16 to du_bf (may
 // alias dact).  A channel sub-range of a wider BN is this call with every pointer moved to the
 // range's first channel (a multiple of 8) and `c` its length; `P` is the BN's pixel count.
-hipError_t bn_relu_bwd_apply(const void* x, int64_t x_ld, const void* dact, int64_t d_ld, void* du_bf, int64_t du_ld,
+static hipError_t bn_relu_bwd_apply(const void* x, int64_t x_ld, const void* dact, int64_t d_ld, void* du_bf, int64_t du_ld,
                              float* G, int64_t g_ld, int64_t P, int c, const float* gamma, const float* beta,
                              const float* mean, const float* istd, const float* dgamma, const float* dbeta,
                              hipStream_t st) {

@@ -1,0 +1,704 @@
+// bf16 / NHWC backward chain of a bottleneck layer: the kernels that carry the dependence from layer
+// l+1 to layer l.  Three launches per layer (the weight gradients hang off them):
+//
+//   k_dgrad3      3x3 data gradient of g_l, ReLU mask of BN2 and its two sums in the epilogue
+//   k_bn2_apply   gradient of b_l from those sums (element-wise on P x B)
+//   k_dgrad1      1x1 data gradient; BN1+ReLU backward and the concatenation's backward
+//                 (accumulate into the slab G) in the epilogue, with BN1's two sums
+//
+// BN1's backward is  du = s*(dz - dbeta/P - xhat*dgamma/P),  dz = the masked gradient, s = gamma*istd.
+// Its first term needs no sum, so it is added into the slab where dz is formed; the other two are
+// constants per channel times 1 and xhat, and xhat does not depend on the layer (a channel's
+// statistics are those of the produced feature).  They are therefore collected per channel,
+//   K0 = sum_l s_l*dbeta_l/P,   K1 = sum_l s_l*dgamma_l/P,
+// and taken off once, where a slice of the slab is finally read:  g = G - K0 - K1*xhat.  A layer
+// then moves 10 bytes per element of its concatenated input (x 2, G 4 + 4) instead of the 22 of
+// separate passes (gradient written 2; reduction 2 + 2; element-wise pass 2 + 2 + 4 + 4; the slab's
+// initial copy of dy, another 6 per element of the block's output, goes away too: the first layer
+// that touches the slab reads dy in its place).  Against the separate passes, on one stream where
+// those ran beside a helper stream: DenseNet-264-shaped step at batch 32, 25.9 -> 20.5 ms;
+// DenseNet-161-shaped, 20.1 -> 17.2 ms at batch 32, 11.6 -> 8.0 ms at batch 2.
+#include "dnb_internal.h"
+#include "dnb_nhwc_dev.h"
+#include "dnb_stats.h"
+
+namespace dnb {
+namespace nhwc {
+
+namespace {
+
+// ---------------------------------------------------------------- 3x3 data gradient
+
+struct Dgrad3Args {
+  const u16* dy;                        // last layer: the slice of dy, row stride g_ld; else null
+  const float* G; int64_t g_ld;         // slab at the slice's first channel
+  const u16* x; int64_t x_ld;           // features at the slice's first channel
+  const float2* K;                      // K0, K1 of the layers above l+1 at the slice (null: none yet)
+  const float2* part1; int T1, C1;      // layer l+1's BN1 partials [T1][C1]
+  int c1;                               // ... and the slice's first channel among the C1
+  const float2* fold1;                  // layer l+1's folded BN1 at the slice
+  const float *mean, *istd;             // of the slice's features
+  float inv_p;
+  u16* gl;                              // out: g_l, [P][k] (not written for the last layer)
+  int k;
+  const u16* W; int M16, K32;           // packed weights [9][M16][K32]
+  const u16* b; const float2* fold2; const float *mean_b, *istd_b;
+  int B;
+  u16* dz;                              // out [P][B]: masked gradient of BN2's output
+  float2* part2; int T2;                // out [T2][B]: BN2's sums
+  int H, Wd, tpi, tiles, gy;
+  // finalisation of layer l+1's BN1 by extra workgroups: parameter gradients, K0 / K1
+  float *dgamma, *dbeta; float2* Kall; const float2* fold1all; int Ckeep, first;
+};
+
+// Sum over the T partials of channel ch, the four waves taking every fourth; call with all threads,
+// ch clamped into range.  sh: 4*64 float2.  Result valid in wave 0.
+__device__ __forceinline__ float2 sum_partials64(const float2* __restrict__ part, int T, int C, int ch, float2* sh) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  float2 s = make_float2(0.f, 0.f);
+  int t = wave;
+  for (; t + 28 < T; t += 32) {
+    float2 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(t + 4 * u) * C + ch];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) { s.x += v[u].x; s.y += v[u].y; }
+  }
+  for (; t < T; t += 4) { const float2 v = part[(int64_t)t * C + ch]; s.x += v.x; s.y += v.y; }
+  __syncthreads();
+  sh[wave * 64 + lane] = s;
+  __syncthreads();
+  float2 r = sh[lane];
+#pragma unroll
+  for (int w = 1; w < 4; ++w) { r.x += sh[w * 64 + lane].x; r.y += sh[w * 64 + lane].y; }
+  return r;
+}
+
+// Output channels (B of them) on M, pixels of one image on N.  A workgroup owns a tile of 64*NT
+// consecutive pixels and MT M-tiles; its four waves split the pixels (NT N-tiles each) and every wave
+// forms all MT M-tiles, so nothing is added across waves but the two sums at the end.  The slice
+// of the slab is corrected, rounded to bf16 and staged once per tile with a halo of a row and a
+// pixel on either side; in passes of 64 channels (k above 64).  Workgroups walk over tiles T2 apart.
+template <int NT, int MT>
+__global__ __launch_bounds__(256) void k_dgrad3(Dgrad3Args A) {
+  extern __shared__ u16 lds[];
+  __shared__ float2 sh[256];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 15, g = lane >> 4;
+  const int nconv = A.T2 * A.gy;
+  if ((int)blockIdx.x >= nconv) {  // finalise 64 channels of layer l+1's BN1
+    const int ch = ((int)blockIdx.x - nconv) * 64 + lane, cc = min(ch, A.C1 - 1);
+    const float2 s = sum_partials64(A.part1, A.T1, A.C1, cc, sh);
+    if (wave == 0 && ch < A.C1) {
+      A.dbeta[ch] = s.x;
+      A.dgamma[ch] = s.y;
+      if (ch < A.Ckeep) {
+        const float sc = A.fold1all[ch].x * A.inv_p;
+        const float2 o = A.first ? make_float2(0.f, 0.f) : A.Kall[ch];
+        A.Kall[ch] = make_float2(__fmaf_rn(sc, s.x, o.x), __fmaf_rn(sc, s.y, o.y));
+      }
+    }
+    return;
+  }
+  constexpr int PITCH = 64 + 8, TP = 64 * NT;
+  const int HW = A.H * A.Wd, W = A.Wd, halo = W + 1, seg = TP + 2 * halo;
+  const int pw = blockIdx.x / A.gy, m0 = (blockIdx.x % A.gy) * MT * 16;
+  float* coef = reinterpret_cast<float*>(lds + seg * PITCH);  // [3][k]: K0, K1*istd, mean
+  if (!A.dy) {
+    for (int c0 = 0; c0 < A.k; c0 += 64) {
+      const int i = c0 + lane, ic = min(i, A.k - 1);
+      const float2 s = sum_partials64(A.part1, A.T1, A.C1, A.c1 + ic, sh);
+      if (wave == 0 && i < A.k) {
+        const float sc = A.fold1[ic].x * A.inv_p;
+        const float2 o = A.K ? A.K[ic] : make_float2(0.f, 0.f);
+        coef[i] = __fmaf_rn(sc, s.x, o.x);
+        coef[A.k + i] = __fmaf_rn(sc, s.y, o.y) * A.istd[ic];
+        coef[2 * A.k + i] = A.mean[ic];
+      }
+    }
+  }
+  float s0[MT][4], s1[MT][4], fs[MT][4], ft[MT][4], mu[MT][4];
+  int mch[MT];
+#pragma unroll
+  for (int a = 0; a < MT; ++a) {
+    mch[a] = m0 + a * 16 + 4 * g;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = min(mch[a] + r, A.B - 1);
+      const float2 f = A.fold2[m];
+      fs[a][r] = f.x; ft[a][r] = f.y; mu[a][r] = A.mean_b[m];
+      s0[a][r] = s1[a][r] = 0.f;
+    }
+  }
+
+  for (int tile = pw; tile < A.tiles; tile += A.T2) {
+    const int img = tile / A.tpi, q0 = (tile - img * A.tpi) * TP;
+    const int64_t p0 = (int64_t)img * HW;
+    f32x4 acc[MT][NT];
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[a][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    uint2 braw[MT][NT];  // b_l at the outputs' positions, requested before the staging
+    bool lok[NT], rok[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int q = q0 + (wave * NT + t) * 16 + j, qc = min(q, HW - 1), wc = q % W;
+      lok[t] = wc != 0;
+      rok[t] = wc != W - 1;
+#pragma unroll
+      for (int a = 0; a < MT; ++a)
+        braw[a][t] = *reinterpret_cast<const uint2*>(A.b + (p0 + qc) * A.B + min(mch[a], A.B - 4));
+    }
+    for (int c0 = 0; c0 < A.K32; c0 += 64) {
+      const int kw = min(64, A.K32 - c0), vsh = kw == 64 ? 3 : 2, nvec = seg << vsh;
+      __syncthreads();  // coefficients written; the previous pass's fragment reads are done
+      for (int base = 0; base < nvec; base += 4 * 256) {
+        uint4 ga[4], gb[4], xr[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {  // loads unconditional at clamped addresses
+          const int idx = min(base + u * 256 + tid, nvec - 1), s = idx >> vsh;
+          const int ch = min(c0 + 8 * (idx & ((1 << vsh) - 1)), A.k - 8);
+          const int64_t p = p0 + min(max(q0 - halo + s, 0), HW - 1);
+          if (A.dy) {
+            ga[u] = *reinterpret_cast<const uint4*>(A.dy + p * A.g_ld + ch);
+          } else {
+            const float* gp = A.G + p * A.g_ld + ch;
+            ga[u] = *reinterpret_cast<const uint4*>(gp);
+            gb[u] = *reinterpret_cast<const uint4*>(gp + 4);
+            xr[u] = *reinterpret_cast<const uint4*>(A.x + p * A.x_ld + ch);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int idx = base + u * 256 + tid;
+          if (idx < nvec) {
+            const int s = idx >> vsh, v = idx & ((1 << vsh) - 1), ch = c0 + 8 * v, q = q0 - halo + s;
+            V8 o;
+            o.q = make_uint4(0u, 0u, 0u, 0u);
+            if (q >= 0 && q < HW && ch < A.k) {
+              if (A.dy) {
+                o.q = ga[u];
+              } else {
+                V8 xv;
+                xv.q = xr[u];
+                const float gf[8] = {__uint_as_float(ga[u].x), __uint_as_float(ga[u].y), __uint_as_float(ga[u].z),
+                                     __uint_as_float(ga[u].w), __uint_as_float(gb[u].x), __uint_as_float(gb[u].y),
+                                     __uint_as_float(gb[u].z), __uint_as_float(gb[u].w)};
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                  o.h[e] = f2bf(gf[e] - coef[ch + e] - coef[A.k + ch + e] * (bf2f(xv.h[e]) - coef[2 * A.k + ch + e]));
+                if (m0 == 0 && s >= halo && s < halo + TP)
+                  *reinterpret_cast<uint4*>(A.gl + (p0 + q) * A.k + ch) = o.q;
+              }
+            }
+            *reinterpret_cast<uint4*>(&lds[s * PITCH + 8 * v]) = o.q;
+          }
+        }
+      }
+      __syncthreads();
+      const int rows = A.M16 - 1;
+#pragma unroll
+      for (int t9 = 0; t9 < 9; ++t9) {
+        const int di = t9 / 3 - 1, dj = t9 % 3 - 1;
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+          if (kk * 32 < kw) {
+            V8 wv[MT], bv[NT];
+#pragma unroll
+            for (int a = 0; a < MT; ++a)
+              wv[a].q = *reinterpret_cast<const uint4*>(A.W + ((int64_t)t9 * A.M16 + min(m0 + a * 16 + j, rows)) * A.K32 +
+                                                        c0 + kk * 32 + 8 * g);
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+              bv[t].q = *reinterpret_cast<const uint4*>(
+                  &lds[((wave * NT + t) * 16 + j + halo + di * W + dj) * PITCH + kk * 32 + 8 * g]);
+              if ((dj < 0 && !lok[t]) || (dj > 0 && !rok[t])) bv[t].q = make_uint4(0u, 0u, 0u, 0u);
+            }
+#pragma unroll
+            for (int a = 0; a < MT; ++a)
+#pragma unroll
+              for (int t = 0; t < NT; ++t) acc[a][t] = mfma_bf16(wv[a], bv[t], acc[a][t]);
+          }
+        }
+      }
+    }
+    // ReLU mask of BN2, the two sums over what is stored
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const int q = q0 + (wave * NT + t) * 16 + j;
+        if (q < HW && mch[a] < A.B) {
+          const float bf[4] = {bf2f((u16)braw[a][t].x), bf2f((u16)(braw[a][t].x >> 16)), bf2f((u16)braw[a][t].y),
+                               bf2f((u16)(braw[a][t].y >> 16))};
+          u16 h[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            h[r] = __fmaf_rn(bf[r], fs[a][r], ft[a][r]) > 0.f ? f2bf(acc[a][t][r]) : (u16)0;
+            const float dz = bf2f(h[r]);
+            s0[a][r] += dz;
+            s1[a][r] = __fmaf_rn(dz, bf[r] - mu[a][r], s1[a][r]);
+          }
+          *reinterpret_cast<uint2*>(A.dz + (p0 + q) * A.B + mch[a]) =
+              make_uint2((unsigned)h[0] | ((unsigned)h[1] << 16), (unsigned)h[2] | ((unsigned)h[3] << 16));
+        }
+      }
+  }
+  // sums: over the 16 pixel lanes, then over the waves
+  __syncthreads();
+  float* red = reinterpret_cast<float*>(lds);  // [4][MT*16][2]
+#pragma unroll
+  for (int a = 0; a < MT; ++a)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float u = s0[a][r], v = s1[a][r];
+#pragma unroll
+      for (int off = 1; off < 16; off <<= 1) { u += __shfl_xor(u, off, 64); v += __shfl_xor(v, off, 64); }
+      if (j == 0) {
+        float* p = red + ((wave * MT + a) * 16 + 4 * g + r) * 2;
+        p[0] = u; p[1] = v;
+      }
+    }
+  __syncthreads();
+  if (tid < MT * 16) {
+    const int m = m0 + tid;
+    if (m < A.B) {
+      float u = 0.f, v = 0.f;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) { u += red[(w * MT * 16 + tid) * 2]; v += red[(w * MT * 16 + tid) * 2 + 1]; }
+      A.part2[(int64_t)pw * A.B + m] = make_float2(u, v * A.istd_b[m]);
+    }
+  }
+}
+
+// ---------------------------------------------------------------- BN2 backward, element-wise
+
+// out[c] = sum over T of part[T][C], one workgroup per 64 channels
+__global__ __launch_bounds__(256) void k_sum_pairs(const float2* __restrict__ part, int T, int C, float2* __restrict__ out) {
+  __shared__ float2 sh[256];
+  const int ch = blockIdx.x * 64 + (threadIdx.x & 63);
+  const float2 s = sum_partials64(part, T, C, min(ch, C - 1), sh);
+  if (threadIdx.x < 64 && ch < C) out[ch] = s;
+}
+
+// db = s2*(dz - dbeta/P - xhat*dgamma/P) in place.  Thread = (8-channel vector, pixel row); grid
+// (pixel ranges, groups of 8*L channels).  Every workgroup adds the T partials of its channels
+// itself (T is small: see launch_dgrad3), the first of a group stores the parameter gradients.
+__global__ __launch_bounds__(256) void k_bn2_apply(u16* __restrict__ dz, const u16* __restrict__ b, int64_t P, int B,
+                                                   int ppb, int lsh, float inv_p, const float2* __restrict__ fold2,
+                                                   const float* __restrict__ mean, const float* __restrict__ istd,
+                                                   const float2* __restrict__ part, int T, float* __restrict__ dgamma,
+                                                   float* __restrict__ dbeta) {
+  __shared__ float2 sh[256];
+  __shared__ float4 co[256];  // scale, scale*dbeta/P, scale*dgamma/P*istd, mean
+  const int L = 1 << lsh, rows = 256 >> lsh, cvl = threadIdx.x & (L - 1), pr = threadIdx.x >> lsh;
+  const int cb = blockIdx.y * L * 8, ch0 = cb + cvl * 8;
+  const int64_t p0 = (int64_t)blockIdx.x * ppb, p1 = min(P, p0 + ppb);
+  const bool ok = ch0 < B;
+  const int chc = ok ? ch0 : 0;
+  V8 d0[2], b0[2];  // the first rows' data, in flight while the sums are formed
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int64_t p = min(p0 + pr + u * rows, p1 - 1);
+    d0[u].q = *reinterpret_cast<const uint4*>(dz + p * B + chc);
+    b0[u].q = *reinterpret_cast<const uint4*>(b + p * B + chc);
+  }
+  for (int c0 = 0; c0 < L * 8; c0 += 64) {
+    const int cl = c0 + (threadIdx.x & 63), ch = cb + cl;
+    const float2 s = sum_partials64(part, T, B, min(ch, B - 1), sh);
+    if (threadIdx.x < 64 && cl < L * 8 && ch < B) {
+      const float sc = fold2[ch].x;
+      co[cl] = make_float4(sc, sc * (s.x * inv_p), sc * (s.y * inv_p) * istd[ch], mean[ch]);
+      if (blockIdx.x == 0) { dbeta[ch] = s.x; dgamma[ch] = s.y; }
+    }
+  }
+  __syncthreads();
+  if (!ok) return;
+  float4 f[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) f[e] = co[cvl * 8 + e];
+  for (int64_t pb = p0 + pr; pb < p1; pb += 2 * rows) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int64_t p = pb + u * rows;
+      if (p < p1) {
+        V8 o;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          o.h[e] = f2bf(__fmaf_rn(f[e].x, bf2f(d0[u].h[e]), -f[e].y) - f[e].z * (bf2f(b0[u].h[e]) - f[e].w));
+        *reinterpret_cast<uint4*>(dz + p * B + ch0) = o.q;
+      }
+      const int64_t pn = min(p + 2 * rows, p1 - 1);
+      if (pb + 2 * rows < p1) {
+        d0[u].q = *reinterpret_cast<const uint4*>(dz + pn * B + ch0);
+        b0[u].q = *reinterpret_cast<const uint4*>(b + pn * B + ch0);
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------- 1x1 data gradient + BN1 backward
+
+struct Dgrad1Args {
+  const u16* db; int B;                 // gradient of b_l [P][B]
+  const u16* W; int C16, B32;           // packed weights [C16][B32]
+  const u16* x; int64_t x_ld;           // concatenated features
+  const u16* dy; float* G; int64_t g_ld;  // slab; dy replaces its first read (FIRST)
+  const float2* fold1; const float *mean, *istd;
+  float2* part1; int C;                 // out [T1][C]
+  int64_t P;
+  int ppw;                              // pixels per wave, a multiple of 32
+};
+
+// Output channels on M, pixels on N; bound by the slab's traffic (10 bytes per element against
+// 2*B flops).  A workgroup owns 32 channels (two M-tiles) whose weights stay in registers and a
+// range of pixels, of which each wave walks a quarter in steps of 32 (two N-tiles); a lane then
+// holds 4 consecutive channels of a pixel: the slab is read and written in 16-byte pieces, 128
+// contiguous bytes per pixel and wave.  Waves share nothing until the sums at the end.
+// KS = K-steps of 32 (0: more than eight, weights read in the loop).
+template <int KS, bool FIRST>
+__global__ __launch_bounds__(256) void k_dgrad1(Dgrad1Args A) {
+  __shared__ float red[4][32][2];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 15, g = lane >> 4;
+  const int c0 = blockIdx.x * 32;
+  const int64_t pw0 = ((int64_t)blockIdx.y * 4 + wave) * A.ppw;
+  const int64_t pw1 = min(A.P, pw0 + A.ppw);
+  constexpr int KR = KS > 0 ? KS : 1;
+  const int ksteps = A.B32 >> 5;
+  V8 w[2][KR];
+  const u16* wr[2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    wr[a] = A.W + (int64_t)min(c0 + a * 16 + j, A.C16 - 1) * A.B32 + 8 * g;
+    if (KS > 0) {
+#pragma unroll
+      for (int s = 0; s < KR; ++s) w[a][s].q = *reinterpret_cast<const uint4*>(wr[a] + 32 * s);
+    }
+  }
+  float sc[2][4], sf[2][4], mu[2][4], s0[2][4], s1[2][4];
+  int ch[2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    ch[a] = min(c0 + a * 16 + 4 * g, A.C - 4);  // C % 8 == 0: a lane's four channels are in or out together
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float2 f = A.fold1[ch[a] + r];
+      sc[a][r] = f.x; sf[a][r] = f.y; mu[a][r] = A.mean[ch[a] + r];
+      s0[a][r] = s1[a][r] = 0.f;
+    }
+  }
+  const bool cok[2] = {c0 + 4 * g < A.C, c0 + 16 + 4 * g < A.C};
+
+  for (int64_t pb = pw0; pb < pw1; pb += 32) {
+    int64_t p[2];
+    uint2 xr[2][2], dr[2][2];
+    float4 gr[2][2];
+    V8 d[2][KR];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      p[t] = min(pb + t * 16 + j, pw1 - 1);  // clamped: masked below
+      if (KS > 0) {
+#pragma unroll
+        for (int s = 0; s < KR; ++s)
+          d[t][s].q = *reinterpret_cast<const uint4*>(A.db + p[t] * A.B + min(32 * s + 8 * g, A.B - 8));
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        xr[t][a] = *reinterpret_cast<const uint2*>(A.x + p[t] * A.x_ld + ch[a]);
+        if (FIRST) dr[t][a] = *reinterpret_cast<const uint2*>(A.dy + p[t] * A.g_ld + ch[a]);
+        else gr[t][a] = *reinterpret_cast<const float4*>(A.G + p[t] * A.g_ld + ch[a]);
+      }
+    f32x4 acc[2][2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int a = 0; a < 2; ++a) acc[t][a] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    if (KS > 0) {
+#pragma unroll
+      for (int s = 0; s < KR; ++s)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int a = 0; a < 2; ++a) acc[t][a] = mfma_bf16(w[a][s], d[t][s], acc[t][a]);
+    } else {
+      for (int s = 0; s < ksteps; ++s) {
+        V8 ww[2], dd[2];
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          ww[a].q = *reinterpret_cast<const uint4*>(wr[a] + 32 * s);
+          dd[a].q = *reinterpret_cast<const uint4*>(A.db + p[a] * A.B + min(32 * s + 8 * g, A.B - 8));
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int a = 0; a < 2; ++a) acc[t][a] = mfma_bf16(ww[a], dd[t], acc[t][a]);
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        if (pb + t * 16 + j < pw1 && cok[a]) {
+          const float xf[4] = {bf2f((u16)xr[t][a].x), bf2f((u16)(xr[t][a].x >> 16)), bf2f((u16)xr[t][a].y),
+                               bf2f((u16)(xr[t][a].y >> 16))};
+          float gv[4];
+          if (FIRST) {
+            gv[0] = bf2f((u16)dr[t][a].x); gv[1] = bf2f((u16)(dr[t][a].x >> 16));
+            gv[2] = bf2f((u16)dr[t][a].y); gv[3] = bf2f((u16)(dr[t][a].y >> 16));
+          } else {
+            gv[0] = gr[t][a].x; gv[1] = gr[t][a].y; gv[2] = gr[t][a].z; gv[3] = gr[t][a].w;
+          }
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const float dz = __fmaf_rn(xf[r], sc[a][r], sf[a][r]) > 0.f ? acc[t][a][r] : 0.f;
+            gv[r] = __fmaf_rn(sc[a][r], dz, gv[r]);
+            s0[a][r] += dz;
+            s1[a][r] = __fmaf_rn(dz, xf[r] - mu[a][r], s1[a][r]);
+          }
+          *reinterpret_cast<float4*>(A.G + p[t] * A.g_ld + ch[a]) = make_float4(gv[0], gv[1], gv[2], gv[3]);
+        }
+      }
+  }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float u = s0[a][r], v = s1[a][r];
+#pragma unroll
+      for (int off = 1; off < 16; off <<= 1) { u += __shfl_xor(u, off, 64); v += __shfl_xor(v, off, 64); }
+      if (j == 0) { red[wave][a * 16 + 4 * g + r][0] = u; red[wave][a * 16 + 4 * g + r][1] = v; }
+    }
+  __syncthreads();
+  if (tid < 32 && c0 + tid < A.C) {
+    float u = 0.f, v = 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) { u += red[q][tid][0]; v += red[q][tid][1]; }
+    A.part1[(int64_t)blockIdx.y * A.C + c0 + tid] = make_float2(u, v * A.istd[c0 + tid]);
+  }
+}
+
+// ---------------------------------------------------------------- gradient of the block input
+
+// dx0 = bf16(G - K0 - K1*xhat) on the block input's channels, with the first layer's BN1 finalised
+// on the way (its input is exactly these channels).  grid (groups of 256 channels, pixel ranges).
+__global__ __launch_bounds__(256) void k_dx0(const float* __restrict__ G, int64_t g_ld, const u16* __restrict__ x,
+                                             int64_t x_ld, u16* __restrict__ dx0, int64_t P, int C, int ppb, float inv_p,
+                                             const float2* __restrict__ K, const float2* __restrict__ part, int T,
+                                             const float2* __restrict__ fold1, const float* __restrict__ mean,
+                                             const float* __restrict__ istd, float* __restrict__ dgamma,
+                                             float* __restrict__ dbeta) {
+  __shared__ float co[3][256];
+  const int cb = blockIdx.x * 256;
+  {
+    const int ch = cb + threadIdx.x, cc = min(ch, C - 1);
+    float2 s = make_float2(0.f, 0.f);
+    int t = 0;
+    for (; t + 8 <= T; t += 8) {
+      float2 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(t + u) * C + cc];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) { s.x += v[u].x; s.y += v[u].y; }
+    }
+    for (; t < T; ++t) { const float2 v = part[(int64_t)t * C + cc]; s.x += v.x; s.y += v.y; }
+    const float sc = fold1[cc].x * inv_p;
+    const float2 o = K ? K[cc] : make_float2(0.f, 0.f);
+    co[0][threadIdx.x] = __fmaf_rn(sc, s.x, o.x);
+    co[1][threadIdx.x] = __fmaf_rn(sc, s.y, o.y) * istd[cc];
+    co[2][threadIdx.x] = mean[cc];
+    if (blockIdx.y == 0 && ch < C) { dbeta[ch] = s.x; dgamma[ch] = s.y; }
+  }
+  __syncthreads();
+  const int cvl = threadIdx.x & 31, pr = threadIdx.x >> 5, ch0 = cb + cvl * 8;
+  if (ch0 >= C) return;
+  float a[8], b[8], mu[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) { a[e] = co[0][cvl * 8 + e]; b[e] = co[1][cvl * 8 + e]; mu[e] = co[2][cvl * 8 + e]; }
+  const int64_t p0 = (int64_t)blockIdx.y * ppb, p1 = min(P, p0 + ppb);
+  for (int64_t pb = p0 + pr; pb < p1; pb += 32) {
+    V8 xv[4];
+    float4 ga[4], gb[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t p = min(pb + 8 * u, p1 - 1);
+      xv[u].q = *reinterpret_cast<const uint4*>(x + p * x_ld + ch0);
+      ga[u] = *reinterpret_cast<const float4*>(G + p * g_ld + ch0);
+      gb[u] = *reinterpret_cast<const float4*>(G + p * g_ld + ch0 + 4);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t p = pb + 8 * u;
+      if (p < p1) {
+        const float gf[8] = {ga[u].x, ga[u].y, ga[u].z, ga[u].w, gb[u].x, gb[u].y, gb[u].z, gb[u].w};
+        V8 o;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o.h[e] = f2bf(gf[e] - a[e] - b[e] * (bf2f(xv[u].h[e]) - mu[e]));
+        *reinterpret_cast<uint4*>(dx0 + p * C + ch0) = o.q;
+      }
+    }
+  }
+}
+
+// Tile plan of k_dgrad3.  NT: the largest tile (64*NT pixels of one image: less halo per pixel)
+// that leaves at most 15 % of its pixels unused, else the one that leaves the fewest, within 64 KB
+// of LDS.  MT: two M-tiles per workgroup where that still gives one workgroup per CU (each M group
+// stages the tile again; four need more than 256 registers).  T2: workgroups per M group; one per
+// tile up to 256, beyond that each takes several.
+struct Dgrad3Plan {
+  int NT, MT, tpi, tiles, gy, T2;
+  size_t lds;
+};
+Dgrad3Plan plan_dgrad3(int n, int h, int w, int k, int B) {
+  Dgrad3Plan p{};
+  const int hw = h * w, mtiles = (B + 15) / 16;
+  int best = 0;
+  for (int nt : {4, 2, 1}) {
+    const size_t lds = (size_t)(64 * nt + 2 * (w + 1)) * 72 * sizeof(u16) + (size_t)3 * k * sizeof(float);
+    if (lds > 60 * 1024 && nt > 1) continue;
+    const int used = (hw + 64 * nt - 1) / (64 * nt) * 64 * nt;
+    if (best == 0 || used < best) { best = used; p.NT = nt; p.lds = lds; }
+    if (used * 100 <= 115 * hw) break;
+  }
+  p.tpi = (hw + 64 * p.NT - 1) / (64 * p.NT);
+  p.tiles = n * p.tpi;
+  p.MT = mtiles >= 2 && (int64_t)p.tiles * ((mtiles + 1) / 2) >= 256 ? 2 : 1;
+  p.gy = (mtiles + p.MT - 1) / p.MT;
+  const int per = (p.tiles + 255) / 256;
+  p.T2 = (p.tiles + per - 1) / per;
+  return p;
+}
+
+}  // namespace
+
+// Partials of k_dgrad1: workgroups along the pixels, so that about 1024 workgroups (four per CU)
+// cover the slab; each wave takes at least one step of 32 pixels.
+static int dgrad1_splits(int64_t P, int C, int* ppw) {
+  const int64_t cols = (C + 31) / 32;
+  int64_t t = 1024 / cols;
+  if (t > 256) t = 256;
+  if (t > (P + 127) / 128) t = (P + 127) / 128;
+  if (t < 1) t = 1;
+  const int64_t px = ((P + 4 * t - 1) / (4 * t) + 31) / 32 * 32;
+  *ppw = (int)px;
+  return (int)((P + 4 * px - 1) / (4 * px));
+}
+
+size_t bwd_partial1_floats(int64_t P, int C) {
+  int ppw;
+  return (size_t)2 * C * dgrad1_splits(P, C, &ppw);
+}
+size_t bwd_partial2_floats(int n, int h, int w, int k, int B) {
+  return (size_t)2 * B * (plan_dgrad3(n, h, w, k, B).T2 + 1);
+}
+
+hipError_t bwd_dgrad3(const BwdLayer& L, hipStream_t st) {
+  const Dgrad3Plan p = plan_dgrad3(L.n, L.h, L.w, L.k, L.B);
+  const int64_t P = (int64_t)L.n * L.h * L.w;
+  Dgrad3Args A{};
+  A.dy = L.last ? (const u16*)L.dy + L.c : nullptr;
+  A.G = L.G + L.c; A.g_ld = L.ld;
+  A.x = (const u16*)L.y + L.c; A.x_ld = L.ld;
+  A.k = L.k;
+  A.mean = L.mean_y + L.c; A.istd = L.istd_y + L.c;
+  A.inv_p = 1.0f / (float)P;
+  A.gl = (u16*)L.gl;
+  A.M16 = (L.B + 15) & ~15; A.K32 = (L.k + 31) & ~31;
+  A.W = (const u16*)L.pk3t;
+  A.b = (const u16*)L.b; A.fold2 = L.fold2; A.mean_b = L.mean_b; A.istd_b = L.istd_b; A.B = L.B;
+  A.dz = (u16*)L.db;
+  A.part2 = (float2*)L.part2; A.T2 = p.T2;
+  A.H = L.h; A.Wd = L.w; A.tpi = p.tpi; A.tiles = p.tiles; A.gy = p.gy;
+  int fin = 0;
+  if (!L.last) {  // the layer above: C1 = c + k input channels
+    int ppw;
+    A.C1 = L.c + L.k; A.c1 = L.c;
+    A.T1 = dgrad1_splits(P, A.C1, &ppw);
+    A.part1 = (const float2*)L.part1;
+    A.K = L.above_first ? nullptr : L.K + L.c;
+    A.Kall = L.K; A.first = L.above_first; A.Ckeep = L.c;
+    A.fold1all = L.above_fold1; A.fold1 = L.above_fold1 + L.c;
+    A.dgamma = L.above_dgamma; A.dbeta = L.above_dbeta;
+    fin = (A.C1 + 63) / 64;
+  }
+  const dim3 grid((unsigned)(p.T2 * p.gy + fin));
+#define DNB_D3(NT, MT) hipLaunchKernelGGL((k_dgrad3<NT, MT>), grid, dim3(256), p.lds, st, A)
+#define DNB_D3M(NT)                                   \
+  do {                                                \
+    if (p.MT == 2) DNB_D3(NT, 2); else DNB_D3(NT, 1); \
+  } while (0)
+  if (p.NT == 4) DNB_D3M(4); else if (p.NT == 2) DNB_D3M(2); else DNB_D3M(1);
+#undef DNB_D3M
+#undef DNB_D3
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  // BN2's element-wise pass.  Up to 64 partials per channel are added by its own workgroups; more
+  // (large images, where a launch weighs little) are first brought down to one.
+  const float2* part = (const float2*)L.part2;
+  int T = p.T2;
+  if (T > 64) {
+    float2* one = (float2*)L.part2 + (int64_t)T * L.B;
+    hipLaunchKernelGGL(k_sum_pairs, dim3((unsigned)((L.B + 63) / 64)), dim3(256), 0, st, part, T, L.B, one);
+    part = one;
+    T = 1;
+  }
+  const int cv = L.B / 8;
+  int lsh = 5;
+  for (int s = 4; s >= 2; --s)
+    if (((cv + (1 << s) - 1) >> s << s) < ((cv + (1 << lsh) - 1) >> lsh << lsh)) lsh = s;
+  const int rows = 256 >> lsh;
+  int64_t ppb = (int64_t)rows * 2;
+  while ((P + ppb - 1) / ppb > 2048) ppb *= 2;
+  const dim3 ga((unsigned)((P + ppb - 1) / ppb), (unsigned)((cv + (1 << lsh) - 1) >> lsh));
+  hipLaunchKernelGGL(k_bn2_apply, ga, dim3(256), 0, st, (u16*)L.db, (const u16*)L.b, P, L.B, (int)ppb, lsh, A.inv_p,
+                     L.fold2, L.mean_b, L.istd_b, part, T, L.dgamma2, L.dbeta2);
+  return hipGetLastError();
+}
+
+hipError_t bwd_dgrad1(const BwdLayer& L, hipStream_t st) {
+  const int64_t P = (int64_t)L.n * L.h * L.w;
+  Dgrad1Args A{};
+  A.db = (const u16*)L.db; A.B = L.B;
+  A.W = (const u16*)L.pk1t; A.C16 = (L.c + 15) & ~15; A.B32 = (L.B + 31) & ~31;
+  A.x = (const u16*)L.x; A.x_ld = L.x_ld;
+  A.dy = (const u16*)L.dy; A.G = L.G; A.g_ld = L.ld;
+  A.fold1 = L.fold1; A.mean = L.mean_y; A.istd = L.istd_y;
+  A.part1 = (float2*)L.part1; A.C = L.c; A.P = P;
+  const int T = dgrad1_splits(P, L.c, &A.ppw);
+  const dim3 grid((unsigned)((L.c + 31) / 32), (unsigned)T);
+#define DNB_D1(KS)                                                                          \
+  do {                                                                                      \
+    if (L.last) hipLaunchKernelGGL((k_dgrad1<KS, true>), grid, dim3(256), 0, st, A);        \
+    else hipLaunchKernelGGL((k_dgrad1<KS, false>), grid, dim3(256), 0, st, A);              \
+  } while (0)
+  switch (A.B32 >> 5) {
+    case 1: DNB_D1(1); break;
+    case 2: DNB_D1(2); break;
+    case 3: DNB_D1(3); break;
+    case 4: DNB_D1(4); break;
+    case 5: DNB_D1(5); break;
+    case 6: DNB_D1(6); break;
+    case 7: DNB_D1(7); break;
+    case 8: DNB_D1(8); break;
+    default: DNB_D1(0); break;
+  }
+#undef DNB_D1
+  return hipGetLastError();
+}
+
+hipError_t bwd_dx0(const BwdLayer& L, void* dx0, hipStream_t st) {
+  const int64_t P = (int64_t)L.n * L.h * L.w;
+  int ppw;
+  const int T = dgrad1_splits(P, L.c, &ppw);
+  int64_t ppb = 64;
+  while ((P + ppb - 1) / ppb * ((L.c + 255) / 256) > 2048) ppb *= 2;
+  hipLaunchKernelGGL(k_dx0, dim3((unsigned)((L.c + 255) / 256), (unsigned)((P + ppb - 1) / ppb)), dim3(256), 0, st, L.G, L.ld,
+                     (const u16*)L.y, L.ld, (u16*)dx0, P, L.c, (int)ppb, 1.0f / (float)P, L.last ? nullptr : L.K,
+                     (const float2*)L.part1, T, L.fold1, L.mean_y, L.istd_y, L.dgamma1, L.dbeta1);
+  return hipGetLastError();
+}
+
+}  // namespace nhwc
+}  // namespace dnb

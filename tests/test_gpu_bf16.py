@@ -428,3 +428,17 @@ def test_nhwc_bn_relu_backward(dnb, oracle, shape, accumulate):
     assert_close(got, odu, 1e-2, "du")
     assert_close(dg.cpu().numpy(), odg, 1e-2, "dgamma")
     assert_close(db.cpu().numpy(), odb, 1e-2, "dbeta")
+
+
+# the backward chain's own edges: k above one 64-channel staging pass with B above eight K-steps of 32 and not a
+# multiple of 32; more tiles than BN2 partials are added in place; more tiles than workgroups; a single short wave
+CHAIN_CFGS = [wl.BlockCfg(2, 16, 3, 5, 3, 72, 296), wl.BlockCfg(70, 8, 4, 4, 3, 8, 32), wl.BlockCfg(300, 8, 2, 2, 2, 8, 24),
+              wl.BlockCfg(1, 24, 9, 17, 2, 24, 40), wl.BlockCfg(2, 8, 7, 3, 1, 48, 192)]
+
+
+@pytest.mark.parametrize("cfg", CHAIN_CFGS, ids=[f"n{c.n}c{c.c0}h{c.h}w{c.w}m{c.layers}k{c.growth}B{c.bottleneck}" for c in CHAIN_CFGS])
+def test_bf16_backward_chain_edges_match_oracle(dnb, oracle, cfg):
+    """Tolerances and decisions as above.  These blocks are small and shallow: the storage format's own
+    share stays below the 2e-2 that the others are held to."""
+    x0, lp, dy = wl.make_block_inputs(cfg, affine="random")
+    check_bf16_block(dnb, oracle, cfg, to_bf16_values(x0), lp, to_bf16_values(dy))
