@@ -251,6 +251,7 @@ int backward_bf16(dnb_block* b, const void* yv, const void* dy, void* dx0, float
   L.part1 = (float*)(ws + b->off_part);
   L.part2 = L.part1 + b->part1_floats;
   L.K = (float2*)(ws + b->off_K);
+  nhwc::WgradSum sum1{}, sum3{};
   for (int l = m; l >= 1; --l) {
     const int c = c_in(d, l);
     const LayerGrads gp = layer_ptrs<LayerGrads, float>(b, dparams, l);
@@ -279,11 +280,15 @@ int backward_bf16(dnb_block* b, const void* yv, const void* dy, void* dx0, float
     }
     DNB_TRY(nhwc::bwd_dgrad1(L, st));
     const void* gl = l == m ? (const void*)((const unsigned short*)dy + c) : L.gl;
-    DNB_TRY(nhwc::wgrad(fused ? L.b : S3, B, gl, l == m ? cout : k, false, partA, gp.W3, n, B, k, d.h, d.w, 9,
-                        fused ? L.fold2 : nullptr, st));
-    DNB_TRY(nhwc::wgrad(fused ? (const void*)y : S2, fused ? cout : c, L.db, B, false, partB, gp.W1, n, c, B, d.h, d.w, 1,
-                        fused ? L.fold1 : nullptr, st));
+    // both weight gradients, and the sums of layer l+1's (partial buffers used alternately)
+    const nhwc::WgradIn w3{fused ? L.b : S3, B, gl, l == m ? cout : k, partA + (l & 1) * b->partA_floats, gp.W3, B, k,
+                           fused ? L.fold2 : nullptr};
+    const nhwc::WgradIn w1{fused ? (const void*)y : S2, fused ? cout : c, L.db, B, partB + (l & 1) * b->partB_floats, gp.W1, c,
+                           B, fused ? L.fold1 : nullptr};
+    if (!nhwc::wgrad_pair(w1, w3, n, d.h, d.w, &sum1, &sum3, st)) return DNB_E_UNSUPPORTED;
+    DNB_TRY(hipGetLastError());
   }
+  DNB_TRY(nhwc::wgrad_finish(&sum1, &sum3, st));
   DNB_TRY(nhwc::bwd_dx0(L, dx0, st));
   return DNB_OK;
 }
@@ -540,15 +545,14 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
     }
   }
   const size_t kf = bf16 ? (size_t)cout * 2 : 0;
-  mem.scratch_bytes = (uint64_t)(part + (bf16 ? 1 : 2) * (partA + partB) + pack + kf) * sizeof(float);
+  mem.scratch_bytes = (uint64_t)(part + 2 * (partA + partB) + pack + kf) * sizeof(float);
   b->off_part = carve(part * sizeof(float), false);
-  // fp32: two buffers each, used alternately by consecutive layers (a layer's partials are
+  // two buffers each, used alternately by consecutive layers (a layer's partials are
   // summed by extra workgroups of the next layer's weight-gradient launch)
   b->partA_floats = partA;
   b->partB_floats = partB;
-  const size_t nbuf = bf16 ? 1 : 2;
-  b->off_partA = carve(nbuf * partA * sizeof(float), false);
-  b->off_partB = carve(nbuf * partB * sizeof(float), false);
+  b->off_partA = carve(2 * partA * sizeof(float), false);
+  b->off_partB = carve(2 * partB * sizeof(float), false);
   b->off_pack = carve(pack * sizeof(float), false);
   b->off_K = carve(kf * sizeof(float), false);
   // measured on MI355X: with the weight gradients on helper streams the fp32 step is slower (idle

@@ -192,6 +192,29 @@ size_t conv_stats_partial_floats(int n, int cout, int h, int w);
 hipError_t conv(const void* in, int64_t in_ld, bool in_f32, const void* Wp, void* out, int64_t out_ld, int n,
                 int cin, int cout, int h, int w, int taps, const float2* fold, float* spart, int* sT,
                 hipStream_t st);
+// One weight gradient: dw[m][c][t] = sum_p g[p][m] * act(a[p + shift(t)][c]), fold = BN+ReLU of a (or null).
+struct WgradIn {
+  const void* a; int64_t a_ld;
+  const void* g; int64_t g_ld;
+  float *part, *dw;
+  int cin, cout;
+  const float2* fold;
+};
+// The sum of a launch's partials, left for a later launch on the same stream (taps 0: nothing pending).
+struct WgradSum {
+  const float* part;
+  float* out;
+  int taps, S, gy, gz, mt, cin, cout;
+};
+// (dnb_nhwc_wgrad.hip) Partial floats of the kernels there, 0 if they do not take the shape.
+size_t wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps);
+// Launches the partials and describes their sum in *own; false (nothing launched) if the shape is not taken.
+bool wgrad_fast(const WgradIn& in, bool g_f32, int n, int h, int w, int taps, WgradSum* own, hipStream_t st);
+// A layer's 1x1 and 3x3 weight gradients in one launch (bf16 gradient operands).  *s1 / *s3: in, the sums
+// pending from the layer before (of other partial buffers), carried out in this launch; out, this layer's.
+bool wgrad_pair(const WgradIn& w1, const WgradIn& w3, int n, int h, int w, WgradSum* s1, WgradSum* s3, hipStream_t st);
+// Carries out what is pending (either may be null).
+hipError_t wgrad_finish(WgradSum* s1, WgradSum* s3, hipStream_t st);
 size_t wgrad_partial_floats(int n, int cin, int cout, int h, int w, int taps);
 // writes per-split partials to `part` and their sum to dw ([cout][cin][taps])
 hipError_t wgrad(const void* a, int64_t a_ld, const void* g, int64_t g_ld, bool g_f32, float* part, float* dw, int n,

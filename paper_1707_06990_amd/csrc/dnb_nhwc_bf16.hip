@@ -546,428 +546,6 @@ __global__ __launch_bounds__(256) void k_wgrad(
     }
 }
 
-// 3x3 weight gradient with the activation tile staged once.  A tile is R image rows of one image;
-// aT[c][row][x] holds rows r0-1 .. r0+R of the (prologue-applied) activations, pixel-contiguous
-// per channel with 8 zero pixels on either side of each row, so a tap is the same tile read at a
-// shifted position: the centre column is one aligned 16-byte read, the left and right columns
-// are that read funnel-shifted by one element with the neighbouring dword.  gT[m][row][x] holds
-// the gradient tile.  A K-step is four 8-pixel row fragments (one per lane group).  Rows of both
-// arrays are permuted (channel 8v+e sits in row v+8e) so that the staging stores of one wave
-// spread over all banks.  Everything the staging loops do not write stays zero from the initial
-// fill: the row margins, fragments past the tile, channels past cin / cout.
-constexpr int WG3_AP = 328, WG3_GP = 136;  // row pitches, both = 8 (mod 64) elements
-constexpr int WG3_ROWPIX = 320;            // (R+2) * (8*FR+16) must fit in this
-constexpr int WG3_BLOCK = 64 * 64 * 9;     // partial floats per (split, c group, m group)
-struct Wg3Geom {
-  bool ok;
-  int R, FR, tpi;
-};
-static Wg3Geom wg3_geom(int h, int w) {
-  Wg3Geom q{};
-  q.FR = (w + 7) / 8;
-  const int XP = q.FR * 8 + 16;
-  if (3 * XP > WG3_ROWPIX) return q;
-  int R = WG3_ROWPIX / XP - 2;
-  if (R > 16 / q.FR) R = 16 / q.FR;
-  if (R > h) R = h;
-  q.R = R;
-  q.tpi = (h + R - 1) / R;
-  q.ok = true;
-  return q;
-}
-
-template <typename TG, bool PRO>
-__global__ __launch_bounds__(512) void k_wgrad3(
-    const u16* __restrict__ a, int64_t a_ld, const TG* __restrict__ gout, int64_t g_ld,
-    float* __restrict__ part, int cin, int cout, int n, int H, int W, int R, int FR, int tiles_per_img,
-    int tiles_per_split, const float2* __restrict__ fold) {
-  constexpr int AP = WG3_AP, GP = WG3_GP;
-  __shared__ __attribute__((aligned(16))) u16 aT[64 * AP];
-  __shared__ __attribute__((aligned(16))) u16 gT[64 * GP];
-  const int RW = FR * 8, XP = RW + 16, F = R * FR, KS = (F + 3) >> 2;
-  // eight waves: wave & 3 = m-tile of the group, wave >> 2 = which pair of the four c-tiles
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, mw = wave & 3, yh = wave >> 2;
-  const int j = lane & 15, g = lane >> 4, v = tid & 7;
-  const int c0 = blockIdx.y * 64, m0 = blockIdx.z * 64;
-  const int total_tiles = n * tiles_per_img;
-  const int t_begin = blockIdx.x * tiles_per_split, t_end = min(total_tiles, t_begin + tiles_per_split);
-
-  for (int i = tid; i < 64 * AP / 8; i += 512) reinterpret_cast<uint4*>(aT)[i] = make_uint4(0u, 0u, 0u, 0u);
-  for (int i = tid; i < 64 * GP / 8; i += 512) reinterpret_cast<uint4*>(gT)[i] = make_uint4(0u, 0u, 0u, 0u);
-
-  const int chv = c0 + 8 * v, mv = m0 + 8 * v;
-  const bool ch_ok = chv < cin, m_ok = mv < cout;  // cin % 8 == 0, cout % 8 == 0
-  const int chl = ch_ok ? chv : 0, ml = m_ok ? mv : 0;  // load addresses stay inside the tensors
-  float fs[8], fb[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    fs[e] = 0.f;
-    fb[e] = 0.f;
-    if (PRO) {
-      const float2 fl = fold[chl + e];
-      fs[e] = fl.x;
-      fb[e] = fl.y;
-    }
-  }
-  int boff[4];  // per K-step: offset of this lane group's fragment inside an aT row block
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const int f = 4 * s + g, fv = f < F ? f : 0;  // fragments past the tile meet zeros in gT
-    const int r = fv / FR;
-    boff[s] = r * XP + (fv - r * FR) * 8;
-  }
-
-  f32x4 acc[9][2];
-#pragma unroll
-  for (int t = 0; t < 9; ++t)
-#pragma unroll
-    for (int y = 0; y < 2; ++y) acc[t][y] = (f32x4){0.f, 0.f, 0.f, 0.f};
-
-  // Software pipeline: the global loads of tile i+1 are issued before the MFMA phase of tile i
-  // and deposited (prologue, bf16 rounding, transposing 2-byte stores) after it.  Every load is
-  // unconditional at a clamped in-range address, so none of them waits for another; what lies
-  // outside the image or the tile is replaced by zero when it is deposited.
-  const int na = (R + 2) * RW * 8, ng = R * RW * 8;  // at most 5 and 2 vectors per thread
-  uint4 ra[5], rg[2];  // kept as whole vectors across the MFMA phase; taken apart only in deposit
-  float4 rgl[2], rgh[2];
-  auto issue = [&](int tile) {
-    const int img = tile / tiles_per_img, r0 = (tile - img * tiles_per_img) * R;
-    const u16* ab = a + (int64_t)img * H * W * a_ld + chl;
-    const TG* gb = gout + (int64_t)img * H * W * g_ld + ml;
-#pragma unroll
-    for (int u = 0; u < 5; ++u) {
-      const int pos = (tid + 512 * u) >> 3;
-      const int rr = pos / RW, x = min(pos - rr * RW, W - 1), ir = min(max(r0 - 1 + rr, 0), H - 1);
-      ra[u] = *reinterpret_cast<const uint4*>(ab + ((int64_t)ir * W + x) * a_ld);
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int pos = (tid + 512 * u) >> 3;
-      const int r = pos / RW, x = min(pos - r * RW, W - 1), ir = min(r0 + r, H - 1);
-      const int64_t q = (int64_t)ir * W + x;
-      if (sizeof(TG) == 2) {
-        rg[u] = *reinterpret_cast<const uint4*>(reinterpret_cast<const u16*>(gb) + q * g_ld);
-      } else {
-        const float* pf = reinterpret_cast<const float*>(gb) + q * g_ld;
-        rgl[u] = *reinterpret_cast<const float4*>(pf);
-        rgh[u] = *reinterpret_cast<const float4*>(pf + 4);
-      }
-    }
-  };
-  auto deposit = [&](int tile) {
-    const int img = tile / tiles_per_img, r0 = (tile - img * tiles_per_img) * R;
-#pragma unroll
-    for (int u = 0; u < 5; ++u) {
-      const int idx = tid + 512 * u, pos = idx >> 3;
-      const int rr = pos / RW, x = pos - rr * RW, ir = r0 - 1 + rr;
-      if (ch_ok && idx < na) {
-        const bool in = ir >= 0 && ir < H && x < W;
-        const int dst = rr * XP + 8 + x;
-        V8 t;
-        t.q = ra[u];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          u16 hv = t.h[e];
-          if (PRO) hv = f2bf(fmaxf(__fmaf_rn(bf2f(hv), fs[e], fb[e]), 0.f));
-          aT[(v + 8 * e) * AP + dst] = in ? hv : (u16)0;
-        }
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int idx = tid + 512 * u, pos = idx >> 3;
-      const int r = pos / RW, x = pos - r * RW, ir = r0 + r;
-      if (m_ok && idx < ng) {
-        const bool in = ir < H && x < W;
-        V8 t;
-        if (sizeof(TG) == 2) {
-          t.q = rg[u];
-        } else {
-          t.h[0] = f2bf(rgl[u].x); t.h[1] = f2bf(rgl[u].y); t.h[2] = f2bf(rgl[u].z); t.h[3] = f2bf(rgl[u].w);
-          t.h[4] = f2bf(rgh[u].x); t.h[5] = f2bf(rgh[u].y); t.h[6] = f2bf(rgh[u].z); t.h[7] = f2bf(rgh[u].w);
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) gT[(v + 8 * e) * GP + pos] = in ? t.h[e] : (u16)0;
-      }
-    }
-  };
-
-  if (t_begin < t_end) issue(t_begin);
-  for (int tile = t_begin; tile < t_end; ++tile) {
-    __syncthreads();  // the previous tile's fragment reads (first pass: the zero fill) are done
-    deposit(tile);
-    __syncthreads();
-    if (tile + 1 < t_end) issue(tile + 1);
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      if (s < KS) {
-        V8 af;
-        af.q = *reinterpret_cast<const uint4*>(&gT[(mw * 16 + j) * GP + (4 * s + g) * 8]);
-        const int lb = (yh * 32 + j) * AP + boff[s] + 8;
-        uint4 cq[6];
-        unsigned pv[6], nx[6];
-#pragma unroll
-        for (int i = 0; i < 6; ++i) {  // i = c-tile of the pair * 3 + image row offset + 1
-          const int base = lb + (i / 3) * 16 * AP + (i % 3) * XP;
-          cq[i] = *reinterpret_cast<const uint4*>(&aT[base]);
-          pv[i] = *reinterpret_cast<const unsigned*>(&aT[base - 2]);
-          nx[i] = *reinterpret_cast<const unsigned*>(&aT[base + 8]);
-        }
-#pragma unroll
-        for (int i = 0; i < 6; ++i) {
-          const int y = i / 3, d = i % 3;
-          V8 cur, lf, rf;
-          cur.q = cq[i];
-          const unsigned s0 = __builtin_amdgcn_alignbit(cur.q.y, cur.q.x, 16);
-          const unsigned s1 = __builtin_amdgcn_alignbit(cur.q.z, cur.q.y, 16);
-          const unsigned s2 = __builtin_amdgcn_alignbit(cur.q.w, cur.q.z, 16);
-          lf.q = make_uint4(__builtin_amdgcn_alignbit(cur.q.x, pv[i], 16), s0, s1, s2);
-          rf.q = make_uint4(s0, s1, s2, __builtin_amdgcn_alignbit(nx[i], cur.q.w, 16));
-          acc[d * 3 + 0][y] = mfma_bf16(af, lf, acc[d * 3 + 0][y]);
-          acc[d * 3 + 1][y] = mfma_bf16(af, cur, acc[d * 3 + 1][y]);
-          acc[d * 3 + 2][y] = mfma_bf16(af, rf, acc[d * 3 + 2][y]);
-        }
-      }
-    }
-  }
-
-  // partials in accumulator order: [split][c group][m group][wave][tap][c-tile of the pair][lane][4]
-  float* pb = part + (((int64_t)blockIdx.x * gridDim.y + blockIdx.y) * gridDim.z + blockIdx.z) * WG3_BLOCK +
-              (int64_t)wave * 18 * 256 + lane * 4;
-#pragma unroll
-  for (int t9 = 0; t9 < 9; ++t9)
-#pragma unroll
-    for (int y = 0; y < 2; ++y)
-      *reinterpret_cast<float4*>(pb + (t9 * 2 + y) * 256) = make_float4(acc[t9][y][0], acc[t9][y][1], acc[t9][y][2], acc[t9][y][3]);
-}
-
-// Sums the splits of k_wgrad3's partials and writes dW[m][c][tap].  A workgroup covers 64
-// accumulator quads; its four 64-thread groups each sum every fourth split (loads batched four
-// deep), and the four results are added in group order.
-__global__ __launch_bounds__(256) void k_sum_wgrad3(const float* __restrict__ part, int S, int gy, int gz, int cin,
-                                                    int cout, float* __restrict__ dw) {
-  __shared__ float4 red[3][64];
-  const int64_t per_split = (int64_t)gy * gz * WG3_BLOCK;
-  const int t = threadIdx.x & 63, sg = threadIdx.x >> 6;
-  const int64_t i = ((int64_t)blockIdx.x * 64 + t) * 4;  // per_split is a multiple of 256
-  float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
-  const float* p = part + i;
-  int s = sg;
-  for (; s + 12 < S; s += 16) {
-    const float4 a0 = *reinterpret_cast<const float4*>(p + (int64_t)s * per_split);
-    const float4 a1 = *reinterpret_cast<const float4*>(p + (int64_t)(s + 4) * per_split);
-    const float4 a2 = *reinterpret_cast<const float4*>(p + (int64_t)(s + 8) * per_split);
-    const float4 a3 = *reinterpret_cast<const float4*>(p + (int64_t)(s + 12) * per_split);
-    sum.x += a0.x; sum.y += a0.y; sum.z += a0.z; sum.w += a0.w;
-    sum.x += a1.x; sum.y += a1.y; sum.z += a1.z; sum.w += a1.w;
-    sum.x += a2.x; sum.y += a2.y; sum.z += a2.z; sum.w += a2.w;
-    sum.x += a3.x; sum.y += a3.y; sum.z += a3.z; sum.w += a3.w;
-  }
-  for (; s < S; s += 4) {
-    const float4 a0 = *reinterpret_cast<const float4*>(p + (int64_t)s * per_split);
-    sum.x += a0.x; sum.y += a0.y; sum.z += a0.z; sum.w += a0.w;
-  }
-  if (sg > 0) red[sg - 1][t] = sum;
-  __syncthreads();
-  if (sg > 0) return;
-#pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    const float4 o = red[q][t];
-    sum.x += o.x; sum.y += o.y; sum.z += o.z; sum.w += o.w;
-  }
-  const int blk = (int)(i / WG3_BLOCK), rem = (int)(i - (int64_t)blk * WG3_BLOCK);
-  const int by = blk / gz, bz = blk - by * gz;
-  const int lane = (rem >> 2) & 63, ty = rem >> 8;  // ty = (wave*9 + tap)*2 + c-tile of the pair
-  const int wave = ty / 18, t9 = (ty - wave * 18) >> 1, y = 2 * (wave >> 2) + (ty & 1);
-  const int j = lane & 15, g = lane >> 4;
-  const int rc = y * 16 + j, c = by * 64 + 8 * (rc & 7) + (rc >> 3);
-  if (c >= cin) return;
-  const float o4[4] = {sum.x, sum.y, sum.z, sum.w};
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int rm = (wave & 3) * 16 + 4 * g + r, m = bz * 64 + 8 * (rm & 7) + (rm >> 3);
-    if (m < cout) dw[((int64_t)m * cin + c) * 9 + t9] = o4[r];
-  }
-}
-
-// 1x1 weight gradient, bf16 gradient operand.  A workgroup (eight waves) owns up to 256 input
-// channels and up to 192 output channels, so the activations are read once when cout <= 192 and
-// the gradient once per 256 input channels.  A tile is 32 pixels of the flattened pixel axis (one
-// K-step); both operands are staged transposed, rows permuted inside each block of 64 channels
-// (channel 8v+e in row v+8e) so that the 2-byte staging stores of a wave spread over all banks.
-// Wave (mh, cq) accumulates m-tiles mh, mh+2, .. and c-tiles cq, cq+4, ...  The next tile's loads
-// are issued, unconditionally at clamped addresses, before the MFMA phase.
-constexpr int WG1_PT = 40, WG1_CG = 256, WG1_MG = 192, WG1_BLOCK = WG1_CG * WG1_MG;
-
-template <bool PRO>
-__global__ __launch_bounds__(512) void k_wgrad1(
-    const u16* __restrict__ a, int64_t a_ld, const u16* __restrict__ gout, int64_t g_ld,
-    float* __restrict__ part, int cin, int cout, int64_t P, int tiles_per_split, const float2* __restrict__ fold) {
-  constexpr int PT = WG1_PT;
-  __shared__ __attribute__((aligned(16))) u16 aT[WG1_CG * PT];
-  __shared__ __attribute__((aligned(16))) u16 gT[WG1_MG * PT];
-  __shared__ __attribute__((aligned(16))) float2 fl[WG1_CG];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, mh = wave & 1, cq = wave >> 1;
-  const int j = lane & 15, g = lane >> 4, v = lane & 7, pl = lane >> 3;
-  const int c0 = blockIdx.y * WG1_CG, m0 = blockIdx.z * WG1_MG;
-  const int64_t tiles = (P + 31) / 32;
-  const int64_t t_begin = (int64_t)blockIdx.x * tiles_per_split;
-  const int64_t t_end = min(tiles, t_begin + tiles_per_split);
-  if (PRO) {
-    for (int i = tid; i < WG1_CG; i += 512) fl[i] = c0 + i < cin ? fold[c0 + i] : make_float2(0.f, 0.f);
-  }
-
-  // staging units of 64 lanes = (8 pixels) x (8 channel vectors): 16 for the activations, 12 for
-  // the gradient; wave w takes units w and w + 8
-  int a_row[2], a_px[2], g_row[2], g_px[2];
-  bool a_ok[2], g_ok[2], g_unit[2];
-  const u16* a_src[2];
-  const u16* g_src[2];
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int unit = wave + 8 * u, blk = unit >> 2, pg = unit & 3;
-    const int ch = c0 + blk * 64 + 8 * v, m = m0 + blk * 64 + 8 * v;
-    a_ok[u] = ch < cin;  // cin % 8 == 0, cout % 8 == 0
-    a_row[u] = blk * 64 + v;
-    a_px[u] = pg * 8 + pl;
-    a_src[u] = a + (a_ok[u] ? ch : 0);
-    g_unit[u] = unit < 12;
-    g_ok[u] = g_unit[u] && m < cout;
-    g_row[u] = blk * 64 + v;
-    g_px[u] = pg * 8 + pl;
-    g_src[u] = gout + (g_ok[u] ? m : 0);
-  }
-
-  f32x4 acc[6][4];
-#pragma unroll
-  for (int i = 0; i < 6; ++i)
-#pragma unroll
-    for (int k = 0; k < 4; ++k) acc[i][k] = (f32x4){0.f, 0.f, 0.f, 0.f};
-
-  uint4 ra[2], rg[2];
-  auto issue = [&](int64_t tile) {
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int64_t pa = min(tile * 32 + a_px[u], P - 1), pg = min(tile * 32 + g_px[u], P - 1);
-      ra[u] = *reinterpret_cast<const uint4*>(a_src[u] + pa * a_ld);
-      rg[u] = *reinterpret_cast<const uint4*>(g_src[u] + pg * g_ld);
-    }
-  };
-  auto deposit = [&](int64_t tile) {
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const bool in = a_ok[u] && tile * 32 + a_px[u] < P;
-      V8 t;
-      t.q = ra[u];
-      float2 f8[8];
-      if (PRO) {
-        const float4* fp = reinterpret_cast<const float4*>(&fl[(a_row[u] & ~63) + 8 * v]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float4 q = fp[e];
-          f8[2 * e] = make_float2(q.x, q.y);
-          f8[2 * e + 1] = make_float2(q.z, q.w);
-        }
-      }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        u16 hv = t.h[e];
-        if (PRO) hv = f2bf(fmaxf(__fmaf_rn(bf2f(hv), f8[e].x, f8[e].y), 0.f));
-        aT[(a_row[u] + 8 * e) * PT + a_px[u]] = in ? hv : (u16)0;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      if (g_unit[u]) {
-        const bool in = g_ok[u] && tile * 32 + g_px[u] < P;
-        V8 t;
-        t.q = rg[u];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) gT[(g_row[u] + 8 * e) * PT + g_px[u]] = in ? t.h[e] : (u16)0;
-      }
-    }
-  };
-
-  if (t_begin < t_end) issue(t_begin);
-  __syncthreads();  // fold parameters are in LDS
-  for (int64_t tile = t_begin; tile < t_end; ++tile) {
-    deposit(tile);
-    __syncthreads();
-    if (tile + 1 < t_end) issue(tile + 1);
-    // every row of both arrays is deposited each tile (zeros past cin / cout), so all 24 products
-    // are formed unguarded
-    V8 af[6], bf[4];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) af[i].q = *reinterpret_cast<const uint4*>(&gT[((mh + 2 * i) * 16 + j) * PT + 8 * g]);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) bf[k].q = *reinterpret_cast<const uint4*>(&aT[((cq + 4 * k) * 16 + j) * PT + 8 * g]);
-#pragma unroll
-    for (int i = 0; i < 6; ++i)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) acc[i][k] = mfma_bf16(af[i], bf[k], acc[i][k]);
-    __syncthreads();  // fragment reads done before the next tile is deposited
-  }
-
-  // partials in accumulator order: [split][c group][m group][wave][m-tile i][c-tile k][lane][4]
-  float* pb = part + (((int64_t)blockIdx.x * gridDim.y + blockIdx.y) * gridDim.z + blockIdx.z) * WG1_BLOCK +
-              (int64_t)wave * 24 * 256 + lane * 4;
-#pragma unroll
-  for (int i = 0; i < 6; ++i)
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      *reinterpret_cast<float4*>(pb + (i * 4 + k) * 256) = make_float4(acc[i][k][0], acc[i][k][1], acc[i][k][2], acc[i][k][3]);
-}
-
-// Sums the splits of k_wgrad1's partials (same scheme as k_sum_wgrad3) and writes dW[m][c].
-__global__ __launch_bounds__(256) void k_sum_wgrad1(const float* __restrict__ part, int S, int gy, int gz, int cin,
-                                                    int cout, float* __restrict__ dw) {
-  __shared__ float4 red[3][64];
-  const int64_t per_split = (int64_t)gy * gz * WG1_BLOCK;
-  const int t = threadIdx.x & 63, sg = threadIdx.x >> 6;
-  const int64_t i = ((int64_t)blockIdx.x * 64 + t) * 4;
-  const int blk = (int)(i / WG1_BLOCK), rem = (int)(i - (int64_t)blk * WG1_BLOCK);
-  const int by = blk / gz, bz = blk - by * gz;
-  const int lane = (rem >> 2) & 63, ty = rem >> 8;  // ty = wave*24 + i*4 + k
-  const int wave = ty / 24, ik = ty - wave * 24, mt = (wave & 1) + 2 * (ik >> 2), ct = (wave >> 1) + 4 * (ik & 3);
-  // the 64 quads of a workgroup share (wave, m-tile, c-tile): uniform early exit for tiles whose
-  // whole block of 64 (the unit of the row permutation) lies past the tensor
-  if (bz * WG1_MG + (mt >> 2) * 64 >= cout || by * WG1_CG + (ct >> 2) * 64 >= cin) return;
-  float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
-  const float* p = part + i;
-  int s = sg;
-  for (; s + 12 < S; s += 16) {
-    const float4 a0 = *reinterpret_cast<const float4*>(p + (int64_t)s * per_split);
-    const float4 a1 = *reinterpret_cast<const float4*>(p + (int64_t)(s + 4) * per_split);
-    const float4 a2 = *reinterpret_cast<const float4*>(p + (int64_t)(s + 8) * per_split);
-    const float4 a3 = *reinterpret_cast<const float4*>(p + (int64_t)(s + 12) * per_split);
-    sum.x += a0.x; sum.y += a0.y; sum.z += a0.z; sum.w += a0.w;
-    sum.x += a1.x; sum.y += a1.y; sum.z += a1.z; sum.w += a1.w;
-    sum.x += a2.x; sum.y += a2.y; sum.z += a2.z; sum.w += a2.w;
-    sum.x += a3.x; sum.y += a3.y; sum.z += a3.z; sum.w += a3.w;
-  }
-  for (; s < S; s += 4) {
-    const float4 a0 = *reinterpret_cast<const float4*>(p + (int64_t)s * per_split);
-    sum.x += a0.x; sum.y += a0.y; sum.z += a0.z; sum.w += a0.w;
-  }
-  if (sg > 0) red[sg - 1][t] = sum;
-  __syncthreads();
-  if (sg > 0) return;
-#pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    const float4 o = red[q][t];
-    sum.x += o.x; sum.y += o.y; sum.z += o.z; sum.w += o.w;
-  }
-  const int j = lane & 15, g = lane >> 4;
-  const int rc = ct * 16 + j, c = by * WG1_CG + (rc & ~63) + 8 * (rc & 7) + ((rc & 63) >> 3);
-  if (c >= cin) return;
-  const float o4[4] = {sum.x, sum.y, sum.z, sum.w};
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int rm = mt * 16 + 4 * g + r, m = bz * WG1_MG + (rm & ~63) + 8 * (rm & 7) + ((rm & 63) >> 3);
-    if (m < cout) dw[(int64_t)m * cin + c] = o4[r];
-  }
-}
-
 // ----------------------------------------------------------------------------- BN + ReLU backward
 
 // Thread = (pixel row pr, 8-channel vector cv); workgroup = 256 threads covering `rows` pixels per
@@ -1244,35 +822,11 @@ hipError_t conv(const void* in, int64_t in_ld, bool in_f32, const void* Wp, void
   return hipGetLastError();
 }
 
-// Workgroups of the row-tiled weight-gradient kernels (k_wgrad3, k_wgrad1).  Each ends with a
-// partial of 147 / 196 KB that the sum kernel reads again, and both run beside the data-gradient
-// chain on a helper stream, so a part of the CUs serves better than all of them.  Per step of
-// the DenseNet-161-shaped blocks, with three helper streams: targets of 256 / 128 / 64 / 32
-// workgroups gave 15.06 / 14.71 / 14.56 / 15.50 ms (the same order in each block taken alone,
-// 56x56 to 7x7); with the one helper stream now used: 64 / 96 / 128 / 192 / 256 gave 14.83 /
-// 13.87 / 13.90 / 14.19 / 14.40 ms.
-constexpr int WG_TARGET = 96;
-
-static int wgrad_tiles(int n, int h, int w, int taps) {
-  const Wg3Geom q = wg3_geom(h, w);
-  return (taps == 9 && q.ok) ? n * q.tpi : n * ((h * w + 63) / 64);
-}
-int wgrad_splits(int n, int cin, int cout, int h, int w, int taps) {
-  const int tiles = wgrad_tiles(n, h, w, taps);
-  const int gy = (cin + 63) / 64, gz = (cout + 63) / 64;
-  // k_wgrad3: about WG_TARGET workgroups in all, evenly loaded
-  int s = ((taps == 9 && wg3_geom(h, w).ok) ? WG_TARGET : 1024) / (gy * gz);
-  if (s < 1) s = 1;
-  if (s > tiles) s = tiles;
-  if (s > 128) s = 128;
-  const int tps = (tiles + s - 1) / s;
-  return (tiles + tps - 1) / tps;
-}
-// k_wgrad1: 32-pixel tiles of the flattened pixel axis, about WG_TARGET workgroups in all
-static int wgrad1_splits(int64_t P, int cin, int cout) {
-  const int64_t tiles = (P + 31) / 32;
-  const int gy = (cin + WG1_CG - 1) / WG1_CG, gz = (cout + WG1_MG - 1) / WG1_MG;
-  int64_t s = WG_TARGET / (gy * gz);
+// The any-shape weight gradient k_wgrad: what dnb_nhwc_wgrad.hip's kernels do not take (rows of more
+// than 95 pixels on the 3x3, 2^30 pixels and more).
+static int wgrad_splits(int n, int cin, int cout, int h, int w) {
+  const int64_t tiles = (int64_t)n * (((int64_t)h * w + 63) / 64);
+  int64_t s = 1024 / (((cin + 63) / 64) * ((cout + 63) / 64));
   if (s < 1) s = 1;
   if (s > tiles) s = tiles;
   if (s > 128) s = 128;
@@ -1280,65 +834,34 @@ static int wgrad1_splits(int64_t P, int cin, int cout) {
   return (int)((tiles + tps - 1) / tps);
 }
 size_t wgrad_partial_floats(int n, int cin, int cout, int h, int w, int taps) {
-  const size_t S = (size_t)wgrad_splits(n, cin, cout, h, w, taps);
-  if (taps == 9 && wg3_geom(h, w).ok) return S * ((cin + 63) / 64) * ((cout + 63) / 64) * WG3_BLOCK;
-  size_t f = S * cin * cout * taps;
-  if (taps == 1) {  // either 1x1 kernel may run, depending on the gradient operand's type
-    const size_t f1 = (size_t)wgrad1_splits((int64_t)n * h * w, cin, cout) * ((cin + WG1_CG - 1) / WG1_CG) *
-                      ((cout + WG1_MG - 1) / WG1_MG) * WG1_BLOCK;
-    if (f1 > f) f = f1;
-  }
-  return f;
+  const size_t f = wgrad_fast_partial_floats(n, cin, cout, h, w, taps);
+  return f ? f : (size_t)wgrad_splits(n, cin, cout, h, w) * cin * cout * taps;
 }
 
-// g_f32: the gradient operand is the fp32 slab (3x3), else bf16 (1x1).  The caller adds the
-// partials (launch_sum_partials) -- *splits says how many.
+// g_f32: the gradient operand is an fp32 tensor, else bf16.  Writes the partials and adds them into dw.
 hipError_t wgrad(const void* a, int64_t a_ld, const void* g, int64_t g_ld, bool g_f32, float* part, float* dw, int n,
                  int cin, int cout, int h, int w, int taps, const float2* fold, hipStream_t st) {
-  if (taps == 1 && !g_f32) {
-    const int64_t P = (int64_t)n * h * w, tiles = (P + 31) / 32;
-    const int S = wgrad1_splits(P, cin, cout);
-    const int tps = (int)((tiles + S - 1) / S);
-    dim3 grid((unsigned)S, (unsigned)((cin + WG1_CG - 1) / WG1_CG), (unsigned)((cout + WG1_MG - 1) / WG1_MG));
-    if (fold)
-      hipLaunchKernelGGL((k_wgrad1<true>), grid, dim3(512), 0, st, (const u16*)a, a_ld, (const u16*)g, g_ld, part,
-                         cin, cout, P, tps, fold);
-    else
-      hipLaunchKernelGGL((k_wgrad1<false>), grid, dim3(512), 0, st, (const u16*)a, a_ld, (const u16*)g, g_ld, part,
-                         cin, cout, P, tps, fold);
-    const int64_t per_split = (int64_t)grid.y * grid.z * WG1_BLOCK;
-    hipLaunchKernelGGL(k_sum_wgrad1, dim3((unsigned)(per_split / 256)), dim3(256), 0, st, part, S, (int)grid.y,
-                       (int)grid.z, cin, cout, dw);
-    return hipGetLastError();
-  }
   if (g_f32 && fold) return hipErrorInvalidValue;  // the block's gradient operands are bf16
-  const Wg3Geom q3 = wg3_geom(h, w);
-  const bool three = taps == 9 && q3.ok;
-  const int tpi = three ? q3.tpi : (h * w + 63) / 64, tiles = n * tpi;
-  const int S = wgrad_splits(n, cin, cout, h, w, taps);
+  WgradSum own{};
+  if (wgrad_fast(WgradIn{a, a_ld, g, g_ld, part, dw, cin, cout, fold}, g_f32, n, h, w, taps, &own, st)) {
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : wgrad_finish(taps == 1 ? &own : nullptr, taps == 1 ? nullptr : &own, st);
+  }
+  const int tpi = (int)(((int64_t)h * w + 63) / 64), tiles = n * tpi;
+  const int S = wgrad_splits(n, cin, cout, h, w);
   const int tps = (tiles + S - 1) / S;
   dim3 grid((unsigned)S, (unsigned)((cin + 63) / 64), (unsigned)((cout + 63) / 64));
-  if (three) {
-#define DNB_W3(TG, PRO)                                                                                \
-  hipLaunchKernelGGL((k_wgrad3<TG, PRO>), grid, dim3(512), 0, st, (const u16*)a, a_ld, (const TG*)g, \
-                     g_ld, part, cin, cout, n, h, w, q3.R, q3.FR, tpi, tps, fold)
-    if (g_f32) DNB_W3(float, false);
-    else       { if (fold) DNB_W3(u16, true); else DNB_W3(u16, false); }
-#undef DNB_W3
-    const int64_t per_split = (int64_t)grid.y * grid.z * WG3_BLOCK;
-    hipLaunchKernelGGL(k_sum_wgrad3, dim3((unsigned)(per_split / 256)), dim3(256), 0, st, part, S,
-                       (int)grid.y, (int)grid.z, cin, cout, dw);
-    return hipGetLastError();
-  }
 #define DNB_W(TAPS, TG, PRO)                                                                              \
   hipLaunchKernelGGL((k_wgrad<TAPS, TG, PRO>), grid, dim3(256), 0, st, (const u16*)a, a_ld, (const TG*)g, \
                      g_ld, part, cin, cout, n, h, w, tpi, tps, fold)
-  if (taps == 9) {
-    if (g_f32) DNB_W(9, float, false);
-    else       { if (fold) DNB_W(9, u16, true); else DNB_W(9, u16, false); }
-  } else {
-    DNB_W(1, float, false);  // (a bf16 gradient operand has taken k_wgrad1 above)
-  }
+#define DNB_W2(TAPS)                                                                                      \
+  do {                                                                                                    \
+    if (g_f32) DNB_W(TAPS, float, false);                                                                 \
+    else if (fold) DNB_W(TAPS, u16, true);                                                                \
+    else DNB_W(TAPS, u16, false);                                                                         \
+  } while (0)
+  if (taps == 9) DNB_W2(9); else DNB_W2(1);
+#undef DNB_W2
 #undef DNB_W
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

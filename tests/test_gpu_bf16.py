@@ -363,6 +363,24 @@ def test_nhwc_conv_ops_on_channel_slices_of_wider_slabs(dnb, oracle, ks):
         assert_close(dw.cpu().numpy(), oracle.conv_wgrad(x, g, ks), 1e-2, "wgrad")
 
 
+@pytest.mark.parametrize("n,cin,cout,h,w,ks", [(1, 8, 8, 1, 1, 3), (1, 8, 8, 1, 1, 1), (3, 72, 80, 5, 31, 3), (1, 16, 64, 3, 32, 3),
+                                               (2, 8, 48, 3, 94, 3), (5, 64, 24, 5, 13, 1), (1, 136, 320, 8, 8, 1), (9, 40, 16, 7, 7, 3)])
+@pytest.mark.parametrize("g_f32", [0, 1])
+def test_nhwc_wgrad_tile_edges(dnb, oracle, n, cin, cout, h, w, ks, g_f32):
+    """One pixel; rows at the two sizes of the 3x3's pixel ring (31 | 32 and its widest, 94); tiles that span
+    images; one to three 16-channel output tiles per group, several groups, ragged input groups.  Operands are
+    bf16 values, so the products are exact and only fp32 sums of at most 600 terms round: 1e-5."""
+    r = np.random.default_rng(21)
+    x = to_bf16_values(r.standard_normal((n, cin, h, w)).astype(np.float32))
+    g = to_bf16_values(r.standard_normal((n, cout, h, w)).astype(np.float32))
+    scratch = torch.empty(dnb.dnb_op_nhwc_scratch_bytes(n, cin, cout, h, w, ks), dtype=torch.uint8, device="cuda")
+    dw = torch.full((cout, cin, ks, ks), float("nan"), device="cuda")
+    dnb.dnb_op_nhwc_conv_wgrad(nhwc_bf16(x), cin, nhwc_f32(g) if g_f32 else nhwc_bf16(g), cout, g_f32, dw, n, cin, cout, h, w, ks,
+                               scratch)
+    torch.cuda.synchronize()
+    assert_close(dw.cpu().numpy(), oracle.conv_wgrad(x, g, ks), 1e-5, "wgrad")
+
+
 @pytest.mark.parametrize("g_f32", [0, 1])
 def test_nhwc_wgrad_rows_wider_than_the_row_tiled_kernel_takes(dnb, oracle, g_f32):
     """96-pixel rows: the 3x3 weight gradient falls back to the kernel that stages 64-pixel tiles
