@@ -57,11 +57,21 @@ __device__ __forceinline__ float elem(const float4& v, int e) {
 // ------------------------------------------------------------------------------- packed weights
 //
 // The fast forward / data-gradient kernels read their A operand straight from global memory
-// (it is small and stays in L2), 16 bytes per lane, so the weights are first re-laid as
-// [tap][Mpad][Kpad], zero padded to multiples of 16, with the K index permuted inside each
-// 16-chunk: position 16*chunk + 4*g + ks holds channel 16*chunk + 4*ks + g.
+// (it is small and stays in L2), 16 bytes per lane, so the weights are first re-laid, zero padded to
+// multiples of 16, in fragment order: [tap][M-tile of 16][chunk of 16 channels][lane][4], lane (j, g)
+// holding row j, channels g, 4+g, 8+g, 12+g of the chunk.  A wave's load is 1 KB of consecutive memory
+// (as rows of Kpad floats it was sixteen 64-byte pieces at strides that share L2 channels; with the row
+// sums of dnb_stats.h the DenseNet-BC-100 step went from 5.46 to 5.26 ms, BC-250's from 46.2 to 45.0).
 
-__device__ __forceinline__ int unperm16(int pos) { return (pos & ~15) + 4 * (pos & 3) + ((pos >> 2) & 3); }
+__device__ __forceinline__ const float* wfrag(const float* W, int Kpad, int mtile, int chunk) {
+  return W + ((int64_t)mtile * (Kpad >> 4) + chunk) * 256 + (threadIdx.x & 63) * 4;
+}
+// position e inside one tap's [M16][K16] block -> row, channel
+__device__ __forceinline__ void wunfrag(int e, int K16, int& m, int& c) {
+  const int mt = e / (16 * K16), r = e - mt * 16 * K16, lane = (r >> 2) & 63;
+  m = mt * 16 + (lane & 15);
+  c = (r >> 8) * 16 + 4 * (r & 3) + (lane >> 4);
+}
 
 __global__ __launch_bounds__(256) void k_pack_weights(const float* __restrict__ w, int64_t sm, int64_t sc,
                                                       int flip, int cout, int cin, int taps,
@@ -69,10 +79,9 @@ __global__ __launch_bounds__(256) void k_pack_weights(const float* __restrict__ 
   const int M16 = (cout + 15) & ~15, K16 = (cin + 15) & ~15;
   const int64_t total = (int64_t)taps * M16 * K16;
   for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * 256) {
-    const int pos = (int)(idx % K16);
-    const int64_t rem = idx / K16;
-    const int m = (int)(rem % M16), t = (int)(rem / M16);
-    const int c = unperm16(pos);
+    const int t = (int)(idx / (M16 * K16));
+    int m, c;
+    wunfrag((int)(idx - (int64_t)t * (M16 * K16)), K16, m, c);
     outp[idx] = (m < cout && c < cin) ? w[(int64_t)m * sm + (int64_t)c * sc + (flip ? taps - 1 - t : t)] : 0.f;
   }
 }
@@ -99,21 +108,22 @@ __global__ __launch_bounds__(256) void k_pack_block_weights(const float* __restr
   for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * 256) {
     float v = 0.f;
     if (idx < n1) {
-      const int m = (int)(idx / C16), c = unperm16((int)(idx % C16));
+      int m, c;
+      wunfrag((int)idx, C16, m, c);
       if (m < B && c < C) v = W1[(int64_t)m * C + c];
     } else if (idx < 2 * n1) {
-      const int64_t e = idx - n1;
-      const int cc = (int)(e / B16), o = unperm16((int)(e % B16));
+      int cc, o;
+      wunfrag((int)(idx - n1), B16, cc, o);
       if (cc < C && o < B) v = W1[(int64_t)o * C + cc];
     } else if (idx < 2 * n1 + n3) {
-      const int64_t e = idx - 2 * n1;
-      const int t = (int)(e / (k16 * B16)), rem = (int)(e % (k16 * B16));
-      const int mm = rem / B16, c = unperm16(rem % B16);
+      const int e = (int)(idx - 2 * n1), t = e / (k16 * B16);
+      int mm, c;
+      wunfrag(e - t * (k16 * B16), B16, mm, c);
       if (mm < k && c < B) v = W3[((int64_t)mm * B + c) * 9 + t];
     } else {
-      const int64_t e = idx - 2 * n1 - n3;
-      const int t = (int)(e / (B16 * k16)), rem = (int)(e % (B16 * k16));
-      const int cc = rem / k16, o = unperm16(rem % k16);
+      const int e = (int)(idx - 2 * n1 - n3), t = e / (B16 * k16);
+      int cc, o;
+      wunfrag(e - t * (B16 * k16), k16, cc, o);
       if (cc < B && o < k) v = W3[((int64_t)o * B + cc) * 9 + (8 - t)];
     }
     A[idx] = v;
@@ -186,8 +196,7 @@ __device__ __forceinline__ void tile_stats(const f32x4 (&acc)[NT], bool pix_ok, 
     float s = 0.f;
 #pragma unroll
     for (int t = 0; t < NT; ++t) s += pix_ok ? acc[t][r] : 0.f;
-#pragma unroll
-    for (int off = 1; off < 16; off <<= 1) s += __shfl_xor(s, off, 64);
+    s = row16_sum(s);
     const float mu = s / cnt;
     float m2 = 0.f;
 #pragma unroll
@@ -195,8 +204,7 @@ __device__ __forceinline__ void tile_stats(const f32x4 (&acc)[NT], bool pix_ok, 
       const float dlt = acc[t][r] - mu;
       m2 += pix_ok ? dlt * dlt : 0.f;
     }
-#pragma unroll
-    for (int off = 1; off < 16; off <<= 1) m2 += __shfl_xor(m2, off, 64);
+    m2 = row16_sum(m2);
     const int m = mfirst + 4 * g + r;
     if (j == 0 && m < cout) {
       float* p = part + ((int64_t)m * T + tile_id) * 3;
@@ -229,7 +237,6 @@ __global__ __launch_bounds__(256) void k_conv1x1_v3(
   const int M16 = (cout + 15) & ~15;
   const int nchunks = Kpad >> 4;
   const int cstart = KSPLIT ? wave : 0, cstep = KSPLIT ? nw : 1;
-  const float* wrow = Wp + (int64_t)(mbase + j) * Kpad + 4 * g;
   const bool m_ok = mbase < M16;  // this wave's first tile exists in the packed rows
 
   f32x4 acc[MT][PPL];
@@ -270,9 +277,8 @@ __global__ __launch_bounds__(256) void k_conv1x1_v3(
     }
 #pragma unroll
     for (int a = 0; a < MT; ++a) {
-      // M-tiles past the padded output-channel count read tile 0's rows; they are never stored
-      const int row = (mbase + a * 16 < M16) ? mbase + a * 16 + j : j;
-      w4[a] = ldg4(Wp + (int64_t)row * Kpad + 4 * g + ch0);
+      // M-tiles past the padded output-channel count read tile 0; they are never stored
+      w4[a] = ldg4(wfrag(Wp, Kpad, mbase + a * 16 < M16 ? (mbase >> 4) + a : 0, ch0 >> 4));
     }
   };
 
@@ -415,7 +421,7 @@ __global__ __launch_bounds__(256) void k_conv3x3_v3(
 #pragma unroll
         for (int a = 0; a < MT; ++a)
           w4[t][a] = (mbase + a * 16 < Mpad)
-                         ? ldg4(Wp + ((int64_t)t * Mpad + mbase + a * 16 + j) * Kpad + c0 + 4 * g)
+                         ? ldg4(wfrag(Wp + (int64_t)t * Mpad * Kpad, Kpad, (mbase >> 4) + a, ci))
                          : zero4();
 #pragma unroll
       for (int di = -1; di <= 1; ++di) {
@@ -580,7 +586,7 @@ __global__ __launch_bounds__(256) void k_conv3x3_v4(
 #pragma unroll
       for (int a = 0; a < MT; ++a)
         w4[t][ci][a] = (a * 16 < Mpad && ci * 16 < Kpad)
-                           ? ldg4(Wp + ((int64_t)t * Mpad + a * 16 + j) * Kpad + ci * 16 + 4 * g)
+                           ? ldg4(wfrag(Wp + (int64_t)t * Mpad * Kpad, Kpad, a, ci))
                            : zero4();
 
   // the gaps between staged rows (and the pitch padding) stay zero for the whole kernel
@@ -635,14 +641,9 @@ __global__ __launch_bounds__(256) void k_conv3x3_v4(
       if (STATS) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          float s = v[r];
-#pragma unroll
-          for (int off = 1; off < 16; off <<= 1) s += __shfl_xor(s, off, 64);
-          const float mu = s * (1.0f / 16.0f);
+          const float mu = row16_sum(v[r]) * (1.0f / 16.0f);
           const float dlt = v[r] - mu;
-          float m2 = dlt * dlt;
-#pragma unroll
-          for (int off = 1; off < 16; off <<= 1) m2 += __shfl_xor(m2, off, 64);
+          const float m2 = row16_sum(dlt * dlt);
           if (j == 0) {
             float* ps = &lds[SST0 + (((cur * 4 + wave) * (MT * 16)) + a * 16 + 4 * g + r) * 3];
             ps[0] = 16.f; ps[1] = mu; ps[2] = m2;

@@ -84,8 +84,8 @@ struct WeightView {
   int flip;
 };
 
-// Packed weights for the fast kernels: [taps][cout16][cin16], zero padded to multiples of 16,
-// K index permuted inside each 16-chunk (see dnb_conv_f32_fast.hip).
+// Packed weights for the fast kernels: [taps][cout16 x cin16], zero padded to multiples of 16,
+// in fragment order (see dnb_conv_f32_fast.hip).
 size_t packed_weight_floats(int cout, int cin, int taps);
 hipError_t launch_pack_weights(WeightView wv, int cout, int cin, int taps, float* packed, hipStream_t st);
 // All layers of a block in one launch.  Layer l (input width c) occupies packed_layer_floats

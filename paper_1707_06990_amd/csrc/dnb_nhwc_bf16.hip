@@ -115,7 +115,7 @@ __global__ __launch_bounds__(256) void k_stats_partial(const u16* __restrict__ x
   }
 }
 
-// Packed bf16 weights: [taps][M16][K32] (K padded to a multiple of 32, zero filled), K natural order.
+// Packed bf16 weights: per tap [M16][K32] (zero filled) in fragment order, see wfrag.
 __global__ __launch_bounds__(256) void k_pack_block_weights(const float* __restrict__ params,
                                                             u16* __restrict__ packed, int c0, int k, int B) {
   const int l = blockIdx.y + 1;
@@ -135,21 +135,22 @@ __global__ __launch_bounds__(256) void k_pack_block_weights(const float* __restr
   for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * 256) {
     float v = 0.f;
     if (idx < n1) {                       // 1x1 forward  [B16][C32]
-      const int m = (int)(idx / C32), c = (int)(idx % C32);
+      int m, c;
+      wunfrag((int)idx, C32, m, c);
       if (m < B && c < C) v = W1[(int64_t)m * C + c];
     } else if (idx < n1 + n2) {           // 1x1 dgrad    [C16][B32]
-      const int64_t e = idx - n1;
-      const int cc = (int)(e / B32), o = (int)(e % B32);
+      int cc, o;
+      wunfrag((int)(idx - n1), B32, cc, o);
       if (cc < C && o < B) v = W1[(int64_t)o * C + cc];
     } else if (idx < n1 + n2 + n3) {      // 3x3 forward  [9][k16][B32]
-      const int64_t e = idx - n1 - n2;
-      const int t = (int)(e / (k16 * B32)), rem = (int)(e % (k16 * B32));
-      const int mm = rem / B32, c = rem % B32;
+      const int e = (int)(idx - n1 - n2), t = e / (k16 * B32);
+      int mm, c;
+      wunfrag(e - t * (k16 * B32), B32, mm, c);
       if (mm < k && c < B) v = W3[((int64_t)mm * B + c) * 9 + t];
     } else {                              // 3x3 dgrad    [9][B16][k32], transposed and flipped
-      const int64_t e = idx - n1 - n2 - n3;
-      const int t = (int)(e / (B16 * k32)), rem = (int)(e % (B16 * k32));
-      const int cc = rem / k32, o = rem % k32;
+      const int e = (int)(idx - n1 - n2 - n3), t = e / (B16 * k32);
+      int cc, o;
+      wunfrag(e - t * (B16 * k32), k32, cc, o);
       if (cc < B && o < k) v = W3[((int64_t)o * B + cc) * 9 + (8 - t)];
     }
     A[idx] = f2bf(v);
@@ -162,9 +163,9 @@ __global__ __launch_bounds__(256) void k_pack_weights(const float* __restrict__ 
   const int M16 = (cout + 15) & ~15, K32 = (cin + 31) & ~31;
   const int64_t total = (int64_t)taps * M16 * K32;
   for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * 256) {
-    const int c = (int)(idx % K32);
-    const int64_t rem = idx / K32;
-    const int m = (int)(rem % M16), t = (int)(rem / M16);
+    const int t = (int)(idx / (M16 * K32));
+    int m, c;
+    wunfrag((int)(idx - (int64_t)t * (M16 * K32)), K32, m, c);
     const float v = (m < cout && c < cin) ? w[(int64_t)m * sm + (int64_t)c * sc + (flip ? taps - 1 - t : t)] : 0.f;
     outp[idx] = f2bf(v);
   }
@@ -294,8 +295,8 @@ __global__ __launch_bounds__(256) void k_conv(
     for (int a = 0; a < MT; ++a)
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk)
-        ws.w[a][kk] = *reinterpret_cast<const uint4*>(Wp + ((int64_t)t9 * M16 + min(mbase + a * 16 + j, M16 - 1)) * K32 +
-                                                      min(c0 + kk * 32, K32 - 32) + 8 * g);
+        ws.w[a][kk] = *reinterpret_cast<const uint4*>(
+            wfrag(Wp + (int64_t)t9 * M16 * K32, K32, min(mbase + a * 16, M16 - 16) >> 4, min(c0 + kk * 32, K32 - 32) >> 5));
   };
   // the MFMAs of one (chunk, tap) on the tile staged at boff
   auto mm = [&](int c0, int t9, int boff, const WSet& ws) {
@@ -400,8 +401,7 @@ __global__ __launch_bounds__(256) void k_conv(
         float s = 0.f;
 #pragma unroll
         for (int t = 0; t < 4; ++t) s += (q0 + t * 16 + j < limit) ? rv[t][r] : 0.f;
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) s += __shfl_xor(s, off, 64);
+        s = row16_sum(s);
         const float mu = s / (float)tile_px;
         float m2 = 0.f;
 #pragma unroll
@@ -409,8 +409,7 @@ __global__ __launch_bounds__(256) void k_conv(
           const float d = rv[t][r] - mu;
           m2 += (q0 + t * 16 + j < limit) ? d * d : 0.f;
         }
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) m2 += __shfl_xor(m2, off, 64);
+        m2 = row16_sum(m2);
         const int m = mbase + a * 16 + 4 * g + r;
         if (j == 0 && m < cout) {
           float* p = spart + ((int64_t)m * sT + tile_id) * 3;

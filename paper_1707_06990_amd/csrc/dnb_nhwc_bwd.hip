@@ -41,7 +41,7 @@ struct Dgrad3Args {
   float inv_p;
   u16* gl;                              // out: g_l, [P][k] (not written for the last layer)
   int k;
-  const u16* W; int M16, K32;           // packed weights [9][M16][K32]
+  const u16* W; int M16, K32;           // packed weights, nine taps of [M16][K32]
   const u16* b; const float2* fold2; const float *mean_b, *istd_b;
   int B;
   u16* dz;                              // out [P][B]: masked gradient of BN2's output
@@ -196,7 +196,6 @@ __global__ __launch_bounds__(256) void k_dgrad3(Dgrad3Args A) {
         }
       }
       __syncthreads();
-      const int rows = A.M16 - 1;
 #pragma unroll
       for (int t9 = 0; t9 < 9; ++t9) {
         const int di = t9 / 3 - 1, dj = t9 % 3 - 1;
@@ -206,8 +205,8 @@ __global__ __launch_bounds__(256) void k_dgrad3(Dgrad3Args A) {
             V8 wv[MT], bv[NT];
 #pragma unroll
             for (int a = 0; a < MT; ++a)
-              wv[a].q = *reinterpret_cast<const uint4*>(A.W + ((int64_t)t9 * A.M16 + min(m0 + a * 16 + j, rows)) * A.K32 +
-                                                        c0 + kk * 32 + 8 * g);
+              wv[a].q = *reinterpret_cast<const uint4*>(
+                  wfrag(A.W + (int64_t)t9 * A.M16 * A.K32, A.K32, min(m0 + a * 16, A.M16 - 16) >> 4, (c0 >> 5) + kk));
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
               bv[t].q = *reinterpret_cast<const uint4*>(
@@ -251,9 +250,7 @@ __global__ __launch_bounds__(256) void k_dgrad3(Dgrad3Args A) {
   for (int a = 0; a < MT; ++a)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      float u = s0[a][r], v = s1[a][r];
-#pragma unroll
-      for (int off = 1; off < 16; off <<= 1) { u += __shfl_xor(u, off, 64); v += __shfl_xor(v, off, 64); }
+      const float u = row16_sum(s0[a][r]), v = row16_sum(s1[a][r]);
       if (j == 0) {
         float* p = red + ((wave * MT + a) * 16 + 4 * g + r) * 2;
         p[0] = u; p[1] = v;
@@ -369,10 +366,10 @@ __global__ __launch_bounds__(256) void k_dgrad1(Dgrad1Args A) {
   const u16* wr[2];
 #pragma unroll
   for (int a = 0; a < 2; ++a) {
-    wr[a] = A.W + (int64_t)min(c0 + a * 16 + j, A.C16 - 1) * A.B32 + 8 * g;
+    wr[a] = wfrag(A.W, A.B32, min(c0 + a * 16, A.C16 - 16) >> 4, 0);
     if (KS > 0) {
 #pragma unroll
-      for (int s = 0; s < KR; ++s) w[a][s].q = *reinterpret_cast<const uint4*>(wr[a] + 32 * s);
+      for (int s = 0; s < KR; ++s) w[a][s].q = *reinterpret_cast<const uint4*>(wr[a] + 512 * s);
     }
   }
   float sc[2][4], sf[2][4], mu[2][4], s0[2][4], s1[2][4];
@@ -428,7 +425,7 @@ __global__ __launch_bounds__(256) void k_dgrad1(Dgrad1Args A) {
         V8 ww[2], dd[2];
 #pragma unroll
         for (int a = 0; a < 2; ++a) {
-          ww[a].q = *reinterpret_cast<const uint4*>(wr[a] + 32 * s);
+          ww[a].q = *reinterpret_cast<const uint4*>(wr[a] + 512 * s);
           dd[a].q = *reinterpret_cast<const uint4*>(A.db + p[a] * A.B + min(32 * s + 8 * g, A.B - 8));
         }
 #pragma unroll
@@ -466,9 +463,7 @@ __global__ __launch_bounds__(256) void k_dgrad1(Dgrad1Args A) {
   for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      float u = s0[a][r], v = s1[a][r];
-#pragma unroll
-      for (int off = 1; off < 16; off <<= 1) { u += __shfl_xor(u, off, 64); v += __shfl_xor(v, off, 64); }
+      const float u = row16_sum(s0[a][r]), v = row16_sum(s1[a][r]);
       if (j == 0) { red[wave][a * 16 + 4 * g + r][0] = u; red[wave][a * 16 + 4 * g + r][1] = v; }
     }
   __syncthreads();

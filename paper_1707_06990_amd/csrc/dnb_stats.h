@@ -4,6 +4,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace dnb {
 
 // The one place BN's affine map is folded into (scale, shift); forward, recomputation
@@ -16,6 +18,22 @@ __device__ __forceinline__ void bn_fold(float gamma, float beta, float mean, flo
 
 __device__ __forceinline__ float bn_istd(float m2, float cnt, float eps) {
   return __fdiv_rn(1.0f, __fsqrt_rn(__fadd_rn(__fdiv_rn(m2, cnt), eps)));
+}
+
+// Sum over each row of 16 lanes, every lane gets it: four vector additions whose second operand comes
+// from another lane of the row.  The order of additions (and the bits) is that of a butterfly over
+// lane distances 1, 2, 4, 8: after two steps the lanes of a quad agree, so the mirrored lane 7 - i holds
+// what lane i ^ 4 does, then 15 - i what i ^ 8 does.  Through __shfl_xor each step goes to the LDS
+// crossbar and back; with two such sums per output channel that was 3 us of a convolution's launch.
+__device__ __forceinline__ float row16_sum(float v) {
+  auto from = [](float x, auto ctrl) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  v += from(v, std::integral_constant<int, 0xB1>{});   // quad_perm [1,0,3,2]
+  v += from(v, std::integral_constant<int, 0x4E>{});   // quad_perm [2,3,0,1]
+  v += from(v, std::integral_constant<int, 0x141>{});  // row_half_mirror
+  v += from(v, std::integral_constant<int, 0x140>{});  // row_mirror
+  return v;
 }
 
 struct Stat3 {
