@@ -295,8 +295,8 @@ int backward_bf16(dnb_block* b, const void* yv, const void* dy, void* dx0, float
 
 // ---- fp32 NCHW without a bottleneck: each layer is BN -> ReLU -> 3x3 conv on the concatenation
 // (the composite function as first defined, Section 2 "Dense connectivity").  Storage 1 and 2 are
-// used exactly as with a bottleneck; there is no storage 3 and no kept b_l.  The generic
-// implicit-GEMM kernels take the wide 3x3 (C_l input channels); everything runs in program order
+// used exactly as with a bottleneck; there is no storage 3 and no kept b_l.  The 
+// K-chunked 3x3 kernels take the wide conv (C_l input channels); everything runs in program order
 // on the caller's stream.
 int forward_plain3x3(dnb_block* b, const float* x0, const float* params, float* y, char* ws, hipStream_t st) {
   const dnb_block_desc& d = b->d;
@@ -305,6 +305,8 @@ int forward_plain3x3(dnb_block* b, const float* x0, const float* params, float* 
   float* mean_y = (float*)(ws + b->off_stat_y);
   float* istd_y = mean_y + b->cout;
   float* part = (float*)(ws + b->off_part);
+  float* pack = (float*)(ws + b->off_pack);
+  DNB_TRY(launch_pack_block_weights(params, pack, d.c0, k, 0, m, st));
   DNB_TRY(launch_copy_slab(x0, (int64_t)d.c0 * hw, y, ys, n, (int64_t)d.c0 * hw, st));
   int freshT = 0;
   DNB_TRY(launch_bn_stats_partial(y, ys, n, d.c0, hw, part, &freshT, st));
@@ -315,11 +317,13 @@ int forward_plain3x3(dnb_block* b, const float* x0, const float* params, float* 
     float* S1 = (float*)(ws + b->off_u[l]);
     float* S2 = (float*)(ws + b->off_a[l]);
     float* xl = y + (int64_t)c * hw;
+    ConvExtras e3{nullptr, l < m ? part : nullptr, 0, false};
     DNB_TRY(launch_bn_relu(y, ys, S2, (int64_t)c * hw, S1, (int64_t)c * hw, n, c, hw, p.g1, p.b1,
                            StatsSrc{mean_y, istd_y, part, freshT, fresh_lo, fresh_hi, d.eps}, st));
-    DNB_TRY(launch_conv_igemm(S2, (int64_t)c * hw, WeightView{p.W3, (int64_t)c * 9, 9, 0}, nullptr, xl, ys,
-                              n, c, k, d.h, d.w, 9, nullptr, st));
-    if (l < m) DNB_TRY(launch_bn_stats_partial(xl, ys, n, k, hw, part, &freshT, st));
+    DNB_TRY(launch_conv_igemm(S2, (int64_t)c * hw, WeightView{p.W3, (int64_t)c * 9, 9, 0}, pack + b->pk[l], xl, ys,
+                              n, c, k, d.h, d.w, 9, &e3, st));
+    freshT = e3.stats_T;
+    if (l < m && !e3.used_fast) DNB_TRY(launch_bn_stats_partial(xl, ys, n, k, hw, part, &freshT, st));
     fresh_lo = c; fresh_hi = c + k;
   }
   return DNB_OK;
@@ -337,6 +341,7 @@ int backward_plain3x3(dnb_block* b, const float* params, const float* y, const f
   float* partA = (float*)(ws + b->off_partA);
   float* G = (float*)(ws + b->off_G);
   float* dS2 = (float*)(ws + b->off_dS2);
+  const float* pack = (const float*)(ws + b->off_pack);  // packed by the forward pass
   DNB_TRY(launch_copy_slab(dy, ys, G, ys, n, ys, st));
   for (int l = m; l >= 1; --l) {
     const int c = c_in(d, l);
@@ -349,7 +354,8 @@ int backward_plain3x3(dnb_block* b, const float* params, const float* y, const f
       DNB_TRY(launch_bn_relu(y, ys, S2, (int64_t)c * hw, S1, (int64_t)c * hw, n, c, hw, p.g1, p.b1,
                              StatsSrc{mean_y, istd_y, nullptr, 0, 0, 0, d.eps}, st));
     DNB_TRY(launch_conv_wgrad(S2, (int64_t)c * hw, gl, ys, gp.W3, n, c, k, d.h, d.w, 9, partA, nullptr, st));
-    DNB_TRY(launch_conv_igemm(gl, ys, WeightView{p.W3, 9, (int64_t)c * 9, 1}, nullptr, dS2, (int64_t)c * hw,
+    const size_t k16 = (size_t)((k + 15) & ~15), c16 = (size_t)((c + 15) & ~15);
+    DNB_TRY(launch_conv_igemm(gl, ys, WeightView{p.W3, 9, (int64_t)c * 9, 1}, pack + b->pk[l] + 9 * k16 * c16, dS2, (int64_t)c * hw,
                               n, k, c, d.h, d.w, 9, nullptr, st));
     DNB_TRY(launch_bn_relu_bwd(S1, (int64_t)c * hw, dS2, (int64_t)c * hw, G, ys, true, n, c, hw, p.g1, p.b1,
                                mean_y, istd_y, gp.g1, gp.b1, part, st));
@@ -538,6 +544,8 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
       for (int l = 1; l <= m; ++l) {
         const size_t f = conv_wgrad_partial_floats(d.n, c_in(d, l), k, d.h, d.w, 9);
         if (f > partA) partA = f;
+        b->pk[l] = pack;
+        pack += packed_layer_floats(c_in(d, l), k, 0);
       }
     } else {
       partA = conv_wgrad_partial_floats(d.n, B, k, d.h, d.w, 9);

@@ -21,6 +21,10 @@ bool conv_fast_ok(const float* in, int64_t in_stride, const float* out, int64_t 
 bool launch_conv_fast(const float* in, int64_t in_stride, const float* packed, float* out,
                       int64_t out_stride, int n, int cin, int cout, int h, int w, int taps,
                       const float2* fold, float* spart, int* sT, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);
+// 3x3 of any number of input channels and (moderate) image width, dnb_conv3x3_f32.hip; false: not taken
+bool launch_conv3x3_any(const float* in, int64_t in_stride, const float* packed, float* out, int64_t out_stride, int n,
+                        int cin, int cout, int h, int w, float* spart, int* sT, hipStream_t st, hipEvent_t ev0,
+                        hipEvent_t ev1);
 size_t conv_wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps);
 // Launches the fast weight-gradient kernel if it applies (returns false otherwise).  *own
 // describes the sum of its partials, which is left to the caller; *absorb (may be null or of kind
@@ -182,16 +186,21 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(
   const int split = blockIdx.x, c0 = blockIdx.y * CB, m0 = blockIdx.z * MB;
   const int ntiles = MTW * CTW * TAPS;
 
+  // A wave's tiles are wave, wave + 4, ...; past the last it repeats tile 0 and does not store (a test
+  // around each product would make every one of them wait for its own LDS reads: 25 -> 11 us per launch
+  // on the 14x14 layers at batch 37).
   f32x4 acc[TW];
-  int t_mt[TW], t_ct[TW], t_tap[TW];
+  int aoff[TW], boff[TW], t_mt[TW], t_ct[TW], t_dj[TW];
 #pragma unroll
   for (int j = 0; j < TW; ++j) {
     acc[j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    const int t = wave + 4 * j;
-    const int tt = t < ntiles ? t : 0;
-    t_tap[j] = tt % TAPS;
+    const int t = wave + 4 * j, tt = t < ntiles ? t : 0, tap = tt % TAPS;
+    const int di = TAPS == 9 ? tap / 3 - 1 : 0;
+    t_dj[j] = TAPS == 9 ? tap % 3 - 1 : 0;
     t_ct[j] = (tt / TAPS) % CTW;
     t_mt[j] = tt / (TAPS * CTW);
+    aoff[j] = (t_mt[j] * 16 + i16) * PG + kk;
+    boff[j] = (t_ct[j] * 16 + i16) * PA + kk + halo + di * W + t_dj[j];
   }
 
   const int ch_begin = split * cps, ch_end = min(total_chunks, ch_begin + cps);
@@ -200,40 +209,58 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(
     const float* inb = in + (int64_t)img * in_stride;
     const float* gb = gout + (int64_t)img * g_stride;
     __syncthreads();
-    for (int idx = tid; idx < CB * seg; idx += 256) {
-      const int row = idx / seg, s = idx - row * seg;
-      const int q = q0 - halo + s, c = c0 + row;
-      float v = 0.f;
-      if (c < cin && q >= 0 && q < HW) v = inb[(int64_t)c * HW + q];
-      al[row * PA + s] = v;
-    }
-    for (int idx = tid; idx < MB * TPIX; idx += 256) {
-      const int row = idx / TPIX, s = idx - row * TPIX;
-      const int q = q0 + s, m = m0 + row;
-      float v = 0.f;
-      if (m < cout && q < HW) v = gb[(int64_t)m * HW + q];
-      gl[row * PG + s] = v;
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int s = 0; s < TPIX / 4; ++s) {
-      const int p = 4 * s + kk;
-      const int wc = (q0 + p) % W;
-      const bool lok = wc != 0, rok = wc != W - 1;
+    // Sixteen threads to a row, a thread's loads of 128 columns in one batch at clamped addresses
+    // (taken one by one under a bounds test, each waited for the last: two thirds of the launch).
+    const int prow = tid >> 4, pcol = tid & 15;
+    for (int r0 = 0; r0 < CB + MB; r0 += 16) {  // the activations' rows, then the gradient's
+      const bool act = r0 < CB;
+      const int row = act ? r0 + prow : r0 - CB + prow, ch = act ? c0 + row : m0 + row, nch = act ? cin : cout;
+      const int base = act ? q0 - halo : q0, cols = act ? seg : TPIX;
+      const float* src = (act ? inb : gb) + (int64_t)min(ch, nch - 1) * HW;
+      float* dst = act ? al + row * PA : gl + row * PG;
+      for (int s0 = 0; s0 < cols; s0 += 128) {
+        float v[8];
 #pragma unroll
-      for (int j = 0; j < TW; ++j) {
-        if (wave + 4 * j < ntiles) {
-          const int di = (TAPS == 9) ? t_tap[j] / 3 - 1 : 0, dj = (TAPS == 9) ? t_tap[j] % 3 - 1 : 0;
-          const float a = gl[(t_mt[j] * 16 + i16) * PG + p];
-          float b = al[(t_ct[j] * 16 + i16) * PA + halo + p + di * W + dj];
-          if (dj < 0 && !lok) b = 0.f;
-          if (dj > 0 && !rok) b = 0.f;
-          acc[j] = mfma16(a, b, acc[j]);
+        for (int u = 0; u < 8; ++u) v[u] = src[min(max(base + s0 + pcol + 16 * u, 0), HW - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int s = s0 + pcol + 16 * u, q = base + s;
+          if (s < cols) dst[s] = ch < nch && q >= 0 && q < HW ? v[u] : 0.f;
         }
       }
     }
+    __syncthreads();
+    int wc = (q0 + kk) % W;
+    const int wstep = 4 % W;
+#pragma unroll 4
+    for (int s = 0; s < TPIX / 4; ++s) {
+      const bool lout = wc == 0, rout = wc == W - 1;
+      float av[TW], bv[TW];
+#pragma unroll
+      for (int j = 0; j < TW; ++j) {
+        av[j] = gl[aoff[j] + 4 * s];
+        bv[j] = al[boff[j] + 4 * s];
+      }
+#pragma unroll
+      for (int j = 0; j < TW; ++j) {
+        if (TAPS == 9 && ((t_dj[j] < 0 && lout) || (t_dj[j] > 0 && rout))) bv[j] = 0.f;
+        acc[j] = mfma16(av[j], bv[j], acc[j]);
+      }
+      wc += wstep;
+      if (wc >= W) wc -= W;
+    }
   }
 
+  if (TAPS == 9) {
+    // accumulator order (tile, lane, 4 rows), as the fast kernel's partials: 16-byte stores, contiguous
+    // across the wave (in OIHW order every lane's 4 bytes were a cache line of their own)
+    float* pa = part + (((int64_t)split * gridDim.z + blockIdx.z) * gridDim.y + blockIdx.y) * ntiles * 256 + lane * 4;
+#pragma unroll
+    for (int j = 0; j < TW; ++j)
+      if (wave + 4 * j < ntiles)
+        *reinterpret_cast<float4*>(pa + (wave + 4 * j) * 256) = make_float4(acc[j][0], acc[j][1], acc[j][2], acc[j][3]);
+    return;
+  }
   float* pb = part + (int64_t)split * cout * cin * TAPS;
 #pragma unroll
   for (int j = 0; j < TW; ++j) {
@@ -242,7 +269,7 @@ __global__ __launch_bounds__(256) void k_conv_wgrad(
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int m = m0 + t_mt[j] * 16 + 4 * kk + r;
-        if (m < cout && c < cin) pb[((int64_t)m * cin + c) * TAPS + t_tap[j]] = acc[j][r];
+        if (m < cout && c < cin) pb[(int64_t)m * cin + c] = acc[j][r];
       }
     }
   }
@@ -381,7 +408,7 @@ WgradPlan plan_wgrad(int n, int cin, int cout, int h, int w, int taps) {
   int splits = 1024 / (gy * gz);
   if (splits < 1) splits = 1;
   if (splits > p.total) splits = p.total;
-  if (splits > 64) splits = 64;
+  if (splits > 256) splits = 256;  // (a cap of 64 left the 14x14 and 7x7 blocks at batch 37 on 64 CUs)
   p.cps = (p.total + splits - 1) / splits;
   p.splits = (p.total + p.cps - 1) / p.cps;
   const int halo = taps == 9 ? w + 1 : 0;
@@ -399,11 +426,17 @@ hipError_t launch_conv_igemm(const float* in, int64_t in_stride, WeightView wv, 
                              int taps, ConvExtras* ex, hipStream_t st) {
   if (n <= 0 || cout <= 0 || h <= 0 || w <= 0) return hipSuccess;
   if (ex) ex->used_fast = false;
-  if (packed && conv_fast_ok(in, in_stride, out, out_stride, h, w, taps) &&
-      launch_conv_fast(in, in_stride, packed, out, out_stride, n, cin, cout, h, w, taps,
-                       ex ? ex->fold : nullptr, ex ? ex->stats_part : nullptr,
-                       ex ? &ex->stats_T : nullptr, st, ex ? ex->ev_start : nullptr,
-                       ex ? ex->ev_stop : nullptr)) {
+  // the 1x1 kernel takes single floats where rows are not 16-byte friendly
+  const ConvExtras x = ex ? *ex : ConvExtras{};
+  int* T = ex ? &ex->stats_T : nullptr;
+  if (packed && (((taps == 1 && !x.fold) || conv_fast_ok(in, in_stride, out, out_stride, h, w, taps)) &&
+                 launch_conv_fast(in, in_stride, packed, out, out_stride, n, cin, cout, h, w, taps, x.fold, x.stats_part, T, st,
+                                  x.ev_start, x.ev_stop))) {
+    if (ex) ex->used_fast = true;
+    return hipGetLastError();
+  }
+  if (packed && taps == 9 && !x.fold &&
+      launch_conv3x3_any(in, in_stride, packed, out, out_stride, n, cin, cout, h, w, x.stats_part, T, st, x.ev_start, x.ev_stop)) {
     if (ex) ex->used_fast = true;
     return hipGetLastError();
   }
@@ -424,7 +457,9 @@ int conv_wgrad_splits(int n, int cin, int cout, int h, int w, int taps) {
 }
 
 size_t conv_wgrad_partial_floats(int n, int cin, int cout, int h, int w, int taps) {
-  const size_t a = (size_t)conv_wgrad_splits(n, cin, cout, h, w, taps) * cin * cout * taps;
+  const WgradPlan p = plan_wgrad(n, cin, cout, h, w, taps);
+  const size_t a = taps == 9 ? (size_t)p.splits * p.grid.y * p.grid.z * p.mtw * p.ctw * 9 * 256
+                             : (size_t)p.splits * cin * cout;
   const size_t b = conv_wgrad_fast_partial_floats(n, cin, cout, h, w, taps);
   return a > b ? a : b;
 }
@@ -464,7 +499,12 @@ hipError_t launch_conv_wgrad(const float* in, int64_t in_stride, const float* g,
   else
     hipLaunchKernelGGL((k_conv_wgrad<1, 3>), p.grid, dim3(256), p.lds, st, in, in_stride, g, g_stride,
                        partials, cin, cout, h, w, p.cpi, p.total, p.cps, p.mtw, p.ctw, p.PA, p.PG);
-  return launch_sum_partials(partials, p.splits, (int64_t)cin * cout * taps, dw, st);
+  own.kind = taps == 9 ? 2 : 1;
+  own.part = partials; own.out = dw; own.splits = p.splits;
+  own.gy = (int)p.grid.y; own.gz = (int)p.grid.z; own.mtw = p.mtw; own.ctw = p.ctw; own.cin = cin; own.cout = cout;
+  own.count = taps == 9 ? (int64_t)own.gz * own.gy * p.mtw * p.ctw * 9 * 256 : (int64_t)cin * cout;
+  if (defer) { *defer = own; return hipGetLastError(); }
+  return launch_pending_sum(&own, st);
 }
 
 hipError_t launch_conv_wgrad_pair(const float* in1, int64_t in1_stride, const float* g1, int64_t g1_stride,

@@ -31,6 +31,7 @@
 constexpr int kV4Workgroups = 512;  // workgroups of the persistent 3x3 kernel (two per CU)
 static_assert(kV4Workgroups % 8 == 0, "tiles are dealt to workgroups per XCD (8 of them)");
 
+#include "dnb_f32_dev.h"
 #include "dnb_internal.h"
 #include <hip/hip_ext.h>
 
@@ -42,18 +43,6 @@ namespace dnb {
 
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-__device__ __forceinline__ float4 ldg4(const float* p) { return *reinterpret_cast<const float4*>(p); }
-__device__ __forceinline__ float4 zero4() { return make_float4(0.f, 0.f, 0.f, 0.f); }
-__device__ __forceinline__ float elem(const float4& v, int e) {
-  return e == 0 ? v.x : (e == 1 ? v.y : (e == 2 ? v.z : v.w));
-}
-
 // ------------------------------------------------------------------------------- packed weights
 //
 // The fast forward / data-gradient kernels read their A operand straight from global memory
@@ -62,16 +51,6 @@ __device__ __forceinline__ float elem(const float4& v, int e) {
 // holding row j, channels g, 4+g, 8+g, 12+g of the chunk.  A wave's load is 1 KB of consecutive memory
 // (as rows of Kpad floats it was sixteen 64-byte pieces at strides that share L2 channels; with the row
 // sums of dnb_stats.h the DenseNet-BC-100 step went from 5.46 to 5.26 ms, BC-250's from 46.2 to 45.0).
-
-__device__ __forceinline__ const float* wfrag(const float* W, int Kpad, int mtile, int chunk) {
-  return W + ((int64_t)mtile * (Kpad >> 4) + chunk) * 256 + (threadIdx.x & 63) * 4;
-}
-// position e inside one tap's [M16][K16] block -> row, channel
-__device__ __forceinline__ void wunfrag(int e, int K16, int& m, int& c) {
-  const int mt = e / (16 * K16), r = e - mt * 16 * K16, lane = (r >> 2) & 63;
-  m = mt * 16 + (lane & 15);
-  c = (r >> 8) * 16 + 4 * (r & 3) + (lane >> 4);
-}
 
 __global__ __launch_bounds__(256) void k_pack_weights(const float* __restrict__ w, int64_t sm, int64_t sc,
                                                       int flip, int cout, int cin, int taps,
@@ -88,15 +67,23 @@ __global__ __launch_bounds__(256) void k_pack_weights(const float* __restrict__ 
 
 // All layers of a dense block in one launch (grid.y = layer).  Per layer, in order:
 // 1x1 forward [B16][C16], 1x1 data gradient [C16][B16], 3x3 forward [9][k16][B16],
-// 3x3 data gradient [9][B16][k16] (transposed and flipped).
+// 3x3 data gradient [9][B16][k16] (transposed and flipped).  Without a bottleneck (B = 0) the two 3x3
+// matrices only, with the layer's input channels in B's place.
 __global__ __launch_bounds__(256) void k_pack_block_weights(const float* __restrict__ params,
                                                             float* __restrict__ packed, int c0, int k,
                                                             int B) {
   const int l = blockIdx.y + 1;
-  const int B16 = (B + 15) & ~15, k16 = (k + 15) & ~15;
+  const int k16 = (k + 15) & ~15;
+  const bool plain = B == 0;
+  int B16 = (B + 15) & ~15;
   int64_t poff = 0, koff = 0;
   for (int i = 1; i < l; ++i) {
     const int c = c0 + (i - 1) * k, c16 = (c + 15) & ~15;
+    if (plain) {
+      poff += 2 * (int64_t)c + 9 * (int64_t)k * c;
+      koff += 18 * (int64_t)k16 * c16;
+      continue;
+    }
     poff += 2 * (int64_t)c + (int64_t)B * c + 2 * B + 9 * (int64_t)k * B;
     koff += 2 * (int64_t)B16 * c16 + 18 * (int64_t)k16 * B16;
   }
@@ -104,7 +91,9 @@ __global__ __launch_bounds__(256) void k_pack_block_weights(const float* __restr
   const float* W1 = params + poff + 2 * C;
   const float* W3 = W1 + (int64_t)B * C + 2 * B;
   float* A = packed + koff;
-  const int64_t n1 = (int64_t)B16 * C16, n3 = 9 * (int64_t)k16 * B16, total = 2 * n1 + 2 * n3;
+  const int64_t n1 = (int64_t)B16 * C16;
+  if (plain) { B = C; B16 = C16; }
+  const int64_t n3 = 9 * (int64_t)k16 * B16, total = 2 * n1 + 2 * n3;
   for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * 256) {
     float v = 0.f;
     if (idx < n1) {
@@ -127,49 +116,6 @@ __global__ __launch_bounds__(256) void k_pack_block_weights(const float* __restr
       if (cc < B && o < k) v = W3[((int64_t)o * B + cc) * 9 + (8 - t)];
     }
     A[idx] = v;
-  }
-}
-
-// Sums the accumulators of the K-split waves of a workgroup (fixed order 0,1,2,...).  M-tile a
-// is owned by wave a % nw: every other wave writes its copy of the tile to LDS, the owner adds
-// the copies (its own stays in registers, inserted at its place in the order) and keeps the
-// result.  red: [MT*NT][nw-1 slots][64 lanes][4].
-template <int MT, int NT>
-__device__ __forceinline__ void ksplit_reduce(f32x4 (&acc)[MT][NT], float* red, int wave, int lane, int nw) {
-  __syncthreads();  // (wave = index inside the K group, nw = waves per K group, red = the group's buffer)
-  if (nw == 1) return;
-#pragma unroll
-  for (int a = 0; a < MT; ++a) {
-    const int owner = a % nw;
-    if (wave != owner) {
-      const int slot = (wave - owner - 1 + nw) % nw;
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-        *reinterpret_cast<float4*>(&red[((((a * NT + t) * (nw - 1)) + slot) * 64 + lane) * 4]) =
-            make_float4(acc[a][t][0], acc[a][t][1], acc[a][t][2], acc[a][t][3]);
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int a = 0; a < MT; ++a) {
-    const int owner = a % nw;
-    if (wave == owner) {
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        f32x4 s = (f32x4){0.f, 0.f, 0.f, 0.f};
-        for (int w = 0; w < nw; ++w) {
-          if (w == owner) {
-            s[0] += acc[a][t][0]; s[1] += acc[a][t][1]; s[2] += acc[a][t][2]; s[3] += acc[a][t][3];
-          } else {
-            const int slot = (w - owner - 1 + nw) % nw;
-            const float4 v = *reinterpret_cast<const float4*>(
-                &red[((((a * NT + t) * (nw - 1)) + slot) * 64 + lane) * 4]);
-            s[0] += v.x; s[1] += v.y; s[2] += v.z; s[3] += v.w;
-          }
-        }
-        acc[a][t] = s;
-      }
-    }
   }
 }
 
@@ -1232,7 +1178,7 @@ hipError_t launch_pack_weights(WeightView wv, int cout, int cin, int taps, float
 
 size_t packed_layer_floats(int c, int k, int B) {
   const size_t B16 = (B + 15) & ~15, k16 = (k + 15) & ~15, c16 = (c + 15) & ~15;
-  return 2 * B16 * c16 + 18 * k16 * B16;
+  return B > 0 ? 2 * B16 * c16 + 18 * k16 * B16 : 18 * k16 * c16;
 }
 
 hipError_t launch_pack_block_weights(const float* params, float* packed, int c0, int k, int B, int m,
@@ -1285,7 +1231,10 @@ bool launch_conv_fast(const float* in, int64_t in_stride, const float* packed, f
     // Smaller launches take 16-pixel tiles with a four-way K-split for more loads in flight.
     const int64_t tiles64 = (int64_t)((hw + 63) / 64) * gy * n;
     const bool one_tile = ksplit && tiles64 >= 256 && tiles64 < 512;
-    const int ppl = (tiles64 >= 512 || one_tile) ? 4 : 1;
+    // Rows or operands that are not 16-byte friendly take the 16-pixel tiles, whose lanes load single
+    // floats, whatever the size.
+    const bool vec = conv_fast_ok(in, in_stride, out, out_stride, h, w, 1);
+    const int ppl = vec && (tiles64 >= 512 || one_tile) ? 4 : 1;
     const int tiles = (hw + 16 * ppl - 1) / (16 * ppl);
     // (with at most 16 chunks a wave takes a tile's whole K range, four tiles per workgroup and no
     // reduction: 0.9 % off the DenseNet-BC-100 step; with the long K ranges of k = 24 nets it was

@@ -1,0 +1,76 @@
+// Device helpers shared by the fp32 convolution kernel files.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace dnb {
+namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ float4 ldg4(const float* p) { return *reinterpret_cast<const float4*>(p); }
+__device__ __forceinline__ float4 zero4() { return make_float4(0.f, 0.f, 0.f, 0.f); }
+__device__ __forceinline__ float elem(const float4& v, int e) {
+  return e == 0 ? v.x : (e == 1 ? v.y : (e == 2 ? v.z : v.w));
+}
+
+__device__ __forceinline__ const float* wfrag(const float* W, int Kpad, int mtile, int chunk) {
+  return W + ((int64_t)mtile * (Kpad >> 4) + chunk) * 256 + (threadIdx.x & 63) * 4;
+}
+// position e inside one tap's [M16][K16] block -> row, channel
+__device__ __forceinline__ void wunfrag(int e, int K16, int& m, int& c) {
+  const int mt = e / (16 * K16), r = e - mt * 16 * K16, lane = (r >> 2) & 63;
+  m = mt * 16 + (lane & 15);
+  c = (r >> 8) * 16 + 4 * (r & 3) + (lane >> 4);
+}
+
+// Sums the accumulators of the K-split waves of a workgroup (fixed order 0,1,2,...).  M-tile a
+// is owned by wave a % nw: every other wave writes its copy of the tile to LDS, the owner adds
+// the copies (its own stays in registers, inserted at its place in the order) and keeps the
+// result.  red: [MT*NT][nw-1 slots][64 lanes][4].
+template <int MT, int NT>
+__device__ __forceinline__ void ksplit_reduce(f32x4 (&acc)[MT][NT], float* red, int wave, int lane, int nw) {
+  __syncthreads();  // (wave = index inside the K group, nw = waves per K group, red = the group's buffer)
+  if (nw == 1) return;
+#pragma unroll
+  for (int a = 0; a < MT; ++a) {
+    const int owner = a % nw;
+    if (wave != owner) {
+      const int slot = (wave - owner - 1 + nw) % nw;
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        *reinterpret_cast<float4*>(&red[((((a * NT + t) * (nw - 1)) + slot) * 64 + lane) * 4]) =
+            make_float4(acc[a][t][0], acc[a][t][1], acc[a][t][2], acc[a][t][3]);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int a = 0; a < MT; ++a) {
+    const int owner = a % nw;
+    if (wave == owner) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        f32x4 s = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int w = 0; w < nw; ++w) {
+          if (w == owner) {
+            s[0] += acc[a][t][0]; s[1] += acc[a][t][1]; s[2] += acc[a][t][2]; s[3] += acc[a][t][3];
+          } else {
+            const int slot = (w - owner - 1 + nw) % nw;
+            const float4 v = *reinterpret_cast<const float4*>(
+                &red[((((a * NT + t) * (nw - 1)) + slot) * 64 + lane) * 4]);
+            s[0] += v.x; s[1] += v.y; s[2] += v.z; s[3] += v.w;
+          }
+        }
+        acc[a][t] = s;
+      }
+    }
+  }
+}
+
+}  // namespace
+}  // namespace dnb

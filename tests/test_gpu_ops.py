@@ -153,6 +153,20 @@ def test_conv_forward_dgrad_wgrad(dnb, oracle, n, cin, cout, h, w, ks):
     assert_close(dw.cpu().numpy(), oracle.conv_wgrad(x, g, ks), TOL, "wgrad")
 
 
+@pytest.mark.parametrize("n,cin,cout,h,w,ks", [
+    # rows at the widest the wave-private 3x3 takes without and with 16-byte loads (and one more: the kernel
+    # behind it), 64-pixel tiles cut by the image, one pixel
+    (2, 18, 20, 3, 31, 3), (1, 18, 20, 3, 33, 3), (1, 250, 12, 2, 60, 3), (1, 250, 12, 2, 64, 3), (1, 40, 16, 1, 1, 3),
+    # K over two, three and four waves with one chunk over, one to three M-tiles; M over the waves
+    (2, 32, 16, 9, 9, 3), (2, 33, 20, 14, 14, 3), (2, 292, 12, 16, 16, 3), (1, 330, 48, 14, 10, 3), (2, 12, 292, 16, 16, 3),
+    (3, 8, 130, 7, 7, 3),
+    # 1x1 on rows that are not 16-byte friendly: K split and not, many M-tiles
+    (2, 100, 48, 7, 7, 1), (2, 48, 210, 9, 9, 1), (1, 20, 20, 1, 3, 1)])
+def test_conv_tile_edges(dnb, oracle, n, cin, cout, h, w, ks):
+    """Edges of the any-width and any-depth convolutions and of the weight gradient beside them."""
+    test_conv_forward_dgrad_wgrad(dnb, oracle, n, cin, cout, h, w, ks)
+
+
 def test_conv_on_channel_slices_of_wider_slabs(dnb, oracle):
     """Input and output addressed in place inside wider tensors (explicit image strides),
     as the block does with the output slab y and the gradient slab."""
