@@ -166,11 +166,12 @@ int dnb_block_relu_decisions(dnb_block* b, const void* params, const void* y, co
                              void* d2, void* stream);
 
 /* Section 4's "regular back-propagation" after re-population leaves the order of independent
- * kernels open: the fp32 backward pass can run its two weight-gradient chains on helper streams owned
- * by the block (created at the first such backward call, joined to `stream` before the call's last
- * kernel), so that they overlap the data-gradient chain.  enable = 0 puts everything on `stream` in
+ * kernels open: the fp32 backward pass of images whose rows are not 16-byte vectors (w % 4 != 0) can run
+ * its two weight-gradient chains on helper streams owned by the block (created at the first such
+ * backward call, joined to `stream` before the call's last kernel), so that they overlap the
+ * data-gradient chain.  enable = 0 puts everything on `stream` in
  * program order; results are bit-identical either way.  Default: disabled (measured slower on one
- * MI355X).  The bf16 backward pass is one chain of launches on `stream` and takes no notice of it. */
+ * MI355X).  Every other backward pass is one chain of launches on `stream` and takes no notice of it. */
 int dnb_block_set_concurrency(dnb_block* b, int enable);
 
 const char* dnb_status_string(int status);

@@ -23,7 +23,7 @@ struct dnb_block {
   std::vector<size_t> off_stat_b;            // per layer mean[B], istd[B]
   std::vector<size_t> off_fold1, off_fold2;  // fused schedule: per layer folded (scale, shift) of BN1 / BN2
   size_t off_part;                           // reduction partials of the main chain (BN)
-  size_t off_K, part1_floats;                // bf16 backward: K0, K1 per channel; where BN2's partials start in off_part
+  size_t off_K, part1_floats;                // backward: K0, K1 per channel; where BN2's partials start in off_part
   size_t partA_floats, partB_floats;         // size of one weight-gradient partial buffer
   size_t off_partA, off_partB;               // partials of the 3x3 / 1x1 weight gradients
   // with concurrency on, backward runs three chains: the data-gradient chain on the caller's
@@ -293,6 +293,77 @@ int backward_bf16(dnb_block* b, const void* yv, const void* dy, void* dx0, float
   return DNB_OK;
 }
 
+// fp32 with a bottleneck, rows of 16-byte vectors: program order on the caller's stream, four chain
+// launches per layer (dnb_bwd_f32.hip) and one for both weight gradients, which also carries the sums of
+// the layer before.  The shared schedule re-populates its storages as described at dnb_block_backward.
+int backward_f32(dnb_block* b, const float* params, const float* y, const float* dy, float* dx0, float* dparams, char* ws,
+                 hipStream_t st) {
+  const dnb_block_desc& d = b->d;
+  const int n = d.n, m = d.layers, k = d.growth, B = d.bottleneck, hw = (int)b->hw;
+  const bool fused = d.schedule == DNB_SCHED_FUSED, recompute = d.schedule == DNB_SCHED_SHARED;
+  const int64_t ys = (int64_t)b->cout * hw;
+  const float* pack = (const float*)(ws + b->off_pack);  // packed by the forward pass
+  const size_t B16 = (size_t)((B + 15) & ~15), k16 = (size_t)((k + 15) & ~15);
+  float* mean_y = (float*)(ws + b->off_stat_y);
+  float* istd_y = mean_y + b->cout;
+  Bwd32Layer L{};
+  L.n = n; L.h = d.h; L.w = d.w; L.k = k; L.B = B;
+  L.y = y; L.dy = dy; L.ys = ys;
+  L.G = (float*)(ws + b->off_G);
+  L.gl = (float*)(ws + b->off_dS2);  // the gradient of storage 2 is consumed where it is formed: its storage holds g_l
+  L.db = (float*)(ws + b->off_dS3);
+  L.mean_y = mean_y; L.istd_y = istd_y;
+  L.part1 = (float2*)(ws + b->off_part);
+  L.part2 = (float2*)((float*)(ws + b->off_part) + b->part1_floats);
+  L.K = (float2*)(ws + b->off_K);
+  PendingSum pendA, pendB;
+  for (int l = m; l >= 1; --l) {
+    const int c = c_in(d, l);
+    const LayerParams p = layer_ptrs<LayerParams, const float>(b, params, l);
+    const LayerGrads gp = layer_ptrs<LayerGrads, float>(b, dparams, l);
+    float* S1 = (float*)(ws + b->off_u[l]);
+    float* S2 = (float*)(ws + b->off_a[l]);
+    float* S3 = (float*)(ws + b->off_a2[l]);
+    const float* bl = (const float*)(ws + b->off_b[l]);
+    float* mean_b = (float*)(ws + b->off_stat_b[l]);
+    const size_t c16 = (size_t)((c + 15) & ~15);
+    L.c = c;
+    L.last = l == m;
+    L.b = bl;
+    L.x = fused ? y : S1; L.x_stride = fused ? ys : (int64_t)c * hw;
+    L.pk1t = pack + b->pk[l] + B16 * c16;
+    L.pk3t = pack + b->pk[l] + 2 * B16 * c16 + 9 * k16 * B16;
+    L.g1 = p.g1; L.b1 = p.b1; L.g2 = p.g2; L.b2 = p.b2;
+    L.mean_b = mean_b; L.istd_b = mean_b + B;
+    L.dgamma1 = gp.g1; L.dbeta1 = gp.b1;
+    int T2 = 0;
+    DNB_TRY(bwd32_dgrad3(L, &T2, st));
+    DNB_TRY(launch_bn_bwd_apply(bl, (int64_t)B * hw, L.db, (int64_t)B * hw, L.db, (int64_t)B * hw, n, B, hw, p.g2, p.b2, mean_b,
+                                mean_b + B, gp.g2, gp.b2, (const float*)L.part2, T2, st));
+    if (recompute) {
+      DNB_TRY(launch_bn_relu(bl, (int64_t)B * hw, S3, (int64_t)B * hw, nullptr, 0, n, B, hw, p.g2, p.b2,
+                             StatsSrc{mean_b, mean_b + B, nullptr, 0, 0, 0, d.eps}, st));
+      DNB_TRY(launch_bn_relu(y, ys, S2, (int64_t)c * hw, S1, (int64_t)c * hw, n, c, hw, p.g1, p.b1,
+                             StatsSrc{mean_y, istd_y, nullptr, 0, 0, 0, d.eps}, st));
+    }
+    DNB_TRY(bwd32_dgrad1(L, st));
+    const float* gl = l == m ? dy + (int64_t)c * hw : L.gl;
+    Bn1Finish fin;
+    bwd32_bn1_finish(L, &fin);
+    DNB_TRY(launch_conv_wgrad_pair(fused ? y : S2, fused ? ys : (int64_t)c * hw, L.db, (int64_t)B * hw, gp.W1, c,
+                                   (float*)(ws + b->off_partB) + (size_t)(l & 1) * b->partB_floats,
+                                   fused ? (const float2*)(ws + b->off_fold1[l]) : nullptr, fused ? bl : S3, (int64_t)B * hw, gl,
+                                   l == m ? ys : (int64_t)k * hw, gp.W3, k,
+                                   (float*)(ws + b->off_partA) + (size_t)(l & 1) * b->partA_floats,
+                                   fused ? (const float2*)(ws + b->off_fold2[l]) : nullptr, n, B, d.h, d.w, st, &pendB, &pendA, nullptr,
+                                   nullptr, nullptr, nullptr, nullptr, &fin));
+  }
+  DNB_TRY(launch_pending_sum(&pendA, st));
+  DNB_TRY(launch_pending_sum(&pendB, st));
+  DNB_TRY(bwd32_dx0(L, dx0, st));
+  return DNB_OK;
+}
+
 // ---- fp32 NCHW without a bottleneck: each layer is BN -> ReLU -> 3x3 conv on the concatenation
 // (the composite function as first defined, Section 2 "Dense connectivity").  Storage 1 and 2 are
 // used exactly as with a bottleneck; there is no storage 3 and no kept b_l.  The 
@@ -535,6 +606,15 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
       need(conv_stats_partial_floats(d.n, B, d.h, d.w));  // epilogue statistics of the two convs
     }
     need(conv_stats_partial_floats(d.n, k, d.h, d.w));
+    if (B > 0 && bwd32_ok(d.n, d.h, d.w, k, B)) {
+      size_t p1 = 0;
+      for (int l = 1; l <= m; ++l) {
+        const size_t f1 = bwd32_partial1_floats(d.n, (int)hw, c_in(d, l));
+        if (f1 > p1) p1 = f1;
+      }
+      b->part1_floats = p1;
+      need(p1 + bwd32_partial2_floats(d.n, d.h, d.w, B));
+    }
     for (int l = 1; l <= m; ++l) {
       need(bn_bwd_partial_floats(d.n, c_in(d, l), (int)hw));
       const size_t f = B > 0 ? conv_wgrad_partial_floats(d.n, c_in(d, l), B, d.h, d.w, 1) : 0;
@@ -552,7 +632,7 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
       for (int l = 1; l <= m; ++l) { b->pk[l] = pack; pack += packed_layer_floats(c_in(d, l), k, B); }
     }
   }
-  const size_t kf = bf16 ? (size_t)cout * 2 : 0;
+  const size_t kf = B > 0 ? (size_t)cout * 2 : 0;
   mem.scratch_bytes = (uint64_t)(part + 2 * (partA + partB) + pack + kf) * sizeof(float);
   b->off_part = carve(part * sizeof(float), false);
   // two buffers each, used alternately by consecutive layers (a layer's partials are
@@ -764,6 +844,9 @@ int dnb_block_backward(dnb_block* b, const void* paramsv, const void* yv, const 
   if (d.bottleneck == 0)
     return backward_plain3x3(b, (const float*)paramsv, (const float*)yv, (const float*)dyv, (float*)dx0v,
                              (float*)dparamsv, (char*)wsv, st);
+  if (bwd32_ok(d.n, d.h, d.w, d.growth, d.bottleneck))
+    return backward_f32(b, (const float*)paramsv, (const float*)yv, (const float*)dyv, (float*)dx0v, (float*)dparamsv,
+                        (char*)wsv, st);
   const int n = d.n, m = d.layers, k = d.growth, B = d.bottleneck, hw = (int)b->hw;
   const bool recompute = d.schedule == DNB_SCHED_SHARED;
   const bool fused = d.schedule == DNB_SCHED_FUSED;

@@ -1,0 +1,241 @@
+// fp32 / NCHW backward chain of a bottleneck layer, the part behind the 3x3 data gradient:
+//
+//   k_dgrad3_v4 / _v3         (dnb_conv_f32_fast.hip) 3x3 data gradient, BN2's mask and sums
+//   k_bn_bwd_apply            gradient of b_l, element-wise on P x B
+//   k_dgrad1                  1x1 data gradient; BN1+ReLU backward and the concatenation's backward
+//                             (accumulate into the slab G) in the epilogue, with BN1's two sums
+//   k_wgrad_pair              both weight gradients, the end of this BN1 (bn1_finish_body) and the sums of
+//                             the previous layer's weight-gradient partials
+//
+// BN1's backward is  du = s*(dz - dbeta/P - xhat*dgamma/P),  dz = the masked gradient, s = gamma*istd.
+// Its first term needs no sum, so it is added into the slab where dz is formed; the other two are
+// constants per channel times 1 and xhat, and xhat does not depend on the layer.  They are collected per
+// channel, K0 = sum_l s_l*dbeta_l/P and K1 = sum_l s_l*dgamma_l/P, and taken off once, where a slice of
+// the slab is finally read:  g = G - K0 - K1*xhat.  Per layer that is 12 bytes per element of the
+// concatenated input (x, G read, G write) instead of 36 (gradient written; read with x by the reduction;
+// read with x and G by the element-wise pass, G written), and five launches per layer instead of six or seven.
+// DenseNet-BC-100 step 5.25 -> 4.92 ms (fused), 6.54 -> 6.20 ms (shared), DenseNet-BC-250 45.0 -> 42.5 ms.  What
+// is left: the 3x3 data gradient, 20 us with the correction and BN2's sums against 15 without on the first block of
+// BC-100 (its 108 weight registers leave none for prefetching), and k_dgrad1 at 2.3 to 3.4 TB/s.
+#include "dnb_f32_dev.h"
+#include "dnb_internal.h"
+#include "dnb_stats.h"
+
+namespace dnb {
+
+namespace {
+
+struct Dgrad1Args {
+  const float* db; int64_t db_stride; int B;  // gradient of b_l
+  const float* W; int C16, B16;               // packed weights [C16][B16]
+  const float* x; int64_t x_stride;           // concatenated features
+  const float* dy; float* G; int64_t g_stride;  // slab; dy replaces its first read (FIRST)
+  const float *gamma, *beta, *mean, *istd;
+  float2* part1; int C, T;                    // out [C][T]
+  int hw, tpi, tiles, nwm;
+};
+
+// Output channels on M, pixels on N; bound by the slab's traffic (12 bytes per element against 2*B
+// flops).  A wave owns 32 channels (two M-tiles) and walks over 64-pixel tiles T apart: a lane holds 4
+// consecutive pixels of 8 channels, so x and the slab move in 16-byte pieces, 256 contiguous bytes per
+// channel.  The waves of a workgroup take neighbouring channels of the same tile (the db rows they share
+// come from L1) or, where there are few channels, other tiles; they share nothing else, the sums stay in
+// registers until a wave's last tile.
+// NCH: 16-channel chunks of b_l whose weights stay in registers; 0: read in the loop.
+template <int NCH, bool FIRST>
+__global__ __launch_bounds__(256, 2) void k_dgrad1(Dgrad1Args A) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = lane & 15, g = lane >> 4;
+  const int wm = wave % A.nwm, wp = wave / A.nwm, nwp = 4 / A.nwm;
+  const int m0 = ((int)blockIdx.y * A.nwm + wm) * 32, t0 = (int)blockIdx.x * nwp + wp;
+  if (m0 >= A.C || t0 >= A.T) return;
+  const int HW = A.hw, nch = A.B16 >> 4;
+  const int mt[2] = {m0 >> 4, min((m0 >> 4) + 1, (A.C16 >> 4) - 1)};
+  constexpr int KR = NCH > 0 ? NCH : 1;
+  float4 w[2][KR];
+  if (NCH > 0) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int c = 0; c < KR; ++c) w[a][c] = ldg4(wfrag(A.W, A.B16, mt[a], c));
+  }
+  float sc[2][4], sf[2][4], mu[2][4], s0[2][4], s1[2][4];
+  auto ch = [&](int a, int r) { return min(m0 + a * 16 + 4 * g + r, A.C - 1); };
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int c = ch(a, r);
+      mu[a][r] = A.mean[c];
+      bn_fold(A.gamma[c], A.beta[c], mu[a][r], A.istd[c], sc[a][r], sf[a][r]);
+      s0[a][r] = s1[a][r] = 0.f;
+    }
+
+  for (int tile = t0; tile < A.tiles; tile += A.T) {
+    const int img = tile / A.tpi, q = (tile - img * A.tpi) * 64 + 4 * j;
+    const bool ok = q < HW;  // HW % 4 == 0: a lane's four pixels are in or out together
+    const int qc = ok ? q : 0;
+    const float* dbp = A.db + (int64_t)img * A.db_stride + qc;
+    const float* xp = A.x + (int64_t)img * A.x_stride + qc;
+    const float* rp = (FIRST ? A.dy : A.G) + (int64_t)img * A.g_stride + qc;
+    float4 d[KR][4], x4[2][4], g4[2][4];
+    if (NCH > 0) {
+#pragma unroll
+      for (int c = 0; c < KR; ++c)
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) d[c][ks] = ldg4(dbp + (int64_t)min(c * 16 + 4 * ks + g, A.B - 1) * HW);
+    }
+    auto load_slab = [&](int a) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        x4[a][r] = ldg4(xp + (int64_t)ch(a, r) * HW);
+        g4[a][r] = ldg4(rp + (int64_t)ch(a, r) * HW);
+      }
+    };
+    load_slab(0);
+    if (NCH > 0) load_slab(1);  // (beside the chunk ring of the other form there are registers for one half)
+    f32x4 acc[2][4];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc[a][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    auto products = [&](const float4(&dd)[4], const float4& w0, const float4& w1) {
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          acc[0][t] = mfma16(elem(w0, ks), elem(dd[ks], t), acc[0][t]);
+          acc[1][t] = mfma16(elem(w1, ks), elem(dd[ks], t), acc[1][t]);
+        }
+    };
+    if (NCH > 0) {
+#pragma unroll
+      for (int c = 0; c < KR; ++c) products(d[c], w[0][c], w[1][c]);
+    } else {
+      float4 da[2][4], wa[2][2];  // two chunks in flight
+      auto load = [&](int c, float4(&dd)[4], float4(&ww)[2]) {
+        c = min(c, nch - 1);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) dd[ks] = ldg4(dbp + (int64_t)min(c * 16 + 4 * ks + g, A.B - 1) * HW);
+        ww[0] = ldg4(wfrag(A.W, A.B16, mt[0], c));
+        ww[1] = ldg4(wfrag(A.W, A.B16, mt[1], c));
+      };
+      load(0, da[0], wa[0]);
+      load(1, da[1], wa[1]);
+      for (int c = 0; c < nch; c += 2) {
+        products(da[0], wa[0][0], wa[0][1]);
+        load(c + 2, da[0], wa[0]);
+        if (c + 1 < nch) products(da[1], wa[1][0], wa[1][1]);
+        load(c + 3, da[1], wa[1]);
+      }
+      load_slab(1);
+    }
+    if (ok) {
+      float* op = A.G + (int64_t)img * A.g_stride + q;
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          float o[4];
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const float xv = elem(x4[a][r], t), dz = __fmaf_rn(xv, sc[a][r], sf[a][r]) > 0.f ? acc[a][t][r] : 0.f;
+            o[t] = __fmaf_rn(sc[a][r], dz, elem(g4[a][r], t));
+            s0[a][r] += dz;
+            s1[a][r] = __fmaf_rn(dz, xv - mu[a][r], s1[a][r]);
+          }
+          if (m0 + a * 16 + 4 * g + r < A.C)
+            *reinterpret_cast<float4*>(op + (int64_t)ch(a, r) * HW) = make_float4(o[0], o[1], o[2], o[3]);
+        }
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float u = row16_sum(s0[a][r]), v = row16_sum(s1[a][r]);
+      const int m = m0 + a * 16 + 4 * g + r;
+      if (j == 0 && m < A.C) A.part1[(int64_t)m * A.T + t0] = make_float2(u, v * A.istd[m]);
+    }
+}
+
+// dx0 = G - K0 - K1*xhat on the block input's channels.  grid (channels, image ranges), 16-byte accesses.
+__global__ __launch_bounds__(256) void k_dx0(const float* __restrict__ G, int64_t g_stride, const float* __restrict__ x,
+                                             int64_t x_stride, float* __restrict__ dx0, int64_t d_stride, int n, int hw,
+                                             int ipb, const float2* __restrict__ K, const float* __restrict__ mean,
+                                             const float* __restrict__ istd) {
+  const int ch = blockIdx.x, n0 = blockIdx.y * ipb, ni = min(n, n0 + ipb) - n0;
+  const float k0 = K[ch].x, k1 = K[ch].y * istd[ch], mu = mean[ch];
+  const int64_t inner = (int64_t)ch * hw;
+  for (RowIter it(hw / 4, threadIdx.x, 256); it.img < ni; it.next()) {
+    const int64_t im = n0 + it.img, q = inner + (int64_t)it.q * 4;
+    const float4 gv = ldg4(G + im * g_stride + q), xv = ldg4(x + im * x_stride + q);
+    *reinterpret_cast<float4*>(dx0 + im * d_stride + q) =
+        make_float4((gv.x - k0) - k1 * (xv.x - mu), (gv.y - k0) - k1 * (xv.y - mu), (gv.z - k0) - k1 * (xv.z - mu),
+                    (gv.w - k0) - k1 * (xv.w - mu));
+  }
+}
+
+__global__ __launch_bounds__(256) void k_bn1_finish(Bn1Finish f) { bn1_finish_body(f, blockIdx.x); }
+
+}  // namespace
+
+// Pixel ranges of k_dgrad1 (= partial pairs per channel): about 2048 waves in all (two per SIMD), at most
+// one tile each.
+int bwd32_dgrad1_splits(int n, int hw, int c) {
+  const int64_t tiles = (int64_t)((hw + 63) / 64) * n, groups = (c + 31) / 32;
+  int64_t t = 2048 / groups;
+  if (t > 512) t = 512;
+  if (t > tiles) t = tiles;
+  return t < 1 ? 1 : (int)t;
+}
+size_t bwd32_partial1_floats(int n, int hw, int c) { return 2 * (size_t)c * bwd32_dgrad1_splits(n, hw, c); }
+
+hipError_t bwd32_dgrad1(const Bwd32Layer& L, hipStream_t st) {
+  Dgrad1Args A{};
+  const int hw = L.h * L.w, groups = (L.c + 31) / 32;
+  A.db = L.db; A.db_stride = (int64_t)L.B * hw; A.B = L.B;
+  A.W = L.pk1t; A.C16 = (L.c + 15) & ~15; A.B16 = (L.B + 15) & ~15;
+  A.x = L.x; A.x_stride = L.x_stride;
+  A.dy = L.dy; A.G = L.G; A.g_stride = L.ys;
+  A.gamma = L.g1; A.beta = L.b1; A.mean = L.mean_y; A.istd = L.istd_y;
+  A.part1 = L.part1; A.C = L.c; A.T = bwd32_dgrad1_splits(L.n, hw, L.c);
+  A.hw = hw; A.tpi = (hw + 63) / 64; A.tiles = A.tpi * L.n;
+  A.nwm = groups >= 3 ? 4 : groups;
+  const int nwp = 4 / A.nwm;
+  const dim3 grid((unsigned)((A.T + nwp - 1) / nwp), (unsigned)((groups + A.nwm - 1) / A.nwm));
+#define DNB_L(NCH)                                                                       \
+  do {                                                                                   \
+    if (L.last) hipLaunchKernelGGL((k_dgrad1<NCH, true>), grid, dim3(256), 0, st, A);    \
+    else hipLaunchKernelGGL((k_dgrad1<NCH, false>), grid, dim3(256), 0, st, A);          \
+  } while (0)
+  switch (A.B16 >> 4) {
+    case 1: DNB_L(1); break; case 2: DNB_L(2); break; case 3: DNB_L(3); break; default: DNB_L(0); break;
+  }
+#undef DNB_L
+  return hipGetLastError();
+}
+
+void bwd32_bn1_finish(const Bwd32Layer& L, Bn1Finish* out) {
+  const int hw = L.h * L.w;
+  *out = Bn1Finish{L.part1, bwd32_dgrad1_splits(L.n, hw, L.c), L.c, (L.c + 3) / 4, L.g1, L.istd_y,
+                   1.0f / ((float)L.n * (float)hw), L.K, L.last ? 1 : 0, L.dgamma1, L.dbeta1};
+}
+hipError_t launch_bn1_finish(const Bn1Finish& f, hipStream_t st) {
+  if (f.wgs == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_bn1_finish, dim3((unsigned)f.wgs), dim3(256), 0, st, f);
+  return hipGetLastError();
+}
+
+hipError_t bwd32_dx0(const Bwd32Layer& L, float* dx0, hipStream_t st) {
+  const int hw = L.h * L.w;
+  int s = 1024 / L.c, cap = (L.n * (hw / 4) + 255) / 256;  // at least one position per thread
+  if (s > cap) s = cap;
+  if (s > L.n) s = L.n;
+  if (s < 1) s = 1;
+  const int ipb = (L.n + s - 1) / s;
+  hipLaunchKernelGGL(k_dx0, dim3((unsigned)L.c, (unsigned)((L.n + ipb - 1) / ipb)), dim3(256), 0, st, L.G, L.ys, L.y, L.ys, dx0,
+                     (int64_t)L.c * hw, L.n, hw, ipb, (const float2*)L.K, L.mean_y, L.istd_y);
+  return hipGetLastError();
+}
+
+}  // namespace dnb

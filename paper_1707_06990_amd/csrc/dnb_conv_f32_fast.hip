@@ -287,6 +287,36 @@ __global__ __launch_bounds__(256) void k_conv1x1_v3(
   }
 }
 
+// ---- what the 3x3 data gradient does beside the convolution in the backward chain (BWD): its input is a
+// slice of the gradient slab, from which the mean terms of the later layers' BN1 backward are taken off
+// while it is staged (see dnb_bwd_f32.hip), and its epilogue masks the result by BN2's ReLU and forms
+// BN2's two sums.
+struct Bwd3Args {
+  const float* x; int64_t x_stride;      // features at the slice's first channel
+  const float2* K;                       // K0, K1 at the slice; null: last layer, no correction
+  const float *mean, *istd;              // statistics of the slice's features
+  float* gl; int64_t gl_stride;          // out: the corrected slice
+  const float* b; int64_t b_stride;      // b_l
+  const float *g2, *b2, *mean_b, *istd_b;
+  float2* part2; int T2;                 // out: BN2's sums, [B][T2]
+};
+constexpr int kBwdMaxK = 128;  // channels of a slice whose coefficients are kept in LDS
+
+// coef = K0, K1*istd, mean of the slice's channels (a barrier must follow)
+__device__ __forceinline__ void bwd_coefs(const Bwd3Args& A, int k, float (*coef)[kBwdMaxK]) {
+  for (int ch = threadIdx.x; ch < k; ch += blockDim.x) {
+    const float2 K = A.K[ch];
+    coef[0][ch] = K.x;
+    coef[1][ch] = K.y * A.istd[ch];
+    coef[2][ch] = A.mean[ch];
+  }
+}
+__device__ __forceinline__ float bwd_corr(float g, float x, float k0, float k1, float mu) { return (g - k0) - k1 * (x - mu); }
+__device__ __forceinline__ float4 bwd_corr4(float4 g, float4 x, float k0, float k1, float mu) {
+  return make_float4(bwd_corr(g.x, x.x, k0, k1, mu), bwd_corr(g.y, x.y, k0, k1, mu), bwd_corr(g.z, x.z, k0, k1, mu),
+                     bwd_corr(g.w, x.w, k0, k1, mu));
+}
+
 // ------------------------------------------------------------------------------- 3x3, fwd/dgrad
 //
 // The workgroup owns 64 consecutive pixels of one image.  ALL input channels of that pixel
@@ -298,15 +328,20 @@ __global__ __launch_bounds__(256) void k_conv1x1_v3(
 // (W is a multiple of 4), which are masked.  Waves split K (forward: 9*B long K, k outputs)
 // or M (data gradient: k*9 short K, B outputs) as in the 1x1 kernel; packed weights come
 // from L2, 16 bytes per lane per (tap, chunk).
-template <int MT, bool KSPLIT, bool PRO, bool STATS>
-__global__ __launch_bounds__(256) void k_conv3x3_v3(
+template <int MT, bool KSPLIT, bool PRO, bool STATS, bool BWD>
+__device__ __forceinline__ void conv3x3_v3_body(
     const float* __restrict__ in, int64_t in_stride, const float* __restrict__ Wp, int Mpad,
     int Kpad, float* __restrict__ out, int64_t out_stride, int cin, int cout, int H, int W, int CS,
-    const float2* __restrict__ fold, float* __restrict__ spart, int sT) {
+    const float2* __restrict__ fold, float* __restrict__ spart, int sT, const Bwd3Args& bw) {
   extern __shared__ float lds[];
+  __shared__ float coef[3][BWD ? kBwdMaxK : 1];
   const int HW = H * W;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nthr = blockDim.x, nw = nthr >> 6;
   const int j = lane & 15, g = lane >> 4;
+  if constexpr (BWD) {
+    if (bw.K) bwd_coefs(bw, cin, coef);
+    __syncthreads();
+  }
   const int q0 = blockIdx.x * 64, img = blockIdx.z;
   const int origin = q0 - W - 4;
   const int seg4 = (64 + 2 * W + 8) >> 2;
@@ -324,7 +359,7 @@ __global__ __launch_bounds__(256) void k_conv3x3_v3(
   const int total = rows * seg4;
   constexpr int U = 8;
   for (int base = 0; base < total; base += nthr * U) {
-    float4 v[U];
+    float4 v[U], xv[BWD ? U : 1];
     float2 f[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -333,6 +368,8 @@ __global__ __launch_bounds__(256) void k_conv3x3_v3(
       const int qq = origin + 4 * (idx % seg4);
       v[u] = ldg4(inb + (int64_t)row * HW + min(max(qq, 0), HW - 4));
       if (PRO) f[u] = fold[row];
+      if constexpr (BWD)
+        if (bw.K) xv[u] = ldg4(bw.x + (int64_t)img * bw.x_stride + (int64_t)row * HW + min(max(qq, 0), HW - 4));
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -344,6 +381,14 @@ __global__ __launch_bounds__(256) void k_conv3x3_v3(
       if (PRO) {  // BN + ReLU on the way in; the zero padding stays zero
         x.x = fmaxf(__fmaf_rn(x.x, f[u].x, f[u].y), 0.f); x.y = fmaxf(__fmaf_rn(x.y, f[u].x, f[u].y), 0.f);
         x.z = fmaxf(__fmaf_rn(x.z, f[u].x, f[u].y), 0.f); x.w = fmaxf(__fmaf_rn(x.w, f[u].x, f[u].y), 0.f);
+      }
+      if constexpr (BWD) {
+        if (bw.K) {
+          const int rc = min(row, cin - 1);
+          x = bwd_corr4(x, xv[u], coef[0][rc], coef[1][rc], coef[2][rc]);
+          if (ok && idx < total && blockIdx.y == 0 && qq >= q0 && qq < q0 + 64)
+            *reinterpret_cast<float4*>(bw.gl + (int64_t)img * bw.gl_stride + (int64_t)row * HW + qq) = x;
+        }
       }
       if (!ok) x = zero4();
       if (idx < total) *reinterpret_cast<float4*>(&lds[row * CS + 4 * c4]) = x;
@@ -420,6 +465,26 @@ __global__ __launch_bounds__(256) void k_conv3x3_v3(
     if (STATS)
       tile_stats<4>(acc[a], q < HW, (float)tile_px, mbase + a * 16, cout, spart, sT,
                     img * gridDim.x + blockIdx.x);
+    if constexpr (BWD) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = mbase + a * 16 + 4 * g + r, mc = min(m, cout - 1);
+        const float4 b4 = ldg4(bw.b + (int64_t)img * bw.b_stride + (int64_t)mc * HW + min(q, HW - 4));
+        const float mu = bw.mean_b[mc], is = bw.istd_b[mc];
+        float sc, sf, s0 = 0.f, s1 = 0.f;
+        bn_fold(bw.g2[mc], bw.b2[mc], mu, is, sc, sf);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const float b = elem(b4, t), dz = q < HW && __fmaf_rn(b, sc, sf) > 0.f ? acc[a][t][r] : 0.f;
+          acc[a][t][r] = dz;
+          s0 += dz;
+          s1 = __fmaf_rn(dz, b - mu, s1);
+        }
+        s0 = row16_sum(s0);
+        s1 = row16_sum(s1);
+        if (j == 0 && m < cout) bw.part2[(int64_t)m * bw.T2 + img * gridDim.x + blockIdx.x] = make_float2(s0, s1 * is);
+      }
+    }
     if (q < HW) {
       float* ob = out + (int64_t)img * out_stride + q;
 #pragma unroll
@@ -431,6 +496,21 @@ __global__ __launch_bounds__(256) void k_conv3x3_v3(
       }
     }
   }
+}
+
+template <int MT, bool KSPLIT, bool PRO, bool STATS>
+__global__ __launch_bounds__(256) void k_conv3x3_v3(const float* in, int64_t in_stride, const float* Wp, int Mpad, int Kpad,
+                                                    float* out, int64_t out_stride, int cin, int cout, int H, int W, int CS,
+                                                    const float2* fold, float* spart, int sT) {
+  conv3x3_v3_body<MT, KSPLIT, PRO, STATS, false>(in, in_stride, Wp, Mpad, Kpad, out, out_stride, cin, cout, H, W, CS, fold,
+                                                 spart, sT, Bwd3Args{});
+}
+template <int MT>
+__global__ __launch_bounds__(256) void k_dgrad3_v3(const float* in, int64_t in_stride, const float* Wp, int Mpad, int Kpad,
+                                                   float* out, int64_t out_stride, int cin, int cout, int H, int W, int CS,
+                                                   Bwd3Args bw) {
+  conv3x3_v3_body<MT, false, false, false, true>(in, in_stride, Wp, Mpad, Kpad, out, out_stride, cin, cout, H, W, CS, nullptr,
+                                                 nullptr, 0, bw);
 }
 
 // ------------------------------------------------------------------------------- 3x3, persistent
@@ -448,18 +528,21 @@ __global__ __launch_bounds__(256) void k_conv3x3_v3(
 //   * the image width is a template parameter and every staged image row keeps a 4-float zero gap
 //     in front of it, so a tap is one LDS read at a compile-time offset from a single per-lane
 //     base -- no edge masks and no address arithmetic between the MFMAs;
-//   * two interleaved accumulators per M-tile break the MFMA dependence chain.
+//   * three M-tiles, or two interleaved accumulators per M-tile, break the MFMA dependence chain.
 // LDS is addressed through lds[] with integer offsets only (generic pointers to LDS must not be
 // formed here: loads through them become flat instructions).
 // Workgroup b takes tiles of its own contiguous range (consecutive workgroups sit on different
 // XCDs: each XCD's workgroups share halo rows through that XCD's L2).
-template <int MT, int NCH, int W, bool PRO, bool STATS>
-__global__ __launch_bounds__(256) void k_conv3x3_v4(
+template <int MT, int NCH, int W, bool PRO, bool STATS, bool BWD>
+__device__ __forceinline__ void conv3x3_v4_body(
     const float* __restrict__ in, int64_t in_stride, const float* __restrict__ Wp, int Mpad,
     int Kpad, float* __restrict__ out, int64_t out_stride, int cin, int cout, int H,
     const float2* __restrict__ fold, float* __restrict__ spart, int sT, int tiles_per_img,
-    int total_tiles) {
+    int total_tiles, const Bwd3Args& bw) {
   extern __shared__ float lds[];
+  __shared__ float coef[3][BWD ? kBwdMaxK : 1];          // the slice's correction
+  __shared__ float4 cb[BWD ? MT * 16 : 1];               // BN2's scale, shift, mean
+  __shared__ float2 bsum[BWD ? 4 * MT * 16 : 1];
   constexpr int ROWS = NCH * 16;             // staged channel planes
   constexpr int RW = W + 4, TR = 64 / W;     // LDS pitch of an image row; image rows per tile
   constexpr int NR = TR + 2, W4 = W / 4;     // staged image rows (one of halo above and below)
@@ -480,6 +563,9 @@ __global__ __launch_bounds__(256) void k_conv3x3_v4(
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   const int t_lo = xcd * tpx, t_hi = min(total_tiles, t_lo + tpx);
   int tile = t_lo + slot;
+  if constexpr (BWD) {
+    if (tile >= t_hi && tid < cout) bw.part2[(int64_t)tid * bw.T2 + blockIdx.x] = make_float2(0.f, 0.f);
+  }
   if (tile >= t_hi) return;  // uniform for the workgroup
 
   // staging slots of this thread: the same (plane, image row, 4-pixel column) in every tile
@@ -495,6 +581,7 @@ __global__ __launch_bounds__(256) void k_conv3x3_v4(
     slo[u] = sch[u] * CS + sry[u] * RW + 4 + sgo[u];
     sfold[u] = (PRO && sch[u] < cin) ? fold[sch[u]] : make_float2(1.f, 0.f);
   }
+  float4 xv[BWD ? U : 1];  // BWD: features at the staged positions, requested with them
   auto request = [&](int tl, float4(&v)[U]) {
     const int img = tl / tiles_per_img, y0 = (tl - img * tiles_per_img) * TR;
     const float* inb = in + (int64_t)img * in_stride;
@@ -502,6 +589,9 @@ __global__ __launch_bounds__(256) void k_conv3x3_v4(
     for (int u = 0; u < U; ++u) {
       const int y = min(max(y0 - 1 + sry[u], 0), H - 1);
       v[u] = ldg4(inb + (int64_t)min(sch[u], cin - 1) * HW + y * W + sgo[u]);
+      if constexpr (BWD)
+        if (bw.K)
+          xv[u] = ldg4(bw.x + (int64_t)img * bw.x_stride + (int64_t)min(sch[u], cin - 1) * HW + y * W + sgo[u]);
     }
   };
   auto deposit = [&](int tl, const float4(&v)[U], int boff) {
@@ -513,6 +603,14 @@ __global__ __launch_bounds__(256) void k_conv3x3_v4(
       if (PRO) {
         x.x = fmaxf(__fmaf_rn(x.x, sfold[u].x, sfold[u].y), 0.f); x.y = fmaxf(__fmaf_rn(x.y, sfold[u].x, sfold[u].y), 0.f);
         x.z = fmaxf(__fmaf_rn(x.z, sfold[u].x, sfold[u].y), 0.f); x.w = fmaxf(__fmaf_rn(x.w, sfold[u].x, sfold[u].y), 0.f);
+      }
+      if constexpr (BWD) {
+        if (bw.K) {
+          const int rc = min(sch[u], cin - 1);
+          x = bwd_corr4(x, xv[u], coef[0][rc], coef[1][rc], coef[2][rc]);
+          if (sch[u] < cin && sry[u] >= 1 && sry[u] <= TR && u * 256 + tid < TOTAL)  // the tile's own rows (H % TR == 0)
+            *reinterpret_cast<float4*>(bw.gl + (int64_t)img * bw.gl_stride + (int64_t)sch[u] * HW + y * W + sgo[u]) = x;
+        }
       }
       if (!(sch[u] < cin && y >= 0 && y < H)) x = zero4();  // channel tail, rows above / below the image
       if (u * 256 + tid < TOTAL) *reinterpret_cast<float4*>(&lds[boff + slo[u]]) = x;
@@ -538,6 +636,20 @@ __global__ __launch_bounds__(256) void k_conv3x3_v4(
   // the gaps between staged rows (and the pitch padding) stay zero for the whole kernel
   for (int i = tid; i < 2 * BUF / 4; i += 256) *reinterpret_cast<float4*>(&lds[4 * i]) = zero4();
 
+  float2 bs[BWD ? MT : 1][4];  // this lane's part of BN2's sums
+  if constexpr (BWD) {
+    if (bw.K) bwd_coefs(bw, cin, coef);
+    for (int i = tid; i < MT * 16; i += 256) {
+      const int m = min(i, cout - 1);
+      float sc, sf;
+      bn_fold(bw.g2[m], bw.b2[m], bw.mean_b[m], bw.istd_b[m], sc, sf);
+      cb[i] = make_float4(sc, sf, bw.mean_b[m], bw.istd_b[m]);
+    }
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) bs[a][r] = make_float2(0.f, 0.f);
+  }
   __syncthreads();  // zero fill done before the first rows land
   deposit(tile, v0, 0);
   __syncthreads();
@@ -553,10 +665,14 @@ __global__ __launch_bounds__(256) void k_conv3x3_v4(
     const bool more = nxt < t_hi;
     float4 vn[U];
     if (more) request(nxt, vn);
+    const int img = tile / tiles_per_img, q = (tile - img * tiles_per_img) * 64 + p;
 
-    f32x4 acc[MT][2];
+    constexpr int NA = MT >= 3 ? 1 : 2;  // accumulators per M-tile
+    f32x4 acc[MT][NA];
 #pragma unroll
-    for (int a = 0; a < MT; ++a) { acc[a][0] = (f32x4){0.f, 0.f, 0.f, 0.f}; acc[a][1] = (f32x4){0.f, 0.f, 0.f, 0.f}; }
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+      for (int i = 0; i < NA; ++i) acc[a][i] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ci = 0; ci < NCH; ++ci) {
 #pragma unroll
@@ -569,21 +685,37 @@ __global__ __launch_bounds__(256) void k_conv3x3_v4(
             const float b = lds[boff + lane_base + (ci * 16 + 4 * ks) * CS + di * RW + dj];
 #pragma unroll
             for (int a = 0; a < MT; ++a) {
-              acc[a][ks & 1] = mfma16(elem(w4[t][ci][a], ks), b, acc[a][ks & 1]);
+              acc[a][ks % NA] = mfma16(elem(w4[t][ci][a], ks), b, acc[a][ks % NA]);
             }
           }
         }
       }
     }
 
+    float braw[BWD ? MT : 1][4];  // (requested here: before the products there are no registers for them)
+    if constexpr (BWD) {
+#pragma unroll
+      for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          braw[a][r] = bw.b[(int64_t)img * bw.b_stride + (int64_t)min(a * 16 + 4 * g + r, cout - 1) * HW + q];
+    }
     // epilogue of this wave's 16 pixels (all inside the image: HW is a multiple of 64)
-    const int img = tile / tiles_per_img, q = (tile - img * tiles_per_img) * 64 + p;
 #pragma unroll
     for (int a = 0; a < MT; ++a) {
       if (a * 16 >= Mpad) continue;
       float v[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) v[r] = acc[a][0][r] + acc[a][1][r];
+      for (int r = 0; r < 4; ++r) v[r] = NA == 2 ? acc[a][0][r] + acc[a][NA - 1][r] : acc[a][0][r];
+      if constexpr (BWD) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float4 f = cb[a * 16 + 4 * g + r];
+          v[r] = __fmaf_rn(braw[a][r], f.x, f.y) > 0.f ? v[r] : 0.f;
+          bs[a][r].x += v[r];
+          bs[a][r].y = __fmaf_rn(v[r], braw[a][r] - f.z, bs[a][r].y);
+        }
+      }
       if (STATS) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -618,6 +750,38 @@ __global__ __launch_bounds__(256) void k_conv3x3_v4(
       o[0] = r.c; o[1] = r.m; o[2] = r.m2;
     }
   }
+  if constexpr (BWD) {
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float u = row16_sum(bs[a][r].x), v = row16_sum(bs[a][r].y);
+        if (j == 0) bsum[wave * (MT * 16) + a * 16 + 4 * g + r] = make_float2(u, v);
+      }
+    __syncthreads();
+    if (tid < MT * 16 && tid < cout) {
+      float2 t = bsum[tid];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) { const float2 o = bsum[w * (MT * 16) + tid]; t.x += o.x; t.y += o.y; }
+      bw.part2[(int64_t)tid * bw.T2 + blockIdx.x] = make_float2(t.x, t.y * cb[tid].w);
+    }
+  }
+}
+
+template <int MT, int NCH, int W, bool PRO, bool STATS>
+__global__ __launch_bounds__(256) void k_conv3x3_v4(const float* in, int64_t in_stride, const float* Wp, int Mpad, int Kpad,
+                                                    float* out, int64_t out_stride, int cin, int cout, int H,
+                                                    const float2* fold, float* spart, int sT, int tiles_per_img,
+                                                    int total_tiles) {
+  conv3x3_v4_body<MT, NCH, W, PRO, STATS, false>(in, in_stride, Wp, Mpad, Kpad, out, out_stride, cin, cout, H, fold, spart, sT,
+                                                 tiles_per_img, total_tiles, Bwd3Args{});
+}
+template <int W>
+__global__ __launch_bounds__(256, 2) void k_dgrad3_v4(const float* in, int64_t in_stride, const float* Wp, int Mpad, int Kpad,
+                                                   float* out, int64_t out_stride, int cin, int cout, int H,
+                                                   int tiles_per_img, int total_tiles, Bwd3Args bw) {
+  conv3x3_v4_body<3, 1, W, false, false, true>(in, in_stride, Wp, Mpad, Kpad, out, out_stride, cin, cout, H, nullptr, nullptr,
+                                               0, tiles_per_img, total_tiles, bw);
 }
 
 // A pending sum of partials carried out by extra workgroups of a weight-gradient launch (the
@@ -1038,7 +1202,8 @@ __global__ __launch_bounds__(256) void k_wgrad3x3_fast(Wg3Args A, SumRole sr, in
 // the 1x1 role; 140 registers hold the same code without spilling.
 template <int M1, int C1, int M3, int C3, bool PRO>
 __global__ __launch_bounds__(256, 3) void k_wgrad_pair(Wg1Args A1, int gx1, int gy1, int gz1, int n1, Wg3Args A3, int gy3, int gz3,
-                                                    int n3, SumRole s1, SumRole s3, BnBwdPartialArgs bn, int nbn) {
+                                                    int n3, SumRole s1, SumRole s3, BnBwdPartialArgs bn, int nbn,
+                                                    Bn1Finish fin) {
   int id = blockIdx.x;
   if (id < n1) {
     // Workgroups go to the 8 XCDs in turn (id % 8), each with an L2 of its own.  All the (c, m)
@@ -1068,6 +1233,8 @@ __global__ __launch_bounds__(256, 3) void k_wgrad_pair(Wg1Args A1, int gx1, int 
     return;
   }
   id -= nbn;
+  if (id < fin.wgs) { bn1_finish_body(fin, id); return; }
+  id -= fin.wgs;
   if (id < s1.wgs) { sum_role(s1, id); return; }
   id -= s1.wgs;
   if (id < s3.wgs) sum_role(s3, id);
@@ -1323,6 +1490,75 @@ bool launch_conv_fast(const float* in, int64_t in_stride, const float* packed, f
   return true;
 }
 
+// ---- the 3x3 data gradient of the backward chain (see Bwd3Args)
+
+struct Bwd3Plan {
+  bool v4;
+  int mt, nw, gy, CS, T2;
+  size_t lds;
+};
+static Bwd3Plan plan_bwd3(int n, int h, int w, int k, int B) {
+  Bwd3Plan p{};
+  const int hw = h * w, mtiles = (B + 15) / 16;
+  p.v4 = mtiles == 3 && k <= 16 && (w == 8 || w == 16 || w == 32) && hw % 64 == 0;
+  if (p.v4) {
+    const int64_t tiles = (int64_t)(hw / 64) * n;
+    p.T2 = tiles < kV4Workgroups ? (int)(tiles + 7) / 8 * 8 : kV4Workgroups;
+    p.lds = ((size_t)2 * (16 * 144 + 4)) * sizeof(float);
+    return p;
+  }
+  p.nw = mtiles >= 4 ? 4 : mtiles;
+  p.mt = mtiles > 4 ? 2 : 1;
+  p.gy = (mtiles + p.nw * p.mt - 1) / (p.nw * p.mt);
+  p.CS = pad4mod32(64 + 2 * w + 8);
+  p.lds = (size_t)((k + 3) & ~3) * p.CS * sizeof(float);
+  p.T2 = (hw + 63) / 64 * n;
+  return p;
+}
+bool bwd32_ok(int n, int h, int w, int k, int B) {
+  if (h * w % 4 || w % 4 || k > kBwdMaxK) return false;
+  return plan_bwd3(n, h, w, k, B).lds <= 60 * 1024;
+}
+size_t bwd32_partial2_floats(int n, int h, int w, int B) {
+  const size_t t = (size_t)((h * w + 63) / 64) * n;
+  return 2 * (size_t)B * (t > kV4Workgroups ? t : kV4Workgroups);
+}
+
+hipError_t bwd32_dgrad3(const Bwd32Layer& L, int* T2, hipStream_t st) {
+  const Bwd3Plan p = plan_bwd3(L.n, L.h, L.w, L.k, L.B);
+  const int hw = L.h * L.w, M16 = (L.B + 15) & ~15, K16 = (L.k + 15) & ~15;
+  *T2 = p.T2;
+  Bwd3Args A{};
+  const int64_t so = (int64_t)L.c * hw;  // the slice inside an image
+  const float* in = (L.last ? L.dy : L.G) + so;
+  A.b = L.b; A.b_stride = (int64_t)L.B * hw;
+  A.g2 = L.g2; A.b2 = L.b2; A.mean_b = L.mean_b; A.istd_b = L.istd_b;
+  A.part2 = L.part2; A.T2 = p.T2;
+  if (!L.last) {
+    A.x = L.y + so; A.x_stride = L.ys;
+    A.K = L.K + L.c;
+    A.mean = L.mean_y + L.c; A.istd = L.istd_y + L.c;
+    A.gl = L.gl; A.gl_stride = (int64_t)L.k * hw;
+  }
+  if (p.v4) {
+    const int tpi = hw / 64;
+    const dim3 grid((unsigned)p.T2);
+#define DNB_L(WW)                                                                                                      \
+  hipLaunchKernelGGL((k_dgrad3_v4<WW>), grid, dim3(256), p.lds, st, in, L.ys, L.pk3t, M16, K16, L.db, A.b_stride, L.k,  \
+                     L.B, L.h, tpi, tpi * L.n, A)
+    if (L.w == 32) DNB_L(32); else if (L.w == 16) DNB_L(16); else DNB_L(8);
+#undef DNB_L
+    return hipGetLastError();
+  }
+  const dim3 grid((unsigned)((hw + 63) / 64), (unsigned)p.gy, (unsigned)L.n);
+#define DNB_L(MT)                                                                                                      \
+  hipLaunchKernelGGL((k_dgrad3_v3<MT>), grid, dim3(64 * p.nw), p.lds, st, in, L.ys, L.pk3t, M16, K16, L.db, A.b_stride, \
+                     L.k, L.B, L.h, L.w, p.CS, A)
+  if (p.mt == 2) DNB_L(2); else DNB_L(1);
+#undef DNB_L
+  return hipGetLastError();
+}
+
 // ---- weight gradient plans (shared by the scratch-size query and the launcher)
 
 struct WgFastPlan {
@@ -1496,8 +1732,8 @@ bool launch_wgrad_pair_fast(const float* in1, int64_t in1_stride, const float* g
                             float* dw1, int cin1, const float2* fold1, const float* in3, int64_t in3_stride,
                             const float* g3, int64_t g3_stride, float* part3, float* dw3, int cout3,
                             const float2* fold3, int n, int B, int h, int w, PendingSum* own1, PendingSum* own3,
-                            PendingSum* absorb1, PendingSum* absorb3, const BnBwdPartialArgs* bn, hipStream_t st,
-                            hipEvent_t ev0, hipEvent_t ev1) {
+                            PendingSum* absorb1, PendingSum* absorb3, const BnBwdPartialArgs* bn, const Bn1Finish* fin,
+                            hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
   if ((fold1 != nullptr) != (fold3 != nullptr)) return false;
   if (in1_stride % 4 || g1_stride % 4 || in3_stride % 4 || g3_stride % 4 || !aligned16(in1) || !aligned16(g1) ||
       !aligned16(in3) || !aligned16(g3))
@@ -1513,14 +1749,15 @@ bool launch_wgrad_pair_fast(const float* in1, int64_t in1_stride, const float* g
   const int n1 = (p1.gx + 7) / 8 * 8 * p1.gy * p1.gz, n3 = p3.gx * p3.gy * p3.gz;  // 1x1: whole pixel ranges per XCD
   const BnBwdPartialArgs bna = bn ? *bn : BnBwdPartialArgs{};
   const int nbn = bn ? bn->c * bn->splits : 0;
-  const dim3 grid((unsigned)(n1 + n3 + nbn + s1.wgs + s3.wgs));
+  const Bn1Finish fina = fin ? *fin : Bn1Finish{};
+  const dim3 grid((unsigned)(n1 + n3 + nbn + fina.wgs + s1.wgs + s3.wgs));
   const size_t lds = p1.lds > p3.lds ? p1.lds : p3.lds;
 #define DNB_P(C1, M3, C3)                                                                                             \
   do {                                                                                                                \
     if (fold1) hipExtLaunchKernelGGL((k_wgrad_pair<3, C1, M3, C3, true>), grid, dim3(256), lds, st, ev0, ev1, 0, A1,  \
-                                     p1.gx, p1.gy, p1.gz, n1, A3, p3.gy, p3.gz, n3, s1, s3, bna, nbn);                       \
+                                     p1.gx, p1.gy, p1.gz, n1, A3, p3.gy, p3.gz, n3, s1, s3, bna, nbn, fina);                       \
     else hipExtLaunchKernelGGL((k_wgrad_pair<3, C1, M3, C3, false>), grid, dim3(256), lds, st, ev0, ev1, 0, A1, p1.gx, p1.gy, \
-                               p1.gz, n1, A3, p3.gy, p3.gz, n3, s1, s3, bna, nbn);                                    \
+                               p1.gz, n1, A3, p3.gy, p3.gz, n3, s1, s3, bna, nbn, fina);                              \
   } while (0)
 #define DNB_P1(M3, C3)                                                                          \
   switch (p1.ctw) {                                                                             \

@@ -254,9 +254,9 @@ __global__ __launch_bounds__(kThreads) void k_bn_bwd_apply(
   if (threadIdx.x < 64) {
     const int lane = threadIdx.x;
     float sb = 0.f, sg = 0.f;
-    if (lane < psplits) {
-      const float* p = part + ((int64_t)ch * psplits + lane) * 2;
-      sb = p[0]; sg = p[1];
+    for (int i = lane; i < psplits; i += 64) {
+      const float* p = part + ((int64_t)ch * psplits + i) * 2;
+      sb += p[0]; sg += p[1];
     }
     sb = wave_sum(sb);
     sg = wave_sum(sg);
@@ -413,6 +413,17 @@ hipError_t launch_bn_relu_bwd(const float* x, int64_t x_stride, const float* dac
   if (v4) { if (accumulate) DNB_LAUNCH_BNBWD(4, true); else DNB_LAUNCH_BNBWD(4, false); }
   else    { if (accumulate) DNB_LAUNCH_BNBWD(1, true); else DNB_LAUNCH_BNBWD(1, false); }
 #undef DNB_LAUNCH_BNBWD
+  return hipGetLastError();
+}
+
+hipError_t launch_bn_bwd_apply(const float* x, int64_t x_stride, const float* dact, int64_t dact_stride, float* du,
+                               int64_t du_stride, int n, int c, int hw, const float* gamma, const float* beta,
+                               const float* mean, const float* istd, float* dgamma, float* dbeta, const float* partials,
+                               int psplits, hipStream_t st) {
+  const Split p = split_plan(n, c, hw);
+  hipLaunchKernelGGL((k_bn_bwd_apply<4, false>), dim3((unsigned)c, (unsigned)p.gs), dim3(kThreads), 0, st, x, x_stride, dact,
+                     dact_stride, du, du_stride, n, hw, p.ipb, 1.0f / ((float)n * (float)hw), gamma, beta, mean, istd,
+                     partials, psplits, dgamma, dbeta);
   return hipGetLastError();
 }
 

@@ -58,6 +58,42 @@ hipError_t launch_bn_relu_bwd(const float* x, int64_t x_stride, const float* dac
                               float* partials, hipStream_t st, int passes = 3 /*1 reduce | 2 apply*/,
                               hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 
+// The element-wise pass alone, from `psplits` partial pairs per channel in [c][psplits] order.
+hipError_t launch_bn_bwd_apply(const float* x, int64_t x_stride, const float* dact, int64_t dact_stride, float* du,
+                               int64_t du_stride, int n, int c, int hw, const float* gamma, const float* beta,
+                               const float* mean, const float* istd, float* dgamma, float* dbeta, const float* partials,
+                               int psplits, hipStream_t st);
+
+// One bottleneck layer of the fp32 backward chain (dnb_conv_f32_fast.hip: the 3x3; dnb_bwd_f32.hip: the
+// rest).  c = C_l input channels; image strides in elements.
+struct Bwd32Layer {
+  int n, h, w, c, k, B;
+  bool last;                             // l = m: the slab is not written yet, dy stands in for it
+  const float *y, *dy; int64_t ys;       // features and gradient of the output
+  const float* x; int64_t x_stride;      // concatenated input of the layer: y in place, or storage 1
+  const float* b;                        // b_l
+  float *G, *gl, *db;                    // slab (stride ys), corrected slice [n][k][hw], gradient of b_l
+  const float *pk1t, *pk3t;              // packed data-gradient weights
+  const float *g1, *b1, *g2, *b2;
+  const float *mean_y, *istd_y, *mean_b, *istd_b;
+  float *dgamma1, *dbeta1;
+  float2 *part1, *part2, *K;
+};
+bool bwd32_ok(int n, int h, int w, int k, int B);
+size_t bwd32_partial1_floats(int n, int hw, int c);
+size_t bwd32_partial2_floats(int n, int h, int w, int B);
+int bwd32_dgrad1_splits(int n, int hw, int c);
+// 3x3 data gradient of the corrected slice, masked by BN2's ReLU, with BN2's sums.  *T2: partial pairs per channel.
+hipError_t bwd32_dgrad3(const Bwd32Layer& L, int* T2, hipStream_t st);
+// 1x1 data gradient, BN1 backward and concat backward into the slab
+hipError_t bwd32_dgrad1(const Bwd32Layer& L, hipStream_t st);
+// the end of the layer's BN1, for launch_conv_wgrad_pair to carry (or launch_bn1_finish on its own)
+struct Bn1Finish;
+void bwd32_bn1_finish(const Bwd32Layer& L, Bn1Finish* out);
+hipError_t launch_bn1_finish(const Bn1Finish& f, hipStream_t st);
+// gradient of the block input, after every layer's BN1 is finished
+hipError_t bwd32_dx0(const Bwd32Layer& L, float* dx0, hipStream_t st);
+
 // out[(img*c + ch)*hw + q] = 1 if fma(u[img*stride + ch*hw + q], scale, shift) > 0 else 0, with
 // (scale, shift) = bn_fold(gamma, beta, mean, istd): the ReLU decision exactly as every kernel takes it.
 hipError_t launch_relu_decisions(const float* u, int64_t stride, int n, int c, int hw, const float* gamma,
@@ -160,14 +196,16 @@ hipError_t launch_conv_wgrad(const float* in, int64_t in_stride, const float* g,
 // gradient of b_l, B channels) and the 3x3 (in3: B channels, g3: the gradient of x_l, k
 // channels).  One launch when the fast pair applies, else two launch_conv_wgrad calls.  *pend1 /
 // *pend3: in, the previous layer's pending sums (carried out here); out, this layer's.
+struct Bn1Finish;
 hipError_t launch_conv_wgrad_pair(const float* in1, int64_t in1_stride, const float* g1, int64_t g1_stride,
                                   float* dw1, int cin1, float* part1, const float2* fold1, const float* in3,
                                   int64_t in3_stride, const float* g3, int64_t g3_stride, float* dw3, int cout3,
                                   float* part3, const float2* fold3, int n, int B, int h, int w, hipStream_t st,
                                   PendingSum* pend1, PendingSum* pend3, const BnBwdPartialArgs* bn = nullptr,
                                   bool* bn_done = nullptr, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr,
-                                  bool* paired = nullptr);
-// (bn: a BN backward reduction to carry in the same launch, *bn_done says whether it was;
+                                  bool* paired = nullptr, const Bn1Finish* fin = nullptr);
+// (fin: the end of a layer's BN1, always carried out;
+//  bn: a BN backward reduction to carry in the same launch, *bn_done says whether it was;
 //  ev_start / ev_stop are stamped around the shared launch, *paired says whether there was one)
 
 // out[e] = sum over splits of partials[split][e] (fixed order).

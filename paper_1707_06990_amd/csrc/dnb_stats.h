@@ -135,6 +135,35 @@ struct RowIter {
   }
 };
 
+// ---- the end of a layer's BN1 in the fp32 backward chain: sums of the partial pairs [ch][T], parameter
+// gradients and the running constants K (see dnb_bwd_f32.hip).  Carried by the layer's weight-gradient
+// launch; a wave per channel.
+struct Bn1Finish {
+  const float2* part;
+  int T, C, wgs;               // wgs = 0: nothing to do
+  const float *gamma, *istd;
+  float inv_p;
+  float2* K;
+  int first;                   // K is set, not added to
+  float *dgamma, *dbeta;
+};
+__device__ __forceinline__ void bn1_finish_body(const Bn1Finish& A, int wg) {
+  const int ch = wg * (int)(blockDim.x >> 6) + (int)(threadIdx.x >> 6);
+  if (ch >= A.C) return;
+  const float2* p = A.part + (int64_t)ch * A.T;
+  float2 s = make_float2(0.f, 0.f);
+  for (int i = threadIdx.x & 63; i < A.T; i += 64) { const float2 v = p[i]; s.x += v.x; s.y += v.y; }
+  s.x = bnb_wave_sum(s.x);
+  s.y = bnb_wave_sum(s.y);
+  if ((threadIdx.x & 63) == 0) {
+    const float sc = __fmul_rn(A.gamma[ch], A.istd[ch]) * A.inv_p;
+    const float2 o = A.first ? make_float2(0.f, 0.f) : A.K[ch];
+    A.K[ch] = make_float2(__fmaf_rn(sc, s.x, o.x), __fmaf_rn(sc, s.y, o.y));
+    A.dbeta[ch] = s.x;
+    A.dgamma[ch] = s.y;
+  }
+}
+
 struct BnBwdPartialArgs {
   const float* x; int64_t x_stride; const float* dact; int64_t dact_stride;
   int n, hw, ipb;

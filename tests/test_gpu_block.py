@@ -70,6 +70,27 @@ def test_fused_schedule_matches_oracle_and_shared_schedule(dnb, oracle, i):
         assert np.array_equal(fused[key], conc[key]), key
 
 
+@pytest.mark.parametrize("cfg", [
+    wl.BlockCfg(2, 30, 8, 8, 1, 12, 48),        # one layer: dy is read where the slab would be
+    wl.BlockCfg(3, 5, 12, 12, 3, 8, 16),        # one 16-channel chunk and M-tile; 144 pixels: a last tile of 16
+    wl.BlockCfg(2, 17, 4, 20, 3, 12, 40),       # B not a multiple of 16, a last tile of 16 pixels, odd channel counts
+    wl.BlockCfg(2, 90, 4, 4, 3, 20, 80),        # 16 pixels per image; five chunks; 32-channel groups 3 and 4
+    wl.BlockCfg(1, 200, 8, 8, 2, 32, 128),      # eight chunks, two slices of 16, groups over two workgroups
+    wl.BlockCfg(2, 40, 6, 12, 3, 40, 160),      # ten chunks
+], ids=lambda c: f"n{c.n}c{c.c0}h{c.h}w{c.w}m{c.layers}k{c.growth}B{c.bottleneck}")
+def test_backward_chain_tile_edges(dnb, oracle, cfg):
+    """The fp32 backward chain at the edges of its tiles and variants: fused against the oracle, the
+    materialised schedules bit for bit."""
+    x0, lp, dy = wl.make_block_inputs(cfg, affine="random")
+    fused = run_block_gpu(dnb, cfg, x0, lp, dy, schedule=2)
+    ores, osl = run_block_oracle(oracle, cfg, x0, lp, dy)
+    compare(fused, ores, osl, cfg)
+    for schedule in (0, 1):
+        other = run_block_gpu(dnb, cfg, x0, lp, dy, schedule=schedule)
+        for key in ("y", "dx0", "dparams"):
+            assert np.array_equal(fused[key], other[key]), (schedule, key)
+
+
 def test_config1_exact_recipe(dnb, oracle):
     """The stated small configuration with its own recipe: gamma = 1, beta = 0, seeds 0/1/2."""
     cfg = wl.config1()
