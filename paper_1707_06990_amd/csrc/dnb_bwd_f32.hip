@@ -14,9 +14,9 @@
 // the slab is finally read:  g = G - K0 - K1*xhat.  Per layer that is 12 bytes per element of the
 // concatenated input (x, G read, G write) instead of 36 (gradient written; read with x by the reduction;
 // read with x and G by the element-wise pass, G written), and five launches per layer instead of six or seven.
-// DenseNet-BC-100 step 5.25 -> 4.92 ms (fused), 6.54 -> 6.20 ms (shared), DenseNet-BC-250 45.0 -> 42.5 ms.  What
-// is left: the 3x3 data gradient, 20 us with the correction and BN2's sums against 15 without on the first block of
-// BC-100 (its 108 weight registers leave none for prefetching), and k_dgrad1 at 2.3 to 3.4 TB/s.
+// DenseNet-BC-100 step 5.25 -> 4.92 ms (fused), 6.54 -> 6.20 ms (shared), DenseNet-BC-250 45.0 -> 42.5 ms, before
+// k_dgrad1s.  What is left: the 3x3 data gradient, 20 us with the correction and BN2's sums against 15 without on
+// the first block of BC-100 (its 108 weight registers leave none for prefetching).
 #include "dnb_f32_dev.h"
 #include "dnb_internal.h"
 #include "dnb_stats.h"
@@ -158,6 +158,111 @@ __global__ __launch_bounds__(256, 2) void k_dgrad1(Dgrad1Args A) {
     }
 }
 
+// The same where a workgroup's four waves have four groups of 32 channels to share a tile among: the tile
+// of db sits in LDS, staged one tile ahead, so that the products wait for no load of their own; x and the
+// slab, requested before them, arrive under them.  (Read by every wave for itself, the db rows of a tile
+// queued behind the slab's loads: loads return in order.)  DenseNet-BC-250 step 42.4 -> 39.95 ms, BC-100 4.96 -> 4.83.
+template <int NCH, bool FIRST>
+__global__ __launch_bounds__(256, 2) void k_dgrad1s(Dgrad1Args A) {
+  __shared__ __attribute__((aligned(16))) float tile_db[NCH * 16 * 64];
+  __shared__ float4 cst[128];  // scale, shift, mean, 1/std of the workgroup's channels
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 15, g = lane >> 4;
+  const int mw = (int)blockIdx.y * 128, m0 = mw + wave * 32, HW = A.hw, t0 = blockIdx.x;
+  if (tid < 128) {
+    const int c = min(mw + tid, A.C - 1);
+    float sc, sf;
+    bn_fold(A.gamma[c], A.beta[c], A.mean[c], A.istd[c], sc, sf);
+    cst[tid] = make_float4(sc, sf, A.mean[c], A.istd[c]);
+  }
+  const int mtl = (A.C16 >> 4) - 1;
+  float4 w[2][NCH];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) w[a][c] = ldg4(wfrag(A.W, A.B16, min((m0 >> 4) + a, mtl), c));
+  auto ch = [&](int a, int r) { return min(m0 + a * 16 + 4 * g + r, A.C - 1); };
+  float s0[2][4], s1[2][4];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s0[a][r] = s1[a][r] = 0.f;
+
+  float4 st[NCH];  // thread: row 16u + tid/16, pixels 4*(tid%16)..+3
+  const int srow = tid >> 4, scol = 4 * (tid & 15);
+  auto request = [&](int tile) {
+    const int img = tile / A.tpi, q = min((tile - img * A.tpi) * 64 + scol, HW - 4);
+    const float* p = A.db + (int64_t)img * A.db_stride + q;
+#pragma unroll
+    for (int u = 0; u < NCH; ++u) st[u] = ldg4(p + (int64_t)min(u * 16 + srow, A.B - 1) * HW);
+  };
+  request(t0);
+  for (int tile = t0; tile < A.tiles; tile += A.T) {
+    __syncthreads();  // the previous tile's reads are done
+#pragma unroll
+    for (int u = 0; u < NCH; ++u) *reinterpret_cast<float4*>(&tile_db[(u * 16 + srow) * 64 + scol]) = st[u];
+    __syncthreads();
+    const int img = tile / A.tpi, q = (tile - img * A.tpi) * 64 + 4 * j;
+    const bool ok = q < HW;  // HW % 4 == 0: a lane's four pixels are in or out together
+    const int qc = ok ? q : 0;
+    const float* xp = A.x + (int64_t)img * A.x_stride + qc;
+    const float* rp = (FIRST ? A.dy : A.G) + (int64_t)img * A.g_stride + qc;
+    float4 x4[2][4], g4[2][4];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        x4[a][r] = ldg4(xp + (int64_t)ch(a, r) * HW);
+        g4[a][r] = ldg4(rp + (int64_t)ch(a, r) * HW);
+      }
+    request(min(tile + A.T, A.tiles - 1));
+    __builtin_amdgcn_sched_barrier(0);  // all of these are in flight before the products
+    f32x4 acc[2][4];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc[a][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < NCH; ++c)
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        const float4 d = *reinterpret_cast<const float4*>(&tile_db[(c * 16 + 4 * ks + g) * 64 + 4 * j]);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          acc[0][t] = mfma16(elem(w[0][c], ks), elem(d, t), acc[0][t]);
+          acc[1][t] = mfma16(elem(w[1][c], ks), elem(d, t), acc[1][t]);
+        }
+      }
+    __builtin_amdgcn_sched_barrier(0);
+    if (ok) {
+      float* op = A.G + (int64_t)img * A.g_stride + q;
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float4 k = cst[wave * 32 + a * 16 + 4 * g + r];
+          float o[4];
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const float xv = elem(x4[a][r], t), dz = __fmaf_rn(xv, k.x, k.y) > 0.f ? acc[a][t][r] : 0.f;
+            o[t] = __fmaf_rn(k.x, dz, elem(g4[a][r], t));
+            s0[a][r] += dz;
+            s1[a][r] = __fmaf_rn(dz, xv - k.z, s1[a][r]);
+          }
+          if (m0 + a * 16 + 4 * g + r < A.C)
+            *reinterpret_cast<float4*>(op + (int64_t)ch(a, r) * HW) = make_float4(o[0], o[1], o[2], o[3]);
+        }
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float u = row16_sum(s0[a][r]), v = row16_sum(s1[a][r]);
+      const int m = m0 + a * 16 + 4 * g + r;
+      if (j == 0 && m < A.C) A.part1[(int64_t)m * A.T + t0] = make_float2(u, v * cst[wave * 32 + a * 16 + 4 * g + r].w);
+    }
+}
+
 // dx0 = G - K0 - K1*xhat on the block input's channels.  grid (channels, image ranges), 16-byte accesses.
 __global__ __launch_bounds__(256) void k_dx0(const float* __restrict__ G, int64_t g_stride, const float* __restrict__ x,
                                              int64_t x_stride, float* __restrict__ dx0, int64_t d_stride, int n, int hw,
@@ -202,6 +307,21 @@ hipError_t bwd32_dgrad1(const Bwd32Layer& L, hipStream_t st) {
   A.hw = hw; A.tpi = (hw + 63) / 64; A.tiles = A.tpi * L.n;
   A.nwm = groups >= 3 ? 4 : groups;
   const int nwp = 4 / A.nwm;
+  // (fewer chunks: the products are too few to hide anything; more: no registers for their weights)
+  if (A.nwm == 4 && A.B16 >= 48 && A.B16 <= 128) {
+    const dim3 grid((unsigned)A.T, (unsigned)((groups + 3) / 4));
+#define DNB_L(NCH)                                                                       \
+  do {                                                                                   \
+    if (L.last) hipLaunchKernelGGL((k_dgrad1s<NCH, true>), grid, dim3(256), 0, st, A);   \
+    else hipLaunchKernelGGL((k_dgrad1s<NCH, false>), grid, dim3(256), 0, st, A);         \
+  } while (0)
+    switch (A.B16 >> 4) {
+      case 3: DNB_L(3); break; case 4: DNB_L(4); break; case 5: DNB_L(5); break; case 6: DNB_L(6); break;
+      case 7: DNB_L(7); break; default: DNB_L(8); break;
+    }
+#undef DNB_L
+    return hipGetLastError();
+  }
   const dim3 grid((unsigned)((A.T + nwp - 1) / nwp), (unsigned)((groups + A.nwm - 1) / A.nwm));
 #define DNB_L(NCH)                                                                       \
   do {                                                                                   \
