@@ -867,6 +867,8 @@ int dnb_block_backward(dnb_block* b, const void* paramsv, const void* yv, const 
   float* partA = (float*)(ws + b->off_partA);
   float* partB = (float*)(ws + b->off_partB);
 
+  // From here on: shapes whose rows are not 16-byte vectors (w % 4 != 0), and slices too wide for the
+  // chain of dnb_bwd_f32.hip (bwd32_ok).
   // Three chains.  Only the data-gradient chain (dgrad 3x3 -> BN2 bwd -> dgrad 1x1 -> BN1 bwd)
   // carries the dependence from layer l to layer l-1; the weight gradients, and the
   // recomputation that feeds only them, hang off it.  With concurrency on they run on two
@@ -875,12 +877,11 @@ int dnb_block_backward(dnb_block* b, const void* paramsv, const void* yv, const 
   //   B: [recompute storage 1,2] -> wgrad 1x1 -> sum      (needs db_l; storage 1 also feeds BN1 bwd)
   // In the fused schedule there is nothing to recompute and both weight gradients go out as one
   // paired launch on a single helper stream, issued after the main chain's 1x1 data gradient so
-  // that a captured graph keeps the main chain on its hardware queue (5.88 ms per DenseNet-BC-100
-  // step against 6.53 ms with two helper streams and separate launches).
-  // With concurrency off (the fp32 default, 5.56 ms) the same kernels run on the caller's stream,
-  // and the leaves are gathered: a layer's two weight gradients, the previous layer's partial
-  // sums and the reduction pass of BN1's backward go out as one launch just before BN1's apply
-  // pass; every wait of the main chain for another queue costs about 10 us, more than the
+  // that a captured graph keeps the main chain on its hardware queue.
+  // With concurrency off (the default) the same kernels run on the caller's stream, and the leaves
+  // are gathered: a layer's two weight gradients, the previous layer's partial sums and the reduction
+  // pass of BN1's backward go out as one launch just before BN1's apply pass, where the paired kernel
+  // takes the shape; every wait of the main chain for another queue costs about 10 us, more than the
   // overlap buys at these kernel sizes.
   const bool conc = b->concurrency != 0;
   if (conc) {

@@ -26,8 +26,9 @@
 //   * 1x1 weight gradient: operands two steps ahead in static register stages: 17.5 -> 15.5 us on
 //     average; 96 instead of 64 input channels per workgroup (fewer re-reads of the gradient
 //     operand, 236 registers) changed nothing.
-//   * BN-backward sums computed in the data-gradient convs' epilogues (to drop the separate
-//     reduction launch) made those convs 6-15 us slower, more than the launch they saved.
+//   * BN-backward sums in the data-gradient convs' epilogues cost more than the launch they saved as long
+//     as every tile summed its lanes through the LDS crossbar; kept in registers over a workgroup's tiles
+//     and added once, with the element-wise pass gone too, they pay (dnb_bwd_f32.hip).
 constexpr int kV4Workgroups = 512;  // workgroups of the persistent 3x3 kernel (two per CU)
 static_assert(kV4Workgroups % 8 == 0, "tiles are dealt to workgroups per XCD (8 of them)");
 

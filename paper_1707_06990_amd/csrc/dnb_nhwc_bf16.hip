@@ -8,9 +8,9 @@
 // Convolutions (forward / data gradient): the workgroup stages a 64-pixel tile (+ one image row
 // of halo for 3x3) of a 64-channel chunk in LDS, double-buffered, applying the BN+ReLU prologue
 // once per element; its four waves split the output-channel tiles and take packed bf16 weights
-// from L2 through register rings.  Weight gradients contract over pixels, which NHWC keeps on
-// the slow axis, so both operands are transposed on their way into LDS ([channel][pixel]); the
-// 3x3 stages a row tile once and reads its nine taps as shifted fragments.
+// from L2 through register rings.  The backward chain is in dnb_nhwc_bwd.hip, the weight gradients in
+// dnb_nhwc_wgrad.hip; here only the one for rows wider than those take (both operands transposed on
+// their way into LDS, one staging per tap).
 #include "dnb_internal.h"
 #include "dnb_nhwc_dev.h"
 #include "dnb_stats.h"
