@@ -721,8 +721,7 @@ __device__ __forceinline__ void conv3x3_v4_body(
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const float mu = row16_sum(v[r]) * (1.0f / 16.0f);
-          const float dlt = v[r] - mu;
-          const float m2 = row16_sum(dlt * dlt);
+          const float m2 = row16_sumsq0(v[r] - mu);
           if (j == 0) {
             float* ps = &lds[SST0 + (((cur * 4 + wave) * (MT * 16)) + a * 16 + 4 * g + r) * 3];
             ps[0] = 16.f; ps[1] = mu; ps[2] = m2;

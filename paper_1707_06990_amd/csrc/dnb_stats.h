@@ -4,8 +4,6 @@
 
 #include <hip/hip_runtime.h>
 
-#include <type_traits>
-
 namespace dnb {
 
 // The one place BN's affine map is folded into (scale, shift); forward, recomputation
@@ -20,19 +18,36 @@ __device__ __forceinline__ float bn_istd(float m2, float cnt, float eps) {
   return __fdiv_rn(1.0f, __fsqrt_rn(__fadd_rn(__fdiv_rn(m2, cnt), eps)));
 }
 
+template <int CTRL>
+__device__ __forceinline__ float row16_from(float v) {  // the value of another lane of the row of 16
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+
 // Sum over each row of 16 lanes, every lane gets it: four vector additions whose second operand comes
 // from another lane of the row.  The order of additions (and the bits) is that of a butterfly over
 // lane distances 1, 2, 4, 8: after two steps the lanes of a quad agree, so the mirrored lane 7 - i holds
-// what lane i ^ 4 does, then 15 - i what i ^ 8 does.  Through __shfl_xor each step goes to the LDS
-// crossbar and back; with two such sums per output channel that was 3 us of a convolution's launch.
+// what lane i ^ 4 does, then 15 - i what i ^ 8 does.  That needs every step to round: a product passed in
+// must not be fused into the first addition (the lanes of a pair would differ), hence no contraction here.
+// Through __shfl_xor each step goes to the LDS crossbar and back; with two such sums per output channel
+// that was 3 us of a convolution's launch.
 __device__ __forceinline__ float row16_sum(float v) {
-  auto from = [](float x, auto ctrl) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, true));
-  };
-  v += from(v, std::integral_constant<int, 0xB1>{});   // quad_perm [1,0,3,2]
-  v += from(v, std::integral_constant<int, 0x4E>{});   // quad_perm [2,3,0,1]
-  v += from(v, std::integral_constant<int, 0x141>{});  // row_half_mirror
-  v += from(v, std::integral_constant<int, 0x140>{});  // row_mirror
+#pragma clang fp contract(off)
+  v = v + row16_from<0xB1>(v);   // quad_perm [1,0,3,2]
+  v = v + row16_from<0x4E>(v);   // quad_perm [2,3,0,1]
+  v = v + row16_from<0x141>(v);  // row_half_mirror
+  v = v + row16_from<0x140>(v);  // row_mirror
+  return v;
+}
+
+// Sum of squares over each row of 16 lanes, for the row's lane 0 only.  Lane 0 adds as the butterfly
+// does, d0*d0 entering unrounded: ((d0^2 + d1^2) + (d2^2 + d3^2)) + ..., its partners at distances 4 and 8
+// taken by rotation (the lanes of a quad differ in the last place here, so a mirrored lane would not do).
+__device__ __forceinline__ float row16_sumsq0(float d) {
+#pragma clang fp contract(off)
+  float v = __fmaf_rn(d, d, row16_from<0xB1>(__fmul_rn(d, d)));
+  v = v + row16_from<0x4E>(v);
+  v = v + row16_from<0x12C>(v);  // row_ror 12: lane i takes lane i + 4
+  v = v + row16_from<0x128>(v);  // row_ror 8
   return v;
 }
 

@@ -215,6 +215,54 @@ def test_fused_conv_bnrelu_forward_and_statistics(dnb, oracle, n, cin, cout, h, 
     assert_close(m2 / (n * hw), ref.var(axis=(0, 2, 3)), TOL, "variance")
 
 
+def fma32(a, b, c):
+    """round(a*b + c) to fp32: the product of two fp32 values is exact in fp64, the sum in extended precision."""
+    return (np.longdouble(a) * np.longdouble(b) + np.longdouble(c)).astype(np.float32)
+
+
+@pytest.mark.parametrize("w", [8, 16, 32])
+def test_3x3_statistics_are_the_butterfly_sums_bit_for_bit(dnb, w):
+    """The (count, mean, M2) of a 64-pixel tile, from the convolution's own output: each wave adds its 16
+    pixels as a butterfly over lane distances 1, 2, 4, 8 does (in M2, lane 0's first square enters the first
+    addition unrounded), the four waves are merged in order.  Whether the merge's last product is rounded
+    before it is added is the compiler's choice; both forms are formed and one of them must be met."""
+    n, cin, cout, h = 3, 48, 12, 16
+    r, hw = rng(23), 16 * w
+    x = f32(r.standard_normal((n, cin, h, w)))
+    wgt = f32(r.standard_normal((cout, cin, 3, 3)) * np.sqrt(2.0 / (cin * 9)))
+    fold = f32(np.stack([1.0 + 0.3 * r.standard_normal(cin), 0.3 * r.standard_normal(cin)], axis=1))
+    out = torch.empty((n, cout, h, w), device="cuda")
+    pk = torch.empty(dnb.dnb_op_conv_scratch_bytes(cin, cout, 3), dtype=torch.uint8, device="cuda")
+    stats = torch.empty(dnb.dnb_op_conv_stats_bytes(n, cout, h, w) // 4, device="cuda")
+    T = dnb.dnb_op_conv_bnrelu_forward(dev(x), cin * hw, dev(wgt), dev(fold), out, cout * hw, stats, n, cin, cout, h, w, 3, pk)
+    torch.cuda.synchronize()
+    assert T == n * hw // 64
+    got = stats.cpu().numpy()[:cout * T * 3].reshape(cout, T, 3)
+    v = out.cpu().numpy().reshape(n, cout, hw // 64, 4, 16).transpose(1, 0, 2, 3, 4).reshape(cout, T, 4, 16)
+    lane = np.arange(16)
+    s = v
+    for off in (1, 2, 4, 8):
+        s = s + s[..., lane ^ off]
+    mu = s[..., 0] * np.float32(1 / 16)
+    d = v - mu[..., None]
+    q = fma32(d, d, (d * d)[..., lane ^ 1])
+    for off in (2, 4, 8):
+        q = q + q[..., lane ^ off]
+    m2 = q[..., 0]
+    ok = []
+    for fused in (False, True):
+        c, m, acc = np.float32(16), mu[..., 0], m2[..., 0]
+        for u in range(1, 4):
+            tot, dd = c + np.float32(16), mu[..., u] - m
+            m = fma32(dd, np.float32(16) / tot, m)
+            sum2, f = acc + m2[..., u], c * np.float32(16) / tot
+            acc = fma32(dd * dd, f, sum2) if fused else sum2 + dd * dd * f
+            c = tot
+        ok.append(np.array_equal(got[..., 0], np.full((cout, T), c)) and np.array_equal(got[..., 1], m)
+                  and np.array_equal(got[..., 2], acc))
+    assert any(ok)
+
+
 @pytest.mark.parametrize("n,cin,cout,h,w,ks", [(2, 48, 12, 32, 32, 3), (3, 40, 48, 16, 16, 1), (2, 204, 48, 8, 8, 1),
                                                (2, 24, 12, 8, 12, 3), (1, 16, 12, 4, 64, 3)])
 def test_fused_conv_bnrelu_wgrad(dnb, oracle, n, cin, cout, h, w, ks):
