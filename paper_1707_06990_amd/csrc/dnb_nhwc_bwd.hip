@@ -79,7 +79,8 @@ __device__ __forceinline__ float2 sum_partials64(const float2* __restrict__ part
 // forms all MT M-tiles, so nothing is added across waves but the two sums at the end.  The slice
 // of the slab is corrected, rounded to bf16 and staged once per tile with a halo of a row and a
 // pixel on either side; in passes of 64 channels (k above 64).  Workgroups walk over tiles T2 apart.
-template <int NT, int MT>
+// BYPASS: the coefficients of a pass's channels are formed before it, else all of them first.
+template <int NT, int MT, bool BYPASS>
 __global__ __launch_bounds__(256) void k_dgrad3(Dgrad3Args A) {
   extern __shared__ u16 lds[];
   __shared__ float2 sh[256];
@@ -102,20 +103,21 @@ __global__ __launch_bounds__(256) void k_dgrad3(Dgrad3Args A) {
   constexpr int PITCH = 64 + 8, TP = 64 * NT;
   const int HW = A.H * A.Wd, W = A.Wd, halo = W + 1, seg = TP + 2 * halo;
   const int pw = blockIdx.x / A.gy, m0 = (blockIdx.x % A.gy) * MT * 16;
-  float* coef = reinterpret_cast<float*>(lds + seg * PITCH);  // [3][k]: K0, K1*istd, mean
-  if (!A.dy) {
-    for (int c0 = 0; c0 < A.k; c0 += 64) {
-      const int i = c0 + lane, ic = min(i, A.k - 1);
-      const float2 s = sum_partials64(A.part1, A.T1, A.C1, A.c1 + ic, sh);
-      if (wave == 0 && i < A.k) {
-        const float sc = A.fold1[ic].x * A.inv_p;
-        const float2 o = A.K ? A.K[ic] : make_float2(0.f, 0.f);
-        coef[i] = __fmaf_rn(sc, s.x, o.x);
-        coef[A.k + i] = __fmaf_rn(sc, s.y, o.y) * A.istd[ic];
-        coef[2 * A.k + i] = A.mean[ic];
-      }
+  float* coef = reinterpret_cast<float*>(lds + seg * PITCH);  // [3][kc]: K0, K1*istd, mean
+  const int kc = BYPASS ? 64 : A.k;
+  auto form_coef = [&](int c0, int at) {  // of channels c0..c0+63, to positions at..
+    const int i = c0 + lane, ic = min(i, A.k - 1);
+    const float2 s = sum_partials64(A.part1, A.T1, A.C1, A.c1 + ic, sh);
+    if (wave == 0 && i < A.k) {
+      const float sc = A.fold1[ic].x * A.inv_p;
+      const float2 o = A.K ? A.K[ic] : make_float2(0.f, 0.f);
+      coef[at + lane] = __fmaf_rn(sc, s.x, o.x);
+      coef[kc + at + lane] = __fmaf_rn(sc, s.y, o.y) * A.istd[ic];
+      coef[2 * kc + at + lane] = A.mean[ic];
     }
-  }
+  };
+  if (!BYPASS && !A.dy)
+    for (int c0 = 0; c0 < A.k; c0 += 64) form_coef(c0, c0);
   float s0[MT][4], s1[MT][4], fs[MT][4], ft[MT][4], mu[MT][4];
   int mch[MT];
 #pragma unroll
@@ -150,7 +152,8 @@ __global__ __launch_bounds__(256) void k_dgrad3(Dgrad3Args A) {
         braw[a][t] = *reinterpret_cast<const uint2*>(A.b + (p0 + qc) * A.B + min(mch[a], A.B - 4));
     }
     for (int c0 = 0; c0 < A.K32; c0 += 64) {
-      const int kw = min(64, A.K32 - c0), vsh = kw == 64 ? 3 : 2, nvec = seg << vsh;
+      const int kw = min(64, A.K32 - c0), vsh = kw == 64 ? 3 : 2, nvec = seg << vsh, cb = BYPASS ? c0 : 0;
+      if (BYPASS && !A.dy) form_coef(c0, 0);  // (its barriers: the previous pass has read the last ones)
       __syncthreads();  // coefficients written; the previous pass's fragment reads are done
       for (int base = 0; base < nvec; base += 4 * 256) {
         uint4 ga[4], gb[4], xr[4];
@@ -186,7 +189,7 @@ __global__ __launch_bounds__(256) void k_dgrad3(Dgrad3Args A) {
                                      __uint_as_float(gb[u].z), __uint_as_float(gb[u].w)};
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
-                  o.h[e] = f2bf(gf[e] - coef[ch + e] - coef[A.k + ch + e] * (bf2f(xv.h[e]) - coef[2 * A.k + ch + e]));
+                  o.h[e] = f2bf(gf[e] - coef[ch - cb + e] - coef[kc + ch - cb + e] * (bf2f(xv.h[e]) - coef[2 * kc + ch - cb + e]));
                 if (m0 == 0 && s >= halo && s < halo + TP)
                   *reinterpret_cast<uint4*>(A.gl + (p0 + q) * A.k + ch) = o.q;
               }
@@ -541,17 +544,21 @@ __global__ __launch_bounds__(256) void k_dx0(const float* __restrict__ G, int64_
 // that leaves at most 15 % of its pixels unused, else the one that leaves the fewest, within 64 KB
 // of LDS.  MT: two M-tiles per workgroup where that still gives one workgroup per CU (each M group
 // stages the tile again; four need more than 256 registers).  T2: workgroups per M group; one per
-// tile up to 256, beyond that each takes several.
+// tile up to 256, beyond that each takes several.  bypass: the slice's coefficients stay in LDS up to 512
+// channels (6 KB); wider slices form those of a 64-channel pass before it, so that LDS does not grow with k
+// and every width of a row that dnb_block_create takes fits 64 KB.
 struct Dgrad3Plan {
   int NT, MT, tpi, tiles, gy, T2;
+  bool bypass;
   size_t lds;
 };
 Dgrad3Plan plan_dgrad3(int n, int h, int w, int k, int B) {
   Dgrad3Plan p{};
   const int hw = h * w, mtiles = (B + 15) / 16;
   int best = 0;
+  p.bypass = k > 512;
   for (int nt : {4, 2, 1}) {
-    const size_t lds = (size_t)(64 * nt + 2 * (w + 1)) * 72 * sizeof(u16) + (size_t)3 * k * sizeof(float);
+    const size_t lds = (size_t)(64 * nt + 2 * (w + 1)) * 72 * sizeof(u16) + (size_t)3 * (p.bypass ? 64 : k) * sizeof(float);
     if (lds > 60 * 1024 && nt > 1) continue;
     const int used = (hw + 64 * nt - 1) / (64 * nt) * 64 * nt;
     if (best == 0 || used < best) { best = used; p.NT = nt; p.lds = lds; }
@@ -619,7 +626,11 @@ hipError_t bwd_dgrad3(const BwdLayer& L, hipStream_t st) {
     fin = (A.C1 + 63) / 64;
   }
   const dim3 grid((unsigned)(p.T2 * p.gy + fin));
-#define DNB_D3(NT, MT) hipLaunchKernelGGL((k_dgrad3<NT, MT>), grid, dim3(256), p.lds, st, A)
+#define DNB_D3(NT, MT)                                                                             \
+  do {                                                                                             \
+    if (p.bypass) hipLaunchKernelGGL((k_dgrad3<NT, MT, true>), grid, dim3(256), p.lds, st, A);     \
+    else hipLaunchKernelGGL((k_dgrad3<NT, MT, false>), grid, dim3(256), p.lds, st, A);             \
+  } while (0)
 #define DNB_D3M(NT)                                   \
   do {                                                \
     if (p.MT == 2) DNB_D3(NT, 2); else DNB_D3(NT, 1); \

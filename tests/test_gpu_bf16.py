@@ -91,7 +91,7 @@ def decisions_nchw(flat, cfg, widths):
     return np.concatenate(out)
 
 
-def check_bf16_block(dnb, oracle, cfg, x0, lp, dy, storage_allowance=False):
+def check_bf16_block(dnb, oracle, cfg, x0, lp, dy, storage_allowance=False, schedule=2):
     """GPU block against the plain float64 block evaluated with the kernels' ReLU decisions.
     storage_allowance=False: every tensor within TOL.  True (the full-size blocks: dozens of layers,
     10^5 pixels): bf16 storage by itself moves single gradient tensors by more than TOL even with
@@ -100,7 +100,7 @@ def check_bf16_block(dnb, oracle, cfg, x0, lp, dy, storage_allowance=False):
     tensor must lie within err_s + TOL of the plain block on both measures, and within
     max(TOL, 1.5 err_s) in L2, max(TOL, 2.5 err_s) in the worst element: as close to the plain
     block as the storage format lets anything be.  The output y keeps TOL outright."""
-    gpu = run_block_gpu_bf16(dnb, cfg, x0, lp, dy, decisions=True)
+    gpu = run_block_gpu_bf16(dnb, cfg, x0, lp, dy, decisions=True, schedule=schedule)
     assert set(np.unique(gpu["d1"])) <= {0, 1} and set(np.unique(gpu["d2"])) <= {0, 1}
     d1 = decisions_nchw(gpu["d1"], cfg, [cfg.c_in(l) for l in range(1, cfg.layers + 1)])
     d2 = decisions_nchw(gpu["d2"], cfg, [cfg.bottleneck] * cfg.layers)
@@ -449,9 +449,10 @@ def test_nhwc_bn_relu_backward(dnb, oracle, shape, accumulate):
 
 
 # the backward chain's own edges: k above one 64-channel staging pass with B above eight K-steps of 32 and not a
-# multiple of 32; more tiles than BN2 partials are added in place; more tiles than workgroups; a single short wave
+# multiple of 32; more tiles than BN2 partials are added in place; more tiles than workgroups; a single short wave;
+# a slice whose coefficients are formed pass by pass, with a last pass of 24 channels
 CHAIN_CFGS = [wl.BlockCfg(2, 16, 3, 5, 3, 72, 296), wl.BlockCfg(70, 8, 4, 4, 3, 8, 32), wl.BlockCfg(300, 8, 2, 2, 2, 8, 24),
-              wl.BlockCfg(1, 24, 9, 17, 2, 24, 40), wl.BlockCfg(2, 8, 7, 3, 1, 48, 192)]
+              wl.BlockCfg(1, 24, 9, 17, 2, 24, 40), wl.BlockCfg(2, 8, 7, 3, 1, 48, 192), wl.BlockCfg(2, 8, 5, 9, 3, 536, 16)]
 
 
 @pytest.mark.parametrize("cfg", CHAIN_CFGS, ids=[f"n{c.n}c{c.c0}h{c.h}w{c.w}m{c.layers}k{c.growth}B{c.bottleneck}" for c in CHAIN_CFGS])
@@ -460,3 +461,12 @@ def test_bf16_backward_chain_edges_match_oracle(dnb, oracle, cfg):
     share stays below the 2e-2 that the others are held to."""
     x0, lp, dy = wl.make_block_inputs(cfg, affine="random")
     check_bf16_block(dnb, oracle, cfg, to_bf16_values(x0), lp, to_bf16_values(dy))
+
+
+def test_bf16_backward_of_a_slice_wider_than_lds(dnb, oracle):
+    """13600 channels a layer, which dnb_block_create accepts: three coefficients for each would need more
+    than the 160 KB of LDS a compute unit has.  (Shared schedule: the fused one keeps BN's folded pairs of
+    the widest input in LDS and refuses this width.)"""
+    cfg = wl.BlockCfg(1, 8, 4, 4, 2, 13600, 8)
+    x0, lp, dy = wl.make_block_inputs(cfg, affine="random")
+    check_bf16_block(dnb, oracle, cfg, to_bf16_values(x0), lp, to_bf16_values(dy), schedule=0)
