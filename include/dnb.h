@@ -91,7 +91,8 @@ typedef struct {
   uint64_t grad_bytes;        /* gradient slab G (C_out) + the two shared gradient scratch maps */
   uint64_t peak_bytes;        /* sum of the three lines above: the feature-map memory           */
   uint64_t stats_bytes;       /* cached fp32 per-channel BN mean and 1/sqrt(var+eps)            */
-  uint64_t scratch_bytes;     /* reduction partials (not feature maps)                          */
+  uint64_t scratch_bytes;     /* reduction partials and packed weights, as far as they are not in the
+                                 part of the gradient scratch that the backward pass leaves free  */
   uint64_t workspace_bytes;   /* what the caller must allocate: everything above that lives in
                                  the workspace, plus alignment padding                          */
 } dnb_block_memory;

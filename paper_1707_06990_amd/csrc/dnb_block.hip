@@ -24,8 +24,7 @@ struct dnb_block {
   std::vector<size_t> off_fold1, off_fold2;  // fused schedule: per layer folded (scale, shift) of BN1 / BN2
   size_t off_part;                           // reduction partials of the main chain (BN)
   size_t off_K, part1_floats;                // backward: K0, K1 per channel; where BN2's partials start in off_part
-  size_t partA_floats, partB_floats;         // size of one weight-gradient partial buffer
-  size_t off_partA, off_partB;               // partials of the 3x3 / 1x1 weight gradients
+  size_t off_partA[2], off_partB[2];         // partials of the 3x3 / 1x1 weight gradients, layer l's in [l & 1]
   // with concurrency on, backward runs three chains: the data-gradient chain on the caller's
   // stream and the two weight-gradient chains on these helper streams (created at the first
   // such backward call); off, everything runs on the caller's stream
@@ -80,6 +79,13 @@ T layer_ptrs(const dnb_block* b, P* base, int l) {
   return r;  // (B = 0: W1, g2, b2 are empty and W3 starts right after b1)
 }
 
+
+// Partial floats of a weight gradient on the block's own buffers (16-byte aligned, image strides multiples of
+// h*w): the vector kernel wherever its plan takes the shape, else the any-shape one.
+size_t block_wgrad_partial_floats(const dnb_block_desc& d, int cin, int cout, int taps) {
+  const size_t f = conv_wgrad_fast_partial_floats(d.n, cin, cout, d.h, d.w, taps);
+  return f ? f : conv_wgrad_partial_floats(d.n, cin, cout, d.h, d.w, taps);
+}
 
 // ReLU decisions as the kernels take them: fma(u, scale, shift) > 0 with (scale, shift) folded by
 // bn_fold from the cached statistics -- the one expression every forward, recomputing and backward
@@ -235,8 +241,6 @@ int backward_bf16(dnb_block* b, const void* yv, const void* dy, void* dx0, float
   const int n = d.n, m = d.layers, k = d.growth, B = d.bottleneck, cout = b->cout;
   const int64_t P = b->P;
   const unsigned short* y = (const unsigned short*)yv;
-  float* partA = (float*)(ws + b->off_partA);
-  float* partB = (float*)(ws + b->off_partB);
   const unsigned short* pack = (const unsigned short*)(ws + b->off_pack);
   const size_t B16 = (size_t)((B + 15) & ~15), k16 = (size_t)((k + 15) & ~15), B32 = (size_t)((B + 31) & ~31);
   const bool fused = d.schedule == DNB_SCHED_FUSED, recompute = d.schedule == DNB_SCHED_SHARED;
@@ -281,9 +285,9 @@ int backward_bf16(dnb_block* b, const void* yv, const void* dy, void* dx0, float
     DNB_TRY(nhwc::bwd_dgrad1(L, st));
     const void* gl = l == m ? (const void*)((const unsigned short*)dy + c) : L.gl;
     // both weight gradients, and the sums of layer l+1's (partial buffers used alternately)
-    const nhwc::WgradIn w3{fused ? L.b : S3, B, gl, l == m ? cout : k, partA + (l & 1) * b->partA_floats, gp.W3, B, k,
+    const nhwc::WgradIn w3{fused ? L.b : S3, B, gl, l == m ? cout : k, (float*)(ws + b->off_partA[l & 1]), gp.W3, B, k,
                            fused ? L.fold2 : nullptr};
-    const nhwc::WgradIn w1{fused ? (const void*)y : S2, fused ? cout : c, L.db, B, partB + (l & 1) * b->partB_floats, gp.W1, c,
+    const nhwc::WgradIn w1{fused ? (const void*)y : S2, fused ? cout : c, L.db, B, (float*)(ws + b->off_partB[l & 1]), gp.W1, c,
                            B, fused ? L.fold1 : nullptr};
     if (!nhwc::wgrad_pair(w1, w3, n, d.h, d.w, &sum1, &sum3, st)) return DNB_E_UNSUPPORTED;
     DNB_TRY(hipGetLastError());
@@ -351,10 +355,10 @@ int backward_f32(dnb_block* b, const float* params, const float* y, const float*
     Bn1Finish fin;
     bwd32_bn1_finish(L, &fin);
     DNB_TRY(launch_conv_wgrad_pair(fused ? y : S2, fused ? ys : (int64_t)c * hw, L.db, (int64_t)B * hw, gp.W1, c,
-                                   (float*)(ws + b->off_partB) + (size_t)(l & 1) * b->partB_floats,
+                                   (float*)(ws + b->off_partB[l & 1]),
                                    fused ? (const float2*)(ws + b->off_fold1[l]) : nullptr, fused ? bl : S3, (int64_t)B * hw, gl,
                                    l == m ? ys : (int64_t)k * hw, gp.W3, k,
-                                   (float*)(ws + b->off_partA) + (size_t)(l & 1) * b->partA_floats,
+                                   (float*)(ws + b->off_partA[l & 1]),
                                    fused ? (const float2*)(ws + b->off_fold2[l]) : nullptr, n, B, d.h, d.w, st, &pendB, &pendA, nullptr,
                                    nullptr, nullptr, nullptr, nullptr, &fin));
   }
@@ -409,7 +413,7 @@ int backward_plain3x3(dnb_block* b, const float* params, const float* y, const f
   float* mean_y = (float*)(ws + b->off_stat_y);
   float* istd_y = mean_y + b->cout;
   float* part = (float*)(ws + b->off_part);
-  float* partA = (float*)(ws + b->off_partA);
+  float* partA = (float*)(ws + b->off_partA[0]);
   float* G = (float*)(ws + b->off_G);
   float* dS2 = (float*)(ws + b->off_dS2);
   const float* pack = (const float*)(ws + b->off_pack);  // packed by the forward pass
@@ -613,36 +617,54 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
         if (f1 > p1) p1 = f1;
       }
       b->part1_floats = p1;
-      need(p1 + bwd32_partial2_floats(d.n, d.h, d.w, B));
+      need(p1 + bwd32_partial2_floats(d.n, d.h, d.w, k, B));
     }
     for (int l = 1; l <= m; ++l) {
       need(bn_bwd_partial_floats(d.n, c_in(d, l), (int)hw));
-      const size_t f = B > 0 ? conv_wgrad_partial_floats(d.n, c_in(d, l), B, d.h, d.w, 1) : 0;
+      const size_t f = B > 0 ? block_wgrad_partial_floats(d, c_in(d, l), B, 1) : 0;
       if (f > partB) partB = f;
     }
     if (B == 0) {
       for (int l = 1; l <= m; ++l) {
-        const size_t f = conv_wgrad_partial_floats(d.n, c_in(d, l), k, d.h, d.w, 9);
+        const size_t f = block_wgrad_partial_floats(d, c_in(d, l), k, 9);
         if (f > partA) partA = f;
         b->pk[l] = pack;
         pack += packed_layer_floats(c_in(d, l), k, 0);
       }
     } else {
-      partA = conv_wgrad_partial_floats(d.n, B, k, d.h, d.w, 9);
+      partA = block_wgrad_partial_floats(d, B, k, 9);
       for (int l = 1; l <= m; ++l) { b->pk[l] = pack; pack += packed_layer_floats(c_in(d, l), k, B); }
     }
   }
-  const size_t kf = B > 0 ? (size_t)cout * 2 : 0;
-  mem.scratch_bytes = (uint64_t)(part + 2 * (partA + partB) + pack + kf) * sizeof(float);
-  b->off_part = carve(part * sizeof(float), false);
-  // two buffers each, used alternately by consecutive layers (a layer's partials are
+  // The merged backward chains keep only the k channels of g_l in the gradient scratch of storage 2 (the
+  // 1x1 data gradient is consumed where it is formed): the rest of it holds what a backward pass needs and
+  // nothing else does, as far as there is room.
+  size_t hole = 0, hole_end = 0;
+  if (bf16 || (B > 0 && bwd32_ok(d.n, d.h, d.w, k, B))) {
+    hole = align_up(b->off_dS2 + (size_t)k * Ps, 256);
+    hole_end = b->off_dS2 + (size_t)b->cm * Ps;
+  }
+  size_t scratch = 0;
+  auto carve_scratch = [&](size_t floats, bool backward_only) {
+    const size_t bytes = floats * sizeof(float);
+    if (backward_only && hole < hole_end && bytes <= hole_end - hole) {
+      const size_t o = hole;
+      hole = align_up(hole + bytes, 256);
+      return o;
+    }
+    scratch += bytes;
+    return carve(bytes, false);
+  };
+  b->off_part = carve_scratch(part, false);
+  // with a bottleneck two buffers each, used alternately by consecutive layers (a layer's partials are
   // summed by extra workgroups of the next layer's weight-gradient launch)
-  b->partA_floats = partA;
-  b->partB_floats = partB;
-  b->off_partA = carve(2 * partA * sizeof(float), false);
-  b->off_partB = carve(2 * partB * sizeof(float), false);
-  b->off_pack = carve(pack * sizeof(float), false);
-  b->off_K = carve(kf * sizeof(float), false);
+  for (int i = 0; i < 2; ++i) {
+    b->off_partB[i] = carve_scratch(partB, true);
+    b->off_partA[i] = B > 0 || i == 0 ? carve_scratch(partA, true) : b->off_partA[0];
+  }
+  b->off_pack = carve_scratch(pack, false);
+  b->off_K = carve_scratch(B > 0 ? (size_t)cout * 2 : 0, true);
+  mem.scratch_bytes = (uint64_t)scratch;
   // measured on MI355X: with the weight gradients on helper streams the fp32 step is slower (idle
   // time between dependent launches of different streams outweighs the overlap); the bf16 backward
   // pass is one chain of launches on the caller's stream
@@ -864,8 +886,6 @@ int dnb_block_backward(dnb_block* b, const void* paramsv, const void* yv, const 
 
   const float* pack = (const float*)(ws + b->off_pack);  // packed by the forward pass
   const size_t B16 = (size_t)((B + 15) & ~15), k16 = (size_t)((k + 15) & ~15);
-  float* partA = (float*)(ws + b->off_partA);
-  float* partB = (float*)(ws + b->off_partB);
 
   // From here on: shapes whose rows are not 16-byte vectors (w % 4 != 0), and slices too wide for the
   // chain of dnb_bwd_f32.hip (bwd32_ok).
@@ -925,7 +945,7 @@ int dnb_block_backward(dnb_block* b, const void* paramsv, const void* yv, const 
                              p.b2, StatsSrc{mean_b, istd_b, nullptr, 0, 0, 0, d.eps}, sA));
     // (the sum of this launch's partials is left to the next layer's launch on this chain).
     // On one stream the 3x3 weight gradient waits for the 1x1's launch below and shares it.
-    float* pA = partA + (size_t)(l & 1) * b->partA_floats;
+    float* pA = (float*)(ws + b->off_partA[l & 1]);
     const float* in3 = fused ? bl : S3;
     const float2* f3 = fused ? (const float2*)(ws + b->off_fold2[l]) : nullptr;
     if (conc && !oneh) {  // (fused: BN2+ReLU of b_l is applied while the kernel stages its tile)
@@ -952,7 +972,7 @@ int dnb_block_backward(dnb_block* b, const void* paramsv, const void* yv, const 
 
     // ---- chain B, second half: the 1x1 weight gradient from storage 2 and db_l
     DNB_TRY(wait(sB, ev(l, EV_DB)));
-    float* pB = partB + (size_t)(l & 1) * b->partB_floats;
+    float* pB = (float*)(ws + b->off_partB[l & 1]);
     const float* in1 = fused ? y : S2;
     const int64_t in1s = fused ? ys : (int64_t)c * hw;
     const float2* f1 = fused ? (const float2*)(ws + b->off_fold1[l]) : nullptr;

@@ -1519,10 +1519,7 @@ bool bwd32_ok(int n, int h, int w, int k, int B) {
   if (h * w % 4 || w % 4 || k > kBwdMaxK) return false;
   return plan_bwd3(n, h, w, k, B).lds <= 60 * 1024;
 }
-size_t bwd32_partial2_floats(int n, int h, int w, int B) {
-  const size_t t = (size_t)((h * w + 63) / 64) * n;
-  return 2 * (size_t)B * (t > kV4Workgroups ? t : kV4Workgroups);
-}
+size_t bwd32_partial2_floats(int n, int h, int w, int k, int B) { return 2 * (size_t)B * plan_bwd3(n, h, w, k, B).T2; }
 
 hipError_t bwd32_dgrad3(const Bwd32Layer& L, int* T2, hipStream_t st) {
   const Bwd3Plan p = plan_bwd3(L.n, L.h, L.w, L.k, L.B);

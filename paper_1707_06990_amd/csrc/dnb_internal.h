@@ -81,7 +81,7 @@ struct Bwd32Layer {
 };
 bool bwd32_ok(int n, int h, int w, int k, int B);
 size_t bwd32_partial1_floats(int n, int hw, int c);
-size_t bwd32_partial2_floats(int n, int h, int w, int B);
+size_t bwd32_partial2_floats(int n, int h, int w, int k, int B);
 int bwd32_dgrad1_splits(int n, int hw, int c);
 // 3x3 data gradient of the corrected slice, masked by BN2's ReLU, with BN2's sums.  *T2: partial pairs per channel.
 hipError_t bwd32_dgrad3(const Bwd32Layer& L, int* T2, hipStream_t st);

@@ -128,6 +128,28 @@ CFGS = [wl.config1(), wl.BlockCfg(3, 5, 5, 7, 3, 4, 6), wl.BlockCfg(1, 7, 3, 3, 
 NOBOTTLE = [wl.BlockCfg(2, 8, 8, 8, 3, 4, 0), wl.BlockCfg(3, 5, 5, 7, 4, 3, 0)]   # BN-ReLU-3x3 layers (bottleneck = 0)
 
 
+@pytest.mark.parametrize("kind,limit,args,bf16", [
+    ("block", 626_176, dict(n=2, c0=16, h=8, w=8, layers=4, growth=12, bottleneck=48, schedule=2), False),
+    ("block", 102_255_104, dict(n=64, c0=160, h=16, w=16, layers=12, growth=12, bottleneck=0, schedule=0), False),
+    ("block", 166_136_320, dict(n=17, c0=256, h=28, w=28, layers=12, growth=32, bottleneck=128, schedule=0), True),
+    ("net", 873_996_288, dict(n=64, image=32, depth=100, growth=12, classes=10, schedule=2), False),
+    ("net", 1_045_927_424, dict(n=64, image=32, depth=100, growth=12, classes=10, schedule=0), False),
+    ("net", 4_202_403_584, dict(n=64, image=32, depth=250, growth=24, classes=100, schedule=2), False),
+], ids=["small-block", "plain-block", "bf16-block", "bc100-fused", "bc100-shared", "bc250-fused"])
+def test_weight_gradient_partials_do_not_grow_the_workspace(dnb, kind, limit, args, bf16):
+    """The limits are what these shapes took with separate BN backward passes.  The merged backward chains
+    need a second partial buffer in bf16, more splits of the any-shape kernel and packed weights without a
+    bottleneck; the partials of kernels that a block never launches are not counted, a block without a
+    bottleneck has one buffer, and what only the backward pass uses lies in the gradient scratch that the
+    merged chains leave free."""
+    if bf16:
+        args = dict(args, dtype=dnb.DNB_BF16, layout=dnb.DNB_NHWC)
+    h = getattr(dnb, f"dnb_{kind}_create")(**args)
+    got = getattr(dnb, f"dnb_{kind}_workspace_bytes")(h)
+    getattr(dnb, f"dnb_{kind}_destroy")(h)
+    assert got <= limit
+
+
 @pytest.mark.parametrize("cfg", CFGS + NOBOTTLE, ids=lambda c: f"{c.n}x{c.c0}x{c.h}x{c.w}-m{c.layers}k{c.growth}B{c.bottleneck}")
 def test_peak_bytes_formula(dnb, cfg):
     """Linear-memory formula (shared) and quadratic one (store-all), in bytes."""
