@@ -158,9 +158,8 @@ def test_bf16_schedules_bit_identical_and_their_bytes(dnb, cfg):
 
 
 @pytest.mark.parametrize("cfg", [CFGS[1], CFGS[3]], ids=[IDS[1], IDS[3]])
-def test_bf16_backward_chains_on_helper_streams_give_the_same_bits(dnb, cfg):
-    """The weight gradients run on two helper streams beside the data-gradient chain; with
-    concurrency off everything runs in program order on one stream.  Same kernels, same sums."""
+def test_bf16_backward_takes_no_notice_of_the_concurrency_switch(dnb, cfg):
+    """The bf16 backward pass is one chain of launches on the caller's stream either way."""
     x0, lp, dy = wl.make_block_inputs(cfg, affine="random")
     x0, dy = to_bf16_values(x0), to_bf16_values(dy)
     a = run_block_gpu_bf16(dnb, cfg, x0, lp, dy, concurrency=True)
@@ -170,9 +169,8 @@ def test_bf16_backward_chains_on_helper_streams_give_the_same_bits(dnb, cfg):
 
 
 def test_bf16_hip_graph_replays_match_eager(dnb):
-    """The bf16 block's forward and backward captured in a HIP graph with the library's default
-    stream order (the backward forks onto its helper stream and joins again), as bench.py times
-    it: every replay, with eager work and synchronisation in between, reproduces the eager bits."""
+    """The bf16 block's forward and backward captured in a HIP graph, as bench.py times it: every
+    replay, with eager work and synchronisation in between, reproduces the eager bits."""
     cfg = CFGS[3]
     x0, lp, dy = wl.make_block_inputs(cfg, affine="random")
     x0, dy = to_bf16_values(x0), to_bf16_values(dy)

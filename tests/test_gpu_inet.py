@@ -89,10 +89,9 @@ def test_inet_full_widths_and_depths_at_batch_2(dnb, oracle, which):
 
 
 def test_inet_hip_graph_replays_match_eager(dnb, oracle):
-    """The whole ImageNet-shaped step captured in a HIP graph with the library's default stream order
-    (the blocks' backward passes fork onto their helper stream and join again), as bench.py times it:
-    every replay, with eager work and synchronisation in between and the workspace poisoned before
-    it, reproduces the eager bits of the loss, the logits and every parameter gradient."""
+    """The whole ImageNet-shaped step captured in a HIP graph, as bench.py times it: every replay, with
+    eager work and synchronisation in between and the workspace poisoned before it, reproduces the
+    eager bits of the loss, the logits and every parameter gradient."""
     from harness import dev, pack_inet
     cfg = CFGS[1]
     x, labels, params = wl.make_inet_inputs(cfg, affine="random")

@@ -31,8 +31,9 @@ def test_net_step_matches_oracle(dnb, oracle, cfg, schedule):
         assert_close(dp[sl], odp[sl], TOL, f"d{name}")
 
 
-def test_net_schedules_agree_and_replays_are_deterministic(dnb, oracle):
-    cfg = CFGS[2]
+@pytest.mark.parametrize("cfg", [CFGS[1], CFGS[2]], ids=["ragged", "aligned"])
+def test_net_schedules_agree_and_replays_are_deterministic(dnb, oracle, cfg):
+    """(The ragged network's second and third block, 6x6 and 3x3, use the helper streams when they are on.)"""
     x, labels, params = wl.make_net_inputs(cfg, affine="random")
     a = run_net_gpu(dnb, oracle, cfg, x, labels, params, 0)
     b = run_net_gpu(dnb, oracle, cfg, x, labels, params, 1)
