@@ -1,21 +1,36 @@
 """Host-side emulation of the index arithmetic of the persistent 3x3 convolution kernel
-(k_conv3x3_v4 in csrc/dnb_conv_f32_fast.hip): for every workgroup, tile, thread and staging slot it
-recomputes the addresses the kernel forms -- global loads of the input rows, packed-weight loads,
-LDS stores of the staged rows, LDS operand reads of the nine taps, the statistics scratch and the
-output stores -- with the kernel's own constants (plane pitch 144, row pitch W + 4, 512 workgroups
+(conv3x3_v4_body in csrc/dnb_conv_f32_fast.hip, as k_conv3x3_v4 and as the backward chain's
+k_dgrad3_v4): for every workgroup, tile, thread and staging slot it recomputes the addresses the kernel
+forms -- global loads of the input rows, packed-weight loads (fragment order, held against the order the
+packing kernel writes), LDS stores of the staged rows, LDS operand reads of the nine taps, the statistics
+scratch and the output stores; in the backward form also the feature loads, the stores of the corrected
+slice (every element once) and the partial sums (every slot once, zeros from workgroups without a tile)
+-- with the kernel's own constants (plane pitch 144, row pitch W + 4, 512 workgroups
 dealt to 8 XCDs) and checks that each stays inside its buffer and that every tile is taken exactly
 once.  An earlier version of the kernel overran the last staged row by one float; this is the
 check that found it.  CPU only: nothing is launched."""
 import pytest
 
 
-def check(n, cin, cout, H, W, label, sample=None):
+def wfrag(K16, mtile, chunk, lane):  # offset of a lane's four weights inside one tap's block
+    return (mtile*(K16>>4)+chunk)*256+lane*4
+
+
+def wunfrag(e, K16):  # position inside one tap's block -> row, channel, as the packing kernel writes it
+    mt=e//(16*K16); r=e-mt*16*K16; lane=(r>>2)&63
+    return mt*16+(lane&15), (r>>8)*16+4*(r&3)+(lane>>4)
+
+
+def check(n, cin, cout, H, W, label, sample=None, bwd=False):
     HW=H*W; mtiles=(cout+15)//16; M16=mtiles*16; K16=(cin+15)//16*16; nch=K16//16
     assert (mtiles,nch) in ((1,3),(3,1)) and W in (8,16,32) and HW%64==0
     MT,NCH=mtiles,nch; ROWS=NCH*16; RW=W+4; TR=64//W; NR=TR+2; W4=W//4; CS=144
     assert NR*RW<=CS
     PER=NR*W4; TOTAL=ROWS*PER; U=(TOTAL+255)//256; BUF=ROWS*CS+4; SST0=2*BUF
-    lds_floats=2*(NCH*16*144+4)+2*4*mtiles*16*3
+    assert not bwd or (MT,NCH)==(3,1)  # (what k_dgrad3_v4 is instantiated for)
+    lds_floats=2*(NCH*16*144+4)+(0 if bwd else 2*4*mtiles*16*3)
+    static_bytes=(3*128*4+MT*16*16+4*MT*16*8) if bwd else 0  # coefficients, BN2's constants, its sums
+    gl_written={}; part2={}
     tpi=HW//64; total_tiles=tpi*n
     G=(total_tiles+7)//8*8 if total_tiles<512 else 512
     tpx=(total_tiles+7)>>3; wgx=G>>3
@@ -25,6 +40,8 @@ def check(n, cin, cout, H, W, label, sample=None):
     for b in wgs:
         xcd=b&7; slot=b>>3; t_lo=xcd*tpx; t_hi=min(total_tiles,t_lo+tpx); tile=t_lo+slot
         it=0
+        if bwd:  # the workgroup's partial of every output channel, or zeros if it has no tile
+            for m in range(cout): part2[m*G+b]=part2.get(m*G+b,0)+1
         while tile<t_hi:
             assert tile not in done; done.add(tile)
             img=tile//tpi; y0=(tile-img*tpi)*TR
@@ -39,11 +56,17 @@ def check(n, cin, cout, H, W, label, sample=None):
                     if u*256+tid<TOTAL:
                         for boff in (0,BUF):
                             if not(0<=boff+slo and boff+slo+3<boff+BUF-4): bad+=1
+                    if bwd and sch<cin and 1<=sry<=TR and u*256+tid<TOTAL:
+                        gq=(img*cin+sch)*HW+(y0-1+sry)*W+sgo  # gl [n][cin][HW], four pixels
+                        if not(0<=gq and gq+3<in_elems): bad+=1
+                        gl_written[gq]=gl_written.get(gq,0)+1
                 for t in range(9):
                     for a_ in range(MT):
                         for ci in range(NCH):
-                            wa=((t*M16+a_*16+j)*K16+ci*16+4*g)
+                            wa=t*M16*K16+wfrag(K16,a_,ci,lane)
                             if not(0<=wa and wa+3<w_elems): bad+=1
+                            for ks in range(4):  # the channel whose plane the ks-th product reads
+                                if wunfrag(wa-t*M16*K16+ks,K16)!=(a_*16+j,ci*16+4*ks+g): bad+=1
                 p=16*wave+j; base=g*CS+(p//W+1)*RW+4+(p%W)
                 for boff in (0,BUF):
                     for ci in range(NCH):
@@ -60,11 +83,17 @@ def check(n, cin, cout, H, W, label, sample=None):
                         if m<cout:
                             o=img*cout*HW+q+m*HW
                             if not(0<=o<out_elems): bad+=1
+                        if bwd: continue
                         sidx=SST0+(((1*4+wave)*(MT*16))+a_*16+4*g+r)*3
                         if not(sidx+2<lds_floats): bad+=1
             tile+=wgx; it+=1
     assert (not full) or done==set(range(total_tiles)), label
-    return bad, lds_floats * 4
+    if bwd:
+        assert all(v==1 for v in gl_written.values()) and all(v==1 for v in part2.values()), label
+        if full:
+            assert sorted(gl_written)==list(range(0,n*cin*HW,4)), label
+            assert sorted(part2)==list(range(cout*G)), label
+    return bad, lds_floats * 4 + static_bytes
 
 
 CASES = [
@@ -81,6 +110,23 @@ CASES = [
     (4, 40, 12, 8, 8, "fwd, 40 input channels (channel tail)", None),
     (2, 12, 40, 8, 16, "dgrad, 40 output channels, 8x16 image", None),
 ]
+
+
+BWD_CASES = [
+    (2, 12, 48, 8, 8, "8x8, workgroups without a tile", None),
+    (3, 16, 33, 16, 16, "16x16, 16 and 33 channels", None),
+    (2, 8, 40, 8, 16, "8x16, 8 and 40 channels", None),
+    (1, 12, 48, 32, 32, "32x32", None),
+    (64, 12, 48, 32, 32, "first block of DenseNet-BC-100 at batch 64", 6),
+    (70, 12, 48, 16, 16, "16x16 at batch 70", 6),
+]
+
+
+@pytest.mark.parametrize("n,cin,cout,H,W,label,sample", BWD_CASES, ids=[c[5] for c in BWD_CASES])
+def test_every_access_of_the_backward_form_is_in_bounds(n, cin, cout, H, W, label, sample):
+    bad, lds_bytes = check(n, cin, cout, H, W, label, sample, bwd=True)
+    assert bad == 0
+    assert lds_bytes <= 64 * 1024
 
 
 @pytest.mark.parametrize("n,cin,cout,H,W,label,sample", CASES, ids=[c[5] for c in CASES])
