@@ -502,7 +502,7 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
     // the materialised fp32 schedules fall back to the any-shape kernels: their 3x3 tiles (64 pixels
     // plus a halo of two rows) must fit LDS, else the shape is refused here rather than at launch
     const int cin3 = d.bottleneck > 0 ? d.bottleneck : d.c0 + (d.layers - 1) * d.growth;
-    if (!conv_generic_fits(d.n, cin3, d.growth, d.h, d.w, 9)) return DNB_E_UNSUPPORTED;
+    if (!conv3x3_generic_fits(d.n, cin3, d.growth, d.h, d.w)) return DNB_E_UNSUPPORTED;
   }
 
   dnb_block* b = new (std::nothrow) dnb_block();
@@ -794,7 +794,7 @@ int dnb_block_forward(dnb_block* b, const void* x0v, const void* paramsv, void* 
   // y[:, 0:c0] = x0, and the statistics of those channels (every later layer reuses them:
   // a channel's batch statistics do not depend on which layer consumes it)
   float* pack = (float*)(ws + b->off_pack);
-  const size_t B16 = (size_t)((B + 15) & ~15), k16 = (size_t)((k + 15) & ~15);
+  const size_t B16 = (size_t)((B + 15) & ~15);
   DNB_TRY(launch_pack_block_weights(params, pack, d.c0, k, B, m, st));
   DNB_TRY(launch_copy_slab(x0, (int64_t)d.c0 * hw, y, ys, n, (int64_t)d.c0 * hw, st));
   // Statistics exist first as partials in `part` -- from the statistics kernel (block input) or

@@ -1,6 +1,7 @@
-// fp32 convolutions of the dense block as MFMA implicit GEMMs on gfx950 (NCHW).
+// fp32 convolutions of the dense block as MFMA implicit GEMMs on gfx950 (NCHW): the kernels for any shape,
+// behind the dispatch to the faster ones.
 //
-// Forward and data gradient share one kernel: out[m][q] = sum_{c,t} W(m,c,t) * in[c][q+shift(t)].
+// 3x3 forward and data gradient share one kernel: out[m][q] = sum_{c,t} W(m,c,t) * in[c][q+shift(t)].
 // The 16x16x4 fp32 MFMA is used with output channels on its M axis (k = 12 pads to 16 only)
 // and 16 consecutive pixels on its N axis, so activation reads and output writes run along the
 // contiguous pixel axis of NCHW.  Activations are staged through LDS once per channel chunk
@@ -68,20 +69,19 @@ inline int pad4mod64(int v) {
   return r;
 }
 
-template <int TAPS, int MT, int NT>
+template <int MT, int NT>
 __global__ __launch_bounds__(256) void k_conv_igemm(
     const float* __restrict__ in, int64_t in_stride, const float* __restrict__ wgt, int64_t w_sm,
     int64_t w_sc, int flip, float* __restrict__ out, int64_t out_stride, int cin, int cout, int H,
-    int W, int wm, int CS, int MS) {
+    int W, int CS, int MS) {
   extern __shared__ float lds[];
   const int HW = H * W;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wn = 4 / wm;
-  const int wave_m = wave % wm, wave_n = wave / wm;
+  constexpr int TAPS = 9;
   constexpr int TPW = NT * 16;  // pixels per wave
-  constexpr int MW = MT * 16;   // output channels per wave
-  const int TP = wn * TPW, MB = wm * MW;
-  const int halo = (TAPS == 9) ? (W + 1) : 0;
+  constexpr int MB = MT * 16;   // output channels (every wave forms all of them)
+  constexpr int TP = 4 * TPW;
+  const int halo = W + 1;
   const int seg = TP + 2 * halo;
   float* al = lds;            // [KC][CS]   activations, flat pixel index with halo
   float* wl = lds + KC * CS;  // [TAPS][KC][MS] weights, output channel fastest
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(256) void k_conv_igemm(
   bool lok[NT], rok[NT];
 #pragma unroll
   for (int b = 0; b < NT; ++b) {
-    pl[b] = wave_n * TPW + b * 16 + i16;
+    pl[b] = wave * TPW + b * 16 + i16;
     const int wc = (q0 + pl[b]) % W;
     lok[b] = wc != 0;
     rok[b] = wc != W - 1;
@@ -126,14 +126,13 @@ __global__ __launch_bounds__(256) void k_conv_igemm(
     __syncthreads();
 #pragma unroll
     for (int t = 0; t < TAPS; ++t) {
-      const int di = (TAPS == 9) ? t / 3 - 1 : 0, dj = (TAPS == 9) ? t % 3 - 1 : 0;
-      const int shift = halo + di * W + dj;
+      const int di = t / 3 - 1, dj = t % 3 - 1, shift = halo + di * W + dj;
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
         const int kc = ks * 4 + g;
         float a[MT], b[NT];
 #pragma unroll
-        for (int x = 0; x < MT; ++x) a[x] = wl[(t * KC + kc) * MS + wave_m * MW + x * 16 + i16];
+        for (int x = 0; x < MT; ++x) a[x] = wl[(t * KC + kc) * MS + x * 16 + i16];
 #pragma unroll
         for (int x = 0; x < NT; ++x) {
           float v = al[kc * CS + pl[x] + shift];
@@ -157,7 +156,7 @@ __global__ __launch_bounds__(256) void k_conv_igemm(
       const int q = q0 + pl[y];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wave_m * MW + x * 16 + 4 * g + r;
+        const int m = m0 + x * 16 + 4 * g + r;
         if (m < cout && q < HW) ob[(int64_t)m * HW + q] = acc[x][y][r];
       }
     }
@@ -325,65 +324,46 @@ hipError_t launch_sum_partials(const float* partials, int splits, int64_t count,
 namespace {
 
 struct IgemmPlan {
-  int mt, nt, wm;
+  int mt, nt;
   dim3 grid;
   int CS, MS;
   size_t lds;
 };
 
-IgemmPlan plan_igemm(int n, int cout, int h, int w, int taps) {
+IgemmPlan plan_igemm(int n, int cout, int h, int w) {
   IgemmPlan p;
   const int hw = h * w, mtiles = (cout + 15) / 16;
-  // 3x3: keep the staged weights of a chunk (taps*KC*MB floats) small -> one wave column
-  p.wm = taps == 9 ? 1 : (mtiles >= 12 ? 4 : (mtiles >= 6 ? 2 : 1));
-  const int per_wave = (mtiles + p.wm - 1) / p.wm;
-  p.mt = per_wave >= 4 ? 4 : per_wave;  // tiles per wave, at most 4 (grid.y covers the rest)
-  if (p.mt == 4 && per_wave % 4 != 0 && per_wave % 3 == 0) p.mt = 3;
-  const int wn = 4 / p.wm;
-  const int mb = p.wm * p.mt * 16;
+  p.mt = mtiles >= 4 ? 4 : mtiles;  // at most 4 tiles (grid.y covers the rest): 9*KC*16*mt staged weights
+  if (p.mt == 4 && mtiles % 4 != 0 && mtiles % 3 == 0) p.mt = 3;
+  const int mb = p.mt * 16;
   const int gy = (cout + mb - 1) / mb;
   p.nt = 1;
   for (int nt = 4; nt >= 2; nt >>= 1) {
-    const int tp = wn * nt * 16;
+    const int tp = 4 * nt * 16;
     if (tp / 2 >= hw) continue;  // tile would be mostly outside the image
     const int64_t wgs = (int64_t)((hw + tp - 1) / tp) * gy * n;
     if (wgs >= 512) { p.nt = nt; break; }  // keep at least two workgroups per compute unit
   }
-  const int tp = wn * p.nt * 16;
-  const int halo = taps == 9 ? w + 1 : 0;
-  p.CS = pad16mod32(tp + 2 * halo);
+  const int tp = 4 * p.nt * 16;
+  p.CS = pad16mod32(tp + 2 * (w + 1));
   p.MS = pad16mod32(mb);
-  p.lds = (size_t)(KC * p.CS + taps * KC * p.MS) * sizeof(float);
+  p.lds = (size_t)(KC * p.CS + 9 * KC * p.MS) * sizeof(float);
   p.grid = dim3((unsigned)((hw + tp - 1) / tp), (unsigned)gy, (unsigned)n);
   return p;
 }
 
-template <int TAPS, int MT>
-hipError_t launch_igemm_nt(const IgemmPlan& p, const float* in, int64_t in_stride, WeightView wv,
-                           float* out, int64_t out_stride, int cin, int cout, int h, int w,
-                           hipStream_t st) {
+template <int MT>
+void launch_igemm_nt(const IgemmPlan& p, const float* in, int64_t in_stride, WeightView wv, float* out,
+                     int64_t out_stride, int cin, int cout, int h, int w, hipStream_t st) {
 #define DNB_IGEMM(NT)                                                                              \
-  hipLaunchKernelGGL((k_conv_igemm<TAPS, MT, NT>), p.grid, dim3(256), p.lds, st, in, in_stride,    \
-                     wv.w, wv.sm, wv.sc, wv.flip, out, out_stride, cin, cout, h, w, p.wm, p.CS, p.MS)
+  hipLaunchKernelGGL((k_conv_igemm<MT, NT>), p.grid, dim3(256), p.lds, st, in, in_stride,          \
+                     wv.w, wv.sm, wv.sc, wv.flip, out, out_stride, cin, cout, h, w, p.CS, p.MS)
   switch (p.nt) {
     case 4: DNB_IGEMM(4); break;
     case 2: DNB_IGEMM(2); break;
     default: DNB_IGEMM(1); break;
   }
 #undef DNB_IGEMM
-  return hipGetLastError();
-}
-
-template <int TAPS>
-hipError_t launch_igemm_mt(const IgemmPlan& p, const float* in, int64_t in_stride, WeightView wv,
-                           float* out, int64_t out_stride, int cin, int cout, int h, int w,
-                           hipStream_t st) {
-  switch (p.mt) {
-    case 4: return launch_igemm_nt<TAPS, 4>(p, in, in_stride, wv, out, out_stride, cin, cout, h, w, st);
-    case 3: return launch_igemm_nt<TAPS, 3>(p, in, in_stride, wv, out, out_stride, cin, cout, h, w, st);
-    case 2: return launch_igemm_nt<TAPS, 2>(p, in, in_stride, wv, out, out_stride, cin, cout, h, w, st);
-    default: return launch_igemm_nt<TAPS, 1>(p, in, in_stride, wv, out, out_stride, cin, cout, h, w, st);
-  }
 }
 
 struct WgradPlan {
@@ -426,7 +406,7 @@ hipError_t launch_conv_igemm(const float* in, int64_t in_stride, WeightView wv, 
                              int taps, ConvExtras* ex, hipStream_t st) {
   if (n <= 0 || cout <= 0 || h <= 0 || w <= 0) return hipSuccess;
   if (ex) ex->used_fast = false;
-  // the 1x1 kernel takes single floats where rows are not 16-byte friendly
+  // the 1x1 kernel takes single floats where rows are not 16-byte friendly: every 1x1 without a prologue
   const ConvExtras x = ex ? *ex : ConvExtras{};
   int* T = ex ? &ex->stats_T : nullptr;
   if (packed && (((taps == 1 && !x.fold) || conv_fast_ok(in, in_stride, out, out_stride, h, w, taps)) &&
@@ -440,20 +420,21 @@ hipError_t launch_conv_igemm(const float* in, int64_t in_stride, WeightView wv, 
     if (ex) ex->used_fast = true;
     return hipGetLastError();
   }
-  if (ex && ex->fold) return hipErrorInvalidValue;  // the generic kernels have no BN prologue
-  const IgemmPlan p = plan_igemm(n, cout, h, w, taps);
+  if (taps != 9 || x.fold) return hipErrorInvalidValue;  // the generic kernel is a 3x3 without a BN prologue
+  const IgemmPlan p = plan_igemm(n, cout, h, w);
   if (p.lds > 64 * 1024) return hipErrorInvalidValue;
-  if (taps == 9) return launch_igemm_mt<9>(p, in, in_stride, wv, out, out_stride, cin, cout, h, w, st);
-  return launch_igemm_mt<1>(p, in, in_stride, wv, out, out_stride, cin, cout, h, w, st);
+  switch (p.mt) {
+    case 4: launch_igemm_nt<4>(p, in, in_stride, wv, out, out_stride, cin, cout, h, w, st); break;
+    case 3: launch_igemm_nt<3>(p, in, in_stride, wv, out, out_stride, cin, cout, h, w, st); break;
+    case 2: launch_igemm_nt<2>(p, in, in_stride, wv, out, out_stride, cin, cout, h, w, st); break;
+    default: launch_igemm_nt<1>(p, in, in_stride, wv, out, out_stride, cin, cout, h, w, st); break;
+  }
+  return hipGetLastError();
 }
 
-bool conv_generic_fits(int n, int cin, int cout, int h, int w, int taps) {
-  return plan_igemm(n, cout, h, w, taps).lds <= 64 * 1024 && plan_igemm(n, cin, h, w, taps).lds <= 64 * 1024 &&
-         plan_wgrad(n, cin, cout, h, w, taps).lds <= 64 * 1024;
-}
-
-int conv_wgrad_splits(int n, int cin, int cout, int h, int w, int taps) {
-  return plan_wgrad(n, cin, cout, h, w, taps).splits;
+bool conv3x3_generic_fits(int n, int cin, int cout, int h, int w) {
+  return plan_igemm(n, cout, h, w).lds <= 64 * 1024 && plan_igemm(n, cin, h, w).lds <= 64 * 1024 &&
+         plan_wgrad(n, cin, cout, h, w, 9).lds <= 64 * 1024;
 }
 
 size_t conv_wgrad_partial_floats(int n, int cin, int cout, int h, int w, int taps) {

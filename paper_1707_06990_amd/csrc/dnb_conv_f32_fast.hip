@@ -179,7 +179,6 @@ __global__ __launch_bounds__(256) void k_conv1x1_v3(
   const int q = tile * (16 * PPL) + PPL * j;
   const int img = blockIdx.z;
   const bool pix_ok = q < HW;
-  const float* inb = in + (int64_t)img * in_stride + q;
   const int mbase = KSPLIT ? blockIdx.y * (MT * 16) : (blockIdx.y * nw + wave) * (MT * 16);
   const int M16 = (cout + 15) & ~15;
   const int nchunks = Kpad >> 4;
@@ -1008,7 +1007,6 @@ __device__ __forceinline__ void wgrad3x3_body(const Wg3Args& A3, int bx, int by,
   const int img = bx / tiles_per_img, q0 = (bx - img * tiles_per_img) * TPIX;
   const int c0 = by * CB, m0 = bz * (MTW * 16);
   const int origin = q0 - W - 4;
-  const int seg4 = (TPIX + 2 * W + 8) >> 2;
   const float* ab = a + (int64_t)img * a_stride;
   const float* gb = gout + (int64_t)img * g_stride;
 

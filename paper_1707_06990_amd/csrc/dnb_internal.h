@@ -154,7 +154,7 @@ hipError_t launch_conv_igemm(const float* in, int64_t in_stride, WeightView wv, 
                              int taps, ConvExtras* ex, hipStream_t st);
 // whether the any-shape kernels (forward, data gradient, weight gradient) have LDS for this shape: they
 // are the fallback wherever an operand is not 16-byte friendly, so a plan must not count on the fast ones
-bool conv_generic_fits(int n, int cin, int cout, int h, int w, int taps);
+bool conv3x3_generic_fits(int n, int cin, int cout, int h, int w);
 bool conv_fast_ok(const float* in, int64_t in_stride, const float* out, int64_t out_stride, int h,
                   int w, int taps);
 
@@ -165,7 +165,6 @@ hipError_t launch_bn_fold(const float* gamma, const float* beta, float* mean, fl
                           float2* fold, hipStream_t st);
 
 // dW[m][c][t] = sum_{n,q} g[n][m][q] * in[n][c][q + shift(t)]  (OIHW result).
-int conv_wgrad_splits(int n, int cin, int cout, int h, int w, int taps);
 size_t conv_wgrad_partial_floats(int n, int cin, int cout, int h, int w, int taps);
 // partial floats of the fast (16-byte-vector) weight-gradient kernel for this shape, 0 if its tile plan does not fit
 size_t conv_wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps);

@@ -114,7 +114,7 @@ __device__ __forceinline__ void wgrad1_body(const Wg1Args& A, int id, u16* lds) 
   const int cg = col / A.gz, mg = col % A.gz;
   constexpr int GP = gpitch(MG), GV = 2 * MG, GU = MG / 2;
   u16* gS = lds + 64 * AP;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 15, g = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4;
   const int c0 = cg * 64, m0 = mg * MG * 16;
   const int tiles = (A.P + 63) >> 6, t_begin = bx * A.tps, t_end = min(tiles, t_begin + A.tps);
 
