@@ -44,11 +44,12 @@ def parse():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-compare", action="store_true", help="skip timing the other schedule")
     ap.add_argument("--only-block", type=int, default=-1, help="time a single dense block of the workload (diagnostic)")
-    ap.add_argument("--serial", action="store_true", help="no helper streams in backward (the library's default for fp32)")
-    ap.add_argument("--concurrent", action="store_true", help="weight gradients on helper streams in backward (the library's default for bf16)")
+    ap.add_argument("--serial", action="store_true", help="no helper streams in backward (the library's default)")
+    ap.add_argument("--concurrent", action="store_true", help="weight gradients on helper streams in backward, at the fp32 shapes that have them (w %% 4 != 0, slices too "
+                         "wide for the merged chain): none of the named workloads")
     ap.add_argument("--forward-only", action="store_true", help="time the forward pass alone (diagnostic, not the metric)")
     ap.add_argument("--no-extra", action="store_true",
-                    help="skip the other workloads (config3: whole network; config4 / config5: dense-block sets) that the "
+                    help="skip the other workloads (config3 to config5: whole networks, and the bf16 dense-block sets) that the "
                          "default run times after the metric's workload and reports as objects of their own")
     return ap.parse_args()
 
@@ -268,15 +269,15 @@ def dominant_kernel_roofline(dnb, torch, runs, traffic_key):
     """Live measurement of the kernel with the largest share of the step in the committed
     rocprofv3 summary (profiles/): the launch that holds a bottleneck layer's two weight
     gradients (1x1 and 3x3, BN+ReLU of their activation operands recomputed in the operand
-    loads, fp32 MFMA with pixels on the K axis) and the reduction pass of the layer's first BN
-    backward.  Algorithmic work per launch: 2*P*C_l*B + 18*P*B*k flops; 4*(P*(C_l + B) + C_l*B)
-    + 4*(P*(B + k) + 9*B*k) + 8*P*C_l bytes (the BN reduction reads the features and their
-    gradient once more).  The roof whose time over the launches below is the larger is reported:
-    at these widths HBM (8 TB/s).  The launches are the layers of the workload's largest dense
-    block that take this instantiation (C_l >= 49), with the block's own slab strides, through
-    the single-op entry point, each launch stamping its own pair of events at the kernel's start
-    and end on the launch stream.  (Inside the step the launch also adds up the previous layer's
-    weight-gradient partial sums: about 20 MB more.)"""
+    loads, fp32 MFMA with pixels on the K axis).  Algorithmic work per launch: 2*P*C_l*B +
+    18*P*B*k flops; 4*(P*(C_l + B) + C_l*B) + 4*(P*(B + k) + 9*B*k) bytes.  The roof whose time
+    over the launches below is the larger is reported: fp32 MFMA at k = 12 (9.6 us against 7.9 at
+    8 TB/s) and at k = 24.  The launches are the layers of the workload's largest dense block that take this
+    instantiation (C_l >= 49), with the block's own strides (x_l's gradient is the compact slice
+    that the 3x3 data gradient writes), through the single-op entry point, each launch stamping
+    its own pair of events at the kernel's start and end on the launch stream.  (Inside the step
+    the launch also ends the layer's BN1 backward, a few hundred partial sums per channel, and
+    adds up the previous layer's weight-gradient partials: about 20 MB more.)"""
     import numpy as np
     cfg = runs[0].cfg
     n, B, k, h, w, m = cfg.n, cfg.bottleneck, cfg.growth, cfg.h, cfg.w, cfg.layers
@@ -284,7 +285,7 @@ def dominant_kernel_roofline(dnb, torch, runs, traffic_key):
     c_out = cfg.c0 + m * k
     dev = "cuda"
     y = torch.randn((n, c_out, h, w), device=dev)
-    G = torch.randn((n, c_out, h, w), device=dev)
+    g = torch.randn((n, k, h, w), device=dev)
     db = torch.randn((n, B, h, w), device=dev)
     bact = torch.randn((n, B, h, w), device=dev)
     fold2 = torch.stack([torch.ones(B, device=dev), torch.zeros(B, device=dev)], dim=1).contiguous()
@@ -295,32 +296,28 @@ def dominant_kernel_roofline(dnb, torch, runs, traffic_key):
     for c in cs:
         fold1 = torch.stack([torch.ones(c, device=dev), torch.zeros(c, device=dev)], dim=1).contiguous()
         dw1 = torch.empty((B, c, 1, 1), device=dev)
-        dact = torch.randn((n, c, h, w), device=dev)
-        ones, zeros = torch.ones(c, device=dev), torch.zeros(c, device=dev)
         scratch = torch.empty(dnb.dnb_op_layer_wgrads_scratch_bytes(n, c, B, k, h, w), dtype=torch.uint8, device=dev)
-        g = G[:, c:c + k]     # the slab's slice of this layer, image stride c_out*hw
-        args = (y, c_out * hw, fold1, db, dw1, c, bact, fold2, g, c_out * hw, dw3, n, B, k, h, w, scratch)
-        kw = dict(bn_dact=dact, bn_gamma=ones, bn_beta=zeros, bn_mean=zeros, bn_istd=ones)
-        dnb.dnb_op_layer_wgrads(*args, **kw)   # warm
+        args = (y, c_out * hw, fold1, db, dw1, c, bact, fold2, g, k * hw, dw3, n, B, k, h, w, scratch)
+        dnb.dnb_op_layer_wgrads(*args)   # warm
         evs = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(reps)]
         for e0, e1 in evs:
             e0.record(); e1.record()   # creates the handles; the launch below re-stamps both
-            dnb.dnb_op_layer_wgrads(*args, ev_start=e0, ev_stop=e1, **kw)
+            dnb.dnb_op_layer_wgrads(*args, ev_start=e0, ev_stop=e1)
         torch.cuda.synchronize()
         ms_sum += float(np.mean([e0.elapsed_time(e1) for e0, e1 in evs]))
         flops += 2.0 * n * hw * c * B + 18.0 * n * hw * B * k
-        nbytes += 4.0 * (n * hw * (c + B) + c * B) + 4.0 * (n * hw * (B + k) + 9 * B * k) + 8.0 * n * hw * c
+        nbytes += 4.0 * (n * hw * (c + B) + c * B) + 4.0 * (n * hw * (B + k) + 9 * B * k)
         launches += 1
     ms = ms_sum / launches
     t_hbm, t_mfma = nbytes / (HBM_PEAK_GBS * 1e9), flops / (MFMA_F32_PEAK_TF * 1e12)
     common = {"kernel": DOMINANT.get(traffic_key, ("k_wgrad_pair",))[0] +
-              " (a layer's 1x1 and 3x3 weight gradients and its BN1 backward reduction in one launch)",
+              " (a layer's 1x1 and 3x3 weight gradients in one launch)",
               "traffic": measured_traffic(traffic_key), "avg_launch_ms": round(ms, 5),
               "algorithmic_flops_per_launch": int(flops / launches),
               "algorithmic_bytes_per_launch": int(nbytes / launches), "launches_averaged": launches * reps,
               "shapes": "B = %d, k = %d over P = %d pixels, C_l = %d..%d (the %d layers of the first dense block with "
                         "C_l >= 49)" % (B, k, n * hw, cs[0], cs[-1], launches)}
-    del y, G, db, bact
+    del y, g, db, bact
     if t_hbm >= t_mfma:
         achieved = nbytes / (ms_sum * 1e-3) / 1e9
         return dict({"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -411,23 +408,15 @@ def extra_fp32_net(dnb, torch, wl, name, steps, warmup):
 
 
 def extra_bf16_blocks(dnb, torch, wl, name, steps, warmup, use_graph=True, compare=True):
-    """The dense-block set of an ImageNet-shaped bf16 / NHWC workload (batch 32): the fused schedule
-    as the library runs it by default (weight gradients on a helper stream) and, for the recompute
-    overhead, the three schedules in program order on one stream (the materialised ones only run
-    that way), with their exact peak feature-map bytes."""
+    """The dense-block set of an ImageNet-shaped bf16 / NHWC workload (batch 32): the three schedules,
+    each in program order on one stream, with their exact peak feature-map bytes."""
     sched = {"shared": dnb.DNB_SCHED_SHARED, "store_all": dnb.DNB_SCHED_STORE_ALL, "fused": dnb.DNB_SCHED_FUSED}
     blocks, wname = workload_blocks(wl, name, 0)
     batch = blocks[0].n
     out = {"workload": wname, "steps": steps, "warmup": warmup}
     t = {}
-    for label, sname, serial in (("fused", "fused", False), ("fused_one_stream", "fused", True), ("shared", "shared", True),
-                                 ("store_all", "store_all", True)):
-        if not compare and label != "fused":
-            continue
-        runs = [BlockRun(dnb, torch, wl, c, sched[sname], 10 * i, True) for i, c in enumerate(blocks)]
-        if serial:
-            for r in runs:
-                dnb.dnb_block_set_concurrency(r.h, False)
+    for label in ("fused", "shared", "store_all") if compare else ("fused",):
+        runs = [BlockRun(dnb, torch, wl, c, sched[label], 10 * i, True) for i, c in enumerate(blocks)]
         t[label] = time_steps(torch, make_step(dnb, runs), steps, warmup, use_graph)
         out[label] = {"images_per_s": round(batch * steps / t[label], 2), "ms_per_step": round(1e3 * t[label] / steps, 4),
                       "feature_map_bytes": sum(r.mem["peak_bytes"] for r in runs)}
@@ -437,28 +426,22 @@ def extra_bf16_blocks(dnb, torch, wl, name, steps, warmup, use_graph=True, compa
         torch.cuda.empty_cache()
     if compare:
         out["recompute_overhead"] = round(t["shared"] / t["store_all"] - 1.0, 4)
-        out["fused_vs_store_all_time"] = round(t["fused_one_stream"] / t["store_all"] - 1.0, 4)
+        out["fused_vs_store_all_time"] = round(t["fused"] / t["store_all"] - 1.0, 4)
     return out
 
 
 def extra_bf16_net(dnb, torch, wl, name, steps, warmup, use_graph=True, compare=True):
     """The whole training step of an ImageNet-shaped bf16 / NHWC workload (batch 32, 224x224 inputs:
-    stem, max pool, four dense blocks, transitions, head, loss): the fused schedule as the library
-    runs it by default and the three schedules in program order on one stream, with the exact
-    feature-map bytes of the whole network."""
+    stem, max pool, four dense blocks, transitions, head, loss) under the three schedules, each in
+    program order on one stream, with the exact feature-map bytes of the whole network."""
     sched = {"shared": dnb.DNB_SCHED_SHARED, "store_all": dnb.DNB_SCHED_STORE_ALL, "fused": dnb.DNB_SCHED_FUSED}
     icfg = wl.inet_config4() if name == "config4" else wl.inet_config5()
     shape = "DenseNet-161-shaped k=48, blocks 6-12-36-24" if name == "config4" else "DenseNet-264-shaped k=32, blocks 6-12-64-48"
     out = {"workload": f"{shape}, batch {icfg.n}, 3x224x224 inputs, bf16 NHWC, whole network: 7x7 stride-2 stem, max pool, 4 dense "
                        "blocks, 3 transitions, head, softmax cross-entropy (fwd+bwd)", "steps": steps, "warmup": warmup}
     t = {}
-    for label, sname, serial in (("fused", "fused", False), ("fused_one_stream", "fused", True), ("shared", "shared", True),
-                                 ("store_all", "store_all", True)):
-        if not compare and label != "fused":
-            continue
-        r = InetRun(dnb, torch, wl, icfg, sched[sname])
-        if serial:
-            dnb.dnb_inet_set_concurrency(r.h, False)
+    for label in ("fused", "shared", "store_all") if compare else ("fused",):
+        r = InetRun(dnb, torch, wl, icfg, sched[label])
         t[label] = time_steps(torch, make_inet_step(dnb, r), steps, warmup, use_graph)
         out[label] = {"images_per_s": round(icfg.n * steps / t[label], 2), "ms_per_step": round(1e3 * t[label] / steps, 4),
                       "network_feature_map_bytes": r.peak, "workspace_bytes": r.workspace}
@@ -467,7 +450,7 @@ def extra_bf16_net(dnb, torch, wl, name, steps, warmup, use_graph=True, compare=
         torch.cuda.empty_cache()
     if compare:
         out["recompute_overhead"] = round(t["shared"] / t["store_all"] - 1.0, 4)
-        out["fused_vs_store_all_time"] = round(t["fused_one_stream"] / t["store_all"] - 1.0, 4)
+        out["fused_vs_store_all_time"] = round(t["fused"] / t["store_all"] - 1.0, 4)
     return out
 
 
