@@ -167,12 +167,15 @@ int dnb_block_relu_decisions(dnb_block* b, const void* params, const void* y, co
                              void* d2, void* stream);
 
 /* Section 4's "regular back-propagation" after re-population leaves the order of independent
- * kernels open: the fp32 backward pass of images whose rows are not 16-byte vectors (w % 4 != 0) can run
- * its two weight-gradient chains on helper streams owned by the block (created at the first such
+ * kernels open.  The fp32 backward passes of bottleneck layers that keep the BN passes apart can run
+ * their two weight-gradient chains on helper streams owned by the block (created at the first such
  * backward call, joined to `stream` before the call's last kernel), so that they overlap the
- * data-gradient chain.  enable = 0 puts everything on `stream` in
- * program order; results are bit-identical either way.  Default: disabled (measured slower on one
- * MI355X).  Every other backward pass is one chain of launches on `stream` and takes no notice of it. */
+ * data-gradient chain: images whose rows are not 16-byte vectors (w % 4 != 0), growth rates above 128,
+ * and slices whose staged rows take more than 60 KB of LDS (above 116 channels at w = 16, 92 at w = 32).
+ * enable = 0 puts everything on `stream` in program order; results are bit-identical either way.
+ * Default: disabled (measured slower on one MI355X).  Every other backward pass (all bf16 ones, the
+ * aligned fp32 ones, blocks without a bottleneck) is one chain of launches on `stream` and takes no
+ * notice of it. */
 int dnb_block_set_concurrency(dnb_block* b, int enable);
 
 const char* dnb_status_string(int status);
@@ -356,7 +359,7 @@ int dnb_net_workspace_piece(const dnb_net* net, int i, const char** name, int* i
  * dnb_net_forward on the same workspace and stream; `out` is a device pointer. */
 size_t dnb_net_relu_decision_bytes(const dnb_net* net);
 int dnb_net_relu_decisions(dnb_net* net, const void* params, const void* workspace, void* out, void* stream);
-int dnb_net_set_concurrency(dnb_net* net, int enable); /* helper streams in the blocks' backward */
+int dnb_net_set_concurrency(dnb_net* net, int enable); /* dnb_block_set_concurrency on every block */
 int dnb_net_forward(dnb_net* net, const void* x, const int32_t* labels, const void* params, float* loss,
                     float* logits, void* workspace, void* stream);
 int dnb_net_backward(dnb_net* net, const void* x, const void* params, void* dparams, void* workspace,
@@ -411,7 +414,7 @@ size_t dnb_inet_param_count(const dnb_inet* net);
 int dnb_inet_param_offset(const dnb_inet* net, int part, size_t* offset, size_t* count);
 size_t dnb_inet_workspace_bytes(const dnb_inet* net);
 size_t dnb_inet_peak_bytes(const dnb_inet* net);   /* feature-map bytes: the blocks' exact accounting plus the glue's */
-int dnb_inet_set_concurrency(dnb_inet* net, int enable);
+int dnb_inet_set_concurrency(dnb_inet* net, int enable);   /* accepted; the bf16 backward is one chain either way */
 int dnb_inet_forward(dnb_inet* net, const void* x, const int32_t* labels, const void* params, float* loss,
                      float* logits, void* workspace, void* stream);
 int dnb_inet_backward(dnb_inet* net, const void* x, const void* params, void* dparams, void* workspace,

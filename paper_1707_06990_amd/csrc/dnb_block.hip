@@ -25,9 +25,9 @@ struct dnb_block {
   size_t off_part;                           // reduction partials of the main chain (BN)
   size_t off_K, part1_floats;                // backward: K0, K1 per channel; where BN2's partials start in off_part
   size_t off_partA[2], off_partB[2];         // partials of the 3x3 / 1x1 weight gradients, layer l's in [l & 1]
-  // with concurrency on, backward runs three chains: the data-gradient chain on the caller's
-  // stream and the two weight-gradient chains on these helper streams (created at the first
-  // such backward call); off, everything runs on the caller's stream
+  // with concurrency on, the fp32 backward with separate BN passes runs three chains: the data-gradient
+  // chain on the caller's stream and the two weight-gradient chains on these helper streams (created at
+  // the first such backward call); off, and in the merged chains, everything runs on the caller's stream
   int concurrency;
   bool streams_ready;
   hipStream_t sA, sB;
@@ -370,7 +370,7 @@ int backward_f32(dnb_block* b, const float* params, const float* y, const float*
 
 // ---- fp32 NCHW without a bottleneck: each layer is BN -> ReLU -> 3x3 conv on the concatenation
 // (the composite function as first defined, Section 2 "Dense connectivity").  Storage 1 and 2 are
-// used exactly as with a bottleneck; there is no storage 3 and no kept b_l.  The 
+// used exactly as with a bottleneck; there is no storage 3 and no kept b_l.  The
 // K-chunked 3x3 kernels take the wide conv (C_l input channels); everything runs in program order
 // on the caller's stream.
 int forward_plain3x3(dnb_block* b, const float* x0, const float* params, float* y, char* ws, hipStream_t st) {
@@ -666,8 +666,7 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
   b->off_K = carve_scratch(B > 0 ? (size_t)cout * 2 : 0, true);
   mem.scratch_bytes = (uint64_t)scratch;
   // measured on MI355X: with the weight gradients on helper streams the fp32 step is slower (idle
-  // time between dependent launches of different streams outweighs the overlap); the bf16 backward
-  // pass is one chain of launches on the caller's stream
+  // time between dependent launches of different streams outweighs the overlap)
   b->concurrency = 0;
   b->streams_ready = false;
   b->sA = b->sB = nullptr;

@@ -16,8 +16,8 @@
 // separate passes (gradient written 2; reduction 2 + 2; element-wise pass 2 + 2 + 4 + 4; the slab's
 // initial copy of dy, another 6 per element of the block's output, goes away too: the first layer
 // that touches the slab reads dy in its place).  Against the separate passes, on one stream where
-// those ran beside a helper stream: DenseNet-264-shaped step at batch 32, 25.9 -> 20.5 ms;
-// DenseNet-161-shaped, 20.1 -> 17.2 ms at batch 32, 11.6 -> 8.0 ms at batch 2.
+// those ran beside a helper stream: DenseNet-264-shaped step at batch 32, 22.5 -> 20.4 ms;
+// DenseNet-161-shaped, 17.4 -> 17.2 ms at batch 32, 10.6 -> 8.0 ms at batch 2.
 #include "dnb_internal.h"
 #include "dnb_nhwc_dev.h"
 #include "dnb_stats.h"
