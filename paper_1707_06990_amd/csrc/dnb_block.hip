@@ -34,6 +34,7 @@ struct dnb_block {
   std::vector<hipEvent_t> ev;                // per layer: main done, db ready, S1/S2 ready, wgrad1 done
   hipEvent_t ev_start, ev_endA, ev_endB;
   size_t off_pack;                           // packed weights of all layers
+  size_t off_tail;                           // from here on: scratch that no call leaves anything in for another
   std::vector<size_t> pk;                    // per layer: float offset of its packed weights
   std::vector<size_t> poff;                  // parameter offsets (elements) per layer
   size_t pcount;
@@ -441,6 +442,16 @@ int backward_plain3x3(dnb_block* b, const float* params, const float* y, const f
 
 }  // namespace
 
+// The scratch at the end of a block's workspace holds nothing from one call to the next, so blocks that run one
+// after the other on one stream can share one: its offset in the block's own workspace, and the offset (from
+// the start of that workspace) at which the block is to look for it instead.
+size_t dnb::block_tail_offset(const dnb_block* b) { return b->off_tail; }
+void dnb::block_move_tail(dnb_block* b, size_t to) {
+  for (size_t* o : {&b->off_part, &b->off_partA[0], &b->off_partA[1], &b->off_partB[0], &b->off_partB[1], &b->off_K})
+    if (*o >= b->off_tail) *o = *o - b->off_tail + to;
+  b->off_tail = to;
+}
+
 extern "C" {
 
 const char* dnb_status_string(int status) {
@@ -655,6 +666,8 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
     scratch += bytes;
     return carve(bytes, false);
   };
+  b->off_pack = carve_scratch(pack, false);
+  b->off_tail = off;
   b->off_part = carve_scratch(part, false);
   // with a bottleneck two buffers each, used alternately by consecutive layers (a layer's partials are
   // summed by extra workgroups of the next layer's weight-gradient launch)
@@ -662,7 +675,6 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
     b->off_partB[i] = carve_scratch(partB, true);
     b->off_partA[i] = B > 0 || i == 0 ? carve_scratch(partA, true) : b->off_partA[0];
   }
-  b->off_pack = carve_scratch(pack, false);
   b->off_K = carve_scratch(B > 0 ? (size_t)cout * 2 : 0, true);
   mem.scratch_bytes = (uint64_t)scratch;
   // measured on MI355X: with the weight gradients on helper streams the fp32 step is slower (idle

@@ -490,12 +490,15 @@ int dnb_inet_create(const dnb_inet_desc* desc, dnb_inet** out) {
   auto need = [&](size_t f) { if (f > part) part = f; };
   need(nhwc::bn_bwd_partial_floats((int64_t)Ps, cs));
   need((size_t)stem_wgrad_groups(d.n, d.image) * cs * kTaps);
+  size_t tail_max = 0;
   for (int b = 0; b < 4; ++b) {
     const dnb_block_desc& bd = net->bd[b];
     const size_t hw = (size_t)bd.h * bd.w, P = hw * d.n, co = (size_t)net->cout[b];
     net->o_feat[b] = carve((size_t)bd.c0 * P * 2, true);
     net->o_y[b] = carve(co * P * 2, true);
-    net->o_ws[b] = carve(dnb_block_workspace_bytes(net->blk[b]), false);
+    const size_t tail = dnb_block_workspace_bytes(net->blk[b]) - block_tail_offset(net->blk[b]);
+    if (tail > tail_max) tail_max = tail;
+    net->o_ws[b] = carve(block_tail_offset(net->blk[b]), false);
     net->o_stat[b] = carve(co * 8, false);
     net->o_fold[b] = carve(co * 8, false);
     if (co * P > pmax) pmax = co * P;
@@ -517,6 +520,9 @@ int dnb_inet_create(const dnb_inet_desc* desc, dnb_inet** out) {
   net->o_dconv = carve(conv_max * 2, true);   // gradient of a transition's conv output
   net->o_dfeat = carve(feat_max * 2, true);   // gradient of a block input
   net->o_da0 = carve(Ps * cs * 2, true);      // gradient of the stem's BN+ReLU output, then of the stem conv's output
+  // one scratch for the four blocks, which run one after the other
+  const size_t o_tail = carve(tail_max, false);
+  for (int b = 0; b < 4; ++b) block_move_tail(net->blk[b], o_tail - net->o_ws[b]);
   net->o_part = carve(part * 4, false);
   net->o_stem_wt = carve((size_t)kTaps * cs * 4, false);
   const size_t C = (size_t)net->cout[3];

@@ -5,7 +5,13 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+struct dnb_block;
+
 namespace dnb {
+
+// (dnb_block.hip) where a block's call-local scratch starts in its workspace, and moving it elsewhere
+size_t block_tail_offset(const dnb_block* b);
+void block_move_tail(dnb_block* b, size_t to);
 
 // ---- element-wise and reduction kernels (HBM-bound) -------------------------------------
 

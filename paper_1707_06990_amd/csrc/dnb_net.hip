@@ -313,13 +313,15 @@ int dnb_net_create(const dnb_net_desc* desc, dnb_net** out) {
     net->layout.push_back(dnb_net::Piece{name, index, o, bytes});
     return o;
   };
-  size_t part = 0, pmax = 0;
+  size_t part = 0, pmax = 0, tail_max = 0;
   for (int b = 0; b < 3; ++b) {
     const dnb_block_desc& bd = net->bd[b];
     const size_t hw = (size_t)bd.h * bd.w, P = hw * d.n, co = (size_t)net->cout[b];
     net->o_feat[b] = carve((size_t)bd.c0 * P * 4, true, "feat", b);
     net->o_y[b] = carve(co * P * 4, true, "y", b);
-    net->o_ws[b] = carve(dnb_block_workspace_bytes(net->blk[b]), false, "block_ws", b);
+    const size_t tail = dnb_block_workspace_bytes(net->blk[b]) - block_tail_offset(net->blk[b]);
+    if (tail > tail_max) tail_max = tail;
+    net->o_ws[b] = carve(block_tail_offset(net->blk[b]), false, "block_ws", b);
     net->o_tz[b] = carve(co * P * 4, true, "tz", b);
     net->o_mean[b] = carve(co * 4, false, "mean", b);
     net->o_istd[b] = carve(co * 4, false, "istd", b);
@@ -351,6 +353,9 @@ int dnb_net_create(const dnb_net_desc* desc, dnb_net** out) {
   net->o_dtz = carve(pmax * 4, true, "dtz");        // gradient of a transition's BN+ReLU output
   net->o_dconv = carve(conv_max * 4, true, "dconv");  // gradient of a transition's conv output
   net->o_dfeat = carve(feat_max * 4, true, "dfeat");  // gradient of a block input
+  // one scratch for the three blocks, which run one after the other
+  const size_t o_tail = carve(tail_max, false, "block_scratch");
+  for (int b = 0; b < 3; ++b) block_move_tail(net->blk[b], o_tail - net->o_ws[b]);
   net->o_part = carve(part * 4, false, "part");
   const size_t C = (size_t)net->cout[2];
   net->o_pooled = carve((size_t)d.n * C * 4, false, "pooled");

@@ -135,13 +135,16 @@ NOBOTTLE = [wl.BlockCfg(2, 8, 8, 8, 3, 4, 0), wl.BlockCfg(3, 5, 5, 7, 4, 3, 0)] 
     ("net", 873_996_288, dict(n=64, image=32, depth=100, growth=12, classes=10, schedule=2), False),
     ("net", 1_045_927_424, dict(n=64, image=32, depth=100, growth=12, classes=10, schedule=0), False),
     ("net", 4_202_403_584, dict(n=64, image=32, depth=250, growth=24, classes=100, schedule=2), False),
-], ids=["small-block", "plain-block", "bf16-block", "bc100-fused", "bc100-shared", "bc250-fused"])
+    ("inet", 1_812_315_904, dict(n=32, image=224, growth=48, layers=(6, 12, 36, 24), classes=1000, schedule=2), False),
+    ("inet", 1_407_834_624, dict(n=32, image=224, growth=32, layers=(6, 12, 64, 48), classes=1000, schedule=2), False),
+    ("inet", 305_884_928, dict(n=2, image=224, growth=48, layers=(6, 12, 36, 24), classes=1000, schedule=2), False),
+], ids=["small-block", "plain-block", "bf16-block", "bc100-fused", "bc100-shared", "bc250-fused", "dn161", "dn264", "dn161-batch-2"])
 def test_weight_gradient_partials_do_not_grow_the_workspace(dnb, kind, limit, args, bf16):
     """The limits are what these shapes took with separate BN backward passes.  The merged backward chains
     need a second partial buffer in bf16, more splits of the any-shape kernel and packed weights without a
     bottleneck; the partials of kernels that a block never launches are not counted, a block without a
-    bottleneck has one buffer, and what only the backward pass uses lies in the gradient scratch that the
-    merged chains leave free."""
+    bottleneck has one buffer, what only the backward pass uses lies in the gradient scratch that the merged
+    chains leave free, and the four blocks of an ImageNet-shaped network share one call-local scratch."""
     if bf16:
         args = dict(args, dtype=dnb.DNB_BF16, layout=dnb.DNB_NHWC)
     h = getattr(dnb, f"dnb_{kind}_create")(**args)
