@@ -182,7 +182,7 @@ __global__ __launch_bounds__(256) void k_pack_weights(const float* __restrict__ 
 // buffer (BN+ReLU applied, rounded to bf16) after them: one barrier per chunk, load latency
 // under the matrix work.  TIN = u16 (bf16) or float (the gradient slab).  STATS: per-tile
 // (count, mean, M2) of the rounded outputs, as in the fp32 kernels: spart[(m*T + tile)*3].
-template <int TAPS, int MT, typename TIN, bool PRO, bool STATS, bool RING>
+template <int TAPS, int MT, typename TIN, bool PRO, bool STATS>
 __global__ __launch_bounds__(256) void k_conv(
     const TIN* __restrict__ in, int64_t in_ld, const u16* __restrict__ Wp, int M16, int K32,
     u16* __restrict__ out, int64_t out_ld, int cin, int cout, int H, int W, int64_t Ptot,
@@ -285,9 +285,9 @@ __global__ __launch_bounds__(256) void k_conv(
   };
 
   // packed weights of one (chunk, tap): MT M-tiles x 2 K-steps, 16 bytes per lane each.  They
-  // come from L2 at best and, early in a launch, from HBM, so they are requested several steps
-  // before their use, into a ring of register sets indexed statically: the 1x1 keeps four chunks
-  // in flight (chunk loop unrolled by four), the 3x3 nine taps (MT == 1) or three.  Rows past M16
+  // come from L2 at best and, early in a launch, from HBM, so they are requested before their use, into
+  // a ring of register sets indexed statically: the 1x1 one chunk ahead, the 3x3 nine taps (MT == 1) or
+  // three.  Rows past M16
   // and K-steps past K32 are clamped: their products are never formed or never stored.
   struct WSet { uint4 w[MT][2]; };
   auto wload = [&](int c0, int t9, WSet& ws) {
@@ -326,61 +326,31 @@ __global__ __launch_bounds__(256) void k_conv(
   };
 
   const int clast = ((cin - 1) / KC) * KC;  // start of the last chunk
-  if (RING) {  // 1x1 with many chunks
-    // chunk x lives in ring slot x % 4 (activations and weights alike): step s multiplies chunk
-    // c, requests chunk c+4 into the slots it has just freed and deposits chunk c+1
-    Raw r[4][U];
-    WSet wt[4];
-    request(0, r[0]);
-    wload(0, 0, wt[0]);
+  constexpr int WD = TAPS == 1 ? 1 : (MT == 1 ? 9 : 3);
+  Raw va[U];
+  {
+    Raw v[U];
+    request(0, v);
+    request(min(KC, clast), va);
+    deposit(0, v, 0);
+  }
+  WSet wt[WD];
 #pragma unroll
-    for (int x = 1; x < 4; ++x) {
-      wload(min(x * KC, clast), 0, wt[x]);
-      request(min(x * KC, clast), r[x]);
+  for (int s = 0; s < WD; ++s) wload(0, s, wt[s]);
+  __syncthreads();
+  int it = 0;
+  for (int c0 = 0; c0 < cin; c0 += KC, ++it) {
+    const int boff = (it & 1) * BUFE;
+    const int cn = min(c0 + KC, clast);
+#pragma unroll
+    for (int t9 = 0; t9 < TAPS; ++t9) {
+      mm(c0, t9, boff, wt[t9 % WD]);
+      if (t9 + WD < TAPS) wload(c0, t9 + WD, wt[t9 % WD]);
+      else wload(cn, t9 + WD - TAPS, wt[t9 % WD]);
     }
-    deposit(0, r[0], 0);
+    if (c0 + KC < cin) deposit(c0 + KC, va, ((it & 1) ^ 1) * BUFE);
+    request(min(c0 + 2 * KC, clast), va);  // in flight across the barrier and the next chunk's MFMAs
     __syncthreads();
-    // The loop always runs whole groups of four steps: steps past the last chunk load (clamped),
-    // deposit and synchronise like the others and only skip the MFMAs, so the sequence of loads
-    // and of waits for them is the same on every path.
-    for (int cb = 0; cb < cin; cb += 4 * KC) {
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int c0 = cb + s * KC, cn = min(c0 + 4 * KC, clast);
-        if (c0 < cin) mm(c0, 0, (s & 1) * BUFE, wt[s]);
-        wload(cn, 0, wt[s]);
-        request(cn, r[s]);
-        deposit(min(c0 + KC, clast), r[(s + 1) & 3], ((s & 1) ^ 1) * BUFE);
-        __syncthreads();
-      }
-    }
-  } else {
-    constexpr int WD = TAPS == 1 ? 1 : (MT == 1 ? 9 : 3);
-    Raw va[U];
-    {
-      Raw v[U];
-      request(0, v);
-      request(min(KC, clast), va);
-      deposit(0, v, 0);
-    }
-    WSet wt[WD];
-#pragma unroll
-    for (int s = 0; s < WD; ++s) wload(0, s, wt[s]);
-    __syncthreads();
-    int it = 0;
-    for (int c0 = 0; c0 < cin; c0 += KC, ++it) {
-      const int boff = (it & 1) * BUFE;
-      const int cn = min(c0 + KC, clast);
-#pragma unroll
-      for (int t9 = 0; t9 < TAPS; ++t9) {
-        mm(c0, t9, boff, wt[t9 % WD]);
-        if (t9 + WD < TAPS) wload(c0, t9 + WD, wt[t9 % WD]);
-        else wload(cn, t9 + WD - TAPS, wt[t9 % WD]);
-      }
-      if (c0 + KC < cin) deposit(c0 + KC, va, ((it & 1) ^ 1) * BUFE);
-      request(min(c0 + 2 * KC, clast), va);  // in flight across the barrier and the next chunk's MFMAs
-      __syncthreads();
-    }
   }
 
   if (!m_ok) return;
@@ -780,6 +750,9 @@ hipError_t conv(const void* in, int64_t in_ld, bool in_f32, const void* Wp, void
   const int64_t P = (int64_t)n * hw;
   // 1x1: flat 64-pixel tiles over all images; 3x3: tiles of one image
   const int64_t ptiles = taps == 9 ? (int64_t)((hw + 63) / 64) * n : (P + 63) / 64;
+  if ((fold != nullptr) != (spart != nullptr) && fold) return hipErrorInvalidValue;
+  if (taps == 1 && spart && !in_f32 && conv1_stats(in, in_ld, Wp, out, out_ld, P, cin, cout, fold, spart, sT, st))
+    return hipGetLastError();
   int mt = (mtiles + 3) / 4;
   if (mt > 3) mt = 3;
   // few pixel tiles: split the output channels over more workgroups (each repeats the staging,
@@ -792,29 +765,21 @@ hipError_t conv(const void* in, int64_t in_ld, bool in_f32, const void* Wp, void
   const int halo = taps == 9 ? w + 1 : 0;
   const size_t lds = (size_t)2 * (64 + 2 * halo) * 72 * sizeof(u16) + (fold ? (size_t)cin * 8 : 0);
   if (lds > 64 * 1024 || (taps == 9 && (64 + 2 * halo) * 8 > 8 * 256)) return hipErrorInvalidValue;
-  if ((fold != nullptr) != (spart != nullptr) && fold) return hipErrorInvalidValue;
-  // eight chunks or more, and about one workgroup per compute unit (with several, their phases
-  // already cover one another's latencies and the ring's extra loads only cost).  (Chunks of 128
-  // channels instead of 64 in this form -- half the barriers, 171-218 registers -- were slower:
-  // 13.9 -> 14.3 ms per step of the DenseNet-161-shaped blocks.)
-  const bool ring = taps == 1 && cin >= 512 && ptiles * gy <= 320;
-#define DNB_K(TAPS, MT, TIN, PRO, STATS, RING)                                                                  \
-  hipLaunchKernelGGL((k_conv<TAPS, MT, TIN, PRO, STATS, RING>), grid, dim3(256), lds, st, (const TIN*)in, in_ld, \
+#define DNB_K(TAPS, MT, TIN, PRO, STATS)                                                                        \
+  hipLaunchKernelGGL((k_conv<TAPS, MT, TIN, PRO, STATS>), grid, dim3(256), lds, st, (const TIN*)in, in_ld, \
                      (const u16*)Wp, M16, K32, (u16*)out, out_ld, cin, cout, h, w, P, fold, spart, T)
-#define DNB_K2(TAPS, MT, RING)                                                        \
+#define DNB_K2(TAPS, MT)                                                              \
   do {                                                                                \
-    if (in_f32) DNB_K(TAPS, MT, float, false, false, RING);                           \
-    else if (fold) DNB_K(TAPS, MT, u16, true, true, RING);                            \
-    else if (spart) DNB_K(TAPS, MT, u16, false, true, RING);                          \
-    else DNB_K(TAPS, MT, u16, false, false, RING);                                    \
+    if (in_f32) DNB_K(TAPS, MT, float, false, false);                                 \
+    else if (fold) DNB_K(TAPS, MT, u16, true, true);                                  \
+    else if (spart) DNB_K(TAPS, MT, u16, false, true);                                \
+    else DNB_K(TAPS, MT, u16, false, false);                                          \
   } while (0)
-#define DNB_K3(TAPS, RING)                                                            \
+#define DNB_K3(TAPS)                                                                  \
   do {                                                                                \
-    if (mt == 3) DNB_K2(TAPS, 3, RING); else if (mt == 2) DNB_K2(TAPS, 2, RING); else DNB_K2(TAPS, 1, RING); \
+    if (mt == 3) DNB_K2(TAPS, 3); else if (mt == 2) DNB_K2(TAPS, 2); else DNB_K2(TAPS, 1); \
   } while (0)
-  if (taps == 9) DNB_K3(9, false);
-  else if (ring) DNB_K3(1, true);
-  else DNB_K3(1, false);
+  if (taps == 9) DNB_K3(9); else DNB_K3(1);
 #undef DNB_K3
 #undef DNB_K2
 #undef DNB_K

@@ -468,3 +468,22 @@ def test_bf16_backward_of_a_slice_wider_than_lds(dnb, oracle):
     cfg = wl.BlockCfg(1, 8, 4, 4, 2, 13600, 8)
     x0, lp, dy = wl.make_block_inputs(cfg, affine="random")
     check_bf16_block(dnb, oracle, cfg, to_bf16_values(x0), lp, to_bf16_values(dy), schedule=0)
+
+
+# The two-role 1x1 (few pixel tiles): channel tails inside a step of 128 and a K-step of 32, a last tile of 19
+# pixels, idle consumers, several groups, the six-tile groups (85 < tiles <= 128 at 192 outputs), the last tile
+# count it takes and the first it leaves to the chunked kernel.  (No batches of a few pixels: a stored b moves by
+# 2^-9 |b| and BN divides that by the channel's deviation, which over 3 values can be any fraction of |b|; with 1/10,
+# 2e-2 is gone.  Over 39 values the deviation stays near |b|.)
+FEW_PIXEL_CFGS = [wl.BlockCfg(3, 392, 7, 7, 2, 8, 40), wl.BlockCfg(2, 520, 6, 6, 1, 16, 200), wl.BlockCfg(1, 8, 3, 13, 2, 8, 8),
+                  wl.BlockCfg(25, 72, 16, 16, 1, 8, 192), wl.BlockCfg(64, 24, 16, 16, 1, 8, 64), wl.BlockCfg(257, 24, 8, 8, 1, 8, 64)]
+
+
+@pytest.mark.parametrize("cfg", FEW_PIXEL_CFGS, ids=[f"n{c.n}c{c.c0}h{c.h}w{c.w}m{c.layers}k{c.growth}B{c.bottleneck}" for c in FEW_PIXEL_CFGS])
+def test_bf16_few_pixel_convolutions_match_oracle(dnb, oracle, cfg):
+    x0, lp, dy = wl.make_block_inputs(cfg, 41, 42, 43, affine="random")
+    x0, dy = to_bf16_values(x0), to_bf16_values(dy)
+    fused = check_bf16_block(dnb, oracle, cfg, x0, lp, dy)
+    shared = run_block_gpu_bf16(dnb, cfg, x0, lp, dy, schedule=0)
+    for k in ("y", "dx0", "dparams"):
+        assert np.array_equal(fused[k], shared[k]), k
