@@ -238,6 +238,9 @@ hipError_t conv(const void* in, int64_t in_ld, bool in_f32, const void* Wp, void
 // (dnb_nhwc_conv1.hip) The 1x1 with statistics of its output, few pixels; false (nothing launched) if the shape is not taken.
 bool conv1_stats(const void* in, int64_t in_ld, const void* Wp, void* out, int64_t out_ld, int64_t P, int cin, int cout,
                  const float2* fold, float* spart, int* sT, hipStream_t st);
+// (dnb_nhwc_conv3.hip) The 3x3 with statistics of its output; false (nothing launched) if the shape is not taken.
+bool conv3_stats(const void* in, int64_t in_ld, const void* Wp, void* out, int64_t out_ld, int n, int cin, int cout, int h, int w,
+                 const float2* fold, float* spart, int* sT, hipStream_t st);
 // One weight gradient: dw[m][c][t] = sum_p g[p][m] * act(a[p + shift(t)][c]), fold = BN+ReLU of a (or null).
 struct WgradIn {
   const void* a; int64_t a_ld;

@@ -753,6 +753,8 @@ hipError_t conv(const void* in, int64_t in_ld, bool in_f32, const void* Wp, void
   if ((fold != nullptr) != (spart != nullptr) && fold) return hipErrorInvalidValue;
   if (taps == 1 && spart && !in_f32 && conv1_stats(in, in_ld, Wp, out, out_ld, P, cin, cout, fold, spart, sT, st))
     return hipGetLastError();
+  if (taps == 9 && spart && !in_f32 && conv3_stats(in, in_ld, Wp, out, out_ld, n, cin, cout, h, w, fold, spart, sT, st))
+    return hipGetLastError();
   int mt = (mtiles + 3) / 4;
   if (mt > 3) mt = 3;
   // few pixel tiles: split the output channels over more workgroups (each repeats the staging,

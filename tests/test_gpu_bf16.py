@@ -476,7 +476,10 @@ def test_bf16_backward_of_a_slice_wider_than_lds(dnb, oracle):
 # 2^-9 |b| and BN divides that by the channel's deviation, which over 3 values can be any fraction of |b|; with 1/10,
 # 2e-2 is gone.  Over 39 values the deviation stays near |b|.)
 FEW_PIXEL_CFGS = [wl.BlockCfg(3, 392, 7, 7, 2, 8, 40), wl.BlockCfg(2, 520, 6, 6, 1, 16, 200), wl.BlockCfg(1, 8, 3, 13, 2, 8, 8),
-                  wl.BlockCfg(25, 72, 16, 16, 1, 8, 192), wl.BlockCfg(64, 24, 16, 16, 1, 8, 64), wl.BlockCfg(257, 24, 8, 8, 1, 8, 64)]
+                  wl.BlockCfg(25, 72, 16, 16, 1, 8, 192), wl.BlockCfg(64, 24, 16, 16, 1, 8, 64), wl.BlockCfg(257, 24, 8, 8, 1, 8, 64),
+                  # the whole-width 3x3: two, three and four M-tiles a workgroup (of five), more than 64 KB of LDS
+                  wl.BlockCfg(100, 8, 10, 10, 1, 24, 40), wl.BlockCfg(130, 8, 10, 10, 1, 48, 40), wl.BlockCfg(257, 8, 8, 8, 1, 72, 24),
+                  wl.BlockCfg(1, 8, 4, 56, 2, 8, 192)]
 
 
 @pytest.mark.parametrize("cfg", FEW_PIXEL_CFGS, ids=[f"n{c.n}c{c.c0}h{c.h}w{c.w}m{c.layers}k{c.growth}B{c.bottleneck}" for c in FEW_PIXEL_CFGS])
