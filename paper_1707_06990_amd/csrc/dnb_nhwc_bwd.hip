@@ -51,27 +51,66 @@ struct Dgrad3Args {
   float *dgamma, *dbeta; float2* Kall; const float2* fold1all; int Ckeep, first;
 };
 
-// Sum over the T partials of channel ch, the four waves taking every fourth; call with all threads,
-// ch clamped into range.  sh: 4*64 float2.  Result valid in wave 0.
+// Unsigned division of x < 2^31 by a fixed d <= 2^30: m = ceil(2^s / d) with s = 31 + ceil(log2 d), so that
+// m*d - 2^s < d <= 2^(s-31) and the excess x*(m*d - 2^s) stays below 2^s.
+struct DivBy {
+  unsigned m;
+  int s;
+  __device__ __forceinline__ unsigned div(unsigned x) const { return (unsigned)(((unsigned long long)x * m) >> s); }
+};
+
+// Sum over the T partials of channel ch, the NW waves taking every NW-th; call with all threads,
+// ch clamped into range.  sh: NW*64 float2.  Result valid in wave 0.
+template <int NW>
 __device__ __forceinline__ float2 sum_partials64(const float2* __restrict__ part, int T, int C, int ch, float2* sh) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float2 s = make_float2(0.f, 0.f);
   int t = wave;
-  for (; t + 28 < T; t += 32) {
+  for (; t + 7 * NW < T; t += 8 * NW) {
     float2 v[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(t + 4 * u) * C + ch];
+    for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(t + NW * u) * C + ch];
 #pragma unroll
     for (int u = 0; u < 8; ++u) { s.x += v[u].x; s.y += v[u].y; }
   }
-  for (; t < T; t += 4) { const float2 v = part[(int64_t)t * C + ch]; s.x += v.x; s.y += v.y; }
+  for (; t + 3 * NW < T; t += 4 * NW) {
+    float2 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = part[(int64_t)(t + NW * u) * C + ch];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) { s.x += v[u].x; s.y += v[u].y; }
+  }
+  for (; t < T; t += NW) { const float2 v = part[(int64_t)t * C + ch]; s.x += v.x; s.y += v.y; }
   __syncthreads();
   sh[wave * 64 + lane] = s;
   __syncthreads();
   float2 r = sh[lane];
 #pragma unroll
-  for (int w = 1; w < 4; ++w) { r.x += sh[w * 64 + lane].x; r.y += sh[w * 64 + lane].y; }
+  for (int w = 1; w < NW; ++w) { r.x += sh[w * 64 + lane].x; r.y += sh[w * 64 + lane].y; }
   return r;
+}
+
+// The same for channels ch and ch + 1 (ch even, C even), four waves.  sh: 4*64 float4.
+__device__ __forceinline__ float4 sum_partials128(const float2* __restrict__ part, int T, int C, int ch, float4* sh) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  int t = wave;
+  auto add = [&](const float4& v) { s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w; };
+  for (; t + 28 < T; t += 32) {
+    float4 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float4*>(part + (int64_t)(t + 4 * u) * C + ch);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) add(v[u]);
+  }
+  for (; t < T; t += 4) add(*reinterpret_cast<const float4*>(part + (int64_t)t * C + ch));
+  __syncthreads();
+  sh[wave * 64 + lane] = s;
+  __syncthreads();
+  s = sh[lane];
+#pragma unroll
+  for (int w = 1; w < 4; ++w) add(sh[w * 64 + lane]);
+  return s;
 }
 
 // Output channels (B of them) on M, pixels of one image on N.  A workgroup owns a tile of 64*NT
@@ -88,7 +127,7 @@ __global__ __launch_bounds__(256) void k_dgrad3(Dgrad3Args A) {
   const int nconv = A.T2 * A.gy;
   if ((int)blockIdx.x >= nconv) {  // finalise 64 channels of layer l+1's BN1
     const int ch = ((int)blockIdx.x - nconv) * 64 + lane, cc = min(ch, A.C1 - 1);
-    const float2 s = sum_partials64(A.part1, A.T1, A.C1, cc, sh);
+    const float2 s = sum_partials64<4>(A.part1, A.T1, A.C1, cc, sh);
     if (wave == 0 && ch < A.C1) {
       A.dbeta[ch] = s.x;
       A.dgamma[ch] = s.y;
@@ -107,7 +146,7 @@ __global__ __launch_bounds__(256) void k_dgrad3(Dgrad3Args A) {
   const int kc = BYPASS ? 64 : A.k;
   auto form_coef = [&](int c0, int at) {  // of channels c0..c0+63, to positions at..
     const int i = c0 + lane, ic = min(i, A.k - 1);
-    const float2 s = sum_partials64(A.part1, A.T1, A.C1, A.c1 + ic, sh);
+    const float2 s = sum_partials64<4>(A.part1, A.T1, A.C1, A.c1 + ic, sh);
     if (wave == 0 && i < A.k) {
       const float sc = A.fold1[ic].x * A.inv_p;
       const float2 o = A.K ? A.K[ic] : make_float2(0.f, 0.f);
@@ -271,13 +310,194 @@ __global__ __launch_bounds__(256) void k_dgrad3(Dgrad3Args A) {
   }
 }
 
+// The same for growth rates up to 64 (K-steps KS = 1 or 2 of 32 channels), which is every network of the
+// paper's family.  A workgroup walks over tiles of 64 pixels of the flat pixel axis of all images (a tap
+// outside a pixel's image is a read of a row of zeros); each of its eight waves forms one M-tile of up to
+// eight of all 64 pixels, so a tile's slice is staged once for 128 channels, the wave's weights (nine taps)
+// stay in its registers, and the sums need no exchange.  The next tile's slice is requested before the
+// current tile's products and staged into the other LDS buffer after them; the first tile's is in flight
+// while the coefficients' partial sums are added.  U: vectors of 8 channels a thread stages per tile.
+// Bounds: few pixels, two memory latencies (partial sums, slice), the staging and 36 or 72 MFMAs a wave; many,
+// LDS reads (36 or 72 KB a tile and wave) and the traffic of b and dz.  us a launch at 32 images, against
+// k_dgrad3 (which waited for its weights tap by tap, staged the tile for every 16 or 32 output channels and
+// rounded each image up to whole tiles): 32 channels to 128, 14x14 8.9 (14.2), 7x7 7.8 (9.4), 28x28 14.5 (23),
+// 56x56 35.6 (56); 48 to 192, 14x14 13 (20), 28x28 28 (43), 56x56 79 (108).
+template <int KS, int U>
+__global__ __launch_bounds__(512) void k_dgrad3s(Dgrad3Args A, int T, DivBy dhw, DivBy dw) {
+  extern __shared__ __attribute__((aligned(16))) u16 lds[];
+  __shared__ float2 sh[512];
+  __shared__ __attribute__((aligned(16))) float coef[3][64];  // K0, K1*istd, mean
+  constexpr int VS = KS == 2 ? 3 : 2, PITCH = 32 * KS + 8, RS = 512 >> VS;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), j = lane & 15, g = lane >> 4;
+  const int nconv = (A.T2 + 7) / 8 * 8 * A.gy;
+  if ((int)blockIdx.x >= nconv) {  // finalise 64 channels of layer l+1's BN1
+    const int ch = ((int)blockIdx.x - nconv) * 64 + lane, cc = min(ch, A.C1 - 1);
+    const float2 s = sum_partials64<8>(A.part1, A.T1, A.C1, cc, sh);
+    if (wave == 0 && ch < A.C1) {
+      A.dbeta[ch] = s.x;
+      A.dgamma[ch] = s.y;
+      if (ch < A.Ckeep) {
+        const float sc = A.fold1all[ch].x * A.inv_p;
+        const float2 o = A.first ? make_float2(0.f, 0.f) : A.Kall[ch];
+        A.Kall[ch] = make_float2(__fmaf_rn(sc, s.x, o.x), __fmaf_rn(sc, s.y, o.y));
+      }
+    }
+    return;
+  }
+  const int slot = blockIdx.x >> 3, grp = slot % A.gy, pw = (slot / A.gy) * 8 + (blockIdx.x & 7);
+  if (pw >= A.T2) return;
+  const int W = A.Wd, HW = A.H * W, halo = W + 1, seg = 64 + 2 * halo, BUFE = (seg + 1) * PITCH, P = A.tiles;
+  const int v = tid & ((1 << VS) - 1), r = tid >> VS, ch = min(8 * v, A.k - 8);
+  const bool cok = 8 * v < A.k;
+
+  // staging: three loads a vector (two of them again what the first brings where dy stands in for the slab)
+  struct Raw { uint4 a, b, x; };
+  const int gsz = A.dy ? 2 : 4, goff = A.dy ? 0 : 16;
+  const unsigned grow = (unsigned)A.g_ld * gsz, xrow = (unsigned)(A.dy ? A.g_ld : A.x_ld) * 2;
+  Raw raw[U];
+  auto request = [&](int tile) {
+    const int first = max(tile * 64 - halo, 0);  // scalar bases at the tile's first row, 32-bit offsets from there
+    const char* gb = (A.dy ? reinterpret_cast<const char*>(A.dy) : reinterpret_cast<const char*>(A.G)) + (int64_t)first * grow;
+    const char* xb = (A.dy ? reinterpret_cast<const char*>(A.dy) : reinterpret_cast<const char*>(A.x)) + (int64_t)first * xrow;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int s = min(r + u * RS, seg - 1);
+      const unsigned row = min(max(tile * 64 - halo + s, 0), P - 1) - first;
+      const unsigned o = row * grow + ch * gsz;
+      raw[u].a = *reinterpret_cast<const uint4*>(gb + o);
+      raw[u].b = *reinterpret_cast<const uint4*>(gb + (o + goff));
+      raw[u].x = *reinterpret_cast<const uint4*>(xb + (row * xrow + 2 * ch));
+    }
+  };
+  float k0[8], k1[8], mu0[8];
+  auto deposit = [&](int tile, int buf) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int s = r + u * RS, p = tile * 64 - halo + s;
+      V8 o, xv;
+      xv.q = raw[u].x;
+      const float gf[8] = {__uint_as_float(raw[u].a.x), __uint_as_float(raw[u].a.y), __uint_as_float(raw[u].a.z),
+                           __uint_as_float(raw[u].a.w), __uint_as_float(raw[u].b.x), __uint_as_float(raw[u].b.y),
+                           __uint_as_float(raw[u].b.z), __uint_as_float(raw[u].b.w)};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o.h[e] = f2bf(gf[e] - k0[e] - k1[e] * (bf2f(xv.h[e]) - mu0[e]));
+      if (A.dy) o.q = raw[u].a;
+      if (!A.dy && grp == 0 && cok && s >= halo && s < halo + 64 && p < P)
+        *reinterpret_cast<uint4*>(A.gl + (int64_t)p * A.k + ch) = o.q;
+      if (!cok) o.q = make_uint4(0u, 0u, 0u, 0u);
+      if (s < seg) *reinterpret_cast<uint4*>(lds + buf * BUFE + s * PITCH + 8 * v) = o.q;
+    }
+  };
+  request(pw);
+
+  const int mt = grp * 8 + wave, mtiles = A.M16 >> 4, mch = mt * 16 + 4 * g, mc = min(mch, A.B - 4);
+  const bool m_ok = mt < mtiles;  // uniform
+  V8 wv[9][KS];
+#pragma unroll
+  for (int t9 = 0; t9 < 9; ++t9)
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk)
+      wv[t9][kk].q = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(A.W) +
+                                                     (((int64_t)t9 * mtiles + min(mt, mtiles - 1)) * KS + kk) * 1024 + (unsigned)lane * 16);
+  float fs[4], ft[4], mu[4], s0[4], s1[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float2 f = A.fold2[mc + e];
+    fs[e] = f.x; ft[e] = f.y; mu[e] = A.mean_b[mc + e];
+    s0[e] = s1[e] = 0.f;
+  }
+  if (!A.dy) {
+    const int ic = min(lane, A.k - 1);
+    const float2 s = sum_partials64<8>(A.part1, A.T1, A.C1, A.c1 + ic, sh);
+    if (wave == 0) {
+      const float sc = A.fold1[ic].x * A.inv_p;
+      const float2 o = A.K ? A.K[ic] : make_float2(0.f, 0.f);
+      coef[0][lane] = __fmaf_rn(sc, s.x, o.x);
+      coef[1][lane] = __fmaf_rn(sc, s.y, o.y) * A.istd[ic];
+      coef[2][lane] = A.mean[ic];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { k0[e] = coef[0][ch + e]; k1[e] = coef[1][ch + e]; mu0[e] = coef[2][ch + e]; }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) k0[e] = k1[e] = mu0[e] = 0.f;
+  }
+  if (tid < PITCH / 4) *reinterpret_cast<uint4*>(lds + (tid / (PITCH / 8)) * BUFE + seg * PITCH + 8 * (tid % (PITCH / 8))) = make_uint4(0u, 0u, 0u, 0u);
+  deposit(pw, 0);
+  __syncthreads();
+
+  int buf = 0;
+  for (int tile = pw; tile < T; tile += A.T2, buf ^= 1) {
+    const int next = min(tile + A.T2, T - 1);
+    request(next);
+    if (m_ok) {
+      uint2 braw[4];
+      unsigned mask[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int p = tile * 64 + t * 16 + j, pc = min(p, P - 1);
+        braw[t] = *reinterpret_cast<const uint2*>(A.b + (int64_t)pc * A.B + mc);
+        const int q = pc - (int)dhw.div(pc) * HW, y = (int)dw.div(q), x = q - y * W;
+        const unsigned r3 = (x > 0 ? 1u : 0u) | 2u | (x < W - 1 ? 4u : 0u);
+        mask[t] = (y > 0 ? r3 : 0u) | (r3 << 3) | (y < A.H - 1 ? r3 << 6 : 0u);
+      }
+      f32x4 acc[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      const u16* lb = lds + buf * BUFE + 8 * g;
+#pragma unroll
+      for (int t9 = 0; t9 < 9; ++t9) {
+        const int off = (halo + (t9 / 3 - 1) * W + t9 % 3 - 1 + j) * PITCH;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const u16* xp = lb + ((mask[t] >> t9) & 1 ? off + t * 16 * PITCH : seg * PITCH);
+#pragma unroll
+          for (int kk = 0; kk < KS; ++kk) {
+            V8 x;
+            x.q = *reinterpret_cast<const uint4*>(xp + kk * 32);
+            acc[t] = mfma_bf16(wv[t9][kk], x, acc[t]);
+          }
+        }
+      }
+      // ReLU mask of BN2, the two sums over what is stored
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int p = tile * 64 + t * 16 + j;
+        if (p < P && mch < A.B) {
+          const float bf[4] = {bf2f((u16)braw[t].x), bf2f((u16)(braw[t].x >> 16)), bf2f((u16)braw[t].y), bf2f((u16)(braw[t].y >> 16))};
+          u16 h[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            h[e] = __fmaf_rn(bf[e], fs[e], ft[e]) > 0.f ? f2bf(acc[t][e]) : (u16)0;
+            const float dz = bf2f(h[e]);
+            s0[e] += dz;
+            s1[e] = __fmaf_rn(dz, bf[e] - mu[e], s1[e]);
+          }
+          *reinterpret_cast<uint2*>(A.dz + (int64_t)p * A.B + mch) =
+              make_uint2((unsigned)h[0] | ((unsigned)h[1] << 16), (unsigned)h[2] | ((unsigned)h[3] << 16));
+        }
+      }
+    }
+    if (tile + A.T2 < T) deposit(next, buf ^ 1);
+    __syncthreads();
+  }
+  if (m_ok) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float a = row16_sum(s0[e]), b = row16_sum(s1[e]);
+      if (j == 0 && mch < A.B) A.part2[(int64_t)pw * A.B + mch + e] = make_float2(a, b * A.istd_b[mch + e]);
+    }
+  }
+}
+
 // ---------------------------------------------------------------- BN2 backward, element-wise
 
 // out[c] = sum over T of part[T][C], one workgroup per 64 channels
 __global__ __launch_bounds__(256) void k_sum_pairs(const float2* __restrict__ part, int T, int C, float2* __restrict__ out) {
   __shared__ float2 sh[256];
   const int ch = blockIdx.x * 64 + (threadIdx.x & 63);
-  const float2 s = sum_partials64(part, T, C, min(ch, C - 1), sh);
+  const float2 s = sum_partials64<4>(part, T, C, min(ch, C - 1), sh);
   if (threadIdx.x < 64 && ch < C) out[ch] = s;
 }
 
@@ -289,7 +509,7 @@ __global__ __launch_bounds__(256) void k_bn2_apply(u16* __restrict__ dz, const u
                                                    const float* __restrict__ mean, const float* __restrict__ istd,
                                                    const float2* __restrict__ part, int T, float* __restrict__ dgamma,
                                                    float* __restrict__ dbeta) {
-  __shared__ float2 sh[256];
+  __shared__ float4 sh[256];
   __shared__ float4 co[256];  // scale, scale*dbeta/P, scale*dgamma/P*istd, mean
   const int L = 1 << lsh, rows = 256 >> lsh, cvl = threadIdx.x & (L - 1), pr = threadIdx.x >> lsh;
   const int cb = blockIdx.y * L * 8, ch0 = cb + cvl * 8;
@@ -303,13 +523,17 @@ __global__ __launch_bounds__(256) void k_bn2_apply(u16* __restrict__ dz, const u
     d0[u].q = *reinterpret_cast<const uint4*>(dz + p * B + chc);
     b0[u].q = *reinterpret_cast<const uint4*>(b + p * B + chc);
   }
-  for (int c0 = 0; c0 < L * 8; c0 += 64) {
-    const int cl = c0 + (threadIdx.x & 63), ch = cb + cl;
-    const float2 s = sum_partials64(part, T, B, min(ch, B - 1), sh);
+  for (int c0 = 0; c0 < L * 8; c0 += 128) {  // two channels a lane (B % 8 == 0)
+    const int cl = c0 + 2 * (threadIdx.x & 63), ch = cb + cl;
+    const float4 s = sum_partials128(part, T, B, min(ch, B - 2), sh);
     if (threadIdx.x < 64 && cl < L * 8 && ch < B) {
-      const float sc = fold2[ch].x;
-      co[cl] = make_float4(sc, sc * (s.x * inv_p), sc * (s.y * inv_p) * istd[ch], mean[ch]);
-      if (blockIdx.x == 0) { dbeta[ch] = s.x; dgamma[ch] = s.y; }
+      const float sx[2] = {s.x, s.z}, sy[2] = {s.y, s.w};
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const float sc = fold2[ch + e].x;
+        co[cl + e] = make_float4(sc, sc * (sx[e] * inv_p), sc * (sy[e] * inv_p) * istd[ch + e], mean[ch + e]);
+        if (blockIdx.x == 0) { dbeta[ch + e] = sx[e]; dgamma[ch + e] = sy[e]; }
+      }
     }
   }
   __syncthreads();
@@ -540,7 +764,8 @@ __global__ __launch_bounds__(256) void k_dx0(const float* __restrict__ G, int64_
   }
 }
 
-// Tile plan of k_dgrad3.  NT: the largest tile (64*NT pixels of one image: less halo per pixel)
+// Tile plan.  Growth rates up to 64 take k_dgrad3s: groups of up to eight M-tiles, at most one workgroup per CU,
+// as even a number of 64-pixel tiles each as that gives.  Wider ones k_dgrad3.  NT: the largest tile (64*NT pixels of one image: less halo per pixel)
 // that leaves at most 15 % of its pixels unused, else the one that leaves the fewest, within 64 KB
 // of LDS.  MT: two M-tiles per workgroup where that still gives one workgroup per CU (each M group
 // stages the tile again; four need more than 256 registers).  T2: workgroups per M group; one per
@@ -550,11 +775,27 @@ __global__ __launch_bounds__(256) void k_dx0(const float* __restrict__ G, int64_
 struct Dgrad3Plan {
   int NT, MT, tpi, tiles, gy, T2;
   bool bypass;
+  int ks, u;  // k_dgrad3s: K-steps, vectors per thread; tiles = pixels there
   size_t lds;
 };
 Dgrad3Plan plan_dgrad3(int n, int h, int w, int k, int B) {
   Dgrad3Plan p{};
   const int hw = h * w, mtiles = (B + 15) / 16;
+  const int64_t P = (int64_t)n * hw;
+  if (k <= 64 && P < ((int64_t)1 << 30)) {
+    p.ks = (k + 31) / 32;
+    const int seg = 64 + 2 * (w + 1), T = (int)((P + 63) / 64);
+    p.u = (seg + (512 >> (p.ks == 2 ? 3 : 2)) - 1) / (512 >> (p.ks == 2 ? 3 : 2));
+    p.lds = (size_t)2 * (seg + 1) * (32 * p.ks + 8) * sizeof(u16);
+    p.gy = (mtiles + 7) / 8;
+    p.tiles = (int)P;
+    int most = 256 / p.gy;
+    if (most < 1) most = 1;
+    const int per = (T + most - 1) / most;
+    p.T2 = (T + per - 1) / per;
+    if (p.u <= 2 * p.ks) return p;
+    p = Dgrad3Plan{};
+  }
   int best = 0;
   p.bypass = k > 512;
   for (int nt : {4, 2, 1}) {
@@ -626,6 +867,20 @@ hipError_t bwd_dgrad3(const BwdLayer& L, hipStream_t st) {
     fin = (A.C1 + 63) / 64;
   }
   const dim3 grid((unsigned)(p.T2 * p.gy + fin));
+  if (p.ks) {
+    auto by = [](unsigned d) {
+      int c = 0;
+      while ((1u << c) < d) ++c;
+      return DivBy{(unsigned)((((unsigned long long)1 << (31 + c)) + d - 1) / d), 31 + c};
+    };
+    const dim3 gs((unsigned)((p.T2 + 7) / 8 * 8 * p.gy + fin));
+    const int T = (int)((P + 63) / 64);
+    const DivBy dhw = by((unsigned)(L.h * L.w)), dw = by((unsigned)L.w);
+#define DNB_D3S(KS, U) hipLaunchKernelGGL((k_dgrad3s<KS, U>), gs, dim3(512), p.lds, st, A, T, dhw, dw)
+    if (p.ks == 1) { if (p.u == 1) DNB_D3S(1, 1); else DNB_D3S(1, 2); }
+    else if (p.u <= 2) DNB_D3S(2, 2); else if (p.u == 3) DNB_D3S(2, 3); else DNB_D3S(2, 4);
+#undef DNB_D3S
+  } else {
 #define DNB_D3(NT, MT)                                                                             \
   do {                                                                                             \
     if (p.bypass) hipLaunchKernelGGL((k_dgrad3<NT, MT, true>), grid, dim3(256), p.lds, st, A);     \
@@ -638,13 +893,14 @@ hipError_t bwd_dgrad3(const BwdLayer& L, hipStream_t st) {
   if (p.NT == 4) DNB_D3M(4); else if (p.NT == 2) DNB_D3M(2); else DNB_D3M(1);
 #undef DNB_D3M
 #undef DNB_D3
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // BN2's element-wise pass.  Up to 64 partials per channel are added by its own workgroups; more
-  // (large images, where a launch weighs little) are first brought down to one.
+  // BN2's element-wise pass.  Up to 128 partials per channel are added by its own workgroups (98 take them 1 us,
+  // a launch 4.5); more (large images, where a launch weighs little) are first brought down to one.
   const float2* part = (const float2*)L.part2;
   int T = p.T2;
-  if (T > 64) {
+  if (T > 128) {
     float2* one = (float2*)L.part2 + (int64_t)T * L.B;
     hipLaunchKernelGGL(k_sum_pairs, dim3((unsigned)((L.B + 63) / 64)), dim3(256), 0, st, part, T, L.B, one);
     part = one;

@@ -450,7 +450,11 @@ def test_nhwc_bn_relu_backward(dnb, oracle, shape, accumulate):
 # multiple of 32; more tiles than BN2 partials are added in place; more tiles than workgroups; a single short wave;
 # a slice whose coefficients are formed pass by pass, with a last pass of 24 channels
 CHAIN_CFGS = [wl.BlockCfg(2, 16, 3, 5, 3, 72, 296), wl.BlockCfg(70, 8, 4, 4, 3, 8, 32), wl.BlockCfg(300, 8, 2, 2, 2, 8, 24),
-              wl.BlockCfg(1, 24, 9, 17, 2, 24, 40), wl.BlockCfg(2, 8, 7, 3, 1, 48, 192), wl.BlockCfg(2, 8, 5, 9, 3, 536, 16)]
+              wl.BlockCfg(1, 24, 9, 17, 2, 24, 40), wl.BlockCfg(2, 8, 7, 3, 1, 48, 192), wl.BlockCfg(2, 8, 5, 9, 3, 536, 16),
+              # the chain's 3x3 for growth rates up to 64: one and two vectors a thread and K-step, the widest row, two
+              # channel groups, several tiles a workgroup, rates that are no multiple of a K-step
+              wl.BlockCfg(1, 8, 4, 70, 3, 8, 24), wl.BlockCfg(1, 8, 3, 79, 3, 40, 40), wl.BlockCfg(2, 8, 9, 57, 3, 64, 136),
+              wl.BlockCfg(300, 8, 8, 8, 3, 8, 24), wl.BlockCfg(150, 8, 11, 11, 3, 56, 264)]
 
 
 @pytest.mark.parametrize("cfg", CHAIN_CFGS, ids=[f"n{c.n}c{c.c0}h{c.h}w{c.w}m{c.layers}k{c.growth}B{c.bottleneck}" for c in CHAIN_CFGS])
