@@ -69,50 +69,98 @@ __global__ __launch_bounds__(kT) void k_global_avgpool_bwd(const float* __restri
     din[i] = dout[i / hw] * inv;
 }
 
-// logits[i][o] = bl[o] + sum_j Wl[o][j] f[i][j]; one wave per (i, o).
+// logits[i][o] = bl[o] + sum_j Wl[o][j] f[i][j].  A wave forms NO classes of 8 samples: each loaded value meets
+// 8 or NO others (one wave per logit read 10 KB for 2500 products: 63 us at 32 x 2656 x 1000, now 25).  A lane
+// takes every 64th column in order, the lanes are added by a butterfly.  grid (classes / (4*NO), samples / 8).
+template <int NO>
 __global__ __launch_bounds__(kT) void k_linear(const float* __restrict__ f, const float* __restrict__ wl,
                                                const float* __restrict__ bl, float* __restrict__ logits, int n,
                                                int c, int classes) {
-  const int idx = blockIdx.x * (kT / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (idx >= n * classes) return;
-  const int i = idx / classes, o = idx - i * classes;
-  float s = 0.f;
-  for (int j = lane; j < c; j += 64) s = __fmaf_rn(wl[(int64_t)o * c + j], f[(int64_t)i * c + j], s);
+  const int lane = threadIdx.x & 63, o0 = (blockIdx.x * (kT / 64) + (threadIdx.x >> 6)) * NO, i0 = blockIdx.y * 8;
+  if (o0 >= classes) return;
+  const float* fr[8];
+  const float* wr[NO];
 #pragma unroll
-  for (int off = 1; off < 64; off <<= 1) s += __shfl_xor(s, off, 64);
-  if (lane == 0) logits[idx] = s + bl[o];
+  for (int u = 0; u < 8; ++u) fr[u] = f + (int64_t)min(i0 + u, n - 1) * c;
+#pragma unroll
+  for (int v = 0; v < NO; ++v) wr[v] = wl + (int64_t)min(o0 + v, classes - 1) * c;
+  float s[8][NO];
+#pragma unroll
+  for (int u = 0; u < 8; ++u)
+#pragma unroll
+    for (int v = 0; v < NO; ++v) s[u][v] = 0.f;
+#pragma unroll 2
+  for (int j = lane; j < c; j += 64) {
+    float fv[8], wv[NO];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) fv[u] = fr[u][j];
+#pragma unroll
+    for (int v = 0; v < NO; ++v) wv[v] = wr[v][j];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int v = 0; v < NO; ++v) s[u][v] = __fmaf_rn(wv[v], fv[u], s[u][v]);
+  }
+#pragma unroll
+  for (int u = 0; u < 8; ++u)
+#pragma unroll
+    for (int v = 0; v < NO; ++v) {
+      float t = s[u][v];
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) t += __shfl_xor(t, off, 64);
+      if (lane == 0 && i0 + u < n && o0 + v < classes) logits[(int64_t)(i0 + u) * classes + o0 + v] = t + bl[o0 + v];
+    }
 }
 
-// Per sample: log-sum-exp, loss term, dlogits = (softmax - onehot)/n.  One workgroup; each wave takes
-// samples wave, wave + 4, ... and its lanes stride over the classes (butterfly maximum and sum, so
-// every lane holds the same values).  Then the loss terms are added in sample order by thread 0 (n
-// is a batch size: a few hundred at most).
-__global__ __launch_bounds__(kT) void k_softmax_xent(const float* __restrict__ logits,
-                                                     const int32_t* __restrict__ labels, float* __restrict__ dlogits,
-                                                     float* __restrict__ terms, float* __restrict__ loss, int n,
-                                                     int classes) {
+// Per sample: log-sum-exp, loss term, dlogits = (softmax - onehot)/n.  One workgroup of 16 waves (with four,
+// 32 samples of 1000 classes took 88 us); each wave takes samples wave, wave + 16, ... and its lanes stride over
+// the classes, the first 1024 of them in registers (butterfly maximum and sum, so every lane holds the same
+// values).  Then the loss terms are added in sample order by thread 0, from LDS (up to 4096 samples).
+constexpr int kXentWaves = 16, kXentRegs = 16;
+__global__ __launch_bounds__(64 * kXentWaves) void k_softmax_xent(const float* __restrict__ logits,
+                                                                  const int32_t* __restrict__ labels,
+                                                                  float* __restrict__ dlogits, float* __restrict__ terms,
+                                                                  float* __restrict__ loss, int n, int classes) {
+  __shared__ float sterms[4096];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int i = wave; i < n; i += kT / 64) {
+  for (int i = wave; i < n; i += kXentWaves) {
     const float* z = logits + (int64_t)i * classes;
+    const int lab = labels[i];
+    float r[kXentRegs];
+#pragma unroll
+    for (int u = 0; u < kXentRegs; ++u) r[u] = z[min(lane + 64 * u, classes - 1)];
     float mx = -3.4e38f;
-    for (int o = lane; o < classes; o += 64) mx = fmaxf(mx, z[o]);
+#pragma unroll
+    for (int u = 0; u < kXentRegs; ++u) mx = lane + 64 * u < classes ? fmaxf(mx, r[u]) : mx;
+    for (int o = lane + 64 * kXentRegs; o < classes; o += 64) mx = fmaxf(mx, z[o]);
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
     float se = 0.f;
-    for (int o = lane; o < classes; o += 64) se += expf(z[o] - mx);
+#pragma unroll
+    for (int u = 0; u < kXentRegs; ++u) se += lane + 64 * u < classes ? expf(r[u] - mx) : 0.f;
+    for (int o = lane + 64 * kXentRegs; o < classes; o += 64) se += expf(z[o] - mx);
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) se += __shfl_xor(se, off, 64);
     const float lse = mx + logf(se);
-    const int lab = labels[i];
     const bool valid = lab >= 0 && lab < classes;  // a sample with a label out of range adds nothing
-    if (lane == 0) terms[i] = valid ? lse - z[lab] : 0.f;
-    for (int o = lane; o < classes; o += 64)
-      dlogits[(int64_t)i * classes + o] = valid ? (expf(z[o] - lse) - (o == lab ? 1.f : 0.f)) / (float)n : 0.f;
+    if (lane == 0) {
+      const float t = valid ? lse - z[lab] : 0.f;
+      terms[i] = t;
+      if (n <= 4096) sterms[i] = t;
+    }
+    float* d = dlogits + (int64_t)i * classes;
+#pragma unroll
+    for (int u = 0; u < kXentRegs; ++u) {
+      const int o = lane + 64 * u;
+      if (o < classes) d[o] = valid ? (expf(r[u] - lse) - (o == lab ? 1.f : 0.f)) / (float)n : 0.f;
+    }
+    for (int o = lane + 64 * kXentRegs; o < classes; o += 64)
+      d[o] = valid ? (expf(z[o] - lse) - (o == lab ? 1.f : 0.f)) / (float)n : 0.f;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     float s = 0.f;
-    for (int i = 0; i < n; ++i) s += terms[i];
+    for (int i = 0; i < n; ++i) s += n <= 4096 ? sterms[i] : terms[i];
     *loss = s / (float)n;
   }
 }
@@ -127,7 +175,8 @@ __global__ __launch_bounds__(64 * kLbdWaves) void k_linear_bwd_data(const float*
                                                                     const float* __restrict__ wl, float* __restrict__ df,
                                                                     int n, int c, int classes) {
   __shared__ float sh[kLbdWaves - 1][8][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // (the wave's index is uniform: dlogits come through the scalar cache)
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int j = blockIdx.x * 64 + lane, jc = min(j, c - 1), i0 = blockIdx.y * 8;
   const int per = (classes + kLbdWaves - 1) / kLbdWaves, o0 = wave * per, o1 = min(classes, o0 + per);
   const float* drow[8];
@@ -211,9 +260,15 @@ namespace dnb {
 // cross-entropy with its gradient (all fp32), and the head's backward pass.
 hipError_t launch_head_forward(const float* pooled, const float* wl, const float* bl, const int32_t* labels, float* logits,
                                float* dlogits, float* terms, float* loss, int n, int c, int classes, hipStream_t st) {
-  hipLaunchKernelGGL(k_linear, dim3(grid_for((int64_t)n * classes, kT / 64)), dim3(kT), 0, st, pooled, wl, bl, logits, n, c,
-                     classes);
-  hipLaunchKernelGGL(k_softmax_xent, dim3(1), dim3(kT), 0, st, logits, labels, dlogits, terms, loss, n, classes);
+  // four classes a wave where that leaves a wave for every CU or so, else one (few classes: latency)
+  const unsigned gs = (unsigned)((n + 7) / 8);
+  if ((int64_t)classes * gs >= 512)
+    hipLaunchKernelGGL(k_linear<4>, dim3((unsigned)((classes + kT / 16 - 1) / (kT / 16)), gs), dim3(kT), 0, st, pooled, wl, bl,
+                       logits, n, c, classes);
+  else
+    hipLaunchKernelGGL(k_linear<1>, dim3((unsigned)((classes + kT / 64 - 1) / (kT / 64)), gs), dim3(kT), 0, st, pooled, wl, bl,
+                       logits, n, c, classes);
+  hipLaunchKernelGGL(k_softmax_xent, dim3(1), dim3(64 * kXentWaves), 0, st, logits, labels, dlogits, terms, loss, n, classes);
   return hipGetLastError();
 }
 
