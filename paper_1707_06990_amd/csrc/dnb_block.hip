@@ -23,7 +23,8 @@ struct dnb_block {
   std::vector<size_t> off_stat_b;            // per layer mean[B], istd[B]
   std::vector<size_t> off_fold1, off_fold2;  // fused schedule: per layer folded (scale, shift) of BN1 / BN2
   size_t off_part;                           // reduction partials of the main chain (BN)
-  size_t off_K, part1_floats;                // backward: K0, K1 per channel; where BN2's partials start in off_part
+  size_t off_K, off_db2, part1_floats, near_floats;                // backward: K0, K1 per channel; a second db (bf16, pairs of layers); where BN2's
+                                             // partials, a slice's own BN1 sums start in off_part
   size_t off_partA[2], off_partB[2];         // partials of the 3x3 / 1x1 weight gradients, layer l's in [l & 1]
   // with concurrency on, the fp32 backward with separate BN passes runs three chains: the data-gradient
   // chain on the caller's stream and the two weight-gradient chains on these helper streams (created at
@@ -253,10 +254,18 @@ int backward_bf16(dnb_block* b, const void* yv, const void* dy, void* dx0, float
   L.db = ws + b->off_dS3;
   L.mean_y = (const float*)(ws + b->off_stat_y);
   L.istd_y = L.mean_y + cout;
-  L.part1 = (float*)(ws + b->off_part);
-  L.part2 = L.part1 + b->part1_floats;
+  float* part1 = (float*)(ws + b->off_part);
+  float2* near_part = (float2*)(part1 + b->near_floats);
+  L.part2 = part1 + b->part1_floats;
   L.K = (float2*)(ws + b->off_K);
+  // Layers in pairs (upper, lower) from the top, an odd bottom layer by itself: see dnb_nhwc_bwd.hip.  Very wide
+  // bottlenecks one layer at a time, the 1x1 data gradient in a launch of its own.
+  const bool pairs = B <= nhwc::kDgrad1MaxB;
+  void* const dbs[2] = {ws + b->off_dS3, ws + b->off_db2};
+  nhwc::Dgrad1In far{};  // the pair's channels below both layers
+  far.mean = L.mean_y; far.istd = L.istd_y;
   nhwc::WgradSum sum1{}, sum3{};
+  float *up_dgamma = nullptr, *up_dbeta = nullptr;
   for (int l = m; l >= 1; --l) {
     const int c = c_in(d, l);
     const LayerGrads gp = layer_ptrs<LayerGrads, float>(b, dparams, l);
@@ -264,34 +273,66 @@ int backward_bf16(dnb_block* b, const void* yv, const void* dy, void* dx0, float
     void* S1 = ws + b->off_u[l];
     void* S2 = ws + b->off_a[l];
     void* S3 = ws + b->off_a2[l];
+    const bool upper = pairs && (m - l) % 2 == 0 && l > 1, lower = pairs && (m - l) % 2 == 1;
     L.c = c;
     L.last = l == m;
-    L.above_first = l + 1 == m;
     L.b = ws + b->off_b[l];
+    L.db = dbs[upper ? 1 : 0];
     L.x = fused ? (const void*)y : S1; L.x_ld = fused ? cout : c;
     L.pk1t = pack + b->pk[l] + B16 * c32;                              // 1x1 data gradient
     L.pk3t = pack + b->pk[l] + B16 * c32 + c16 * B32 + 9 * k16 * B32;  // 3x3 data gradient
-    L.above_fold1 = L.fold1;
-    L.above_dgamma = L.dgamma1; L.above_dbeta = L.dbeta1;
     L.fold1 = (const float2*)(ws + b->off_fold1[l]);
     L.fold2 = (const float2*)(ws + b->off_fold2[l]);
     L.mean_b = (const float*)(ws + b->off_stat_b[l]);
     L.istd_b = L.mean_b + B;
     L.dgamma1 = gp.g1; L.dbeta1 = gp.b1; L.dgamma2 = gp.g2; L.dbeta2 = gp.b2;
     DNB_TRY(nhwc::bwd_dgrad3(L, st));
+    if (L.above.n && L.above.base == 0) L.K_set = true;  // (a slice's own sums leave nothing below it)
     if (recompute) {
       DNB_TRY(nhwc::bn_relu_rows(L.b, B, L.fold2, S3, B, nullptr, 0, P, B, st));
       DNB_TRY(nhwc::bn_relu_rows(y, cout, L.fold1, S2, c, S1, c, P, c, st));
     }
-    DNB_TRY(nhwc::bwd_dgrad1(L, st));
+    // what this layer's 1x1 data gradient forms now: the lower layer's slice, both layers' channels below, or its own
+    nhwc::Dgrad1In d1 = far;
+    nhwc::BwdSums S{};
+    int most = nhwc::bwd_far_splits();
+    if (pairs) {
+      const int at = lower ? 1 : 0;
+      far.db[at] = L.db; far.W[at] = L.pk1t; far.C16[at] = (int)c16; far.fold1[at] = L.fold1;
+      d1 = far;
+      d1.x = L.x; d1.x_ld = L.x_ld;
+      d1.dy = dy; d1.G = L.G; d1.ld = cout; d1.B = B;
+      d1.nl = lower ? 2 : 1;
+      d1.cb = upper ? c - k : 0;
+      d1.ce = c;
+      d1.first = l == m || (lower && l + 1 == m);
+      S.base = d1.cb; S.width = d1.ce - d1.cb;
+      S.n = d1.nl;
+      d1.part[0] = upper ? near_part : (float2*)part1;
+      if (upper) most = nhwc::bwd_near_splits();
+      S.fold1[at] = L.fold1; S.dgamma[at] = gp.g1; S.dbeta[at] = gp.b1;
+      if (lower) { S.fold1[0] = far.fold1[0]; S.dgamma[0] = up_dgamma; S.dbeta[0] = up_dbeta; }
+      if (upper) { up_dgamma = gp.g1; up_dbeta = gp.b1; }
+    } else {
+      d1.nl = 0;
+      S.n = 1; S.base = 0; S.width = c;
+      S.part[0] = (const float2*)part1; S.fold1[0] = L.fold1; S.dgamma[0] = gp.g1; S.dbeta[0] = gp.b1;
+      DNB_TRY(nhwc::bwd_dgrad1(L, (float2*)part1, &S.T, st));
+    }
+    if (pairs) {  // the second layer's partials behind the first's
+      int ppw;
+      d1.part[1] = d1.part[0] + (size_t)S.width * nhwc::dgrad1_splits(P, S.width, most, &ppw);
+      S.part[0] = d1.part[0]; S.part[1] = d1.part[1];
+    }
     const void* gl = l == m ? (const void*)((const unsigned short*)dy + c) : L.gl;
     // both weight gradients, and the sums of layer l+1's (partial buffers used alternately)
     const nhwc::WgradIn w3{fused ? L.b : S3, B, gl, l == m ? cout : k, (float*)(ws + b->off_partA[l & 1]), gp.W3, B, k,
                            fused ? L.fold2 : nullptr};
     const nhwc::WgradIn w1{fused ? (const void*)y : S2, fused ? cout : c, L.db, B, (float*)(ws + b->off_partB[l & 1]), gp.W1, c,
                            B, fused ? L.fold1 : nullptr};
-    if (!nhwc::wgrad_pair(w1, w3, n, d.h, d.w, &sum1, &sum3, st)) return DNB_E_UNSUPPORTED;
+    if (!nhwc::wgrad_pair(w1, w3, n, d.h, d.w, &sum1, &sum3, d1, most, &S.T, st)) return DNB_E_UNSUPPORTED;
     DNB_TRY(hipGetLastError());
+    L.above = S;
   }
   DNB_TRY(nhwc::wgrad_finish(&sum1, &sum3, st));
   DNB_TRY(nhwc::bwd_dx0(L, dx0, st));
@@ -447,7 +488,7 @@ int backward_plain3x3(dnb_block* b, const float* params, const float* y, const f
 // the start of that workspace) at which the block is to look for it instead.
 size_t dnb::block_tail_offset(const dnb_block* b) { return b->off_tail; }
 void dnb::block_move_tail(dnb_block* b, size_t to) {
-  for (size_t* o : {&b->off_part, &b->off_partA[0], &b->off_partA[1], &b->off_partB[0], &b->off_partB[1], &b->off_K})
+  for (size_t* o : {&b->off_part, &b->off_partA[0], &b->off_partA[1], &b->off_partB[0], &b->off_partB[1], &b->off_K, &b->off_db2})
     if (*o >= b->off_tail) *o = *o - b->off_tail + to;
   b->off_tail = to;
 }
@@ -601,13 +642,15 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
     need(nhwc::conv_stats_partial_floats(d.n, k, d.h, d.w));
     size_t pe = 0, p1 = 0;  // pe: bf16 elements
     for (int l = 1; l <= m; ++l) {
-      const size_t f1 = nhwc::bwd_partial1_floats(P, c_in(d, l));
+      const size_t f1 = nhwc::bwd_partial1_near(P, c_in(d, l), B);
       if (f1 > p1) p1 = f1;
       const size_t f = nhwc::wgrad_partial_floats(d.n, c_in(d, l), B, d.h, d.w, 1);
       if (f > partB) partB = f;
       b->pk[l] = pe;
       pe += nhwc::packed_layer_elems(c_in(d, l), k, B);
     }
+    b->near_floats = p1;
+    p1 += nhwc::bwd_partial1_floats(P, k, k, B) - nhwc::bwd_partial1_near(P, k, B);
     b->part1_floats = p1;
     need(p1 + nhwc::bwd_partial2_floats(d.n, d.h, d.w, k, B));
     partA = nhwc::wgrad_partial_floats(d.n, B, k, d.h, d.w, 9);
@@ -676,6 +719,7 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
     b->off_partA[i] = B > 0 || i == 0 ? carve_scratch(partA, true) : b->off_partA[0];
   }
   b->off_K = carve_scratch(B > 0 ? (size_t)cout * 2 : 0, true);
+  b->off_db2 = carve_scratch(bf16 && m > 1 && B <= nhwc::kDgrad1MaxB ? ((size_t)B * Ps + 3) / 4 : 0, true);
   mem.scratch_bytes = (uint64_t)scratch;
   // measured on MI355X: with the weight gradients on helper streams the fp32 step is slower (idle
   // time between dependent launches of different streams outweighs the overlap)

@@ -259,9 +259,28 @@ struct WgradSum {
 size_t wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps);
 // Launches the partials and describes their sum in *own; false (nothing launched) if the shape is not taken.
 bool wgrad_fast(const WgradIn& in, bool g_f32, int n, int h, int w, int taps, WgradSum* own, hipStream_t st);
+// 1x1 data gradient with BN1 + concat backward on channels cb..ce-1, for one layer or for two at once (layer 0 the
+// upper one): partial sums [T][ce - cb] per layer.
+struct Dgrad1In {
+  int nl;                        // layers, 0: nothing to do
+  const void *db[2], *W[2];      // gradient of b_l [P][B]; packed weights [C16][B32]
+  int C16[2];
+  const float2* fold1[2];
+  float2* part[2];
+  const void* x; int64_t x_ld;   // concatenated features
+  const void* dy; float* G; int64_t ld;  // the slab; dy replaces its first read
+  bool first;
+  const float *mean, *istd;      // of y's channels
+  int B, cb, ce;
+};
+// ... carried by the weight-gradient launch if B <= dgrad1_max_b; pixel splits T and pixels per wave
+constexpr int kDgrad1MaxB = 256;
+int dgrad1_splits(int64_t P, int C, int most, int* ppw);
 // A layer's 1x1 and 3x3 weight gradients in one launch (bf16 gradient operands).  *s1 / *s3: in, the sums
 // pending from the layer before (of other partial buffers), carried out in this launch; out, this layer's.
-bool wgrad_pair(const WgradIn& w1, const WgradIn& w3, int n, int h, int w, WgradSum* s1, WgradSum* s3, hipStream_t st);
+// d1: a data gradient carried beside them (nl 0: none); *T1 = its splits.
+bool wgrad_pair(const WgradIn& w1, const WgradIn& w3, int n, int h, int w, WgradSum* s1, WgradSum* s3, const Dgrad1In& d1,
+                int most_splits, int* T1, hipStream_t st);
 // Carries out what is pending (either may be null).
 hipError_t wgrad_finish(WgradSum* s1, WgradSum* s3, hipStream_t st);
 size_t wgrad_partial_floats(int n, int cin, int cout, int h, int w, int taps);
@@ -274,30 +293,43 @@ hipError_t bn_relu_bwd(const void* x, int64_t x_ld, const void* dact, int64_t d_
                        const float* mean, const float* istd, float* dgamma, float* dbeta, float* part,
                        hipStream_t st);
 
+// BN1 sums still to be turned into parameter gradients and K0 / K1: of one layer or two, over channels
+// base .. base + width - 1, partials [T][width] each.  n = 0: none.
+struct BwdSums {
+  int n, T, width, base;
+  const float2* part[2];
+  const float2* fold1[2];
+  float *dgamma[2], *dbeta[2];
+};
 // One layer of the backward chain (dnb_nhwc_bwd.hip).  c = C_l input channels, ld = C_out.
 struct BwdLayer {
   int n, h, w, c, k, B;
   int64_t ld;
   bool last;                     // l = m: the slab is not written yet, dy stands in for it
-  bool above_first;              // layer l+1 is the last one: K0 / K1 are set, not added to
+  bool K_set;                    // K0 / K1 hold something
+  BwdSums above;                 // the sums the launches since the last dgrad3 left
   const void *y, *dy, *b;        // features, gradient of the output, b_l
   const void* x; int64_t x_ld;   // concatenated input of the layer: y in place, or storage 1
   float* G;                      // gradient slab
   void *gl, *db;                 // g_l in bf16 [P][k] (l < m), gradient of b_l [P][B]
   const void *pk1t, *pk3t;       // packed data-gradient weights
-  const float2 *fold1, *fold2, *above_fold1;
+  const float2 *fold1, *fold2;
   const float *mean_y, *istd_y, *mean_b, *istd_b;
-  float *dgamma1, *dbeta1, *dgamma2, *dbeta2, *above_dgamma, *above_dbeta;
-  float *part1, *part2;          // partial sums of BN1 (kept for the next layer down) and BN2
+  float *dgamma1, *dbeta1, *dgamma2, *dbeta2;
+  float* part2;                  // partial sums of BN2
   float2* K;                     // per channel of y: K0, K1
 };
-size_t bwd_partial1_floats(int64_t P, int C);
+// partial sums of BN1: of a pair of layers over C channels, then of the upper one over the lower one's k
+size_t bwd_partial1_floats(int64_t P, int C, int k, int B);
+size_t bwd_partial1_near(int64_t P, int C, int B);  // floats before the latter
+int bwd_near_splits();                              // most splits of the latter, of the former
+int bwd_far_splits();
 size_t bwd_partial2_floats(int n, int h, int w, int k, int B);
-// 3x3 data gradient and BN2 backward: db, g_l, BN2's parameter gradients, and layer l+1's BN1 parameter gradients
+// 3x3 data gradient and BN2 backward: db, g_l, BN2's parameter gradients, and what L.above holds
 hipError_t bwd_dgrad3(const BwdLayer& L, hipStream_t st);
-// 1x1 data gradient, BN1 backward and concat backward into the slab
-hipError_t bwd_dgrad1(const BwdLayer& L, hipStream_t st);
-// gradient of the block input and layer 1's BN1 parameter gradients (L: layer 1)
+// B > kDgrad1MaxB: 1x1 data gradient, BN1 backward and concat backward into the slab, one layer; *T = splits
+hipError_t bwd_dgrad1(const BwdLayer& L, float2* part, int* T, hipStream_t st);
+// gradient of the block input and the last BN1 sums (L.above over exactly its channels)
 hipError_t bwd_dx0(const BwdLayer& L, void* dx0, hipStream_t st);
 }  // namespace nhwc
 

@@ -1,10 +1,16 @@
 // bf16 / NHWC backward chain of a bottleneck layer: the kernels that carry the dependence from layer
-// l+1 to layer l.  Three launches per layer (the weight gradients hang off them):
+// l+1 to layer l.
 //
-//   k_dgrad3      3x3 data gradient of g_l, ReLU mask of BN2 and its two sums in the epilogue
-//   k_bn2_apply   gradient of b_l from those sums (element-wise on P x B)
-//   k_dgrad1      1x1 data gradient; BN1+ReLU backward and the concatenation's backward
-//                 (accumulate into the slab G) in the epilogue, with BN1's two sums
+//   k_dgrad3s / k_dgrad3   3x3 data gradient of g_l, ReLU mask of BN2 and its two sums in the epilogue
+//   k_bn2_apply            gradient of b_l from those sums (element-wise on P x B)
+//   dgrad1_body            1x1 data gradient; BN1+ReLU backward and the concatenation's backward
+//                          (accumulate into the slab G) in the epilogue, with BN1's two sums
+//
+// The last is a role of the weight-gradient launch (dnb_nhwc_wgrad.hip), which only needs db_l too, and takes
+// layers in pairs: layer l-1 needs of layer l only its own slice of the slab, so beside layer l's weight
+// gradients only those k channels are formed, and beside layer l-1's the channels of both layers below, in one
+// pass over the slab.  Three launches a layer, and 6 bytes per element of a layer's concatenated input instead of
+// 10.
 //
 // BN1's backward is  du = s*(dz - dbeta/P - xhat*dgamma/P),  dz = the masked gradient, s = gamma*istd.
 // Its first term needs no sum, so it is added into the slab where dz is formed; the other two are
@@ -12,7 +18,7 @@
 // statistics are those of the produced feature).  They are therefore collected per channel,
 //   K0 = sum_l s_l*dbeta_l/P,   K1 = sum_l s_l*dgamma_l/P,
 // and taken off once, where a slice of the slab is finally read:  g = G - K0 - K1*xhat.  A layer
-// then moves 10 bytes per element of its concatenated input (x 2, G 4 + 4) instead of the 22 of
+// by itself then moves 10 bytes per element of its concatenated input (x 2, G 4 + 4) instead of the 22 of
 // separate passes (gradient written 2; reduction 2 + 2; element-wise pass 2 + 2 + 4 + 4; the slab's
 // initial copy of dy, another 6 per element of the block's output, goes away too: the first layer
 // that touches the slab reads dy in its place).  Against the separate passes, on one stream where
@@ -33,10 +39,9 @@ struct Dgrad3Args {
   const u16* dy;                        // last layer: the slice of dy, row stride g_ld; else null
   const float* G; int64_t g_ld;         // slab at the slice's first channel
   const u16* x; int64_t x_ld;           // features at the slice's first channel
-  const float2* K;                      // K0, K1 of the layers above l+1 at the slice (null: none yet)
-  const float2* part1; int T1, C1;      // layer l+1's BN1 partials [T1][C1]
-  int c1;                               // ... and the slice's first channel among the C1
-  const float2* fold1;                  // layer l+1's folded BN1 at the slice
+  BwdSums S;                            // BN1 sums of layers above, not yet in K: they cover the slice
+  int c;                                // the slice's first channel
+  float2* K; int K_set;                 // K0, K1 of what came before (K_set: there was something)
   const float *mean, *istd;             // of the slice's features
   float inv_p;
   u16* gl;                              // out: g_l, [P][k] (not written for the last layer)
@@ -47,8 +52,6 @@ struct Dgrad3Args {
   u16* dz;                              // out [P][B]: masked gradient of BN2's output
   float2* part2; int T2;                // out [T2][B]: BN2's sums
   int H, Wd, tpi, tiles, gy;
-  // finalisation of layer l+1's BN1 by extra workgroups: parameter gradients, K0 / K1
-  float *dgamma, *dbeta; float2* Kall; const float2* fold1all; int Ckeep, first;
 };
 
 // Unsigned division of x < 2^31 by a fixed d <= 2^30: m = ceil(2^s / d) with s = 31 + ceil(log2 d), so that
@@ -113,6 +116,39 @@ __device__ __forceinline__ float4 sum_partials128(const float2* __restrict__ par
   return s;
 }
 
+// Extra workgroups of the 3x3 data gradient: 64 channels of S's BN1, their parameter gradients and, where a
+// layer further down will read them, K0 / K1.
+template <int NW>
+__device__ __forceinline__ void finish_bn1(const Dgrad3Args& A, int wg, float2* sh) {
+  const int i = wg * 64 + (threadIdx.x & 63), ic = min(i, A.S.width - 1), ch = A.S.base + ic;
+  float2 k = make_float2(0.f, 0.f);
+  if (A.K_set) k = A.K[ch];
+  for (int q = 0; q < A.S.n; ++q) {
+    const float2 s = sum_partials64<NW>(q ? A.S.part[1] : A.S.part[0], A.S.T, A.S.width, ic, sh);
+    const float sc = (q ? A.S.fold1[1] : A.S.fold1[0])[ch].x * A.inv_p;
+    k = make_float2(__fmaf_rn(sc, s.x, k.x), __fmaf_rn(sc, s.y, k.y));
+    if (threadIdx.x < 64 && i < A.S.width) {
+      (q ? A.S.dbeta[1] : A.S.dbeta[0])[ch] = s.x;
+      (q ? A.S.dgamma[1] : A.S.dgamma[0])[ch] = s.y;
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x < 64 && i < A.S.width && ch < A.c) A.K[ch] = k;
+}
+// K0, K1 of the slice's channel ic, with what S holds; valid in wave 0.  Call with all threads.
+template <int NW>
+__device__ __forceinline__ float2 slice_k(const Dgrad3Args& A, int ic, float2* sh) {
+  float2 k = make_float2(0.f, 0.f);
+  if (A.K_set) k = A.K[A.c + ic];
+  for (int q = 0; q < A.S.n; ++q) {
+    const float2 s = sum_partials64<NW>(q ? A.S.part[1] : A.S.part[0], A.S.T, A.S.width, A.c - A.S.base + ic, sh);
+    const float sc = (q ? A.S.fold1[1] : A.S.fold1[0])[A.c + ic].x * A.inv_p;
+    k = make_float2(__fmaf_rn(sc, s.x, k.x), __fmaf_rn(sc, s.y, k.y));
+    __syncthreads();
+  }
+  return k;
+}
+
 // Output channels (B of them) on M, pixels of one image on N.  A workgroup owns a tile of 64*NT
 // consecutive pixels and MT M-tiles; its four waves split the pixels (NT N-tiles each) and every wave
 // forms all MT M-tiles, so nothing is added across waves but the two sums at the end.  The slice
@@ -125,20 +161,7 @@ __global__ __launch_bounds__(256) void k_dgrad3(Dgrad3Args A) {
   __shared__ float2 sh[256];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 15, g = lane >> 4;
   const int nconv = A.T2 * A.gy;
-  if ((int)blockIdx.x >= nconv) {  // finalise 64 channels of layer l+1's BN1
-    const int ch = ((int)blockIdx.x - nconv) * 64 + lane, cc = min(ch, A.C1 - 1);
-    const float2 s = sum_partials64<4>(A.part1, A.T1, A.C1, cc, sh);
-    if (wave == 0 && ch < A.C1) {
-      A.dbeta[ch] = s.x;
-      A.dgamma[ch] = s.y;
-      if (ch < A.Ckeep) {
-        const float sc = A.fold1all[ch].x * A.inv_p;
-        const float2 o = A.first ? make_float2(0.f, 0.f) : A.Kall[ch];
-        A.Kall[ch] = make_float2(__fmaf_rn(sc, s.x, o.x), __fmaf_rn(sc, s.y, o.y));
-      }
-    }
-    return;
-  }
+  if ((int)blockIdx.x >= nconv) { finish_bn1<4>(A, (int)blockIdx.x - nconv, sh); return; }
   constexpr int PITCH = 64 + 8, TP = 64 * NT;
   const int HW = A.H * A.Wd, W = A.Wd, halo = W + 1, seg = TP + 2 * halo;
   const int pw = blockIdx.x / A.gy, m0 = (blockIdx.x % A.gy) * MT * 16;
@@ -146,12 +169,10 @@ __global__ __launch_bounds__(256) void k_dgrad3(Dgrad3Args A) {
   const int kc = BYPASS ? 64 : A.k;
   auto form_coef = [&](int c0, int at) {  // of channels c0..c0+63, to positions at..
     const int i = c0 + lane, ic = min(i, A.k - 1);
-    const float2 s = sum_partials64<4>(A.part1, A.T1, A.C1, A.c1 + ic, sh);
+    const float2 k = slice_k<4>(A, ic, sh);
     if (wave == 0 && i < A.k) {
-      const float sc = A.fold1[ic].x * A.inv_p;
-      const float2 o = A.K ? A.K[ic] : make_float2(0.f, 0.f);
-      coef[at + lane] = __fmaf_rn(sc, s.x, o.x);
-      coef[kc + at + lane] = __fmaf_rn(sc, s.y, o.y) * A.istd[ic];
+      coef[at + lane] = k.x;
+      coef[kc + at + lane] = k.y * A.istd[ic];
       coef[2 * kc + at + lane] = A.mean[ic];
     }
   };
@@ -330,20 +351,7 @@ __global__ __launch_bounds__(512) void k_dgrad3s(Dgrad3Args A, int T, DivBy dhw,
   constexpr int VS = KS == 2 ? 3 : 2, PITCH = 32 * KS + 8, RS = 512 >> VS;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), j = lane & 15, g = lane >> 4;
   const int nconv = (A.T2 + 7) / 8 * 8 * A.gy;
-  if ((int)blockIdx.x >= nconv) {  // finalise 64 channels of layer l+1's BN1
-    const int ch = ((int)blockIdx.x - nconv) * 64 + lane, cc = min(ch, A.C1 - 1);
-    const float2 s = sum_partials64<8>(A.part1, A.T1, A.C1, cc, sh);
-    if (wave == 0 && ch < A.C1) {
-      A.dbeta[ch] = s.x;
-      A.dgamma[ch] = s.y;
-      if (ch < A.Ckeep) {
-        const float sc = A.fold1all[ch].x * A.inv_p;
-        const float2 o = A.first ? make_float2(0.f, 0.f) : A.Kall[ch];
-        A.Kall[ch] = make_float2(__fmaf_rn(sc, s.x, o.x), __fmaf_rn(sc, s.y, o.y));
-      }
-    }
-    return;
-  }
+  if ((int)blockIdx.x >= nconv) { finish_bn1<8>(A, (int)blockIdx.x - nconv, sh); return; }
   const int slot = blockIdx.x >> 3, grp = slot % A.gy, pw = (slot / A.gy) * 8 + (blockIdx.x & 7);
   if (pw >= A.T2) return;
   const int W = A.Wd, HW = A.H * W, halo = W + 1, seg = 64 + 2 * halo, BUFE = (seg + 1) * PITCH, P = A.tiles;
@@ -408,12 +416,10 @@ __global__ __launch_bounds__(512) void k_dgrad3s(Dgrad3Args A, int T, DivBy dhw,
   }
   if (!A.dy) {
     const int ic = min(lane, A.k - 1);
-    const float2 s = sum_partials64<8>(A.part1, A.T1, A.C1, A.c1 + ic, sh);
+    const float2 k = slice_k<8>(A, ic, sh);
     if (wave == 0) {
-      const float sc = A.fold1[ic].x * A.inv_p;
-      const float2 o = A.K ? A.K[ic] : make_float2(0.f, 0.f);
-      coef[0][lane] = __fmaf_rn(sc, s.x, o.x);
-      coef[1][lane] = __fmaf_rn(sc, s.y, o.y) * A.istd[ic];
+      coef[0][lane] = k.x;
+      coef[1][lane] = k.y * A.istd[ic];
       coef[2][lane] = A.mean[ic];
     }
     __syncthreads();
@@ -574,30 +580,21 @@ struct Dgrad1Args {
   int ppw;                              // pixels per wave, a multiple of 32
 };
 
-// Output channels on M, pixels on N; bound by the slab's traffic (10 bytes per element against
-// 2*B flops).  A workgroup owns 32 channels (two M-tiles) whose weights stay in registers and a
-// range of pixels, of which each wave walks a quarter in steps of 32 (two N-tiles); a lane then
-// holds 4 consecutive channels of a pixel: the slab is read and written in 16-byte pieces, 128
-// contiguous bytes per pixel and wave.  Waves share nothing until the sums at the end.
-// KS = K-steps of 32 (0: more than eight, weights read in the loop).
-template <int KS, bool FIRST>
+// One layer with more than kDgrad1MaxB outputs (fewer: dgrad1_body of dnb_nhwc_wgrad.hip, which keeps the weights
+// in LDS).  Output channels on M, pixels on N.  A workgroup owns 32 channels (two M-tiles) and a range of pixels, of
+// which each wave walks a quarter in steps of 32 (two N-tiles); weights and gradients are read in the loop over K.
+template <bool FIRST>
 __global__ __launch_bounds__(256) void k_dgrad1(Dgrad1Args A) {
   __shared__ float red[4][32][2];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 15, g = lane >> 4;
   const int c0 = blockIdx.x * 32;
   const int64_t pw0 = ((int64_t)blockIdx.y * 4 + wave) * A.ppw;
   const int64_t pw1 = min(A.P, pw0 + A.ppw);
-  constexpr int KR = KS > 0 ? KS : 1;
   const int ksteps = A.B32 >> 5;
-  V8 w[2][KR];
   const u16* wr[2];
 #pragma unroll
   for (int a = 0; a < 2; ++a) {
     wr[a] = wfrag(A.W, A.B32, min(c0 + a * 16, A.C16 - 16) >> 4, 0);
-    if (KS > 0) {
-#pragma unroll
-      for (int s = 0; s < KR; ++s) w[a][s].q = *reinterpret_cast<const uint4*>(wr[a] + 512 * s);
-    }
   }
   float sc[2][4], sf[2][4], mu[2][4], s0[2][4], s1[2][4];
   int ch[2];
@@ -617,15 +614,9 @@ __global__ __launch_bounds__(256) void k_dgrad1(Dgrad1Args A) {
     int64_t p[2];
     uint2 xr[2][2], dr[2][2];
     float4 gr[2][2];
-    V8 d[2][KR];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       p[t] = min(pb + t * 16 + j, pw1 - 1);  // clamped: masked below
-      if (KS > 0) {
-#pragma unroll
-        for (int s = 0; s < KR; ++s)
-          d[t][s].q = *reinterpret_cast<const uint4*>(A.db + p[t] * A.B + min(32 * s + 8 * g, A.B - 8));
-      }
     }
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -640,26 +631,17 @@ __global__ __launch_bounds__(256) void k_dgrad1(Dgrad1Args A) {
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int a = 0; a < 2; ++a) acc[t][a] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    if (KS > 0) {
+    for (int s = 0; s < ksteps; ++s) {
+      V8 ww[2], dd[2];
 #pragma unroll
-      for (int s = 0; s < KR; ++s)
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int a = 0; a < 2; ++a) acc[t][a] = mfma_bf16(w[a][s], d[t][s], acc[t][a]);
-    } else {
-      for (int s = 0; s < ksteps; ++s) {
-        V8 ww[2], dd[2];
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-          ww[a].q = *reinterpret_cast<const uint4*>(wr[a] + 512 * s);
-          dd[a].q = *reinterpret_cast<const uint4*>(A.db + p[a] * A.B + min(32 * s + 8 * g, A.B - 8));
-        }
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int a = 0; a < 2; ++a) acc[t][a] = mfma_bf16(ww[a], dd[t], acc[t][a]);
+      for (int a = 0; a < 2; ++a) {
+        ww[a].q = *reinterpret_cast<const uint4*>(wr[a] + 512 * s);
+        dd[a].q = *reinterpret_cast<const uint4*>(A.db + p[a] * A.B + min(32 * s + 8 * g, A.B - 8));
       }
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int a = 0; a < 2; ++a) acc[t][a] = mfma_bf16(ww[a], dd[t], acc[t][a]);
     }
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -704,34 +686,39 @@ __global__ __launch_bounds__(256) void k_dgrad1(Dgrad1Args A) {
 
 // ---------------------------------------------------------------- gradient of the block input
 
-// dx0 = bf16(G - K0 - K1*xhat) on the block input's channels, with the first layer's BN1 finalised
-// on the way (its input is exactly these channels).  grid (groups of 256 channels, pixel ranges).
+// dx0 = bf16(G - K0 - K1*xhat) on the block input's channels, with the last BN1 sums (which cover exactly these
+// channels) finished on the way.  grid (groups of 256 channels, pixel ranges).
 __global__ __launch_bounds__(256) void k_dx0(const float* __restrict__ G, int64_t g_ld, const u16* __restrict__ x,
                                              int64_t x_ld, u16* __restrict__ dx0, int64_t P, int C, int ppb, float inv_p,
-                                             const float2* __restrict__ K, const float2* __restrict__ part, int T,
-                                             const float2* __restrict__ fold1, const float* __restrict__ mean,
-                                             const float* __restrict__ istd, float* __restrict__ dgamma,
-                                             float* __restrict__ dbeta) {
+                                             const float2* __restrict__ K, BwdSums S, const float* __restrict__ mean,
+                                             const float* __restrict__ istd) {
   __shared__ float co[3][256];
   const int cb = blockIdx.x * 256;
   {
     const int ch = cb + threadIdx.x, cc = min(ch, C - 1);
-    float2 s = make_float2(0.f, 0.f);
-    int t = 0;
-    for (; t + 8 <= T; t += 8) {
-      float2 v[8];
+    float2 k = K ? K[cc] : make_float2(0.f, 0.f);
+    for (int q = 0; q < S.n; ++q) {
+      const float2* part = q ? S.part[1] : S.part[0];
+      float2 s = make_float2(0.f, 0.f);
+      int t = 0;
+      for (; t + 8 <= S.T; t += 8) {
+        float2 v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(t + u) * C + cc];
+        for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(t + u) * C + cc];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) { s.x += v[u].x; s.y += v[u].y; }
+        for (int u = 0; u < 8; ++u) { s.x += v[u].x; s.y += v[u].y; }
+      }
+      for (; t < S.T; ++t) { const float2 v = part[(int64_t)t * C + cc]; s.x += v.x; s.y += v.y; }
+      const float sc = (q ? S.fold1[1] : S.fold1[0])[cc].x * inv_p;
+      k = make_float2(__fmaf_rn(sc, s.x, k.x), __fmaf_rn(sc, s.y, k.y));
+      if (blockIdx.y == 0 && ch < C) {
+        (q ? S.dbeta[1] : S.dbeta[0])[ch] = s.x;
+        (q ? S.dgamma[1] : S.dgamma[0])[ch] = s.y;
+      }
     }
-    for (; t < T; ++t) { const float2 v = part[(int64_t)t * C + cc]; s.x += v.x; s.y += v.y; }
-    const float sc = fold1[cc].x * inv_p;
-    const float2 o = K ? K[cc] : make_float2(0.f, 0.f);
-    co[0][threadIdx.x] = __fmaf_rn(sc, s.x, o.x);
-    co[1][threadIdx.x] = __fmaf_rn(sc, s.y, o.y) * istd[cc];
+    co[0][threadIdx.x] = k.x;
+    co[1][threadIdx.x] = k.y * istd[cc];
     co[2][threadIdx.x] = mean[cc];
-    if (blockIdx.y == 0 && ch < C) { dbeta[ch] = s.x; dgamma[ch] = s.y; }
   }
   __syncthreads();
   const int cvl = threadIdx.x & 31, pr = threadIdx.x >> 5, ch0 = cb + cvl * 8;
@@ -816,26 +803,25 @@ Dgrad3Plan plan_dgrad3(int n, int h, int w, int k, int B) {
 
 }  // namespace
 
-// Partials of k_dgrad1: workgroups along the pixels, so that about 1024 workgroups (four per CU)
-// cover the slab; each wave takes at least one step of 32 pixels.
-static int dgrad1_splits(int64_t P, int C, int* ppw) {
-  const int64_t cols = (C + 31) / 32;
-  int64_t t = 1024 / cols;
-  if (t > 256) t = 256;
-  if (t > (P + 127) / 128) t = (P + 127) / 128;
-  if (t < 1) t = 1;
-  const int64_t px = ((P + 4 * t - 1) / (4 * t) + 31) / 32 * 32;
-  *ppw = (int)px;
-  return (int)((P + 4 * px - 1) / (4 * px));
-}
+// Splits of the upper layer's share of the lower one's slice: its partials are added by every workgroup of the
+// next launch, and it runs beside the weight gradients.
+constexpr int kNearSplits = 64;
+constexpr int kFarSplits = 256;
 
-size_t bwd_partial1_floats(int64_t P, int C) {
+size_t bwd_partial1_near(int64_t P, int C, int B) {
   int ppw;
-  return (size_t)2 * C * dgrad1_splits(P, C, &ppw);
+  return (size_t)(B <= kDgrad1MaxB ? 4 : 2) * C * dgrad1_splits(P, C, kFarSplits, &ppw);
+}
+size_t bwd_partial1_floats(int64_t P, int C, int k, int B) {
+  int ppw;
+  return bwd_partial1_near(P, C, B) + (B <= kDgrad1MaxB ? (size_t)2 * k * dgrad1_splits(P, k, kNearSplits, &ppw) : 0);
 }
 size_t bwd_partial2_floats(int n, int h, int w, int k, int B) {
   return (size_t)2 * B * (plan_dgrad3(n, h, w, k, B).T2 + 1);
 }
+
+int bwd_near_splits() { return kNearSplits; }
+int bwd_far_splits() { return kFarSplits; }
 
 hipError_t bwd_dgrad3(const BwdLayer& L, hipStream_t st) {
   const Dgrad3Plan p = plan_dgrad3(L.n, L.h, L.w, L.k, L.B);
@@ -854,18 +840,10 @@ hipError_t bwd_dgrad3(const BwdLayer& L, hipStream_t st) {
   A.dz = (u16*)L.db;
   A.part2 = (float2*)L.part2; A.T2 = p.T2;
   A.H = L.h; A.Wd = L.w; A.tpi = p.tpi; A.tiles = p.tiles; A.gy = p.gy;
-  int fin = 0;
-  if (!L.last) {  // the layer above: C1 = c + k input channels
-    int ppw;
-    A.C1 = L.c + L.k; A.c1 = L.c;
-    A.T1 = dgrad1_splits(P, A.C1, &ppw);
-    A.part1 = (const float2*)L.part1;
-    A.K = L.above_first ? nullptr : L.K + L.c;
-    A.Kall = L.K; A.first = L.above_first; A.Ckeep = L.c;
-    A.fold1all = L.above_fold1; A.fold1 = L.above_fold1 + L.c;
-    A.dgamma = L.above_dgamma; A.dbeta = L.above_dbeta;
-    fin = (A.C1 + 63) / 64;
-  }
+  A.S = L.above;
+  A.c = L.c;
+  A.K = L.K; A.K_set = L.K_set;
+  const int fin = L.above.n ? (L.above.width + 63) / 64 : 0;
   const dim3 grid((unsigned)(p.T2 * p.gy + fin));
   if (p.ks) {
     auto by = [](unsigned d) {
@@ -919,7 +897,7 @@ hipError_t bwd_dgrad3(const BwdLayer& L, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t bwd_dgrad1(const BwdLayer& L, hipStream_t st) {
+hipError_t bwd_dgrad1(const BwdLayer& L, float2* part, int* Tp, hipStream_t st) {
   const int64_t P = (int64_t)L.n * L.h * L.w;
   Dgrad1Args A{};
   A.db = (const u16*)L.db; A.B = L.B;
@@ -927,38 +905,22 @@ hipError_t bwd_dgrad1(const BwdLayer& L, hipStream_t st) {
   A.x = (const u16*)L.x; A.x_ld = L.x_ld;
   A.dy = (const u16*)L.dy; A.G = L.G; A.g_ld = L.ld;
   A.fold1 = L.fold1; A.mean = L.mean_y; A.istd = L.istd_y;
-  A.part1 = (float2*)L.part1; A.C = L.c; A.P = P;
-  const int T = dgrad1_splits(P, L.c, &A.ppw);
+  A.part1 = part; A.C = L.c; A.P = P;
+  const int T = dgrad1_splits(P, L.c, kFarSplits, &A.ppw);
+  *Tp = T;
   const dim3 grid((unsigned)((L.c + 31) / 32), (unsigned)T);
-#define DNB_D1(KS)                                                                          \
-  do {                                                                                      \
-    if (L.last) hipLaunchKernelGGL((k_dgrad1<KS, true>), grid, dim3(256), 0, st, A);        \
-    else hipLaunchKernelGGL((k_dgrad1<KS, false>), grid, dim3(256), 0, st, A);              \
-  } while (0)
-  switch (A.B32 >> 5) {
-    case 1: DNB_D1(1); break;
-    case 2: DNB_D1(2); break;
-    case 3: DNB_D1(3); break;
-    case 4: DNB_D1(4); break;
-    case 5: DNB_D1(5); break;
-    case 6: DNB_D1(6); break;
-    case 7: DNB_D1(7); break;
-    case 8: DNB_D1(8); break;
-    default: DNB_D1(0); break;
-  }
-#undef DNB_D1
+  if (L.last) hipLaunchKernelGGL(k_dgrad1<true>, grid, dim3(256), 0, st, A);
+  else hipLaunchKernelGGL(k_dgrad1<false>, grid, dim3(256), 0, st, A);
   return hipGetLastError();
 }
 
 hipError_t bwd_dx0(const BwdLayer& L, void* dx0, hipStream_t st) {
   const int64_t P = (int64_t)L.n * L.h * L.w;
-  int ppw;
-  const int T = dgrad1_splits(P, L.c, &ppw);
   int64_t ppb = 64;
   while ((P + ppb - 1) / ppb * ((L.c + 255) / 256) > 2048) ppb *= 2;
   hipLaunchKernelGGL(k_dx0, dim3((unsigned)((L.c + 255) / 256), (unsigned)((P + ppb - 1) / ppb)), dim3(256), 0, st, L.G, L.ld,
-                     (const u16*)L.y, L.ld, (u16*)dx0, P, L.c, (int)ppb, 1.0f / (float)P, L.last ? nullptr : L.K,
-                     (const float2*)L.part1, T, L.fold1, L.mean_y, L.istd_y, L.dgamma1, L.dbeta1);
+                     (const u16*)L.y, L.ld, (u16*)dx0, P, L.c, (int)ppb, 1.0f / (float)P, L.K_set ? L.K : nullptr, L.above,
+                     L.mean_y, L.istd_y);
   return hipGetLastError();
 }
 

@@ -362,17 +362,189 @@ __device__ __forceinline__ void sum_body(const SumArgs& s, int wg, float4* red) 
     if (m + r < s.cout) s.out[((int64_t)(m + r) * s.cin + c) * s.taps + t9] = o4[r];
 }
 
+// ---------------------------------------------------------------- 1x1 data gradient + BN1 backward
+
+// du_c = W_c . db (over the B outputs), masked by BN1's ReLU, scaled and added into the slab, with BN1's sums
+// of dz and dz*(x - mean): see dnb_nhwc_bwd.hip.  Bound by the slab's traffic: 10 bytes per element (x 2, G 4 + 4)
+// against 2*B flops, so two layers that both read a channel are done in one pass (the upper one's share of the
+// lower one's own slice goes first, beside the upper one's weight gradients, and only that delays the chain):
+// 6 bytes per element and layer, and no launch of its own.
+struct D1Args {
+  int nl, n, cols, T, nk;         // layers; workgroups (cols x T); K-steps of 32 outputs
+  const u16* db[2]; const u16* W[2];
+  int mtiles[2];
+  const float2* fold[2];
+  float2* part[2];
+  const u16* x; int64_t x_ld;
+  const u16* dy; float* G; int64_t ld;
+  int first;
+  const float *mean, *istd;
+  int B, cb, ce;
+  int P, ppw;                     // pixels per wave, a multiple of 32
+};
+
+// Output channels on M, pixels on N.  A workgroup owns 32 channels (two M-tiles, weights and coefficients of
+// both layers in LDS) and a range of pixels, of which each wave walks a quarter in steps of 32 (two N-tiles); a
+// lane then holds 4 consecutive channels of a pixel: the slab is read and written in 16-byte pieces, 128
+// contiguous bytes per pixel and wave.  Waves share nothing until the sums at the end.
+template <int KS>
+__device__ __forceinline__ void dgrad1_body(const D1Args& A, int id, u16* lds) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 15, g = lane >> 4;
+  const int col = id % A.cols, ty = id / A.cols, c00 = (A.cb & ~15) + col * 32;
+  float* cf = reinterpret_cast<float*>(lds + A.nl * 2 * A.nk * 512);  // [nl][32][2]
+  for (int i = tid; i < A.nl * 2 * A.nk * 64; i += 256) {
+    const int f = i >> 6, s = f % A.nk, a = (f / A.nk) & 1, li = f / (2 * A.nk);
+    const int mt = min((c00 >> 4) + a, (li ? A.mtiles[1] : A.mtiles[0]) - 1);
+    *reinterpret_cast<uint4*>(lds + i * 8) =
+        *reinterpret_cast<const uint4*>((li ? A.W[1] : A.W[0]) + ((int64_t)mt * A.nk + s) * 512 + (i & 63) * 8);
+  }
+  if (tid < 32 * A.nl) {
+    const float2 f = (tid < 32 ? A.fold[0] : A.fold[1])[min(c00 + (tid & 31), A.ce - 1)];
+    cf[2 * tid] = f.x; cf[2 * tid + 1] = f.y;
+  }
+  float mu[2][4], s0[2][2][4], s1[2][2][4];
+  int ch[2];
+  bool cok[2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    const int c = c00 + a * 16 + 4 * g;  // cb, ce % 8 == 0: a lane's four channels are in or out together
+    cok[a] = c >= A.cb && c < A.ce;
+    ch[a] = min(c, A.ce - 4);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      mu[a][r] = A.mean[ch[a] + r];
+#pragma unroll
+      for (int li = 0; li < 2; ++li) s0[li][a][r] = s1[li][a][r] = 0.f;
+    }
+  }
+  __syncthreads();
+  const int pw0 = (ty * 4 + wave) * A.ppw, pw1 = min(A.P, pw0 + A.ppw);
+  for (int pb = pw0; pb < pw1; pb += 32) {
+    int p[2];
+    uint2 xr[2][2];
+    float gv[2][2][4];
+    V8 d[2][KS];
+    auto dload = [&](const u16* db, int s0) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+          d[t][s].q = *reinterpret_cast<const uint4*>(db + (int64_t)p[t] * A.B + min(32 * (s0 + s) + 8 * g, A.B - 8));
+    };
+#pragma unroll
+    for (int t = 0; t < 2; ++t) p[t] = min(pb + t * 16 + j, pw1 - 1);  // clamped: masked below
+    dload(A.db[0], 0);
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int a = 0; a < 2; ++a) xr[t][a] = *reinterpret_cast<const uint2*>(A.x + (int64_t)p[t] * A.x_ld + ch[a]);
+    if (A.first) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          const uint2 v = *reinterpret_cast<const uint2*>(A.dy + (int64_t)p[t] * A.ld + ch[a]);
+          gv[t][a][0] = bf2f((u16)v.x); gv[t][a][1] = bf2f((u16)(v.x >> 16));
+          gv[t][a][2] = bf2f((u16)v.y); gv[t][a][3] = bf2f((u16)(v.y >> 16));
+        }
+    } else {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          const float4 v = *reinterpret_cast<const float4*>(A.G + (int64_t)p[t] * A.ld + ch[a]);
+          gv[t][a][0] = v.x; gv[t][a][1] = v.y; gv[t][a][2] = v.z; gv[t][a][3] = v.w;
+        }
+    }
+#pragma unroll
+    for (int li = 0; li < 2; ++li) {
+      if (li < A.nl) {
+        f32x4 acc[2][2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int a = 0; a < 2; ++a) acc[t][a] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int sb = 0; sb < A.nk; sb += KS) {
+          if (li > 0 || sb > 0) dload(A.db[li], sb);
+#pragma unroll
+          for (int s = 0; s < KS; ++s) {
+            if (sb + s < A.nk) {
+              V8 w[2];
+#pragma unroll
+              for (int a = 0; a < 2; ++a) w[a].q = *reinterpret_cast<const uint4*>(lds + ((li * 2 + a) * A.nk + sb + s) * 512 + lane * 8);
+#pragma unroll
+              for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int a = 0; a < 2; ++a) acc[t][a] = mfma_bf16(w[a], d[t][s], acc[t][a]);
+            }
+          }
+        }
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          const float4* fp = reinterpret_cast<const float4*>(cf + (li * 32 + a * 16 + 4 * g) * 2);
+          const float4 f0 = fp[0], f1 = fp[1];
+          const float sc[4] = {f0.x, f0.z, f1.x, f1.z}, sf[4] = {f0.y, f0.w, f1.y, f1.w};
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            const bool ok = pb + t * 16 + j < pw1 && cok[a];
+            const float xf[4] = {bf2f((u16)xr[t][a].x), bf2f((u16)(xr[t][a].x >> 16)), bf2f((u16)xr[t][a].y),
+                                 bf2f((u16)(xr[t][a].y >> 16))};
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const float dz = ok && __fmaf_rn(xf[r], sc[r], sf[r]) > 0.f ? acc[t][a][r] : 0.f;
+              gv[t][a][r] = __fmaf_rn(sc[r], dz, gv[t][a][r]);
+              s0[li][a][r] += dz;
+              s1[li][a][r] = __fmaf_rn(dz, xf[r] - mu[a][r], s1[li][a][r]);
+            }
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+        if (pb + t * 16 + j < pw1 && cok[a])
+          *reinterpret_cast<float4*>(A.G + (int64_t)p[t] * A.ld + ch[a]) = make_float4(gv[t][a][0], gv[t][a][1], gv[t][a][2], gv[t][a][3]);
+  }
+  __syncthreads();  // the weights are read
+  float* red = reinterpret_cast<float*>(lds);  // [2][4][32][2]
+#pragma unroll
+  for (int li = 0; li < 2; ++li)
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float u = row16_sum(s0[li][a][r]), v = row16_sum(s1[li][a][r]);
+        if (j == 0) {
+          float* o = red + ((li * 4 + wave) * 32 + a * 16 + 4 * g + r) * 2;
+          o[0] = u; o[1] = v;
+        }
+      }
+  __syncthreads();
+  const int li = tid >> 5, c = c00 + (tid & 31);
+  if (li < A.nl && c >= A.cb && c < A.ce) {
+    float u = 0.f, v = 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) { u += red[((li * 4 + q) * 32 + (tid & 31)) * 2]; v += red[((li * 4 + q) * 32 + (tid & 31)) * 2 + 1]; }
+    (li ? A.part[1] : A.part[0])[(int64_t)ty * (A.ce - A.cb) + c - A.cb] = make_float2(u, v * A.istd[c]);
+  }
+}
+
 // ---------------------------------------------------------------- kernels
 
-// A layer's two weight gradients and the pending sums of the layer before it.  The 3x3's workgroups
-// first: they are the fewer and the longer ones.
+// A layer's two weight gradients, the pending sums of the layer before it and a data gradient (which reads the
+// gradient of b_l as the 1x1's does and writes only the slab and its sums).  The 3x3's workgroups first: they are
+// the fewer and the longer ones.
 // (Waves per SIMD asked for: left alone the allocator takes 200 registers where 168 hold the code.)
 template <int MG, int MT, bool PRO>
-__global__ __launch_bounds__(256, (MT == 3 ? 2 : 3)) void k_wgrad_pair(Wg1Args A1, Wg3Args A3, SumArgs s1, SumArgs s3) {
+__global__ __launch_bounds__(256, (MT == 3 ? 2 : 3)) void k_wgrad_pair(Wg1Args A1, Wg3Args A3, SumArgs s1, SumArgs s3, D1Args D) {
   extern __shared__ __attribute__((aligned(16))) u16 lds[];
   int id = blockIdx.x;
   if (id < A3.n) { wgrad3_body<MT, PRO, u16>(A3, id, lds); return; }
   id -= A3.n;
+  if (id < D.n) { dgrad1_body<MG / 2>(D, id, lds); return; }
+  id -= D.n;
   if (id < A1.n) { wgrad1_body<MG, PRO, u16>(A1, id, lds); return; }
   id -= A1.n;
   if (id < s1.wgs) { sum_body(s1, id, reinterpret_cast<float4*>(lds)); return; }
@@ -402,8 +574,9 @@ __global__ __launch_bounds__(256) void k_wgrad_sums(SumArgs s1, SumArgs s3) {
 // Workgroups of the 1x1 and of the 3x3.  A split costs a partial of the whole weight tensor: the
 // lower bounds fill the chip, the upper ones apply where a split still has eight tiles (large images,
 // small partials).  Not sharp: lower bounds of 192..512 and 64..256, upper ones of 512..1024 and
-// 256..768 moved the DenseNet-264-shaped step between 16.03 and 16.35 ms.
-constexpr int WG1_MIN = 256, WG1_MAX = 1024, WG3_MIN = 128, WG3_MAX = 256, LONG_TILES = 8;
+// 256..768 moved the DenseNet-264-shaped step between 16.03 and 16.35 ms; 512 instead of 1024 for the 1x1 takes 27..50 MB
+// of partials from the workspace of the ImageNet-shaped networks.
+constexpr int WG1_MIN = 256, WG1_MAX = 512, WG3_MIN = 128, WG3_MAX = 256, LONG_TILES = 8;
 
 int splits_for(int tiles, int cols, int lo, int hi) {
   int s = lo / cols, s2 = hi / cols;
@@ -528,7 +701,20 @@ bool wgrad_fast(const WgradIn& in, bool g_f32, int n, int h, int w, int taps, Wg
   return true;
 }
 
-bool wgrad_pair(const WgradIn& w1, const WgradIn& w3, int n, int h, int w, WgradSum* s1, WgradSum* s3, hipStream_t st) {
+// About 1024 workgroups over the slab, at most `most` splits; each wave takes at least one step of 32 pixels.
+int dgrad1_splits(int64_t P, int C, int most, int* ppw) {
+  const int64_t cols = (C + 31) / 32;
+  int64_t t = 1024 / cols;
+  if (t > most) t = most;
+  if (t > (P + 127) / 128) t = (P + 127) / 128;
+  if (t < 1) t = 1;
+  const int64_t px = ((P + 4 * t - 1) / (4 * t) + 31) / 32 * 32;
+  *ppw = (int)px;
+  return (int)((P + 4 * px - 1) / (4 * px));
+}
+
+bool wgrad_pair(const WgradIn& w1, const WgradIn& w3, int n, int h, int w, WgradSum* s1, WgradSum* s3, const Dgrad1In& d1,
+                int most_splits, int* T1, hipStream_t st) {
   if (!fits(n, h, w)) return false;
   const int P = n * h * w;
   const Plan1 p1 = plan1(P, w1.cin, w1.cout);
@@ -537,12 +723,30 @@ bool wgrad_pair(const WgradIn& w1, const WgradIn& w3, int n, int h, int w, Wgrad
   const Wg1Args A1 = args1(p1, w1, P);
   const Wg3Args A3 = args3(p3, w3, P, h, w);
   const SumArgs a1 = sum_args(s1), a3 = sum_args(s3);
-  const dim3 grid((unsigned)(A1.n + A3.n + a1.wgs + a3.wgs));
-  const size_t lds = p1.lds > p3.lds ? p1.lds : p3.lds;
+  size_t lds = p1.lds > p3.lds ? p1.lds : p3.lds;
+  D1Args D{};
+  if (d1.nl) {
+    if (d1.B > kDgrad1MaxB) return false;
+    D.nl = d1.nl;
+    D.nk = (d1.B + 31) / 32;
+    D.cols = (d1.ce - (d1.cb & ~15) + 31) / 32;
+    D.T = dgrad1_splits(P, d1.ce - d1.cb, most_splits, &D.ppw);
+    D.n = D.cols * D.T;
+    for (int i = 0; i < 2; ++i) {
+      D.db[i] = (const u16*)d1.db[i]; D.W[i] = (const u16*)d1.W[i]; D.mtiles[i] = d1.C16[i] / 16;
+      D.fold[i] = d1.fold1[i]; D.part[i] = d1.part[i];
+    }
+    D.x = (const u16*)d1.x; D.x_ld = d1.x_ld; D.dy = (const u16*)d1.dy; D.G = d1.G; D.ld = d1.ld; D.first = d1.first;
+    D.mean = d1.mean; D.istd = d1.istd; D.B = d1.B; D.cb = d1.cb; D.ce = d1.ce; D.P = P;
+    *T1 = D.T;
+    const size_t need = (size_t)D.nl * 2 * D.nk * 1024 + (size_t)D.nl * 256;  // (the sums' 2 KB reuse it)
+    if (need > lds) lds = need;
+  }
+  const dim3 grid((unsigned)(A1.n + A3.n + D.n + a1.wgs + a3.wgs));
 #define DNB_L(MG, MT)                                                                                               \
   do {                                                                                                              \
-    if (w1.fold) hipLaunchKernelGGL((k_wgrad_pair<MG, MT, true>), grid, dim3(256), lds, st, A1, A3, a1, a3);         \
-    else hipLaunchKernelGGL((k_wgrad_pair<MG, MT, false>), grid, dim3(256), lds, st, A1, A3, a1, a3);                \
+    if (w1.fold) hipLaunchKernelGGL((k_wgrad_pair<MG, MT, true>), grid, dim3(256), lds, st, A1, A3, a1, a3, D);         \
+    else hipLaunchKernelGGL((k_wgrad_pair<MG, MT, false>), grid, dim3(256), lds, st, A1, A3, a1, a3, D);                \
   } while (0)
 #define DNB_L2(MG)                                                                                                  \
   switch (p3.mt) { case 1: DNB_L(MG, 1); break; case 2: DNB_L(MG, 2); break; default: DNB_L(MG, 3); break; }
