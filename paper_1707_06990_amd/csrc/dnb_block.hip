@@ -23,7 +23,7 @@ struct dnb_block {
   std::vector<size_t> off_stat_b;            // per layer mean[B], istd[B]
   std::vector<size_t> off_fold1, off_fold2;  // fused schedule: per layer folded (scale, shift) of BN1 / BN2
   size_t off_part;                           // reduction partials of the main chain (BN)
-  size_t off_K, off_db2, part1_floats, near_floats;                // backward: K0, K1 per channel; a second db (bf16, pairs of layers); where BN2's
+  size_t off_K, off_db2, part1_floats, near_floats;                // backward: K0, K1 per channel; a second db (pairs of layers); where BN2's
                                              // partials, a slice's own BN1 sums start in off_part
   size_t off_partA[2], off_partB[2];         // partials of the 3x3 / 1x1 weight gradients, layer l's in [l & 1]
   // with concurrency on, the fp32 backward with separate BN passes runs three chains: the data-gradient
@@ -357,11 +357,13 @@ int backward_f32(dnb_block* b, const float* params, const float* y, const float*
   L.y = y; L.dy = dy; L.ys = ys;
   L.G = (float*)(ws + b->off_G);
   L.gl = (float*)(ws + b->off_dS2);  // the gradient of storage 2 is consumed where it is formed: its storage holds g_l
-  L.db = (float*)(ws + b->off_dS3);
   L.mean_y = mean_y; L.istd_y = istd_y;
   L.part1 = (float2*)(ws + b->off_part);
   L.part2 = (float2*)((float*)(ws + b->off_part) + b->part1_floats);
   L.K = (float2*)(ws + b->off_K);
+  // Where the slab is large, layers go in pairs (upper, lower) that share the pass over it: see dnb_bwd_f32.hip.
+  float* const dbs[2] = {(float*)(ws + b->off_dS3), (float*)(ws + b->off_db2)};
+  bool lower = false;  // this layer is the lower one of a pair
   PendingSum pendA, pendB;
   for (int l = m; l >= 1; --l) {
     const int c = c_in(d, l);
@@ -373,8 +375,17 @@ int backward_f32(dnb_block* b, const float* params, const float* y, const float*
     const float* bl = (const float*)(ws + b->off_b[l]);
     float* mean_b = (float*)(ws + b->off_stat_b[l]);
     const size_t c16 = (size_t)((c + 15) & ~15);
+    const bool upper = !lower && l > 1 && bwd32_pair_ok(n, hw, c - k, B);
     L.c = c;
     L.last = l == m;
+    L.lo = upper ? c - k : 0; L.cw = c;
+    L.first = l == m || (lower && l + 1 == m);
+    if (lower) {
+      L.up_db = L.db; L.up_pk1t = L.pk1t; L.up_g1 = L.g1; L.up_b1 = L.b1; L.up_dgamma1 = L.dgamma1; L.up_dbeta1 = L.dbeta1;
+    } else {
+      L.up_db = nullptr;
+    }
+    L.db = dbs[upper ? 1 : 0];
     L.b = bl;
     L.x = fused ? y : S1; L.x_stride = fused ? ys : (int64_t)c * hw;
     L.pk1t = pack + b->pk[l] + B16 * c16;
@@ -403,6 +414,7 @@ int backward_f32(dnb_block* b, const float* params, const float* y, const float*
                                    (float*)(ws + b->off_partA[l & 1]),
                                    fused ? (const float2*)(ws + b->off_fold2[l]) : nullptr, n, B, d.h, d.w, st, &pendB, &pendA, nullptr,
                                    nullptr, nullptr, nullptr, nullptr, &fin));
+    lower = upper;
   }
   DNB_TRY(launch_pending_sum(&pendA, st));
   DNB_TRY(launch_pending_sum(&pendB, st));
@@ -665,7 +677,7 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
     }
     need(conv_stats_partial_floats(d.n, k, d.h, d.w));
     if (B > 0 && bwd32_ok(d.n, d.h, d.w, k, B)) {
-      size_t p1 = 0;
+      size_t p1 = bwd32_partial1_near_floats(d.n, (int)hw, k);
       for (int l = 1; l <= m; ++l) {
         const size_t f1 = bwd32_partial1_floats(d.n, (int)hw, c_in(d, l));
         if (f1 > p1) p1 = f1;
@@ -719,7 +731,9 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
     b->off_partA[i] = B > 0 || i == 0 ? carve_scratch(partA, true) : b->off_partA[0];
   }
   b->off_K = carve_scratch(B > 0 ? (size_t)cout * 2 : 0, true);
-  b->off_db2 = carve_scratch(bf16 && m > 1 && B <= nhwc::kDgrad1MaxB ? ((size_t)B * Ps + 3) / 4 : 0, true);
+  const bool second_db = bf16 ? m > 1 && B <= nhwc::kDgrad1MaxB
+                              : B > 0 && m > 1 && bwd32_ok(d.n, d.h, d.w, k, B) && bwd32_pair_ok(d.n, (int)hw, c_in(d, m - 1), B);
+  b->off_db2 = carve_scratch(second_db ? ((size_t)B * Ps + 3) / 4 : 0, true);
   mem.scratch_bytes = (uint64_t)scratch;
   // measured on MI355X: with the weight gradients on helper streams the fp32 step is slower (idle
   // time between dependent launches of different streams outweighs the overlap)

@@ -2,8 +2,11 @@
 //
 //   k_dgrad3_v4 / _v3         (dnb_conv_f32_fast.hip) 3x3 data gradient, BN2's mask and sums
 //   k_bn_bwd_apply            gradient of b_l, element-wise on P x B
-//   k_dgrad1                  1x1 data gradient; BN1+ReLU backward and the concatenation's backward
-//                             (accumulate into the slab G) in the epilogue, with BN1's two sums
+//   k_dgrad1 / s / p          1x1 data gradient; BN1+ReLU backward and the concatenation's backward
+//                             (accumulate into the slab G) in the epilogue, with BN1's two sums.  Where the slab
+//                             is large, layers go in pairs: layer l-1 needs of layer l only its own slice, so
+//                             after layer l's b_l gradient only those k channels are formed, and after layer
+//                             l-1's the channels below, of both layers, in one pass (k_dgrad1p)
 //   k_wgrad_pair              both weight gradients, the end of this BN1 (bn1_finish_body) and the sums of
 //                             the previous layer's weight-gradient partials
 //
@@ -31,8 +34,14 @@ struct Dgrad1Args {
   const float* x; int64_t x_stride;           // concatenated features
   const float* dy; float* G; int64_t g_stride;  // slab; dy replaces its first read (FIRST)
   const float *gamma, *beta, *mean, *istd;
-  float2* part1; int C, T;                    // out [C][T]
+  float2* part1; int lo, C, T;                // channels lo..C-1; out [C - lo][T]
   int hw, tpi, tiles, nwm;
+};
+// The lower layer of a pair (k_dgrad1p); Dgrad1Args holds the upper one.
+struct Dgrad1Lower {
+  const float *db, *W; int C16;
+  const float *gamma, *beta;
+  float2* part1;
 };
 
 // Output channels on M, pixels on N; bound by the slab's traffic (12 bytes per element against 2*B
@@ -46,7 +55,7 @@ template <int NCH, bool FIRST>
 __global__ __launch_bounds__(256, 2) void k_dgrad1(Dgrad1Args A) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = lane & 15, g = lane >> 4;
   const int wm = wave % A.nwm, wp = wave / A.nwm, nwp = 4 / A.nwm;
-  const int m0 = ((int)blockIdx.y * A.nwm + wm) * 32, t0 = (int)blockIdx.x * nwp + wp;
+  const int m0 = (A.lo & ~15) + ((int)blockIdx.y * A.nwm + wm) * 32, t0 = (int)blockIdx.x * nwp + wp;
   if (m0 >= A.C || t0 >= A.T) return;
   const int HW = A.hw, nch = A.B16 >> 4;
   const int mt[2] = {m0 >> 4, min((m0 >> 4) + 1, (A.C16 >> 4) - 1)};
@@ -143,7 +152,7 @@ __global__ __launch_bounds__(256, 2) void k_dgrad1(Dgrad1Args A) {
             s0[a][r] += dz;
             s1[a][r] = __fmaf_rn(dz, xv - mu[a][r], s1[a][r]);
           }
-          if (m0 + a * 16 + 4 * g + r < A.C)
+          if (m0 + a * 16 + 4 * g + r < A.C && m0 + a * 16 + 4 * g + r >= A.lo)
             *reinterpret_cast<float4*>(op + (int64_t)ch(a, r) * HW) = make_float4(o[0], o[1], o[2], o[3]);
         }
     }
@@ -154,7 +163,7 @@ __global__ __launch_bounds__(256, 2) void k_dgrad1(Dgrad1Args A) {
     for (int r = 0; r < 4; ++r) {
       const float u = row16_sum(s0[a][r]), v = row16_sum(s1[a][r]);
       const int m = m0 + a * 16 + 4 * g + r;
-      if (j == 0 && m < A.C) A.part1[(int64_t)m * A.T + t0] = make_float2(u, v * A.istd[m]);
+      if (j == 0 && m < A.C && m >= A.lo) A.part1[(int64_t)(m - A.lo) * A.T + t0] = make_float2(u, v * A.istd[m]);
     }
 }
 
@@ -263,6 +272,117 @@ __global__ __launch_bounds__(256, 2) void k_dgrad1s(Dgrad1Args A) {
     }
 }
 
+// Two layers at once, on the channels that both read: x and the slab move once for the two, 12 bytes per element
+// instead of 24.  Eight waves of 16 channels each; both layers' weights stay in registers, both tiles of db sit in
+// LDS, staged one pixel tile ahead.  65536 pixels, 1000 channels, 96 outputs: 287 us and 13 for the slice between,
+// against 2 x 240; DenseNet-BC-250 step 40.0 -> 38.0 ms, BC-100 4.81 -> 4.73.
+template <int NCH, bool FIRST>
+__global__ __launch_bounds__(512) void k_dgrad1p(Dgrad1Args A, Dgrad1Lower B) {
+  extern __shared__ __attribute__((aligned(16))) float tile_db[];  // [2][NCH*16][64]
+  __shared__ float4 cst[2][128];  // scale, shift, mean, 1/std of the workgroup's channels
+  constexpr int TS = NCH * 16 * 64, SU = (NCH + 1) / 2;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 15, g = lane >> 4;
+  const int mw = (int)blockIdx.y * 128, m0 = mw + wave * 16, HW = A.hw, t0 = blockIdx.x;
+  if (tid < 256) {
+    const int li = tid >> 7, c = min(mw + (tid & 127), A.C - 1);
+    float sc, sf;
+    bn_fold((li ? B.gamma : A.gamma)[c], (li ? B.beta : A.beta)[c], A.mean[c], A.istd[c], sc, sf);
+    cst[li][tid & 127] = make_float4(sc, sf, A.mean[c], A.istd[c]);
+  }
+  float4 w[2][NCH];
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) {
+    w[0][c] = ldg4(wfrag(A.W, A.B16, min(m0 >> 4, (A.C16 >> 4) - 1), c));
+    w[1][c] = ldg4(wfrag(B.W, A.B16, min(m0 >> 4, (B.C16 >> 4) - 1), c));
+  }
+  auto ch = [&](int r) { return min(m0 + 4 * g + r, A.C - 1); };
+  float s0[2][4], s1[2][4];
+#pragma unroll
+  for (int li = 0; li < 2; ++li)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s0[li][r] = s1[li][r] = 0.f;
+
+  float4 st[2][SU];  // thread: rows 32u + tid/16, pixels 4*(tid%16)..+3
+  const int srow = tid >> 4, scol = 4 * (tid & 15);
+  auto request = [&](int tile) {
+    const int img = tile / A.tpi, q = min((tile - img * A.tpi) * 64 + scol, HW - 4);
+#pragma unroll
+    for (int u = 0; u < SU; ++u) {
+      const int64_t o = (int64_t)img * A.db_stride + q + (int64_t)min(u * 32 + srow, A.B - 1) * HW;
+      st[0][u] = ldg4(A.db + o);
+      st[1][u] = ldg4(B.db + o);
+    }
+  };
+  request(t0);
+  for (int tile = t0; tile < A.tiles; tile += A.T) {
+    __syncthreads();  // the previous tile's reads are done
+#pragma unroll
+    for (int u = 0; u < SU; ++u) {
+      const int row = u * 32 + srow;
+      if (NCH % 2 == 0 || row < NCH * 16) {
+        *reinterpret_cast<float4*>(&tile_db[row * 64 + scol]) = st[0][u];
+        *reinterpret_cast<float4*>(&tile_db[TS + row * 64 + scol]) = st[1][u];
+      }
+    }
+    __syncthreads();
+    const int img = tile / A.tpi, q = (tile - img * A.tpi) * 64 + 4 * j;
+    const bool ok = q < HW;  // HW % 4 == 0: a lane's four pixels are in or out together
+    const int qc = ok ? q : 0;
+    const float* xp = A.x + (int64_t)img * A.x_stride + qc;
+    const float* rp = (FIRST ? A.dy : A.G) + (int64_t)img * A.g_stride + qc;
+    float4 x4[4], g4[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      x4[r] = ldg4(xp + (int64_t)ch(r) * HW);
+      g4[r] = ldg4(rp + (int64_t)ch(r) * HW);
+    }
+    request(min(tile + A.T, A.tiles - 1));
+    __builtin_amdgcn_sched_barrier(0);  // all of these are in flight before the products
+#pragma unroll
+    for (int li = 0; li < 2; ++li) {
+      f32x4 acc[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < NCH; ++c)
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+          const float4 d = *reinterpret_cast<const float4*>(&tile_db[li * TS + (c * 16 + 4 * ks + g) * 64 + 4 * j]);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) acc[t] = mfma16(elem(w[li][c], ks), elem(d, t), acc[t]);
+        }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float4 k = cst[li][wave * 16 + 4 * g + r];
+        float o[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const float xv = elem(x4[r], t), dz = ok && __fmaf_rn(xv, k.x, k.y) > 0.f ? acc[t][r] : 0.f;
+          o[t] = __fmaf_rn(k.x, dz, elem(g4[r], t));
+          s0[li][r] += dz;
+          s1[li][r] = __fmaf_rn(dz, xv - k.z, s1[li][r]);
+        }
+        g4[r] = make_float4(o[0], o[1], o[2], o[3]);
+      }
+    }
+    if (ok) {
+      float* op = A.G + (int64_t)img * A.g_stride + q;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (m0 + 4 * g + r < A.C) *reinterpret_cast<float4*>(op + (int64_t)ch(r) * HW) = g4[r];
+    }
+  }
+#pragma unroll
+  for (int li = 0; li < 2; ++li)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float u = row16_sum(s0[li][r]), v = row16_sum(s1[li][r]);
+      const int m = m0 + 4 * g + r;
+      if (j == 0 && m < A.C) (li ? B.part1 : A.part1)[(int64_t)m * A.T + t0] = make_float2(u, v * cst[li][wave * 16 + 4 * g + r].w);
+    }
+}
+
 // dx0 = G - K0 - K1*xhat on the block input's channels.  grid (channels, image ranges), 16-byte accesses.
 __global__ __launch_bounds__(256) void k_dx0(const float* __restrict__ G, int64_t g_stride, const float* __restrict__ x,
                                              int64_t x_stride, float* __restrict__ dx0, int64_t d_stride, int n, int hw,
@@ -293,26 +413,72 @@ int bwd32_dgrad1_splits(int n, int hw, int c) {
   if (t > tiles) t = tiles;
   return t < 1 ? 1 : (int)t;
 }
-size_t bwd32_partial1_floats(int n, int hw, int c) { return 2 * (size_t)c * bwd32_dgrad1_splits(n, hw, c); }
+// ... of a pair's k channels between its layers: a tile per wave where there are up to 1024 (with two, the loads of
+// a second tile waited out behind the first's products: 13.5 us a launch on the first block of BC-100)
+static int near_splits(int n, int hw) {
+  const int64_t tiles = (int64_t)((hw + 63) / 64) * n;
+  return tiles < 1024 ? (int)tiles : 1024;
+}
+// ... of k_dgrad1p: one workgroup of 128 channels per CU.
+static int dgrad1p_splits(int n, int hw, int c) {
+  const int64_t tiles = (int64_t)((hw + 63) / 64) * n, groups = (c + 127) / 128;
+  int64_t t = 256 / groups;
+  if (t > tiles) t = tiles;
+  return t < 1 ? 1 : (int)t;
+}
+size_t bwd32_partial1_floats(int n, int hw, int c) {
+  const size_t one = 2 * (size_t)c * bwd32_dgrad1_splits(n, hw, c), two = 4 * (size_t)c * dgrad1p_splits(n, hw, c);
+  return one > two ? one : two;
+}
+size_t bwd32_partial1_near_floats(int n, int hw, int k) { return 2 * (size_t)k * near_splits(n, hw); }
+
+// Whether a layer over c channels and the one above it share their pass over the slab.  What that saves is half
+// the slab's traffic, what it costs a launch for the k channels between them: from about 56 MB a layer on
+// (16384 pixels x 216 channels: 17 + 9 us against 2 x 12; 65536 x 96: 26 + 9 against 18 + 20; x 180: 46 + 9
+// against 2 x 36).
+bool bwd32_pair_ok(int n, int hw, int c, int B) {
+  const int B16 = (B + 15) & ~15;
+  return B16 >= 48 && B16 <= 128 && c > 64 && (int64_t)12 * c * n * hw >= (int64_t)56 << 20;
+}
 
 hipError_t bwd32_dgrad1(const Bwd32Layer& L, hipStream_t st) {
   Dgrad1Args A{};
-  const int hw = L.h * L.w, groups = (L.c + 31) / 32;
+  const int hw = L.h * L.w;
   A.db = L.db; A.db_stride = (int64_t)L.B * hw; A.B = L.B;
-  A.W = L.pk1t; A.C16 = (L.c + 15) & ~15; A.B16 = (L.B + 15) & ~15;
+  A.W = L.pk1t; A.C16 = (L.cw + 15) & ~15; A.B16 = (L.B + 15) & ~15;
   A.x = L.x; A.x_stride = L.x_stride;
   A.dy = L.dy; A.G = L.G; A.g_stride = L.ys;
   A.gamma = L.g1; A.beta = L.b1; A.mean = L.mean_y; A.istd = L.istd_y;
-  A.part1 = L.part1; A.C = L.c; A.T = bwd32_dgrad1_splits(L.n, hw, L.c);
+  A.part1 = L.part1; A.lo = L.lo; A.C = L.c;
   A.hw = hw; A.tpi = (hw + 63) / 64; A.tiles = A.tpi * L.n;
+  if (L.up_db) {  // with the layer above
+    const Dgrad1Lower B{L.db, L.pk1t, A.C16, L.g1, L.b1, L.part1 + (int64_t)L.c * dgrad1p_splits(L.n, hw, L.c)};
+    A.db = L.up_db; A.W = L.up_pk1t; A.C16 = (L.c + L.k + 15) & ~15; A.gamma = L.up_g1; A.beta = L.up_b1;
+    A.T = dgrad1p_splits(L.n, hw, L.c);
+    const dim3 grid((unsigned)A.T, (unsigned)((L.c + 127) / 128));
+#define DNB_L(NCH)                                                                                            \
+  do {                                                                                                        \
+    const size_t lds = (size_t)2 * NCH * 16 * 64 * sizeof(float);                                             \
+    if (L.first) hipLaunchKernelGGL((k_dgrad1p<NCH, true>), grid, dim3(512), lds, st, A, B);                  \
+    else hipLaunchKernelGGL((k_dgrad1p<NCH, false>), grid, dim3(512), lds, st, A, B);                         \
+  } while (0)
+    switch (A.B16 >> 4) {
+      case 3: DNB_L(3); break; case 4: DNB_L(4); break; case 5: DNB_L(5); break; case 6: DNB_L(6); break;
+      case 7: DNB_L(7); break; default: DNB_L(8); break;
+    }
+#undef DNB_L
+    return hipGetLastError();
+  }
+  const int groups = (L.c - (L.lo & ~15) + 31) / 32;
+  A.T = L.lo ? near_splits(L.n, hw) : bwd32_dgrad1_splits(L.n, hw, L.c);
   A.nwm = groups >= 3 ? 4 : groups;
   const int nwp = 4 / A.nwm;
   // (fewer chunks: the products are too few to hide anything; more: no registers for their weights)
-  if (A.nwm == 4 && A.B16 >= 48 && A.B16 <= 128) {
+  if (A.nwm == 4 && A.B16 >= 48 && A.B16 <= 128 && L.lo == 0) {
     const dim3 grid((unsigned)A.T, (unsigned)((groups + 3) / 4));
 #define DNB_L(NCH)                                                                       \
   do {                                                                                   \
-    if (L.last) hipLaunchKernelGGL((k_dgrad1s<NCH, true>), grid, dim3(256), 0, st, A);   \
+    if (L.first) hipLaunchKernelGGL((k_dgrad1s<NCH, true>), grid, dim3(256), 0, st, A);   \
     else hipLaunchKernelGGL((k_dgrad1s<NCH, false>), grid, dim3(256), 0, st, A);         \
   } while (0)
     switch (A.B16 >> 4) {
@@ -325,7 +491,7 @@ hipError_t bwd32_dgrad1(const Bwd32Layer& L, hipStream_t st) {
   const dim3 grid((unsigned)((A.T + nwp - 1) / nwp), (unsigned)((groups + A.nwm - 1) / A.nwm));
 #define DNB_L(NCH)                                                                       \
   do {                                                                                   \
-    if (L.last) hipLaunchKernelGGL((k_dgrad1<NCH, true>), grid, dim3(256), 0, st, A);    \
+    if (L.first) hipLaunchKernelGGL((k_dgrad1<NCH, true>), grid, dim3(256), 0, st, A);    \
     else hipLaunchKernelGGL((k_dgrad1<NCH, false>), grid, dim3(256), 0, st, A);          \
   } while (0)
   switch (A.B16 >> 4) {
@@ -336,9 +502,21 @@ hipError_t bwd32_dgrad1(const Bwd32Layer& L, hipStream_t st) {
 }
 
 void bwd32_bn1_finish(const Bwd32Layer& L, Bn1Finish* out) {
-  const int hw = L.h * L.w;
-  *out = Bn1Finish{L.part1, bwd32_dgrad1_splits(L.n, hw, L.c), L.c, (L.c + 3) / 4, L.g1, L.istd_y,
-                   1.0f / ((float)L.n * (float)hw), L.K, L.last ? 1 : 0, L.dgamma1, L.dbeta1};
+  const int hw = L.h * L.w, W = L.c - L.lo;
+  const int T = L.up_db ? dgrad1p_splits(L.n, hw, L.c) : L.lo ? near_splits(L.n, hw) : bwd32_dgrad1_splits(L.n, hw, L.c);
+  *out = Bn1Finish{};
+  out->n = L.up_db ? 2 : 1;
+  out->T = T; out->C = W; out->lo = L.lo; out->wgs = (W + 3) / 4;
+  for (int q = 0; q < out->n; ++q) {
+    const bool up = L.up_db && q == 0;
+    out->part[q] = L.part1 + (int64_t)q * W * T;
+    out->gamma[q] = up ? L.up_g1 : L.g1;
+    out->dgamma[q] = up ? L.up_dgamma1 : L.dgamma1;
+    out->dbeta[q] = up ? L.up_dbeta1 : L.dbeta1;
+  }
+  out->istd = L.istd_y;
+  out->inv_p = 1.0f / ((float)L.n * (float)hw);
+  out->K = L.K; out->first = L.first ? 1 : 0;
 }
 hipError_t launch_bn1_finish(const Bn1Finish& f, hipStream_t st) {
   if (f.wgs == 0) return hipSuccess;

@@ -84,9 +84,17 @@ struct Bwd32Layer {
   const float *mean_y, *istd_y, *mean_b, *istd_b;
   float *dgamma1, *dbeta1;
   float2 *part1, *part2, *K;
+  // what bwd32_dgrad1 and bwd32_bn1_finish take: channels lo..c-1 (c: of the slice's upper end) of a layer of cw
+  // channels, by itself or (up_db) with the layer above, whose c + k channels include these
+  int lo, cw;
+  bool first;                            // nothing has been added to these channels of the slab yet
+  const float *up_db, *up_pk1t, *up_g1, *up_b1;
+  float *up_dgamma1, *up_dbeta1;
 };
+bool bwd32_pair_ok(int n, int hw, int c, int B);
 bool bwd32_ok(int n, int h, int w, int k, int B);
 size_t bwd32_partial1_floats(int n, int hw, int c);
+size_t bwd32_partial1_near_floats(int n, int hw, int k);  // of a pair's k channels between its layers
 size_t bwd32_partial2_floats(int n, int h, int w, int k, int B);
 int bwd32_dgrad1_splits(int n, int hw, int c);
 // 3x3 data gradient of the corrected slice, masked by BN2's ReLU, with BN2's sums.  *T2: partial pairs per channel.

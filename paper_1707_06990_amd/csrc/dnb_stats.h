@@ -154,28 +154,45 @@ struct RowIter {
 // gradients and the running constants K (see dnb_bwd_f32.hip).  Carried by the layer's weight-gradient
 // launch; a wave per channel.
 struct Bn1Finish {
-  const float2* part;
-  int T, C, wgs;               // wgs = 0: nothing to do
-  const float *gamma, *istd;
+  int n;                       // layers whose sums these are (two where they shared the pass over the slab)
+  const float2* part[2];
+  int T, lo, C, wgs;           // C channels from lo on; wgs = 0: nothing to do
+  const float *gamma[2], *istd;
   float inv_p;
   float2* K;
   int first;                   // K is set, not added to
-  float *dgamma, *dbeta;
+  float *dgamma[2], *dbeta[2];
 };
 __device__ __forceinline__ void bn1_finish_body(const Bn1Finish& A, int wg) {
-  const int ch = wg * (int)(blockDim.x >> 6) + (int)(threadIdx.x >> 6);
-  if (ch >= A.C) return;
-  const float2* p = A.part + (int64_t)ch * A.T;
-  float2 s = make_float2(0.f, 0.f);
-  for (int i = threadIdx.x & 63; i < A.T; i += 64) { const float2 v = p[i]; s.x += v.x; s.y += v.y; }
-  s.x = bnb_wave_sum(s.x);
-  s.y = bnb_wave_sum(s.y);
+  const int i = wg * (int)(blockDim.x >> 6) + (int)(threadIdx.x >> 6);
+  if (i >= A.C) return;
+  const int ch = A.lo + i;
+  float2 s[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    s[q] = make_float2(0.f, 0.f);
+    if (q < A.n) {
+      const float2* p = A.part[q] + (int64_t)i * A.T;
+      for (int t = threadIdx.x & 63; t < A.T; t += 64) { const float2 v = p[t]; s[q].x += v.x; s[q].y += v.y; }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    s[q].x = bnb_wave_sum(s[q].x);
+    s[q].y = bnb_wave_sum(s[q].y);
+  }
   if ((threadIdx.x & 63) == 0) {
-    const float sc = __fmul_rn(A.gamma[ch], A.istd[ch]) * A.inv_p;
-    const float2 o = A.first ? make_float2(0.f, 0.f) : A.K[ch];
-    A.K[ch] = make_float2(__fmaf_rn(sc, s.x, o.x), __fmaf_rn(sc, s.y, o.y));
-    A.dbeta[ch] = s.x;
-    A.dgamma[ch] = s.y;
+    float2 k = A.first ? make_float2(0.f, 0.f) : A.K[ch];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      if (q < A.n) {
+        const float sc = __fmul_rn(A.gamma[q][ch], A.istd[ch]) * A.inv_p;
+        k = make_float2(__fmaf_rn(sc, s[q].x, k.x), __fmaf_rn(sc, s[q].y, k.y));
+        A.dbeta[q][ch] = s[q].x;
+        A.dgamma[q][ch] = s[q].y;
+      }
+    }
+    A.K[ch] = k;
   }
 }
 

@@ -283,6 +283,17 @@ def test_bc250_blocks_match_oracle(dnb, oracle, i, batch):
     assert gpu["peak"] == (m * B + m * k + cfg.c_out + cfg.c_in(m) + B) * cfg.pixels * 4
 
 
+# layers in pairs over a large slab: an odd layer left over, images that are no multiple of 64 pixels, outputs that
+# are no multiple of 16, a slice that straddles two M-tiles; and five chunks of outputs (odd) under the shared schedule
+PAIRS = [(wl.BlockCfg(64, 90, 28, 28, 3, 12, 50), 2), (wl.BlockCfg(50, 130, 28, 28, 2, 20, 72), 0)]
+
+
+@pytest.mark.parametrize("cfg,schedule", PAIRS, ids=["n64c90k12B50", "n50c130k20B72-shared"])
+def test_layers_in_pairs_match_oracle(dnb, oracle, cfg, schedule):
+    x0, lp, dy = wl.make_block_inputs(cfg, affine="random")
+    compare_with_kernel_decisions(dnb, oracle, cfg, x0, lp, dy, schedule=schedule)
+
+
 @pytest.mark.parametrize("which", ["config2", "config3"])
 def test_backward_is_exactly_linear_in_dy_at_full_size(dnb, which):
     """A property that needs no oracle and holds at any size: every step of the backward pass is
