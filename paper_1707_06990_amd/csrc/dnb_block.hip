@@ -23,7 +23,7 @@ struct dnb_block {
   std::vector<size_t> off_stat_b;            // per layer mean[B], istd[B]
   std::vector<size_t> off_fold1, off_fold2;  // fused schedule: per layer folded (scale, shift) of BN1 / BN2
   size_t off_part;                           // reduction partials of the main chain (BN)
-  size_t off_K, off_db2, part1_floats, near_floats;                // backward: K0, K1 per channel; a second db (pairs of layers); where BN2's
+  size_t off_K, off_db2, part1_floats, near_floats, stat_floats;                // backward: K0, K1 per channel; a second db (pairs of layers); where BN2's
                                              // partials, a slice's own BN1 sums start in off_part
   size_t off_partA[2], off_partB[2];         // partials of the 3x3 / 1x1 weight gradients, layer l's in [l & 1]
   // with concurrency on, the fp32 backward with separate BN passes runs three chains: the data-gradient
@@ -158,7 +158,8 @@ int forward_bf16(dnb_block* b, const void* x0, const float* params, void* yv, ch
   unsigned short* y = (unsigned short*)yv;
   float* mean_y = (float*)(ws + b->off_stat_y);
   float* istd_y = mean_y + cout;
-  float* part = (float*)(ws + b->off_part);
+  float* const part0 = (float*)(ws + b->off_part);
+  float* part = part0;
   unsigned short* pack = (unsigned short*)(ws + b->off_pack);
   const size_t B16 = (size_t)((B + 15) & ~15), k16 = (size_t)((k + 15) & ~15), B32 = (size_t)((B + 31) & ~31);
   DNB_TRY(nhwc::pack_block_weights(params, pack, d.c0, k, B, m, st));
@@ -178,18 +179,33 @@ int forward_bf16(dnb_block* b, const void* x0, const float* params, void* yv, ch
     const unsigned short* pk1 = pack + b->pk[l];                   // 1x1 forward
     const unsigned short* pk3 = pk1 + B16 * c32 + c16 * B32;       // 3x3 forward
     int T1 = 0, T3 = 0;
-    DNB_TRY(launch_bn_fold(p.g1, p.b1, mean_y, istd_y, part, freshT, fresh_lo, fresh_hi, d.eps, c, fold1, st));
-    if (d.schedule == DNB_SCHED_FUSED) {
-      DNB_TRY(nhwc::conv(y, cout, false, pk1, bl, B, n, c, B, d.h, d.w, 1, fold1, part, &T1, st));
-      DNB_TRY(launch_bn_fold(p.g2, p.b2, mean_b, istd_b, part, T1, 0, B, d.eps, B, fold2, st));
-      DNB_TRY(nhwc::conv(bl, B, false, pk3, y + c, cout, n, B, k, d.h, d.w, 9, fold2, part, &T3, st));
+    const bool fused = d.schedule == DNB_SCHED_FUSED;
+    // few pixels: the convolutions fold the BN they apply themselves (its partials from one half of the buffer, their
+    // own to the other); else k_bn_fold does
+    const FoldIn F1{p.g1, p.b1, mean_y, istd_y, part, freshT, (int)b->hw, freshT / n, (float)P, fresh_lo, fresh_hi, d.eps, fold1};
+    float* const next = part == part0 ? part0 + b->stat_floats : part0;
+    const bool rows = l > 1 && freshT <= kRowStats;  // (the block input's partials come from k_stats_partial)
+    const bool in1 = fused && rows && nhwc::conv1_stats(y, cout, pk1, bl, B, P, c, B, fold1, next, &T1, &F1, st);
+    if (in1) { DNB_TRY(hipGetLastError()); part = next; }
+    else DNB_TRY(launch_bn_fold(p.g1, p.b1, mean_y, istd_y, part, freshT, fresh_lo, fresh_hi, d.eps, c, fold1, st, rows));
+    if (fused) {
+      if (!in1) DNB_TRY(nhwc::conv(y, cout, false, pk1, bl, B, n, c, B, d.h, d.w, 1, fold1, part, &T1, st));
+      const FoldIn F2{p.g2, p.b2, mean_b, istd_b, part, T1, (int)P, T1, (float)P, 0, B, d.eps, fold2};
+      float* const next3 = part == part0 ? part0 + b->stat_floats : part0;
+      if (nhwc::conv3_stats(bl, B, pk3, y + c, cout, n, B, k, d.h, d.w, fold2, next3, &T3, &F2, st)) {
+        DNB_TRY(hipGetLastError());
+        part = next3;
+      } else {
+        DNB_TRY(launch_bn_fold(p.g2, p.b2, mean_b, istd_b, part, T1, 0, B, d.eps, B, fold2, st, T1 <= kRowStats));
+        DNB_TRY(nhwc::conv(bl, B, false, pk3, y + c, cout, n, B, k, d.h, d.w, 9, fold2, part, &T3, st));
+      }
     } else {
       void* S1 = ws + b->off_u[l];
       void* S2 = ws + b->off_a[l];
       void* S3 = ws + b->off_a2[l];
       DNB_TRY(nhwc::bn_relu_rows(y, cout, fold1, S2, c, S1, c, P, c, st));  // concat -> storage 1, BN+ReLU -> storage 2
       DNB_TRY(nhwc::conv(S2, c, false, pk1, bl, B, n, c, B, d.h, d.w, 1, nullptr, part, &T1, st));
-      DNB_TRY(launch_bn_fold(p.g2, p.b2, mean_b, istd_b, part, T1, 0, B, d.eps, B, fold2, st));
+      DNB_TRY(launch_bn_fold(p.g2, p.b2, mean_b, istd_b, part, T1, 0, B, d.eps, B, fold2, st, T1 <= kRowStats));
       DNB_TRY(nhwc::bn_relu_rows(bl, B, fold2, S3, B, nullptr, 0, P, B, st));
       DNB_TRY(nhwc::conv(S3, B, false, pk3, y + c, cout, n, B, k, d.h, d.w, 9, nullptr, part, &T3, st));
     }
@@ -652,6 +668,8 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
     need(nhwc::stats_partial_floats(P, d.c0));
     need(nhwc::conv_stats_partial_floats(d.n, B, d.h, d.w));
     need(nhwc::conv_stats_partial_floats(d.n, k, d.h, d.w));
+    b->stat_floats = align_up(part, 4);
+    if (d.schedule == DNB_SCHED_FUSED) need(2 * b->stat_floats);  // two halves: see forward_bf16
     size_t pe = 0, p1 = 0;  // pe: bf16 elements
     for (int l = 1; l <= m; ++l) {
       const size_t f1 = nhwc::bwd_partial1_near(P, c_in(d, l), B);

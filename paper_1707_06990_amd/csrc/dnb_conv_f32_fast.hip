@@ -1287,14 +1287,15 @@ __global__ __launch_bounds__(256) void k_sum_wgrad3x3(const float* __restrict__ 
 __global__ __launch_bounds__(256) void k_bn_fold(const float* __restrict__ gamma, const float* __restrict__ beta,
                                                 float* mean, float* istd, const float* __restrict__ part,
                                                 int T, int fresh_lo, int fresh_hi, float eps,
-                                                float2* __restrict__ fold) {
+                                                float2* __restrict__ fold, int rows) {
   __shared__ float sh[12];
   const int ch = blockIdx.x;
   // requested before the merge: behind its barriers they would cost a second memory round trip
   const float ga = gamma[ch], be = beta[ch];
   float mu, is;
   if (ch >= fresh_lo && ch < fresh_hi) {
-    const Stat3 r = stat_merge_block(part + (int64_t)(ch - fresh_lo) * T * 3, T, sh);
+    const int C = fresh_hi - fresh_lo, c = ch - fresh_lo;
+    const Stat3 r = stat_merge_block(part + (rows ? (int64_t)c * 3 : (int64_t)c * T * 3), T, sh, rows ? C * 3 : 3);
     mu = r.m;
     is = bn_istd(r.m2, r.c, eps);
     if (threadIdx.x == 0) { mean[ch] = mu; istd[ch] = is; }
@@ -1357,10 +1358,10 @@ hipError_t launch_pack_block_weights(const float* params, float* packed, int c0,
 
 hipError_t launch_bn_fold(const float* gamma, const float* beta, float* mean, float* istd,
                           const float* part, int T, int fresh_lo, int fresh_hi, float eps, int nch,
-                          float2* fold, hipStream_t st) {
+                          float2* fold, hipStream_t st, bool rows) {
   if (nch <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_bn_fold, dim3((unsigned)nch), dim3(256), 0, st, gamma, beta, mean, istd, part, T,
-                     fresh_lo, fresh_hi, eps, fold);
+                     fresh_lo, fresh_hi, eps, fold, rows ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -176,7 +176,7 @@ bool conv_fast_ok(const float* in, int64_t in_stride, const float* out, int64_t 
 // [fresh_lo, fresh_hi) are first finalised from their [T][3] partial statistics.
 hipError_t launch_bn_fold(const float* gamma, const float* beta, float* mean, float* istd,
                           const float* part, int T, int fresh_lo, int fresh_hi, float eps, int nch,
-                          float2* fold, hipStream_t st);
+                          float2* fold, hipStream_t st, bool rows = false);
 
 // dW[m][c][t] = sum_{n,q} g[n][m][q] * in[n][c][q + shift(t)]  (OIHW result).
 size_t conv_wgrad_partial_floats(int n, int cin, int cout, int h, int w, int taps);
@@ -226,6 +226,7 @@ hipError_t launch_sum_partials(const float* partials, int splits, int64_t count,
 
 // ---- bf16 / NHWC path (dnb_nhwc_bf16.hip): feature maps bf16 with channels contiguous, row
 // strides ("ld") in elements; parameters, statistics, gradient slab and partials fp32.
+struct FoldIn;
 namespace nhwc {
 hipError_t copy_rows(const void* src, int64_t sld, void* dst, int64_t dld, int64_t P, int c, hipStream_t st);
 // out = bf16(max(0, fma(x, fold.x, fold.y))) per channel; copy (may be null) = x  (storage 2 / storage 1)
@@ -244,11 +245,12 @@ hipError_t conv(const void* in, int64_t in_ld, bool in_f32, const void* Wp, void
                 int cin, int cout, int h, int w, int taps, const float2* fold, float* spart, int* sT,
                 hipStream_t st);
 // (dnb_nhwc_conv1.hip) The 1x1 with statistics of its output, few pixels; false (nothing launched) if the shape is not taken.
+// F (may be null): the BN of the input is folded by the kernel itself (fold is then an output).
 bool conv1_stats(const void* in, int64_t in_ld, const void* Wp, void* out, int64_t out_ld, int64_t P, int cin, int cout,
-                 const float2* fold, float* spart, int* sT, hipStream_t st);
+                 const float2* fold, float* spart, int* sT, const FoldIn* F, hipStream_t st);
 // (dnb_nhwc_conv3.hip) The 3x3 with statistics of its output; false (nothing launched) if the shape is not taken.
 bool conv3_stats(const void* in, int64_t in_ld, const void* Wp, void* out, int64_t out_ld, int n, int cin, int cout, int h, int w,
-                 const float2* fold, float* spart, int* sT, hipStream_t st);
+                 const float2* fold, float* spart, int* sT, const FoldIn* F, hipStream_t st);
 // One weight gradient: dw[m][c][t] = sum_p g[p][m] * act(a[p + shift(t)][c]), fold = BN+ReLU of a (or null).
 struct WgradIn {
   const void* a; int64_t a_ld;

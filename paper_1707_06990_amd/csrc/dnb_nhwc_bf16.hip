@@ -200,7 +200,7 @@ __global__ __launch_bounds__(256) void k_pack_weights(const float* __restrict__ 
 // requested from HBM before the current chunk's MFMAs are issued and written to the other
 // buffer (BN+ReLU applied, rounded to bf16) after them: one barrier per chunk, load latency
 // under the matrix work.  TIN = u16 (bf16) or float (the gradient slab).  STATS: per-tile
-// (count, mean, M2) of the rounded outputs, as in the fp32 kernels: spart[(m*T + tile)*3].
+// (count, mean, M2) of the rounded outputs, at stat_at.
 template <int TAPS, int MT, typename TIN, bool PRO, bool STATS>
 __global__ __launch_bounds__(256) void k_conv(
     const TIN* __restrict__ in, int64_t in_ld, const u16* __restrict__ Wp, int M16, int K32,
@@ -401,7 +401,7 @@ __global__ __launch_bounds__(256) void k_conv(
         m2 = row16_sum(m2);
         const int m = mbase + a * 16 + 4 * g + r;
         if (j == 0 && m < cout) {
-          float* p = spart + ((int64_t)m * sT + tile_id) * 3;
+          float* p = spart + stat_at(sT, cout, tile_id, m);
           p[0] = (float)tile_px; p[1] = mu; p[2] = m2;
         }
       }
@@ -773,9 +773,9 @@ hipError_t conv(const void* in, int64_t in_ld, bool in_f32, const void* Wp, void
   // 1x1: flat 64-pixel tiles over all images; 3x3: tiles of one image
   const int64_t ptiles = taps == 9 ? (int64_t)((hw + 63) / 64) * n : (P + 63) / 64;
   if ((fold != nullptr) != (spart != nullptr) && fold) return hipErrorInvalidValue;
-  if (taps == 1 && spart && !in_f32 && conv1_stats(in, in_ld, Wp, out, out_ld, P, cin, cout, fold, spart, sT, st))
+  if (taps == 1 && spart && !in_f32 && conv1_stats(in, in_ld, Wp, out, out_ld, P, cin, cout, fold, spart, sT, nullptr, st))
     return hipGetLastError();
-  if (taps == 9 && spart && !in_f32 && conv3_stats(in, in_ld, Wp, out, out_ld, n, cin, cout, h, w, fold, spart, sT, st))
+  if (taps == 9 && spart && !in_f32 && conv3_stats(in, in_ld, Wp, out, out_ld, n, cin, cout, h, w, fold, spart, sT, nullptr, st))
     return hipGetLastError();
   int mt = (mtiles + 3) / 4;
   if (mt > 3) mt = 3;

@@ -32,13 +32,18 @@ struct Conv1Args {
   const float2* fold;
   float* spart; int T;               // partials per channel = tiles of 64 pixels
   int gy;                            // groups of NC M-tiles
+  FoldIn F; int cap;                 // FOLD: BN1 folded here; fresh channels, rounded up to a power of two
 };
+constexpr int kFresh = 64;           // most fresh channels folded inside
 
 // D: steps in flight.  Tiles are dealt to the XCDs in turn, the gy workgroups of a tile to one XCD (they
 // read the same features).  Both roles run whole groups of D steps, every step with the same loads (at
 // clamped addresses) and one barrier, so that a use waits for its own load and not for all of them; past
 // the last step only the products are skipped.
-template <int NC, int NP, int D, bool PRO>
+// FOLD: BN1 is folded here: the producers form a step's pairs from the channels' statistics; those of the fresh
+// channels (the last layer's output) are merged by the consumers before the first step, who have nothing else to
+// do then.  The first workgroup keeps what the backward pass needs.
+template <int NC, int NP, int D, bool PRO, bool FOLD>
 __global__ __launch_bounds__((NC + NP) * 64) void k_conv1(Conv1Args A) {
   constexpr int KC = 128, PITCH = KC + 8, BUFE = 64 * PITCH;
   constexpr int RS = NP * 4, U = 64 / RS;  // 64 pixels x 16 vectors of 8 channels over NP waves
@@ -46,8 +51,11 @@ __global__ __launch_bounds__((NC + NP) * 64) void k_conv1(Conv1Args A) {
   // (scale, shift) of a step's channels: pair e of the 8-channel vectors v side by side, [e][v][4] (a lane's
   // four reads at 64-byte strides met on a quarter of the banks: 16.2 -> 14.4 us a launch)
   __shared__ __attribute__((aligned(16))) float cof[2][2 * KC];
+  __shared__ float2 fresh[FOLD ? kFresh : 1];
+  __shared__ float2 runs[FOLD ? 2 * 256 : 1], table[FOLD ? 127 : 1];
   const int slot = blockIdx.x >> 3, grp = slot % A.gy, tile = (slot / A.gy) * 8 + (blockIdx.x & 7);
   if (tile >= A.T) return;
+  const bool keep = FOLD && tile == 0 && grp == 0;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nst = (A.cin + KC - 1) / KC, steps = (nst + D - 1) / D * D;
   const int tile_px = (int)min((int64_t)64, A.P - (int64_t)tile * 64);
@@ -55,19 +63,38 @@ __global__ __launch_bounds__((NC + NP) * 64) void k_conv1(Conv1Args A) {
   if (wave >= NC) {
     // ---- producer: vector v of rows r, r + RS, ...; a scalar base and 32-bit offsets (64 rows)
     const int pid = (wave - NC) * 64 + lane, v = pid & 15, r = pid >> 4;
-    const int ci = pid & (2 * KC - 1), cw = ((ci >> 2) & 3) * 64 + (ci >> 4) * 4 + (ci & 3);  // coefficient, its place
-    const bool cwr = (wave - NC) * 64 < 2 * KC;
+    // coefficient of a step (FOLD: channel, both its coefficients) that this thread brings, its place in cof
+    const int ci = pid & ((FOLD ? 1 : 2) * KC - 1), c2 = FOLD ? 2 * ci : ci, cw = ((c2 >> 2) & 3) * 64 + (c2 >> 4) * 4 + (c2 & 3);
+    const bool cwr = (wave - NC) * 64 < (FOLD ? 1 : 2) * KC;
     const char* tb = reinterpret_cast<const char*>(A.in + (int64_t)tile * 64 * A.in_ld);
     unsigned ro[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) ro[u] = (unsigned)min(r + u * RS, tile_px - 1) * (unsigned)(2 * A.in_ld);
     uint4 ring[D][U];
-    float cr[D];
-    auto request = [&](int s, uint4(&q)[U], float& c) {
+    struct Coef { float a, b, m, i; };  // FOLD: gamma, beta, mean, 1/std
+    Coef cr[D];
+    auto request = [&](int s, uint4(&q)[U], Coef& c) {
       const unsigned co = min(s * 2 * KC + 16 * v, 2 * A.cin - 16);  // cin % 8 == 0
 #pragma unroll
       for (int u = 0; u < U; ++u) q[u] = *reinterpret_cast<const uint4*>(tb + (ro[u] + co));
-      if (PRO) c = reinterpret_cast<const float*>(A.fold)[min(s * 2 * KC + ci, 2 * A.cin - 1)];
+      if (FOLD) {
+        const int ch = min(s * KC + ci, A.cin - 1);
+        c = Coef{A.F.gamma[ch], A.F.beta[ch], A.F.mean[ch], A.F.istd[ch]};
+      } else if (PRO) {
+        c.a = reinterpret_cast<const float*>(A.fold)[min(s * 2 * KC + ci, 2 * A.cin - 1)];
+      }
+    };
+    auto coefs = [&](int s, const Coef& c) {  // of step s, to its buffer
+      if (FOLD) {
+        const int ch = s * KC + ci;
+        float2 o;
+        bn_fold(c.a, c.b, c.m, c.i, o.x, o.y);
+        if (ch >= A.F.lo && ch < A.cin) o = fresh[ch - A.F.lo];
+        *reinterpret_cast<float2*>(&cof[s & 1][cw]) = o;
+        if (keep && ch < A.cin) A.F.fold[ch] = o;
+      } else {
+        cof[s & 1][cw] = c.a;
+      }
     };
     auto deposit = [&](int s, const uint4(&q)[U], int buf) {
       u16* o = lds + buf * BUFE + r * PITCH + 8 * v;
@@ -99,7 +126,12 @@ __global__ __launch_bounds__((NC + NP) * 64) void k_conv1(Conv1Args A) {
     };
 #pragma unroll
     for (int s = 0; s < D; ++s) request(s, ring[s], cr[s]);
-    if (PRO && cwr) { cof[0][cw] = cr[0]; cof[1][cw] = cr[1]; }
+    if (FOLD) {  // the fresh channels' pairs
+      __syncthreads();
+      __syncthreads();
+      __syncthreads();
+    }
+    if (PRO && cwr) { coefs(0, cr[0]); coefs(1, cr[1]); }
     __syncthreads();
     // step s: coefficients of step s + 1 into the buffer that step s - 1 has left, deposit of step s, request
     // of step s + D into the registers that frees.  The consumers read step s - 1.
@@ -107,7 +139,7 @@ __global__ __launch_bounds__((NC + NP) * 64) void k_conv1(Conv1Args A) {
 #pragma unroll
       for (int u = 0; u < D; ++u) {
         const int s = sb + u, par = s & 1;
-        if (PRO && cwr) cof[par ^ 1][cw] = cr[(u + 1) % D];
+        if (PRO && cwr) coefs(s + 1, cr[(u + 1) % D]);
         deposit(s, ring[u], par);
         request(s + D, ring[u], cr[u]);
         __syncthreads();
@@ -131,6 +163,30 @@ __global__ __launch_bounds__((NC + NP) * 64) void k_conv1(Conv1Args A) {
   for (int t = 0; t < 4; ++t) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int s = 0; s < D; ++s) wload(s, ring[s]);
+  if (FOLD) {
+    const int tid = threadIdx.x, nf = A.F.hi - A.F.lo;  // (the first 256 threads)
+    stat_table(StatRuns{A.F.T, A.F.per, A.F.tpr}, table, tid);
+    __syncthreads();
+    if (tid < 256) {
+      const int ch = min(tid & (A.cap - 1), nf - 1), ql = tid / A.cap;
+      if (A.cap == 16) stat_merge_runs<16>(A.F.part, A.F.T, nf, ch, ql, table, runs, 256, tid);
+      else if (A.cap == 32) stat_merge_runs<8>(A.F.part, A.F.T, nf, ch, ql, table, runs, 256, tid);
+      else stat_merge_runs<4>(A.F.part, A.F.T, nf, ch, ql, table, runs, 256, tid);
+    }
+    __syncthreads();
+    if (tid < nf) {
+      const float ga = A.F.gamma[A.F.lo + tid], be = A.F.beta[A.F.lo + tid];
+      const float2 m = A.cap == 16 ? stat_merge_finish<16>(runs, A.F.T, table, 16, 256, tid)
+                      : A.cap == 32 ? stat_merge_finish<8>(runs, A.F.T, table, 32, 256, tid)
+                                    : stat_merge_finish<4>(runs, A.F.T, table, 64, 256, tid);
+      const float is = bn_istd(m.y, A.F.count, A.F.eps);
+      float2 o;
+      bn_fold(ga, be, m.x, is, o.x, o.y);
+      fresh[tid] = o;
+      if (keep) { A.F.mean[A.F.lo + tid] = m.x; A.F.istd[A.F.lo + tid] = is; }
+    }
+    __syncthreads();
+  }
   __syncthreads();
   __syncthreads();  // step 0 is in LDS
   for (int sb = 0; sb < steps; sb += D) {
@@ -177,7 +233,7 @@ __global__ __launch_bounds__((NC + NP) * 64) void k_conv1(Conv1Args A) {
     }
     m2 = row16_sum(m2);
     if (j == 0) {
-      float* o = A.spart + ((int64_t)(m + e) * A.T + tile) * 3;
+      float* o = A.spart + stat_at(A.T, A.cout, tile, m + e);
       o[0] = (float)tile_px; o[1] = mu; o[2] = m2;
     }
   }
@@ -211,9 +267,10 @@ static int conv1_group(int64_t P, int64_t in_ld, int cout) {
 // The 1x1 with statistics; false (nothing launched) if the shape is not taken.  Wp: packed weights
 // [M16][K32]; *sT = partials per channel.
 bool conv1_stats(const void* in, int64_t in_ld, const void* Wp, void* out, int64_t out_ld, int64_t P, int cin, int cout,
-                 const float2* fold, float* spart, int* sT, hipStream_t st) {
+                 const float2* fold, float* spart, int* sT, const FoldIn* F, hipStream_t st) {
   const int nc = conv1_group(P, in_ld, cout);
   if (!nc) return false;
+  if (F && (F->T > kRowStats || F->hi != cin || F->hi - F->lo > kFresh)) return false;
   Conv1Args A{};
   A.in = (const u16*)in; A.in_ld = in_ld;
   A.W = (const u16*)Wp; A.nk = (cin + 31) / 32;
@@ -222,12 +279,17 @@ bool conv1_stats(const void* in, int64_t in_ld, const void* Wp, void* out, int64
   A.P = P; A.fold = fold; A.spart = spart;
   A.T = (int)((P + 63) / 64);
   A.gy = (A.M16 / 16 + nc - 1) / nc;
+  if (F) {
+    A.F = *F;
+    A.cap = F->hi - F->lo <= 16 ? 16 : F->hi - F->lo <= 32 ? 32 : 64;
+  }
   if (sT) *sT = A.T;
   const dim3 grid((unsigned)((A.T + 7) / 8 * 8 * A.gy));
-#define DNB_C1(NC)                                                                                       \
-  do {                                                                                                   \
-    if (fold) hipLaunchKernelGGL((k_conv1<NC, 8, 3, true>), grid, dim3((NC + 8) * 64), 0, st, A);        \
-    else hipLaunchKernelGGL((k_conv1<NC, 8, 3, false>), grid, dim3((NC + 8) * 64), 0, st, A);            \
+#define DNB_C1(NC)                                                                                             \
+  do {                                                                                                         \
+    if (F) hipLaunchKernelGGL((k_conv1<NC, 8, 3, true, true>), grid, dim3((NC + 8) * 64), 0, st, A);           \
+    else if (fold) hipLaunchKernelGGL((k_conv1<NC, 8, 3, true, false>), grid, dim3((NC + 8) * 64), 0, st, A);  \
+    else hipLaunchKernelGGL((k_conv1<NC, 8, 3, false, false>), grid, dim3((NC + 8) * 64), 0, st, A);           \
   } while (0)
   if (nc == 4) DNB_C1(4); else DNB_C1(6);
 #undef DNB_C1

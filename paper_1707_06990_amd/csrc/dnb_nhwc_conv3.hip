@@ -10,6 +10,9 @@
 // computed) and about 2300 cycles per tile each of LDS reads, weight loads and MFMAs.
 // us a launch against k_conv's: 32 images of 14x14, 128 -> 32 channels 5.8 (11.5), 192 -> 48 9.0 (17);
 // 7x7 5.6 (10.5) and 6.2 (14); 28x28 9.1 (13.6) and 14.1 (25); 56x56 34 (47) and 49 (66).
+// Where its partials are few it folds BN2 itself (FOLD): 6.5 -> 9.5 us a launch at 14x14 with 98 partials of 128
+// channels, for a k_bn_fold of 4.8 us and its place in the stream; DenseNet-264-shaped forward 4.60 -> 4.15 ms with the
+// 1x1's.
 // Each output's K order (chunk, tap, K-step), its rounding and the statistics' 64-pixel groups are those of
 // k_conv (same bits).
 #include "dnb_internal.h"
@@ -29,15 +32,19 @@ struct Conv3Args {
   int tpi, tiles, gy;                // 64-pixel tiles per image, in all; groups of MG M-tiles
   const float2* fold;
   float* spart;
+  FoldIn F; int cap;                 // FOLD: BN2 folded here; channels, rounded up to a power of two
 };
+
+constexpr int kFoldMax = 256;  // most channels folded inside (512 threads, two lanes a channel)
 
 // A workgroup owns 64 pixels of one image (with a row and a pixel of halo on either side) and MG M-tiles;
 // wave w < 2*MG forms M-tile w / 2 of two of the tile's four pixel tiles, all eight waves stage.
 // (Two workgroups a CU asked for where tiles are many: 56x56 45 -> 34 us, 28x28 11.6 -> 9.1 us.)
-template <int MG, bool PRO>
-__global__ __launch_bounds__(512, (MG > 1 ? 4 : 2)) void k_conv3(Conv3Args A) {
+template <int MG, bool PRO, bool FOLD>
+__global__ __launch_bounds__(512, (MG > 1 && !FOLD ? 4 : 2)) void k_conv3(Conv3Args A) {
   extern __shared__ __attribute__((aligned(16))) u16 lds[];
   __shared__ uint2 xch[MG][4][64];
+  __shared__ float2 cfl[FOLD ? kFoldMax : 1], table[FOLD ? 127 : 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), j = lane & 15, g = lane >> 4;
   const int slot = blockIdx.x >> 3, grp = slot % A.gy, tile = (slot / A.gy) * 8 + (blockIdx.x & 7);
   if (tile >= A.tiles) return;
@@ -51,10 +58,6 @@ __global__ __launch_bounds__(512, (MG > 1 ? 4 : 2)) void k_conv3(Conv3Args A) {
   const u16* ib = A.in + (int64_t)img * HW * A.in_ld + min(8 * v, A.cin - 8);
   const bool cok = 8 * v < A.cin;
   float2 f[8];
-  if (PRO) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) f[e] = A.fold[min(8 * v, A.cin - 8) + e];
-  }
   auto request = [&](int p0, uint4(&q)[4]) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -87,6 +90,36 @@ __global__ __launch_bounds__(512, (MG > 1 ? 4 : 2)) void k_conv3(Conv3Args A) {
   };
   uint4 q[4];
   request(0, q);
+  if (PRO) {
+    const int cf = min(8 * v, A.cin - 8);
+    if (FOLD) {  // every workgroup folds the BN of its input for itself, the first keeps the result
+      float2* sh = reinterpret_cast<float2*>(lds);  // [2][512], before the tile
+      const int ch = tid & (A.cap - 1), ql = tid / A.cap, cc = min(ch, A.cin - 1);
+      stat_table(StatRuns{A.F.T, A.F.per, A.F.tpr}, table, tid);
+      __syncthreads();
+      if (A.cap == 64) stat_merge_runs<8>(A.F.part, A.F.T, A.cin, cc, ql, table, sh, 512, tid);
+      else if (A.cap == 128) stat_merge_runs<4>(A.F.part, A.F.T, A.cin, cc, ql, table, sh, 512, tid);
+      else stat_merge_runs<2>(A.F.part, A.F.T, A.cin, cc, ql, table, sh, 512, tid);
+      __syncthreads();
+      if (tid < A.cin) {
+        const float ga = A.F.gamma[tid], be = A.F.beta[tid];
+        const float2 m = A.cap == 64 ? stat_merge_finish<8>(sh, A.F.T, table, 64, 512, tid)
+                         : A.cap == 128 ? stat_merge_finish<4>(sh, A.F.T, table, 128, 512, tid)
+                                        : stat_merge_finish<2>(sh, A.F.T, table, 256, 512, tid);
+        const float is = bn_istd(m.y, A.F.count, A.F.eps);
+        float2 o;
+        bn_fold(ga, be, m.x, is, o.x, o.y);
+        cfl[tid] = o;
+        if (tile == 0 && grp == 0) { A.F.mean[tid] = m.x; A.F.istd[tid] = is; A.F.fold[tid] = o; }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < 8; ++e) f[e] = cfl[cf + e];
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) f[e] = A.fold[cf + e];
+    }
+  }
 
   const int mt = grp * MG + (wave >> 1), tp = (wave & 1) * 2;
   const int left = min(64, HW - q0);               // pixels of the tile
@@ -176,7 +209,7 @@ __global__ __launch_bounds__(512, (MG > 1 ? 4 : 2)) void k_conv3(Conv3Args A) {
     }
     m2 = row16_sum(m2);
     if (j == 0) {
-      float* o = A.spart + ((int64_t)(ms + e) * A.tiles + tile) * 3;
+      float* o = A.spart + stat_at(A.tiles, A.cout, tile, ms + e);
       o[0] = (float)left; o[1] = mu; o[2] = m2;
     }
   }
@@ -190,10 +223,10 @@ __global__ __launch_bounds__(512, (MG > 1 ? 4 : 2)) void k_conv3(Conv3Args A) {
 // of them, up to four, where tiles alone fill the chip.  Wp: packed weights, nine taps
 // of [M16][K32]; *sT = partials per channel.
 bool conv3_stats(const void* in, int64_t in_ld, const void* Wp, void* out, int64_t out_ld, int n, int cin, int cout, int h, int w,
-                 const float2* fold, float* spart, int* sT, hipStream_t st) {
+                 const float2* fold, float* spart, int* sT, const FoldIn* F, hipStream_t st) {
   const int hw = h * w, nch = (cin + 63) / 64;
   const int64_t tpi = (hw + 63) / 64, tiles = tpi * n;
-  const size_t lds = (size_t)(64 + 2 * (w + 1) + 1) * (nch * 64 + 8) * sizeof(u16);
+  size_t lds = (size_t)(64 + 2 * (w + 1) + 1) * (nch * 64 + 8) * sizeof(u16);
   if (lds > 76 * 1024 || nch * 8 > 512 || tiles > (1 << 24)) return false;
   Conv3Args A{};
   A.in = (const u16*)in; A.in_ld = in_ld;
@@ -202,6 +235,13 @@ bool conv3_stats(const void* in, int64_t in_ld, const void* Wp, void* out, int64
   A.cin = cin; A.cout = cout; A.H = h; A.Wd = w;
   A.tpi = (int)tpi; A.tiles = (int)tiles;
   A.fold = fold; A.spart = spart;
+  if (F) {
+    if (F->T > kRowStats || cin > kFoldMax) return false;
+    A.F = *F;
+    A.cap = cin <= 64 ? 64 : cin <= 128 ? 128 : 256;
+    if (A.cap * F->T > 16384) return false;  // 32 partials a thread: at 49 a launch of k_bn_fold is faster again
+    if (lds < 2 * 512 * sizeof(float2)) lds = 2 * 512 * sizeof(float2);
+  }
   if (sT) *sT = A.tiles;
   const int mtiles = A.M16 / 16;
   int mg = 1;
@@ -211,8 +251,9 @@ bool conv3_stats(const void* in, int64_t in_ld, const void* Wp, void* out, int64
   const dim3 grid((unsigned)((A.tiles + 7) / 8 * 8 * A.gy));
 #define DNB_C3(MG)                                                                              \
   do {                                                                                          \
-    if (fold) hipLaunchKernelGGL((k_conv3<MG, true>), grid, dim3(512), lds, st, A);             \
-    else hipLaunchKernelGGL((k_conv3<MG, false>), grid, dim3(512), lds, st, A);                 \
+    if (F) hipLaunchKernelGGL((k_conv3<MG, true, true>), grid, dim3(512), lds, st, A);          \
+    else if (fold) hipLaunchKernelGGL((k_conv3<MG, true, false>), grid, dim3(512), lds, st, A); \
+    else hipLaunchKernelGGL((k_conv3<MG, false, false>), grid, dim3(512), lds, st, A);          \
   } while (0)
   switch (mg) { case 1: DNB_C3(1); break; case 2: DNB_C3(2); break; case 3: DNB_C3(3); break; default: DNB_C3(4); break; }
 #undef DNB_C3

@@ -80,10 +80,10 @@ __device__ __forceinline__ Stat3 stat_merge_wave(Stat3 v) {
   return v;
 }
 
-// Merges T partials stored as [T][3] floats with the whole workgroup (blockDim a multiple of
+// Merges T partials of three floats each, st apart, with the whole workgroup (blockDim a multiple of
 // 64, at most 1024): thread t folds partials t, t+blockDim, ... in order, then waves, then the
 // per-wave results in wave order.  `sh` needs 3 floats per wave.  Result in every thread.
-__device__ __forceinline__ Stat3 stat_merge_block(const float* __restrict__ p, int T, float* sh) {
+__device__ __forceinline__ Stat3 stat_merge_block(const float* __restrict__ p, int T, float* sh, int st = 3) {
   Stat3 v{0.f, 0.f, 0.f};
   // four of the thread's partials are requested before the first is folded in (a fold per load
   // would wait out one memory latency per partial); loads past T repeat the last partial and
@@ -94,7 +94,8 @@ __device__ __forceinline__ Stat3 stat_merge_block(const float* __restrict__ p, i
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int q = min(i + u * bd, T - 1);
-      o[u] = Stat3{p[3 * q], p[3 * q + 1], p[3 * q + 2]};
+      const float* e = p + (int64_t)q * st;
+      o[u] = Stat3{e[0], e[1], e[2]};
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -112,6 +113,110 @@ __device__ __forceinline__ Stat3 stat_merge_block(const float* __restrict__ p, i
   return r;
 }
 
+
+// Where partials of (count, mean, M2) are few they lie [T][C][3], else [C][T][3]: the kernels that merge the few
+// have a lane per channel (one of [C][T][3] read 64 cache lines at a time: 18 us for 128 channels x 98).
+constexpr int kRowStats = 128;
+__host__ __device__ __forceinline__ int64_t stat_at(int T, int C, int t, int ch) {
+  return T <= kRowStats ? ((int64_t)t * C + ch) * 3 : ((int64_t)ch * T + t) * 3;
+}
+
+// Merging T <= kRowStats partials ([T][C][3]) of many channels inside a kernel, in the order and with the bits of
+// stat_merge_block with 256 threads: per 64 partials a balanced tree, then those in order.  The counts (tiles of 64
+// pixels of runs of `per` pixels, tpr tiles each) are the same for every channel, so the two quotients of each
+// node, the only slow part, are formed once: table[node] = (nb / (na + nb), na * nb / (na + nb)); an empty right side
+// is marked by 0.  Threads: table by the first 127; after a barrier thread tid takes channel tid % cap and one of
+// Q = NT / cap runs of 64 / Q leaves, to sh[2][NT]; after another the first cap threads finish a channel each.  For
+// kernels that fold the BN they apply themselves: a launch of k_bn_fold is two memory latencies and a kernel boundary.
+struct StatRuns { int T, per, tpr; };
+__device__ __forceinline__ int stat_pixels(const StatRuns& R, int t) {  // of the first t tiles
+  t = min(t, R.T);
+  return (t / R.tpr) * R.per + min((t % R.tpr) * 64, R.per);
+}
+__device__ __forceinline__ void stat_table(const StatRuns& R, float2* table, int tid) {
+  if (tid >= 127) return;
+  int lo = 0, half = 64;  // the node that joins the two groups of 64
+  if (tid < 126) {
+    int i = tid % 63, n = 32;
+    half = 1;
+    while (i >= n) { i -= n; n >>= 1; half <<= 1; }
+    lo = (tid / 63) * 64 + i * 2 * half;
+  }
+  const int m = stat_pixels(R, lo + half);
+  const float na = (float)(m - stat_pixels(R, lo)), nb = (float)(stat_pixels(R, lo + 2 * half) - m), tot = __fadd_rn(na, nb);
+  table[tid] = nb > 0.f ? make_float2(__fdiv_rn(nb, tot), __fdiv_rn(__fmul_rn(na, nb), tot)) : make_float2(0.f, 0.f);
+}
+__device__ __forceinline__ float2 stat_join(float2 a, float2 b, float2 w) {  // (mean, M2)
+  const float d = __fsub_rn(b.x, a.x);
+  const float m = __fmaf_rn(d, w.x, a.x), m2 = __fadd_rn(__fadd_rn(a.y, b.y), __fmul_rn(__fmul_rn(d, d), w.y));
+  return w.x > 0.f ? make_float2(m, m2) : a;
+}
+// S leaves a group: 64, or 16 or 32 where T is no more than that (the joins left out meet empty sets only).
+template <int Q, int S>
+__device__ __forceinline__ void stat_runs(const float* __restrict__ p, int T, int C, int ch, int q, const float2* table,
+                                          float2* sh, int NT, int tid) {
+  constexpr int L = S / Q;
+  for (int w = 0; w < 2; ++w) {
+    float2 v[L];
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+      const float* e = p + ((int64_t)min(w * 64 + q * L + i, T - 1) * C + ch) * 3;
+      v[i] = make_float2(e[1], e[2]);
+    }
+    int off = w * 63;
+#pragma unroll
+    for (int h = 1; h < L; h <<= 1) {  // pairs h leaves apart
+#pragma unroll
+      for (int i = 0; i < L; i += 2 * h) v[i] = stat_join(v[i], v[i + h], table[off + (q * L + i) / (2 * h)]);
+      off += 32 / h;
+    }
+    sh[w * NT + tid] = v[0];
+    if (T <= 64) break;
+  }
+}
+template <int Q, int S>
+__device__ __forceinline__ float2 stat_finish(const float2* sh, int T, const float2* table, int cap, int NT, int ch) {
+  float2 g[2];
+  for (int w = 0; w < 2; ++w) {
+    float2 v[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) v[q] = sh[w * NT + q * cap + ch];
+    int off = w * 63 + 64 - 64 / (S / Q);  // the levels above S / Q leaves
+#pragma unroll
+    for (int h = 1; h < Q; h <<= 1) {
+#pragma unroll
+      for (int i = 0; i < Q; i += 2 * h) v[i] = stat_join(v[i], v[i + h], table[off + i / (2 * h)]);
+      off += 32 / (S / Q) / h;
+    }
+    if (T <= 64) return v[0];
+    if (w == 0) g[0] = v[0]; else g[1] = v[0];
+  }
+  return stat_join(g[0], g[1], table[126]);
+}
+template <int Q>
+__device__ __forceinline__ void stat_merge_runs(const float* __restrict__ p, int T, int C, int ch, int q, const float2* table,
+                                                float2* sh, int NT, int tid) {
+  if (T <= 16) stat_runs<Q, 16>(p, T, C, ch, q, table, sh, NT, tid);
+  else if (T <= 32) stat_runs<Q, 32>(p, T, C, ch, q, table, sh, NT, tid);
+  else stat_runs<Q, 64>(p, T, C, ch, q, table, sh, NT, tid);
+}
+template <int Q>
+__device__ __forceinline__ float2 stat_merge_finish(const float2* sh, int T, const float2* table, int cap, int NT, int ch) {
+  return T <= 16 ? stat_finish<Q, 16>(sh, T, table, cap, NT, ch)
+         : T <= 32 ? stat_finish<Q, 32>(sh, T, table, cap, NT, ch) : stat_finish<Q, 64>(sh, T, table, cap, NT, ch);
+}
+
+// What k_bn_fold does for channels lo..hi-1, given to a kernel that folds by itself.
+struct FoldIn {
+  const float *gamma, *beta;
+  float *mean, *istd;          // of all channels; lo..hi-1 are written by one workgroup
+  const float* part; int T;    // partials of lo..hi-1, [T][hi - lo][3] (T <= kRowStats)
+  int per, tpr;                // pixels and tiles of 64 pixels of a run of tiles (an image, or all pixels)
+  float count;                 // pixels in all
+  int lo, hi;
+  float eps;
+  float2* fold;                // out: folded pairs, by one workgroup
+};
 
 // ---- pieces of the fp32 BN+ReLU backward reduction shared by its own kernel and by the launch
 // that carries it beside the weight gradients (same code, same bits)
