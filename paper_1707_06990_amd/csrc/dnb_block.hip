@@ -674,7 +674,7 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
     for (int l = 1; l <= m; ++l) {
       const size_t f1 = nhwc::bwd_partial1_near(P, c_in(d, l), B);
       if (f1 > p1) p1 = f1;
-      const size_t f = nhwc::wgrad_partial_floats(d.n, c_in(d, l), B, d.h, d.w, 1);
+      const size_t f = nhwc::wgrad_partial_floats(d.n, c_in(d, l), B, d.h, d.w, 1, true);
       if (f > partB) partB = f;
       b->pk[l] = pe;
       pe += nhwc::packed_layer_elems(c_in(d, l), k, B);

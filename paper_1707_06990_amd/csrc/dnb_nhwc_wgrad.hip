@@ -574,9 +574,9 @@ __global__ __launch_bounds__(256) void k_wgrad_sums(SumArgs s1, SumArgs s3) {
 // Workgroups of the 1x1 and of the 3x3.  A split costs a partial of the whole weight tensor: the
 // lower bounds fill the chip, the upper ones apply where a split still has eight tiles (large images,
 // small partials).  Not sharp: lower bounds of 192..512 and 64..256, upper ones of 512..1024 and
-// 256..768 moved the DenseNet-264-shaped step between 16.03 and 16.35 ms; 512 instead of 1024 for the 1x1 takes 27..50 MB
-// of partials from the workspace of the ImageNet-shaped networks.
-constexpr int WG1_MIN = 256, WG1_MAX = 512, WG3_MIN = 128, WG3_MAX = 256, LONG_TILES = 8;
+// 256..768 moved the DenseNet-264-shaped step between 16.03 and 16.35 ms; in the launch of a pair, whose other
+// roles fill the chip too, 512 at most for the 1x1 (a transition's gradient by itself: 260 us with 512, 111 with 1024).
+constexpr int WG1_MIN = 256, WG1_MAX = 1024, WG1_PAIR_MAX = 512, WG3_MIN = 128, WG3_MAX = 256, LONG_TILES = 8;
 
 int splits_for(int tiles, int cols, int lo, int hi) {
   int s = lo / cols, s2 = hi / cols;
@@ -592,7 +592,7 @@ struct Plan1 {
   int mg, gy, gz, S, tps, n;
   size_t lds, floats;
 };
-Plan1 plan1(int P, int cin, int cout) {
+Plan1 plan1(int P, int cin, int cout, int most) {
   Plan1 p{};
   const int mt = (cout + 15) / 16;
   int best = 0;
@@ -603,7 +603,7 @@ Plan1 plan1(int P, int cin, int cout) {
   p.gy = (cin + 63) / 64;
   p.gz = (mt + p.mg - 1) / p.mg;
   const int tiles = (P + 63) / 64;
-  p.S = splits_for(tiles, p.gy * p.gz, WG1_MIN, WG1_MAX);
+  p.S = splits_for(tiles, p.gy * p.gz, WG1_MIN, most);
   p.tps = (tiles + p.S - 1) / p.S;
   p.n = (p.S + 7) / 8 * 8 * p.gy * p.gz;
   p.lds = (size_t)64 * (AP + gpitch(p.mg)) * sizeof(u16);
@@ -654,10 +654,10 @@ SumArgs sum_args(WgradSum* s) {
 // pixel indexes (with a halo) are 32-bit in these kernels
 static bool fits(int n, int h, int w) { return (int64_t)n * h * w < (int64_t)1 << 30; }
 
-size_t wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps) {
+size_t wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool pair) {
   if (!fits(n, h, w)) return 0;
   const int P = n * h * w;
-  if (taps == 1) return plan1(P, cin, cout).floats;
+  if (taps == 1) return plan1(P, cin, cout, pair ? WG1_PAIR_MAX : WG1_MAX).floats;
   const Plan3 p = plan3(P, w, cin, cout);
   return p.ok ? p.floats : 0;
 }
@@ -673,7 +673,7 @@ bool wgrad_fast(const WgradIn& in, bool g_f32, int n, int h, int w, int taps, Wg
   if ((g_f32 && in.fold) || !fits(n, h, w)) return false;
   const int P = n * h * w;
   if (taps == 1) {
-    const Plan1 p = plan1(P, in.cin, in.cout);
+    const Plan1 p = plan1(P, in.cin, in.cout, WG1_MAX);
     const Wg1Args A = args1(p, in, P);
 #define DNB_L(MG)                                                                                                 \
   do {                                                                                                            \
@@ -717,7 +717,7 @@ bool wgrad_pair(const WgradIn& w1, const WgradIn& w3, int n, int h, int w, Wgrad
                 int most_splits, int* T1, hipStream_t st) {
   if (!fits(n, h, w)) return false;
   const int P = n * h * w;
-  const Plan1 p1 = plan1(P, w1.cin, w1.cout);
+  const Plan1 p1 = plan1(P, w1.cin, w1.cout, WG1_PAIR_MAX);
   const Plan3 p3 = plan3(P, w, w3.cin, w3.cout);
   if (!p3.ok || (w1.fold != nullptr) != (w3.fold != nullptr)) return false;
   const Wg1Args A1 = args1(p1, w1, P);
