@@ -27,7 +27,7 @@ namespace {
 
 // VEC: 16-byte loads (W % 4 == 0 and aligned operands).  WN: column groups of 16 lanes per channel row.
 template <int MT, bool VEC, int WN, bool STATS>
-__global__ __launch_bounds__(256, 2) void k_conv3x3_v5(const float* __restrict__ in, int64_t in_stride,
+__global__ __launch_bounds__(512, 2) void k_conv3x3_v5(const float* __restrict__ in, int64_t in_stride,
                                                        const float* __restrict__ Wp, int Mpad, int Kpad,
                                                        float* __restrict__ out, int64_t out_stride, int cin, int cout, int H,
                                                        int W, int wk, float* __restrict__ spart, int sT) {
@@ -204,7 +204,7 @@ bool launch_conv3x3_any(const float* in, int64_t in_stride, const float* packed,
   // M-tiles; else the M-tiles are split, as many per wave as leave a workgroup per CU.
   int nw = 4, wk = 1, mt = 1;
   if (mtiles <= 3 && nchunks >= 2) {
-    wk = nw = nchunks <= 4 ? nchunks : (nchunks % 4 != 0 && nchunks % 3 == 0 && nchunks <= 12 ? 3 : 4);
+    wk = nw = nchunks <= 4 ? nchunks : (nchunks % 4 != 0 && nchunks % 3 == 0 && nchunks <= 9 ? 3 : nchunks < 8 ? 4 : 8);
     mt = mtiles;
   } else {
     if (mtiles < 4) nw = mtiles;
