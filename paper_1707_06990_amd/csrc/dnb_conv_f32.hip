@@ -26,14 +26,14 @@ bool launch_conv_fast(const float* in, int64_t in_stride, const float* packed, f
 bool launch_conv3x3_any(const float* in, int64_t in_stride, const float* packed, float* out, int64_t out_stride, int n,
                         int cin, int cout, int h, int w, float* spart, int* sT, hipStream_t st, hipEvent_t ev0,
                         hipEvent_t ev1);
-size_t conv_wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps);
+size_t conv_wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool alone);
 // Launches the fast weight-gradient kernel if it applies (returns false otherwise).  *own
 // describes the sum of its partials, which is left to the caller; *absorb (may be null or of kind
 // 0) is carried out by extra workgroups of the same launch and cleared.
 bool launch_wgrad_fast(const float* in, int64_t in_stride, const float* g, int64_t g_stride,
                        float* partials, float* dw, int n, int cin, int cout, int h, int w, int taps,
                        const float2* fold, PendingSum* own, PendingSum* absorb, hipStream_t st, hipEvent_t ev0,
-                       hipEvent_t ev1);
+                       hipEvent_t ev1, bool alone);
 hipError_t launch_sum_wgrad3x3(const PendingSum& p, hipStream_t st);
 bool launch_wgrad_pair_fast(const float* in1, int64_t in1_stride, const float* g1, int64_t g1_stride, float* part1,
                             float* dw1, int cin1, const float2* fold1, const float* in3, int64_t in3_stride,
@@ -437,11 +437,11 @@ bool conv3x3_generic_fits(int n, int cin, int cout, int h, int w) {
          plan_wgrad(n, cin, cout, h, w, 9).lds <= 64 * 1024;
 }
 
-size_t conv_wgrad_partial_floats(int n, int cin, int cout, int h, int w, int taps) {
+size_t conv_wgrad_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool alone) {
   const WgradPlan p = plan_wgrad(n, cin, cout, h, w, taps);
   const size_t a = taps == 9 ? (size_t)p.splits * p.grid.y * p.grid.z * p.mtw * p.ctw * 9 * 256
                              : (size_t)p.splits * cin * cout;
-  const size_t b = conv_wgrad_fast_partial_floats(n, cin, cout, h, w, taps);
+  const size_t b = conv_wgrad_fast_partial_floats(n, cin, cout, h, w, taps, alone);
   return a > b ? a : b;
 }
 
@@ -456,13 +456,13 @@ hipError_t launch_pending_sum(PendingSum* p, hipStream_t st) {
 hipError_t launch_conv_wgrad(const float* in, int64_t in_stride, const float* g, int64_t g_stride,
                              float* dw, int n, int cin, int cout, int h, int w, int taps,
                              float* partials, const float2* fold, hipStream_t st, hipEvent_t ev0,
-                             hipEvent_t ev1, bool* used_fast, PendingSum* absorb, PendingSum* defer) {
+                             hipEvent_t ev1, bool* used_fast, PendingSum* absorb, PendingSum* defer, bool alone) {
   if (defer) defer->kind = 0;
   if (cin <= 0 || cout <= 0) return absorb ? launch_pending_sum(absorb, st) : hipSuccess;
   if (used_fast) *used_fast = true;
   PendingSum own;
   if (launch_wgrad_fast(in, in_stride, g, g_stride, partials, dw, n, cin, cout, h, w, taps, fold, &own, absorb, st,
-                        ev0, ev1)) {
+                        ev0, ev1, alone)) {
     if (defer) { *defer = own; return hipGetLastError(); }
     return launch_pending_sum(&own, st);
   }

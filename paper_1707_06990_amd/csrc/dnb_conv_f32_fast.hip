@@ -1565,7 +1565,8 @@ struct WgFastPlan {
   size_t lds;
 };
 
-static WgFastPlan plan_wgrad_fast(int n, int cin, int cout, int h, int w, int taps) {
+// alone: the launch holds nothing else.
+static WgFastPlan plan_wgrad_fast(int n, int cin, int cout, int h, int w, int taps, bool alone = false) {
   WgFastPlan p{};
   const int hw = h * w, mtiles = (cout + 15) / 16, ctiles = (cin + 15) / 16;
   p.ok = hw % 4 == 0 && (taps == 1 || (w % 4 == 0 && w >= 4));
@@ -1584,7 +1585,9 @@ static WgFastPlan plan_wgrad_fast(int n, int cin, int cout, int h, int w, int ta
     // DenseNet-BC-100 step than 128; 96 and 192 were within 0.5 % of 128.
     // With many (m, c) tile columns (wide layers, k = 24 nets) the columns alone fill the chip and the
     // pixel ranges can be longer still: a cap of 64 steps there took 1.2 % off the DenseNet-BC-250 step.
-    int spw = (int)(((int64_t)p.total_steps * p.gy * p.gz + 4 * 128 - 1) / (4 * 128));
+    // By itself (a transition's) nothing else fills the CUs: 512 workgroups.
+    const int wgs = alone ? 512 : 128;
+    int spw = (int)(((int64_t)p.total_steps * p.gy * p.gz + 4 * wgs - 1) / (4 * wgs));
     const int cap = p.gy * p.gz > 8 ? 64 : 16;
     if (spw < 1) spw = 1;
     if (spw > cap) spw = cap;
@@ -1617,8 +1620,8 @@ static WgFastPlan plan_wgrad_fast(int n, int cin, int cout, int h, int w, int ta
   return p;
 }
 
-size_t conv_wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps) {
-  const WgFastPlan p = plan_wgrad_fast(n, cin, cout, h, w, taps);
+size_t conv_wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool alone) {
+  const WgFastPlan p = plan_wgrad_fast(n, cin, cout, h, w, taps, alone);
   if (!p.ok) return 0;
   if (taps == 9) return (size_t)p.gx * p.gy * p.gz * p.mtw * p.ctw * 9 * 256;  // accumulator-order partials
   return (size_t)p.gx * cin * cout;
@@ -1647,9 +1650,9 @@ hipError_t launch_sum_wgrad3x3(const PendingSum& p, hipStream_t st) {
 bool launch_wgrad_fast(const float* in, int64_t in_stride, const float* g, int64_t g_stride,
                        float* partials, float* dw, int n, int cin, int cout, int h, int w, int taps,
                        const float2* fold, PendingSum* own, PendingSum* absorb, hipStream_t st, hipEvent_t ev0,
-                       hipEvent_t ev1) {
+                       hipEvent_t ev1, bool alone) {
   if (in_stride % 4 || g_stride % 4 || !aligned16(in) || !aligned16(g)) return false;
-  const WgFastPlan p = plan_wgrad_fast(n, cin, cout, h, w, taps);
+  const WgFastPlan p = plan_wgrad_fast(n, cin, cout, h, w, taps, alone);
   if (!p.ok) return false;
   SumRole sr{};
   unsigned sx = 0;

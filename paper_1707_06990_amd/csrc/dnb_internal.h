@@ -179,9 +179,9 @@ hipError_t launch_bn_fold(const float* gamma, const float* beta, float* mean, fl
                           float2* fold, hipStream_t st, bool rows = false);
 
 // dW[m][c][t] = sum_{n,q} g[n][m][q] * in[n][c][q + shift(t)]  (OIHW result).
-size_t conv_wgrad_partial_floats(int n, int cin, int cout, int h, int w, int taps);
+size_t conv_wgrad_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool alone = false);
 // partial floats of the fast (16-byte-vector) weight-gradient kernel for this shape, 0 if its tile plan does not fit
-size_t conv_wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps);
+size_t conv_wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool alone = false);
 // A sum of weight-gradient partials that a launch has left for later.  In a chain of weight
 // gradients on one stream the next weight-gradient launch carries it out with extra workgroups
 // (the partials are complete when that launch starts), which saves a launch per layer; what is
@@ -203,7 +203,7 @@ hipError_t launch_conv_wgrad(const float* in, int64_t in_stride, const float* g,
                              float* dw, int n, int cin, int cout, int h, int w, int taps,
                              float* partials, const float2* fold, hipStream_t st, hipEvent_t ev_start = nullptr,
                              hipEvent_t ev_stop = nullptr /*stamped around the fast kernel (not the sum)*/,
-                             bool* used_fast = nullptr, PendingSum* absorb = nullptr, PendingSum* defer = nullptr);
+                             bool* used_fast = nullptr, PendingSum* absorb = nullptr, PendingSum* defer = nullptr, bool alone = false);
 
 // Both weight gradients of a bottleneck layer on one stream: the 1x1 (in1: C_l channels, g1: the
 // gradient of b_l, B channels) and the 3x3 (in3: B channels, g3: the gradient of x_l, k

@@ -385,7 +385,7 @@ int dnb_net_create(const dnb_net_desc* desc, dnb_net** out) {
     need(bn_stats_partial_floats(d.n, (int)co, (int)hw));
     need(bn_bwd_partial_floats(d.n, (int)co, (int)hw));
     if (b < 2) {
-      need(conv_wgrad_partial_floats(d.n, (int)co, (int)(co / 2), bd.h, bd.w, 1));
+      need(conv_wgrad_partial_floats(d.n, (int)co, (int)(co / 2), bd.h, bd.w, 1, true));
       net->o_pack[b] = carve(packed_weight_floats((int)(co / 2), (int)co, 1) * 4 * 2, false, "pack", b);  // forward + transposed
     }
   }
@@ -627,7 +627,7 @@ int dnb_net_backward(dnb_net* net, const void* xv, const void* paramsv, void* dp
                          pd.h, pd.w);
       DNB_TRYH(hipGetLastError());
       DNB_TRYH(launch_conv_wgrad(tzp, (int64_t)cp * hwp, dconv, (int64_t)ch * hwp, dparams + net->p_w[b - 1], n, cp,
-                                 ch, pd.h, pd.w, 1, part, nullptr, st));
+                                 ch, pd.h, pd.w, 1, part, nullptr, st, nullptr, nullptr, nullptr, nullptr, nullptr, true));
       DNB_TRYH(launch_conv_igemm(dconv, (int64_t)ch * hwp, WeightView{W, 1, cp, 0}, pkt, dtz, (int64_t)cp * hwp, n, ch,
                                  cp, pd.h, pd.w, 1, nullptr, st));
     }

@@ -237,11 +237,15 @@ __global__ __launch_bounds__(256) void k_conv(
 
   // PRO: the folded BN (scale, shift) of all input channels is copied to LDS once, behind the two
   // tile buffers (the staging reads it for every vector it transforms)
+  // Inside a chunk pair e of the eight 8-channel vectors lies side by side, [e][v][4]: a thread keeps one vector
+  // per chunk, and its reads at 64-byte strides met on a quarter of the banks.
   float* flds = reinterpret_cast<float*>(lds + 2 * BUFE);  // 2*BUFE*2 bytes is a multiple of 16
+  auto fpos = [](int c) { return ((c >> 1) & 3) * 32 + (c >> 3) * 4 + (c & 1) * 2; };
   if (PRO) {
     for (int i = tid; i < cin; i += 256) {
       const float2 fl = fold[i];
-      flds[2 * i] = fl.x; flds[2 * i + 1] = fl.y;
+      float* o = flds + (i & ~(KC - 1)) * 2 + fpos(i & (KC - 1));
+      o[0] = fl.x; o[1] = fl.y;
     }
     __syncthreads();
   }
@@ -266,11 +270,17 @@ __global__ __launch_bounds__(256) void k_conv(
     }
   };
   auto deposit = [&](int c0, const Raw(&v)[U], int boff) {
+    const int vv = tid & 7, ch = c0 + 8 * vv;
+    float4 fl[4];
+    if (PRO) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) fl[e] = *reinterpret_cast<const float4*>(&flds[2 * c0 + e * 32 + vv * 4]);
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int idx = u * 256 + tid;
       if (idx < nvec) {
-        const int s = idx >> 3, vv = idx & 7, ch = c0 + 8 * vv;
+        const int s = idx >> 3;
         const int64_t q = q0 - halo + s;
         V8 o;
         o.q = make_uint4(0u, 0u, 0u, 0u);
@@ -289,10 +299,9 @@ __global__ __launch_bounds__(256) void k_conv(
           }
           if (PRO) {
 #pragma unroll
-            for (int e = 0; e < 8; e += 2) {  // (scale, shift) pairs from their LDS copy, 16 bytes at a time
-              const float4 fl = *reinterpret_cast<const float4*>(&flds[2 * (ch + e)]);
-              f[e] = fmaxf(__fmaf_rn(f[e], fl.x, fl.y), 0.f);
-              f[e + 1] = fmaxf(__fmaf_rn(f[e + 1], fl.z, fl.w), 0.f);
+            for (int e = 0; e < 4; ++e) {
+              f[2 * e] = fmaxf(__fmaf_rn(f[2 * e], fl[e].x, fl[e].y), 0.f);
+              f[2 * e + 1] = fmaxf(__fmaf_rn(f[2 * e + 1], fl[e].z, fl[e].w), 0.f);
             }
           }
 #pragma unroll
@@ -787,8 +796,8 @@ hipError_t conv(const void* in, int64_t in_ld, bool in_f32, const void* Wp, void
   const int T = (int)ptiles;
   if (sT) *sT = T;
   const int halo = taps == 9 ? w + 1 : 0;
-  const size_t lds = (size_t)2 * (64 + 2 * halo) * 72 * sizeof(u16) + (fold ? (size_t)cin * 8 : 0);
-  if (lds > 64 * 1024 || (taps == 9 && (64 + 2 * halo) * 8 > 8 * 256)) return hipErrorInvalidValue;
+  const size_t lds = (size_t)2 * (64 + 2 * halo) * 72 * sizeof(u16) + (fold ? (size_t)((cin + 63) & ~63) * 8 : 0);
+  if (lds > 64 * 1024 + (fold ? 56 * 8 : 0) || (taps == 9 && (64 + 2 * halo) * 8 > 8 * 256)) return hipErrorInvalidValue;
 #define DNB_K(TAPS, MT, TIN, PRO, STATS)                                                                        \
   hipLaunchKernelGGL((k_conv<TAPS, MT, TIN, PRO, STATS>), grid, dim3(256), lds, st, (const TIN*)in, in_ld, \
                      (const u16*)Wp, M16, K32, (u16*)out, out_ld, cin, cout, h, w, P, fold, spart, T)
