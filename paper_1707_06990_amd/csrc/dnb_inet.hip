@@ -107,71 +107,106 @@ __global__ __launch_bounds__(256) void k_stem_conv7(const u16* __restrict__ x, c
   }
 }
 
-// Stem weight gradient: dW (C, 3, 7, 7) = sum over output pixels of g (n, S/2, S/2, C) bf16 times the
-// input patch.  A workgroup walks over 8x8 output tiles (tile = blockIdx.x, += gridDim.x), staging
-// the tile's gradients and input patch in LDS; a thread keeps 4 channels x TPC taps of the result in
-// registers over all its tiles and stores them into its workgroup's partial, OIHW order
-// ([gridDim.x][C*147] floats, summed afterwards in a fixed order).  C/4 channel quads x 256/(C/4)
-// tap chunks of TPC taps.
-template <int C, int TPC>
+// Stem weight gradient: dW (C, 3, 7, 7) = sum over output pixels of g (n, S/2, S/2, C) bf16 times the input patch:
+// a contraction over pixels of C channels against 147 taps, on the matrix cores (both operands are bf16 as they
+// are stored, sums in fp32).  A workgroup walks over 8x8 output tiles (tile = blockIdx.x, += gridDim.x).  The patch
+// is laid out as a row of taps per pixel, [ky][22] with the 21 (kx, ci) pairs of a row of taps contiguous in the
+// patch too (so it is copied in dwords; the 22nd is a column nobody stores), gradients and taps are then taken with
+// the transposing LDS read as in the block's weight gradients.  Waves split the ten tiles of 16 taps; the next
+// tile's loads are in flight during the products.  Each workgroup's partial in OIHW order ([gridDim.x][C*147]
+// floats, summed afterwards in a fixed order).  67 us for 64 and 80 us for 96 channels at
+// batch 32 (219 and 292 on fp32 vector FMAs, 4 channels x 10 or 15 taps a thread).
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+template <int C>
 __global__ __launch_bounds__(256) void k_stem_wgrad7(const u16* __restrict__ x, const u16* __restrict__ g,
                                                      float* __restrict__ part, int S, int n) {
-  constexpr int QUADS = C / 4, CHUNKS = 256 / QUADS;
-  static_assert(CHUNKS * TPC >= kTaps, "the tap chunks cover all 147 taps");
-  extern __shared__ float lds[];
-  float* gl = lds;                       // [64][C]
-  float* patch = lds + 64 * C;           // [21*21*3]
+  constexpr int MT = C / 16, GP = C == 16 ? 16 : C <= 64 ? 80 : 144;  // 32 or 160 bytes (mod 256): see dnb_nhwc_wgrad.hip
+  constexpr int BP = 212, PP = 90;  // row pitches of the taps (8-byte rows, two lanes a bank) and of the patch
+  constexpr int GU = (64 * C / 8 + 255) / 256, PE = kPatch * kPatch * 3, PU = (PE + 255) / 256;
+  __shared__ __attribute__((aligned(16))) u16 gS[64 * GP];
+  __shared__ __attribute__((aligned(16))) u16 bS[64 * BP];
+  __shared__ __attribute__((aligned(16))) u16 patch[kPatch * PP];
   const int So = S / 2, tiles = So / kTile, per_img = tiles * tiles, total = per_img * n;
-  const int quad = threadIdx.x % QUADS, chunk = threadIdx.x / QUADS;
-  const bool active = chunk < CHUNKS;
-  int off[TPC];
-  bool live[TPC];
-#pragma unroll
-  for (int tt = 0; tt < TPC; ++tt) {
-    const int t = chunk * TPC + tt;        // OIHW tap index (ci*7 + ky)*7 + kx
-    live[tt] = active && t < kTaps;
-    const int tc = live[tt] ? t : 0;
-    const int ci = tc / 49, r = tc - ci * 49, ky = r / 7, kx = r - ky * 7;
-    off[tt] = (ky * kPatch + kx) * 3 + ci;
-  }
-  float4 acc[TPC];
-#pragma unroll
-  for (int tt = 0; tt < TPC; ++tt) acc[tt] = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, grp = lane >> 4;
+  uint4 rg[GU];
+  u16 rp[PU];
+  auto request = [&](int tile) {
     const int img = tile / per_img, r = tile - img * per_img, ty = r / tiles, tx = r - ty * tiles;
-    __syncthreads();  // the previous tile's reads are done
-    stage_patch(x, S, img, ty, tx, patch);
-    for (int i = threadIdx.x; i < 64 * (C / 8); i += 256) {
-      const int p = i / (C / 8), v = i - p * (C / 8);
-      const int oy = ty * kTile + (p >> 3), ox = tx * kTile + (p & 7);
-      V8 raw;
-      raw.q = *reinterpret_cast<const uint4*>(g + (((int64_t)img * So + oy) * So + ox) * C + 8 * v);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) gl[p * C + 8 * v + e] = bf2f(raw.h[e]);
+    for (int u = 0; u < GU; ++u) {
+      const int i = min(tid + 256 * u, 64 * C / 8 - 1), p = i / (C / 8), v = i - p * (C / 8);
+      const int oy = ty * kTile + (p >> 3), ox = tx * kTile + (p & 7);
+      rg[u] = *reinterpret_cast<const uint4*>(g + (((int64_t)img * So + oy) * So + ox) * C + 8 * v);
+    }
+    const int y0 = 2 * ty * kTile - 3, x0 = 2 * tx * kTile - 3;
+#pragma unroll
+    for (int u = 0; u < PU; ++u) {
+      const int i = min(tid + 256 * u, PE - 1), row = i / (kPatch * 3), rem = i - row * (kPatch * 3), q = rem / 3;
+      const int yy = y0 + row, xx = x0 + q;
+      const u16 v = x[(((int64_t)img * S + min(max(yy, 0), S - 1)) * S + min(max(xx, 0), S - 1)) * 3 + rem - 3 * q];
+      rp[u] = yy >= 0 && yy < S && xx >= 0 && xx < S ? v : (u16)0;
+    }
+  };
+  f32x4 acc[3][MT];
+#pragma unroll
+  for (int y = 0; y < 3; ++y)
+#pragma unroll
+    for (int a = 0; a < MT; ++a) acc[y][a] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  if (tid < kPatch) patch[tid * PP + kPatch * 3] = 0;
+  const int row = 4 * grp + ((lane >> 2) & 3), cc = 4 * (lane & 3);
+  auto frag = [&](const u16* lo, int pitch) {  // K index 8*grp + e = pixel 4*grp + e (e < 4) or 16 + 4*grp + e - 4
+    const uint2 a = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)lo));
+    const uint2 b = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(lo + 16 * pitch)));
+    return __builtin_bit_cast(bf16x8, make_uint4(a.x, a.y, b.x, b.y));
+  };
+  request(min((int)blockIdx.x, total - 1));
+  for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
+    __syncthreads();  // the previous tile's reads are done
+#pragma unroll
+    for (int u = 0; u < GU; ++u) {
+      const int i = tid + 256 * u, p = i / (C / 8), v = i - p * (C / 8);
+      if (i < 64 * C / 8) *reinterpret_cast<uint4*>(gS + p * GP + 8 * v) = rg[u];
+    }
+#pragma unroll
+    for (int u = 0; u < PU; ++u) {
+      const int i = tid + 256 * u, r = i / (kPatch * 3);
+      if (i < PE) patch[r * PP + i - r * (kPatch * 3)] = rp[u];
     }
     __syncthreads();
-    if (active) {
-      for (int p = 0; p < 64; ++p) {
-        const float4 g4 = *reinterpret_cast<const float4*>(gl + p * C + 4 * quad);
-        const float* pb = patch + ((2 * (p >> 3)) * kPatch + 2 * (p & 7)) * 3;
+    request(min(tile + (int)gridDim.x, total - 1));
+    for (int ky = wave; ky < 7; ky += 4) {  // lane = pixel
+      const unsigned* src = reinterpret_cast<const unsigned*>(patch + (2 * (lane >> 3) + ky) * PP + 6 * (lane & 7));
+      unsigned* dst = reinterpret_cast<unsigned*>(bS + lane * BP + ky * 22);
 #pragma unroll
-        for (int tt = 0; tt < TPC; ++tt) {
-          const float v = pb[off[tt]];
-          acc[tt].x = __fmaf_rn(g4.x, v, acc[tt].x); acc[tt].y = __fmaf_rn(g4.y, v, acc[tt].y);
-          acc[tt].z = __fmaf_rn(g4.z, v, acc[tt].z); acc[tt].w = __fmaf_rn(g4.w, v, acc[tt].w);
+      for (int d = 0; d < 11; ++d) dst[d] = src[d];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      bf16x8 a[MT];
+#pragma unroll
+      for (int m = 0; m < MT; ++m) a[m] = frag(gS + (ks * 32 + row) * GP + m * 16 + cc, GP);
+#pragma unroll
+      for (int y = 0; y < 3; ++y) {
+        if (wave + 4 * y < 10) {
+          const bf16x8 b = frag(bS + (ks * 32 + row) * BP + (wave + 4 * y) * 16 + cc, BP);
+#pragma unroll
+          for (int m = 0; m < MT; ++m) acc[y][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], b, acc[y][m], 0, 0, 0);
         }
       }
     }
   }
   float* po = part + (int64_t)blockIdx.x * (C * kTaps);
 #pragma unroll
-  for (int tt = 0; tt < TPC; ++tt) {
-    if (live[tt]) {
-      const int t = chunk * TPC + tt;
-      po[(4 * quad + 0) * kTaps + t] = acc[tt].x;
-      po[(4 * quad + 1) * kTaps + t] = acc[tt].y;
-      po[(4 * quad + 2) * kTaps + t] = acc[tt].z;
-      po[(4 * quad + 3) * kTaps + t] = acc[tt].w;
+  for (int y = 0; y < 3; ++y) {
+    const int s = (wave + 4 * y) * 16 + (lane & 15), ky = s / 22, rem = s - ky * 22, kx = rem / 3, ci = rem - 3 * kx;
+    if (s < 154 && rem < 21) {
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) po[(m * 16 + 4 * grp + r) * kTaps + (ci * 7 + ky) * 7 + kx] = acc[y][m][r];
     }
   }
 }
@@ -391,12 +426,11 @@ int stem_wgrad_groups(int n, int S) {
 
 hipError_t launch_stem_wgrad(const u16* x, const u16* g, float* part, float* dW, int n, int S, int C, hipStream_t st) {
   const int G = stem_wgrad_groups(n, S);
-  const size_t lds = ((size_t)64 * C + kPatch * kPatch * 3) * sizeof(float);
   switch (C) {
-    case 16: hipLaunchKernelGGL((k_stem_wgrad7<16, 3>), dim3(G), dim3(256), lds, st, x, g, part, S, n); break;
-    case 32: hipLaunchKernelGGL((k_stem_wgrad7<32, 5>), dim3(G), dim3(256), lds, st, x, g, part, S, n); break;
-    case 64: hipLaunchKernelGGL((k_stem_wgrad7<64, 10>), dim3(G), dim3(256), lds, st, x, g, part, S, n); break;
-    case 96: hipLaunchKernelGGL((k_stem_wgrad7<96, 15>), dim3(G), dim3(256), lds, st, x, g, part, S, n); break;
+    case 16: hipLaunchKernelGGL(k_stem_wgrad7<16>, dim3(G), dim3(256), 0, st, x, g, part, S, n); break;
+    case 32: hipLaunchKernelGGL(k_stem_wgrad7<32>, dim3(G), dim3(256), 0, st, x, g, part, S, n); break;
+    case 64: hipLaunchKernelGGL(k_stem_wgrad7<64>, dim3(G), dim3(256), 0, st, x, g, part, S, n); break;
+    case 96: hipLaunchKernelGGL(k_stem_wgrad7<96>, dim3(G), dim3(256), 0, st, x, g, part, S, n); break;
     default: return hipErrorInvalidValue;
   }
   hipError_t e = hipGetLastError();
