@@ -783,6 +783,166 @@ __global__ __launch_bounds__(256, 2) void k_dgrad3_v4(const float* in, int64_t i
                                                0, tiles_per_img, total_tiles, bw);
 }
 
+// 3x3 data gradient of the backward chain for k = 17 ... 32 and B = 65 ... 128: the persistent form again, with a wave
+// per M-tile.  k_dgrad3_v3 took 32 us a launch on DenseNet-BC-250 (k = 24, B = 96) against 10 us of products: two
+// M-tiles for each of four waves are eight where there are six, k pads to 32, and a tile's loads, products and
+// epilogue follow each other.  Here NW waves hold one M-tile each, all nine taps' weights of 4 NK channels in
+// registers (NK = 6: no products for padding at k = 24), and form all 64 pixels of a tile: four accumulators, an
+// LDS read for each MFMA (2 cycles of the CU's LDS against 8 of its matrix cores).  The tiles are staged and dealt
+// as in conv3x3_v4_body; the sums of a channel stay with one wave.  B <= 64 would leave two of six waves idle.
+// At batch 64, k = 24, B = 96: 41.4 us at 32x32, 13.8 at 16x16, 12.6 at 8x8, 22.6 on average against 31.7; the
+// DenseNet-BC-250 step 38.0 -> 36.9 ms.  Bound by the first tile's loads and the last one's stores: a workgroup has
+// two tiles at most there, and the products alone are 17 us at 32x32.
+template <int NW, int NK, int W>
+__global__ __launch_bounds__(NW * 64, NW == 6 && NK == 6 ? 3 : 2) void k_dgrad3_v5(
+    const float* __restrict__ in, int64_t in_stride, const float* __restrict__ Wp, int Mpad, int Kpad, float* __restrict__ out,
+    int64_t out_stride, int cin, int cout, int H, int tiles_per_img, int total_tiles, Bwd3Args bw) {
+  extern __shared__ float lds[];
+  __shared__ float coef[3][kBwdMaxK];
+  __shared__ float4 cb[NW * 16];
+  constexpr int NT = NW * 64, ROWS = 4 * NK, RW = W + 4, TR = 64 / W, NR = TR + 2, W4 = W / 4, CS = 144;
+  static_assert(NR * RW <= CS, "plane pitch");
+  constexpr int PER_PLANE = NR * W4, TOTAL = ROWS * PER_PLANE, U = (TOTAL + NT - 1) / NT, BUF = ROWS * CS + 4;
+  const int HW = H * W, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j = lane & 15, g = lane >> 4;
+  const int G = gridDim.x, tpx = (total_tiles + 7) >> 3, wgx = G >> 3;
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int t_lo = xcd * tpx, t_hi = min(total_tiles, t_lo + tpx);
+  int tile = t_lo + slot;
+  if (tile >= t_hi) {  // uniform for the workgroup
+    if (tid < cout) bw.part2[(int64_t)tid * bw.T2 + blockIdx.x] = make_float2(0.f, 0.f);
+    return;
+  }
+
+  int sch[U], sry[U], sgo[U], slo[U];  // channel, staged row, offset in the image row, LDS offset
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int idx = min(u * NT + tid, TOTAL - 1);
+    sch[u] = idx / PER_PLANE;
+    const int rem = idx - sch[u] * PER_PLANE;
+    sry[u] = rem / W4;
+    sgo[u] = 4 * (rem - sry[u] * W4);
+    slo[u] = sch[u] * CS + sry[u] * RW + 4 + sgo[u];
+  }
+  float4 xv[U];
+  auto request = [&](int tl, float4(&v)[U]) {
+    const int img = tl / tiles_per_img, y0 = (tl - img * tiles_per_img) * TR;
+    const char *inb = (const char*)(in + (int64_t)img * in_stride), *xb = (const char*)(bw.x + (int64_t)img * bw.x_stride);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const unsigned o = 4u * (unsigned)(min(sch[u], cin - 1) * HW + min(max(y0 - 1 + sry[u], 0), H - 1) * W + sgo[u]);
+      v[u] = *reinterpret_cast<const float4*>(inb + o);
+      if (bw.K) xv[u] = *reinterpret_cast<const float4*>(xb + o);
+    }
+  };
+  auto deposit = [&](int tl, const float4(&v)[U], int boff) {
+    const int img = tl / tiles_per_img, y0 = (tl - img * tiles_per_img) * TR;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int y = y0 - 1 + sry[u];
+      const bool mine = u * NT + tid < TOTAL;
+      float4 x = v[u];
+      if (bw.K) {
+        const int rc = min(sch[u], cin - 1);
+        x = bwd_corr4(x, xv[u], coef[0][rc], coef[1][rc], coef[2][rc]);
+        if (sch[u] < cin && sry[u] >= 1 && sry[u] <= TR && mine)  // the tile's own rows (H % TR == 0)
+          *reinterpret_cast<float4*>((char*)(bw.gl + (int64_t)img * bw.gl_stride) + 4u * (unsigned)(sch[u] * HW + y * W + sgo[u])) = x;
+      }
+      if (!(sch[u] < cin && y >= 0 && y < H)) x = zero4();
+      if (mine) *reinterpret_cast<float4*>(&lds[boff + slo[u]]) = x;
+    }
+  };
+
+  float4 v0[U];
+  request(tile, v0);
+  float w[9][NK];
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int ci = 0; ci < (NK + 3) / 4; ++ci) {  // Kpad = 32: both chunks are there
+      const float4 f = ldg4(wfrag(Wp + (int64_t)t * Mpad * Kpad, Kpad, min(wave, (Mpad >> 4) - 1), ci));
+#pragma unroll
+      for (int ks = 0; ks < 4 && 4 * ci + ks < NK; ++ks) w[t][4 * ci + ks] = elem(f, ks);
+    }
+  for (int i = tid; i < 2 * BUF / 4; i += NT) *reinterpret_cast<float4*>(&lds[4 * i]) = zero4();
+  if (bw.K) bwd_coefs(bw, cin, coef);
+  if (tid < NW * 16) {
+    const int m = min(tid, cout - 1);
+    float sc, sf;
+    bn_fold(bw.g2[m], bw.b2[m], bw.mean_b[m], bw.istd_b[m], sc, sf);
+    cb[tid] = make_float4(sc, sf, bw.mean_b[m], bw.istd_b[m]);
+  }
+  float2 bs[4];  // this lane's part of BN2's sums
+#pragma unroll
+  for (int r = 0; r < 4; ++r) bs[r] = make_float2(0.f, 0.f);
+  __syncthreads();  // zero fill and coefficients done before the first rows land
+  deposit(tile, v0, 0);
+  __syncthreads();
+
+  // pixel 16 t + j: a compile-time offset from pixel j (plane g, staged row 1 + j / W, column 4 + j % W)
+  const int lane_base = g * CS + (j / W + 1) * RW + 4 + (j % W);
+  const int m0 = wave * 16 + 4 * g;
+  unsigned ro[4];  // bytes from the image to pixel j of this lane's rows (hw <= 2^20)
+#pragma unroll
+  for (int r = 0; r < 4; ++r) ro[r] = 4u * (unsigned)(min(m0 + r, cout - 1) * HW + j);
+  for (int it = 0; tile < t_hi; ++it, tile += wgx) {
+    const int boff = (it & 1) * BUF, nxt = tile + wgx;
+    const bool more = nxt < t_hi;
+    const int img = tile / tiles_per_img, q = (tile - img * tiles_per_img) * 64;
+    float braw[4][4];
+    const char* bb = (const char*)(bw.b + (int64_t)img * bw.b_stride + q);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) braw[t][r] = *reinterpret_cast<const float*>(bb + ro[r] + 64 * t);
+    float4 vn[U];
+    if (more) request(nxt, vn);
+
+    f32x4 acc[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    // operands two steps ahead of their products, held there by scheduling barriers (left alone, the compiler reads
+    // two values, waits for them and multiplies, or takes 100 registers for the reads of all taps)
+    float b[3][4];
+    auto operands = [&](int s, float(&o)[4]) {
+      const int t9 = s / NK, kk = s % NK;
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        o[t] = lds[boff + lane_base + 4 * kk * CS + (t9 / 3 - 1 + 16 * t / W) * RW + t9 % 3 - 1 + 16 * t % W];
+    };
+    operands(0, b[0]);
+    operands(1, b[1]);
+#pragma unroll
+    for (int s = 0; s < 9 * NK; ++s) {
+      if (s + 2 < 9 * NK) operands(s + 2, b[(s + 2) % 3]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc[t] = mfma16(w[s / NK][s % NK], b[s % 3][t], acc[t]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+
+    char* ob = (char*)(out + (int64_t)img * out_stride + q);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float4 f = cb[m0 + r];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const float v = __fmaf_rn(braw[t][r], f.x, f.y) > 0.f ? acc[t][r] : 0.f;
+        bs[r].x += v;
+        bs[r].y = __fmaf_rn(v, braw[t][r] - f.z, bs[r].y);
+        if (m0 + r < cout) *reinterpret_cast<float*>(ob + ro[r] + 64 * t) = v;
+      }
+    }
+    if (more) deposit(nxt, vn, ((it & 1) ^ 1) * BUF);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const float u = row16_sum(bs[r].x), v = row16_sum(bs[r].y);
+    if (j == 0 && m0 + r < cout) bw.part2[(int64_t)(m0 + r) * bw.T2 + blockIdx.x] = make_float2(u, v * cb[m0 + r].w);
+  }
+}
+
 // A pending sum of partials carried out by extra workgroups of a weight-gradient launch (the
 // workgroups with blockIdx.x >= gx_main): kind 1 is k_sum_partials' job, kind 2 k_sum_wgrad3x3's,
 // with the same grouping and order of additions, so the sums have the same bits either way.
@@ -1493,6 +1653,7 @@ bool launch_conv_fast(const float* in, int64_t in_stride, const float* packed, f
 
 struct Bwd3Plan {
   bool v4;
+  int v5;  // waves of k_dgrad3_v5, or 0
   int mt, nw, gy, CS, T2;
   size_t lds;
 };
@@ -1504,6 +1665,13 @@ static Bwd3Plan plan_bwd3(int n, int h, int w, int k, int B) {
     const int64_t tiles = (int64_t)(hw / 64) * n;
     p.T2 = tiles < kV4Workgroups ? (int)(tiles + 7) / 8 * 8 : kV4Workgroups;
     p.lds = ((size_t)2 * (16 * 144 + 4)) * sizeof(float);
+    return p;
+  }
+  if (mtiles > 4 && mtiles <= 8 && k > 16 && k <= 32 && (w == 8 || w == 16 || w == 32) && hw % 64 == 0 && hw <= 1 << 20) {
+    const int64_t tiles = (int64_t)(hw / 64) * n;
+    p.v5 = mtiles <= 6 ? 6 : 8;
+    p.T2 = tiles < kV4Workgroups ? (int)(tiles + 7) / 8 * 8 : kV4Workgroups;
+    p.lds = ((size_t)2 * ((k <= 24 ? 24 : 32) * 144 + 4)) * sizeof(float);
     return p;
   }
   p.nw = mtiles >= 4 ? 4 : mtiles;
@@ -1543,6 +1711,19 @@ hipError_t bwd32_dgrad3(const Bwd32Layer& L, int* T2, hipStream_t st) {
   hipLaunchKernelGGL((k_dgrad3_v4<WW>), grid, dim3(256), p.lds, st, in, L.ys, L.pk3t, M16, K16, L.db, A.b_stride, L.k,  \
                      L.B, L.h, tpi, tpi * L.n, A)
     if (L.w == 32) DNB_L(32); else if (L.w == 16) DNB_L(16); else DNB_L(8);
+#undef DNB_L
+    return hipGetLastError();
+  }
+  if (p.v5) {
+    const int tpi = hw / 64;
+    const dim3 grid((unsigned)p.T2);
+#define DNB_L(NW, NK, WW)                                                                                               \
+  hipLaunchKernelGGL((k_dgrad3_v5<NW, NK, WW>), grid, dim3(NW * 64), p.lds, st, in, L.ys, L.pk3t, M16, K16, L.db,        \
+                     A.b_stride, L.k, L.B, L.h, tpi, tpi * L.n, A)
+#define DNB_LW(NW, NK) do { if (L.w == 32) DNB_L(NW, NK, 32); else if (L.w == 16) DNB_L(NW, NK, 16); else DNB_L(NW, NK, 8); } while (0)
+    if (p.v5 == 6) { if (L.k <= 24) DNB_LW(6, 6); else DNB_LW(6, 8); }
+    else { if (L.k <= 24) DNB_LW(8, 6); else DNB_LW(8, 8); }
+#undef DNB_LW
 #undef DNB_L
     return hipGetLastError();
   }

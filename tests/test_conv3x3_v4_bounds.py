@@ -134,3 +134,72 @@ def test_every_access_of_the_persistent_3x3_kernel_is_in_bounds(n, cin, cout, H,
     bad, lds_bytes = check(n, cin, cout, H, W, label, sample)
     assert bad == 0
     assert lds_bytes <= 64 * 1024
+
+
+def check_wave_per_m_tile(n, cin, cout, H, W):
+    """k_dgrad3_v5: NW waves of one M-tile each over the 64 pixels of a tile, 4*NK staged channels."""
+    HW=H*W; M16=(cout+15)//16*16; K16=(cin+15)//16*16; NW=6 if M16<=96 else 8; NK=6 if cin<=24 else 8
+    assert 64<cout<=128 and 16<cin<=32 and W in (8,16,32) and HW%64==0
+    NT=NW*64; ROWS=4*NK; RW=W+4; TR=64//W; NR=TR+2; W4=W//4; CS=144; PER=NR*W4; TOTAL=ROWS*PER; U=(TOTAL+NT-1)//NT
+    BUF=ROWS*CS+4; assert NR*RW<=CS and 2*BUF%4==0
+    tpi=HW//64; total=tpi*n; G=(total+7)//8*8 if total<512 else 512; tpx=(total+7)>>3
+    staged={}; written={}; gl={}; part={}; done=set()
+    for b in range(G):
+        tile=(b&7)*tpx+(b>>3); t_hi=min(total,(b&7)*tpx+tpx)
+        if tile>=t_hi:
+            for m in range(min(cout,NT)): part[m*G+b]=part.get(m*G+b,0)+1
+            continue
+        for wave in range(NW):
+            for lane in range(64):
+                for r in range(4):
+                    m=wave*16+4*(lane>>4)+r
+                    if lane&15==0 and m<cout: part[m*G+b]=part.get(m*G+b,0)+1
+        while tile<t_hi:
+            assert tile not in done; done.add(tile)
+            img=tile//tpi; y0=(tile-img*tpi)*TR; first=b==0 and len(done)==1
+            for tid in range(NT):
+                for u in range(U):
+                    idx=min(u*NT+tid,TOTAL-1); sch=idx//PER; rem=idx-sch*PER; sry=rem//W4; sgo=4*(rem-sry*W4)
+                    slo=sch*CS+sry*RW+4+sgo
+                    assert 0<=slo and slo+3<BUF-4 and slo%4==0
+                    o=min(sch,cin-1)*HW+min(max(y0-1+sry,0),H-1)*W+sgo
+                    assert 0<=o and o+3<cin*HW
+                    if u*NT+tid<TOTAL:
+                        if first:
+                            for e in range(4): staged[slo+e]=(sch,sry-1,sgo+e)
+                        if sch<cin and 1<=sry<=TR:
+                            q=(img*cin+sch)*HW+(y0-1+sry)*W+sgo
+                            gl[q]=gl.get(q,0)+1
+            for wave in range(NW):
+                mt=min(wave,(M16>>4)-1)
+                for lane in range(64):
+                    j=lane&15; g=lane>>4; base=g*CS+(j//W+1)*RW+4+j%W
+                    if first:
+                        for t9 in range(9):
+                            for kk in range(NK):
+                                wa=wfrag(K16,mt,kk//4,lane)+kk%4
+                                assert wa<M16*K16 and wunfrag(wa,K16)==(mt*16+j,4*kk+g)
+                                for t in range(4):
+                                    l=base+4*kk*CS+(t9//3-1+16*t//W)*RW+t9%3-1+16*t%W
+                                    assert 0<=l<BUF
+                                    p=16*t+j; y=p//W+t9//3-1; x=p%W+t9%3-1  # the tap's row and column
+                                    assert staged.get(l)==((4*kk+g,y,x) if 0<=x<W else None)
+                    for r in range(4):
+                        m=wave*16+4*g+r
+                        assert min(m,cout-1)*HW+(tile-img*tpi)*64+48+j<cout*HW
+                        if m<cout:
+                            for t in range(4):
+                                o=(img*cout+m)*HW+(tile-img*tpi)*64+16*t+j
+                                written[o]=written.get(o,0)+1
+            tile+=G>>3
+    assert done==set(range(total))
+    assert len(written)==n*cout*HW and all(v==1 for v in written.values())
+    assert sorted(gl)==list(range(0,n*cin*HW,4)) and all(v==1 for v in gl.values())
+    assert sorted(part)==list(range(cout*G)) and all(v==1 for v in part.values())
+    return 2*BUF*4+3*128*4+NW*16*16
+
+
+@pytest.mark.parametrize("n,cin,cout,H,W", [(1, 24, 96, 32, 32), (3, 24, 96, 8, 8), (5, 17, 65, 8, 16), (1, 32, 128, 4, 16),
+                                            (2, 25, 100, 16, 8), (1, 20, 81, 2, 32), (36, 24, 72, 32, 32)])
+def test_every_access_of_the_wave_per_m_tile_form_is_in_bounds(n, cin, cout, H, W):
+    assert check_wave_per_m_tile(n, cin, cout, H, W) <= 80 * 1024  # two workgroups a CU

@@ -294,6 +294,18 @@ def test_layers_in_pairs_match_oracle(dnb, oracle, cfg, schedule):
     compare_with_kernel_decisions(dnb, oracle, cfg, x0, lp, dy, schedule=schedule)
 
 
+# the 3x3 data gradient with a wave per M-tile (17 <= k <= 32, 64 < B <= 128): six and eight waves, six and eight
+# K-steps, each width, ranges of channels that end inside a tile, fewer tiles than XCDs, several tiles a workgroup
+WAVES = [wl.BlockCfg(2, 30, 8, 8, 3, 17, 65), wl.BlockCfg(3, 24, 16, 16, 3, 24, 96), wl.BlockCfg(2, 20, 8, 16, 3, 28, 100),
+         wl.BlockCfg(2, 24, 4, 32, 3, 20, 81), wl.BlockCfg(5, 64, 16, 8, 2, 32, 128), wl.BlockCfg(66, 24, 32, 32, 2, 24, 72)]
+
+
+@pytest.mark.parametrize("cfg", WAVES, ids=lambda c: f"n{c.n}c{c.c0}h{c.h}w{c.w}k{c.growth}B{c.bottleneck}")
+def test_3x3_data_gradient_with_a_wave_per_m_tile_matches_oracle(dnb, oracle, cfg):
+    x0, lp, dy = wl.make_block_inputs(cfg, affine="random")
+    compare_with_kernel_decisions(dnb, oracle, cfg, x0, lp, dy, schedule=2)
+
+
 @pytest.mark.parametrize("which", ["config2", "config3"])
 def test_backward_is_exactly_linear_in_dy_at_full_size(dnb, which):
     """A property that needs no oracle and holds at any size: every step of the backward pass is
