@@ -82,7 +82,11 @@ typedef struct {
  *   fused schedule    : stored = (m*B + m*k) P s        shared = 0
  *   store-all schedule: stored = (2 sum_l C_l + m(2B + k)) P s   shared = 0
  *   both              : grad   = (C_out + C_m + B) P s
- *   peak = stored + shared + grad.
+ *   peak = stored + shared + grad
+ * (DNB_BF16: the slab of C_out channels inside grad is fp32).  A backward pass that takes layers in
+ * pairs keeps a second gradient of a b_l, (B P s), inside the C_m part of grad, of which it needs only
+ * k channels for itself; blocks whose C_m part has no room for it run one layer at a time, so no
+ * feature map lies outside the peak.
  * `stored` counts the m*k channels x_1..x_m although they live inside the
  * caller's output y (they are conv feature maps the method keeps; Section 4). */
 typedef struct {
@@ -91,8 +95,9 @@ typedef struct {
   uint64_t grad_bytes;        /* gradient slab G (C_out) + the two shared gradient scratch maps */
   uint64_t peak_bytes;        /* sum of the three lines above: the feature-map memory           */
   uint64_t stats_bytes;       /* cached fp32 per-channel BN mean and 1/sqrt(var+eps)            */
-  uint64_t scratch_bytes;     /* reduction partials and packed weights, as far as they are not in the
-                                 part of the gradient scratch that the backward pass leaves free  */
+  uint64_t scratch_bytes;     /* reduction partials and packed weights (no feature maps), as far as they
+                                 are not in the part of the gradient scratch that the backward pass
+                                 leaves free (in bf16 a pair's second gradient goes there first)  */
   uint64_t workspace_bytes;   /* what the caller must allocate: everything above that lives in
                                  the workspace, plus alignment padding                          */
 } dnb_block_memory;

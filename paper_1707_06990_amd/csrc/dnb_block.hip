@@ -22,9 +22,13 @@ struct dnb_block {
   size_t off_stat_y;                         // mean[C_out], istd[C_out]
   std::vector<size_t> off_stat_b;            // per layer mean[B], istd[B]
   std::vector<size_t> off_fold1, off_fold2;  // fused schedule: per layer folded (scale, shift) of BN1 / BN2
-  size_t off_part;                           // reduction partials of the main chain (BN)
-  size_t off_K, off_db2, part1_floats, near_floats, stat_floats;                // backward: K0, K1 per channel; a second db (pairs of layers); where BN2's
-                                             // partials, a slice's own BN1 sums start in off_part
+  size_t off_part, off_bwd;                  // reduction partials of the main chain (BN), of the merged backward chains'
+  size_t off_K;                              // backward: K0, K1 per channel
+  bool pairs;                                // the merged backward chain takes layers in pairs ...
+  size_t off_db2;                            // ... and keeps a second gradient of a b_l here
+  size_t part1_floats, near_floats;          // where BN2's partials, a slice's own BN1 sums start in off_bwd
+  size_t stat_floats;                        // fused bf16 forward: a second buffer of statistics' partials so far into
+                                             // off_part, or (0) at off_G
   size_t off_partA[2], off_partB[2];         // partials of the 3x3 / 1x1 weight gradients, layer l's in [l & 1]
   // with concurrency on, the fp32 backward with separate BN passes runs three chains: the data-gradient
   // chain on the caller's stream and the two weight-gradient chains on these helper streams (created at
@@ -158,7 +162,7 @@ int forward_bf16(dnb_block* b, const void* x0, const float* params, void* yv, ch
   unsigned short* y = (unsigned short*)yv;
   float* mean_y = (float*)(ws + b->off_stat_y);
   float* istd_y = mean_y + cout;
-  float* const part0 = (float*)(ws + b->off_part);
+  float *const part0 = (float*)(ws + b->off_part), *const part1 = b->stat_floats ? part0 + b->stat_floats : (float*)(ws + b->off_G);
   float* part = part0;
   unsigned short* pack = (unsigned short*)(ws + b->off_pack);
   const size_t B16 = (size_t)((B + 15) & ~15), k16 = (size_t)((k + 15) & ~15), B32 = (size_t)((B + 31) & ~31);
@@ -180,10 +184,10 @@ int forward_bf16(dnb_block* b, const void* x0, const float* params, void* yv, ch
     const unsigned short* pk3 = pk1 + B16 * c32 + c16 * B32;       // 3x3 forward
     int T1 = 0, T3 = 0;
     const bool fused = d.schedule == DNB_SCHED_FUSED;
-    // few pixels: the convolutions fold the BN they apply themselves (its partials from one half of the buffer, their
-    // own to the other); else k_bn_fold does
+    // few pixels: the convolutions fold the BN they apply themselves (its partials from one buffer, their own to the
+    // other); else k_bn_fold does
     const FoldIn F1{p.g1, p.b1, mean_y, istd_y, part, freshT, (int)b->hw, freshT / n, (float)P, fresh_lo, fresh_hi, d.eps, fold1};
-    float* const next = part == part0 ? part0 + b->stat_floats : part0;
+    float* const next = part == part0 ? part1 : part0;
     const bool rows = l > 1 && freshT <= kRowStats;  // (the block input's partials come from k_stats_partial)
     const bool in1 = fused && rows && nhwc::conv1_stats(y, cout, pk1, bl, B, P, c, B, fold1, next, &T1, &F1, st);
     if (in1) { DNB_TRY(hipGetLastError()); part = next; }
@@ -191,7 +195,7 @@ int forward_bf16(dnb_block* b, const void* x0, const float* params, void* yv, ch
     if (fused) {
       if (!in1) DNB_TRY(nhwc::conv(y, cout, false, pk1, bl, B, n, c, B, d.h, d.w, 1, fold1, part, &T1, st));
       const FoldIn F2{p.g2, p.b2, mean_b, istd_b, part, T1, (int)P, T1, (float)P, 0, B, d.eps, fold2};
-      float* const next3 = part == part0 ? part0 + b->stat_floats : part0;
+      float* const next3 = part == part0 ? part1 : part0;
       if (nhwc::conv3_stats(bl, B, pk3, y + c, cout, n, B, k, d.h, d.w, fold2, next3, &T3, &F2, st)) {
         DNB_TRY(hipGetLastError());
         part = next3;
@@ -270,13 +274,13 @@ int backward_bf16(dnb_block* b, const void* yv, const void* dy, void* dx0, float
   L.db = ws + b->off_dS3;
   L.mean_y = (const float*)(ws + b->off_stat_y);
   L.istd_y = L.mean_y + cout;
-  float* part1 = (float*)(ws + b->off_part);
+  float* part1 = (float*)(ws + b->off_bwd);
   float2* near_part = (float2*)(part1 + b->near_floats);
   L.part2 = part1 + b->part1_floats;
   L.K = (float2*)(ws + b->off_K);
-  // Layers in pairs (upper, lower) from the top, an odd bottom layer by itself: see dnb_nhwc_bwd.hip.  Very wide
-  // bottlenecks one layer at a time, the 1x1 data gradient in a launch of its own.
-  const bool pairs = B <= nhwc::kDgrad1MaxB;
+  // Layers in pairs (upper, lower) from the top, an odd bottom layer by itself: see dnb_nhwc_bwd.hip.  One at a time
+  // without room for a second db, and with very wide bottlenecks, the 1x1 data gradient then in a launch of its own.
+  const bool carried = B <= nhwc::kDgrad1MaxB, pairs = b->pairs;
   void* const dbs[2] = {ws + b->off_dS3, ws + b->off_db2};
   nhwc::Dgrad1In far{};  // the pair's channels below both layers
   far.mean = L.mean_y; far.istd = L.istd_y;
@@ -312,7 +316,7 @@ int backward_bf16(dnb_block* b, const void* yv, const void* dy, void* dx0, float
     nhwc::Dgrad1In d1 = far;
     nhwc::BwdSums S{};
     int most = nhwc::bwd_far_splits();
-    if (pairs) {
+    if (carried) {
       const int at = lower ? 1 : 0;
       far.db[at] = L.db; far.W[at] = L.pk1t; far.C16[at] = (int)c16; far.fold1[at] = L.fold1;
       d1 = far;
@@ -335,7 +339,7 @@ int backward_bf16(dnb_block* b, const void* yv, const void* dy, void* dx0, float
       S.part[0] = (const float2*)part1; S.fold1[0] = L.fold1; S.dgamma[0] = gp.g1; S.dbeta[0] = gp.b1;
       DNB_TRY(nhwc::bwd_dgrad1(L, (float2*)part1, &S.T, st));
     }
-    if (pairs) {  // the second layer's partials behind the first's
+    if (carried) {  // the second layer's partials behind the first's
       int ppw;
       d1.part[1] = d1.part[0] + (size_t)S.width * nhwc::dgrad1_splits(P, S.width, most, &ppw);
       S.part[0] = d1.part[0]; S.part[1] = d1.part[1];
@@ -374,10 +378,11 @@ int backward_f32(dnb_block* b, const float* params, const float* y, const float*
   L.G = (float*)(ws + b->off_G);
   L.gl = (float*)(ws + b->off_dS2);  // the gradient of storage 2 is consumed where it is formed: its storage holds g_l
   L.mean_y = mean_y; L.istd_y = istd_y;
-  L.part1 = (float2*)(ws + b->off_part);
-  L.part2 = (float2*)((float*)(ws + b->off_part) + b->part1_floats);
+  L.part1 = (float2*)(ws + b->off_bwd);
+  L.part2 = (float2*)((float*)(ws + b->off_bwd) + b->part1_floats);
   L.K = (float2*)(ws + b->off_K);
-  // Where the slab is large, layers go in pairs (upper, lower) that share the pass over it: see dnb_bwd_f32.hip.
+  // Where the slab is large and there is room for a second db, layers go in pairs (upper, lower) that share the pass
+  // over it: see dnb_bwd_f32.hip.
   float* const dbs[2] = {(float*)(ws + b->off_dS3), (float*)(ws + b->off_db2)};
   bool lower = false;  // this layer is the lower one of a pair
   PendingSum pendA, pendB;
@@ -391,7 +396,7 @@ int backward_f32(dnb_block* b, const float* params, const float* y, const float*
     const float* bl = (const float*)(ws + b->off_b[l]);
     float* mean_b = (float*)(ws + b->off_stat_b[l]);
     const size_t c16 = (size_t)((c + 15) & ~15);
-    const bool upper = !lower && l > 1 && bwd32_pair_ok(n, hw, c - k, B);
+    const bool upper = b->pairs && !lower && l > 1 && bwd32_pair_ok(n, hw, c - k, B);
     L.c = c;
     L.last = l == m;
     L.lo = upper ? c - k : 0; L.cw = c;
@@ -516,7 +521,7 @@ int backward_plain3x3(dnb_block* b, const float* params, const float* y, const f
 // the start of that workspace) at which the block is to look for it instead.
 size_t dnb::block_tail_offset(const dnb_block* b) { return b->off_tail; }
 void dnb::block_move_tail(dnb_block* b, size_t to) {
-  for (size_t* o : {&b->off_part, &b->off_partA[0], &b->off_partA[1], &b->off_partB[0], &b->off_partB[1], &b->off_K, &b->off_db2})
+  for (size_t* o : {&b->off_part, &b->off_bwd, &b->off_partA[0], &b->off_partA[1], &b->off_partB[0], &b->off_partB[1], &b->off_K})
     if (*o >= b->off_tail) *o = *o - b->off_tail + to;
   b->off_tail = to;
 }
@@ -660,51 +665,22 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
     }
   }
 
-  size_t part = 0, partA = 0, partB = 0;
+  size_t part = 0, bwd = 0, partA = 0, partB = 0;
   auto need = [&](size_t floats) { if (floats > part) part = floats; };
   b->pk.assign(m + 2, 0);
   size_t pack = 0;  // in floats
   if (bf16) {
-    need(nhwc::stats_partial_floats(P, d.c0));
-    need(nhwc::conv_stats_partial_floats(d.n, B, d.h, d.w));
-    need(nhwc::conv_stats_partial_floats(d.n, k, d.h, d.w));
-    b->stat_floats = align_up(part, 4);
-    if (d.schedule == DNB_SCHED_FUSED) need(2 * b->stat_floats);  // two halves: see forward_bf16
-    size_t pe = 0, p1 = 0;  // pe: bf16 elements
+    size_t pe = 0;  // bf16 elements
     for (int l = 1; l <= m; ++l) {
-      const size_t f1 = nhwc::bwd_partial1_near(P, c_in(d, l), B);
-      if (f1 > p1) p1 = f1;
       const size_t f = nhwc::wgrad_partial_floats(d.n, c_in(d, l), B, d.h, d.w, 1, true);
       if (f > partB) partB = f;
       b->pk[l] = pe;
       pe += nhwc::packed_layer_elems(c_in(d, l), k, B);
     }
-    b->near_floats = p1;
-    p1 += nhwc::bwd_partial1_floats(P, k, k, B) - nhwc::bwd_partial1_near(P, k, B);
-    b->part1_floats = p1;
-    need(p1 + nhwc::bwd_partial2_floats(d.n, d.h, d.w, k, B));
     partA = nhwc::wgrad_partial_floats(d.n, B, k, d.h, d.w, 9);
     pack = (pe + 1) / 2;
   } else {
-    need(bn_stats_partial_floats(d.n, d.c0, (int)hw));
-    need(bn_stats_partial_floats(d.n, k, (int)hw));
-    if (B > 0) {
-      need(bn_stats_partial_floats(d.n, B, (int)hw));
-      need(bn_bwd_partial_floats(d.n, B, (int)hw));
-      need(conv_stats_partial_floats(d.n, B, d.h, d.w));  // epilogue statistics of the two convs
-    }
-    need(conv_stats_partial_floats(d.n, k, d.h, d.w));
-    if (B > 0 && bwd32_ok(d.n, d.h, d.w, k, B)) {
-      size_t p1 = bwd32_partial1_near_floats(d.n, (int)hw, k);
-      for (int l = 1; l <= m; ++l) {
-        const size_t f1 = bwd32_partial1_floats(d.n, (int)hw, c_in(d, l));
-        if (f1 > p1) p1 = f1;
-      }
-      b->part1_floats = p1;
-      need(p1 + bwd32_partial2_floats(d.n, d.h, d.w, k, B));
-    }
     for (int l = 1; l <= m; ++l) {
-      need(bn_bwd_partial_floats(d.n, c_in(d, l), (int)hw));
       const size_t f = B > 0 ? block_wgrad_partial_floats(d, c_in(d, l), B, 1) : 0;
       if (f > partB) partB = f;
     }
@@ -720,38 +696,108 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
       for (int l = 1; l <= m; ++l) { b->pk[l] = pack; pack += packed_layer_floats(c_in(d, l), k, B); }
     }
   }
+
   // The merged backward chains keep only the k channels of g_l in the gradient scratch of storage 2 (the
   // 1x1 data gradient is consumed where it is formed): the rest of it holds what a backward pass needs and
   // nothing else does, as far as there is room.
+  const bool merged = bf16 || (B > 0 && bwd32_ok(d.n, d.h, d.w, k, B));
   size_t hole = 0, hole_end = 0;
-  if (bf16 || (B > 0 && bwd32_ok(d.n, d.h, d.w, k, B))) {
+  if (merged) {
     hole = align_up(b->off_dS2 + (size_t)k * Ps, 256);
     hole_end = b->off_dS2 + (size_t)b->cm * Ps;
   }
-  size_t scratch = 0;
-  auto carve_scratch = [&](size_t floats, bool backward_only) {
-    const size_t bytes = floats * sizeof(float);
-    if (backward_only && hole < hole_end && bytes <= hole_end - hole) {
-      const size_t o = hole;
-      hole = align_up(hole + bytes, 256);
-      return o;
+  auto in_hole = [&](size_t& at, size_t bytes) {
+    if (at >= hole_end || bytes > hole_end - at) return false;
+    at = align_up(at + bytes, 256);
+    return true;
+  };
+  // Partial sums of the weight gradients: with a bottleneck two buffers each, used alternately by consecutive layers
+  // (a layer's partials are summed by extra workgroups of the next layer's weight-gradient launch).  Of the 3x3's
+  // and the 1x1's as many in the hole as fill it best.
+  const size_t bytesA = partA * 4, bytesB = partB * 4, buffers = B > 0 ? 2 : 1;
+  struct Fill { size_t a, b, bytes; };
+  auto fill = [&](size_t from) {
+    Fill best{0, 0, 0};
+    for (size_t a = 0; a <= buffers; ++a)
+      for (size_t c = 0; c <= buffers; ++c) {
+        size_t at = from;
+        bool ok = true;
+        for (size_t i = 0; i < a; ++i) ok = ok && in_hole(at, bytesA);
+        for (size_t i = 0; i < c; ++i) ok = ok && in_hole(at, bytesB);
+        if (ok && a * bytesA + c * bytesB >= best.bytes) best = Fill{a, c, a * bytesA + c * bytesB};
+      }
+    return best;
+  };
+  // First of it the second db of layers in pairs, a feature-map gradient like the first: the peak counts none
+  // outside the gradient scratch, so without room for it there layers go one at a time.  In fp32, where pairs save
+  // a few per cent, also where it would push partial sums out (a DenseNet-BC-100 of 48x48 images took 3.6 % more
+  // workspace); in bf16 (10 % and more of a step) partial sums give way.
+  b->pairs = merged && m > 1 && (bf16 ? B <= nhwc::kDgrad1MaxB : bwd32_pair_ok(d.n, (int)hw, c_in(d, m - 1), B));
+  if (b->pairs) {
+    size_t at = hole;
+    b->off_db2 = hole;
+    b->pairs = in_hole(at, (size_t)B * Ps) && (bf16 || fill(at).bytes == fill(hole).bytes);
+    if (b->pairs) hole = at;
+  }
+
+  if (bf16) {
+    need(nhwc::stats_partial_floats(P, d.c0));
+    need(nhwc::conv_stats_partial_floats(d.n, B, d.h, d.w));
+    need(nhwc::conv_stats_partial_floats(d.n, k, d.h, d.w));
+    // the fused forward's second buffer: in the slab, which only the backward pass uses (images of a few pixels, whose
+    // partials outgrow it: behind the first)
+    b->stat_floats = d.schedule == DNB_SCHED_FUSED && part > (size_t)cout * P ? align_up(part, 4) : 0;
+    need(2 * b->stat_floats);
+    size_t p1 = 0;
+    for (int l = 1; l <= m; ++l) {
+      const size_t f = nhwc::bwd_partial1_floats(P, c_in(d, l), b->pairs ? 2 : 1);
+      if (f > p1) p1 = f;
     }
+    b->near_floats = p1;
+    if (b->pairs) p1 += nhwc::bwd_partial1_near_floats(P, k);
+    b->part1_floats = p1;
+    bwd = p1 + nhwc::bwd_partial2_floats(d.n, d.h, d.w, k, B);
+  } else {
+    need(bn_stats_partial_floats(d.n, d.c0, (int)hw));
+    need(bn_stats_partial_floats(d.n, k, (int)hw));
+    if (B > 0) {
+      need(bn_stats_partial_floats(d.n, B, (int)hw));
+      need(bn_bwd_partial_floats(d.n, B, (int)hw));
+      need(conv_stats_partial_floats(d.n, B, d.h, d.w));  // epilogue statistics of the two convs
+    }
+    need(conv_stats_partial_floats(d.n, k, d.h, d.w));
+    if (merged) {
+      size_t p1 = b->pairs ? bwd32_partial1_near_floats(d.n, (int)hw, k) : 0;
+      for (int l = 1; l <= m; ++l) {
+        const int c = c_in(d, l);
+        size_t f = bwd32_partial1_floats(d.n, (int)hw, c);
+        if (f > p1) p1 = f;
+        if (b->pairs && l < m && bwd32_pair_ok(d.n, (int)hw, c, B) && (f = bwd32_partial1_pair_floats(d.n, (int)hw, c)) > p1)
+          p1 = f;
+      }
+      b->part1_floats = p1;
+      bwd = p1 + bwd32_partial2_floats(d.n, d.h, d.w, k, B);
+    }
+    for (int l = 1; l <= m; ++l) need(bn_bwd_partial_floats(d.n, c_in(d, l), (int)hw));
+  }
+  size_t scratch = 0;
+  auto carve_scratch = [&](size_t bytes, bool in) {
+    const size_t o = hole;
+    if (in && in_hole(hole, bytes)) return o;
     scratch += bytes;
     return carve(bytes, false);
   };
-  b->off_pack = carve_scratch(pack, false);
+  const Fill in = fill(hole);
+  b->off_pack = carve_scratch(pack * 4, false);
   b->off_tail = off;
-  b->off_part = carve_scratch(part, false);
-  // with a bottleneck two buffers each, used alternately by consecutive layers (a layer's partials are
-  // summed by extra workgroups of the next layer's weight-gradient launch)
-  for (int i = 0; i < 2; ++i) {
-    b->off_partB[i] = carve_scratch(partB, true);
-    b->off_partA[i] = B > 0 || i == 0 ? carve_scratch(partA, true) : b->off_partA[0];
+  for (size_t i = 0; i < 2; ++i) {
+    b->off_partB[i] = i < buffers ? carve_scratch(bytesB, i < in.b) : b->off_partB[0];
+    b->off_partA[i] = i < buffers ? carve_scratch(bytesA, i < in.a) : b->off_partA[0];
   }
-  b->off_K = carve_scratch(B > 0 ? (size_t)cout * 2 : 0, true);
-  const bool second_db = bf16 ? m > 1 && B <= nhwc::kDgrad1MaxB
-                              : B > 0 && m > 1 && bwd32_ok(d.n, d.h, d.w, k, B) && bwd32_pair_ok(d.n, (int)hw, c_in(d, m - 1), B);
-  b->off_db2 = carve_scratch(second_db ? ((size_t)B * Ps + 3) / 4 : 0, true);
+  b->off_K = carve_scratch(B > 0 ? (size_t)cout * 8 : 0, true);
+  b->off_bwd = hole;
+  if (bwd && !in_hole(hole, bwd * 4)) { need(bwd); b->off_bwd = off; }  // in the place of the forward's partials
+  b->off_part = carve_scratch(part * 4, false);
   mem.scratch_bytes = (uint64_t)scratch;
   // measured on MI355X: with the weight gradients on helper streams the fp32 step is slower (idle
   // time between dependent launches of different streams outweighs the overlap)

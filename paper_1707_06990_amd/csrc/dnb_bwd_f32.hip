@@ -426,10 +426,8 @@ static int dgrad1p_splits(int n, int hw, int c) {
   if (t > tiles) t = tiles;
   return t < 1 ? 1 : (int)t;
 }
-size_t bwd32_partial1_floats(int n, int hw, int c) {
-  const size_t one = 2 * (size_t)c * bwd32_dgrad1_splits(n, hw, c), two = 4 * (size_t)c * dgrad1p_splits(n, hw, c);
-  return one > two ? one : two;
-}
+size_t bwd32_partial1_floats(int n, int hw, int c) { return 2 * (size_t)c * bwd32_dgrad1_splits(n, hw, c); }
+size_t bwd32_partial1_pair_floats(int n, int hw, int c) { return 4 * (size_t)c * dgrad1p_splits(n, hw, c); }
 size_t bwd32_partial1_near_floats(int n, int hw, int k) { return 2 * (size_t)k * near_splits(n, hw); }
 
 // Whether a layer over c channels and the one above it share their pass over the slab.  What that saves is half

@@ -93,7 +93,8 @@ struct Bwd32Layer {
 };
 bool bwd32_pair_ok(int n, int hw, int c, int B);
 bool bwd32_ok(int n, int h, int w, int k, int B);
-size_t bwd32_partial1_floats(int n, int hw, int c);
+size_t bwd32_partial1_floats(int n, int hw, int c);       // of a layer by itself
+size_t bwd32_partial1_pair_floats(int n, int hw, int c);  // of two layers in one pass
 size_t bwd32_partial1_near_floats(int n, int hw, int k);  // of a pair's k channels between its layers
 size_t bwd32_partial2_floats(int n, int h, int w, int k, int B);
 int bwd32_dgrad1_splits(int n, int hw, int c);
@@ -329,10 +330,10 @@ struct BwdLayer {
   float* part2;                  // partial sums of BN2
   float2* K;                     // per channel of y: K0, K1
 };
-// partial sums of BN1: of a pair of layers over C channels, then of the upper one over the lower one's k
-size_t bwd_partial1_floats(int64_t P, int C, int k, int B);
-size_t bwd_partial1_near(int64_t P, int C, int B);  // floats before the latter
-int bwd_near_splits();                              // most splits of the latter, of the former
+// partial sums of BN1: of one layer or two over C channels; of a pair's upper layer over the lower one's k
+size_t bwd_partial1_floats(int64_t P, int C, int layers);
+size_t bwd_partial1_near_floats(int64_t P, int k);
+int bwd_near_splits();  // most splits of the latter, of the former
 int bwd_far_splits();
 size_t bwd_partial2_floats(int n, int h, int w, int k, int B);
 // 3x3 data gradient and BN2 backward: db, g_l, BN2's parameter gradients, and what L.above holds

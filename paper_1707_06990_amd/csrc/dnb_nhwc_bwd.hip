@@ -808,13 +808,13 @@ Dgrad3Plan plan_dgrad3(int n, int h, int w, int k, int B) {
 constexpr int kNearSplits = 64;
 constexpr int kFarSplits = 256;
 
-size_t bwd_partial1_near(int64_t P, int C, int B) {
+size_t bwd_partial1_floats(int64_t P, int C, int layers) {
   int ppw;
-  return (size_t)(B <= kDgrad1MaxB ? 4 : 2) * C * dgrad1_splits(P, C, kFarSplits, &ppw);
+  return (size_t)2 * layers * C * dgrad1_splits(P, C, kFarSplits, &ppw);
 }
-size_t bwd_partial1_floats(int64_t P, int C, int k, int B) {
+size_t bwd_partial1_near_floats(int64_t P, int k) {
   int ppw;
-  return bwd_partial1_near(P, C, B) + (B <= kDgrad1MaxB ? (size_t)2 * k * dgrad1_splits(P, k, kNearSplits, &ppw) : 0);
+  return (size_t)2 * k * dgrad1_splits(P, k, kNearSplits, &ppw);
 }
 size_t bwd_partial2_floats(int n, int h, int w, int k, int B) {
   return (size_t)2 * B * (plan_dgrad3(n, h, w, k, B).T2 + 1);

@@ -465,6 +465,21 @@ def test_bf16_backward_chain_edges_match_oracle(dnb, oracle, cfg):
     check_bf16_block(dnb, oracle, cfg, to_bf16_values(x0), lp, to_bf16_values(dy))
 
 
+# Layers in pairs need room for a second gradient of a b_l in the gradient scratch (c0 + (m - 2)k >= B), which most
+# blocks above do not have: slices that start inside an M-tile, an odd layer left over, the widest bottleneck that the
+# weight-gradient launch carries, several tiles a workgroup, K-steps of a group cut short, the smallest room
+BF16_PAIRS = [wl.BlockCfg(2, 40, 9, 17, 4, 24, 40), wl.BlockCfg(70, 32, 4, 4, 3, 8, 32), wl.BlockCfg(1, 264, 5, 7, 3, 8, 256),
+              wl.BlockCfg(300, 24, 8, 8, 5, 8, 24), wl.BlockCfg(2, 136, 9, 57, 4, 64, 136), wl.BlockCfg(4, 56, 8, 8, 2, 56, 56)]
+
+
+@pytest.mark.parametrize("cfg", BF16_PAIRS, ids=[f"n{c.n}c{c.c0}h{c.h}w{c.w}m{c.layers}k{c.growth}B{c.bottleneck}" for c in BF16_PAIRS])
+def test_bf16_layers_in_pairs_match_oracle(dnb, oracle, cfg):
+    """With the allowance for the storage format: of the five layers of 300 x 8x8 it alone moves db2 of the fourth, 24
+    sums of 19200 terms of either sign, by 2.04e-2 of its norm (the kernels 2.08e-2, in pairs and one by one)."""
+    x0, lp, dy = wl.make_block_inputs(cfg, affine="random")
+    check_bf16_block(dnb, oracle, cfg, to_bf16_values(x0), lp, to_bf16_values(dy), storage_allowance=True)
+
+
 def test_bf16_backward_of_a_slice_wider_than_lds(dnb, oracle):
     """13600 channels a layer, which dnb_block_create accepts: three coefficients for each would need more
     than the 160 KB of LDS a compute unit has.  (Shared schedule: the fused one keeps BN's folded pairs of

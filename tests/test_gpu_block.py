@@ -285,10 +285,12 @@ def test_bc250_blocks_match_oracle(dnb, oracle, i, batch):
 
 # layers in pairs over a large slab: an odd layer left over, images that are no multiple of 64 pixels, outputs that
 # are no multiple of 16, a slice that straddles two M-tiles; and five chunks of outputs (odd) under the shared schedule
-PAIRS = [(wl.BlockCfg(64, 90, 28, 28, 3, 12, 50), 2), (wl.BlockCfg(50, 130, 28, 28, 2, 20, 72), 0)]
+# (the first has no room for a second gradient beside its partial sums and goes one layer at a time, the third has)
+PAIRS = [(wl.BlockCfg(64, 90, 28, 28, 3, 12, 50), 2), (wl.BlockCfg(50, 130, 28, 28, 2, 20, 72), 0),
+         (wl.BlockCfg(64, 240, 28, 28, 3, 12, 50), 2)]
 
 
-@pytest.mark.parametrize("cfg,schedule", PAIRS, ids=["n64c90k12B50", "n50c130k20B72-shared"])
+@pytest.mark.parametrize("cfg,schedule", PAIRS, ids=["n64c90k12B50", "n50c130k20B72-shared", "n64c240k12B50"])
 def test_layers_in_pairs_match_oracle(dnb, oracle, cfg, schedule):
     x0, lp, dy = wl.make_block_inputs(cfg, affine="random")
     compare_with_kernel_decisions(dnb, oracle, cfg, x0, lp, dy, schedule=schedule)

@@ -153,6 +153,29 @@ def test_weight_gradient_partials_do_not_grow_the_workspace(dnb, kind, limit, ar
     assert got <= limit
 
 
+@pytest.mark.parametrize("kind,limit,args,bf16", [
+    ("block", 543_632_128, dict(n=61, c0=168, h=57, w=71, layers=4, growth=8, bottleneck=96, schedule=2), True),
+    ("block", 276_740_608, dict(n=58, c0=40, h=42, w=40, layers=2, growth=48, bottleneck=192, schedule=2), True),
+    ("block", 49_670_656, dict(n=2, c0=1056, h=7, w=7, layers=24, growth=48, bottleneck=192, schedule=2), True),
+    ("block", 631_856_384, dict(n=89, c0=9, h=42, w=32, layers=9, growth=11, bottleneck=87, schedule=2), False),
+    ("block", 28_802_816, dict(n=64, c0=150, h=8, w=8, layers=16, growth=12, bottleneck=48, schedule=2), False),
+    ("block", 142_529_280, dict(n=77, c0=24, h=38, w=12, layers=7, growth=34, bottleneck=43, schedule=2), False),
+    ("net", 4_844_923_904, dict(n=197, image=48, depth=28, growth=24, classes=10, schedule=0), False),
+    ("net", 1_466_579_712, dict(n=38, image=64, depth=52, growth=16, classes=10, schedule=2), False),
+    ("inet", 579_079_168, dict(n=46, image=256, growth=16, layers=(2, 4, 25, 27), classes=1000, schedule=2), False),
+])
+def test_layers_in_pairs_keep_no_feature_map_outside_the_peak(dnb, kind, limit, args, bf16):
+    """The limits are what these shapes took one layer at a time, where the gradient scratch has no room for a
+    pair's second gradient of a b_l (or, fp32, only instead of partial sums); in the first, bf16, it has, and the
+    limit is that of the 9 MB of partial sums which the 47 MB of that gradient push out."""
+    if bf16:
+        args = dict(args, dtype=dnb.DNB_BF16, layout=dnb.DNB_NHWC)
+    h = getattr(dnb, f"dnb_{kind}_create")(**args)
+    got = getattr(dnb, f"dnb_{kind}_workspace_bytes")(h)
+    getattr(dnb, f"dnb_{kind}_destroy")(h)
+    assert got <= limit
+
+
 @pytest.mark.parametrize("cfg", CFGS + NOBOTTLE, ids=lambda c: f"{c.n}x{c.c0}x{c.h}x{c.w}-m{c.layers}k{c.growth}B{c.bottleneck}")
 def test_peak_bytes_formula(dnb, cfg):
     """Linear-memory formula (shared) and quadratic one (store-all), in bytes."""
