@@ -11,8 +11,8 @@
 // an offset; taps left and right of the image are masked, above and below are staged zeros.
 // Bound by the matrix pipe (9*16*MT*4 instructions of 32 cycles per chunk) once a wave has two chunks;
 // the kernel before it (16-pixel tiles, weights re-packed by every workgroup, two barriers a chunk)
-// took 83 us per launch on the 160..292-channel layers of a 16x16 block at batch 64, this one 22: the
-// 12-layer block without bottleneck 2.13 -> 1.21 ms; the 28x28 DenseNet-BC-40 step at batch 37, with the
+// took 83 us per launch on the 160..292-channel layers of a 16x16 block at batch 64, this one 20: the
+// 12-layer block without bottleneck 2.13 -> 1.20 ms; the 28x28 DenseNet-BC-40 step at batch 37, with the
 // weight gradient of dnb_conv_f32.hip, 2.86 -> 1.96 ms.  (On the shapes the whole-K tiles take it is within
 // 1 % of them on a DenseNet-BC-250 step for k = 24 outputs, and slower as their data gradient.)
 #include <hip/hip_ext.h>
@@ -201,10 +201,14 @@ bool launch_conv3x3_any(const float* in, int64_t in_stride, const float* packed,
   }
   const int tiles = (hw + 63) / 64;
   // K split over the waves where there are chunks for it (three or four, whichever they divide by) and few
-  // M-tiles; else the M-tiles are split, as many per wave as leave a workgroup per CU.
+  // M-tiles; else the M-tiles are split, as many per wave as leave a workgroup per CU.  Eight where no CU gets more
+  // than one workgroup: the other wave of a SIMD then multiplies while one waits for its staging (batch 64, 16x16
+  // rows, 256 channels to 12: 24.9 -> 22.0 us, to 40: 43.8 -> 39.6).  With more, several workgroups of four waves do
+  // that for each other and twice the LDS and waves to add only cost (32x32 rows, 512 workgroups, 128 channels to 12:
+  // 1.33 times four waves' time, 256 to 40: 1.10; 16x16 rows, one M-tile: 0.95 to 1.03).
   int nw = 4, wk = 1, mt = 1;
   if (mtiles <= 3 && nchunks >= 2) {
-    wk = nw = nchunks <= 4 ? nchunks : (nchunks % 4 != 0 && nchunks % 3 == 0 && nchunks <= 9 ? 3 : nchunks < 8 ? 4 : 8);
+    wk = nw = nchunks <= 4 ? nchunks : (nchunks % 4 != 0 && nchunks % 3 == 0 && nchunks <= 9 ? 3 : nchunks >= 8 && (int64_t)tiles * n <= 256 ? 8 : 4);
     mt = mtiles;
   } else {
     if (mtiles < 4) nw = mtiles;

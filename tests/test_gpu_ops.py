@@ -167,6 +167,17 @@ def test_conv_tile_edges(dnb, oracle, n, cin, cout, h, w, ks):
     test_conv_forward_dgrad_wgrad(dnb, oracle, n, cin, cout, h, w, ks)
 
 
+@pytest.mark.parametrize("n,cin,cout,h,w", [(256, 250, 12, 5, 8), (257, 250, 12, 5, 8), (128, 200, 36, 3, 36), (129, 200, 36, 3, 36)])
+def test_conv3x3_of_many_channels_at_a_workgroup_per_cu_and_past_it(dnb, oracle, n, cin, cout, h, w):
+    """K over eight waves (256 tiles of 64 pixels) and over four (257, 258)."""
+    r = rng(8)
+    x, wgt = f32(r.standard_normal((n, cin, h, w))), f32(r.standard_normal((cout, cin, 3, 3)) * 0.1)
+    out = torch.empty(n, cout, h, w, device="cuda")
+    pk = torch.empty(dnb.dnb_op_conv_scratch_bytes(cin, cout, 3), dtype=torch.uint8, device="cuda")
+    dnb.dnb_op_conv_forward(dev(x), cin * h * w, dev(wgt), out, cout * h * w, n, cin, cout, h, w, 3, pk)
+    assert_close(out.cpu().numpy(), oracle.conv_forward(x, wgt), TOL, "forward")
+
+
 def test_conv_on_channel_slices_of_wider_slabs(dnb, oracle):
     """Input and output addressed in place inside wider tensors (explicit image strides),
     as the block does with the output slab y and the gradient slab."""
