@@ -201,7 +201,7 @@ __global__ __launch_bounds__(256) void k_pack_weights(const float* __restrict__ 
 // buffer (BN+ReLU applied, rounded to bf16) after them: one barrier per chunk, load latency
 // under the matrix work.  TIN = u16 (bf16) or float (the gradient slab).  STATS: per-tile
 // (count, mean, M2) of the rounded outputs, at stat_at.
-template <int TAPS, int MT, typename TIN, bool PRO, bool STATS>
+template <int TAPS, int MT, typename TIN, bool PRO, bool STATS, bool RING>
 __global__ __launch_bounds__(256) void k_conv(
     const TIN* __restrict__ in, int64_t in_ld, const u16* __restrict__ Wp, int M16, int K32,
     u16* __restrict__ out, int64_t out_ld, int cin, int cout, int H, int W, int64_t Ptot,
@@ -270,9 +270,9 @@ __global__ __launch_bounds__(256) void k_conv(
     }
   };
   auto deposit = [&](int c0, const Raw(&v)[U], int boff) {
-    const int vv = tid & 7, ch = c0 + 8 * vv;
     float4 fl[4];
     if (PRO) {
+      const int vv = tid & 7;
 #pragma unroll
       for (int e = 0; e < 4; ++e) fl[e] = *reinterpret_cast<const float4*>(&flds[2 * c0 + e * 32 + vv * 4]);
     }
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(256) void k_conv(
     for (int u = 0; u < U; ++u) {
       const int idx = u * 256 + tid;
       if (idx < nvec) {
-        const int s = idx >> 3;
+        const int s = idx >> 3, vv = idx & 7, ch = c0 + 8 * vv;
         const int64_t q = q0 - halo + s;
         V8 o;
         o.q = make_uint4(0u, 0u, 0u, 0u);
@@ -314,9 +314,9 @@ __global__ __launch_bounds__(256) void k_conv(
 
   // packed weights of one (chunk, tap): MT M-tiles x 2 K-steps, 16 bytes per lane each.  They
   // come from L2 at best and, early in a launch, from HBM, so they are requested before their use, into
-  // a ring of register sets indexed statically: the 1x1 one chunk ahead, the 3x3 nine taps (MT == 1) or
-  // three.  Rows past M16
-  // and K-steps past K32 are clamped: their products are never formed or never stored.
+  // a ring of register sets indexed statically: the 1x1 one chunk ahead or (RING) four, the 3x3 nine taps
+  // (MT == 1) or three.  Rows past M16 and K-steps past K32 are clamped: their products are never formed or
+  // never stored.
   struct WSet { uint4 w[MT][2]; };
   auto wload = [&](int c0, int t9, WSet& ws) {
 #pragma unroll
@@ -354,31 +354,61 @@ __global__ __launch_bounds__(256) void k_conv(
   };
 
   const int clast = ((cin - 1) / KC) * KC;  // start of the last chunk
-  constexpr int WD = TAPS == 1 ? 1 : (MT == 1 ? 9 : 3);
-  Raw va[U];
-  {
-    Raw v[U];
-    request(0, v);
-    request(min(KC, clast), va);
-    deposit(0, v, 0);
-  }
-  WSet wt[WD];
+  if (RING) {  // 1x1 with many chunks
+    // chunk x lives in ring slot x % 4 (activations and weights alike): step s multiplies chunk
+    // c, requests chunk c+4 into the slots it has just freed and deposits chunk c+1
+    Raw r[4][U];
+    WSet wt[4];
+    request(0, r[0]);
+    wload(0, 0, wt[0]);
 #pragma unroll
-  for (int s = 0; s < WD; ++s) wload(0, s, wt[s]);
-  __syncthreads();
-  int it = 0;
-  for (int c0 = 0; c0 < cin; c0 += KC, ++it) {
-    const int boff = (it & 1) * BUFE;
-    const int cn = min(c0 + KC, clast);
-#pragma unroll
-    for (int t9 = 0; t9 < TAPS; ++t9) {
-      mm(c0, t9, boff, wt[t9 % WD]);
-      if (t9 + WD < TAPS) wload(c0, t9 + WD, wt[t9 % WD]);
-      else wload(cn, t9 + WD - TAPS, wt[t9 % WD]);
+    for (int x = 1; x < 4; ++x) {
+      wload(min(x * KC, clast), 0, wt[x]);
+      request(min(x * KC, clast), r[x]);
     }
-    if (c0 + KC < cin) deposit(c0 + KC, va, ((it & 1) ^ 1) * BUFE);
-    request(min(c0 + 2 * KC, clast), va);  // in flight across the barrier and the next chunk's MFMAs
+    deposit(0, r[0], 0);
     __syncthreads();
+    // The loop always runs whole groups of four steps: steps past the last chunk load (clamped),
+    // deposit and synchronise like the others and only skip the MFMAs, so the sequence of loads
+    // and of waits for them is the same on every path.
+    for (int cb = 0; cb < cin; cb += 4 * KC) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int c0 = cb + s * KC, cn = min(c0 + 4 * KC, clast);
+        if (c0 < cin) mm(c0, 0, (s & 1) * BUFE, wt[s]);
+        wload(cn, 0, wt[s]);
+        request(cn, r[s]);
+        deposit(min(c0 + KC, clast), r[(s + 1) & 3], ((s & 1) ^ 1) * BUFE);
+        __syncthreads();
+      }
+    }
+  } else {
+    constexpr int WD = TAPS == 1 ? 1 : (MT == 1 ? 9 : 3);
+    Raw va[U];
+    {
+      Raw v[U];
+      request(0, v);
+      request(min(KC, clast), va);
+      deposit(0, v, 0);
+    }
+    WSet wt[WD];
+#pragma unroll
+    for (int s = 0; s < WD; ++s) wload(0, s, wt[s]);
+    __syncthreads();
+    int it = 0;
+    for (int c0 = 0; c0 < cin; c0 += KC, ++it) {
+      const int boff = (it & 1) * BUFE;
+      const int cn = min(c0 + KC, clast);
+#pragma unroll
+      for (int t9 = 0; t9 < TAPS; ++t9) {
+        mm(c0, t9, boff, wt[t9 % WD]);
+        if (t9 + WD < TAPS) wload(c0, t9 + WD, wt[t9 % WD]);
+        else wload(cn, t9 + WD - TAPS, wt[t9 % WD]);
+      }
+      if (c0 + KC < cin) deposit(c0 + KC, va, ((it & 1) ^ 1) * BUFE);
+      request(min(c0 + 2 * KC, clast), va);  // in flight across the barrier and the next chunk's MFMAs
+      __syncthreads();
+    }
   }
 
   if (!m_ok) return;
@@ -798,21 +828,30 @@ hipError_t conv(const void* in, int64_t in_ld, bool in_f32, const void* Wp, void
   const int halo = taps == 9 ? w + 1 : 0;
   const size_t lds = (size_t)2 * (64 + 2 * halo) * 72 * sizeof(u16) + (fold ? (size_t)((cin + 63) & ~63) * 8 : 0);
   if (lds > 64 * 1024 + (fold ? 56 * 8 : 0) || (taps == 9 && (64 + 2 * halo) * 8 > 8 * 256)) return hipErrorInvalidValue;
-#define DNB_K(TAPS, MT, TIN, PRO, STATS)                                                                        \
-  hipLaunchKernelGGL((k_conv<TAPS, MT, TIN, PRO, STATS>), grid, dim3(256), lds, st, (const TIN*)in, in_ld, \
+  // Four chunks in flight with eight or more of them and about one workgroup per compute unit: 392 pixels x 2112
+  // channels x 1056 outputs 30.9 -> 26.4 us, 1568 x 2208 x 192 27.0 -> 21.8.  With several workgroups a unit their
+  // phases already cover one another's latencies and the ring's extra loads only cost (1568 x 1056 x 2112 27.1 -> 30.5),
+  // with few at all the weights come fast enough without (49 x 1056 x 128 12.0 -> 12.8).  With statistics k_conv1 takes
+  // these.
+  const bool ring = taps == 1 && !spart && cin >= 512 && mt == 1 && ptiles * gy >= 64 && ptiles * gy <= 320;
+#define DNB_K(TAPS, MT, TIN, PRO, STATS, RING)                                                                  \
+  hipLaunchKernelGGL((k_conv<TAPS, MT, TIN, PRO, STATS, RING>), grid, dim3(256), lds, st, (const TIN*)in, in_ld, \
                      (const u16*)Wp, M16, K32, (u16*)out, out_ld, cin, cout, h, w, P, fold, spart, T)
-#define DNB_K2(TAPS, MT)                                                              \
-  do {                                                                                \
-    if (in_f32) DNB_K(TAPS, MT, float, false, false);                                 \
-    else if (fold) DNB_K(TAPS, MT, u16, true, true);                                  \
-    else if (spart) DNB_K(TAPS, MT, u16, false, true);                                \
-    else DNB_K(TAPS, MT, u16, false, false);                                          \
+#define DNB_K2(TAPS, MT)                                                                                          \
+  do {                                                                                                            \
+    if (in_f32) DNB_K(TAPS, MT, float, false, false, false);                                                 \
+    else if (fold) DNB_K(TAPS, MT, u16, true, true, false);                                                       \
+    else if (spart) DNB_K(TAPS, MT, u16, false, true, false);                                                     \
+    else DNB_K(TAPS, MT, u16, false, false, false);                                                               \
   } while (0)
 #define DNB_K3(TAPS)                                                                  \
   do {                                                                                \
     if (mt == 3) DNB_K2(TAPS, 3); else if (mt == 2) DNB_K2(TAPS, 2); else DNB_K2(TAPS, 1); \
   } while (0)
-  if (taps == 9) DNB_K3(9); else DNB_K3(1);
+  if (ring && in_f32) DNB_K(1, 1, float, false, false, true);
+  else if (ring) DNB_K(1, 1, u16, false, false, true);
+  else if (taps == 9) DNB_K3(9);
+  else DNB_K3(1);
 #undef DNB_K3
 #undef DNB_K2
 #undef DNB_K

@@ -276,9 +276,12 @@ def back(t):
 
 OP_SHAPES = [(2, 16, 8, 8, 8, 1), (2, 32, 8, 8, 8, 3), (2, 8, 32, 8, 8, 3), (1, 24, 16, 7, 7, 3), (2, 40, 64, 14, 14, 1),
              (1, 192, 48, 12, 20, 3), (2, 48, 192, 9, 11, 3), (1, 200, 192, 10, 10, 1),
-             # 1x1 with nine input chunks, the last one 8 channels wide (forward takes the four-chunk ring);
-             # weight gradient over 3 x 2 channel groups with a ragged last pixel tile
+             # 1x1 with nine input chunks, the last one 8 channels wide; weight gradient over 3 x 2 channel groups
+             # with a ragged last pixel tile
              (2, 520, 200, 9, 7, 1),
+             # the four-chunk ring, forward and data gradient: ten chunks, the last 8 channels, 102 workgroups, a last
+             # pixel tile of 56, outputs that leave three waves of the last group idle
+             (8, 584, 328, 9, 15, 1), (8, 328, 584, 9, 15, 1),
              # 1x1 whose data gradient reduces over nine chunks; output channels over three workgroup rows
              (1, 64, 576, 6, 6, 1),
              # 3x3 weight gradient: two row tiles per image and two channel groups; then more tiles than
