@@ -51,11 +51,12 @@ struct Dgrad1Lower {
 // come from L1) or, where there are few channels, other tiles; they share nothing else, the sums stay in
 // registers until a wave's last tile.
 // NCH: 16-channel chunks of b_l whose weights stay in registers; 0: read in the loop.
-template <int NCH, bool FIRST>
+template <int NCH, bool FIRST, bool SLICE>
 __global__ __launch_bounds__(256, 2) void k_dgrad1(Dgrad1Args A) {
+  const int lo = SLICE ? A.lo : 0;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = lane & 15, g = lane >> 4;
   const int wm = wave % A.nwm, wp = wave / A.nwm, nwp = 4 / A.nwm;
-  const int m0 = (A.lo & ~15) + ((int)blockIdx.y * A.nwm + wm) * 32, t0 = (int)blockIdx.x * nwp + wp;
+  const int m0 = (lo & ~15) + ((int)blockIdx.y * A.nwm + wm) * 32, t0 = (int)blockIdx.x * nwp + wp;
   if (m0 >= A.C || t0 >= A.T) return;
   const int HW = A.hw, nch = A.B16 >> 4;
   const int mt[2] = {m0 >> 4, min((m0 >> 4) + 1, (A.C16 >> 4) - 1)};
@@ -152,7 +153,7 @@ __global__ __launch_bounds__(256, 2) void k_dgrad1(Dgrad1Args A) {
             s0[a][r] += dz;
             s1[a][r] = __fmaf_rn(dz, xv - mu[a][r], s1[a][r]);
           }
-          if (m0 + a * 16 + 4 * g + r < A.C && m0 + a * 16 + 4 * g + r >= A.lo)
+          if (m0 + a * 16 + 4 * g + r < A.C && (!SLICE || m0 + a * 16 + 4 * g + r >= lo))
             *reinterpret_cast<float4*>(op + (int64_t)ch(a, r) * HW) = make_float4(o[0], o[1], o[2], o[3]);
         }
     }
@@ -163,7 +164,7 @@ __global__ __launch_bounds__(256, 2) void k_dgrad1(Dgrad1Args A) {
     for (int r = 0; r < 4; ++r) {
       const float u = row16_sum(s0[a][r]), v = row16_sum(s1[a][r]);
       const int m = m0 + a * 16 + 4 * g + r;
-      if (j == 0 && m < A.C && m >= A.lo) A.part1[(int64_t)(m - A.lo) * A.T + t0] = make_float2(u, v * A.istd[m]);
+      if (j == 0 && m < A.C && (!SLICE || m >= lo)) A.part1[(int64_t)(m - lo) * A.T + t0] = make_float2(u, v * A.istd[m]);
     }
 }
 
@@ -487,14 +488,19 @@ hipError_t bwd32_dgrad1(const Bwd32Layer& L, hipStream_t st) {
     return hipGetLastError();
   }
   const dim3 grid((unsigned)((A.T + nwp - 1) / nwp), (unsigned)((groups + A.nwm - 1) / A.nwm));
-#define DNB_L(NCH)                                                                       \
-  do {                                                                                   \
-    if (L.first) hipLaunchKernelGGL((k_dgrad1<NCH, true>), grid, dim3(256), 0, st, A);    \
-    else hipLaunchKernelGGL((k_dgrad1<NCH, false>), grid, dim3(256), 0, st, A);          \
+#define DNB_LF(NCH, SLICE)                                                                      \
+  do {                                                                                          \
+    if (L.first) hipLaunchKernelGGL((k_dgrad1<NCH, true, SLICE>), grid, dim3(256), 0, st, A);   \
+    else hipLaunchKernelGGL((k_dgrad1<NCH, false, SLICE>), grid, dim3(256), 0, st, A);          \
+  } while (0)
+#define DNB_L(NCH)                                                                              \
+  do {                                                                                          \
+    if (L.lo) DNB_LF(NCH, true); else DNB_LF(NCH, false);                                       \
   } while (0)
   switch (A.B16 >> 4) {
-    case 1: DNB_L(1); break; case 2: DNB_L(2); break; case 3: DNB_L(3); break; default: DNB_L(0); break;
+    case 1: DNB_LF(1, false); break; case 2: DNB_LF(2, false); break; case 3: DNB_L(3); break; default: DNB_L(0); break;
   }
+#undef DNB_LF
 #undef DNB_L
   return hipGetLastError();
 }

@@ -268,37 +268,38 @@ struct Bn1Finish {
   int first;                   // K is set, not added to
   float *dgamma[2], *dbeta[2];
 };
-__device__ __forceinline__ void bn1_finish_body(const Bn1Finish& A, int wg) {
+template <int N>  // of a layer by itself nothing of a second one is loaded, added or waited for
+__device__ __forceinline__ void bn1_finish_layers(const Bn1Finish& A, int wg) {
   const int i = wg * (int)(blockDim.x >> 6) + (int)(threadIdx.x >> 6);
   if (i >= A.C) return;
   const int ch = A.lo + i;
-  float2 s[2];
+  float2 s[N];
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
+  for (int q = 0; q < N; ++q) {
     s[q] = make_float2(0.f, 0.f);
-    if (q < A.n) {
-      const float2* p = A.part[q] + (int64_t)i * A.T;
-      for (int t = threadIdx.x & 63; t < A.T; t += 64) { const float2 v = p[t]; s[q].x += v.x; s[q].y += v.y; }
-    }
+    const float2* p = A.part[q] + (int64_t)i * A.T;
+    for (int t = threadIdx.x & 63; t < A.T; t += 64) { const float2 v = p[t]; s[q].x += v.x; s[q].y += v.y; }
   }
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
+  for (int q = 0; q < N; ++q) {
     s[q].x = bnb_wave_sum(s[q].x);
     s[q].y = bnb_wave_sum(s[q].y);
   }
   if ((threadIdx.x & 63) == 0) {
     float2 k = A.first ? make_float2(0.f, 0.f) : A.K[ch];
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      if (q < A.n) {
-        const float sc = __fmul_rn(A.gamma[q][ch], A.istd[ch]) * A.inv_p;
-        k = make_float2(__fmaf_rn(sc, s[q].x, k.x), __fmaf_rn(sc, s[q].y, k.y));
-        A.dbeta[q][ch] = s[q].x;
-        A.dgamma[q][ch] = s[q].y;
-      }
+    for (int q = 0; q < N; ++q) {
+      const float sc = __fmul_rn(A.gamma[q][ch], A.istd[ch]) * A.inv_p;
+      k = make_float2(__fmaf_rn(sc, s[q].x, k.x), __fmaf_rn(sc, s[q].y, k.y));
+      A.dbeta[q][ch] = s[q].x;
+      A.dgamma[q][ch] = s[q].y;
     }
     A.K[ch] = k;
   }
+}
+__device__ __forceinline__ void bn1_finish_body(const Bn1Finish& A, int wg) {
+  if (A.n == 1) bn1_finish_layers<1>(A, wg);
+  else bn1_finish_layers<2>(A, wg);
 }
 
 struct BnBwdPartialArgs {
