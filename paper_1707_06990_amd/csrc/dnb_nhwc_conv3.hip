@@ -149,26 +149,30 @@ __global__ __launch_bounds__(512, (MG > 1 && !FOLD ? 4 : 2)) void k_conv3(Conv3A
       lok[t] = wc != 0;
       rok[t] = wc != W - 1;
     }
-    for (int c = 0; c < nch; ++c) {
+    auto tap = [&](int c, int t9, int kk) {
+      const int di = t9 / 3 - 1, dj = t9 % 3 - 1, off = (di * W + dj) * PITCH;
+      V8 wv;
+      wv.q = w[t9][kk];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int a = ((dj < 0 && !lok[t]) || (dj > 0 && !rok[t]) ? zero : row[t] + off) + c * 64;
+        V8 x;
+        x.q = *reinterpret_cast<const uint4*>(lds + a + kk * 32);
+        acc[t] = mfma_bf16(wv, x, acc[t]);
+      }
+    };
+    for (int c = 0; c < nk >> 1; ++c) {
 #pragma unroll
       for (int t9 = 0; t9 < 9; ++t9) {
-        const int di = t9 / 3 - 1, dj = t9 % 3 - 1, off = (di * W + dj) * PITCH;
-        int a[2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) a[t] = ((dj < 0 && !lok[t]) || (dj > 0 && !rok[t]) ? zero : row[t] + off) + c * 64;
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-          V8 wv;
-          wv.q = w[t9][kk];
-#pragma unroll
-          for (int t = 0; t < 2; ++t) {
-            V8 x;
-            x.q = *reinterpret_cast<const uint4*>(lds + a[t] + kk * 32);
-            acc[t] = mfma_bf16(wv, x, acc[t]);
-          }
-        }
+        tap(c, t9, 0);
+        tap(c, t9, 1);
         wload(min(c + 1, nch - 1), t9);
       }
+    }
+    // the last chunk's one K-step by itself (beside it lie zeros, but an infinite weight times zero is not zero)
+    if (nk & 1) {
+#pragma unroll
+      for (int t9 = 0; t9 < 9; ++t9) tap(nch - 1, t9, 0);
     }
     const int m = mt * 16 + 4 * g;
 #pragma unroll

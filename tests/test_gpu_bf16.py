@@ -483,6 +483,25 @@ def test_bf16_layers_in_pairs_match_oracle(dnb, oracle, cfg):
     check_bf16_block(dnb, oracle, cfg, to_bf16_values(x0), lp, to_bf16_values(dy), storage_allowance=True)
 
 
+@pytest.mark.parametrize("B", [32, 64, 96, 160])
+@pytest.mark.parametrize("schedule", [0, 2])
+def test_infinite_weight_of_the_3x3_reaches_only_what_it_multiplies(dnb, B, schedule):
+    """One infinite centre weight in the last K-step of 32 bottleneck channels (B = 32, 96, 160: half of a 64-channel
+    chunk): inf where the activation it multiplies is positive, NaN (inf times 0) where it is zero, nothing elsewhere."""
+    cfg = wl.BlockCfg(2, 16, 9, 11, 1, 16, B)
+    x0, lp, dy = wl.make_block_inputs(cfg, affine="random")
+    x0, dy = to_bf16_values(x0), to_bf16_values(dy)
+    plain = run_block_gpu_bf16(dnb, cfg, x0, lp, dy, schedule=schedule)["y"]
+    lp[0]["W3"][2, B - 27, 1, 1] = np.inf
+    gpu = run_block_gpu_bf16(dnb, cfg, x0, lp, dy, decisions=True, schedule=schedule)
+    on = gpu["d2"].reshape(cfg.n, cfg.h, cfg.w, B)[..., B - 27] == 1
+    got = gpu["y"][:, cfg.c0 + 2]
+    assert on.any() and not on.all()
+    assert np.array_equal(got == np.inf, on) and np.array_equal(np.isnan(got), ~on)
+    keep = np.arange(cfg.c_out) != cfg.c0 + 2
+    assert np.array_equal(gpu["y"][:, keep], plain[:, keep])
+
+
 def test_bf16_backward_of_a_slice_wider_than_lds(dnb, oracle):
     """13600 channels a layer, which dnb_block_create accepts: three coefficients for each would need more
     than the 160 KB of LDS a compute unit has.  (Shared schedule: the fused one keeps BN's folded pairs of
