@@ -289,6 +289,7 @@ struct dnb_net {
   dnb_block* blk[3];
   dnb_block_desc bd[3];
   int cout[3];                       // channels leaving block b
+  bool sums_in_dtz[2];               // partial sums of transition b's weight gradient: see dnb_net_create
   size_t p_stem, p_block[3], p_g[3], p_b[3], p_w[3], p_bl, p_count;  // offsets in the pack (floats)
   // workspace offsets (bytes)
   size_t o_feat[3], o_y[3], o_ws[3], o_tz[3], o_mean[3], o_istd[3];
@@ -385,7 +386,6 @@ int dnb_net_create(const dnb_net_desc* desc, dnb_net** out) {
     need(bn_stats_partial_floats(d.n, (int)co, (int)hw));
     need(bn_bwd_partial_floats(d.n, (int)co, (int)hw));
     if (b < 2) {
-      need(conv_wgrad_partial_floats(d.n, (int)co, (int)(co / 2), bd.h, bd.w, 1, true));
       net->o_pack[b] = carve(packed_weight_floats((int)(co / 2), (int)co, 1) * 4 * 2, false, "pack", b);  // forward + transposed
     }
   }
@@ -402,6 +402,14 @@ int dnb_net_create(const dnb_net_desc* desc, dnb_net** out) {
     const size_t P = (size_t)d.n * bd.h * bd.w;
     if ((size_t)bd.c0 * P > feat_max) feat_max = (size_t)bd.c0 * P;
     if (b < 2 && (size_t)(net->cout[b] / 2) * P > conv_max) conv_max = (size_t)(net->cout[b] / 2) * P;
+  }
+  // The partial sums of a transition's weight gradient lie where its data gradient goes next, if that is large enough
+  // for the many workgroups the launch has by itself; else it has fewer, and the place of the other partials.
+  for (int b = 0; b < 2; ++b) {
+    const dnb_block_desc& bd = net->bd[b];
+    net->sums_in_dtz[b] = conv_wgrad_partial_floats(d.n, net->cout[b], net->cout[b] / 2, bd.h, bd.w, 1, true) <= pmax;
+    const size_t f = net->sums_in_dtz[b] ? 0 : conv_wgrad_partial_floats(d.n, net->cout[b], net->cout[b] / 2, bd.h, bd.w, 1);
+    if (f > part) part = f;
   }
   net->o_tconv = carve(conv_max * 4, true, "tconv");  // a transition's 1x1 output before pooling
   net->o_gy = carve(pmax * 4, true, "gy");         // gradient of a block output
@@ -626,8 +634,9 @@ int dnb_net_backward(dnb_net* net, const void* xv, const void* paramsv, void* dp
       hipLaunchKernelGGL(k_avgpool2_bwd, dim3(grid_for(planes * hwp, kT * 4)), dim3(kT), 0, st, dfeat, dconv, planes,
                          pd.h, pd.w);
       DNB_TRYH(hipGetLastError());
-      DNB_TRYH(launch_conv_wgrad(tzp, (int64_t)cp * hwp, dconv, (int64_t)ch * hwp, dparams + net->p_w[b - 1], n, cp,
-                                 ch, pd.h, pd.w, 1, part, nullptr, st, nullptr, nullptr, nullptr, nullptr, nullptr, true));
+      const bool in_dtz = net->sums_in_dtz[b - 1];
+      DNB_TRYH(launch_conv_wgrad(tzp, (int64_t)cp * hwp, dconv, (int64_t)ch * hwp, dparams + net->p_w[b - 1], n, cp, ch,
+                                 pd.h, pd.w, 1, in_dtz ? dtz : part, nullptr, st, nullptr, nullptr, nullptr, nullptr, nullptr, in_dtz));
       DNB_TRYH(launch_conv_igemm(dconv, (int64_t)ch * hwp, WeightView{W, 1, cp, 0}, pkt, dtz, (int64_t)cp * hwp, n, ch,
                                  cp, pd.h, pd.w, 1, nullptr, st));
     }

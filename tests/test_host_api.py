@@ -162,6 +162,7 @@ def test_weight_gradient_partials_do_not_grow_the_workspace(dnb, kind, limit, ar
     ("block", 142_529_280, dict(n=77, c0=24, h=38, w=12, layers=7, growth=34, bottleneck=43, schedule=2), False),
     ("net", 4_844_923_904, dict(n=197, image=48, depth=28, growth=24, classes=10, schedule=0), False),
     ("net", 1_466_579_712, dict(n=38, image=64, depth=52, growth=16, classes=10, schedule=2), False),
+    ("net", 112_052_736, dict(n=9, image=52, depth=88, growth=4, classes=100, schedule=0), False),
     ("inet", 579_079_168, dict(n=46, image=256, growth=16, layers=(2, 4, 25, 27), classes=1000, schedule=2), False),
 ])
 def test_layers_in_pairs_keep_no_feature_map_outside_the_peak(dnb, kind, limit, args, bf16):
