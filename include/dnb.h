@@ -85,8 +85,9 @@ typedef struct {
  *   peak = stored + shared + grad
  * (DNB_BF16: the slab of C_out channels inside grad is fp32).  A backward pass that takes layers in
  * pairs keeps a second gradient of a b_l, (B P s), inside the C_m part of grad, of which it needs only
- * k channels for itself; blocks whose C_m part has no room for it run one layer at a time, so no
- * feature map lies outside the peak.
+ * k channels for itself; blocks whose C_m part has no room for it, or whose reduction partials it
+ * would push out of there (in bf16 beyond a sixteenth of the feature maps), run one layer at a time.
+ * No feature map lies outside the peak.
  * `stored` counts the m*k channels x_1..x_m although they live inside the
  * caller's output y (they are conv feature maps the method keeps; Section 4). */
 typedef struct {

@@ -729,14 +729,16 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
     return best;
   };
   // First of it the second db of layers in pairs, a feature-map gradient like the first: the peak counts none
-  // outside the gradient scratch, so without room for it there layers go one at a time.  In fp32, where pairs save
-  // a few per cent, also where it would push partial sums out (a DenseNet-BC-100 of 48x48 images took 3.6 % more
-  // workspace); in bf16 (10 % and more of a step) partial sums give way.
+  // outside the gradient scratch, so without room for it there layers go one at a time.  Nor are pairs, which save 2
+  // to 7 % of a large bf16 block's step and a few per cent in fp32, worth much memory: in bf16 at most a sixteenth of
+  // the feature maps may be pushed out by it as partial sums (32 images of 56x56, 64 to 256 channels, k = 32: 34 of
+  // 393 MB, and a step of 1256 us one at a time against 1262 in pairs), in fp32 nothing (a DenseNet-BC-100 of 48x48
+  // images took 3.6 % more).
   b->pairs = merged && m > 1 && (bf16 ? B <= nhwc::kDgrad1MaxB : bwd32_pair_ok(d.n, (int)hw, c_in(d, m - 1), B));
   if (b->pairs) {
     size_t at = hole;
     b->off_db2 = hole;
-    b->pairs = in_hole(at, (size_t)B * Ps) && (bf16 || fill(at).bytes == fill(hole).bytes);
+    b->pairs = in_hole(at, (size_t)B * Ps) && fill(hole).bytes - fill(at).bytes <= (bf16 ? off / 16 : 0);
     if (b->pairs) hole = at;
   }
 
