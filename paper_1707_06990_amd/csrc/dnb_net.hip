@@ -115,7 +115,7 @@ __global__ __launch_bounds__(kT) void k_linear(const float* __restrict__ f, cons
 // Per sample: log-sum-exp, loss term, dlogits = (softmax - onehot)/n.  One workgroup of 16 waves (with four,
 // 32 samples of 1000 classes took 88 us); each wave takes samples wave, wave + 16, ... and its lanes stride over
 // the classes, the first 1024 of them in registers (butterfly maximum and sum, so every lane holds the same
-// values).  Then the loss terms are added in sample order by thread 0, from LDS (up to 4096 samples).
+// values).  Then the loss terms are added in sample order by thread 0, from LDS (n <= 4096: every caller's limit).
 constexpr int kXentWaves = 16, kXentRegs = 16;
 __global__ __launch_bounds__(64 * kXentWaves) void k_softmax_xent(const float* __restrict__ logits,
                                                                   const int32_t* __restrict__ labels,
@@ -146,7 +146,7 @@ __global__ __launch_bounds__(64 * kXentWaves) void k_softmax_xent(const float* _
     if (lane == 0) {
       const float t = valid ? lse - z[lab] : 0.f;
       terms[i] = t;
-      if (n <= 4096) sterms[i] = t;
+      sterms[i] = t;
     }
     float* d = dlogits + (int64_t)i * classes;
 #pragma unroll
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(64 * kXentWaves) void k_softmax_xent(const float* _
   __syncthreads();
   if (threadIdx.x == 0) {
     float s = 0.f;
-    for (int i = 0; i < n; ++i) s += n <= 4096 ? sterms[i] : terms[i];
+    for (int i = 0; i < n; ++i) s += sterms[i];
     *loss = s / (float)n;
   }
 }
@@ -260,6 +260,7 @@ namespace dnb {
 // cross-entropy with its gradient (all fp32), and the head's backward pass.
 hipError_t launch_head_forward(const float* pooled, const float* wl, const float* bl, const int32_t* labels, float* logits,
                                float* dlogits, float* terms, float* loss, int n, int c, int classes, hipStream_t st) {
+  if (n > 4096) return hipErrorInvalidValue;
   // four classes a wave where that leaves a wave for every CU or so, else one (few classes: latency)
   const unsigned gs = (unsigned)((n + 7) / 8);
   if ((int64_t)classes * gs >= 512)
