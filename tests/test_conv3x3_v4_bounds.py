@@ -200,6 +200,9 @@ def check_wave_per_m_tile(n, cin, cout, H, W):
 
 
 @pytest.mark.parametrize("n,cin,cout,H,W", [(1, 24, 96, 32, 32), (3, 24, 96, 8, 8), (5, 17, 65, 8, 16), (1, 32, 128, 4, 16),
-                                            (2, 25, 100, 16, 8), (1, 20, 81, 2, 32), (36, 24, 72, 32, 32)])
+                                            (2, 25, 100, 16, 8), (1, 20, 81, 2, 32), (36, 24, 72, 32, 32),
+                                            # the other pairs of waves and K-steps: eight and six, six and eight
+                                            (1, 32, 128, 2, 32), (1, 24, 112, 2, 32), (2, 24, 112, 4, 16), (2, 17, 113, 8, 8),
+                                            (1, 30, 90, 2, 32), (2, 32, 96, 4, 16), (2, 28, 80, 8, 8)])
 def test_every_access_of_the_wave_per_m_tile_form_is_in_bounds(n, cin, cout, H, W):
     assert check_wave_per_m_tile(n, cin, cout, H, W) <= 80 * 1024  # two workgroups a CU

@@ -287,10 +287,13 @@ def test_bc250_blocks_match_oracle(dnb, oracle, i, batch):
 # are no multiple of 16, a slice that straddles two M-tiles; and five chunks of outputs (odd) under the shared schedule
 # (the first has no room for a second gradient beside its partial sums and goes one layer at a time, the third has)
 PAIRS = [(wl.BlockCfg(64, 90, 28, 28, 3, 12, 50), 2), (wl.BlockCfg(50, 130, 28, 28, 2, 20, 72), 0),
-         (wl.BlockCfg(64, 240, 28, 28, 3, 12, 50), 2)]
+         (wl.BlockCfg(64, 240, 28, 28, 3, 12, 50), 2),
+         # seven and eight chunks of outputs, two pairs each
+         (wl.BlockCfg(100, 350, 20, 16, 4, 28, 112), 2), (wl.BlockCfg(100, 350, 20, 16, 4, 32, 128), 0)]
 
 
-@pytest.mark.parametrize("cfg,schedule", PAIRS, ids=["n64c90k12B50", "n50c130k20B72-shared", "n64c240k12B50"])
+@pytest.mark.parametrize("cfg,schedule", PAIRS, ids=["n64c90k12B50", "n50c130k20B72-shared", "n64c240k12B50", "n100c350k28B112",
+                                                     "n100c350k32B128-shared"])
 def test_layers_in_pairs_match_oracle(dnb, oracle, cfg, schedule):
     x0, lp, dy = wl.make_block_inputs(cfg, affine="random")
     compare_with_kernel_decisions(dnb, oracle, cfg, x0, lp, dy, schedule=schedule)
@@ -302,10 +305,17 @@ WAVES = [wl.BlockCfg(2, 30, 8, 8, 3, 17, 65), wl.BlockCfg(3, 24, 16, 16, 3, 24, 
          wl.BlockCfg(2, 24, 4, 32, 3, 20, 81), wl.BlockCfg(5, 64, 16, 8, 2, 32, 128), wl.BlockCfg(66, 24, 32, 32, 2, 24, 72)]
 
 
-@pytest.mark.parametrize("cfg", WAVES, ids=lambda c: f"n{c.n}c{c.c0}h{c.h}w{c.w}k{c.growth}B{c.bottleneck}")
-def test_3x3_data_gradient_with_a_wave_per_m_tile_matches_oracle(dnb, oracle, cfg):
+# the other pairs of waves and K-steps: eight and eight on rows of 32, eight and six, six and eight
+WAVES_SHARED = [wl.BlockCfg(2, 24, 32, 32, 2, 32, 128), wl.BlockCfg(3, 20, 4, 32, 2, 24, 112), wl.BlockCfg(2, 24, 16, 16, 2, 24, 112),
+                wl.BlockCfg(3, 20, 8, 8, 2, 17, 113), wl.BlockCfg(2, 24, 4, 32, 2, 30, 90), wl.BlockCfg(3, 20, 8, 16, 2, 32, 96),
+                wl.BlockCfg(2, 24, 8, 8, 2, 28, 80)]
+
+
+@pytest.mark.parametrize("cfg,schedule", [(c, 2) for c in WAVES] + [(c, 0) for c in WAVES_SHARED],
+                         ids=lambda c: f"n{c.n}c{c.c0}h{c.h}w{c.w}k{c.growth}B{c.bottleneck}" if hasattr(c, "n") else f"s{c}")
+def test_3x3_data_gradient_with_a_wave_per_m_tile_matches_oracle(dnb, oracle, cfg, schedule):
     x0, lp, dy = wl.make_block_inputs(cfg, affine="random")
-    compare_with_kernel_decisions(dnb, oracle, cfg, x0, lp, dy, schedule=2)
+    compare_with_kernel_decisions(dnb, oracle, cfg, x0, lp, dy, schedule=schedule)
 
 
 @pytest.mark.parametrize("which", ["config2", "config3"])

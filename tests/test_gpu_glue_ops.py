@@ -25,12 +25,13 @@ def back(t):        # device (n, h, w, c) -> numpy (n, c, h, w) float32
     return t.float().permute(0, 3, 1, 2).contiguous().cpu().numpy()
 
 
-@pytest.mark.parametrize("n,c,classes", [(64, 342, 10), (64, 1734, 100), (32, 2208, 1000), (5, 70, 3), (3, 64, 17)],
-                         ids=["bc100", "bc250", "dn161", "ragged", "classes17"])
+@pytest.mark.parametrize("n,c,classes", [(64, 342, 10), (64, 1734, 100), (32, 2208, 1000), (5, 70, 3), (3, 64, 17), (3, 64, 1100),
+                                         (19, 24, 2049), (4096, 8, 5)],
+                         ids=["bc100", "bc250", "dn161", "ragged", "classes17", "classes1100", "classes2049", "batch4096"])
 def test_classifier_head(dnb, oracle, n, c, classes):
     """Logits, loss, the loss's gradient and the head's backward pass at the head shapes of the four
-    benchmark networks (the last: 2208 features, 1000 classes, batch 32) and two ragged ones; one
-    label is out of range and must add nothing."""
+    benchmark networks (the last: 2208 features, 1000 classes, batch 32), ragged ones, more classes than
+    a wave keeps in registers (1024) and the largest batch; one label is out of range and must add nothing."""
     rng = np.random.default_rng(1000 + n + c + classes)
     pooled = np.abs(rng.standard_normal((n, c))).astype(np.float32)
     wl = (rng.standard_normal((classes, c)) / np.sqrt(c)).astype(np.float32)
