@@ -672,7 +672,7 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
   if (bf16) {
     size_t pe = 0;  // bf16 elements
     for (int l = 1; l <= m; ++l) {
-      const size_t f = nhwc::wgrad_partial_floats(d.n, c_in(d, l), B, d.h, d.w, 1, true);
+      const size_t f = nhwc::wgrad_partial_floats(d.n, c_in(d, l), B, d.h, d.w, 1, B <= nhwc::kDgrad1MaxB);
       if (f > partB) partB = f;
       b->pk[l] = pe;
       pe += nhwc::packed_layer_elems(c_in(d, l), k, B);

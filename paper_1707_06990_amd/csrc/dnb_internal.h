@@ -267,7 +267,7 @@ struct WgradSum {
   int taps, S, gy, gz, mt, cin, cout;
 };
 // (dnb_nhwc_wgrad.hip) Partial floats of the kernels there, 0 if they do not take the shape.
-size_t wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool pair);
+size_t wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool carrying);
 // Launches the partials and describes their sum in *own; false (nothing launched) if the shape is not taken.
 bool wgrad_fast(const WgradIn& in, bool g_f32, int n, int h, int w, int taps, WgradSum* own, hipStream_t st);
 // 1x1 data gradient with BN1 + concat backward on channels cb..ce-1, for one layer or for two at once (layer 0 the
@@ -294,7 +294,7 @@ bool wgrad_pair(const WgradIn& w1, const WgradIn& w3, int n, int h, int w, Wgrad
                 int most_splits, int* T1, hipStream_t st);
 // Carries out what is pending (either may be null).
 hipError_t wgrad_finish(WgradSum* s1, WgradSum* s3, hipStream_t st);
-size_t wgrad_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool pair = false);  // pair: of wgrad_pair
+size_t wgrad_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool carrying = false);  // carrying: of wgrad_pair with a data gradient
 // writes per-split partials to `part` and their sum to dw ([cout][cin][taps])
 hipError_t wgrad(const void* a, int64_t a_ld, const void* g, int64_t g_ld, bool g_f32, float* part, float* dw, int n,
                  int cin, int cout, int h, int w, int taps, const float2* fold, hipStream_t st);

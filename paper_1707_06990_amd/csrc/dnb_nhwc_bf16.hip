@@ -869,8 +869,8 @@ static int wgrad_splits(int n, int cin, int cout, int h, int w) {
   const int64_t tps = (tiles + s - 1) / s;
   return (int)((tiles + tps - 1) / tps);
 }
-size_t wgrad_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool pair) {
-  const size_t f = wgrad_fast_partial_floats(n, cin, cout, h, w, taps, pair);
+size_t wgrad_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool carrying) {
+  const size_t f = wgrad_fast_partial_floats(n, cin, cout, h, w, taps, carrying);
   return f ? f : (size_t)wgrad_splits(n, cin, cout, h, w) * cin * cout * taps;
 }
 

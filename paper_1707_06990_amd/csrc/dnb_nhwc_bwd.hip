@@ -9,8 +9,8 @@
 // The last is a role of the weight-gradient launch (dnb_nhwc_wgrad.hip), which only needs db_l too, and takes
 // layers in pairs: layer l-1 needs of layer l only its own slice of the slab, so beside layer l's weight
 // gradients only those k channels are formed, and beside layer l-1's the channels of both layers below, in one
-// pass over the slab.  Three launches a layer, and 6 bytes per element of a layer's concatenated input instead of
-// 10.
+// pass over the slab.  Three launches a layer, and 5 bytes per element of a layer's concatenated input instead of
+// 10.  (One at a time where a block has no room for the second gradient of a b_l that a pair keeps, the same role.)
 //
 // BN1's backward is  du = s*(dz - dbeta/P - xhat*dgamma/P),  dz = the masked gradient, s = gamma*istd.
 // Its first term needs no sum, so it is added into the slab where dz is formed; the other two are

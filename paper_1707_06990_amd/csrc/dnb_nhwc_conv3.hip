@@ -222,7 +222,9 @@ __global__ __launch_bounds__(512, (MG > 1 && !FOLD ? 4 : 2)) void k_conv3(Conv3A
 }  // namespace
 
 // The 3x3 with statistics; false (nothing launched) if the shape is not taken: a staged tile of more than
-// 76 KB (two workgroups no longer share a CU's LDS).  M-tiles per workgroup: as few as keep the launch within
+// 76 KB, or more than one workgroup per CU of which no two share a CU's LDS (six layers' forward at batch 16, 192
+// channels: 62x62 to 48 of them 454 us against k_conv's 434, 60x60 to 64 466 against 438; 61x61 to 48, the last
+// that share, 389 against 431).  M-tiles per workgroup: as few as keep the launch within
 // a workgroup per CU, each staging the tile again (14x14, 192 -> 48: one 12.3 us, two 8.6, three 9.4), and all
 // of them, up to four, where tiles alone fill the chip.  Wp: packed weights, nine taps
 // of [M16][K32]; *sT = partials per channel.
@@ -246,12 +248,13 @@ bool conv3_stats(const void* in, int64_t in_ld, const void* Wp, void* out, int64
     if (A.cap * F->T > 16384) return false;  // 32 partials a thread: at 49 a launch of k_bn_fold is faster again
     if (lds < 2 * 512 * sizeof(float2)) lds = 2 * 512 * sizeof(float2);
   }
-  if (sT) *sT = A.tiles;
   const int mtiles = A.M16 / 16;
   int mg = 1;
   const int most = mtiles < 4 ? mtiles : mtiles % 3 == 0 ? 3 : 4;
   while (mg < most && tiles * ((mtiles + mg - 1) / mg) > 256) ++mg;
   A.gy = (mtiles + mg - 1) / mg;
+  if (tiles * A.gy > 256 && (A.gy > 1 || 2 * (lds + (size_t)mg * 4 * 64 * sizeof(uint2)) > 160 * 1024)) return false;
+  if (sT) *sT = A.tiles;
   const dim3 grid((unsigned)((A.tiles + 7) / 8 * 8 * A.gy));
 #define DNB_C3(MG)                                                                              \
   do {                                                                                          \

@@ -368,7 +368,7 @@ __device__ __forceinline__ void sum_body(const SumArgs& s, int wg, float4* red) 
 // of dz and dz*(x - mean): see dnb_nhwc_bwd.hip.  Bound by the slab's traffic: 10 bytes per element (x 2, G 4 + 4)
 // against 2*B flops, so two layers that both read a channel are done in one pass (the upper one's share of the
 // lower one's own slice goes first, beside the upper one's weight gradients, and only that delays the chain):
-// 6 bytes per element and layer, and no launch of its own.
+// 5 bytes per element and layer, and no launch of its own.
 struct D1Args {
   int nl, n, cols, T, nk;         // layers; workgroups (cols x T); K-steps of 32 outputs
   const u16* db[2]; const u16* W[2];
@@ -574,9 +574,10 @@ __global__ __launch_bounds__(256) void k_wgrad_sums(SumArgs s1, SumArgs s3) {
 // Workgroups of the 1x1 and of the 3x3.  A split costs a partial of the whole weight tensor: the
 // lower bounds fill the chip, the upper ones apply where a split still has eight tiles (large images,
 // small partials).  Not sharp: lower bounds of 192..512 and 64..256, upper ones of 512..1024 and
-// 256..768 moved the DenseNet-264-shaped step between 16.03 and 16.35 ms; in the launch of a pair, whose other
-// roles fill the chip too, 512 at most for the 1x1 (a transition's gradient by itself: 260 us with 512, 111 with 1024).
-constexpr int WG1_MIN = 256, WG1_MAX = 1024, WG1_PAIR_MAX = 512, WG3_MIN = 128, WG3_MAX = 256, LONG_TILES = 8;
+// 256..768 moved the DenseNet-264-shaped step between 16.03 and 16.35 ms; beside a data gradient, whose workgroups
+// fill the chip too, 512 at most for the 1x1 (a transition's gradient by itself: 260 us with 512, 111 with 1024; blocks
+// of more than 256 outputs, whose data gradient has a launch of its own: 2 to 5 % of a step).
+constexpr int WG1_MIN = 256, WG1_MAX = 1024, WG1_CARRYING_MAX = 512, WG3_MIN = 128, WG3_MAX = 256, LONG_TILES = 8;
 
 int splits_for(int tiles, int cols, int lo, int hi) {
   int s = lo / cols, s2 = hi / cols;
@@ -654,10 +655,10 @@ SumArgs sum_args(WgradSum* s) {
 // pixel indexes (with a halo) are 32-bit in these kernels
 static bool fits(int n, int h, int w) { return (int64_t)n * h * w < (int64_t)1 << 30; }
 
-size_t wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool pair) {
+size_t wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool carrying) {
   if (!fits(n, h, w)) return 0;
   const int P = n * h * w;
-  if (taps == 1) return plan1(P, cin, cout, pair ? WG1_PAIR_MAX : WG1_MAX).floats;
+  if (taps == 1) return plan1(P, cin, cout, carrying ? WG1_CARRYING_MAX : WG1_MAX).floats;
   const Plan3 p = plan3(P, w, cin, cout);
   return p.ok ? p.floats : 0;
 }
@@ -717,7 +718,7 @@ bool wgrad_pair(const WgradIn& w1, const WgradIn& w3, int n, int h, int w, Wgrad
                 int most_splits, int* T1, hipStream_t st) {
   if (!fits(n, h, w)) return false;
   const int P = n * h * w;
-  const Plan1 p1 = plan1(P, w1.cin, w1.cout, WG1_PAIR_MAX);
+  const Plan1 p1 = plan1(P, w1.cin, w1.cout, d1.nl ? WG1_CARRYING_MAX : WG1_MAX);
   const Plan3 p3 = plan3(P, w, w3.cin, w3.cout);
   if (!p3.ok || (w1.fold != nullptr) != (w3.fold != nullptr)) return false;
   const Wg1Args A1 = args1(p1, w1, P);
