@@ -1,6 +1,6 @@
 // fp32 / NCHW backward chain of a bottleneck layer, the part behind the 3x3 data gradient:
 //
-//   k_dgrad3_v4 / _v5 / _v3   (dnb_conv_f32_fast.hip) 3x3 data gradient, BN2's mask and sums
+//   k_dgrad3_v4 / _wpm / _v3  (dnb_conv_f32_fast.hip) 3x3 data gradient, BN2's mask and sums
 //   k_bn_bwd_apply            gradient of b_l, element-wise on P x B
 //   k_dgrad1 / s / p          1x1 data gradient; BN1+ReLU backward and the concatenation's backward
 //                             (accumulate into the slab G) in the epilogue, with BN1's two sums.  Where the slab

@@ -794,7 +794,7 @@ __global__ __launch_bounds__(256, 2) void k_dgrad3_v4(const float* in, int64_t i
 // DenseNet-BC-250 step 38.0 -> 36.9 ms.  Bound by the first tile's loads and the last one's stores: a workgroup has
 // two tiles at most there, and the products alone are 17 us at 32x32.
 template <int NW, int NK, int W>
-__global__ __launch_bounds__(NW * 64, NW == 6 && NK == 6 ? 3 : 2) void k_dgrad3_v5(
+__global__ __launch_bounds__(NW * 64, NW == 6 && NK == 6 ? 3 : 2) void k_dgrad3_wpm(
     const float* __restrict__ in, int64_t in_stride, const float* __restrict__ Wp, int Mpad, int Kpad, float* __restrict__ out,
     int64_t out_stride, int cin, int cout, int H, int tiles_per_img, int total_tiles, Bwd3Args bw) {
   extern __shared__ float lds[];
@@ -1653,7 +1653,7 @@ bool launch_conv_fast(const float* in, int64_t in_stride, const float* packed, f
 
 struct Bwd3Plan {
   bool v4;
-  int v5;  // waves of k_dgrad3_v5, or 0
+  int wpm;  // waves of k_dgrad3_wpm, or 0
   int mt, nw, gy, CS, T2;
   size_t lds;
 };
@@ -1669,7 +1669,7 @@ static Bwd3Plan plan_bwd3(int n, int h, int w, int k, int B) {
   }
   if (mtiles > 4 && mtiles <= 8 && k > 16 && k <= 32 && (w == 8 || w == 16 || w == 32) && hw % 64 == 0 && hw <= 1 << 20) {
     const int64_t tiles = (int64_t)(hw / 64) * n;
-    p.v5 = mtiles <= 6 ? 6 : 8;
+    p.wpm = mtiles <= 6 ? 6 : 8;
     p.T2 = tiles < kV4Workgroups ? (int)(tiles + 7) / 8 * 8 : kV4Workgroups;
     p.lds = ((size_t)2 * ((k <= 24 ? 24 : 32) * 144 + 4)) * sizeof(float);
     return p;
@@ -1714,14 +1714,14 @@ hipError_t bwd32_dgrad3(const Bwd32Layer& L, int* T2, hipStream_t st) {
 #undef DNB_L
     return hipGetLastError();
   }
-  if (p.v5) {
+  if (p.wpm) {
     const int tpi = hw / 64;
     const dim3 grid((unsigned)p.T2);
 #define DNB_L(NW, NK, WW)                                                                                               \
-  hipLaunchKernelGGL((k_dgrad3_v5<NW, NK, WW>), grid, dim3(NW * 64), p.lds, st, in, L.ys, L.pk3t, M16, K16, L.db,        \
+  hipLaunchKernelGGL((k_dgrad3_wpm<NW, NK, WW>), grid, dim3(NW * 64), p.lds, st, in, L.ys, L.pk3t, M16, K16, L.db,        \
                      A.b_stride, L.k, L.B, L.h, tpi, tpi * L.n, A)
 #define DNB_LW(NW, NK) do { if (L.w == 32) DNB_L(NW, NK, 32); else if (L.w == 16) DNB_L(NW, NK, 16); else DNB_L(NW, NK, 8); } while (0)
-    if (p.v5 == 6) { if (L.k <= 24) DNB_LW(6, 6); else DNB_LW(6, 8); }
+    if (p.wpm == 6) { if (L.k <= 24) DNB_LW(6, 6); else DNB_LW(6, 8); }
     else { if (L.k <= 24) DNB_LW(8, 6); else DNB_LW(8, 8); }
 #undef DNB_LW
 #undef DNB_L

@@ -137,7 +137,7 @@ def test_every_access_of_the_persistent_3x3_kernel_is_in_bounds(n, cin, cout, H,
 
 
 def check_wave_per_m_tile(n, cin, cout, H, W):
-    """k_dgrad3_v5: NW waves of one M-tile each over the 64 pixels of a tile, 4*NK staged channels."""
+    """k_dgrad3_wpm: NW waves of one M-tile each over the 64 pixels of a tile, 4*NK staged channels."""
     HW=H*W; M16=(cout+15)//16*16; K16=(cin+15)//16*16; NW=6 if M16<=96 else 8; NK=6 if cin<=24 else 8
     assert 64<cout<=128 and 16<cin<=32 and W in (8,16,32) and HW%64==0
     NT=NW*64; ROWS=4*NK; RW=W+4; TR=64//W; NR=TR+2; W4=W//4; CS=144; PER=NR*W4; TOTAL=ROWS*PER; U=(TOTAL+NT-1)//NT
