@@ -778,7 +778,9 @@ Dgrad3Plan plan_dgrad3(int n, int h, int w, int k, int B) {
     p.lds = (size_t)2 * (seg + 1) * (32 * p.ks + 8) * sizeof(u16);
     p.gy = (mtiles + 7) / 8;
     p.tiles = (int)P;
-    int most = 256 / p.gy;
+    // workgroups per XCD, not per chip: the gy of a tile share one, and with 85 x 3 five XCDs had 33 for their 32 CUs
+    // (10800 pixels, 8 to 288 channels: 19.5 us a launch for 10)
+    int most = 32 / p.gy * 8;
     if (most < 1) most = 1;
     const int per = (T + most - 1) / most;
     p.T2 = (T + per - 1) / per;
