@@ -398,8 +398,8 @@ __global__ __launch_bounds__(512) void k_dgrad3s(Dgrad3Args A, int T, DivBy dhw,
   };
   request(pw);
 
-  // two groups share the M-tiles evenly (192 channels: six and six, not eight and four: 56x56 block 1010 -> 987 us a step)
-  const int mtiles = A.M16 >> 4, per = A.gy == 2 ? (mtiles + 1) / 2 : 8, mt = grp * per + wave;
+  // the groups share the M-tiles evenly (192 channels: six and six, not eight and four: 56x56 block 1010 -> 987 us a step)
+  const int mtiles = A.M16 >> 4, per = (mtiles + A.gy - 1) / A.gy, mt = grp * per + wave;
   const int mch = mt * 16 + 4 * g, mc = min(mch, A.B - 4);
   const bool m_ok = wave < per && mt < mtiles;  // uniform
   V8 wv[9][KS];
