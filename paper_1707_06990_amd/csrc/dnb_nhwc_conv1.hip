@@ -255,17 +255,15 @@ __global__ __launch_bounds__((NC + NP) * 64) void k_conv1(Conv1Args A) {
 // Output M-tiles per workgroup, 0 if the shape is not taken: 4 or 6, whichever first gives at most one
 // workgroup per CU, counted on the XCD that gets most (tiles are dealt to the eight in turn, all groups of a tile to
 // one; with 83 tiles x 3 groups, 249 workgroups, three XCDs had 33 for 32 CUs: 384 + 48 l channels, 192 outputs, eight
-// layers' forward 281 us, with two groups 233), else on the whole chip (the many groups of a transition fit few XCDs
-// evenly).  (More tiles: several of k_conv's smaller workgroups share a CU and cover one another's latencies;
-// 25088 pixels x 320 channels x 128 outputs 11 us there, 14.6 us here.)
+// layers' forward 281 us, with two groups 233).  More tiles: several of k_conv's smaller workgroups share a CU and
+// cover one another's latencies (25088 pixels x 320 channels x 128 outputs 11 us there, 14.6 us here; 83 tiles, 288
+// outputs, which are three groups at the least, eight layers' forward from 104 channels 350 us there, 375 here).
 static int conv1_group(int64_t P, int64_t in_ld, int cout) {
   const int64_t T = (P + 63) / 64;
   const int mtiles = (cout + 15) / 16;
   if (in_ld >= (1 << 24)) return 0;  // 32-bit offsets inside a tile
   for (int nc : {4, 6})
     if ((T + 7) / 8 * ((mtiles + nc - 1) / nc) <= 32) return nc;
-  for (int nc : {4, 6})
-    if (T * ((mtiles + nc - 1) / nc) <= 256) return nc;
   return 0;
 }
 

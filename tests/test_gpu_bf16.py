@@ -526,6 +526,8 @@ FEW_PIXEL_CFGS = [wl.BlockCfg(3, 392, 7, 7, 2, 8, 40), wl.BlockCfg(2, 520, 6, 6,
                   wl.BlockCfg(20, 24, 15, 15, 3, 16, 64), wl.BlockCfg(9, 40, 13, 13, 3, 24, 96), wl.BlockCfg(13, 8, 13, 13, 3, 64, 128),
                   # tiles that fill the chip with three groups a tile, but overfill some XCDs, and one that does not
                   wl.BlockCfg(83, 72, 8, 8, 1, 8, 192), wl.BlockCfg(80, 72, 8, 8, 1, 8, 192),
+                  # three groups a tile at the least: the chunked kernel, also where layers before it left partials
+                  wl.BlockCfg(83, 72, 8, 8, 2, 8, 208),
                   # more tiles than CUs: the widest row of which two workgroups share a CU's LDS, the first that goes to
                   # the chunked kernel
                   wl.BlockCfg(260, 8, 1, 61, 1, 48, 192), wl.BlockCfg(260, 8, 1, 62, 1, 48, 192)]
