@@ -333,7 +333,7 @@ __device__ __forceinline__ void conv3x3_v3_body(
     const float* __restrict__ in, int64_t in_stride, const float* __restrict__ Wp, int Mpad,
     int Kpad, float* __restrict__ out, int64_t out_stride, int cin, int cout, int H, int W, int CS,
     const float2* __restrict__ fold, float* __restrict__ spart, int sT, const Bwd3Args& bw) {
-  extern __shared__ float lds[];
+  extern __shared__ __attribute__((aligned(16))) float lds[];
   __shared__ float coef[3][BWD ? kBwdMaxK : 1];
   const int HW = H * W;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nthr = blockDim.x, nw = nthr >> 6;
@@ -391,7 +391,7 @@ __device__ __forceinline__ void conv3x3_v3_body(
         }
       }
       if (!ok) x = zero4();
-      if (idx < total) *reinterpret_cast<float4*>(&lds[row * CS + 4 * c4]) = x;
+      if (idx < total) lds_st4(&lds[row * CS + 4 * c4], x);
     }
   }
   __syncthreads();
@@ -423,7 +423,7 @@ __device__ __forceinline__ void conv3x3_v3_body(
         for (int ks = 0; ks < 4; ++ks) {
           if (ks < nks) {
             const float* rowp = &lds[(c0 + 4 * ks + g) * CS + base];
-            V[ks] = *reinterpret_cast<const float4*>(rowp);
+            V[ks] = lds_ld4(rowp);
             eL[ks] = maskL ? 0.f : rowp[-1];
             eR[ks] = maskR ? 0.f : rowp[4];
           } else {
@@ -539,7 +539,7 @@ __device__ __forceinline__ void conv3x3_v4_body(
     int Kpad, float* __restrict__ out, int64_t out_stride, int cin, int cout, int H,
     const float2* __restrict__ fold, float* __restrict__ spart, int sT, int tiles_per_img,
     int total_tiles, const Bwd3Args& bw) {
-  extern __shared__ float lds[];
+  extern __shared__ __attribute__((aligned(16))) float lds[];
   __shared__ float coef[3][BWD ? kBwdMaxK : 1];          // the slice's correction
   __shared__ float4 cb[BWD ? MT * 16 : 1];               // BN2's scale, shift, mean
   __shared__ float2 bsum[BWD ? 4 * MT * 16 : 1];
@@ -613,7 +613,10 @@ __device__ __forceinline__ void conv3x3_v4_body(
         }
       }
       if (!(sch[u] < cin && y >= 0 && y < H)) x = zero4();  // channel tail, rows above / below the image
-      if (u * 256 + tid < TOTAL) *reinterpret_cast<float4*>(&lds[boff + slo[u]]) = x;
+      if (u * 256 + tid < TOTAL) {
+        if constexpr (BWD) *reinterpret_cast<float4*>(&lds[boff + slo[u]]) = x;
+        else lds_st4(&lds[boff + slo[u]], x);
+      }
     }
   };
 
@@ -634,7 +637,7 @@ __device__ __forceinline__ void conv3x3_v4_body(
                            : zero4();
 
   // the gaps between staged rows (and the pitch padding) stay zero for the whole kernel
-  for (int i = tid; i < 2 * BUF / 4; i += 256) *reinterpret_cast<float4*>(&lds[4 * i]) = zero4();
+  for (int i = tid; i < 2 * BUF / 4; i += 256) lds_st4(&lds[4 * i], zero4());
 
   float2 bs[BWD ? MT : 1][4];  // this lane's part of BN2's sums
   if constexpr (BWD) {
@@ -797,7 +800,7 @@ template <int NW, int NK, int W>
 __global__ __launch_bounds__(NW * 64, NW == 6 && NK == 6 ? 3 : 2) void k_dgrad3_wpm(
     const float* __restrict__ in, int64_t in_stride, const float* __restrict__ Wp, int Mpad, int Kpad, float* __restrict__ out,
     int64_t out_stride, int cin, int cout, int H, int tiles_per_img, int total_tiles, Bwd3Args bw) {
-  extern __shared__ float lds[];
+  extern __shared__ __attribute__((aligned(16))) float lds[];
   __shared__ float coef[3][kBwdMaxK];
   __shared__ float4 cb[NW * 16];
   constexpr int NT = NW * 64, ROWS = 4 * NK, RW = W + 4, TR = 64 / W, NR = TR + 2, W4 = W / 4, CS = 144;
@@ -849,7 +852,7 @@ __global__ __launch_bounds__(NW * 64, NW == 6 && NK == 6 ? 3 : 2) void k_dgrad3_
           *reinterpret_cast<float4*>((char*)(bw.gl + (int64_t)img * bw.gl_stride) + 4u * (unsigned)(sch[u] * HW + y * W + sgo[u])) = x;
       }
       if (!(sch[u] < cin && y >= 0 && y < H)) x = zero4();
-      if (mine) *reinterpret_cast<float4*>(&lds[boff + slo[u]]) = x;
+      if (mine) lds_st4(&lds[boff + slo[u]], x);
     }
   };
 
@@ -864,7 +867,7 @@ __global__ __launch_bounds__(NW * 64, NW == 6 && NK == 6 ? 3 : 2) void k_dgrad3_
 #pragma unroll
       for (int ks = 0; ks < 4 && 4 * ci + ks < NK; ++ks) w[t][4 * ci + ks] = elem(f, ks);
     }
-  for (int i = tid; i < 2 * BUF / 4; i += NT) *reinterpret_cast<float4*>(&lds[4 * i]) = zero4();
+  for (int i = tid; i < 2 * BUF / 4; i += NT) lds_st4(&lds[4 * i], zero4());
   if (bw.K) bwd_coefs(bw, cin, coef);
   if (tid < NW * 16) {
     const int m = min(tid, cout - 1);
@@ -1033,7 +1036,7 @@ struct Wg1Args {
 // the work of workgroup (bx, by, bz) of the 1x1 weight gradient's grid
 template <int MTW, int CTW, bool PRO, int NST>
 __device__ __forceinline__ void wgrad1x1_body(const Wg1Args& A, int bx, int by, int bz) {
-  extern __shared__ float lds[];
+  extern __shared__ __attribute__((aligned(16))) float lds[];
   const float* __restrict__ a = A.a;
   const float* __restrict__ gout = A.g;
   float* __restrict__ part = A.part;
@@ -1127,14 +1130,127 @@ __device__ __forceinline__ void wgrad1x1_body(const Wg1Args& A, int bx, int by, 
     }
 }
 
+// The wide form, for more than 48 output channels beside a 3x3: a workgroup forms WM*32 x 128 outputs, its four waves
+// WM*16 x 64 each (two by two).  Steps are 32 pixels: both operands' rows (128 bytes of a row, a cache line) go through
+// registers, requested one step ahead, and BN+ReLU into an LDS tile that all waves read, so a row crosses the L2 once
+// for 128 (WM*32) outputs instead of once for 64 (48), and no two waves hold the same tile: nothing is added at the end.
+// What bounds it is the matrix rate less the time between a step's two barriers, which two more workgroups on the CU
+// cover (two tiles and one barrier a step, two workgroups a CU: 34.0 against 33.7 ms a step of DenseNet-BC-250).
+constexpr size_t wide_lds_bytes(int wm) { return (size_t)(wm * 32 + 128) * 32 * sizeof(float); }
+// float offset of pixels 4c..4c+3 of a staged row: neither 16 rows of a column nor a row's 8 columns share a bank
+__device__ __forceinline__ int wide_at(int row, int c) { return row * 32 + ((c ^ row) & 7) * 4; }
+
+template <int WM, bool PRO>
+__device__ __forceinline__ void wgrad1x1_wide_body(const Wg1Args& A, int bx, int by, int bz) {
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  const int cin = A.cin, cout = A.cout, HW = A.HW, spi = A.spi, total_steps = A.total_steps;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r = lane & 15, kk = lane >> 4;
+  const int c0 = by * 128, m0 = bz * (WM * 32);
+  const int s_begin = bx * A.steps_per_wg, s_end = min(total_steps, s_begin + A.steps_per_wg);
+  const int prow = tid >> 3, pc = tid & 7;  // staging: this thread's row of 32 and 16-byte column of 8
+  const int wr0 = (wave >> 1) * (WM * 16), wc0 = (wave & 1) * 64;
+  const bool busy = m0 + wr0 < cout && c0 + wc0 < cin;  // a wave whose outputs all lie outside only stages
+
+  // rows past cout / cin repeat the last one: computed and never stored
+  int goff[WM], aoff[4];
+  float2 fl[4];
+#pragma unroll
+  for (int x = 0; x < WM; ++x) goff[x] = min(m0 + x * 32 + prow, cout - 1) * HW;
+#pragma unroll
+  for (int y = 0; y < 4; ++y) {
+    const int c = min(c0 + y * 32 + prow, cin - 1);
+    aoff[y] = c * HW;
+    fl[y] = PRO ? A.fold[c] : make_float2(1.f, 0.f);
+  }
+  f32x4 acc[WM][4];
+#pragma unroll
+  for (int x = 0; x < WM; ++x)
+#pragma unroll
+    for (int y = 0; y < 4; ++y) acc[x][y] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+  // loads are unconditional at clamped addresses; pixels past the image are zeroed when they are staged
+  float4 G[WM], V[4];
+  int img = s_begin / spi, qs = (s_begin - img * spi) * 32;  // of the step requested next
+  bool ok = true;
+  auto request = [&]() {
+    const int q = qs + 4 * pc;
+    ok = q < HW;
+    const float* g = A.g + (int64_t)img * A.g_stride + min(q, HW - 4);
+    const float* a = A.a + (int64_t)img * A.a_stride + min(q, HW - 4);
+#pragma unroll
+    for (int x = 0; x < WM; ++x) G[x] = ldg4(g + goff[x]);
+#pragma unroll
+    for (int y = 0; y < 4; ++y) V[y] = ldg4(a + aoff[y]);
+    if (img * spi + qs / 32 + 1 < total_steps) {  // (past the end the last step's rows again)
+      qs += 32;
+      if (qs >= HW) { qs = 0; ++img; }
+    }
+  };
+  request();
+  for (int s = s_begin; s < s_end; ++s) {
+    __syncthreads();  // the tile of the last step has been read
+#pragma unroll
+    for (int x = 0; x < WM; ++x) lds_st4(&lds[wide_at(x * 32 + prow, pc)], ok ? G[x] : zero4());
+#pragma unroll
+    for (int y = 0; y < 4; ++y) {
+      float4 v = V[y];
+      if (PRO) {
+        v.x = fmaxf(__fmaf_rn(v.x, fl[y].x, fl[y].y), 0.f);
+        v.y = fmaxf(__fmaf_rn(v.y, fl[y].x, fl[y].y), 0.f);
+        v.z = fmaxf(__fmaf_rn(v.z, fl[y].x, fl[y].y), 0.f);
+        v.w = fmaxf(__fmaf_rn(v.w, fl[y].x, fl[y].y), 0.f);
+      }
+      lds_st4(&lds[wide_at(WM * 32 + y * 32 + prow, pc)], ok ? v : zero4());
+    }
+    __syncthreads();
+    request();
+    if (busy) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        float4 Af[WM], Bf[4];
+#pragma unroll
+        for (int x = 0; x < WM; ++x) Af[x] = lds_ld4(&lds[wide_at(wr0 + x * 16 + r, h * 4 + kk)]);
+#pragma unroll
+        for (int y = 0; y < 4; ++y) Bf[y] = lds_ld4(&lds[wide_at(WM * 32 + wc0 + y * 16 + r, h * 4 + kk)]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int x = 0; x < WM; ++x)
+#pragma unroll
+            for (int y = 0; y < 4; ++y) acc[x][y] = mfma16(elem(Af[x], e), elem(Bf[y], e), acc[x][y]);
+      }
+    }
+  }
+  float* pb = A.part + (int64_t)bx * cout * cin;
+#pragma unroll
+  for (int x = 0; x < WM; ++x)
+#pragma unroll
+    for (int y = 0; y < 4; ++y) {
+      const int c = c0 + wc0 + y * 16 + r;
+#pragma unroll
+      for (int rr = 0; rr < 4; ++rr) {
+        const int m = m0 + wr0 + x * 16 + 4 * kk + rr;
+        if (m < cout && c < cin) pb[(int64_t)m * cin + c] = acc[x][y][rr];
+      }
+    }
+}
+
+// CTW = 8: the wide form
+template <int MTW, int CTW, bool PRO, int NST>
+__device__ __forceinline__ void wgrad1x1_role(const Wg1Args& A, int bx, int by, int bz) {
+  if constexpr (CTW == 8) wgrad1x1_wide_body<MTW, PRO>(A, bx, by, bz);
+  else wgrad1x1_body<MTW, CTW, PRO, NST>(A, bx, by, bz);
+}
+
 template <int MTW, int CTW, bool PRO>
-__global__ __launch_bounds__(256) void k_wgrad1x1_fast(Wg1Args A, SumRole sr, int gx_main) {
+__global__ __launch_bounds__(256, CTW == 8 ? 3 : 1) void k_wgrad1x1_fast(Wg1Args A, SumRole sr, int gx_main) {
   if ((int)blockIdx.x >= gx_main) {  // extra workgroups: a pending sum of another partial buffer
     const int wg = (((int)blockIdx.x - gx_main) * gridDim.y + blockIdx.y) * gridDim.z + blockIdx.z;
     if (wg < sr.wgs) sum_role(sr, wg);
     return;
   }
-  wgrad1x1_body<MTW, CTW, PRO, 2>(A, blockIdx.x, blockIdx.y, blockIdx.z);
+  wgrad1x1_role<MTW, CTW, PRO, 2>(A, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // ------------------------------------------------------------------------------- 3x3 wgrad
@@ -1152,7 +1268,7 @@ struct Wg3Args {
 // the work of workgroup (bx, by, bz) of the 3x3 weight gradient's grid (gy x gz channel groups)
 template <int MTW, int CTW, bool PRO>
 __device__ __forceinline__ void wgrad3x3_body(const Wg3Args& A3, int bx, int by, int bz, int gy, int gz) {
-  extern __shared__ float lds[];
+  extern __shared__ __attribute__((aligned(16))) float lds[];
   const float* __restrict__ a = A3.a;
   const float* __restrict__ gout = A3.g;
   float* __restrict__ part = A3.part;
@@ -1210,7 +1326,7 @@ __device__ __forceinline__ void wgrad3x3_body(const Wg3Args& A3, int bx, int by,
         float4 v = v0[u][i];
         if (PRO) v = bnrelu(v, pf[u]);
         if (!(ch < cin && qq >= 0 && qq < HW)) v = zero4();
-        *reinterpret_cast<float4*>(&lds[row * PA + 4 * c4]) = v;
+        lds_st4(&lds[row * PA + 4 * c4], v);
       }
     }
   } else {
@@ -1224,7 +1340,7 @@ __device__ __forceinline__ void wgrad3x3_body(const Wg3Args& A3, int bx, int by,
         const bool ok = ch < cin && qq >= 0 && qq < HW;
         float4 v = ok ? ldg4(src + qq) : zero4();
         if (PRO && ok) v = bnrelu(v, f);
-        *reinterpret_cast<float4*>(&lds[row * PA + 4 * c4]) = v;
+        lds_st4(&lds[row * PA + 4 * c4], v);
       }
     }
   }
@@ -1290,7 +1406,7 @@ __device__ __forceinline__ void wgrad3x3_body(const Wg3Args& A3, int bx, int by,
           const int x = T / (CTW * 9), y = (T / 9) % CTW, t = T % 9, di = t / 3 - 1, dj = t % 3 - 1;
           if (T == T0 || t % 3 == 0) {  // first tap of this row in the wave's range
             const int o = (y * 16 + r) * PA + pw + 4 + W + di * W;
-            V = *reinterpret_cast<const float4*>(&lds[o]);
+            V = lds_ld4(&lds[o]);
             eL = maskL ? 0.f : lds[o - 1];
             eR = maskR ? 0.f : lds[o + 4];
           }
@@ -1320,7 +1436,7 @@ __device__ __forceinline__ void wgrad3x3_body(const Wg3Args& A3, int bx, int by,
         float4 v = nxt[u];
         if (PRO) v = bnrelu(v, pf[u]);
         if (!okc) v = zero4();
-        *reinterpret_cast<float4*>(&lds[(u * 16 + prow) * PA + ncol]) = v;
+        lds_st4(&lds[(u * 16 + prow) * PA + ncol], v);
       }
       __syncthreads();
     }
@@ -1366,17 +1482,17 @@ __global__ __launch_bounds__(256, 3) void k_wgrad_pair(Wg1Args A1, int gx1, int 
   if (id < n1) {
     // Workgroups go to the 8 XCDs in turn (id % 8), each with an L2 of its own.  All the (c, m)
     // tile columns of one pixel range read the same gradient rows, and the m groups of a c column
-    // the same feature rows: pixel range bx is given to XCD bx % 8 whole, so that these rows come
-    // from HBM once and from that XCD's L2 afterwards (measured HBM bytes per launch 190 -> 176 MB
-    // on DenseNet-BC-100's first block, 776 -> 562 MB on DenseNet-BC-250's).  n1 counts
-    // ceil(gx1 / 8) ranges per XCD; the ids past the last range have no work.
-    const int xcd = id & 7, slot = id >> 3, cols = gy1 * gz1;
-    const int col = slot % cols, bx = (slot / cols) * 8 + xcd;
+    // the same feature rows: every XCD takes an equal, consecutive share of the (range, column) items, so
+    // that these rows come from HBM once (twice where a range is cut) and from that XCD's L2 afterwards
+    // (ranges spread over the XCDs: measured HBM bytes per launch 190 against 176 MB on
+    // DenseNet-BC-100's first block, 776 against 562 MB on DenseNet-BC-250's).
+    const int cols = gy1 * gz1, item = (id & 7) * (n1 >> 3) + (id >> 3);
+    const int bx = item / cols, col = item - bx * cols;
     if (bx >= gx1) return;
     // three operand stages beside the narrow 3x3 tiles of k = 12 nets (37.8 -> 37.5 us per launch on
     // the first dense block of DenseNet-BC-100), two beside the wide ones (157 against 162 us on
     // DenseNet-BC-250's, where the third stage's registers come out of the same two waves per SIMD)
-    wgrad1x1_body<M1, C1, PRO, (M3 == 1 ? 3 : 2)>(A1, bx, col / gz1, col % gz1);
+    wgrad1x1_role<M1, C1, PRO, (M3 == 1 ? 3 : 2)>(A1, bx, col / gz1, col % gz1);
     return;
   }
   id -= n1;
@@ -1753,6 +1869,29 @@ static WgFastPlan plan_wgrad_fast(int n, int cin, int cout, int h, int w, int ta
   p.ok = hw % 4 == 0 && (taps == 1 || (w % 4 == 0 && w >= 4));
   if (!p.ok) return p;
   if (taps == 1) {
+    // More than 48 output channels, beside a 3x3: the wide form, about one workgroup per CU whatever the shape (they share
+    // the matrix cores with the 3x3's; 192 / 320 / 384 / 512 workgroups: 2.3 / 2.2 / 1.3 / 0.9 % more time per
+    // DenseNet-BC-250 step; fewer also keep the partials small).  With the narrow tiles, whose pixel ranges were dealt to
+    // the XCDs whole, few-pixel layers used only three or four of the eight: 90 -> 61 us per launch on average, 62 -> 25 on
+    // the 8x8 block (P = 4096, 750..1700 channels).  A transition's weight gradient, alone on the chip and up to 516
+    // channels wide, is better balanced in narrow tiles (395 + 785 us against 400 + 953).
+    if (!alone && cout > 48 && cin > 64 && (hw % 32 == 0 || hw >= 128)) {
+      p.ctw = 8;
+      p.mtw = 4;  // the fewest rows of padding, then the largest tile
+      for (int wm = 3; wm >= 2; --wm)
+        if ((cout + 32 * wm - 1) / (32 * wm) * wm < (cout + 32 * p.mtw - 1) / (32 * p.mtw) * p.mtw) p.mtw = wm;
+      p.gy = (cin + 127) / 128;
+      p.gz = (cout + 32 * p.mtw - 1) / (32 * p.mtw);
+      p.spi = (hw + 31) / 32;
+      p.total_steps = n * p.spi;
+      int gx = 256 / (p.gy * p.gz);
+      if (gx < 1) gx = 1;
+      p.steps_per_wg = (p.total_steps + gx - 1) / gx;
+      if (p.steps_per_wg < 4) p.steps_per_wg = 4;
+      p.gx = (p.total_steps + p.steps_per_wg - 1) / p.steps_per_wg;
+      p.lds = wide_lds_bytes(p.mtw);
+      return p;
+    }
     p.mtw = mtiles >= 3 ? 3 : mtiles;
     p.ctw = ctiles >= 4 ? 4 : ctiles;
     p.gy = (ctiles + p.ctw - 1) / p.ctw;
@@ -1859,6 +1998,7 @@ bool launch_wgrad_fast(const float* in, int64_t in_stride, const float* g, int64
   } while (0)
     const int key = p.mtw * 10 + p.ctw;
     switch (key) {
+      case 48: DNB_L(4, 8); break; case 38: DNB_L(3, 8); break; case 28: DNB_L(2, 8); break;
       case 34: DNB_L(3, 4); break; case 33: DNB_L(3, 3); break; case 32: DNB_L(3, 2); break; case 31: DNB_L(3, 1); break;
       case 24: DNB_L(2, 4); break; case 23: DNB_L(2, 3); break; case 22: DNB_L(2, 2); break; case 21: DNB_L(2, 1); break;
       case 14: DNB_L(1, 4); break; case 13: DNB_L(1, 3); break; case 12: DNB_L(1, 2); break; default: DNB_L(1, 1); break;
@@ -1919,30 +2059,31 @@ bool launch_wgrad_pair_fast(const float* in1, int64_t in1_stride, const float* g
       !aligned16(in3) || !aligned16(g3))
     return false;
   const WgFastPlan p1 = plan_wgrad_fast(n, cin1, B, h, w, 1), p3 = plan_wgrad_fast(n, B, cout3, h, w, 9);
-  if (!p1.ok || !p3.ok || p1.mtw != 3) return false;
+  if (!p1.ok || !p3.ok || (p1.mtw != 3 && p1.ctw != 8)) return false;
   const int key3 = p3.mtw * 10 + p3.ctw;
   if (key3 != 13 && key3 != 22) return false;
   const SumRole s1 = make_sum_role(absorb1), s3 = make_sum_role(absorb3);
   const int hw = h * w;
   const Wg1Args A1{in1, in1_stride, g1, g1_stride, part1, cin1, B, hw, p1.spi, p1.total_steps, p1.steps_per_wg, fold1};
   const Wg3Args A3{in3, in3_stride, g3, g3_stride, part3, B, cout3, h, w, p3.tiles_per_img, p3.nms, p3.PA, fold3};
-  const int n1 = (p1.gx + 7) / 8 * 8 * p1.gy * p1.gz, n3 = p3.gx * p3.gy * p3.gz;  // 1x1: whole pixel ranges per XCD
+  const int n1 = (p1.gx * p1.gy * p1.gz + 7) / 8 * 8, n3 = p3.gx * p3.gy * p3.gz;  // 1x1: whole pixel ranges per XCD
   const BnBwdPartialArgs bna = bn ? *bn : BnBwdPartialArgs{};
   const int nbn = bn ? bn->c * bn->splits : 0;
   const Bn1Finish fina = fin ? *fin : Bn1Finish{};
   const dim3 grid((unsigned)(n1 + n3 + nbn + fina.wgs + s1.wgs + s3.wgs));
   const size_t lds = p1.lds > p3.lds ? p1.lds : p3.lds;
-#define DNB_P(C1, M3, C3)                                                                                             \
+#define DNB_P(M1, C1, M3, C3)                                                                                             \
   do {                                                                                                                \
-    if (fold1) hipExtLaunchKernelGGL((k_wgrad_pair<3, C1, M3, C3, true>), grid, dim3(256), lds, st, ev0, ev1, 0, A1,  \
+    if (fold1) hipExtLaunchKernelGGL((k_wgrad_pair<M1, C1, M3, C3, true>), grid, dim3(256), lds, st, ev0, ev1, 0, A1,  \
                                      p1.gx, p1.gy, p1.gz, n1, A3, p3.gy, p3.gz, n3, s1, s3, bna, nbn, fina);                       \
-    else hipExtLaunchKernelGGL((k_wgrad_pair<3, C1, M3, C3, false>), grid, dim3(256), lds, st, ev0, ev1, 0, A1, p1.gx, p1.gy, \
+    else hipExtLaunchKernelGGL((k_wgrad_pair<M1, C1, M3, C3, false>), grid, dim3(256), lds, st, ev0, ev1, 0, A1, p1.gx, p1.gy, \
                                p1.gz, n1, A3, p3.gy, p3.gz, n3, s1, s3, bna, nbn, fina);                              \
   } while (0)
 #define DNB_P1(M3, C3)                                                                          \
-  switch (p1.ctw) {                                                                             \
-    case 4: DNB_P(4, M3, C3); break; case 3: DNB_P(3, M3, C3); break; case 2: DNB_P(2, M3, C3); break; \
-    default: DNB_P(1, M3, C3); break;                                                           \
+  switch (p1.mtw * 10 + p1.ctw) {                                                                         \
+    case 48: DNB_P(4, 8, M3, C3); break; case 38: DNB_P(3, 8, M3, C3); break; case 28: DNB_P(2, 8, M3, C3); break; \
+    case 34: DNB_P(3, 4, M3, C3); break; case 33: DNB_P(3, 3, M3, C3); break; case 32: DNB_P(3, 2, M3, C3); break; \
+    default: DNB_P(3, 1, M3, C3); break;                                                                  \
   }
   if (key3 == 13) { DNB_P1(1, 3) } else { DNB_P1(2, 2) }
 #undef DNB_P1

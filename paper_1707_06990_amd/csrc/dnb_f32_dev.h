@@ -14,6 +14,16 @@ __device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) {
 }
 
 __device__ __forceinline__ float4 ldg4(const float* p) { return *reinterpret_cast<const float4*>(p); }
+// 16 bytes of LDS in one instruction.  Through float4, a struct, the compiler takes such an access apart where its
+// elements are used one by one and, knowing only 4-byte alignment of the LDS array, makes pairs of floats of it, which
+// meet banks that the pitches here avoid for 16 bytes.
+__device__ __forceinline__ float4 lds_ld4(const float* p) {
+  const f32x4 v = *reinterpret_cast<const f32x4*>(p);
+  return make_float4(v[0], v[1], v[2], v[3]);
+}
+__device__ __forceinline__ void lds_st4(float* p, const float4& v) {
+  *reinterpret_cast<f32x4*>(p) = (f32x4){v.x, v.y, v.z, v.w};
+}
 __device__ __forceinline__ float4 zero4() { return make_float4(0.f, 0.f, 0.f, 0.f); }
 __device__ __forceinline__ float elem(const float4& v, int e) {
   return e == 0 ? v.x : (e == 1 ? v.y : (e == 2 ? v.z : v.w));
