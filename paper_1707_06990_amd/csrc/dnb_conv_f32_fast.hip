@@ -786,6 +786,197 @@ __global__ __launch_bounds__(256, 2) void k_dgrad3_v4(const float* in, int64_t i
                                                0, tiles_per_img, total_tiles, bw);
 }
 
+// Forward with 49..128 input channels and up to 32 outputs: a persistent workgroup walks over 64-pixel tiles (whole image
+// rows) of one or two M-tiles; its eight waves split the input channels evenly, so each keeps the weights of its 4*NK
+// channels, all taps and M-tiles, in registers, and reads an operand for MT products.  All channels of the tile lie in LDS
+// as in k_conv3x3_v4; the next tile's rows are requested before the products and deposited after them, between the
+// two barriers in which the waves' parts of the sums change hands too.  A wave then adds the eight parts of one
+// 16-pixel tile, in the order of the channels, and keeps its channels' running statistics (Welford, a lane's pixels one
+// by one), which the workgroup joins once at its end.
+// One workgroup fits a CU (LDS), two waves a SIMD.  96 -> 24 channels at batch 64: 40 us at 32x32 (32 of them the products,
+// 24 channels padded to 32), 17.5 at 16x16 and 11 at 8x8, of which 8 are the launch, the first tile and the weights;
+// k_conv3x3_v3, whose four waves got 2, 2, 1 and 1 of the six chunks of 16 channels: 58, 18, 17.5.
+template <int MT, int NK, int W, bool PRO, bool STATS>
+__global__ __launch_bounds__(512, 2) void k_conv3x3_ks(const float* __restrict__ in, int64_t in_stride,
+                                                       const float* __restrict__ Wp, int Mpad, int Kpad,
+                                                       float* __restrict__ out, int64_t out_stride, int cin, int cout,
+                                                       int H, const float2* __restrict__ fold, float* __restrict__ spart,
+                                                       int T, int tiles_per_img, int total_tiles) {
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  __shared__ float sst[STATS ? 8 * 16 * 2 : 1];  // mean and M2 of a wave's 16 channels
+  constexpr int NT = 512, ROWS = 32 * NK, RW = W + 4, TR = 64 / W, NR = TR + 2, W4 = W / 4, CS = 144;
+  static_assert(NR * RW <= CS, "plane pitch");
+  constexpr int PER_PLANE = NR * W4, TOTAL = ROWS * PER_PLANE, U = (TOTAL + NT - 1) / NT, BUF = ROWS * CS + 4;
+  constexpr int S = 9 * NK, RED = BUF;
+  const int HW = H * W, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j = lane & 15, g = lane >> 4;
+  const int m0 = blockIdx.y * (MT * 16);
+  // tiles are dealt to workgroups per XCD (neighbours share halo rows in its L2)
+  const int G = gridDim.x, tpx = (total_tiles + 7) >> 3, wgx = G >> 3;
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int t_lo = xcd * tpx, t_hi = min(total_tiles, t_lo + tpx);
+  int tile = t_lo + slot;
+  // partials: a workgroup's, or a tile's where no workgroup has more than one (T tiles, some workgroups without)
+  const bool per_tile = total_tiles == T;
+  const int pid = per_tile ? tile : (int)blockIdx.x;
+  if (tile >= t_hi) {  // uniform for the workgroup: no tiles, empty statistics
+    if (STATS && !per_tile && tid < MT * 16 && m0 + tid < cout) {
+      float* p = spart + ((int64_t)(m0 + tid) * T + pid) * 3;
+      p[0] = p[1] = p[2] = 0.f;
+    }
+    return;
+  }
+
+  int sch[U], sry[U], sgo[U], slo[U];  // channel, staged row, offset in the image row, LDS offset
+  float2 sf[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int idx = min(u * NT + tid, TOTAL - 1);
+    sch[u] = idx / PER_PLANE;
+    const int rem = idx - sch[u] * PER_PLANE;
+    sry[u] = rem / W4;
+    sgo[u] = 4 * (rem - sry[u] * W4);
+    slo[u] = sch[u] * CS + sry[u] * RW + 4 + sgo[u];
+    if (PRO) sf[u] = fold[min(sch[u], cin - 1)];
+  }
+  auto request = [&](int tl, float4(&v)[U]) {
+    const int img = tl / tiles_per_img, y0 = (tl - img * tiles_per_img) * TR;
+    const float* inb = in + (int64_t)img * in_stride;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      v[u] = ldg4(inb + min(sch[u], cin - 1) * HW + min(max(y0 - 1 + sry[u], 0), H - 1) * W + sgo[u]);
+  };
+  auto deposit = [&](int tl, const float4(&v)[U]) {
+    const int y0 = tl % tiles_per_img * TR;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int y = y0 - 1 + sry[u];
+      float4 x = v[u];
+      if (PRO) {
+        x.x = fmaxf(__fmaf_rn(x.x, sf[u].x, sf[u].y), 0.f); x.y = fmaxf(__fmaf_rn(x.y, sf[u].x, sf[u].y), 0.f);
+        x.z = fmaxf(__fmaf_rn(x.z, sf[u].x, sf[u].y), 0.f); x.w = fmaxf(__fmaf_rn(x.w, sf[u].x, sf[u].y), 0.f);
+      }
+      if (!(sch[u] < cin && y >= 0 && y < H)) x = zero4();  // channel tail, rows above / below the image
+      if (u * NT + tid < TOTAL) lds_st4(&lds[slo[u]], x);
+    }
+  };
+
+  float4 v[U];
+  request(tile, v);
+  float w[S][MT];
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk) {
+      const int ks = wave * NK + kk, kc = min(ks, (Kpad >> 2) - 1);
+#pragma unroll
+      for (int a = 0; a < MT; ++a) {
+        const int mt = min((m0 >> 4) + a, (Mpad >> 4) - 1);  // (rows past Mpad: computed and never stored)
+        const float x = wfrag(Wp + (int64_t)t * Mpad * Kpad, Kpad, mt, kc >> 2)[kc & 3];
+        w[t * NK + kk][a] = ks == kc ? x : 0.f;
+      }
+    }
+  for (int i = tid; i < BUF / 4; i += NT) lds_st4(&lds[4 * i], zero4());  // the gaps between rows stay zero
+  __syncthreads();
+  deposit(tile, v);
+  __syncthreads();
+
+  // pixel 16 t + j: a compile-time offset from pixel j (plane g, staged row 1 + j / W, column 4 + j % W)
+  const int lane_base = (wave * NK * 4 + g) * CS + (j / W + 1) * RW + 4 + (j % W);
+  const bool owner = wave < 4 * MT;  // of the M-tile wave / 4, pixels 16 (wave % 4) + j
+  float mean[4] = {0.f, 0.f, 0.f, 0.f}, m2[4] = {0.f, 0.f, 0.f, 0.f}, cnt = 0.f;
+  for (; tile < t_hi; tile += wgx) {
+    const int nxt = tile + wgx;
+    const bool more = nxt < t_hi;
+    if (more) request(nxt, v);
+    f32x4 acc[MT][4];
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc[a][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    // operands two steps ahead of their products, held there by scheduling barriers (see k_dgrad3_wpm)
+    float b[3][4];
+    auto operands = [&](int s, float(&o)[4]) {
+      const int t9 = s / NK, kk = s % NK;
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        o[t] = lds[lane_base + 4 * kk * CS + (t9 / 3 - 1 + 16 * t / W) * RW + t9 % 3 - 1 + 16 * t % W];
+    };
+    operands(0, b[0]);
+    operands(1, b[1]);
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      if (s + 2 < S) operands(s + 2, b[(s + 2) % 3]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[a][t] = mfma16(w[s][a], b[s % 3][t], acc[a][t]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();  // the tile has been read, and the parts of the one before
+    if (more) deposit(nxt, v);
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        *reinterpret_cast<f32x4*>(&lds[RED + (((a * 4 + t) * 8 + wave) * 64 + lane) * 4]) = acc[a][t];
+    __syncthreads();
+    if (owner) {
+      f32x4 p[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) p[i] = *reinterpret_cast<const f32x4*>(&lds[RED + ((wave * 8 + i) * 64 + lane) * 4]);
+      f32x4 x = p[0];
+#pragma unroll
+      for (int i = 1; i < 8; ++i) x += p[i];
+      const int img = tile / tiles_per_img, q = (tile - img * tiles_per_img) * 64 + 16 * (wave & 3) + j;
+      const int m = m0 + (wave >> 2) * 16 + 4 * g;
+      float* ob = out + (int64_t)img * out_stride + (int64_t)m * HW + q;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (m + r < cout) ob[r * HW] = x[r];
+      if (STATS) {
+        cnt += 1.f;
+        const float rc = 1.f / cnt;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float d = x[r] - mean[r];
+          mean[r] = __fmaf_rn(d, rc, mean[r]);
+          m2[r] = __fmaf_rn(d, x[r] - mean[r], m2[r]);
+        }
+      }
+    }
+  }
+  if (STATS) {
+    // equal counts everywhere: 16 lanes, then the four waves of an M-tile
+    if (owner) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float mu = row16_sum(mean[r]) * 0.0625f, d = mean[r] - mu;
+        const float q2 = row16_sum(__fmaf_rn(cnt * d, d, m2[r]));
+        if (j == 0) { sst[(wave * 16 + 4 * g + r) * 2] = mu; sst[(wave * 16 + 4 * g + r) * 2 + 1] = q2; }
+      }
+    }
+    if (tid == 0) lds[0] = cnt;
+    __syncthreads();
+    if (tid < MT * 16 && m0 + tid < cout) {
+      const float n16 = 16.f * lds[0];
+      float mu = 0.f, q2 = 0.f;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) mu += sst[(((tid >> 4) * 4 + t) * 16 + (tid & 15)) * 2];
+      mu *= 0.25f;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const float* e = &sst[(((tid >> 4) * 4 + t) * 16 + (tid & 15)) * 2];
+        const float d = e[0] - mu;
+        q2 += __fmaf_rn(n16 * d, d, e[1]);
+      }
+      float* p = spart + ((int64_t)(m0 + tid) * T + pid) * 3;
+      p[0] = 4.f * n16; p[1] = mu; p[2] = q2;
+    }
+  }
+}
+
 // 3x3 data gradient of the backward chain for k = 17 ... 32 and B = 65 ... 128: the persistent form again, with a wave
 // per M-tile.  k_dgrad3_v3 took 32 us a launch on DenseNet-BC-250 (k = 24, B = 96) against 10 us of products: two
 // M-tiles for each of four waves are eight where there are six, k pads to 32, and a tile's loads, products and
@@ -1731,6 +1922,39 @@ bool launch_conv_fast(const float* in, int64_t in_stride, const float* packed, f
 #undef DNB_L4
     return true;
   }
+  // K split over eight waves with the weights in registers: 49..96 input channels, where a launch takes 40 us instead of
+  // 60 (96 -> 24 channels, 65536 pixels), 17.5 instead of 18 (16384), 11 instead of 17.5 (4096); 64 -> 16: 20 instead of 34
+  // (65536); with 97..128 channels only up to 128 tiles (128 -> 32: 4096 pixels 14.8 us instead of 19.3, but 16384 24.4
+  // instead of 20.5 and 65536 58 instead of 59).
+  if (mtiles <= 2 && cin > 48 && (cin <= 96 || (cin <= 128 && (int64_t)hw * n <= 128 * 64)) &&
+      (w == 8 || w == 16 || w == 32) && hw % 64 == 0 && hw <= 1 << 20) {
+    const int tpi = hw / 64, total_tiles = tpi * n, nk = (cin + 31) / 32;
+    const int G = total_tiles < 256 ? (total_tiles + 7) / 8 * 8 : 256;
+    const int mt = mtiles == 2 && total_tiles > 128 ? 2 : 1;
+    const dim3 grid((unsigned)G, (unsigned)(mtiles / mt));
+    const size_t lds = ((size_t)nk * 32 * 144 + 4 + mt * 4 * 8 * 256) * sizeof(float);
+    const int T = total_tiles < 256 ? total_tiles : 256;
+    if (sT) *sT = T;
+#define DNB_LK(MT, NK, WW, PRO, STATS)                                                                      \
+  hipExtLaunchKernelGGL((k_conv3x3_ks<MT, NK, WW, PRO, STATS>), grid, dim3(512), lds, st, ev0, ev1, 0, in, \
+                        in_stride, packed, M16, K16, out, out_stride, cin, cout, h, fold, spart, T, tpi, total_tiles)
+#define DNB_LKM(MT, NK, WW)                                      \
+  do {                                                           \
+    if (mode == 2) DNB_LK(MT, NK, WW, true, true);                \
+    else if (mode == 1) DNB_LK(MT, NK, WW, false, true);          \
+    else DNB_LK(MT, NK, WW, false, false);                        \
+  } while (0)
+#define DNB_LKW(MT, NK)                                                                              \
+  do {                                                                                               \
+    if (w == 32) DNB_LKM(MT, NK, 32); else if (w == 16) DNB_LKM(MT, NK, 16); else DNB_LKM(MT, NK, 8); \
+  } while (0)
+    if (mt == 2) { if (nk == 2) DNB_LKW(2, 2); else DNB_LKW(2, 3); }
+    else { if (nk == 2) DNB_LKW(1, 2); else if (nk == 3) DNB_LKW(1, 3); else DNB_LKW(1, 4); }
+#undef DNB_LKW
+#undef DNB_LKM
+#undef DNB_LK
+    return true;
+  }
   const bool ksplit = nchunks >= 3;
   int nw, mt, gy;
   if (ksplit) {
@@ -1887,7 +2111,7 @@ static WgFastPlan plan_wgrad_fast(int n, int cin, int cout, int h, int w, int ta
       int gx = 256 / (p.gy * p.gz);
       if (gx < 1) gx = 1;
       p.steps_per_wg = (p.total_steps + gx - 1) / gx;
-      if (p.steps_per_wg < 4) p.steps_per_wg = 4;
+      if (p.steps_per_wg < 8) p.steps_per_wg = 8;
       p.gx = (p.total_steps + p.steps_per_wg - 1) / p.steps_per_wg;
       p.lds = wide_lds_bytes(p.mtw);
       return p;

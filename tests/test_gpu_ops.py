@@ -226,6 +226,17 @@ def test_fused_conv_bnrelu_forward_and_statistics(dnb, oracle, n, cin, cout, h, 
     assert_close(m2 / (n * hw), ref.var(axis=(0, 2, 3)), TOL, "variance")
 
 
+@pytest.mark.parametrize("n,cin,cout,h,w", [(1, 49, 12, 8, 8), (9, 64, 16, 8, 8), (3, 65, 17, 16, 16), (33, 96, 24, 16, 16),
+                                            (17, 96, 32, 32, 32), (5, 97, 20, 8, 16), (2, 128, 32, 32, 32), (128, 128, 7, 8, 8),
+                                            (70, 52, 13, 32, 16), (65, 72, 31, 16, 32)])
+def test_3x3_with_its_channels_split_over_eight_waves(dnb, oracle, n, cin, cout, h, w):
+    """The 3x3 of 49..128 input channels at its edges: channel tails, one and two M-tiles, workgroups without a tile, with
+    one, and with several of different images; values and joined statistics with BN+ReLU of the input, and the plain
+    forward call."""
+    test_fused_conv_bnrelu_forward_and_statistics(dnb, oracle, n, cin, cout, h, w, 3)
+    test_conv_forward_dgrad_wgrad(dnb, oracle, n, cin, cout, h, w, 3)
+
+
 def fma32(a, b, c):
     """round(a*b + c) to fp32: the product of two fp32 values is exact in fp64, the sum in extended precision."""
     return (np.longdouble(a) * np.longdouble(b) + np.longdouble(c)).astype(np.float32)
