@@ -207,10 +207,10 @@ int forward_bf16(dnb_block* b, const void* x0, const float* params, void* yv, ch
       void* S1 = ws + b->off_u[l];
       void* S2 = ws + b->off_a[l];
       void* S3 = ws + b->off_a2[l];
-      DNB_TRY(nhwc::bn_relu_rows(y, cout, fold1, S2, c, S1, c, P, c, st));  // concat -> storage 1, BN+ReLU -> storage 2
+      DNB_TRY(nhwc::bn_relu_rows({y, cout, fold1, S2, c, S1, c, c}, nullptr, P, st));  // concat -> storage 1, BN+ReLU -> storage 2
       DNB_TRY(nhwc::conv(S2, c, false, pk1, bl, B, n, c, B, d.h, d.w, 1, nullptr, part, &T1, st));
       DNB_TRY(launch_bn_fold(p.g2, p.b2, mean_b, istd_b, part, T1, 0, B, d.eps, B, fold2, st, T1 <= kRowStats));
-      DNB_TRY(nhwc::bn_relu_rows(bl, B, fold2, S3, B, nullptr, 0, P, B, st));
+      DNB_TRY(nhwc::bn_relu_rows({bl, B, fold2, S3, B, nullptr, 0, B}, nullptr, P, st));
       DNB_TRY(nhwc::conv(S3, B, false, pk3, y + c, cout, n, B, k, d.h, d.w, 9, nullptr, part, &T3, st));
     }
     freshT = T3; fresh_lo = c; fresh_hi = c + k;
@@ -309,8 +309,8 @@ int backward_bf16(dnb_block* b, const void* yv, const void* dy, void* dx0, float
     DNB_TRY(nhwc::bwd_dgrad3(L, st));
     if (L.above.n && L.above.base == 0) L.K_set = true;  // (a slice's own sums leave nothing below it)
     if (recompute) {
-      DNB_TRY(nhwc::bn_relu_rows(L.b, B, L.fold2, S3, B, nullptr, 0, P, B, st));
-      DNB_TRY(nhwc::bn_relu_rows(y, cout, L.fold1, S2, c, S1, c, P, c, st));
+      const nhwc::BnReluRows s3{L.b, B, L.fold2, S3, B, nullptr, 0, B};
+      DNB_TRY(nhwc::bn_relu_rows({y, cout, L.fold1, S2, c, S1, c, c}, &s3, P, st));
     }
     // what this layer's 1x1 data gradient forms now: the lower layer's slice, both layers' channels below, or its own
     nhwc::Dgrad1In d1 = far;
@@ -419,10 +419,8 @@ int backward_f32(dnb_block* b, const float* params, const float* y, const float*
     DNB_TRY(launch_bn_bwd_apply(bl, (int64_t)B * hw, L.db, (int64_t)B * hw, L.db, (int64_t)B * hw, n, B, hw, p.g2, p.b2, mean_b,
                                 mean_b + B, gp.g2, gp.b2, (const float*)L.part2, T2, st));
     if (recompute) {
-      DNB_TRY(launch_bn_relu(bl, (int64_t)B * hw, S3, (int64_t)B * hw, nullptr, 0, n, B, hw, p.g2, p.b2,
-                             StatsSrc{mean_b, mean_b + B, nullptr, 0, 0, 0, d.eps}, st));
-      DNB_TRY(launch_bn_relu(y, ys, S2, (int64_t)c * hw, S1, (int64_t)c * hw, n, c, hw, p.g1, p.b1,
-                             StatsSrc{mean_y, istd_y, nullptr, 0, 0, 0, d.eps}, st));
+      DNB_TRY(launch_bn_relu_two(y, ys, S2, (int64_t)c * hw, S1, (int64_t)c * hw, c, p.g1, p.b1, mean_y, istd_y, bl,
+                                 (int64_t)B * hw, S3, (int64_t)B * hw, B, p.g2, p.b2, mean_b, mean_b + B, n, hw, st));
     }
     DNB_TRY(bwd32_dgrad1(L, st));
     const float* gl = l == m ? dy + (int64_t)c * hw : L.gl;
@@ -1075,7 +1073,8 @@ int dnb_block_backward(dnb_block* b, const void* paramsv, const void* yv, const 
     // ---- chain A: storage 3 and the 3x3 weight gradient.  g_l is complete once layer l+1's
     // BN1 backward has run; storage 3 is free because the previous wgrad ran on this stream.
     if (l < m) DNB_TRY(wait(sA, ev(l + 1, EV_MAIN)));
-    if (recompute)  // re-populate storage 3 from the kept b_l and its cached statistics
+    // (on one stream storage 3 is re-populated with the others, below)
+    if (recompute && conc)  // re-populate storage 3 from the kept b_l and its cached statistics
       DNB_TRY(launch_bn_relu(bl, (int64_t)B * hw, S3, (int64_t)B * hw, nullptr, 0, n, B, hw, p.g2,
                              p.b2, StatsSrc{mean_b, istd_b, nullptr, 0, 0, 0, d.eps}, sA));
     // (the sum of this launch's partials is left to the next layer's launch on this chain).
@@ -1092,9 +1091,12 @@ int dnb_block_backward(dnb_block* b, const void* paramsv, const void* yv, const 
     // ---- chain B, first half: storage 1 and 2.  Storage 1 was last read by layer l+1's BN1
     // backward on the main chain; storage 2 by the previous wgrad on this stream.
     if (l < m) DNB_TRY(wait(sB, ev(l + 1, EV_MAIN)));
-    if (recompute)  // re-populate storage 1 and 2 for this layer
+    if (recompute && conc)  // re-populate storage 1 and 2 for this layer
       DNB_TRY(launch_bn_relu(y, ys, S2, (int64_t)c * hw, S1, (int64_t)c * hw, n, c, hw, p.g1, p.b1,
                              StatsSrc{mean_y, istd_y, nullptr, 0, 0, 0, d.eps}, sB));
+    else if (recompute)  // all three in one launch
+      DNB_TRY(launch_bn_relu_two(y, ys, S2, (int64_t)c * hw, S1, (int64_t)c * hw, c, p.g1, p.b1, mean_y, istd_y, bl,
+                                 (int64_t)B * hw, S3, (int64_t)B * hw, B, p.g2, p.b2, mean_b, istd_b, n, hw, st));
     DNB_TRY(record(ev(l, EV_S12), sB));
 
     // ---- main chain.  dS3 doubles as db_{l+1}, which chain B's wgrad of layer l+1 still reads.

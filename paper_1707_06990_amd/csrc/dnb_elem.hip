@@ -112,16 +112,16 @@ __global__ __launch_bounds__(kThreads) void k_bn_stats_partial(const float* __re
 
 // Finalised statistics of channel ch for the calling workgroup.  Channels in
 // [fresh_lo, fresh_hi) still only have partials ([splits][3] per channel, from the statistics
-// kernel or a convolution epilogue): the workgroup merges them; the one with blockIdx.y == 0
+// kernel or a convolution epilogue): the workgroup merges them; the one with `keep`
 // also stores mean / inverse std so later kernels read them.  Returns (mean, istd) to every thread.
 __device__ __forceinline__ void channel_stats(int ch, float* mean, float* istd, const float* part,
-                                              int splits, int fresh_lo, int fresh_hi, float eps,
+                                              int splits, int fresh_lo, int fresh_hi, float eps, bool keep,
                                               float* sh, float& mu, float& is) {
   if (ch >= fresh_lo && ch < fresh_hi) {  // workgroup-uniform branch
     const Stat3 r = stat_merge_block(part + (int64_t)(ch - fresh_lo) * splits * 3, splits, sh);
     mu = r.m;
     is = bn_istd(r.m2, r.c, eps);
-    if (blockIdx.y == 0 && threadIdx.x == 0) { mean[ch] = mu; istd[ch] = is; }
+    if (keep && threadIdx.x == 0) { mean[ch] = mu; istd[ch] = is; }
   } else {
     mu = mean[ch];
     is = istd[ch];
@@ -143,32 +143,65 @@ __global__ __launch_bounds__(64) void k_bn_stats_finalize(const float* __restric
 
 // ----------------------------------------------------------------------------- BN apply + ReLU
 
-// grid (c, splits).  out = max(0, fma(x, scale, shift)); COPY also writes the raw x (the
-// concatenation into storage 1 and its BN+ReLU into storage 2 in one pass over the features).
+// out = max(0, fma(x, scale, shift)) of one channel over images [s*ipb, min(n, (s+1)*ipb)); COPY also writes the raw x (the
+// concatenation into storage 1 and its BN+ReLU into storage 2 in one pass over the features).  Bound by the copy rate
+// where the slab is large and by memory round trips where it is not: a thread's first position is requested before the
+// channel's statistics, every other before the one ahead of it is stored.
+struct BnReluArgs {
+  const float* x; int64_t x_stride;
+  float* out; int64_t out_stride;
+  float* copy; int64_t copy_stride;
+  int n, hw, ipb;
+  const float *gamma, *beta;
+  float *mean, *istd;
+  const float* part; int splits, fresh_lo, fresh_hi; float eps;
+};
 template <int V, bool COPY>
-__global__ __launch_bounds__(kThreads) void k_bn_relu(
-    const float* __restrict__ x, int64_t x_stride, float* __restrict__ out, int64_t out_stride,
-    float* __restrict__ copy_out, int64_t copy_stride, int n, int hw, int ipb,
-    const float* __restrict__ gamma, const float* __restrict__ beta, float* mean, float* istd,
-    const float* __restrict__ part, int splits, int fresh_lo, int fresh_hi, float eps) {
-  __shared__ float sh[3 * kThreads / 64];
-  const int ch = blockIdx.x, n0 = blockIdx.y * ipb, ni = min(n, n0 + ipb) - n0;
+__device__ __forceinline__ void bn_relu_body(const BnReluArgs& A, int ch, int s, float* sh) {
+  const int n0 = s * A.ipb, ni = min(A.n, n0 + A.ipb) - n0;
+  const int64_t inner = (int64_t)ch * A.hw;
+  const float* xp = A.x + (int64_t)n0 * A.x_stride + inner;
+  float* op = A.out + (int64_t)n0 * A.out_stride + inner;
+  float* cp = COPY ? A.copy + (int64_t)n0 * A.copy_stride + inner : nullptr;
+  const float ga = A.gamma[ch], be = A.beta[ch];
+  RowIter it(A.hw / V, threadIdx.x, blockDim.x);
+  float t[V], nx[V];
+  int im, q;
+  auto request = [&]() {  // (a position past the range repeats the last image's and is not stored)
+    im = it.img; q = it.q * V;
+    Vec<V>::ld(xp + (int64_t)min(it.img, ni - 1) * A.x_stride + q, nx);
+    it.next();
+  };
+  request();
   float mu, is, scale, shift;
-  channel_stats(ch, mean, istd, part, splits, fresh_lo, fresh_hi, eps, sh, mu, is);
-  bn_fold(gamma[ch], beta[ch], mu, is, scale, shift);
-  const int hwv = hw / V;
-  const int64_t inner = (int64_t)ch * hw;
-  const float* xp = x + (int64_t)n0 * x_stride + inner;
-  float* op = out + (int64_t)n0 * out_stride + inner;
-  float* cp = COPY ? copy_out + (int64_t)n0 * copy_stride + inner : nullptr;
-  for (RowIter it(hwv, threadIdx.x, blockDim.x); it.img < ni; it.next()) {
-    float t[V], r[V];
-    Vec<V>::ld(xp + (int64_t)it.img * x_stride + (int64_t)it.q * V, t);
+  channel_stats(ch, A.mean, A.istd, A.part, A.splits, A.fresh_lo, A.fresh_hi, A.eps, s == 0, sh, mu, is);
+  bn_fold(ga, be, mu, is, scale, shift);
+  while (im < ni) {
+    const int64_t oo = (int64_t)im * A.out_stride + q, co = (int64_t)im * A.copy_stride + q;
+    float r[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) t[e] = nx[e];
+    request();
 #pragma unroll
     for (int e = 0; e < V; ++e) r[e] = fmaxf(__fmaf_rn(t[e], scale, shift), 0.f);
-    Vec<V>::st(op + (int64_t)it.img * out_stride + (int64_t)it.q * V, r);
-    if (COPY) Vec<V>::st(cp + (int64_t)it.img * copy_stride + (int64_t)it.q * V, t);
+    Vec<V>::st(op + oo, r);
+    if (COPY) Vec<V>::st(cp + co, t);
   }
+}
+// grid (c, splits)
+template <int V, bool COPY>
+__global__ __launch_bounds__(kThreads) void k_bn_relu(BnReluArgs A) {
+  __shared__ float sh[3 * kThreads / 64];
+  bn_relu_body<V, COPY>(A, blockIdx.x, blockIdx.y, sh);
+}
+// Two in one launch, as the backward pass of the shared schedule re-populates its storages: the first, na workgroups
+// (ca channels side by side), with the copy, the second without.
+template <int V>
+__global__ __launch_bounds__(kThreads) void k_bn_relu_two(BnReluArgs A, int ca, int na, BnReluArgs B, int cb) {
+  __shared__ float sh[3 * kThreads / 64];
+  const int id = blockIdx.x;
+  if (id < na) bn_relu_body<V, true>(A, id % ca, id / ca, sh);
+  else bn_relu_body<V, false>(B, (id - na) % cb, (id - na) / cb, sh);
 }
 
 // ----------------------------------------------------------------------------- BN + ReLU backward
@@ -354,21 +387,44 @@ hipError_t launch_bn_stats(const float* x, int64_t stride, int n, int c, int hw,
   return hipGetLastError();
 }
 
+static BnReluArgs bn_relu_args(const float* x, int64_t x_stride, float* out, int64_t out_stride, float* copy_out,
+                               int64_t copy_stride, int n, int hw, int ipb, const float* gamma, const float* beta,
+                               const StatsSrc& s) {
+  return BnReluArgs{x, x_stride, out, out_stride, copy_out, copy_stride, n, hw, ipb, gamma, beta, s.mean, s.istd, s.part,
+                    s.splits, s.fresh_lo, s.fresh_hi, s.eps};
+}
+static bool bn_relu_vec(const BnReluArgs& A) {
+  return A.hw % 4 == 0 && A.x_stride % 4 == 0 && A.out_stride % 4 == 0 && aligned16(A.x) && aligned16(A.out) &&
+         (!A.copy || (A.copy_stride % 4 == 0 && aligned16(A.copy)));
+}
+
 hipError_t launch_bn_relu(const float* x, int64_t x_stride, float* out, int64_t out_stride,
                           float* copy_out, int64_t copy_stride, int n, int c, int hw,
                           const float* gamma, const float* beta, StatsSrc s, hipStream_t st) {
   if (n <= 0 || c <= 0 || hw <= 0) return hipSuccess;
-  const bool v4 = (hw % 4 == 0) && (x_stride % 4 == 0) && (out_stride % 4 == 0) && aligned16(x) &&
-                  aligned16(out) && (!copy_out || ((copy_stride % 4 == 0) && aligned16(copy_out)));
   const Split p = split_plan(n, c, hw);
-  dim3 grid((unsigned)c, (unsigned)p.gs);
-#define DNB_LAUNCH_BNRELU(V, C)                                                                     \
-  hipLaunchKernelGGL((k_bn_relu<V, C>), grid, dim3(kThreads), 0, st, x, x_stride, out, out_stride, \
-                     copy_out, copy_stride, n, hw, p.ipb, gamma, beta, s.mean, s.istd, s.part,    \
-                     s.splits, s.fresh_lo, s.fresh_hi, s.eps)
-  if (v4) { if (copy_out) DNB_LAUNCH_BNRELU(4, true); else DNB_LAUNCH_BNRELU(4, false); }
-  else    { if (copy_out) DNB_LAUNCH_BNRELU(1, true); else DNB_LAUNCH_BNRELU(1, false); }
+  const BnReluArgs A = bn_relu_args(x, x_stride, out, out_stride, copy_out, copy_stride, n, hw, p.ipb, gamma, beta, s);
+  const dim3 grid((unsigned)c, (unsigned)p.gs);
+#define DNB_LAUNCH_BNRELU(V, C) hipLaunchKernelGGL((k_bn_relu<V, C>), grid, dim3(kThreads), 0, st, A)
+  if (bn_relu_vec(A)) { if (copy_out) DNB_LAUNCH_BNRELU(4, true); else DNB_LAUNCH_BNRELU(4, false); }
+  else { if (copy_out) DNB_LAUNCH_BNRELU(1, true); else DNB_LAUNCH_BNRELU(1, false); }
 #undef DNB_LAUNCH_BNRELU
+  return hipGetLastError();
+}
+
+hipError_t launch_bn_relu_two(const float* xa, int64_t xa_stride, float* outa, int64_t outa_stride, float* copya,
+                              int64_t copya_stride, int ca, const float* gammaa, const float* betaa, float* meana, float* istda,
+                              const float* xb, int64_t xb_stride, float* outb, int64_t outb_stride, int cb,
+                              const float* gammab, const float* betab, float* meanb, float* istdb, int n, int hw, hipStream_t st) {
+  const Split pa = split_plan(n, ca, hw), pb = split_plan(n, cb, hw);
+  const BnReluArgs A = bn_relu_args(xa, xa_stride, outa, outa_stride, copya, copya_stride, n, hw, pa.ipb, gammaa, betaa,
+                                    StatsSrc{meana, istda, nullptr, 0, 0, 0, 0.f});
+  const BnReluArgs B = bn_relu_args(xb, xb_stride, outb, outb_stride, nullptr, 0, n, hw, pb.ipb, gammab, betab,
+                                    StatsSrc{meanb, istdb, nullptr, 0, 0, 0, 0.f});
+  const int na = ca * pa.gs;
+  const dim3 grid((unsigned)(na + cb * pb.gs));
+  if (bn_relu_vec(A) && bn_relu_vec(B)) hipLaunchKernelGGL(k_bn_relu_two<4>, grid, dim3(kThreads), 0, st, A, ca, na, B, cb);
+  else hipLaunchKernelGGL(k_bn_relu_two<1>, grid, dim3(kThreads), 0, st, A, ca, na, B, cb);
   return hipGetLastError();
 }
 

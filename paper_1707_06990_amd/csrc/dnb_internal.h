@@ -46,6 +46,12 @@ hipError_t launch_bn_relu(const float* x, int64_t x_stride, float* out, int64_t 
                           float* copy_out, int64_t copy_stride, int n, int c, int hw,
                           const float* gamma, const float* beta, StatsSrc s, hipStream_t st);
 
+// Two of them with finished statistics in one launch: a with its copy, b without.
+hipError_t launch_bn_relu_two(const float* xa, int64_t xa_stride, float* outa, int64_t outa_stride, float* copya,
+                              int64_t copya_stride, int ca, const float* gammaa, const float* betaa, float* meana, float* istda,
+                              const float* xb, int64_t xb_stride, float* outb, int64_t outb_stride, int cb,
+                              const float* gammab, const float* betab, float* meanb, float* istdb, int n, int hw, hipStream_t st);
+
 // BN+ReLU backward.  Pass 1 reduces dbeta = sum dz, dgamma = sum dz*xhat with
 // dz = dact * [fma(x,scale,shift) > 0]; pass 2 writes
 // du = gamma*istd*(dz - dbeta/P - xhat*dgamma/P), overwriting or accumulating.
@@ -231,8 +237,8 @@ struct FoldIn;
 namespace nhwc {
 hipError_t copy_rows(const void* src, int64_t sld, void* dst, int64_t dld, int64_t P, int c, hipStream_t st);
 // out = bf16(max(0, fma(x, fold.x, fold.y))) per channel; copy (may be null) = x  (storage 2 / storage 1)
-hipError_t bn_relu_rows(const void* x, int64_t ld, const float2* fold, void* out, int64_t old, void* copy, int64_t cld,
-                        int64_t P, int c, hipStream_t st);
+struct BnReluRows { const void* x; int64_t ld; const float2* fold; void* out; int64_t old; void* copy; int64_t cld; int c; };
+hipError_t bn_relu_rows(const BnReluRows& a, const BnReluRows* b /* null, or a second in the same launch */, int64_t P, hipStream_t st);
 size_t stats_partial_floats(int64_t P, int c);
 hipError_t stats_partial(const void* x, int64_t ld, int64_t P, int c, float* part, int* T, hipStream_t st);
 // per layer, in order: 1x1 forward [B16][c32], 1x1 dgrad [c16][B32], 3x3 forward [9][k16][B32],

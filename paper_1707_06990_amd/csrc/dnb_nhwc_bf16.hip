@@ -35,26 +35,48 @@ __global__ __launch_bounds__(256) void k_copy_rows(const u16* __restrict__ src, 
 
 // out[p][0:c] = bf16(max(0, fma(x[p][ch], scale_ch, shift_ch))) with (scale, shift) = fold[ch]: BN+ReLU
 // into shared storage 2 exactly as the fused schedule's convolutions apply it in their operand
-// loads; copy (may be null) receives the raw features (the concatenation into shared storage 1).
-__global__ __launch_bounds__(256) void k_bn_relu_rows(const u16* __restrict__ x, int64_t ld,
-                                                      const float2* __restrict__ fold, u16* __restrict__ out,
-                                                      int64_t old, u16* __restrict__ copy, int64_t cld, int64_t P,
-                                                      int cv) {
-  const int64_t total = P * cv;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-    const int64_t p = i / cv;
-    const int v = (int)(i - p * cv);
-    V8 r, o;
-    r.q = *reinterpret_cast<const uint4*>(x + p * ld + 8 * v);
-    const float4* f4 = reinterpret_cast<const float4*>(fold + 8 * v);
+// loads; copy (may be null) receives the raw features (the concatenation into shared storage 1).  One launch may hold two
+// (the storages that the backward pass re-populates).  Bound by launch, memory round trip and copy rate: a thread requests its four vectors
+// together, and only its first position costs a division.
+struct RowsArgs {
+  const u16* x; int64_t ld;
+  const float2* fold;
+  u16* out; int64_t old;
+  u16* copy; int64_t cld;
+  int total, cv, wgs;  // 8-channel vectors (P * cv < 2^28), of a pixel; workgroups
+};
+__global__ __launch_bounds__(256) void k_bn_relu_rows(RowsArgs A, RowsArgs B) {
+  const bool second = (int)blockIdx.x >= A.wgs;
+  const RowsArgs& R = second ? B : A;
+  const int step = R.wgs * 256, dp = step / R.cv, dv = step - dp * R.cv;
+  int i = ((int)blockIdx.x - (second ? A.wgs : 0)) * 256 + (int)threadIdx.x;
+  int p = i / R.cv, v = i - p * R.cv;
+  for (; i < R.total; ) {
+    V8 r[4];
+    int pp[4], vv[4];
+    bool ok[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float4 f = f4[e];  // two channels' (scale, shift)
-      o.h[2 * e] = f2bf(fmaxf(__fmaf_rn(bf2f(r.h[2 * e]), f.x, f.y), 0.f));
-      o.h[2 * e + 1] = f2bf(fmaxf(__fmaf_rn(bf2f(r.h[2 * e + 1]), f.z, f.w), 0.f));
+    for (int u = 0; u < 4; ++u) {
+      ok[u] = i < R.total;
+      pp[u] = ok[u] ? p : 0; vv[u] = ok[u] ? v : 0;
+      r[u].q = *reinterpret_cast<const uint4*>(R.x + (int64_t)pp[u] * R.ld + 8 * vv[u]);
+      i += step; p += dp; v += dv;
+      if (v >= R.cv) { v -= R.cv; ++p; }
     }
-    *reinterpret_cast<uint4*>(out + p * old + 8 * v) = o.q;
-    if (copy) *reinterpret_cast<uint4*>(copy + p * cld + 8 * v) = r.q;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float4* f4 = reinterpret_cast<const float4*>(R.fold + 8 * vv[u]);
+      V8 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float4 f = f4[e];  // two channels' (scale, shift)
+        o.h[2 * e] = f2bf(fmaxf(__fmaf_rn(bf2f(r[u].h[2 * e]), f.x, f.y), 0.f));
+        o.h[2 * e + 1] = f2bf(fmaxf(__fmaf_rn(bf2f(r[u].h[2 * e + 1]), f.z, f.w), 0.f));
+      }
+      if (!ok[u]) continue;
+      *reinterpret_cast<uint4*>(R.out + (int64_t)pp[u] * R.old + 8 * vv[u]) = o.q;
+      if (R.copy) *reinterpret_cast<uint4*>(R.copy + (int64_t)pp[u] * R.cld + 8 * vv[u]) = r[u].q;
+    }
   }
 }
 
@@ -741,10 +763,14 @@ hipError_t copy_rows(const void* src, int64_t sld, void* dst, int64_t dld, int64
   return hipGetLastError();
 }
 
-hipError_t bn_relu_rows(const void* x, int64_t ld, const float2* fold, void* out, int64_t old, void* copy, int64_t cld,
-                        int64_t P, int c, hipStream_t st) {
-  hipLaunchKernelGGL(k_bn_relu_rows, dim3(grid1d(P * (c / 8), 512, 16384)), dim3(256), 0, st, (const u16*)x, ld, fold,
-                     (u16*)out, old, (u16*)copy, cld, P, c / 8);
+static RowsArgs rows_args(const BnReluRows& r, int64_t P) {
+  RowsArgs A{(const u16*)r.x, r.ld, r.fold, (u16*)r.out, r.old, (u16*)r.copy, r.cld, (int)(P * (r.c / 8)), r.c / 8, 0};
+  A.wgs = (int)grid1d(A.total, 1024, 16384);  // four vectors a thread
+  return A;
+}
+hipError_t bn_relu_rows(const BnReluRows& a, const BnReluRows* b, int64_t P, hipStream_t st) {
+  const RowsArgs A = rows_args(a, P), B = b ? rows_args(*b, P) : RowsArgs{};
+  hipLaunchKernelGGL(k_bn_relu_rows, dim3((unsigned)(A.wgs + B.wgs)), dim3(256), 0, st, A, B);
   return hipGetLastError();
 }
 
