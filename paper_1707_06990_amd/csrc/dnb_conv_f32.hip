@@ -11,6 +11,7 @@
 // The weight gradient is a GEMM over pixels, dW[m][c][t] = sum_q g[m][q] * in[c][q+shift(t)],
 // split over pixel ranges across workgroups; partial results go to scratch and a second kernel
 // adds them in a fixed order (no float atomics: results are reproducible run to run).
+#include "dnb_f32_dev.h"
 #include "dnb_internal.h"
 #include "dnb_stats.h"
 
@@ -44,15 +45,7 @@ bool launch_wgrad_pair_fast(const float* in1, int64_t in1_stride, const float* g
 
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
 constexpr int KC = 16;  // input channels staged per step (4 MFMA k-steps)
-
-// D(16x16) += A(16x4) * B(4x16).  Lane l supplies A[l%16][l/16] and B[l/16][l%16] and holds
-// D[4*(l/16)+r][l%16] in register r.
-__device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
 
 // smallest stride >= v that is 16 mod 32: four 16-lane groups reading four rows hit
 // disjoint LDS banks
@@ -172,7 +165,12 @@ template <int TAPS, int TW>
 __global__ __launch_bounds__(256) void k_conv_wgrad(
     const float* __restrict__ in, int64_t in_stride, const float* __restrict__ gout,
     int64_t g_stride, float* __restrict__ part, int cin, int cout, int H, int W, int cpi /*chunks per image*/,
-    int total_chunks, int cps /*chunks per split*/, int MTW, int CTW, int PA, int PG) {
+    int total_chunks, int cps /*chunks per split*/, int MTW, int CTW, int PA, int PG, SumRole sr, int gx_main) {
+  if ((int)blockIdx.x >= gx_main) {  // extra workgroups: a pending sum of another partial buffer
+    const int wg = (((int)blockIdx.x - gx_main) * gridDim.y + blockIdx.y) * gridDim.z + blockIdx.z;
+    if (wg < sr.wgs) sum_role(sr, wg);
+    return;
+  }
   extern __shared__ float lds[];
   const int HW = H * W;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -467,19 +465,18 @@ hipError_t launch_conv_wgrad(const float* in, int64_t in_stride, const float* g,
     return launch_pending_sum(&own, st);
   }
   if (used_fast) *used_fast = false;
-  if (absorb) {
-    const hipError_t e = launch_pending_sum(absorb, st);
-    if (e != hipSuccess) return e;
-  }
   if (fold) return hipErrorInvalidValue;  // the generic kernel has no BN prologue
   const WgradPlan p = plan_wgrad(n, cin, cout, h, w, taps);
   if (p.lds > 64 * 1024) return hipErrorInvalidValue;
+  const SumRole sr = make_sum_role(absorb);
+  dim3 grid = p.grid;
+  grid.x += (unsigned)((sr.wgs + grid.y * grid.z - 1) / (grid.y * grid.z));
   if (taps == 9)
-    hipLaunchKernelGGL((k_conv_wgrad<9, 7>), p.grid, dim3(256), p.lds, st, in, in_stride, g, g_stride,
-                       partials, cin, cout, h, w, p.cpi, p.total, p.cps, p.mtw, p.ctw, p.PA, p.PG);
+    hipLaunchKernelGGL((k_conv_wgrad<9, 7>), grid, dim3(256), p.lds, st, in, in_stride, g, g_stride,
+                       partials, cin, cout, h, w, p.cpi, p.total, p.cps, p.mtw, p.ctw, p.PA, p.PG, sr, (int)p.grid.x);
   else
-    hipLaunchKernelGGL((k_conv_wgrad<1, 3>), p.grid, dim3(256), p.lds, st, in, in_stride, g, g_stride,
-                       partials, cin, cout, h, w, p.cpi, p.total, p.cps, p.mtw, p.ctw, p.PA, p.PG);
+    hipLaunchKernelGGL((k_conv_wgrad<1, 3>), grid, dim3(256), p.lds, st, in, in_stride, g, g_stride,
+                       partials, cin, cout, h, w, p.cpi, p.total, p.cps, p.mtw, p.ctw, p.PA, p.PG, sr, (int)p.grid.x);
   own.kind = taps == 9 ? 2 : 1;
   own.part = partials; own.out = dw; own.splits = p.splits;
   own.gy = (int)p.grid.y; own.gz = (int)p.grid.z; own.mtw = p.mtw; own.ctw = p.ctw; own.cin = cin; own.cout = cout;

@@ -1137,57 +1137,6 @@ __global__ __launch_bounds__(NW * 64, NW == 6 && NK == 6 ? 3 : 2) void k_dgrad3_
   }
 }
 
-// A pending sum of partials carried out by extra workgroups of a weight-gradient launch (the
-// workgroups with blockIdx.x >= gx_main): kind 1 is k_sum_partials' job, kind 2 k_sum_wgrad3x3's,
-// with the same grouping and order of additions, so the sums have the same bits either way.
-struct SumRole {
-  int kind, wgs;  // kind 0: none; wgs: workgroups the sum needs
-  const float* part;
-  float* out;
-  int splits, G, per;
-  long long count;  // elements of one partial
-  int gy, gz, mtw, ctw, cin, cout;
-};
-
-__device__ __forceinline__ void sum_role(const SumRole& sr, int wg) {
-  extern __shared__ float sh[];  // the launch's dynamic LDS (every weight-gradient launch has >= 1 KB)
-  const int epb = 256 / sr.G;
-  const int le = threadIdx.x % epb, grp = threadIdx.x / epb;
-  const long long f = (long long)wg * epb + le;
-  float s = 0.f;
-  if (f < sr.count) {
-    int i = grp * sr.per;
-    const int end = min(sr.splits, i + sr.per);
-    for (; i + 8 <= end; i += 8) {
-      float v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = sr.part[(long long)(i + u) * sr.count + f];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) s += v[u];
-    }
-    for (; i < end; ++i) s += sr.part[(long long)i * sr.count + f];
-  }
-  sh[threadIdx.x] = s;
-  __syncthreads();
-  if (grp == 0 && f < sr.count) {
-    float t = sh[le];
-    for (int g = 1; g < sr.G; ++g) t += sh[g * epb + le];
-    if (sr.kind == 1) {
-      sr.out[f] = t;
-    } else {
-      const int NT = sr.mtw * sr.ctw * 9;
-      const int rr = (int)(f & 3), lane = (int)((f >> 2) & 63);
-      const long long tl = f >> 8;
-      const int tile = (int)(tl % NT), blk = (int)(tl / NT);
-      const int yb = blk % sr.gy, z = blk / sr.gy;
-      const int tap = tile % 9, y = (tile / 9) % sr.ctw, x = tile / (9 * sr.ctw);
-      const int m = z * (sr.mtw * 16) + x * 16 + 4 * (lane >> 4) + rr;
-      const int c = yb * (sr.ctw * 16) + y * 16 + (lane & 15);
-      if (m < sr.cout && c < sr.cin) sr.out[((long long)m * sr.cin + c) * 9 + tap] = t;
-    }
-  }
-}
-
 // Adds the accumulators of the four waves of a workgroup, a0 + (a1 + (a2 + a3)) element by
 // element: every wave writes its NT tiles to its own LDS region (4 * NT * 256 floats in all),
 // then wave w adds up the tiles t with t % 4 == w, which it alone holds afterwards.
@@ -2171,15 +2120,6 @@ size_t conv_wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, in
   return (size_t)p.gx * cin * cout;
 }
 
-// Grouping of a sum of `splits` partials (the same rule the stand-alone sum kernels use).
-static void sum_grouping(int kind, int splits, int* G, int* per) {
-  int g = 1;
-  if (kind == 2) { while (g < 16 && splits / (g * 2) >= 4) g *= 2; }   // at least 4 partials per group
-  else           { while (g < 16 && splits / g > 16) g <<= 1; }         // about 16 splits per thread
-  *G = g;
-  *per = (splits + g - 1) / g;
-}
-
 hipError_t launch_sum_wgrad3x3(const PendingSum& p, hipStream_t st) {
   int G, per;
   sum_grouping(2, p.splits, &G, &per);
@@ -2198,19 +2138,8 @@ bool launch_wgrad_fast(const float* in, int64_t in_stride, const float* g, int64
   if (in_stride % 4 || g_stride % 4 || !aligned16(in) || !aligned16(g)) return false;
   const WgFastPlan p = plan_wgrad_fast(n, cin, cout, h, w, taps, alone);
   if (!p.ok) return false;
-  SumRole sr{};
-  unsigned sx = 0;
-  if (absorb && absorb->kind != 0) {
-    sr.kind = absorb->kind;
-    sr.part = absorb->part; sr.out = absorb->out; sr.splits = absorb->splits; sr.count = absorb->count;
-    sr.gy = absorb->gy; sr.gz = absorb->gz; sr.mtw = absorb->mtw; sr.ctw = absorb->ctw;
-    sr.cin = absorb->cin; sr.cout = absorb->cout;
-    sum_grouping(sr.kind, sr.splits, &sr.G, &sr.per);
-    const int epb = 256 / sr.G;
-    sr.wgs = (int)((sr.count + epb - 1) / epb);
-    sx = (unsigned)((sr.wgs + p.gy * p.gz - 1) / (p.gy * p.gz));
-    absorb->kind = 0;
-  }
+  const SumRole sr = make_sum_role(absorb);
+  const unsigned sx = (unsigned)((sr.wgs + p.gy * p.gz - 1) / (p.gy * p.gz));
   dim3 grid((unsigned)p.gx + sx, (unsigned)p.gy, (unsigned)p.gz);
   const int hw = h * w;
   if (taps == 1) {
@@ -2250,21 +2179,6 @@ bool launch_wgrad_fast(const float* in, int64_t in_stride, const float* g, int64
     own->gy = p.gy; own->gz = p.gz; own->mtw = p.mtw; own->ctw = p.ctw; own->cin = cin; own->cout = cout;
   }
   return true;
-}
-
-static SumRole make_sum_role(PendingSum* absorb) {
-  SumRole sr{};
-  if (absorb && absorb->kind != 0) {
-    sr.kind = absorb->kind;
-    sr.part = absorb->part; sr.out = absorb->out; sr.splits = absorb->splits; sr.count = absorb->count;
-    sr.gy = absorb->gy; sr.gz = absorb->gz; sr.mtw = absorb->mtw; sr.ctw = absorb->ctw;
-    sr.cin = absorb->cin; sr.cout = absorb->cout;
-    sum_grouping(sr.kind, sr.splits, &sr.G, &sr.per);
-    const int epb = 256 / sr.G;
-    sr.wgs = (int)((sr.count + epb - 1) / epb);
-    absorb->kind = 0;
-  }
-  return sr;
 }
 
 // Both weight gradients of a bottleneck layer in one launch: the 3x3 (in3: the bottleneck

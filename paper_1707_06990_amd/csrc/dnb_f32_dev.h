@@ -4,11 +4,15 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "dnb_internal.h"
+
 namespace dnb {
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+// D(16x16) += A(16x4) * B(4x16).  Lane l supplies A[l%16][l/16] and B[l/16][l%16] and holds
+// D[4*(l/16)+r][l%16] in register r.
 __device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
@@ -80,6 +84,81 @@ __device__ __forceinline__ void ksplit_reduce(f32x4 (&acc)[MT][NT], float* red, 
       }
     }
   }
+}
+
+// A pending sum of partials carried out by extra workgroups of a weight-gradient launch (the
+// workgroups with blockIdx.x >= gx_main): kind 1 is k_sum_partials' job, kind 2 k_sum_wgrad3x3's,
+// with the same grouping and order of additions, so the sums have the same bits either way.
+struct SumRole {
+  int kind, wgs;  // kind 0: none; wgs: workgroups the sum needs
+  const float* part;
+  float* out;
+  int splits, G, per;
+  long long count;  // elements of one partial
+  int gy, gz, mtw, ctw, cin, cout;
+};
+
+__device__ __forceinline__ void sum_role(const SumRole& sr, int wg) {
+  extern __shared__ float sh[];  // the launch's dynamic LDS (every weight-gradient launch has >= 1 KB)
+  const int epb = 256 / sr.G;
+  const int le = threadIdx.x % epb, grp = threadIdx.x / epb;
+  const long long f = (long long)wg * epb + le;
+  float s = 0.f;
+  if (f < sr.count) {
+    int i = grp * sr.per;
+    const int end = min(sr.splits, i + sr.per);
+    for (; i + 8 <= end; i += 8) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = sr.part[(long long)(i + u) * sr.count + f];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    for (; i < end; ++i) s += sr.part[(long long)i * sr.count + f];
+  }
+  sh[threadIdx.x] = s;
+  __syncthreads();
+  if (grp == 0 && f < sr.count) {
+    float t = sh[le];
+    for (int g = 1; g < sr.G; ++g) t += sh[g * epb + le];
+    if (sr.kind == 1) {
+      sr.out[f] = t;
+    } else {
+      const int NT = sr.mtw * sr.ctw * 9;
+      const int rr = (int)(f & 3), lane = (int)((f >> 2) & 63);
+      const long long tl = f >> 8;
+      const int tile = (int)(tl % NT), blk = (int)(tl / NT);
+      const int yb = blk % sr.gy, z = blk / sr.gy;
+      const int tap = tile % 9, y = (tile / 9) % sr.ctw, x = tile / (9 * sr.ctw);
+      const int m = z * (sr.mtw * 16) + x * 16 + 4 * (lane >> 4) + rr;
+      const int c = yb * (sr.ctw * 16) + y * 16 + (lane & 15);
+      if (m < sr.cout && c < sr.cin) sr.out[((long long)m * sr.cin + c) * 9 + tap] = t;
+    }
+  }
+}
+
+// Grouping of a sum of `splits` partials (the same rule the stand-alone sum kernels use).
+inline void sum_grouping(int kind, int splits, int* G, int* per) {
+  int g = 1;
+  if (kind == 2) { while (g < 16 && splits / (g * 2) >= 4) g *= 2; }   // at least 4 partials per group
+  else           { while (g < 16 && splits / g > 16) g <<= 1; }         // about 16 splits per thread
+  *G = g;
+  *per = (splits + g - 1) / g;
+}
+
+inline SumRole make_sum_role(PendingSum* absorb) {
+  SumRole sr{};
+  if (absorb && absorb->kind != 0) {
+    sr.kind = absorb->kind;
+    sr.part = absorb->part; sr.out = absorb->out; sr.splits = absorb->splits; sr.count = absorb->count;
+    sr.gy = absorb->gy; sr.gz = absorb->gz; sr.mtw = absorb->mtw; sr.ctw = absorb->ctw;
+    sr.cin = absorb->cin; sr.cout = absorb->cout;
+    sum_grouping(sr.kind, sr.splits, &sr.G, &sr.per);
+    const int epb = 256 / sr.G;
+    sr.wgs = (int)((sr.count + epb - 1) / epb);
+    absorb->kind = 0;
+  }
+  return sr;
 }
 
 }  // namespace
