@@ -2042,13 +2042,18 @@ static WgFastPlan plan_wgrad_fast(int n, int cin, int cout, int h, int w, int ta
   p.ok = hw % 4 == 0 && (taps == 1 || (w % 4 == 0 && w >= 4));
   if (!p.ok) return p;
   if (taps == 1) {
-    // More than 48 output channels, beside a 3x3: the wide form, about one workgroup per CU whatever the shape (they share
-    // the matrix cores with the 3x3's; 192 / 320 / 384 / 512 workgroups: 2.3 / 2.2 / 1.3 / 0.9 % more time per
-    // DenseNet-BC-250 step; fewer also keep the partials small).  With the narrow tiles, whose pixel ranges were dealt to
-    // the XCDs whole, few-pixel layers used only three or four of the eight: 90 -> 61 us per launch on average, 62 -> 25 on
-    // the 8x8 block (P = 4096, 750..1700 channels).  A transition's weight gradient, alone on the chip and up to 516
-    // channels wide, is better balanced in narrow tiles (395 + 785 us against 400 + 953).
-    if (!alone && cout > 48 && cin > 64 && (hw % 32 == 0 || hw >= 128)) {
+    p.mtw = mtiles >= 3 ? 3 : mtiles;
+    p.ctw = ctiles >= 4 ? 4 : ctiles;
+    p.gy = (ctiles + p.ctw - 1) / p.ctw;
+    p.gz = (mtiles + p.mtw - 1) / p.mtw;
+    // More than 48 output channels and more than eight columns of narrow tiles, beside a 3x3: the wide form, about one
+    // workgroup per CU whatever the shape (they share the matrix cores with the 3x3's; 192 / 320 / 384 / 512 workgroups: 2.3
+    // / 2.2 / 1.3 / 0.9 % more time per DenseNet-BC-250 step; fewer also keep the partials small).  With the narrow tiles,
+    // whose pixel ranges were dealt to the XCDs whole, few-pixel layers used only three or four of the eight: 90 -> 61 us
+    // per launch on average, 62 -> 25 on the 8x8 block (P = 4096, 750..1700 channels).  With fewer columns the two
+    // are alike (54..74 us against 54..82) and the narrow tiles leave fewer partial sums.  A transition's weight gradient,
+    // alone on the chip and up to 516 channels wide, is better balanced in narrow tiles (395 + 785 us against 400 + 953).
+    if (!alone && cout > 48 && p.gy * p.gz > 8 && (hw % 32 == 0 || hw >= 128)) {
       p.ctw = 8;
       p.mtw = 4;  // the fewest rows of padding, then the largest tile
       for (int wm = 3; wm >= 2; --wm)
@@ -2065,10 +2070,6 @@ static WgFastPlan plan_wgrad_fast(int n, int cin, int cout, int h, int w, int ta
       p.lds = wide_lds_bytes(p.mtw);
       return p;
     }
-    p.mtw = mtiles >= 3 ? 3 : mtiles;
-    p.ctw = ctiles >= 4 ? 4 : ctiles;
-    p.gy = (ctiles + p.ctw - 1) / p.ctw;
-    p.gz = (mtiles + p.mtw - 1) / p.mtw;
     p.spi = (hw + 15) / 16;
     p.total_steps = n * p.spi;
     // About 128 workgroups in all, 1..16 (or 64) steps per wave.  A workgroup ends with a cross-wave sum
