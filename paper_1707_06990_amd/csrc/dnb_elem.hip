@@ -165,27 +165,41 @@ __device__ __forceinline__ void bn_relu_body(const BnReluArgs& A, int ch, int s,
   float* cp = COPY ? A.copy + (int64_t)n0 * A.copy_stride + inner : nullptr;
   const float ga = A.gamma[ch], be = A.beta[ch];
   RowIter it(A.hw / V, threadIdx.x, blockDim.x);
-  float t[V], nx[V];
-  int im, q;
-  auto request = [&]() {  // (a position past the range repeats the last image's and is not stored)
-    im = it.img; q = it.q * V;
-    Vec<V>::ld(xp + (int64_t)min(it.img, ni - 1) * A.x_stride + q, nx);
-    it.next();
-  };
-  request();
   float mu, is, scale, shift;
-  channel_stats(ch, A.mean, A.istd, A.part, A.splits, A.fresh_lo, A.fresh_hi, A.eps, s == 0, sh, mu, is);
-  bn_fold(ga, be, mu, is, scale, shift);
-  while (im < ni) {
-    const int64_t oo = (int64_t)im * A.out_stride + q, co = (int64_t)im * A.copy_stride + q;
+  auto stats = [&]() {
+    channel_stats(ch, A.mean, A.istd, A.part, A.splits, A.fresh_lo, A.fresh_hi, A.eps, s == 0, sh, mu, is);
+    bn_fold(ga, be, mu, is, scale, shift);
+  };
+  auto store = [&](int im, int q, const float(&t)[V]) {
     float r[V];
 #pragma unroll
-    for (int e = 0; e < V; ++e) t[e] = nx[e];
-    request();
-#pragma unroll
     for (int e = 0; e < V; ++e) r[e] = fmaxf(__fmaf_rn(t[e], scale, shift), 0.f);
-    Vec<V>::st(op + oo, r);
-    if (COPY) Vec<V>::st(cp + co, t);
+    Vec<V>::st(op + (int64_t)im * A.out_stride + (int64_t)q * V, r);
+    if (COPY) Vec<V>::st(cp + (int64_t)im * A.copy_stride + (int64_t)q * V, t);
+  };
+  float t[V];
+  if (V == 1) {  // (floats one by one: vector work counts too)
+    for (stats(); it.img < ni; it.next()) {
+      Vec<V>::ld(xp + (int64_t)it.img * A.x_stride + it.q, t);
+      store(it.img, it.q, t);
+    }
+    return;
+  }
+  float nx[V];
+  auto request = [&]() {
+    if (it.img < ni) Vec<V>::ld(xp + (int64_t)it.img * A.x_stride + (int64_t)it.q * V, nx);
+  };
+#pragma unroll
+  for (int e = 0; e < V; ++e) nx[e] = 0.f;
+  request();
+  stats();
+  while (it.img < ni) {
+    const int im = it.img, q = it.q;
+#pragma unroll
+    for (int e = 0; e < V; ++e) t[e] = nx[e];
+    it.next();
+    request();
+    store(im, q, t);
   }
 }
 // grid (c, splits)

@@ -36,7 +36,7 @@ __global__ __launch_bounds__(256) void k_copy_rows(const u16* __restrict__ src, 
 // out[p][0:c] = bf16(max(0, fma(x[p][ch], scale_ch, shift_ch))) with (scale, shift) = fold[ch]: BN+ReLU
 // into shared storage 2 exactly as the fused schedule's convolutions apply it in their operand
 // loads; copy (may be null) receives the raw features (the concatenation into shared storage 1).  One launch may hold two
-// (the storages that the backward pass re-populates).  Bound by launch, memory round trip and copy rate: a thread requests its four vectors
+// (the storages that the backward pass re-populates).  Bound by launch, memory round trip and copy rate: a thread requests two vectors
 // together, and only its first position costs a division.
 struct RowsArgs {
   const u16* x; int64_t ld;
@@ -45,18 +45,22 @@ struct RowsArgs {
   u16* copy; int64_t cld;
   int total, cv, wgs;  // 8-channel vectors (P * cv < 2^28), of a pixel; workgroups
 };
+template <bool TWO>
 __global__ __launch_bounds__(256) void k_bn_relu_rows(RowsArgs A, RowsArgs B) {
-  const bool second = (int)blockIdx.x >= A.wgs;
-  const RowsArgs& R = second ? B : A;
+  const bool second = TWO && (int)blockIdx.x >= A.wgs;
+  // (field by field: chosen as a whole, the second's arguments would be read after the first's)
+  const RowsArgs R{second ? B.x : A.x, second ? B.ld : A.ld, second ? B.fold : A.fold, second ? B.out : A.out,
+                   second ? B.old : A.old, second ? B.copy : A.copy, second ? B.cld : A.cld, second ? B.total : A.total,
+                   second ? B.cv : A.cv, second ? B.wgs : A.wgs};
   const int step = R.wgs * 256, dp = step / R.cv, dv = step - dp * R.cv;
   int i = ((int)blockIdx.x - (second ? A.wgs : 0)) * 256 + (int)threadIdx.x;
   int p = i / R.cv, v = i - p * R.cv;
   for (; i < R.total; ) {
-    V8 r[4];
-    int pp[4], vv[4];
-    bool ok[4];
+    V8 r[2];
+    int pp[2], vv[2];
+    bool ok[2];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < 2; ++u) {
       ok[u] = i < R.total;
       pp[u] = ok[u] ? p : 0; vv[u] = ok[u] ? v : 0;
       r[u].q = *reinterpret_cast<const uint4*>(R.x + (int64_t)pp[u] * R.ld + 8 * vv[u]);
@@ -64,7 +68,7 @@ __global__ __launch_bounds__(256) void k_bn_relu_rows(RowsArgs A, RowsArgs B) {
       if (v >= R.cv) { v -= R.cv; ++p; }
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < 2; ++u) {
       const float4* f4 = reinterpret_cast<const float4*>(R.fold + 8 * vv[u]);
       V8 o;
 #pragma unroll
@@ -765,12 +769,14 @@ hipError_t copy_rows(const void* src, int64_t sld, void* dst, int64_t dld, int64
 
 static RowsArgs rows_args(const BnReluRows& r, int64_t P) {
   RowsArgs A{(const u16*)r.x, r.ld, r.fold, (u16*)r.out, r.old, (u16*)r.copy, r.cld, (int)(P * (r.c / 8)), r.c / 8, 0};
-  A.wgs = (int)grid1d(A.total, 1024, 16384);  // four vectors a thread
+  A.wgs = (int)grid1d(A.total, 512, 16384);  // two vectors a thread
   return A;
 }
 hipError_t bn_relu_rows(const BnReluRows& a, const BnReluRows* b, int64_t P, hipStream_t st) {
   const RowsArgs A = rows_args(a, P), B = b ? rows_args(*b, P) : RowsArgs{};
-  hipLaunchKernelGGL(k_bn_relu_rows, dim3((unsigned)(A.wgs + B.wgs)), dim3(256), 0, st, A, B);
+  const dim3 grid((unsigned)(A.wgs + B.wgs));
+  if (b) hipLaunchKernelGGL(k_bn_relu_rows<true>, grid, dim3(256), 0, st, A, B);
+  else hipLaunchKernelGGL(k_bn_relu_rows<false>, grid, dim3(256), 0, st, A, B);
   return hipGetLastError();
 }
 
