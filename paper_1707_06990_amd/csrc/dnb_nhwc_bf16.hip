@@ -111,6 +111,21 @@ __global__ __launch_bounds__(256) void k_stats_partial(const u16* __restrict__ x
     }
     // eight rows requested before the first is added (in row order; a load per row waited out its latency:
     // 74 us for the 401408 x 64 features of a stem)
+    for (; p + 8 * 15 < p1; p += 128) {  // sixteen while there are as many: 401408 x 64 features 46 -> 20 us
+      V8 v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v[u].q = *reinterpret_cast<const uint4*>(x + (p + 8 * u) * ld + ch0);
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float d = bf2f(v[u].h[e]) - K[e];
+          sd[e] += d;
+          sq[e] = __fmaf_rn(d, d, sq[e]);
+        }
+        cnt += 1.f;
+      }
+    }
     for (; p < p1; p += 64) {
       V8 v[8];
 #pragma unroll
@@ -137,15 +152,14 @@ __global__ __launch_bounds__(256) void k_stats_partial(const u16* __restrict__ x
     red[2][e][threadIdx.x] = fmaxf(0.f, __fmaf_rn(-sd[e], md, sq[e]));
   }
   __syncthreads();
-  if (pr == 0 && ok) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      Stat3 a{red[0][e][cvl], red[1][e][cvl], red[2][e][cvl]};
-      for (int r = 1; r < 8; ++r)
-        a = stat_combine(a, Stat3{red[0][e][r * 32 + cvl], red[1][e][r * 32 + cvl], red[2][e][r * 32 + cvl]});
-      float* o = part + ((int64_t)(ch0 + e) * S + s) * 3;
-      o[0] = a.c; o[1] = a.m; o[2] = a.m2;
-    }
+  // a thread a channel (32 threads with eight each took 7 us to form the quotients)
+  const int e = threadIdx.x & 7, cv = threadIdx.x >> 3, ch = blockIdx.x * 256 + (int)threadIdx.x;
+  if (ch < c) {
+    Stat3 a{red[0][e][cv], red[1][e][cv], red[2][e][cv]};
+    for (int r = 1; r < 8; ++r)
+      a = stat_combine(a, Stat3{red[0][e][r * 32 + cv], red[1][e][r * 32 + cv], red[2][e][r * 32 + cv]});
+    float* o = part + ((int64_t)ch * S + s) * 3;
+    o[0] = a.c; o[1] = a.m; o[2] = a.m2;
   }
 }
 
@@ -154,12 +168,16 @@ __global__ __launch_bounds__(256) void k_pack_block_weights(const float* __restr
                                                             u16* __restrict__ packed, int c0, int k, int B) {
   const int l = blockIdx.y + 1;
   const int B16 = (B + 15) & ~15, k16 = (k + 15) & ~15, B32 = (B + 31) & ~31, k32 = (k + 31) & ~31;
+  // the sizes of the layers before this one, a lane each (one after the other they were 3 us of every workgroup at the
+  // 64th layer)
   int64_t poff = 0, koff = 0;
-  for (int i = 1; i < l; ++i) {
+  for (int i = 1 + (int)(threadIdx.x & 63); i < l; i += 64) {
     const int c = c0 + (i - 1) * k, c16 = (c + 15) & ~15, c32 = (c + 31) & ~31;
     poff += 2 * (int64_t)c + (int64_t)B * c + 2 * B + 9 * (int64_t)k * B;
     koff += (int64_t)B16 * c32 + (int64_t)c16 * B32 + 9 * (int64_t)k16 * B32 + 9 * (int64_t)B16 * k32;
   }
+  poff = wave_sum_i64(poff);
+  koff = wave_sum_i64(koff);
   const int C = c0 + (l - 1) * k, C16 = (C + 15) & ~15, C32 = (C + 31) & ~31;
   const float* W1 = params + poff + 2 * C;
   const float* W3 = W1 + (int64_t)B * C + 2 * B;
@@ -809,8 +827,7 @@ size_t packed_layer_elems(int c, int k, int B) {
 hipError_t pack_block_weights(const float* params, void* packed, int c0, int k, int B, int m, hipStream_t st) {
   const size_t most = packed_layer_elems(c0 + (m - 1) * k, k, B);
   unsigned gx = (unsigned)((most / 8 + 255) / 256);  // (a layer's elements are a multiple of 512)
-  // each workgroup adds up the sizes of the layers before its own: some 2048 long ones, not 64 x 256
-  const unsigned cap = (unsigned)(2048 / m) < 16 ? 16 : (unsigned)(2048 / m);
+  const unsigned cap = 8192 / m < 16 ? 16 : (unsigned)(8192 / m);  // (2048 in all: 50 and 47 us for DenseNet-264's last blocks; 44, 43)
   if (gx > cap) gx = cap;
   if (gx < 1) gx = 1;
   hipLaunchKernelGGL(k_pack_block_weights, dim3(gx, (unsigned)m), dim3(256), 0, st, params, (u16*)packed, c0, k, B);

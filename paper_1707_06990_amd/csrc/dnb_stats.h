@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stdint.h>
 
 namespace dnb {
 
@@ -48,6 +49,13 @@ __device__ __forceinline__ float row16_sumsq0(float d) {
   v = v + row16_from<0x4E>(v);
   v = v + row16_from<0x12C>(v);  // row_ror 12: lane i takes lane i + 4
   v = v + row16_from<0x128>(v);  // row_ror 8
+  return v;
+}
+
+// Sum over the 64 lanes, the same in every lane.
+__device__ __forceinline__ int64_t wave_sum_i64(int64_t v) {
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) v += (int64_t)__shfl_xor((long long)v, off, 64);
   return v;
 }
 
