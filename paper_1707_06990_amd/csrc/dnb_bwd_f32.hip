@@ -275,11 +275,12 @@ __global__ __launch_bounds__(256, 2) void k_dgrad1s(Dgrad1Args A) {
 
 // Two layers at once, on the channels that both read: x and the slab move once for the two, 12 bytes per element
 // instead of 24.  Eight waves of 16 channels each; both layers' weights stay in registers, both tiles of db sit in
-// LDS, staged one pixel tile ahead.  65536 pixels, 1000 channels, 96 outputs: 287 us and 13 for the slice between,
-// against 2 x 240; DenseNet-BC-250 step 40.0 -> 38.0 ms, BC-100 4.81 -> 4.73.
+// LDS, in two buffers: the next pixel tile is put down between the two layers' products, one barrier a tile.  65536
+// pixels, 1000 channels, 96 outputs: 232 us (283 with one buffer and operands read as they are needed) and 13 for the
+// slice between, against 2 x 240; 786 MB and 25.8 GFLOP, 74 % of the fp32 matrix rate.
 template <int NCH, bool FIRST>
 __global__ __launch_bounds__(512) void k_dgrad1p(Dgrad1Args A, Dgrad1Lower B) {
-  extern __shared__ __attribute__((aligned(16))) float tile_db[];  // [2][NCH*16][64]
+  extern __shared__ __attribute__((aligned(16))) float tile_db[];  // two buffers of [2][NCH*16][64]
   __shared__ float4 cst[2][128];  // scale, shift, mean, 1/std of the workgroup's channels
   constexpr int TS = NCH * 16 * 64, SU = (NCH + 1) / 2;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 15, g = lane >> 4;
@@ -314,18 +315,21 @@ __global__ __launch_bounds__(512) void k_dgrad1p(Dgrad1Args A, Dgrad1Lower B) {
       st[1][u] = ldg4(B.db + o);
     }
   };
-  request(t0);
-  for (int tile = t0; tile < A.tiles; tile += A.T) {
-    __syncthreads();  // the previous tile's reads are done
+  auto deposit = [&](int buf) {
 #pragma unroll
     for (int u = 0; u < SU; ++u) {
       const int row = u * 32 + srow;
       if (NCH % 2 == 0 || row < NCH * 16) {
-        *reinterpret_cast<float4*>(&tile_db[row * 64 + scol]) = st[0][u];
-        *reinterpret_cast<float4*>(&tile_db[TS + row * 64 + scol]) = st[1][u];
+        lds_st4(&tile_db[buf + row * 64 + scol], st[0][u]);
+        lds_st4(&tile_db[buf + TS + row * 64 + scol], st[1][u]);
       }
     }
-    __syncthreads();
+  };
+  request(t0);
+  deposit(0);
+  request(min(t0 + A.T, A.tiles - 1));
+  __syncthreads();
+  for (int tile = t0, buf = 0; tile < A.tiles; tile += A.T, buf ^= 2 * TS) {
     const int img = tile / A.tpi, q = (tile - img * A.tpi) * 64 + 4 * j;
     const bool ok = q < HW;  // HW % 4 == 0: a lane's four pixels are in or out together
     const int qc = ok ? q : 0;
@@ -337,21 +341,28 @@ __global__ __launch_bounds__(512) void k_dgrad1p(Dgrad1Args A, Dgrad1Lower B) {
       x4[r] = ldg4(xp + (int64_t)ch(r) * HW);
       g4[r] = ldg4(rp + (int64_t)ch(r) * HW);
     }
-    request(min(tile + A.T, A.tiles - 1));
     __builtin_amdgcn_sched_barrier(0);  // all of these are in flight before the products
+    // operands two steps ahead of their products, held there by scheduling barriers (left alone, the compiler reads two
+    // and waits for them)
+    constexpr int S = NCH * 4;
+    float4 d[3];
+    auto operand = [&](int s) { return lds_ld4(&tile_db[buf + s / S * TS + (4 * (s % S) + g) * 64 + 4 * j]); };
+    d[0] = operand(0);
+    d[1] = operand(1);
 #pragma unroll
     for (int li = 0; li < 2; ++li) {
       f32x4 acc[4];
 #pragma unroll
       for (int t = 0; t < 4; ++t) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int c = 0; c < NCH; ++c)
+      for (int i = 0; i < S; ++i) {
+        const int s = li * S + i;
+        if (s + 2 < 2 * S) d[(s + 2) % 3] = operand(s + 2);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-          const float4 d = *reinterpret_cast<const float4*>(&tile_db[li * TS + (c * 16 + 4 * ks + g) * 64 + 4 * j]);
-#pragma unroll
-          for (int t = 0; t < 4; ++t) acc[t] = mfma16(elem(w[li][c], ks), elem(d, t), acc[t]);
-        }
+        for (int t = 0; t < 4; ++t) acc[t] = mfma16(elem(w[li][i / 4], i % 4), elem(d[s % 3], t), acc[t]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -366,6 +377,10 @@ __global__ __launch_bounds__(512) void k_dgrad1p(Dgrad1Args A, Dgrad1Lower B) {
         }
         g4[r] = make_float4(o[0], o[1], o[2], o[3]);
       }
+      if (li == 0) {  // the next tile to the other buffer, whose reads ended before the last barrier
+        deposit(buf ^ (2 * TS));
+        request(min(tile + 2 * A.T, A.tiles - 1));
+      }
     }
     if (ok) {
       float* op = A.G + (int64_t)img * A.g_stride + q;
@@ -373,6 +388,7 @@ __global__ __launch_bounds__(512) void k_dgrad1p(Dgrad1Args A, Dgrad1Lower B) {
       for (int r = 0; r < 4; ++r)
         if (m0 + 4 * g + r < A.C) *reinterpret_cast<float4*>(op + (int64_t)ch(r) * HW) = g4[r];
     }
+    __syncthreads();
   }
 #pragma unroll
   for (int li = 0; li < 2; ++li)
@@ -457,7 +473,7 @@ hipError_t bwd32_dgrad1(const Bwd32Layer& L, hipStream_t st) {
     const dim3 grid((unsigned)A.T, (unsigned)((L.c + 127) / 128));
 #define DNB_L(NCH)                                                                                            \
   do {                                                                                                        \
-    const size_t lds = (size_t)2 * NCH * 16 * 64 * sizeof(float);                                             \
+    const size_t lds = (size_t)4 * NCH * 16 * 64 * sizeof(float);                                             \
     if (L.first) hipLaunchKernelGGL((k_dgrad1p<NCH, true>), grid, dim3(512), lds, st, A, B);                  \
     else hipLaunchKernelGGL((k_dgrad1p<NCH, false>), grid, dim3(512), lds, st, A, B);                         \
   } while (0)

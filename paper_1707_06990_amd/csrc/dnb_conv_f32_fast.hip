@@ -1549,25 +1549,36 @@ __device__ __forceinline__ void wgrad3x3_body(const Wg3Args& A3, int bx, int by,
     auto steps = [&](auto wv) {
       constexpr int WV = decltype(wv)::value;
       constexpr int T0 = WV * TPW, T1 = (T0 + TPW < NT) ? T0 + TPW : NT;
+      // a row of three taps is read while the one before it is multiplied
+      struct Row { float4 V; float eL, eR; };
+      auto read = [&](int sub, int T) {
+        const int y = (T / 9) % CTW, di = (T % 9) / 3 - 1;
+        const int pw = (ms * 4 + sub) * 16 + 4 * kk, wc = (q0 + pw) % W;
+        const int o = (y * 16 + r) * PA + pw + 4 + W + di * W;
+        Row x;
+        x.V = lds_ld4(&lds[o]);
+        x.eL = wc == 0 ? 0.f : lds[o - 1];
+        x.eR = wc + 3 == W - 1 ? 0.f : lds[o + 4];
+        return x;
+      };
+      Row row, next = read(0, T0);
 #pragma unroll
       for (int sub = 0; sub < 4; ++sub) {
-        const int pw = (ms * 4 + sub) * 16 + 4 * kk, wc = (q0 + pw) % W;
-        const bool maskL = wc == 0, maskR = wc + 3 == W - 1;
-        float4 V = zero4();
-        float eL = 0.f, eR = 0.f;
 #pragma unroll
         for (int T = T0; T < T1; ++T) {
-          const int x = T / (CTW * 9), y = (T / 9) % CTW, t = T % 9, di = t / 3 - 1, dj = t % 3 - 1;
+          const int x = T / (CTW * 9), t = T % 9, dj = t % 3 - 1;
           if (T == T0 || t % 3 == 0) {  // first tap of this row in the wave's range
-            const int o = (y * 16 + r) * PA + pw + 4 + W + di * W;
-            V = lds_ld4(&lds[o]);
-            eL = maskL ? 0.f : lds[o - 1];
-            eR = maskR ? 0.f : lds[o + 4];
+            row = next;
+            const int T2 = T - t % 3 + 3;
+            if (T2 < T1) next = read(sub, T2);
+            else if (sub < 3) next = read(sub + 1, T0);
+            __builtin_amdgcn_sched_barrier(0);
           }
-          const float b0 = dj < 0 ? eL : (dj == 0 ? V.x : V.y);
+          const float4 V = row.V;
+          const float b0 = dj < 0 ? row.eL : (dj == 0 ? V.x : V.y);
           const float b1 = dj < 0 ? V.x : (dj == 0 ? V.y : V.z);
           const float b2 = dj < 0 ? V.y : (dj == 0 ? V.z : V.w);
-          const float b3 = dj < 0 ? V.z : (dj == 0 ? V.w : eR);
+          const float b3 = dj < 0 ? V.z : (dj == 0 ? V.w : row.eR);
           f32x4& d = acc[T - T0];
           d = mfma16(A[sub][x].x, b0, d);
           d = mfma16(A[sub][x].y, b1, d);
