@@ -501,12 +501,14 @@ int backward_plain3x3(dnb_block* b, const float* params, const float* y, const f
     if (recompute)  // re-populate storage 1 and 2 for this layer
       DNB_TRY(launch_bn_relu(y, ys, S2, (int64_t)c * hw, S1, (int64_t)c * hw, n, c, hw, p.g1, p.b1,
                              StatsSrc{mean_y, istd_y, nullptr, 0, 0, 0, d.eps}, st));
-    DNB_TRY(launch_conv_wgrad(S2, (int64_t)c * hw, gl, ys, gp.W3, n, c, k, d.h, d.w, 9, partA, nullptr, st));
+    PendingSum own;  // the sum of its partials goes out with BN's reduction
+    DNB_TRY(launch_conv_wgrad(S2, (int64_t)c * hw, gl, ys, gp.W3, n, c, k, d.h, d.w, 9, partA, nullptr, st, nullptr, nullptr, nullptr,
+                              nullptr, &own));
     const size_t k16 = (size_t)((k + 15) & ~15), c16 = (size_t)((c + 15) & ~15);
     DNB_TRY(launch_conv_igemm(gl, ys, WeightView{p.W3, 9, (int64_t)c * 9, 1}, pack + b->pk[l] + 9 * k16 * c16, dS2, (int64_t)c * hw,
                               n, k, c, d.h, d.w, 9, nullptr, st));
     DNB_TRY(launch_bn_relu_bwd(S1, (int64_t)c * hw, dS2, (int64_t)c * hw, G, ys, true, n, c, hw, p.g1, p.b1,
-                               mean_y, istd_y, gp.g1, gp.b1, part, st));
+                               mean_y, istd_y, gp.g1, gp.b1, part, st, 3, nullptr, nullptr, &own));
   }
   DNB_TRY(launch_copy_slab(G, ys, dx0, (int64_t)d.c0 * hw, n, (int64_t)d.c0 * hw, st));
   return DNB_OK;

@@ -9,6 +9,7 @@
 #include <mutex>
 
 #include "../../include/dnb.h"
+#include "dnb_f32_dev.h"
 #include "dnb_internal.h"
 #include "dnb_stats.h"
 
@@ -220,21 +221,27 @@ __global__ __launch_bounds__(kThreads) void k_bn_relu_two(BnReluArgs A, int ca, 
 
 // ----------------------------------------------------------------------------- BN + ReLU backward
 
-// grid (c, splits): partial sums of dz and dz*xhat over a range of images.
+// grid (c, splits, and rows of workgroups for a pending sum that the launch carries): partial sums of dz and dz*xhat over a
+// range of images.
 template <int V>
 __global__ __launch_bounds__(kThreads) void k_bn_bwd_partial(
     const float* __restrict__ x, int64_t x_stride, const float* __restrict__ dact,
     int64_t dact_stride, int n, int hw, int ipb, const float* __restrict__ gamma,
     const float* __restrict__ beta, const float* __restrict__ mean, const float* __restrict__ istd,
-    float* __restrict__ part) {
+    float* __restrict__ part, int splits, SumRole sr) {
+  if ((int)blockIdx.y >= splits) {  // extra workgroups: a pending sum of partials
+    const int wg = ((int)blockIdx.y - splits) * gridDim.x + blockIdx.x;
+    if (wg < sr.wgs) sum_role(sr, wg);
+    return;
+  }
   if (V == 4) {  // the vector form lives in dnb_stats.h: the weight-gradient launch can carry it too
     const BnBwdPartialArgs A{x, x_stride, dact, dact_stride, n, hw, ipb, gamma, beta, mean, istd, part,
-                             (int)gridDim.x, (int)gridDim.y};
+                             (int)gridDim.x, splits};
     bn_bwd_partial_body4(A, blockIdx.x, blockIdx.y);
     return;
   }
   __shared__ float red[kThreads / 64];
-  const int ch = blockIdx.x, s = blockIdx.y, splits = gridDim.y;
+  const int ch = blockIdx.x, s = blockIdx.y;
   const int n0 = s * ipb, ni = min(n, n0 + ipb) - n0;
   float scale, shift;
   const float mu = mean[ch], is = istd[ch];
@@ -459,19 +466,22 @@ hipError_t launch_bn_relu_bwd(const float* x, int64_t x_stride, const float* dac
                               int n, int c, int hw, const float* gamma, const float* beta,
                               const float* mean, const float* istd, float* dgamma, float* dbeta,
                               float* partials, hipStream_t st, int passes, hipEvent_t ev_start,
-                              hipEvent_t ev_stop) {
-  if (n <= 0 || c <= 0 || hw <= 0) return hipSuccess;
+                              hipEvent_t ev_stop, PendingSum* absorb) {
+  if (n <= 0 || c <= 0 || hw <= 0) return absorb ? launch_pending_sum(absorb, st) : hipSuccess;
   const Split p = split_plan(n, c, hw);
   const bool v4 = (hw % 4 == 0) && (x_stride % 4 == 0) && (dact_stride % 4 == 0) &&
                   (du_stride % 4 == 0) && aligned16(x) && aligned16(dact) && aligned16(du);
   dim3 grid((unsigned)c, (unsigned)p.gs);
   if (passes & 1) {
+    const SumRole sr = make_sum_role(absorb);
+    const dim3 gp((unsigned)c, (unsigned)(p.gs + (sr.wgs + c - 1) / c));
+    const size_t lds = sr.kind ? kThreads * sizeof(float) : 0;
     if (v4)
-      hipLaunchKernelGGL(k_bn_bwd_partial<4>, grid, dim3(kThreads), 0, st, x, x_stride, dact, dact_stride,
-                         n, hw, p.ipb, gamma, beta, mean, istd, partials);
+      hipLaunchKernelGGL(k_bn_bwd_partial<4>, gp, dim3(kThreads), lds, st, x, x_stride, dact, dact_stride,
+                         n, hw, p.ipb, gamma, beta, mean, istd, partials, p.gs, sr);
     else
-      hipLaunchKernelGGL(k_bn_bwd_partial<1>, grid, dim3(kThreads), 0, st, x, x_stride, dact, dact_stride,
-                         n, hw, p.ipb, gamma, beta, mean, istd, partials);
+      hipLaunchKernelGGL(k_bn_bwd_partial<1>, gp, dim3(kThreads), lds, st, x, x_stride, dact, dact_stride,
+                         n, hw, p.ipb, gamma, beta, mean, istd, partials, p.gs, sr);
   }
   if (!(passes & 2)) return hipGetLastError();
   const float inv_p = 1.0f / ((float)n * (float)hw);

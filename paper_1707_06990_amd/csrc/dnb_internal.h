@@ -60,6 +60,7 @@ size_t bn_bwd_partial_floats(int n, int c, int hw);
 // Describes the reduction pass (passes & 1) of launch_bn_relu_bwd for another launch to carry
 // (launch_conv_wgrad_pair); false when the 16-byte form does not apply to these operands.
 struct BnBwdPartialArgs;
+struct PendingSum;
 bool bn_bwd_partial_plan(const float* x, int64_t x_stride, const float* dact, int64_t dact_stride, int n, int c,
                          int hw, const float* gamma, const float* beta, const float* mean, const float* istd,
                          float* partials, BnBwdPartialArgs* out);
@@ -68,7 +69,8 @@ hipError_t launch_bn_relu_bwd(const float* x, int64_t x_stride, const float* dac
                               int n, int c, int hw, const float* gamma, const float* beta,
                               const float* mean, const float* istd, float* dgamma, float* dbeta,
                               float* partials, hipStream_t st, int passes = 3 /*1 reduce | 2 apply*/,
-                              hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+                              hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr,
+                              PendingSum* absorb = nullptr /*a pending sum for the reduction to carry; cleared*/);
 
 // The element-wise pass alone, from `psplits` partial pairs per channel in [c][psplits] order.
 hipError_t launch_bn_bwd_apply(const float* x, int64_t x_stride, const float* dact, int64_t dact_stride, float* du,
