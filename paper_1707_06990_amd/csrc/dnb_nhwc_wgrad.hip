@@ -106,10 +106,12 @@ struct Wg3Args {
 // 64 input channels x 16*MG output channels over tps tiles of 64 pixels.  Wave (wave & 1, wave >> 1)
 // holds two c-tiles x MG/2 m-tiles.  The next tile's loads are in flight during the products of the
 // current one; loads are unconditional at clamped addresses, rows past the last pixel become zeros.
-// Workgroups of one pixel range go to one XCD, whose L2 then holds the gradient rows they share.
+// Workgroups go to the eight XCDs in turn; each XCD takes an equal, consecutive share of the (range, column) items, so that
+// its L2 holds the gradient rows that a range's columns share (whole ranges per XCD left XCDs idle where ranges are few:
+// 12 to 6 of them at 14x14 and 7x7).
 template <int MG, bool PRO, typename TG>
 __device__ __forceinline__ void wgrad1_body(const Wg1Args& A, int id, u16* lds) {
-  const int cols = A.gy * A.gz, slot = id >> 3, bx = (slot / cols) * 8 + (id & 7), col = slot % cols;
+  const int cols = A.gy * A.gz, item = (id & 7) * (A.n >> 3) + (id >> 3), bx = item / cols, col = item - bx * cols;
   if (bx >= A.S) return;
   const int cg = col / A.gz, mg = col % A.gz;
   constexpr int GP = gpitch(MG), GV = 2 * MG, GU = MG / 2;
@@ -606,7 +608,7 @@ Plan1 plan1(int P, int cin, int cout, int most) {
   const int tiles = (P + 63) / 64;
   p.S = splits_for(tiles, p.gy * p.gz, WG1_MIN, most);
   p.tps = (tiles + p.S - 1) / p.S;
-  p.n = (p.S + 7) / 8 * 8 * p.gy * p.gz;
+  p.n = (p.S * p.gy * p.gz + 7) / 8 * 8;
   p.lds = (size_t)64 * (AP + gpitch(p.mg)) * sizeof(u16);
   p.floats = (size_t)p.S * p.gy * p.gz * 64 * p.mg * 16;
   return p;
