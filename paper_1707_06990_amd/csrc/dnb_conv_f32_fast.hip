@@ -2098,15 +2098,16 @@ static WgFastPlan plan_wgrad_fast(int n, int cin, int cout, int h, int w, int ta
     }
     p.spi = (hw + 15) / 16;
     p.total_steps = n * p.spi;
-    // About 128 workgroups in all, 1..16 (or 64) steps per wave.  A workgroup ends with a cross-wave sum
+    // About 128 workgroups in all, 192 from 16384 pixels on (DenseNet-BC-100 4595 -> 4565 us a step, shared schedule 5758
+    // -> 5698; 256: 4616 and 5684; with fewer pixels the partials would not fit the gradient scratch), 1..16 (or 64) steps per wave.  A workgroup ends with a cross-wave sum
     // and a partial of mtw*ctw tiles to store, and every partial is read again by the sum that
     // follows, so few long workgroups beat many short ones even when they leave CUs to the other
     // roles of the launch: a target of 512 workgroups (1..8 steps) took 3.3 % more time per
-    // DenseNet-BC-100 step than 128; 96 and 192 were within 0.5 % of 128.
+    // DenseNet-BC-100 step than 128.
     // With many (m, c) tile columns (wide layers, k = 24 nets) the columns alone fill the chip and the
     // pixel ranges can be longer still: a cap of 64 steps there took 1.2 % off the DenseNet-BC-250 step.
     // By itself (a transition's) nothing else fills the CUs: 512 workgroups.
-    const int wgs = alone ? 512 : 128;
+    const int wgs = alone ? 512 : p.total_steps >= 1024 ? 192 : 128;
     int spw = (int)(((int64_t)p.total_steps * p.gy * p.gz + 4 * wgs - 1) / (4 * wgs));
     const int cap = p.gy * p.gz > 8 ? 64 : 16;
     if (spw < 1) spw = 1;
