@@ -251,7 +251,7 @@ def event_time_ms(torch, fn, reps):
 # FETCH_SIZE then WRITE_SIZE, each scaled by the copy kernel of known size): the figure is read from
 # the line "traffic_bytes_per_launch: N" of that file, so it is whatever the committed profile says.
 DOMINANT = {"config2:64": ("k_wgrad_pair<3, 4, 1, 3, true>", "bc100_b64_fp32_wgrad_pair_hbm_traffic.txt"),
-            "config3:64": ("k_wgrad_pair<3, 4, 2, 2, true>", "bc250_b64_fp32_wgrad_pair_hbm_traffic.txt")}
+            "config3:64": ("k_wgrad_pair<3, 8, 2, 2, true>, up to 256 channels <3, 4, 2, 2, true>", "bc250_b64_fp32_wgrad_pair_hbm_traffic.txt")}
 
 
 def measured_traffic(key):

@@ -2232,7 +2232,7 @@ bool launch_wgrad_pair_fast(const float* in1, int64_t in1_stride, const float* g
   const int hw = h * w;
   const Wg1Args A1{in1, in1_stride, g1, g1_stride, part1, cin1, B, hw, p1.spi, p1.total_steps, p1.steps_per_wg, fold1};
   const Wg3Args A3{in3, in3_stride, g3, g3_stride, part3, B, cout3, h, w, p3.tiles_per_img, p3.nms, p3.PA, fold3};
-  const int n1 = (p1.gx * p1.gy * p1.gz + 7) / 8 * 8, n3 = p3.gx * p3.gy * p3.gz;  // 1x1: whole pixel ranges per XCD
+  const int n1 = (p1.gx * p1.gy * p1.gz + 7) / 8 * 8, n3 = p3.gx * p3.gy * p3.gz;  // 1x1: equal shares per XCD
   const BnBwdPartialArgs bna = bn ? *bn : BnBwdPartialArgs{};
   const int nbn = bn ? bn->c * bn->splits : 0;
   const Bn1Finish fina = fin ? *fin : Bn1Finish{};

@@ -241,6 +241,19 @@ def test_bf16_full_size_blocks_match_oracle(dnb, oracle, which, i):
     check_bf16_block(dnb, oracle, cfg, x0, lp, dy, storage_allowance=True)
 
 
+def test_bf16_more_layers_than_lanes(dnb, oracle):
+    """67 layers: the packing kernel adds up the sizes of the layers before its own with a lane for each, in turns of 64.
+    The last three against the plain block on the features that the others produced (through all 67 layers of 128
+    pixels each, bf16 storage alone moves the output by TOL)."""
+    cfg = wl.BlockCfg(2, 16, 8, 8, 67, 8, 16)
+    x0, lp, dy = wl.make_block_inputs(cfg, affine="random")
+    y = run_block_gpu_bf16(dnb, cfg, to_bf16_values(x0), lp, to_bf16_values(dy))["y"]
+    c = cfg.c0 + 64 * cfg.growth
+    tail = wl.BlockCfg(cfg.n, c, cfg.h, cfg.w, 3, cfg.growth, cfg.bottleneck)
+    ores, _ = run_block_oracle(oracle, tail, y[:, :c], lp[64:], dy)
+    assert_close(y[:, c:], ores.y[:, c:], TOL, "the last three layers")
+
+
 def test_bf16_bytes_and_unsupported_combinations(dnb):
     cfg = CFGS[3]
     h = dnb.dnb_block_create(cfg.n, cfg.c0, cfg.h, cfg.w, cfg.layers, cfg.growth, cfg.bottleneck,

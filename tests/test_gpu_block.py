@@ -299,6 +299,14 @@ def test_layers_in_pairs_match_oracle(dnb, oracle, cfg, schedule):
     compare_with_kernel_decisions(dnb, oracle, cfg, x0, lp, dy, schedule=schedule)
 
 
+@pytest.mark.parametrize("schedule", [0, 2])
+def test_more_layers_than_lanes(dnb, oracle, schedule):
+    """70 layers: the packing kernels add up the sizes of the layers before their own with a lane for each, in turns of 64."""
+    cfg = wl.BlockCfg(2, 8, 8, 8, 70, 4, 8)
+    x0, lp, dy = wl.make_block_inputs(cfg, affine="random")
+    compare_with_kernel_decisions(dnb, oracle, cfg, x0, lp, dy, schedule=schedule)
+
+
 # the 3x3 data gradient with a wave per M-tile (17 <= k <= 32, 64 < B <= 128): six and eight waves, six and eight
 # K-steps, each width, ranges of channels that end inside a tile, fewer tiles than XCDs, several tiles a workgroup
 WAVES = [wl.BlockCfg(2, 30, 8, 8, 3, 17, 65), wl.BlockCfg(3, 24, 16, 16, 3, 24, 96), wl.BlockCfg(2, 20, 8, 16, 3, 28, 100),
