@@ -1317,12 +1317,6 @@ __device__ __forceinline__ void wgrad1x1_wide_body(const Wg1Args& A, int bx, int
     aoff[y] = c * HW;
     fl[y] = PRO ? A.fold[c] : make_float2(1.f, 0.f);
   }
-  f32x4 acc[WM][4];
-#pragma unroll
-  for (int x = 0; x < WM; ++x)
-#pragma unroll
-    for (int y = 0; y < 4; ++y) acc[x][y] = (f32x4){0.f, 0.f, 0.f, 0.f};
-
   // loads are unconditional at clamped addresses; pixels past the image are zeroed when they are staged
   float4 G[WM], V[4];
   int img = s_begin / spi, qs = (s_begin - img * spi) * 32;  // of the step requested next
@@ -1342,52 +1336,70 @@ __device__ __forceinline__ void wgrad1x1_wide_body(const Wg1Args& A, int bx, int
     }
   };
   request();
-  for (int s = s_begin; s < s_end; ++s) {
-    __syncthreads();  // the tile of the last step has been read
-#pragma unroll
-    for (int x = 0; x < WM; ++x) lds_st4(&lds[wide_at(x * 32 + prow, pc)], ok ? G[x] : zero4());
-#pragma unroll
-    for (int y = 0; y < 4; ++y) {
-      float4 v = V[y];
-      if (PRO) {
-        v.x = fmaxf(__fmaf_rn(v.x, fl[y].x, fl[y].y), 0.f);
-        v.y = fmaxf(__fmaf_rn(v.y, fl[y].x, fl[y].y), 0.f);
-        v.z = fmaxf(__fmaf_rn(v.z, fl[y].x, fl[y].y), 0.f);
-        v.w = fmaxf(__fmaf_rn(v.w, fl[y].x, fl[y].y), 0.f);
-      }
-      lds_st4(&lds[wide_at(WM * 32 + y * 32 + prow, pc)], ok ? v : zero4());
-    }
-    __syncthreads();
-    request();
-    if (busy) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        float4 Af[WM], Bf[4];
-#pragma unroll
-        for (int x = 0; x < WM; ++x) Af[x] = lds_ld4(&lds[wide_at(wr0 + x * 16 + r, h * 4 + kk)]);
-#pragma unroll
-        for (int y = 0; y < 4; ++y) Bf[y] = lds_ld4(&lds[wide_at(WM * 32 + wc0 + y * 16 + r, h * 4 + kk)]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int x = 0; x < WM; ++x)
-#pragma unroll
-            for (int y = 0; y < 4; ++y) acc[x][y] = mfma16(elem(Af[x], e), elem(Bf[y], e), acc[x][y]);
-      }
-    }
-  }
   float* pb = A.part + (int64_t)bx * cout * cin;
+  // A sum of more than 32 steps is formed in parts that are added in the partial: as one chain of 73 steps (the 1008 channels of
+  // DenseNet-BC-250's first block) it was 6.0e-7 from the sum in 64 bits, in parts it is 4.26e-7 (narrow tiles: 4.28e-7).
+  for (int s = s_begin; s < s_end;) {
+    const bool first = s == s_begin;
+    const int end = min(s_end, s + 32);
+    f32x4 acc[WM][4];
 #pragma unroll
-  for (int x = 0; x < WM; ++x)
+    for (int x = 0; x < WM; ++x)
 #pragma unroll
-    for (int y = 0; y < 4; ++y) {
-      const int c = c0 + wc0 + y * 16 + r;
+      for (int y = 0; y < 4; ++y) acc[x][y] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    for (; s < end; ++s) {
+      __syncthreads();  // the tile of the last step has been read
 #pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        const int m = m0 + wr0 + x * 16 + 4 * kk + rr;
-        if (m < cout && c < cin) pb[(int64_t)m * cin + c] = acc[x][y][rr];
+      for (int x = 0; x < WM; ++x) lds_st4(&lds[wide_at(x * 32 + prow, pc)], ok ? G[x] : zero4());
+#pragma unroll
+      for (int y = 0; y < 4; ++y) {
+        float4 v = V[y];
+        if (PRO) {
+          v.x = fmaxf(__fmaf_rn(v.x, fl[y].x, fl[y].y), 0.f);
+          v.y = fmaxf(__fmaf_rn(v.y, fl[y].x, fl[y].y), 0.f);
+          v.z = fmaxf(__fmaf_rn(v.z, fl[y].x, fl[y].y), 0.f);
+          v.w = fmaxf(__fmaf_rn(v.w, fl[y].x, fl[y].y), 0.f);
+        }
+        lds_st4(&lds[wide_at(WM * 32 + y * 32 + prow, pc)], ok ? v : zero4());
+      }
+      __syncthreads();
+      request();
+      if (busy) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          float4 Af[WM], Bf[4];
+#pragma unroll
+          for (int x = 0; x < WM; ++x) Af[x] = lds_ld4(&lds[wide_at(wr0 + x * 16 + r, h * 4 + kk)]);
+#pragma unroll
+          for (int y = 0; y < 4; ++y) Bf[y] = lds_ld4(&lds[wide_at(WM * 32 + wc0 + y * 16 + r, h * 4 + kk)]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int x = 0; x < WM; ++x)
+#pragma unroll
+              for (int y = 0; y < 4; ++y) acc[x][y] = mfma16(elem(Af[x], e), elem(Bf[y], e), acc[x][y]);
+        }
       }
     }
+    int ld = cin;  // (opaque: the rows' addresses are formed here, not kept in registers over the products)
+    asm volatile("" : "+s"(ld));
+#pragma unroll
+    for (int x = 0; x < WM; ++x)
+#pragma unroll
+      for (int y = 0; y < 4; ++y) {
+        const int c = c0 + wc0 + y * 16 + r, m = m0 + wr0 + x * 16 + 4 * kk;
+        if (c >= ld) continue;
+        float* o = pb + (int64_t)m * ld + c;
+        if (!first) {
+#pragma unroll
+          for (int rr = 0; rr < 4; ++rr)
+            if (m + rr < cout) acc[x][y][rr] += o[rr * ld];
+        }
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr)
+          if (m + rr < cout) o[rr * ld] = acc[x][y][rr];
+      }
+  }
 }
 
 // CTW = 8: the wide form
