@@ -1284,7 +1284,7 @@ __device__ __forceinline__ void wgrad1x1_body(const Wg1Args& A, int bx, int by, 
     }
 }
 
-// The wide form, for more than 48 output channels beside a 3x3: a workgroup forms WM*32 x 128 outputs, its four waves
+// The wide form, for 49..96 output channels beside a 3x3: a workgroup forms WM*32 x 128 outputs, its four waves
 // WM*16 x 64 each (two by two).  Steps are 32 pixels: both operands' rows (128 bytes of a row, a cache line) go through
 // registers, requested one step ahead, and BN+ReLU into an LDS tile that all waves read, so a row crosses the L2 once
 // for 128 (WM*32) outputs instead of once for 64 (48), and no two waves hold the same tile: nothing is added at the end.
@@ -2084,18 +2084,18 @@ static WgFastPlan plan_wgrad_fast(int n, int cin, int cout, int h, int w, int ta
     p.ctw = ctiles >= 4 ? 4 : ctiles;
     p.gy = (ctiles + p.ctw - 1) / p.ctw;
     p.gz = (mtiles + p.mtw - 1) / p.mtw;
-    // More than 48 output channels and more than eight columns of narrow tiles, beside a 3x3: the wide form, about one
+    // 49..96 output channels and more than eight columns of narrow tiles, beside a 3x3: the wide form, about one
     // workgroup per CU whatever the shape (they share the matrix cores with the 3x3's; 192 / 320 / 384 / 512 workgroups: 2.3
     // / 2.2 / 1.3 / 0.9 % more time per DenseNet-BC-250 step; fewer also keep the partials small).  With the narrow tiles,
     // whose pixel ranges were dealt to the XCDs whole, few-pixel layers used only three or four of the eight: 90 -> 61 us
     // per launch on average, 62 -> 25 on the 8x8 block (P = 4096, 750..1700 channels).  With fewer columns the two
     // are alike (54..74 us against 54..82) and the narrow tiles leave fewer partial sums.  A transition's weight gradient,
-    // alone on the chip and up to 516 channels wide, is better balanced in narrow tiles (395 + 785 us against 400 + 953).
-    if (!alone && cout > 48 && p.gy * p.gz > 8 && (hw % 32 == 0 || hw >= 128)) {
+    // alone on the chip and up to 516 channels wide, is better balanced in narrow tiles (395 + 785 us against 400 + 953), and
+    // with more than 96 outputs the narrow ones are faster (128 outputs, 300..650 channels, 16384 pixels: a block of twelve layers
+    // 2676 us against 2804 and 2850 in wide tiles of 64 and 128 rows).
+    if (!alone && cout > 48 && cout <= 96 && p.gy * p.gz > 8 && (hw % 32 == 0 || hw >= 128)) {
       p.ctw = 8;
-      p.mtw = 4;  // the fewest rows of padding, then the largest tile
-      for (int wm = 3; wm >= 2; --wm)
-        if ((cout + 32 * wm - 1) / (32 * wm) * wm < (cout + 32 * p.mtw - 1) / (32 * p.mtw) * p.mtw) p.mtw = wm;
+      p.mtw = cout <= 64 ? 2 : 3;
       p.gy = (cin + 127) / 128;
       p.gz = (cout + 32 * p.mtw - 1) / (32 * p.mtw);
       p.spi = (hw + 31) / 32;
@@ -2191,7 +2191,7 @@ bool launch_wgrad_fast(const float* in, int64_t in_stride, const float* g, int64
   } while (0)
     const int key = p.mtw * 10 + p.ctw;
     switch (key) {
-      case 48: DNB_L(4, 8); break; case 38: DNB_L(3, 8); break; case 28: DNB_L(2, 8); break;
+      case 38: DNB_L(3, 8); break; case 28: DNB_L(2, 8); break;
       case 34: DNB_L(3, 4); break; case 33: DNB_L(3, 3); break; case 32: DNB_L(3, 2); break; case 31: DNB_L(3, 1); break;
       case 24: DNB_L(2, 4); break; case 23: DNB_L(2, 3); break; case 22: DNB_L(2, 2); break; case 21: DNB_L(2, 1); break;
       case 14: DNB_L(1, 4); break; case 13: DNB_L(1, 3); break; case 12: DNB_L(1, 2); break; default: DNB_L(1, 1); break;
@@ -2259,7 +2259,7 @@ bool launch_wgrad_pair_fast(const float* in1, int64_t in1_stride, const float* g
   } while (0)
 #define DNB_P1(M3, C3)                                                                          \
   switch (p1.mtw * 10 + p1.ctw) {                                                                         \
-    case 48: DNB_P(4, 8, M3, C3); break; case 38: DNB_P(3, 8, M3, C3); break; case 28: DNB_P(2, 8, M3, C3); break; \
+    case 38: DNB_P(3, 8, M3, C3); break; case 28: DNB_P(2, 8, M3, C3); break; \
     case 34: DNB_P(3, 4, M3, C3); break; case 33: DNB_P(3, 3, M3, C3); break; case 32: DNB_P(3, 2, M3, C3); break; \
     default: DNB_P(3, 1, M3, C3); break;                                                                  \
   }

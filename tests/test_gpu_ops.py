@@ -383,9 +383,10 @@ def test_layer_weight_gradients_in_one_launch(dnb, oracle, n, cin, B, k, h, w, w
                                            (5, 200, 128, 32, 8, 8), (1, 190, 140, 32, 12, 16), (3, 321, 52, 13, 4, 40),
                                            (2, 256, 96, 24, 8, 8)])
 def test_layer_weight_gradients_in_wide_tiles(dnb, oracle, n, cin, B, k, h, w):
-    """The 1x1's wide tiles (more than 48 output channels, more than eight narrow columns) at the edges of its rule: one channel past a tile, output
-    tiles of 64, 96 and 128 rows full and ragged, images whose last 32 pixels are not all there, fewer steps than
-    workgroups; and the widest input that still takes the narrow ones."""
+    """The 1x1's wide tiles (49..96 output channels, more than eight narrow columns) at the edges of its rule: one channel past a
+    tile, output tiles of 64 and 96 rows full and ragged, images whose last 32 pixels are not all there, fewer steps than
+    workgroups; and the widest input
+    and the outputs that take the narrow ones."""
     layer_wgrads_case(dnb, oracle, n, cin, B, k, h, w, True, seed=43)
 
 
