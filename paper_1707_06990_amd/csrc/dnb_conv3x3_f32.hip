@@ -124,39 +124,57 @@ __global__ __launch_bounds__(512, 2) void k_conv3x3_v5(const float* __restrict__
       deposit(i);
       wave_sync();
       request(i + 1);
-      // Rows that are no 16-byte vectors (four waves a workgroup): operands two steps ahead of their products, held there by
-      // scheduling barriers (left alone, the compiler reads a step's four and waits for them; 28x28 images, batch 37: 1830 ->
-      // 1816 us a step).  With eight waves the other one of a SIMD covers that.
-      constexpr bool AHEAD = !VEC;
-      float b[3][4];
-      auto operand = [&](int s, float(&o)[4]) {
-        const float* base = my + g * CS + j + halo + (s / 12 - 1) * W + s / 4 % 3 - 1 + 4 * (s % 4) * CS;
+      if constexpr (!VEC && MT == 1) {
+        // operands two steps ahead of their products, held there by scheduling barriers (left alone, the compiler reads a
+        // step's four and waits for them; 28x28 images, batch 37: 1904 -> 1898 us a step).  Not with 16-byte rows, where the
+        // other wave of a SIMD covers that.
+        float b[3][4];
+        auto operand = [&](int s, float(&o)[4]) {
+          const float* base = my + g * CS + j + halo + (s / 12 - 1) * W + s / 4 % 3 - 1 + 4 * (s % 4) * CS;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) o[t] = base[16 * t];
-      };
-      if (AHEAD) {
+          for (int t = 0; t < 4; ++t) o[t] = base[16 * t];
+        };
         operand(0, b[0]);
         operand(1, b[1]);
+#pragma unroll
+        for (int s = 0; s < 36; ++s) {
+          const int t9 = s / 4, ks = s % 4;
+          if (s + 2 < 36) operand(s + 2, b[(s + 2) % 3]);
+          __builtin_amdgcn_sched_barrier(0);
+          float x[4];
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            x[t] = b[s % 3][t];
+            if (t9 % 3 == 0 && !lok[t]) x[t] = 0.f;
+            if (t9 % 3 == 2 && !rok[t]) x[t] = 0.f;
+          }
+#pragma unroll
+          for (int a = 0; a < MT; ++a)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[a][t] = mfma16(elem(w4[t9 % WD][a], ks), x[t], acc[a][t]);
+          __builtin_amdgcn_sched_barrier(0);
+          if (ks == 3) wload(i + (t9 + WD >= 9 ? 1 : 0), (t9 + WD) % 9, w4[t9 % WD]);
+        }
+        continue;
       }
 #pragma unroll
-      for (int s = 0; s < 36; ++s) {
-        const int t9 = s / 4, ks = s % 4;
-        if (!AHEAD) operand(s, b[s % 3]);
-        else if (s + 2 < 36) operand(s + 2, b[(s + 2) % 3]);
-        if (AHEAD) __builtin_amdgcn_sched_barrier(0);
-        float x[4];
+      for (int t9 = 0; t9 < 9; ++t9) {
+        const float* base = my + g * CS + j + halo + (t9 / 3 - 1) * W + t9 % 3 - 1;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          x[t] = b[s % 3][t];
-          if (t9 % 3 == 0 && !lok[t]) x[t] = 0.f;
-          if (t9 % 3 == 2 && !rok[t]) x[t] = 0.f;
+        for (int ks = 0; ks < 4; ++ks) {
+          float b[4];
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            b[t] = base[4 * ks * CS + 16 * t];
+            if (t9 % 3 == 0 && !lok[t]) b[t] = 0.f;
+            if (t9 % 3 == 2 && !rok[t]) b[t] = 0.f;
+          }
+#pragma unroll
+          for (int a = 0; a < MT; ++a)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[a][t] = mfma16(elem(w4[t9 % WD][a], ks), b[t], acc[a][t]);
         }
-#pragma unroll
-        for (int a = 0; a < MT; ++a)
-#pragma unroll
-          for (int t = 0; t < 4; ++t) acc[a][t] = mfma16(elem(w4[t9 % WD][a], ks), x[t], acc[a][t]);
-        if (AHEAD) __builtin_amdgcn_sched_barrier(0);
-        if (ks == 3) wload(i + (t9 + WD >= 9 ? 1 : 0), (t9 + WD) % 9, w4[t9 % WD]);
+        wload(i + (t9 + WD >= 9 ? 1 : 0), (t9 + WD) % 9, w4[t9 % WD]);
       }
     }
   }
