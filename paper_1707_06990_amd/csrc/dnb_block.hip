@@ -30,6 +30,7 @@ struct dnb_block {
   size_t stat_floats;                        // fused bf16 forward: a second buffer of statistics' partials so far into
                                              // off_part, or (0) at off_G
   size_t off_partA[2], off_partB[2];         // partials of the 3x3 / 1x1 weight gradients, layer l's in [l & 1]
+  size_t partB_floats;                       // floats of a partB (fp32)
   // with concurrency on, the fp32 backward with separate BN passes runs three chains: the data-gradient
   // chain on the caller's stream and the two weight-gradient chains on these helper streams (created at
   // the first such backward call); off, and in the merged chains, everything runs on the caller's stream
@@ -88,8 +89,8 @@ T layer_ptrs(const dnb_block* b, P* base, int l) {
 
 // Partial floats of a weight gradient on the block's own buffers (16-byte aligned, image strides multiples of
 // h*w): the vector kernel wherever its plan takes the shape, else the any-shape one.
-size_t block_wgrad_partial_floats(const dnb_block_desc& d, int cin, int cout, int taps) {
-  const size_t f = conv_wgrad_fast_partial_floats(d.n, cin, cout, d.h, d.w, taps);
+size_t block_wgrad_partial_floats(const dnb_block_desc& d, int cin, int cout, int taps, size_t most = SIZE_MAX) {
+  const size_t f = conv_wgrad_fast_partial_floats(d.n, cin, cout, d.h, d.w, taps, false, most);
   return f ? f : conv_wgrad_partial_floats(d.n, cin, cout, d.h, d.w, taps);
 }
 
@@ -432,7 +433,7 @@ int backward_f32(dnb_block* b, const float* params, const float* y, const float*
                                    l == m ? ys : (int64_t)k * hw, gp.W3, k,
                                    (float*)(ws + b->off_partA[l & 1]),
                                    fused ? (const float2*)(ws + b->off_fold2[l]) : nullptr, n, B, d.h, d.w, st, &pendB, &pendA, nullptr,
-                                   nullptr, nullptr, nullptr, nullptr, &fin));
+                                   nullptr, nullptr, nullptr, nullptr, &fin, b->partB_floats));
     lower = upper;
   }
   DNB_TRY(launch_pending_sum(&pendA, st));
@@ -520,6 +521,8 @@ int backward_plain3x3(dnb_block* b, const float* params, const float* y, const f
 // after the other on one stream can share one: its offset in the block's own workspace, and the offset (from
 // the start of that workspace) at which the block is to look for it instead.
 size_t dnb::block_tail_offset(const dnb_block* b) { return b->off_tail; }
+// (for tests of the plan)
+bool dnb::block_layers_in_pairs(const dnb_block* b) { return b->pairs; }
 void dnb::block_move_tail(dnb_block* b, size_t to) {
   for (size_t* o : {&b->off_part, &b->off_bwd, &b->off_partA[0], &b->off_partA[1], &b->off_partB[0], &b->off_partB[1], &b->off_K})
     if (*o >= b->off_tail) *o = *o - b->off_tail + to;
@@ -542,7 +545,11 @@ const char* dnb_status_string(int status) {
   }
 }
 
-int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
+int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) { return block_create(desc, 0, out); }
+
+}  // extern "C"
+
+int dnb::block_create(const dnb_block_desc* desc, size_t spare, dnb_block** out) {
   if (!desc || !out) return DNB_E_NULL;
   const dnb_block_desc& d = *desc;
   if (d.n < 1 || d.c0 < 1 || d.h < 1 || d.w < 1 || d.layers < 1 || d.growth < 1 || d.bottleneck < 0)
@@ -665,7 +672,7 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
     }
   }
 
-  size_t part = 0, bwd = 0, partA = 0, partB = 0;
+  size_t part = 0, bwd = 0, partA = 0, partB = 0, partB_least = 0;
   auto need = [&](size_t floats) { if (floats > part) part = floats; };
   b->pk.assign(m + 2, 0);
   size_t pack = 0;  // in floats
@@ -677,12 +684,15 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
       b->pk[l] = pe;
       pe += nhwc::packed_layer_elems(c_in(d, l), k, B);
     }
+    partB_least = partB;
     partA = nhwc::wgrad_partial_floats(d.n, B, k, d.h, d.w, 9);
     pack = (pe + 1) / 2;
   } else {
     for (int l = 1; l <= m; ++l) {
       const size_t f = B > 0 ? block_wgrad_partial_floats(d, c_in(d, l), B, 1) : 0;
+      const size_t g = B > 0 ? block_wgrad_partial_floats(d, c_in(d, l), B, 1, 0) : 0;
       if (f > partB) partB = f;
+      if (g > partB_least) partB_least = g;
     }
     if (B == 0) {
       for (int l = 1; l <= m; ++l) {
@@ -701,106 +711,125 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
   // 1x1 data gradient is consumed where it is formed): the rest of it holds what a backward pass needs and
   // nothing else does, as far as there is room.
   const bool merged = bf16 || (B > 0 && bwd32_ok(d.n, d.h, d.w, k, B));
-  size_t hole = 0, hole_end = 0;
-  if (merged) {
-    hole = align_up(b->off_dS2 + (size_t)k * Ps, 256);
-    hole_end = b->off_dS2 + (size_t)b->cm * Ps;
-  }
-  auto in_hole = [&](size_t& at, size_t bytes) {
-    if (at >= hole_end || bytes > hole_end - at) return false;
-    at = align_up(at + bytes, 256);
-    return true;
-  };
-  // Partial sums of the weight gradients: with a bottleneck two buffers each, used alternately by consecutive layers
-  // (a layer's partials are summed by extra workgroups of the next layer's weight-gradient launch).  Of the 3x3's
-  // and the 1x1's as many in the hole as fill it best.
-  const size_t bytesA = partA * 4, bytesB = partB * 4, buffers = B > 0 ? 2 : 1;
-  struct Fill { size_t a, b, bytes; };
-  auto fill = [&](size_t from) {
-    Fill best{0, 0, 0};
-    for (size_t a = 0; a <= buffers; ++a)
-      for (size_t c = 0; c <= buffers; ++c) {
-        size_t at = from;
-        bool ok = true;
-        for (size_t i = 0; i < a; ++i) ok = ok && in_hole(at, bytesA);
-        for (size_t i = 0; i < c; ++i) ok = ok && in_hole(at, bytesB);
-        if (ok && a * bytesA + c * bytesB >= best.bytes) best = Fill{a, c, a * bytesA + c * bytesB};
-      }
-    return best;
-  };
-  // First of it the second db of layers in pairs, a feature-map gradient like the first: the peak counts none
-  // outside the gradient scratch, so without room for it there layers go one at a time.  Nor are pairs, which save 2
-  // to 7 % of a large bf16 block's step and a few per cent in fp32, worth much memory: in bf16 at most a sixteenth of
-  // the feature maps may be pushed out by it as partial sums (32 images of 56x56, 64 to 256 channels, k = 32: 34 of
-  // 393 MB, and a step of 1256 us one at a time against 1262 in pairs), in fp32 nothing (a DenseNet-BC-100 of 48x48
-  // images took 3.6 % more).
-  b->pairs = merged && m > 1 && (bf16 ? B <= nhwc::kDgrad1MaxB : bwd32_pair_ok(d.n, (int)hw, c_in(d, m - 1), B));
-  if (b->pairs) {
-    size_t at = hole;
-    b->off_db2 = hole;
-    b->pairs = in_hole(at, (size_t)B * Ps) && fill(hole).bytes - fill(at).bytes <= (bf16 ? off / 16 : 0);
-    if (b->pairs) hole = at;
-  }
+  const size_t hole_start = merged ? align_up(b->off_dS2 + (size_t)k * Ps, 256) : 0;
+  const size_t hole_end = merged ? b->off_dS2 + (size_t)b->cm * Ps : 0;
+  // From here on the plan depends on the floats of the 1x1 weight gradient's partials: it is made for a number of them, first
+  // for the fewest, which says whether layers go in pairs.
+  const size_t planned = off;
+  bool decided = false;
+  auto place = [&](size_t partB) {
+    off = planned;
+    part = bwd = 0;
+    b->partB_floats = partB;
+    size_t hole = hole_start;
+    auto in_hole = [&](size_t& at, size_t bytes) {
+      if (at >= hole_end || bytes > hole_end - at) return false;
+      at = align_up(at + bytes, 256);
+      return true;
+    };
+    // Partial sums of the weight gradients: with a bottleneck two buffers each, used alternately by consecutive layers
+    // (a layer's partials are summed by extra workgroups of the next layer's weight-gradient launch).  Of the 3x3's
+    // and the 1x1's as many in the hole as fill it best.
+    const size_t bytesA = partA * 4, bytesB = partB * 4, buffers = B > 0 ? 2 : 1;
+    struct Fill { size_t a, b, bytes; };
+    auto fill = [&](size_t from) {
+      Fill best{0, 0, 0};
+      for (size_t a = 0; a <= buffers; ++a)
+        for (size_t c = 0; c <= buffers; ++c) {
+          size_t at = from;
+          bool ok = true;
+          for (size_t i = 0; i < a; ++i) ok = ok && in_hole(at, bytesA);
+          for (size_t i = 0; i < c; ++i) ok = ok && in_hole(at, bytesB);
+          if (ok && a * bytesA + c * bytesB >= best.bytes) best = Fill{a, c, a * bytesA + c * bytesB};
+        }
+      return best;
+    };
+    // First of it the second db of layers in pairs, a feature-map gradient like the first: the peak counts none
+    // outside the gradient scratch, so without room for it there layers go one at a time.  Nor are pairs, which save 2
+    // to 7 % of a large bf16 block's step and a few per cent in fp32, worth much memory: in bf16 at most a sixteenth of
+    // the feature maps may be pushed out by it as partial sums (32 images of 56x56, 64 to 256 channels, k = 32: 34 of
+    // 393 MB, and a step of 1256 us one at a time against 1262 in pairs), in fp32 nothing (a DenseNet-BC-100 of 48x48
+    // images took 3.6 % more).
+    if (!decided) b->pairs = merged && m > 1 && (bf16 ? B <= nhwc::kDgrad1MaxB : bwd32_pair_ok(d.n, (int)hw, c_in(d, m - 1), B));
+    if (b->pairs) {
+      size_t at = hole;
+      b->off_db2 = hole;
+      b->pairs = in_hole(at, (size_t)B * Ps) && (decided || fill(hole).bytes - fill(at).bytes <= (bf16 ? off / 16 : 0));
+      if (b->pairs) hole = at;
+    }
+    decided = true;
 
-  if (bf16) {
-    need(nhwc::stats_partial_floats(P, d.c0));
-    need(nhwc::conv_stats_partial_floats(d.n, B, d.h, d.w));
-    need(nhwc::conv_stats_partial_floats(d.n, k, d.h, d.w));
-    // the fused forward's second buffer: in the slab, which only the backward pass uses (images of a few pixels, whose
-    // partials outgrow it: behind the first)
-    b->stat_floats = d.schedule == DNB_SCHED_FUSED && part > (size_t)cout * P ? align_up(part, 4) : 0;
-    need(2 * b->stat_floats);
-    size_t p1 = 0;
-    for (int l = 1; l <= m; ++l) {
-      const size_t f = nhwc::bwd_partial1_floats(P, c_in(d, l), b->pairs ? 2 : 1);
-      if (f > p1) p1 = f;
-    }
-    b->near_floats = p1;
-    if (b->pairs) p1 += nhwc::bwd_partial1_near_floats(P, k);
-    b->part1_floats = p1;
-    bwd = p1 + nhwc::bwd_partial2_floats(d.n, d.h, d.w, k, B);
-  } else {
-    need(bn_stats_partial_floats(d.n, d.c0, (int)hw));
-    need(bn_stats_partial_floats(d.n, k, (int)hw));
-    if (B > 0) {
-      need(bn_stats_partial_floats(d.n, B, (int)hw));
-      need(bn_bwd_partial_floats(d.n, B, (int)hw));
-      need(conv_stats_partial_floats(d.n, B, d.h, d.w));  // epilogue statistics of the two convs
-    }
-    need(conv_stats_partial_floats(d.n, k, d.h, d.w));
-    if (merged) {
-      size_t p1 = b->pairs ? bwd32_partial1_near_floats(d.n, (int)hw, k) : 0;
+    if (bf16) {
+      need(nhwc::stats_partial_floats(P, d.c0));
+      need(nhwc::conv_stats_partial_floats(d.n, B, d.h, d.w));
+      need(nhwc::conv_stats_partial_floats(d.n, k, d.h, d.w));
+      // the fused forward's second buffer: in the slab, which only the backward pass uses (images of a few pixels, whose
+      // partials outgrow it: behind the first)
+      b->stat_floats = d.schedule == DNB_SCHED_FUSED && part > (size_t)cout * P ? align_up(part, 4) : 0;
+      need(2 * b->stat_floats);
+      size_t p1 = 0;
       for (int l = 1; l <= m; ++l) {
-        const int c = c_in(d, l);
-        size_t f = bwd32_partial1_floats(d.n, (int)hw, c);
+        const size_t f = nhwc::bwd_partial1_floats(P, c_in(d, l), b->pairs ? 2 : 1);
         if (f > p1) p1 = f;
-        if (b->pairs && l < m && bwd32_pair_ok(d.n, (int)hw, c, B) && (f = bwd32_partial1_pair_floats(d.n, (int)hw, c)) > p1)
-          p1 = f;
       }
+      b->near_floats = p1;
+      if (b->pairs) p1 += nhwc::bwd_partial1_near_floats(P, k);
       b->part1_floats = p1;
-      bwd = p1 + bwd32_partial2_floats(d.n, d.h, d.w, k, B);
+      bwd = p1 + nhwc::bwd_partial2_floats(d.n, d.h, d.w, k, B);
+    } else {
+      need(bn_stats_partial_floats(d.n, d.c0, (int)hw));
+      need(bn_stats_partial_floats(d.n, k, (int)hw));
+      if (B > 0) {
+        need(bn_stats_partial_floats(d.n, B, (int)hw));
+        need(bn_bwd_partial_floats(d.n, B, (int)hw));
+        need(conv_stats_partial_floats(d.n, B, d.h, d.w));  // epilogue statistics of the two convs
+      }
+      need(conv_stats_partial_floats(d.n, k, d.h, d.w));
+      if (merged) {
+        size_t p1 = b->pairs ? bwd32_partial1_near_floats(d.n, (int)hw, k) : 0;
+        for (int l = 1; l <= m; ++l) {
+          const int c = c_in(d, l);
+          size_t f = bwd32_partial1_floats(d.n, (int)hw, c);
+          if (f > p1) p1 = f;
+          if (b->pairs && l < m && bwd32_pair_ok(d.n, (int)hw, c, B) && (f = bwd32_partial1_pair_floats(d.n, (int)hw, c)) > p1)
+            p1 = f;
+        }
+        b->part1_floats = p1;
+        bwd = p1 + bwd32_partial2_floats(d.n, d.h, d.w, k, B);
+      }
+      for (int l = 1; l <= m; ++l) need(bn_bwd_partial_floats(d.n, c_in(d, l), (int)hw));
     }
-    for (int l = 1; l <= m; ++l) need(bn_bwd_partial_floats(d.n, c_in(d, l), (int)hw));
-  }
-  size_t scratch = 0;
-  auto carve_scratch = [&](size_t bytes, bool in) {
-    const size_t o = hole;
-    if (in && in_hole(hole, bytes)) return o;
-    scratch += bytes;
-    return carve(bytes, false);
+    size_t scratch = 0;
+    auto carve_scratch = [&](size_t bytes, bool in) {
+      const size_t o = hole;
+      if (in && in_hole(hole, bytes)) return o;
+      scratch += bytes;
+      return carve(bytes, false);
+    };
+    const Fill in = fill(hole);
+    b->off_pack = carve_scratch(pack * 4, false);
+    b->off_tail = off;
+    for (size_t i = 0; i < 2; ++i) {
+      b->off_partB[i] = i < buffers ? carve_scratch(bytesB, i < in.b) : b->off_partB[0];
+      b->off_partA[i] = i < buffers ? carve_scratch(bytesA, i < in.a) : b->off_partA[0];
+    }
+    b->off_K = carve_scratch(B > 0 ? (size_t)cout * 8 : 0, true);
+    b->off_bwd = hole;
+    if (bwd && !in_hole(hole, bwd * 4)) { need(bwd); b->off_bwd = off; }  // in the place of the forward's partials
+    b->off_part = carve_scratch(part * 4, false);
+    mem.scratch_bytes = (uint64_t)scratch;
   };
-  const Fill in = fill(hole);
-  b->off_pack = carve_scratch(pack * 4, false);
-  b->off_tail = off;
-  for (size_t i = 0; i < 2; ++i) {
-    b->off_partB[i] = i < buffers ? carve_scratch(bytesB, i < in.b) : b->off_partB[0];
-    b->off_partA[i] = i < buffers ? carve_scratch(bytesA, i < in.a) : b->off_partA[0];
+  // fp32: the most partials, in steps of an eighth, that take no memory against the fewest, or none but what the caller has to
+  // spare.  (With as many as they like and pairs where these leave room, blocks took up to 12 % more memory, 22 layers of 165
+  // channels at 20x20, batch 21, and DenseNet-BC L = 100, k = 24, batch 64 lost the pairs of two blocks: 9.29 ms a step, not 8.99.)
+  place(partB_least);
+  if (!bf16 && partB != partB_least) {
+    const size_t bytes = off;
+    for (size_t i = 0; i <= 8; ++i) {
+      place(i == 8 ? partB_least : partB > partB_least ? partB - (partB - partB_least) * i / 8 : partB);
+      if (off <= bytes || off - b->off_tail <= spare) break;
+    }
   }
-  b->off_K = carve_scratch(B > 0 ? (size_t)cout * 8 : 0, true);
-  b->off_bwd = hole;
-  if (bwd && !in_hole(hole, bwd * 4)) { need(bwd); b->off_bwd = off; }  // in the place of the forward's partials
-  b->off_part = carve_scratch(part * 4, false);
-  mem.scratch_bytes = (uint64_t)scratch;
   // measured on MI355X: with the weight gradients on helper streams the fp32 step is slower (idle
   // time between dependent launches of different streams outweighs the overlap)
   b->concurrency = 0;
@@ -811,6 +840,8 @@ int dnb_block_create(const dnb_block_desc* desc, dnb_block** out) {
   *out = b;
   return DNB_OK;
 }
+
+extern "C" {
 
 void dnb_block_destroy(dnb_block* b) {
   if (!b) return;
@@ -1117,7 +1148,7 @@ int dnb_block_backward(dnb_block* b, const void* paramsv, const void* yv, const 
     const float2* f1 = fused ? (const float2*)(ws + b->off_fold1[l]) : nullptr;
     if (conc && !oneh) {  // (fused: BN1+ReLU of the concatenated features is applied in the operand load)
       DNB_TRY(launch_conv_wgrad(in1, in1s, dS3, (int64_t)B * hw, gp.W1, n, c, B, d.h, d.w, 1, pB, f1, sB, nullptr,
-                                nullptr, nullptr, &pendB, &nextB));
+                                nullptr, nullptr, &pendB, &nextB, false, b->partB_floats));
       pendB = nextB;
     }
     if (!oneh) DNB_TRY(record(ev(l, EV_WG1), sB));
@@ -1127,7 +1158,8 @@ int dnb_block_backward(dnb_block* b, const void* paramsv, const void* yv, const 
                               n, B, c, d.h, d.w, 1, nullptr, st));
     if (oneh) {  // issued after the main chain's launch: the main chain keeps its hardware queue in a captured graph
       DNB_TRY(launch_conv_wgrad_pair(in1, in1s, dS3, (int64_t)B * hw, gp.W1, c, pB, f1, in3, (int64_t)B * hw, gl, ys,
-                                     gp.W3, k, pA, f3, n, B, d.h, d.w, sA, &pendB, &pendA, nullptr, nullptr));
+                                     gp.W3, k, pA, f3, n, B, d.h, d.w, sA, &pendB, &pendA, nullptr, nullptr, nullptr, nullptr,
+                                     nullptr, nullptr, b->partB_floats));
       DNB_TRY(record(ev(l, EV_WG1), sA));
     }
     DNB_TRY(wait(st, ev(l, EV_S12)));
@@ -1145,7 +1177,7 @@ int dnb_block_backward(dnb_block* b, const void* paramsv, const void* yv, const 
       bool bn_done = false;
       DNB_TRY(launch_conv_wgrad_pair(in1, in1s, dS3, (int64_t)B * hw, gp.W1, c, pB, f1, in3, (int64_t)B * hw, gl, ys,
                                      gp.W3, k, pA, f3, n, B, d.h, d.w, st, &pendB, &pendA, has_bn ? &bn : nullptr,
-                                     &bn_done));
+                                     &bn_done, nullptr, nullptr, nullptr, nullptr, b->partB_floats));
       if (bn_done) passes = 2;
     }
     DNB_TRY(launch_bn_relu_bwd(x1, x1s, dS2, (int64_t)c * hw, G, ys, true, n, c, hw, p.g1, p.b1, mean_y, istd_y, gp.g1,

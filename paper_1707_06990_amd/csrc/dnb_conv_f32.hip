@@ -27,21 +27,21 @@ bool launch_conv_fast(const float* in, int64_t in_stride, const float* packed, f
 bool launch_conv3x3_any(const float* in, int64_t in_stride, const float* packed, float* out, int64_t out_stride, int n,
                         int cin, int cout, int h, int w, float* spart, int* sT, hipStream_t st, hipEvent_t ev0,
                         hipEvent_t ev1);
-size_t conv_wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool alone);
+size_t conv_wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool alone, size_t most);
 // Launches the fast weight-gradient kernel if it applies (returns false otherwise).  *own
 // describes the sum of its partials, which is left to the caller; *absorb (may be null or of kind
 // 0) is carried out by extra workgroups of the same launch and cleared.
 bool launch_wgrad_fast(const float* in, int64_t in_stride, const float* g, int64_t g_stride,
                        float* partials, float* dw, int n, int cin, int cout, int h, int w, int taps,
                        const float2* fold, PendingSum* own, PendingSum* absorb, hipStream_t st, hipEvent_t ev0,
-                       hipEvent_t ev1, bool alone);
+                       hipEvent_t ev1, bool alone, size_t most);
 hipError_t launch_sum_wgrad3x3(const PendingSum& p, hipStream_t st);
 bool launch_wgrad_pair_fast(const float* in1, int64_t in1_stride, const float* g1, int64_t g1_stride, float* part1,
                             float* dw1, int cin1, const float2* fold1, const float* in3, int64_t in3_stride,
                             const float* g3, int64_t g3_stride, float* part3, float* dw3, int cout3,
                             const float2* fold3, int n, int B, int h, int w, PendingSum* own1, PendingSum* own3,
                             PendingSum* absorb1, PendingSum* absorb3, const BnBwdPartialArgs* bn, const Bn1Finish* fin,
-                            hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);
+                            hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, size_t most1);
 
 namespace {
 
@@ -435,11 +435,11 @@ bool conv3x3_generic_fits(int n, int cin, int cout, int h, int w) {
          plan_wgrad(n, cin, cout, h, w, 9).lds <= 64 * 1024;
 }
 
-size_t conv_wgrad_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool alone) {
+size_t conv_wgrad_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool alone, size_t most) {
   const WgradPlan p = plan_wgrad(n, cin, cout, h, w, taps);
   const size_t a = taps == 9 ? (size_t)p.splits * p.grid.y * p.grid.z * p.mtw * p.ctw * 9 * 256
                              : (size_t)p.splits * cin * cout;
-  const size_t b = conv_wgrad_fast_partial_floats(n, cin, cout, h, w, taps, alone);
+  const size_t b = conv_wgrad_fast_partial_floats(n, cin, cout, h, w, taps, alone, most);
   return a > b ? a : b;
 }
 
@@ -454,13 +454,13 @@ hipError_t launch_pending_sum(PendingSum* p, hipStream_t st) {
 hipError_t launch_conv_wgrad(const float* in, int64_t in_stride, const float* g, int64_t g_stride,
                              float* dw, int n, int cin, int cout, int h, int w, int taps,
                              float* partials, const float2* fold, hipStream_t st, hipEvent_t ev0,
-                             hipEvent_t ev1, bool* used_fast, PendingSum* absorb, PendingSum* defer, bool alone) {
+                             hipEvent_t ev1, bool* used_fast, PendingSum* absorb, PendingSum* defer, bool alone, size_t most) {
   if (defer) defer->kind = 0;
   if (cin <= 0 || cout <= 0) return absorb ? launch_pending_sum(absorb, st) : hipSuccess;
   if (used_fast) *used_fast = true;
   PendingSum own;
   if (launch_wgrad_fast(in, in_stride, g, g_stride, partials, dw, n, cin, cout, h, w, taps, fold, &own, absorb, st,
-                        ev0, ev1, alone)) {
+                        ev0, ev1, alone, most)) {
     if (defer) { *defer = own; return hipGetLastError(); }
     return launch_pending_sum(&own, st);
   }
@@ -490,14 +490,14 @@ hipError_t launch_conv_wgrad_pair(const float* in1, int64_t in1_stride, const fl
                                   int64_t in3_stride, const float* g3, int64_t g3_stride, float* dw3, int cout3,
                                   float* part3, const float2* fold3, int n, int B, int h, int w, hipStream_t st,
                                   PendingSum* pend1, PendingSum* pend3, const BnBwdPartialArgs* bn, bool* bn_done,
-                                  hipEvent_t ev0, hipEvent_t ev1, bool* paired, const Bn1Finish* fin) {
+                                  hipEvent_t ev0, hipEvent_t ev1, bool* paired, const Bn1Finish* fin, size_t most1) {
   PendingSum own1, own3;
   if (paired) *paired = false;
   if (bn_done) *bn_done = false;
   if (cin1 > 0 && B > 0 && cout3 > 0 &&
       launch_wgrad_pair_fast(in1, in1_stride, g1, g1_stride, part1, dw1, cin1, fold1, in3, in3_stride, g3, g3_stride,
                              part3, dw3, cout3, fold3, n, B, h, w, &own1, &own3, pend1, pend3, bn, fin, st, ev0,
-                             ev1)) {
+                             ev1, most1)) {
     *pend1 = own1;
     *pend3 = own3;
     if (bn_done) *bn_done = bn != nullptr;
@@ -511,7 +511,7 @@ hipError_t launch_conv_wgrad_pair(const float* in1, int64_t in1_stride, const fl
   if (e != hipSuccess) return e;
   *pend3 = own3;
   e = launch_conv_wgrad(in1, in1_stride, g1, g1_stride, dw1, n, cin1, B, h, w, 1, part1, fold1, st, nullptr, nullptr,
-                        nullptr, pend1, &own1);
+                        nullptr, pend1, &own1, false, most1);
   *pend1 = own1;
   return e;
 }

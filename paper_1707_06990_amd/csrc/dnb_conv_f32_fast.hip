@@ -2073,8 +2073,9 @@ struct WgFastPlan {
   size_t lds;
 };
 
-// alone: the launch holds nothing else.
-static WgFastPlan plan_wgrad_fast(int n, int cin, int cout, int h, int w, int taps, bool alone = false) {
+// alone: the launch holds nothing else.  most: floats that the 1x1's partials may take; the fewest (most = 0) are those of
+// narrow tiles in 128 workgroups, larger numbers of ranges are used where they fit.
+static WgFastPlan plan_wgrad_fast(int n, int cin, int cout, int h, int w, int taps, bool alone, size_t most) {
   WgFastPlan p{};
   const int hw = h * w, mtiles = (cout + 15) / 16, ctiles = (cin + 15) / 16;
   p.ok = hw % 4 == 0 && (taps == 1 || (w % 4 == 0 && w >= 4));
@@ -2093,39 +2094,52 @@ static WgFastPlan plan_wgrad_fast(int n, int cin, int cout, int h, int w, int ta
     // alone on the chip and up to 516 channels wide, is better balanced in narrow tiles (395 + 785 us against 400 + 953), and
     // with more than 96 outputs the narrow ones are faster (128 outputs, 300..650 channels, 16384 pixels: a block of twelve layers
     // 2676 us against 2804 and 2850 in wide tiles of 64 and 128 rows).
+    // Where that many partials take more than `most`, a workgroup gets up to a third more steps, not beyond 32, where a sum
+    // goes in parts: so far wide tiles stay ahead (both weight gradients of a layer in 256, 192, 128 workgroups and with
+    // narrow tiles: 264 channels, 65536 pixels 99, 103, 141, 113 us; 520, 16384: 44, 49, 61, 61; 1700, 4096: 32, 36, 43, 46;
+    // past 32 steps: 400, 65536: 106, 134, 168, 116; 1008: 178, 227, 312, 185).
     if (!alone && cout > 48 && cout <= 96 && p.gy * p.gz > 8 && (hw % 32 == 0 || hw >= 128)) {
-      p.ctw = 8;
-      p.mtw = cout <= 64 ? 2 : 3;
-      p.gy = (cin + 127) / 128;
-      p.gz = (cout + 32 * p.mtw - 1) / (32 * p.mtw);
-      p.spi = (hw + 31) / 32;
-      p.total_steps = n * p.spi;
-      int gx = 256 / (p.gy * p.gz);
+      WgFastPlan q = p;
+      q.ctw = 8;
+      q.mtw = cout <= 64 ? 2 : 3;
+      q.gy = (cin + 127) / 128;
+      q.gz = (cout + 32 * q.mtw - 1) / (32 * q.mtw);
+      q.spi = (hw + 31) / 32;
+      q.total_steps = n * q.spi;
+      int gx = 256 / (q.gy * q.gz);
       if (gx < 1) gx = 1;
-      p.steps_per_wg = (p.total_steps + gx - 1) / gx;
-      if (p.steps_per_wg < 8) p.steps_per_wg = 8;
-      p.gx = (p.total_steps + p.steps_per_wg - 1) / p.steps_per_wg;
-      p.lds = wide_lds_bytes(p.mtw);
-      return p;
+      int steps = (q.total_steps + gx - 1) / gx;
+      if (steps < 8) steps = 8;
+      const size_t fit = most / ((size_t)cin * cout);  // pixel ranges
+      const int least = fit >= (size_t)q.total_steps ? 1 : fit > 0 ? (int)((q.total_steps + fit - 1) / fit) : 0;
+      if (fit > 0 && least <= (steps < 32 ? min(32, steps + (steps + 2) / 3) : steps)) {
+        q.steps_per_wg = steps > least ? steps : least;
+        q.gx = (q.total_steps + q.steps_per_wg - 1) / q.steps_per_wg;
+        q.lds = wide_lds_bytes(q.mtw);
+        return q;
+      }
     }
     p.spi = (hw + 15) / 16;
     p.total_steps = n * p.spi;
-    // About 128 workgroups in all, 192 from 16384 pixels on (DenseNet-BC-100 4595 -> 4565 us a step, shared schedule 5758
-    // -> 5698; 256: 4616 and 5684; with fewer pixels the partials would not fit the gradient scratch), 1..16 (or 64) steps per wave.  A workgroup ends with a cross-wave sum
-    // and a partial of mtw*ctw tiles to store, and every partial is read again by the sum that
-    // follows, so few long workgroups beat many short ones even when they leave CUs to the other
+    // About 128 workgroups in all, 192 from 16384 pixels on where there is room for their partials (DenseNet-BC-100 4595 ->
+    // 4565 us a step, shared schedule 5758 -> 5698; 256: 4616 and 5684), 1..16 (or 64) steps per wave.  A workgroup ends
+    // with a cross-wave sum and a partial of mtw*ctw tiles to store, and every partial is read again by the sum
+    // that follows, so few long workgroups beat many short ones even when they leave CUs to the other
     // roles of the launch: a target of 512 workgroups (1..8 steps) took 3.3 % more time per
     // DenseNet-BC-100 step than 128.
     // With many (m, c) tile columns (wide layers, k = 24 nets) the columns alone fill the chip and the
     // pixel ranges can be longer still: a cap of 64 steps there took 1.2 % off the DenseNet-BC-250 step.
     // By itself (a transition's) nothing else fills the CUs: 512 workgroups.
-    const int wgs = alone ? 512 : p.total_steps >= 1024 ? 192 : 128;
-    int spw = (int)(((int64_t)p.total_steps * p.gy * p.gz + 4 * wgs - 1) / (4 * wgs));
     const int cap = p.gy * p.gz > 8 ? 64 : 16;
-    if (spw < 1) spw = 1;
-    if (spw > cap) spw = cap;
-    p.steps_per_wg = 4 * spw;
-    p.gx = (p.total_steps + p.steps_per_wg - 1) / p.steps_per_wg;
+    auto split = [&](int wgs) {
+      int spw = (int)(((int64_t)p.total_steps * p.gy * p.gz + 4 * wgs - 1) / (4 * wgs));
+      if (spw < 1) spw = 1;
+      if (spw > cap) spw = cap;
+      p.steps_per_wg = 4 * spw;
+      p.gx = (p.total_steps + p.steps_per_wg - 1) / p.steps_per_wg;
+    };
+    split(alone ? 512 : p.total_steps >= 1024 ? 192 : 128);
+    if (!alone && (size_t)p.gx * cin * cout > most) split(128);
     p.lds = (size_t)4 * p.mtw * p.ctw * 256 * sizeof(float);
   } else {
     p.mtw = mtiles >= 2 ? 2 : 1;
@@ -2153,8 +2167,8 @@ static WgFastPlan plan_wgrad_fast(int n, int cin, int cout, int h, int w, int ta
   return p;
 }
 
-size_t conv_wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool alone) {
-  const WgFastPlan p = plan_wgrad_fast(n, cin, cout, h, w, taps, alone);
+size_t conv_wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool alone, size_t most) {
+  const WgFastPlan p = plan_wgrad_fast(n, cin, cout, h, w, taps, alone, most);
   if (!p.ok) return 0;
   if (taps == 9) return (size_t)p.gx * p.gy * p.gz * p.mtw * p.ctw * 9 * 256;  // accumulator-order partials
   return (size_t)p.gx * cin * cout;
@@ -2174,9 +2188,9 @@ hipError_t launch_sum_wgrad3x3(const PendingSum& p, hipStream_t st) {
 bool launch_wgrad_fast(const float* in, int64_t in_stride, const float* g, int64_t g_stride,
                        float* partials, float* dw, int n, int cin, int cout, int h, int w, int taps,
                        const float2* fold, PendingSum* own, PendingSum* absorb, hipStream_t st, hipEvent_t ev0,
-                       hipEvent_t ev1, bool alone) {
+                       hipEvent_t ev1, bool alone, size_t most) {
   if (in_stride % 4 || g_stride % 4 || !aligned16(in) || !aligned16(g)) return false;
-  const WgFastPlan p = plan_wgrad_fast(n, cin, cout, h, w, taps, alone);
+  const WgFastPlan p = plan_wgrad_fast(n, cin, cout, h, w, taps, alone, most);
   if (!p.ok) return false;
   const SumRole sr = make_sum_role(absorb);
   const unsigned sx = (unsigned)((sr.wgs + p.gy * p.gz - 1) / (p.gy * p.gz));
@@ -2231,12 +2245,12 @@ bool launch_wgrad_pair_fast(const float* in1, int64_t in1_stride, const float* g
                             const float* g3, int64_t g3_stride, float* part3, float* dw3, int cout3,
                             const float2* fold3, int n, int B, int h, int w, PendingSum* own1, PendingSum* own3,
                             PendingSum* absorb1, PendingSum* absorb3, const BnBwdPartialArgs* bn, const Bn1Finish* fin,
-                            hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+                            hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, size_t most1) {
   if ((fold1 != nullptr) != (fold3 != nullptr)) return false;
   if (in1_stride % 4 || g1_stride % 4 || in3_stride % 4 || g3_stride % 4 || !aligned16(in1) || !aligned16(g1) ||
       !aligned16(in3) || !aligned16(g3))
     return false;
-  const WgFastPlan p1 = plan_wgrad_fast(n, cin1, B, h, w, 1), p3 = plan_wgrad_fast(n, B, cout3, h, w, 9);
+  const WgFastPlan p1 = plan_wgrad_fast(n, cin1, B, h, w, 1, false, most1), p3 = plan_wgrad_fast(n, B, cout3, h, w, 9, false, 0);
   if (!p1.ok || !p3.ok || (p1.mtw != 3 && p1.ctw != 8)) return false;
   const int key3 = p3.mtw * 10 + p3.ctw;
   if (key3 != 13 && key3 != 22) return false;

@@ -5,12 +5,18 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "../../include/dnb.h"
+
 struct dnb_block;
 
 namespace dnb {
 
+// dnb_block_create for a caller that has `spare` bytes anyway for the scratch that starts at block_tail_offset
+int block_create(const dnb_block_desc* desc, size_t spare, dnb_block** out);
+
 // (dnb_block.hip) where a block's call-local scratch starts in its workspace, and moving it elsewhere
 size_t block_tail_offset(const dnb_block* b);
+bool block_layers_in_pairs(const dnb_block* b);
 void block_move_tail(dnb_block* b, size_t to);
 
 // ---- element-wise and reduction kernels (HBM-bound) -------------------------------------
@@ -188,9 +194,11 @@ hipError_t launch_bn_fold(const float* gamma, const float* beta, float* mean, fl
                           float2* fold, hipStream_t st, bool rows = false);
 
 // dW[m][c][t] = sum_{n,q} g[n][m][q] * in[n][c][q + shift(t)]  (OIHW result).
-size_t conv_wgrad_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool alone = false);
+// alone: the launch holds nothing else; most: floats that the partials of a 1x1 may take where fewer will do (0: the fewest).
+// The launch is to be given the same two.
+size_t conv_wgrad_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool alone = false, size_t most = SIZE_MAX);
 // partial floats of the fast (16-byte-vector) weight-gradient kernel for this shape, 0 if its tile plan does not fit
-size_t conv_wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool alone = false);
+size_t conv_wgrad_fast_partial_floats(int n, int cin, int cout, int h, int w, int taps, bool alone = false, size_t most = SIZE_MAX);
 // A sum of weight-gradient partials that a launch has left for later.  In a chain of weight
 // gradients on one stream the next weight-gradient launch carries it out with extra workgroups
 // (the partials are complete when that launch starts), which saves a launch per layer; what is
@@ -212,7 +220,8 @@ hipError_t launch_conv_wgrad(const float* in, int64_t in_stride, const float* g,
                              float* dw, int n, int cin, int cout, int h, int w, int taps,
                              float* partials, const float2* fold, hipStream_t st, hipEvent_t ev_start = nullptr,
                              hipEvent_t ev_stop = nullptr /*stamped around the fast kernel (not the sum)*/,
-                             bool* used_fast = nullptr, PendingSum* absorb = nullptr, PendingSum* defer = nullptr, bool alone = false);
+                             bool* used_fast = nullptr, PendingSum* absorb = nullptr, PendingSum* defer = nullptr, bool alone = false,
+                             size_t most = SIZE_MAX);
 
 // Both weight gradients of a bottleneck layer on one stream: the 1x1 (in1: C_l channels, g1: the
 // gradient of b_l, B channels) and the 3x3 (in3: B channels, g3: the gradient of x_l, k
@@ -225,8 +234,8 @@ hipError_t launch_conv_wgrad_pair(const float* in1, int64_t in1_stride, const fl
                                   float* part3, const float2* fold3, int n, int B, int h, int w, hipStream_t st,
                                   PendingSum* pend1, PendingSum* pend3, const BnBwdPartialArgs* bn = nullptr,
                                   bool* bn_done = nullptr, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr,
-                                  bool* paired = nullptr, const Bn1Finish* fin = nullptr);
-// (fin: the end of a layer's BN1, always carried out;
+                                  bool* paired = nullptr, const Bn1Finish* fin = nullptr, size_t most1 = SIZE_MAX);
+// (fin: the end of a layer's BN1, always carried out;  most1: floats that the 1x1's partials may take;
 //  bn: a BN backward reduction to carry in the same launch, *bn_done says whether it was;
 //  ev_start / ev_stop are stamped around the shared launch, *paired says whether there was one)
 

@@ -338,11 +338,13 @@ int dnb_net_create(const dnb_net_desc* desc, dnb_net** out) {
   int c = 2 * k, s = d.image;
   size_t po = (size_t)2 * k * 27;
   net->p_stem = 0;
+  // the blocks' call-local scratch lies in dtz, which holds nothing while a block runs: as large as the first block's output
+  const size_t spare = ((size_t)2 * k + (size_t)per * k) * d.n * d.image * d.image * 4;
   for (int b = 0; b < 3; ++b) {
     dnb_block_desc bd{};
     bd.n = d.n; bd.c0 = c; bd.h = s; bd.w = s; bd.layers = per; bd.growth = k; bd.bottleneck = 4 * k;
     bd.dtype = DNB_F32; bd.layout = DNB_NCHW; bd.schedule = d.schedule; bd.eps = d.eps;
-    const int rc = dnb_block_create(&bd, &net->blk[b]);
+    const int rc = block_create(&bd, spare, &net->blk[b]);
     if (rc != DNB_OK) { dnb_net_destroy(net); return rc; }
     net->bd[b] = bd;
     net->cout[b] = c + per * k;
@@ -371,13 +373,15 @@ int dnb_net_create(const dnb_net_desc* desc, dnb_net** out) {
     return o;
   };
   size_t part = 0, pmax = 0, tail_max = 0;
+  bool in_dtz[3];
   for (int b = 0; b < 3; ++b) {
     const dnb_block_desc& bd = net->bd[b];
     const size_t hw = (size_t)bd.h * bd.w, P = hw * d.n, co = (size_t)net->cout[b];
     net->o_feat[b] = carve((size_t)bd.c0 * P * 4, true, "feat", b);
     net->o_y[b] = carve(co * P * 4, true, "y", b);
     const size_t tail = dnb_block_workspace_bytes(net->blk[b]) - block_tail_offset(net->blk[b]);
-    if (tail > tail_max) tail_max = tail;
+    in_dtz[b] = tail <= spare;
+    if (!in_dtz[b] && tail > tail_max) tail_max = tail;
     net->o_ws[b] = carve(block_tail_offset(net->blk[b]), false, "block_ws", b);
     net->o_tz[b] = carve(co * P * 4, true, "tz", b);
     net->o_mean[b] = carve(co * 4, false, "mean", b);
@@ -409,7 +413,7 @@ int dnb_net_create(const dnb_net_desc* desc, dnb_net** out) {
   for (int b = 0; b < 2; ++b) {
     const dnb_block_desc& bd = net->bd[b];
     net->sums_in_dtz[b] = conv_wgrad_partial_floats(d.n, net->cout[b], net->cout[b] / 2, bd.h, bd.w, 1, true) <= pmax;
-    const size_t f = net->sums_in_dtz[b] ? 0 : conv_wgrad_partial_floats(d.n, net->cout[b], net->cout[b] / 2, bd.h, bd.w, 1);
+    const size_t f = net->sums_in_dtz[b] ? 0 : conv_wgrad_partial_floats(d.n, net->cout[b], net->cout[b] / 2, bd.h, bd.w, 1, false, 0);
     if (f > part) part = f;
   }
   net->o_tconv = carve(conv_max * 4, true, "tconv");  // a transition's 1x1 output before pooling
@@ -417,9 +421,9 @@ int dnb_net_create(const dnb_net_desc* desc, dnb_net** out) {
   net->o_dtz = carve(pmax * 4, true, "dtz");        // gradient of a transition's BN+ReLU output
   net->o_dconv = carve(conv_max * 4, true, "dconv");  // gradient of a transition's conv output
   net->o_dfeat = carve(feat_max * 4, true, "dfeat");  // gradient of a block input
-  // one scratch for the three blocks, which run one after the other
+  // one scratch for the blocks whose own is too large for dtz (they run one after the other)
   const size_t o_tail = carve(tail_max, false, "block_scratch");
-  for (int b = 0; b < 3; ++b) block_move_tail(net->blk[b], o_tail - net->o_ws[b]);
+  for (int b = 0; b < 3; ++b) block_move_tail(net->blk[b], (in_dtz[b] ? net->o_dtz : o_tail) - net->o_ws[b]);
   net->o_part = carve(part * 4, false, "part");
   const size_t C = (size_t)net->cout[2];
   net->o_pooled = carve((size_t)d.n * C * 4, false, "pooled");
@@ -637,7 +641,7 @@ int dnb_net_backward(dnb_net* net, const void* xv, const void* paramsv, void* dp
       DNB_TRYH(hipGetLastError());
       const bool in_dtz = net->sums_in_dtz[b - 1];
       DNB_TRYH(launch_conv_wgrad(tzp, (int64_t)cp * hwp, dconv, (int64_t)ch * hwp, dparams + net->p_w[b - 1], n, cp, ch,
-                                 pd.h, pd.w, 1, in_dtz ? dtz : part, nullptr, st, nullptr, nullptr, nullptr, nullptr, nullptr, in_dtz));
+                                 pd.h, pd.w, 1, in_dtz ? dtz : part, nullptr, st, nullptr, nullptr, nullptr, nullptr, nullptr, in_dtz, 0));
       DNB_TRYH(launch_conv_igemm(dconv, (int64_t)ch * hwp, WeightView{W, 1, cp, 0}, pkt, dtz, (int64_t)cp * hwp, n, ch,
                                  cp, pd.h, pd.w, 1, nullptr, st));
     }

@@ -177,6 +177,29 @@ def test_layers_in_pairs_keep_no_feature_map_outside_the_peak(dnb, kind, limit, 
     assert got <= limit
 
 
+def test_more_partials_cost_neither_memory_nor_pairs(dnb):
+    """Wide tiles and more workgroups leave more partial sums of the 1x1 weight gradients: against plans with the fewest
+    (golden file) no block or network takes more memory, and no block loses its pairs of layers."""
+    lib = ctypes.CDLL(dnb.binding.LIB_PATH)
+    pairs = lib._ZN3dnb21block_layers_in_pairsEPK9dnb_block  # (a C++ name: not a call of the C ABI)
+    pairs.restype, pairs.argtypes = ctypes.c_bool, [ctypes.c_void_p]
+    blocks = nets = 0
+    for line in open(os.path.join(ROOT, "tests", "golden", "fp32_fewest_partials_plans.txt")):
+        kind, *v = line.split()
+        v = [int(x) for x in v] if kind != "#" else v
+        if kind == "block":
+            h = dnb.dnb_block_create(*v[:7], schedule=v[7])
+            assert dnb.dnb_block_workspace_bytes(h) <= v[8] and pairs(h) >= v[9], line
+            dnb.dnb_block_destroy(h)
+            blocks += 1
+        elif kind == "net":
+            h = dnb.dnb_net_create(*v[:5], schedule=v[5])
+            assert dnb.dnb_net_workspace_bytes(h) <= v[6], line
+            dnb.dnb_net_destroy(h)
+            nets += 1
+    assert blocks == 260 and nets == 40
+
+
 @pytest.mark.parametrize("cfg", CFGS + NOBOTTLE, ids=lambda c: f"{c.n}x{c.c0}x{c.h}x{c.w}-m{c.layers}k{c.growth}B{c.bottleneck}")
 def test_peak_bytes_formula(dnb, cfg):
     """Linear-memory formula (shared) and quadratic one (store-all), in bytes."""
