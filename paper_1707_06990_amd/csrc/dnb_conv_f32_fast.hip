@@ -2094,10 +2094,11 @@ static WgFastPlan plan_wgrad_fast(int n, int cin, int cout, int h, int w, int ta
     // alone on the chip and up to 516 channels wide, is better balanced in narrow tiles (395 + 785 us against 400 + 953), and
     // with more than 96 outputs the narrow ones are faster (128 outputs, 300..650 channels, 16384 pixels: a block of twelve layers
     // 2676 us against 2804 and 2850 in wide tiles of 64 and 128 rows).
-    // Where that many partials take more than `most`, a workgroup gets up to a third more steps, not beyond 32, where a sum
-    // goes in parts: so far wide tiles stay ahead (both weight gradients of a layer in 256, 192, 128 workgroups and with
+    // Where that many partials take more than `most`, a workgroup gets up to a third more steps, from 2048 pixels on at
+    // least 4, and not beyond 32, where a sum goes in parts: so far wide tiles stay ahead (both weight gradients of a layer in 256, 192, 128 workgroups and with
     // narrow tiles: 264 channels, 65536 pixels 99, 103, 141, 113 us; 520, 16384: 44, 49, 61, 61; 1700, 4096: 32, 36, 43, 46;
-    // past 32 steps: 400, 65536: 106, 134, 168, 116; 1008: 178, 227, 312, 185).
+    // past 32 steps: 400, 65536: 106, 134, 168, 116; 1008: 178, 227, 312, 185; few pixels, 2, 4 and 8 steps and narrow
+    // tiles: 776, 2048: 22.5, 21.6, 27.5, 21.0; 520, 4096: 25, 25, 31, 27; 520, 1024: 15.8, 18.4, 26.0, 16.6).
     if (!alone && cout > 48 && cout <= 96 && p.gy * p.gz > 8 && (hw % 32 == 0 || hw >= 128)) {
       WgFastPlan q = p;
       q.ctw = 8;
@@ -2109,10 +2110,16 @@ static WgFastPlan plan_wgrad_fast(int n, int cin, int cout, int h, int w, int ta
       int gx = 256 / (q.gy * q.gz);
       if (gx < 1) gx = 1;
       int steps = (q.total_steps + gx - 1) / gx;
-      if (steps < 8) steps = 8;
+      // (few pixels: shorter ranges as long as there are CUs for them.  At least 2, 3, 4, 8 steps: DenseNet-BC L = 250, k = 24,
+      // batch 4 9.48, 9.54, 9.68, 10.33 ms a step; with narrow tiles 10.98.  Both weight gradients of a layer of 900
+      // channels, 256 pixels: 24 us with 8 steps, 15 in narrow tiles, 14 with 2)
+      if (steps < 2) steps = 2;
       const size_t fit = most / ((size_t)cin * cout);  // pixel ranges
       const int least = fit >= (size_t)q.total_steps ? 1 : fit > 0 ? (int)((q.total_steps + fit - 1) / fit) : 0;
-      if (fit > 0 && least <= (steps < 32 ? min(32, steps + (steps + 2) / 3) : steps)) {
+      int more = steps + (steps + 2) / 3;
+      if (more < 4 && q.total_steps >= 64) more = 4;
+      if (more > 32) more = steps > 32 ? steps : 32;
+      if (fit > 0 && least <= more) {
         q.steps_per_wg = steps > least ? steps : least;
         q.gx = (q.total_steps + q.steps_per_wg - 1) / q.steps_per_wg;
         q.lds = wide_lds_bytes(q.mtw);

@@ -299,13 +299,17 @@ def test_layers_in_pairs_match_oracle(dnb, oracle, cfg, schedule):
     compare_with_kernel_decisions(dnb, oracle, cfg, x0, lp, dy, schedule=schedule)
 
 
-# 1x1 weight gradients in wide tiles with less room for their partials than they like: 8 pixel ranges instead of 10, 15 and 13
-# instead of 18, and narrow tiles in the last layer of the third, which gets none of the room
+# 1x1 weight gradients with less room for their partials than they like.  Narrow tiles in all layers (the first four); wide
+# tiles of 19 pixel ranges instead of 38 in two layers and narrow ones in the others, 30 instead of 60 in three, 32 instead of
+# 45 in one
 CAPPED = [(wl.BlockCfg(10, 816, 16, 16, 3, 16, 64), 0), (wl.BlockCfg(11, 790, 20, 20, 3, 16, 52), 0),
-          (wl.BlockCfg(10, 685, 16, 16, 3, 13, 52), 0), (wl.BlockCfg(10, 685, 16, 16, 3, 13, 52), 2)]
+          (wl.BlockCfg(10, 685, 16, 16, 3, 13, 52), 0), (wl.BlockCfg(10, 685, 16, 16, 3, 13, 52), 2),
+          (wl.BlockCfg(15, 283, 12, 12, 4, 24, 52), 0), (wl.BlockCfg(24, 311, 12, 12, 4, 24, 52), 2),
+          (wl.BlockCfg(17, 588, 20, 20, 3, 13, 52), 2)]
 
 
-@pytest.mark.parametrize("cfg,schedule", CAPPED, ids=["n10c816", "n11c790", "n10c685", "n10c685-fused"])
+@pytest.mark.parametrize("cfg,schedule", CAPPED, ids=["n10c816", "n11c790", "n10c685", "n10c685-fused", "n15c283", "n24c311-fused",
+                                                      "n17c588-fused"])
 def test_few_partials_of_the_1x1_weight_gradient_match_oracle(dnb, oracle, cfg, schedule):
     x0, lp, dy = wl.make_block_inputs(cfg, affine="random")
     compare_with_kernel_decisions(dnb, oracle, cfg, x0, lp, dy, schedule=schedule)

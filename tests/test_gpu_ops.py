@@ -390,6 +390,13 @@ def test_layer_weight_gradients_in_wide_tiles(dnb, oracle, n, cin, B, k, h, w):
     layer_wgrads_case(dnb, oracle, n, cin, B, k, h, w, True, seed=43)
 
 
+@pytest.mark.parametrize("n,cin,B,k,h,w", [(1, 264, 64, 16, 4, 8), (1, 300, 96, 24, 8, 8), (3, 257, 52, 13, 4, 8), (4, 900, 96, 24, 8, 8),
+                                           (1, 1700, 96, 24, 12, 12), (5, 390, 64, 16, 8, 16)])
+def test_layer_weight_gradients_in_wide_tiles_of_few_pixels(dnb, oracle, n, cin, B, k, h, w):
+    """Wide tiles with one and two steps of 32 pixels a workgroup, a last range of one, images whose last step is half there."""
+    layer_wgrads_case(dnb, oracle, n, cin, B, k, h, w, True, seed=44)
+
+
 @pytest.mark.parametrize("cin,B,k", [(60, 48, 12), (204, 48, 12), (264, 96, 24), (1008, 96, 24)])
 def test_layer_weight_gradients_at_benchmark_pixel_counts(dnb, oracle, cin, B, k):
     """The same launch at the pixel count the benchmarks run it at (batch 64, 32x32 images: the

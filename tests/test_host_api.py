@@ -177,6 +177,18 @@ def test_layers_in_pairs_keep_no_feature_map_outside_the_peak(dnb, kind, limit, 
     assert got <= limit
 
 
+@pytest.mark.parametrize("n,cin,cout,h,w", [(4, 900, 96, 8, 8), (1, 264, 64, 16, 16), (16, 300, 96, 16, 16), (2, 1700, 52, 8, 8)])
+def test_wide_1x1_weight_gradients_of_few_pixels_use_the_chip(dnb, n, cin, cout, h, w):
+    """Wide tiles with fewer pixels than fill the CUs: a workgroup (128 channels, 64 or 96 outputs) has no more than 64 pixels
+    while there are fewer workgroups than CUs, so that no launch waits for a few long ones."""
+    lib = ctypes.CDLL(dnb.binding.LIB_PATH)
+    floats = lib._ZN3dnb30conv_wgrad_fast_partial_floatsEiiiiiibm  # (a C++ name: not a call of the C ABI)
+    floats.restype, floats.argtypes = ctypes.c_size_t, [ctypes.c_int] * 6 + [ctypes.c_bool, ctypes.c_size_t]
+    ranges = floats(n, cin, cout, h, w, 1, False, 2 ** 64 - 1) // (cin * cout)
+    columns = -(-cin // 128)
+    assert ranges * 64 >= n * h * w or (ranges + 1) * columns > 128, ranges
+
+
 def test_more_partials_cost_neither_memory_nor_pairs(dnb):
     """Wide tiles and more workgroups leave more partial sums of the 1x1 weight gradients: against plans with the fewest
     (golden file) no block or network takes more memory, and no block loses its pairs of layers."""
