@@ -1825,6 +1825,24 @@ size_t conv_stats_partial_floats(int n, int cout, int h, int w) {
 
 // Returns false (nothing launched) if the fast path does not cover this shape.
 // fold != null: BN+ReLU prologue.  spart != null: epilogue statistics, *sT = partials per channel.
+// k_conv3x3_ks for 49..128 input channels; v3_fits: k_conv3x3_v3 takes the shape too.
+// One M-tile of up to 96 channels: always (64 -> 16: 20 us instead of 29 at 1280 tiles of 64 pixels, 8 instead of 11.5 at 64).
+// Two: up to 128 tiles (96 -> 24: 10.4 us instead of 17.4); above, where its steps of four channels per wave, 8 per 32
+// channels, are not many more than k_conv3x3_v3's.  81..96 channels: 16.8 us instead of 17.6 at 256 tiles, 24.4 instead of
+// 27 at 512, 47 instead of 73 at 1280.  49..64: from 513 (22.7 instead of 25.2; at 512 17.7 instead of 17.0), 77..80 likewise
+// (31.4 instead of 38, 24.4 instead of 23.6), 73..76 from 1025 (46 instead of 52, 39 instead of 40.7), 65..72 from 1537 (68: 60.6
+// instead of 62.5 at 1540, 53.7 instead of 54.2 at 1536, 38.6 instead of 35 at 772, 24 instead of 18 at 260).
+// 97..128 channels only up to 128 tiles (128 -> 32: 14.5 us instead of 19 at 64; 24.4 instead of 20.5 at 256, 58 instead of 59
+// at 1024), not where k_conv3x3_v5 has eight waves for them (128 -> 12 at 16x16: 14.3 instead of 13.9 at 64).
+static bool conv3x3_in_eight_waves(int n, int cin, int mtiles, int h, int w, bool v3_fits) {
+  const int hw = h * w;
+  if (mtiles > 2 || cin <= 48 || cin > 128 || (w != 8 && w != 16 && w != 32) || hw % 64 != 0 || hw > 1 << 20) return false;
+  const int64_t tiles = (int64_t)(hw / 64) * n;
+  if (cin > 96) return tiles <= 128 && (v3_fits || mtiles == 2 || cin <= 112);
+  if (mtiles == 1 || tiles <= 128) return true;
+  return tiles > (cin > 80 ? 128 : cin > 76 || cin <= 64 ? 512 : cin > 72 ? 1024 : 1536);
+}
+
 bool launch_conv_fast(const float* in, int64_t in_stride, const float* packed, float* out,
                       int64_t out_stride, int n, int cin, int cout, int h, int w, int taps,
                       const float2* fold, float* spart, int* sT, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
@@ -1909,14 +1927,14 @@ bool launch_conv_fast(const float* in, int64_t in_stride, const float* packed, f
 #undef DNB_L4
     return true;
   }
-  // K split over eight waves with the weights in registers: 49..96 input channels, where a launch takes 40 us instead of
-  // 60 (96 -> 24 channels, 65536 pixels), 17.5 instead of 18 (16384), 11 instead of 17.5 (4096); 64 -> 16: 20 instead of 34
-  // (65536); with 97..128 channels only up to 128 tiles (128 -> 32: 4096 pixels 14.8 us instead of 19.3, but 16384 24.4
-  // instead of 20.5 and 65536 58 instead of 59).
-  if (mtiles <= 2 && cin > 48 && (cin <= 96 || (cin <= 128 && (int64_t)hw * n <= 128 * 64)) &&
-      (w == 8 || w == 16 || w == 32) && hw % 64 == 0 && hw <= 1 << 20) {
+  const int CS = pad4mod32(64 + 2 * w + 8);  // of k_conv3x3_v3
+  const size_t tile = (size_t)((cin + 3) & ~3) * CS * sizeof(float);
+  if (conv3x3_in_eight_waves(n, cin, mtiles, h, w, tile <= 64 * 1024)) {
     const int tpi = hw / 64, total_tiles = tpi * n, nk = (cin + 31) / 32;
     const int G = total_tiles < 256 ? (total_tiles + 7) / 8 * 8 : 256;
+    // two M-tiles, up to 128 tiles: a workgroup for each (96 -> 24 channels: 10.4 us, 17.0 with both in one); more tiles: both
+    // in one (136..256 tiles 16.5 us instead of 19.1, 264..384 24.2 instead of 23.7, 512 24.5 instead of 28.1, 1280 46.6
+    // instead of 53; 64 -> 24, 520 tiles 22.7 instead of 22.1, 2048 49.2 instead of 49.7)
     const int mt = mtiles == 2 && total_tiles > 128 ? 2 : 1;
     const dim3 grid((unsigned)G, (unsigned)(mtiles / mt));
     const size_t lds = ((size_t)nk * 32 * 144 + 4 + mt * 4 * 8 * 256) * sizeof(float);
@@ -1952,9 +1970,7 @@ bool launch_conv_fast(const float* in, int64_t in_stride, const float* packed, f
     mt = mtiles > 4 ? 2 : 1;
     gy = (mtiles + nw * mt - 1) / (nw * mt);
   }
-  const int CS = pad4mod32(64 + 2 * w + 8);
-  const size_t tile = (size_t)((cin + 3) & ~3) * CS, red = ksplit ? (size_t)(nw - 1) * mt * 4 * 256 : 0;
-  const size_t lds = (tile > red ? tile : red) * sizeof(float);
+  const size_t red = ksplit ? (size_t)(nw - 1) * mt * 4 * 256 * sizeof(float) : 0, lds = tile > red ? tile : red;
   if (lds > 64 * 1024) return false;
   dim3 grid((unsigned)((hw + 63) / 64), (unsigned)gy, (unsigned)n);
   const int T = (int)grid.x * n;

@@ -237,6 +237,34 @@ def test_3x3_with_its_channels_split_over_eight_waves(dnb, oracle, n, cin, cout,
     test_conv_forward_dgrad_wgrad(dnb, oracle, n, cin, cout, h, w, 3)
 
 
+@pytest.mark.parametrize("n,cin,cout,h,w,split", [(65, 64, 24, 16, 16, False), (129, 60, 17, 16, 16, True), (65, 68, 24, 16, 16, False),
+                                                  (385, 72, 32, 16, 16, True), (70, 80, 20, 16, 16, False), (129, 80, 20, 16, 16, True),
+                                                  (257, 76, 20, 16, 16, True), (260, 81, 24, 8, 8, True), (260, 64, 16, 8, 8, True)])
+def test_3x3_rule_between_four_and_eight_waves(dnb, oracle, n, cin, cout, h, w, split):
+    """Both sides of the rule that gives a forward 3x3 to the kernel of eight waves (which leaves a partial of the statistics
+    per workgroup, 256, where the other leaves one per 64 pixels): some images against the oracle, the statistics against
+    those of all outputs."""
+    r, hw = rng(24), h * w
+    x, wgt = f32(r.standard_normal((n, cin, h, w))), f32(r.standard_normal((cout, cin, 3, 3)) * np.sqrt(2.0 / (cin * 9)))
+    fold = f32(np.stack([1.0 + 0.3 * r.standard_normal(cin), 0.3 * r.standard_normal(cin)], axis=1))
+    out = torch.full((n, cout, h, w), float("nan"), device="cuda")
+    pk = torch.empty(dnb.dnb_op_conv_scratch_bytes(cin, cout, 3), dtype=torch.uint8, device="cuda")
+    stats = torch.full((dnb.dnb_op_conv_stats_bytes(n, cout, h, w) // 4,), float("nan"), device="cuda")
+    T = dnb.dnb_op_conv_bnrelu_forward(dev(x), cin * hw, dev(wgt), dev(fold), out, cout * hw, stats, n, cin, cout, h, w, 3, pk)
+    assert T == (256 if split else n * hw // 64)
+    few = [0, n // 2, n - 1]  # (images)
+    a = np.maximum(x[few].astype(np.float64) * fold[:, 0].astype(np.float64)[None, :, None, None]
+                   + fold[:, 1].astype(np.float64)[None, :, None, None], 0.0)
+    assert_close(out[few].cpu().numpy(), oracle.conv_forward(a, wgt), TOL, "fused conv")
+    st = stats[:cout * T * 3].view(cout, T, 3).double()
+    o = out.double().transpose(0, 1).reshape(cout, -1)
+    mean = (st[:, :, 0] * st[:, :, 1]).sum(1) / (n * hw)
+    m2 = (st[:, :, 2] + st[:, :, 0] * (st[:, :, 1] - mean[:, None]) ** 2).sum(1)
+    assert torch.equal(st[:, :, 0].sum(1), torch.full((cout,), float(n * hw), dtype=torch.float64, device="cuda"))
+    assert_close(m2.cpu().numpy() / (n * hw), o.var(1, unbiased=False).cpu().numpy(), TOL, "variance")
+    assert float((mean - o.mean(1)).abs().max()) <= 1e-5 * float(o.std())
+
+
 def fma32(a, b, c):
     """round(a*b + c) to fp32: the product of two fp32 values is exact in fp64, the sum in extended precision."""
     return (np.longdouble(a) * np.longdouble(b) + np.longdouble(c)).astype(np.float32)
