@@ -277,7 +277,7 @@ __global__ __launch_bounds__(256, 2) void k_dgrad1s(Dgrad1Args A) {
 // instead of 24.  Eight waves of 16 channels each; both layers' weights stay in registers, both tiles of db sit in
 // LDS, in two buffers: the next pixel tile is put down between the two layers' products, one barrier a tile.  65536
 // pixels, 1000 channels, 96 outputs: 232 us (283 with one buffer and operands read as they are needed) and 13 for the
-// slice between, against 2 x 240; 786 MB and 25.8 GFLOP, 74 % of the fp32 matrix rate.
+// slice between, against 2 x 240; 786 MB and 25.8 GFLOP, 111 TFLOP/s.
 template <int NCH, bool FIRST>
 __global__ __launch_bounds__(512) void k_dgrad1p(Dgrad1Args A, Dgrad1Lower B) {
   extern __shared__ __attribute__((aligned(16))) float tile_db[];  // two buffers of [2][NCH*16][64]

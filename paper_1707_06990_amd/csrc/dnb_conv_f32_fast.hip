@@ -1291,7 +1291,8 @@ __device__ __forceinline__ void wgrad1x1_body(const Wg1Args& A, int bx, int by, 
 // What bounds it is the matrix rate less the time between a step's two barriers, which two more workgroups on the CU
 // cover (two tiles and one barrier a step, two workgroups a CU: 34.0 against 33.7 ms a step of DenseNet-BC-250).
 constexpr size_t wide_lds_bytes(int wm) { return (size_t)(wm * 32 + 128) * 32 * sizeof(float); }
-// float offset of pixels 4c..4c+3 of a staged row: neither 16 rows of a column nor a row's 8 columns share a bank
+// float offset of pixels 4c..4c+3 of a staged row: a row's 8 columns lie in 8 groups of four banks, 8 consecutive rows of a
+// column too (rows 8 apart in the same one)
 __device__ __forceinline__ int wide_at(int row, int c) { return row * 32 + ((c ^ row) & 7) * 4; }
 
 template <int WM, bool PRO>

@@ -86,8 +86,8 @@ __device__ __forceinline__ void ksplit_reduce(f32x4 (&acc)[MT][NT], float* red, 
   }
 }
 
-// A pending sum of partials carried out by extra workgroups of a weight-gradient launch (the
-// workgroups with blockIdx.x >= gx_main): kind 1 is k_sum_partials' job, kind 2 k_sum_wgrad3x3's,
+// A pending sum of partials carried out by extra workgroups, of 256 threads, of a weight-gradient launch or, without a
+// bottleneck, of BN's reduction: kind 1 is k_sum_partials' job, kind 2 k_sum_wgrad3x3's,
 // with the same grouping and order of additions, so the sums have the same bits either way.
 struct SumRole {
   int kind, wgs;  // kind 0: none; wgs: workgroups the sum needs
@@ -99,7 +99,7 @@ struct SumRole {
 };
 
 __device__ __forceinline__ void sum_role(const SumRole& sr, int wg) {
-  extern __shared__ float sh[];  // the launch's dynamic LDS (every weight-gradient launch has >= 1 KB)
+  extern __shared__ float sh[];  // the launch's dynamic LDS: at least 1 KB in every launch that carries a sum
   const int epb = 256 / sr.G;
   const int le = threadIdx.x % epb, grp = threadIdx.x / epb;
   const long long f = (long long)wg * epb + le;
