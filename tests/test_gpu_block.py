@@ -315,6 +315,18 @@ def test_few_partials_of_the_1x1_weight_gradient_match_oracle(dnb, oracle, cfg, 
     compare_with_kernel_decisions(dnb, oracle, cfg, x0, lp, dy, schedule=schedule)
 
 
+# wide tiles on materialised activations (no BN+ReLU in the operand loads): 96, 64 and 52 outputs, a whole last column and one of a
+# few channels, and sums of more than 32 steps (the last)
+MATERIALISED = [(wl.BlockCfg(3, 300, 16, 16, 2, 24, 96), 0), (wl.BlockCfg(5, 368, 8, 16, 2, 16, 64), 0),
+                (wl.BlockCfg(3, 380, 12, 12, 2, 13, 52), 1), (wl.BlockCfg(33, 1008, 32, 32, 1, 24, 96), 0)]
+
+
+@pytest.mark.parametrize("cfg,schedule", MATERIALISED, ids=["n3c300k24", "n5c368k16", "n3c380k13-store-all", "n33c1008k24"])
+def test_wide_1x1_weight_gradients_of_materialised_activations_match_oracle(dnb, oracle, cfg, schedule):
+    x0, lp, dy = wl.make_block_inputs(cfg, affine="random")
+    compare_with_kernel_decisions(dnb, oracle, cfg, x0, lp, dy, schedule=schedule)
+
+
 @pytest.mark.parametrize("schedule", [0, 2])
 def test_more_layers_than_lanes(dnb, oracle, schedule):
     """70 layers: the packing kernels add up the sizes of the layers before their own with a lane for each, in turns of 64."""
