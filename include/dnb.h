@@ -356,8 +356,8 @@ size_t dnb_net_workspace_bytes(const dnb_net* net);  /* bytes the caller allocat
 size_t dnb_net_peak_bytes(const dnb_net* net);
 /* The i-th piece carved from the workspace (i = 0, 1, ... until DNB_E_RANGE): its name ("feat",
  * "y", "block_ws", "tz", "mean", "istd", "pack": one per block `index`; "tconv", "gy", "dtz",
- * "dconv", "dfeat", "block_scratch", "part", "pooled", "dpooled", "logits", "dlogits", "terms": shared by all
- * blocks), byte offset and size.  Host only; lets a caller or a test check the plan. */
+ * "dconv", "dfeat", "block_scratch" (empty where the blocks' scratch fits "dtz"), "part", "pooled", "dpooled",
+ * "logits", "dlogits", "terms": shared by all blocks), byte offset and size.  Host only; lets a caller or a test check the plan. */
 int dnb_net_workspace_piece(const dnb_net* net, int i, const char** name, int* index, size_t* offset, size_t* bytes);
 /* Every ReLU decision of the step as the kernels take it (see dnb_block_relu_decisions), one byte
  * each: for block b = 0, 1, 2 the block's d1, its d2, then the decisions of the BN+ReLU that
