@@ -1826,7 +1826,8 @@ size_t conv_stats_partial_floats(int n, int cout, int h, int w) {
 
 // Returns false (nothing launched) if the fast path does not cover this shape.
 // fold != null: BN+ReLU prologue.  spart != null: epilogue statistics, *sT = partials per channel.
-// k_conv3x3_ks for 49..128 input channels; v3_fits: k_conv3x3_v3 takes the shape too.
+// k_conv3x3_ks for 49..128 input channels; not_v5: the call is not one for k_conv3x3_v5 (it has BN+ReLU in its operand loads,
+// or k_conv3x3_v3 takes it).
 // One M-tile of up to 96 channels: always (64 -> 16: 20 us instead of 29 at 1280 tiles of 64 pixels, 8 instead of 11.5 at 64).
 // Two: up to 128 tiles (96 -> 24: 10.4 us instead of 17.4); above, where its steps of four channels per wave, 8 per 32
 // channels, are not many more than k_conv3x3_v3's.  81..96 channels: 16.8 us instead of 17.6 at 256 tiles, 24.4 instead of
@@ -1835,11 +1836,11 @@ size_t conv_stats_partial_floats(int n, int cout, int h, int w) {
 // instead of 62.5 at 1540, 53.7 instead of 54.2 at 1536, 38.6 instead of 35 at 772, 24 instead of 18 at 260).
 // 97..128 channels only up to 128 tiles (128 -> 32: 14.5 us instead of 19 at 64; 24.4 instead of 20.5 at 256, 58 instead of 59
 // at 1024), not where k_conv3x3_v5 has eight waves for them (128 -> 12 at 16x16: 14.3 instead of 13.9 at 64).
-static bool conv3x3_in_eight_waves(int n, int cin, int mtiles, int h, int w, bool v3_fits) {
+static bool conv3x3_in_eight_waves(int n, int cin, int mtiles, int h, int w, bool not_v5) {
   const int hw = h * w;
   if (mtiles > 2 || cin <= 48 || cin > 128 || (w != 8 && w != 16 && w != 32) || hw % 64 != 0 || hw > 1 << 20) return false;
   const int64_t tiles = (int64_t)(hw / 64) * n;
-  if (cin > 96) return tiles <= 128 && (v3_fits || mtiles == 2 || cin <= 112);
+  if (cin > 96) return tiles <= 128 && (not_v5 || mtiles == 2 || cin <= 112);
   if (mtiles == 1 || tiles <= 128) return true;
   return tiles > (cin > 80 ? 128 : cin > 76 || cin <= 64 ? 512 : cin > 72 ? 1024 : 1536);
 }
@@ -1930,7 +1931,7 @@ bool launch_conv_fast(const float* in, int64_t in_stride, const float* packed, f
   }
   const int CS = pad4mod32(64 + 2 * w + 8);  // of k_conv3x3_v3
   const size_t tile = (size_t)((cin + 3) & ~3) * CS * sizeof(float);
-  if (conv3x3_in_eight_waves(n, cin, mtiles, h, w, tile <= 64 * 1024)) {
+  if (conv3x3_in_eight_waves(n, cin, mtiles, h, w, fold || tile <= 64 * 1024)) {
     const int tpi = hw / 64, total_tiles = tpi * n, nk = (cin + 31) / 32;
     const int G = total_tiles < 256 ? (total_tiles + 7) / 8 * 8 : 256;
     // two M-tiles, up to 128 tiles: a workgroup for each (96 -> 24 channels: 10.4 us, 17.0 with both in one); more tiles: both

@@ -265,6 +265,14 @@ def test_3x3_rule_between_four_and_eight_waves(dnb, oracle, n, cin, cout, h, w, 
     assert float((mean - o.mean(1)).abs().max()) <= 1e-5 * float(o.std())
 
 
+@pytest.mark.parametrize("n,cin,cout,h,w", [(2, 128, 12, 16, 16), (3, 120, 16, 32, 32), (32, 113, 16, 16, 16), (2, 128, 16, 8, 8)])
+def test_3x3_of_113_to_128_channels_and_one_m_tile(dnb, oracle, n, cin, cout, h, w):
+    """Where the plain forward goes to the kernel of any depth, the one with BN+ReLU in its operand loads stays with the eight
+    waves that split the channels."""
+    test_fused_conv_bnrelu_forward_and_statistics(dnb, oracle, n, cin, cout, h, w, 3)
+    test_conv_forward_dgrad_wgrad(dnb, oracle, n, cin, cout, h, w, 3)
+
+
 def fma32(a, b, c):
     """round(a*b + c) to fp32: the product of two fp32 values is exact in fp64, the sum in extended precision."""
     return (np.longdouble(a) * np.longdouble(b) + np.longdouble(c)).astype(np.float32)
